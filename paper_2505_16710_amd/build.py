@@ -1,8 +1,8 @@
-"""Build the HIP library (libseco_hip.so) for gfx950, in-tree.
+"""Build the HIP library (libseco_hip.so) for gfx950 and the extension module of the binding, in-tree.
 
-`python -m paper_2505_16710_amd.build` or `build_library()`; also builds nothing else.
-Objects go to `_build/` next to the sources; the shared library lands in the package
-directory, where the ctypes binding looks for it.
+`python -m paper_2505_16710_amd.build`, or `build_library()` and `build_extension()`.
+Objects go to `_build/` next to the sources; the shared objects land in the package
+directory, where the binding looks for them.
 """
 from __future__ import annotations
 
@@ -74,6 +74,27 @@ def build_library(verbose=True, extra=(), out=None):
     return LIB
 
 
+def build_extension(verbose=True):
+    """_seco_ext: the native half of the Python binding (host code only, links against torch's libraries)."""
+    import sysconfig
+
+    import torch
+    troot = os.path.dirname(torch.__file__)
+    out = os.path.join(HERE, "_seco_ext" + sysconfig.get_config_var("EXT_SUFFIX"))
+    cmd = ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I", INCLUDE,
+           "-isystem", os.path.join(troot, "include"), "-isystem", os.path.join(troot, "include", "torch", "csrc", "api", "include"),
+           "-isystem", sysconfig.get_paths()["include"], "-isystem", os.path.join(os.path.dirname(os.path.dirname(HIPCC)), "include"),
+           os.path.join(CSRC, "binding_ext.cpp"), "-o", out, "-L", os.path.join(troot, "lib"),
+           "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip", "-ldl"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("building the extension failed:\n" + r.stderr[-4000:])
+    if verbose:
+        print(f"built {out}")
+    return out
+
+
 if __name__ == "__main__":
     # usage: python -m paper_2505_16710_amd.build [-o out.so] [extra hipcc flags, e.g. -DSECO_DKDV_RB=2]
     argv = sys.argv[1:]
@@ -81,3 +102,5 @@ if __name__ == "__main__":
     if argv[:1] == ["-o"]:
         out, argv = argv[1], argv[2:]
     build_library(extra=tuple(argv), out=out)
+    if out is None:
+        build_extension()

@@ -607,9 +607,8 @@ int launch_cfg(const AttnParams& p, const SegTable& seg, const RowRuns& rr, hipS
   }
   const int total = n_units * (n_ctiles - ts.n_tiles + ts.n_tiles * ts.hs);
   auto kern = dkdv_bf16_kernel<NCB, RB, ROWS>;
-  if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                          Cfg::kSmemBytes) != hipSuccess)
-    return SECO_ERR_LAUNCH;
+  static std::atomic<uint64_t> ready{0};
+  if (!allow_lds(ready, reinterpret_cast<const void*>(kern), Cfg::kSmemBytes)) return SECO_ERR_LAUNCH;
   {
     ProfScope prof(kKernelDkdv, s);   // the merge of the divided tiles counts as part of the dK/dV pass
     hipLaunchKernelGGL(kern, dim3(xcd_grid(total)), dim3(Cfg::kThreads), Cfg::kSmemBytes, s, p, seg, ts, rr, total);

@@ -293,9 +293,8 @@ template <int KH, bool SPLIT, bool SPARSE>
 int launch_kh(const AttnParams& p, const SegTable& seg, int n_mtiles, int total, hipStream_t s) {
   constexpr int smem = 4 * BNW * KH * kRowBytes;
   auto kern = dq_bf16_kernel<KH, SPLIT, SPARSE>;
-  if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, smem) !=
-      hipSuccess)
-    return SECO_ERR_LAUNCH;
+  static std::atomic<uint64_t> ready{0};
+  if (!allow_lds(ready, reinterpret_cast<const void*>(kern), smem)) return SECO_ERR_LAUNCH;
   {
     ProfScope prof(kKernelDq, s);
     hipLaunchKernelGGL(kern, dim3(xcd_grid(total)), dim3(256 * KH), smem, s, p, seg, n_mtiles, total);

@@ -326,9 +326,8 @@ template <bool SPLIT>
 int launch_fwd4(const AttnParams& p, int n_mtiles, int total, hipStream_t s) {
   constexpr int smem = 5 * BNW * kRowBytes;
   auto kern = fwd4_bf16_kernel<SPLIT>;
-  if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, smem) !=
-      hipSuccess)
-    return SECO_ERR_LAUNCH;
+  static std::atomic<uint64_t> ready{0};
+  if (!allow_lds(ready, reinterpret_cast<const void*>(kern), smem)) return SECO_ERR_LAUNCH;
   {
     ProfScope prof(kKernelFwd, s);
     hipLaunchKernelGGL(kern, dim3(xcd_grid(total)), dim3(256), smem, s, p, n_mtiles, total);

@@ -254,9 +254,8 @@ __global__ __launch_bounds__(512, 2) void fwd8_bf16_kernel(AttnParams p, int n_m
 
 int launch_fwd8(const AttnParams& p, int n_mtiles, int total, hipStream_t s) {
   constexpr int smem = 4 * BNW * 2 * kRowBytes;
-  if (hipFuncSetAttribute(reinterpret_cast<const void*>(fwd8_bf16_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                          smem) != hipSuccess)
-    return SECO_ERR_LAUNCH;
+  static std::atomic<uint64_t> ready{0};
+  if (!allow_lds(ready, reinterpret_cast<const void*>(fwd8_bf16_kernel), smem)) return SECO_ERR_LAUNCH;
   {
     ProfScope prof(kKernelFwd, s);
     hipLaunchKernelGGL(fwd8_bf16_kernel, dim3(xcd_grid(total)), dim3(512), smem, s, p, n_mtiles, total);

@@ -19,7 +19,21 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
+
 namespace seco {
+
+// Lets a kernel use more than the default 64 KiB of dynamic LDS.  The attribute belongs to the kernel on a device:
+// set by the first launch there (`ready`: one bit per device, one variable per kernel), not by every launch.
+inline bool allow_lds(std::atomic<uint64_t>& ready, const void* kernel, int bytes) {
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return false;
+  const uint64_t bit = (uint64_t)1 << (dev & 63);
+  if (dev < 64 && (ready.load(std::memory_order_acquire) & bit)) return true;
+  if (hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) != hipSuccess) return false;
+  ready.fetch_or(bit, std::memory_order_release);
+  return true;
+}
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
