@@ -113,11 +113,11 @@ inline TailPlan tail_plan(int n_units, int n_ctiles, int G, int C) {
   return tp;
 }
 
-// fp32 reference-grade kernels (any head_dim that is a multiple of 4, up to 256)
+// fp32 kernels (any head_dim that is a multiple of 4, up to 256)
 int launch_fwd_f32(const AttnParams& p, hipStream_t s);
 int launch_dq_f32(const AttnParams& p, const SegTable* dq_runs, hipStream_t s);   // dq_runs as in launch_dq_bf16
 int launch_dkdv_f32(const AttnParams& p, const SegTable& seg, hipStream_t s);
-constexpr int kColTileF32 = 4;     // columns per workgroup in launch_dkdv_f32
+constexpr int kColTileF32 = 16;    // columns per workgroup in launch_dkdv_f32
 
 // bf16 matrix-core kernels (head_dim 128)
 int launch_fwd_bf16(const AttnParams& p, hipStream_t s);

@@ -51,6 +51,20 @@ def test_fp32_shapes(B, Hq, Hkv, N, D, C):
     check(got, ref, "f32", f"f32 {B,Hq,Hkv,N,D,C}")
 
 
+@pytest.mark.parametrize("D", [4, 60, 68, 128, 132, 192, 196, 252])
+@pytest.mark.parametrize("N,C", [(17, 17), (49, 16), (95, 31), (290, 145)])
+def test_fp32_tile_edges(D, N, C):
+    """16-row tiles, head_dim in blocks of 64: chunk lengths and head dims on both sides of the edges, G = 3, with
+    unequal weights in the second run."""
+    x = small_layer(11, 1, 3, 1, N, D, "f32")
+    s = 1 / np.sqrt(D)
+    check(run_layer(x, C, s, "f32"), A.seco_layer(x["q"], x["k"], x["v"], x["do"], C, s), "f32", f"f32 {D,N,C}")
+    k = -(-N // C)
+    sel, lam = sorted({0, k - 1}, reverse=True), 1.5
+    check(run_layer(x, C, s, "f32", selected=sel, factor=lam),
+          A.spaco_layer(x["q"], x["k"], x["v"], x["do"], C, s, sel, lam), "f32", f"f32 spaco {D,N,C}")
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,N,C", [
     (1, 4, 1, 512, 256),     # aligned, G = 4
     (2, 4, 2, 640, 256),     # short last chunk (128 rows)
