@@ -101,18 +101,61 @@ __global__ __launch_bounds__(256) void delta_kernel(AttnParams p) {
   if (lane == 0) p.delta[row] = acc;
 }
 
-// Merge of the split forward: the 32 threads of a row (thread = 4 consecutive head_dim elements) combine the
-// n_splits (<= 64) partial rows in split order,
+// Merge of the partial rows of the split kernels (n_splits <= 64 of 128 fp32 each).  GP groups of 32 threads (a thread:
+// 4 consecutive head_dim elements) share a row, each taking the splits sp = group, group + GP, .., at most 8 of them, so
+// that all its loads are in flight at once; the groups' sums meet in LDS and are added in group order (fixed order:
+// reproducible).  What bounds it is the partials' traffic (33 MB for a 32-row chunk of 32 heads in 64 splits): with one
+// group per row and a loop over the splits every load waited for the one before, 23 us for that chunk; now 8.
+// Launchers choose GP = the power of two from which a group has at most 8 splits.
+template <int GP, typename Weight>
+__device__ __forceinline__ bool merge_partials(const float* part, int n_splits, int64_t R, int64_t rowid, int group, int d4,
+                                               Weight weight, float4& acc) {
+  __shared__ float4 sh[GP > 1 ? 256 : 1];
+  float4 x[8];
+#pragma unroll
+  for (int k = 0; k < 8; ++k)
+    if (group + k * GP < n_splits) x[k] = *reinterpret_cast<const float4*>(part + ((group + k * GP) * R + rowid) * 128 + 4 * d4);
+  acc = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    const float w = weight(k);                     // (a cross-lane read: every lane takes part)
+    if (group + k * GP < n_splits && w != 0.f) {   // weight 0: an empty partial, never written
+      acc.x += w * x[k].x;
+      acc.y += w * x[k].y;
+      acc.z += w * x[k].z;
+      acc.w += w * x[k].w;
+    }
+  }
+  if (GP == 1) return true;
+  sh[threadIdx.x] = acc;
+  __syncthreads();
+  if (group != 0) return false;
+#pragma unroll
+  for (int k = 1; k < GP; ++k) {
+    const float4 y = sh[threadIdx.x + 32 * k];     // the groups of a row are adjacent in the workgroup
+    acc.x += y.x;
+    acc.y += y.y;
+    acc.z += y.z;
+    acc.w += y.w;
+  }
+  return true;
+}
+// element offset of row `rowid` = (b * Hq + h) * C + row of a strided [B, Hq, C, 128] tensor
+__device__ __forceinline__ int64_t row_offset(const AttnParams& p, int64_t rowid, const int64_t s[3]) {
+  const int bh = (int)(rowid / p.C), row = (int)(rowid - (int64_t)bh * p.C), b = bh / p.Hq;
+  return b * s[0] + (bh - b * p.Hq) * s[1] + (int64_t)row * s[2];
+}
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+
 //   M = max m_s,  L = sum l_s 2^(m_s - M),  O = sum o_s 2^(m_s - M) / L,  LSE = (M + log2 L) ln 2.
-// Lane i of the row's group loads (m, l) of splits i and i + 32 once; max, sum and the per-split weights then
-// travel by cross-lane shuffles.  A partial with m_s = -inf is empty (nothing was written for its O): weight 0,
-// its O is not read.
+// Lane i of a group loads (m, l) of splits i and i + 32 once; max, sum and the per-split weights then travel by
+// cross-lane shuffles.
+template <int GP>
 __global__ __launch_bounds__(256) void fwd_merge_kernel(AttnParams p) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int64_t R = (int64_t)p.B * p.Hq * p.C;
-  const int64_t rowid = min(i >> 5, R - 1);      // surplus threads of the last block repeat the last row, no store
-  const bool live = (i >> 5) < R;
-  const int l32 = (int)(i & 31);
+  const int group = (threadIdx.x >> 5) % GP, l32 = threadIdx.x & 31;
+  const int64_t mine = (int64_t)blockIdx.x * (8 / GP) + (threadIdx.x >> 5) / GP;
+  const int64_t rowid = min(mine, R - 1);          // surplus threads of the last block repeat the last row, no store
   float m0 = -INFINITY, m1 = -INFINITY, s0 = 0.f, s1 = 0.f;
   if (l32 < p.n_splits) {
     m0 = p.part_ml[2 * (l32 * R + rowid)];
@@ -130,48 +173,30 @@ __global__ __launch_bounds__(256) void fwd_merge_kernel(AttnParams p) {
   float L = w0 * s0 + w1 * s1;
 #pragma unroll
   for (int sh = 16; sh > 0; sh >>= 1) L += __shfl_xor(L, sh, 32);
-  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int sp = 0; sp < p.n_splits; ++sp) {
-    const float w = __shfl(sp < 32 ? w0 : w1, sp & 31, 32);
-    if (w == 0.f) continue;
-    const float4 x = *reinterpret_cast<const float4*>(p.part + (sp * R + rowid) * 128 + 4 * l32);
-    acc.x += w * x.x;
-    acc.y += w * x.y;
-    acc.z += w * x.z;
-    acc.w += w * x.w;
-  }
-  if (!live) return;
+  float4 acc;
+  const bool store = merge_partials<GP>(p.part, p.n_splits, R, rowid, group, l32, [&](int k) {
+    const int sp = group + k * GP;
+    return __shfl(sp < 32 ? w0 : w1, sp & 31, 32);
+  }, acc);
+  if (!store || mine >= R) return;
   const float inv = 1.f / L;
-  const int row = (int)(rowid % p.C);
-  const int h = (int)((rowid / p.C) % p.Hq);
-  const int b = (int)(rowid / ((int64_t)p.C * p.Hq));
-  typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
   const bf16x4 v = {(__bf16)(acc.x * inv), (__bf16)(acc.y * inv), (__bf16)(acc.z * inv), (__bf16)(acc.w * inv)};
-  *reinterpret_cast<bf16x4*>(static_cast<__bf16*>(p.o_out) + b * p.os[0] + h * p.os[1] + (int64_t)row * p.os[2] + 4 * l32) = v;
+  *reinterpret_cast<bf16x4*>(static_cast<__bf16*>(p.o_out) + row_offset(p, rowid, p.os) + 4 * l32) = v;
   if (l32 == 0) p.lse[rowid] = (M + log2f(L)) * 0.6931471805599453f;
 }
 
-// Merge of the split dQ: dQ = scale * (sum of the partials in split order), rounded to bf16.
+// Merge of the split dQ: dQ = scale * (sum of the partials), rounded to bf16.
+template <int GP>
 __global__ __launch_bounds__(256) void dq_merge_kernel(AttnParams p) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int64_t R = (int64_t)p.B * p.Hq * p.C;
-  const int64_t rowid = i >> 5;
-  if (rowid >= R) return;
-  const int d4 = (int)(i & 31);
-  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int sp = 0; sp < p.n_splits; ++sp) {
-    const float4 x = *reinterpret_cast<const float4*>(p.part + (sp * R + rowid) * 128 + 4 * d4);
-    acc.x += x.x;
-    acc.y += x.y;
-    acc.z += x.z;
-    acc.w += x.w;
-  }
-  const int row = (int)(rowid % p.C);
-  const int h = (int)((rowid / p.C) % p.Hq);
-  const int b = (int)(rowid / ((int64_t)p.C * p.Hq));
-  typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+  const int group = (threadIdx.x >> 5) % GP, l32 = threadIdx.x & 31;
+  const int64_t mine = (int64_t)blockIdx.x * (8 / GP) + (threadIdx.x >> 5) / GP;
+  const int64_t rowid = min(mine, R - 1);
+  float4 acc;
+  const bool store = merge_partials<GP>(p.part, p.n_splits, R, rowid, group, l32, [](int) { return 1.f; }, acc);
+  if (!store || mine >= R) return;
   const bf16x4 v = {(__bf16)(acc.x * p.scale), (__bf16)(acc.y * p.scale), (__bf16)(acc.z * p.scale), (__bf16)(acc.w * p.scale)};
-  *reinterpret_cast<bf16x4*>(static_cast<__bf16*>(p.d_q) + b * p.qs[0] + h * p.qs[1] + (int64_t)row * p.qs[2] + 4 * d4) = v;
+  *reinterpret_cast<bf16x4*>(static_cast<__bf16*>(p.d_q) + row_offset(p, rowid, p.qs) + 4 * l32) = v;
 }
 
 // Row-range copy into the cache, 16 bytes per thread and row.  Strides arrive in units of 16 bytes.
@@ -453,23 +478,24 @@ int launch_rope_rows(void* out, const void* in, void* plain_out, const void* pla
   return launch_status();
 }
 
+#define SECO_MERGE_LAUNCH(kernel)                                                                             \
+  const int64_t R = (int64_t)p.B * p.Hq * p.C;                                                                \
+  ProfScope prof(kKernelMerge, s);                                                                            \
+  if (p.n_splits <= 8) hipLaunchKernelGGL(kernel<1>, dim3((unsigned)((R + 7) / 8)), dim3(256), 0, s, p);      \
+  else if (p.n_splits <= 16) hipLaunchKernelGGL(kernel<2>, dim3((unsigned)((R + 3) / 4)), dim3(256), 0, s, p); \
+  else if (p.n_splits <= 32) hipLaunchKernelGGL(kernel<4>, dim3((unsigned)((R + 1) / 2)), dim3(256), 0, s, p); \
+  else hipLaunchKernelGGL(kernel<8>, dim3((unsigned)R), dim3(256), 0, s, p);
+
 int launch_fwd_merge(const AttnParams& p, hipStream_t s) {
-  const int64_t threads = (int64_t)p.B * p.Hq * p.C * 32;
-  {
-    ProfScope prof(kKernelMerge, s);
-    hipLaunchKernelGGL(fwd_merge_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, p);
-  }
+  SECO_MERGE_LAUNCH(fwd_merge_kernel)
   return launch_status();
 }
 
 int launch_dq_merge(const AttnParams& p, hipStream_t s) {
-  const int64_t threads = (int64_t)p.B * p.Hq * p.C * 32;
-  {
-    ProfScope prof(kKernelMerge, s);
-    hipLaunchKernelGGL(dq_merge_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, p);
-  }
+  SECO_MERGE_LAUNCH(dq_merge_kernel)
   return launch_status();
 }
+#undef SECO_MERGE_LAUNCH
 
 int launch_delta(const AttnParams& p, int dtype, hipStream_t s) {
   const int64_t nrows = (int64_t)p.B * p.Hq * p.C;
