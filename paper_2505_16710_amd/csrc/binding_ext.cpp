@@ -16,6 +16,7 @@
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
+#include "decoder.h"
 #include "seco.h"
 
 namespace {
@@ -26,7 +27,8 @@ using at::Tensor;
   X(seco_chunk_attn_fwd) X(seco_chunk_attn_bwd) X(seco_chunk_attn_bwd_noalloc) X(spaco_chunk_attn_bwd)              \
   X(spaco_chunk_attn_bwd_sparse_dq) X(seco_chunk_attn_bwd_gather) X(spaco_chunk_attn_bwd_gather)                    \
   X(seco_workspace_bytes) X(kvgrad_zero) X(kvgrad_accumulate) X(kv_append) X(kvgrad_readout) X(kv_append_rope)      \
-  X(kvgrad_readout_rope) X(rope_rotate)
+  X(kvgrad_readout_rope) X(rope_rotate) X(dec_add_rmsnorm) X(dec_rmsnorm_bwd) X(dec_silu) X(dec_silu_bwd)             \
+  X(dec_cross_entropy) X(dec_embedding_bwd)
 struct Lib {
 #define X(name) decltype(&::name) name = nullptr;
   SECO_ENTRIES(X)
@@ -349,6 +351,89 @@ PyObject* rotate(PyObject* const* a) {
   return a[4] == Py_None ? THPVariable_Wrap(out) : (Py_INCREF(a[4]), a[4]);
 }
 
+// ---- row kernels of the decoder (decoder.h); tensors are contiguous [rows, d] ----
+const Tensor& rows2(PyObject* o) {
+  const Tensor& t = tensor(o);
+  if (t.dim() != 2 || !t.is_contiguous()) raise(PyExc_ValueError, "expected a contiguous [rows, d] tensor");
+  return t;
+}
+void same_as(const Tensor& t, const Tensor& x) {
+  if (t.sizes() != x.sizes() || t.scalar_type() != x.scalar_type() || !t.is_contiguous())
+    raise(PyExc_ValueError, "tensors must share shape and dtype and be contiguous");
+}
+void gain_of(const Tensor& g, const Tensor& x) {
+  if (g.dim() != 1 || g.size(0) != x.size(1) || g.scalar_type() != x.scalar_type() || !g.is_contiguous())
+    raise(PyExc_ValueError, "the gain must be a contiguous [d] tensor of the rows' dtype");
+}
+
+// (x, y or None, gain, x_out or None) -> (x_out, h, rstd): x_out = x + y, h = its RMSNorm; x_out is x when y is None
+PyObject* add_rmsnorm(PyObject* const* a) {
+  const Tensor& x = rows2(a[0]);
+  const Tensor *y = opt_tensor(a[1]), &g = tensor(a[2]);
+  if (y) same_as(*y, x);
+  gain_of(g, x);
+  const Tensor xo = !y ? x : a[3] == Py_None ? like(x) : tensor(a[3]);
+  if (y) same_as(xo, x);
+  const Tensor h = like(x), rstd = at::empty({x.size(0)}, x.options().dtype(at::kFloat).requires_grad(false));
+  check(lib.dec_add_rmsnorm(dtype_code(x), ptr(x), ptr(y), ptr(g), ptr(xo), ptr(h), fptr(rstd), x.size(0), x.size(1),
+                            stream(Py_None)), "dec_add_rmsnorm");
+  return Py_BuildValue("NNN", THPVariable_Wrap(xo), THPVariable_Wrap(h), THPVariable_Wrap(rstd));
+}
+
+// (x, gain, rstd, d_h, d_in or None, gain_part): d_in += gradient at x (or d_h <- it, without d_in); returns that tensor
+PyObject* rmsnorm_bwd(PyObject* const* a) {
+  const Tensor &x = rows2(a[0]), &g = tensor(a[1]), &rstd = tensor(a[2]), &dh = tensor(a[3]), &part = tensor(a[5]);
+  const Tensor* din = opt_tensor(a[4]);
+  same_as(dh, x);
+  if (din) same_as(*din, x);
+  gain_of(g, x);
+  if (rstd.scalar_type() != at::kFloat || rstd.numel() != x.size(0) || part.scalar_type() != at::kFloat ||
+      part.dim() != 2 || part.size(0) != DEC_GAIN_BLOCKS || part.size(1) != x.size(1) || !part.is_contiguous())
+    raise(PyExc_ValueError, "rstd: fp32 [rows]; gain_part: contiguous fp32 [256, d]");
+  PyObject* out = din ? a[4] : a[3];
+  check(lib.dec_rmsnorm_bwd(dtype_code(x), ptr(x), ptr(g), fptr(rstd), ptr(dh), ptr(din), ptr(tensor(out)), fptr(part),
+                            x.size(0), x.size(1), stream(Py_None)), "dec_rmsnorm_bwd");
+  return Py_INCREF(out), out;
+}
+
+// (u) -> silu(u)
+PyObject* silu(PyObject* const* a) {
+  const Tensor& u = rows2(a[0]);
+  const Tensor out = like(u);
+  check(lib.dec_silu(dtype_code(u), ptr(u), ptr(out), u.numel(), stream(Py_None)), "dec_silu");
+  return THPVariable_Wrap(out);
+}
+// (u, d_a): d_a <- d_a * silu'(u)
+PyObject* silu_bwd(PyObject* const* a) {
+  const Tensor &u = rows2(a[0]), &da = tensor(a[1]);
+  same_as(da, u);
+  check(lib.dec_silu_bwd(dtype_code(u), ptr(u), ptr(da), u.numel(), stream(Py_None)), "dec_silu_bwd");
+  return Py_INCREF(a[1]), a[1];
+}
+
+// (logits, target int64 [rows], loss fp32 [rows] or None): with loss the rows' losses, without it logits <- gradient
+PyObject* cross_entropy(PyObject* const* a) {
+  const Tensor &l = rows2(a[0]), &t = tensor(a[1]);
+  const Tensor* loss = opt_tensor(a[2]);
+  if (t.scalar_type() != at::kLong || t.numel() != l.size(0) || !t.is_contiguous() ||
+      (loss && (loss->scalar_type() != at::kFloat || loss->numel() != l.size(0) || !loss->is_contiguous())))
+    raise(PyExc_ValueError, "targets: contiguous int64 [rows]; loss: contiguous float32 [rows]");
+  check(lib.dec_cross_entropy(dtype_code(l), ptr(l), static_cast<const int64_t*>(ptr(t)), fptr(loss), l.size(0), l.size(1),
+                              stream(Py_None)), "dec_cross_entropy");
+  Py_RETURN_NONE;
+}
+
+// (d_x, token int64 [rows], grad [v, d]): grad[token[r]] += d_x[r]
+PyObject* embedding_bwd(PyObject* const* a) {
+  const Tensor &dx = rows2(a[0]), &t = tensor(a[1]), &g = rows2(a[2]);
+  if (t.scalar_type() != at::kLong || t.numel() != dx.size(0) || !t.is_contiguous() || g.size(1) != dx.size(1) ||
+      g.scalar_type() != dx.scalar_type())
+    raise(PyExc_ValueError, "tokens: contiguous int64 [rows]; grad: [v, d] of the rows' dtype");
+  check(lib.dec_embedding_bwd(dtype_code(dx), ptr(dx), static_cast<const int64_t*>(ptr(t)), ptr(g), dx.size(0), dx.size(1),
+                              g.size(0), stream(Py_None)), "dec_embedding_bwd");
+  Py_RETURN_NONE;
+}
+
 // (library path, SecoError)
 PyObject* init(PyObject* const* a) {
   const char* path = PyUnicode_AsUTF8(a[0]);
@@ -384,6 +469,8 @@ PyMethodDef methods[] = {
     METHOD("init", init, 2), METHOD("fwd", fwd, 9), METHOD("bwd", bwd, 16), METHOD("bwd_noalloc", bwd_noalloc, 12),
     METHOD("bwd_gather", bwd_gather, 17), METHOD("zero", zero, 5), METHOD("accumulate", accumulate, 8),
     METHOD("append", append, 7), METHOD("readout", readout, 10), METHOD("rotate", rotate, 6),
+    METHOD("add_rmsnorm", add_rmsnorm, 4), METHOD("rmsnorm_bwd", rmsnorm_bwd, 6), METHOD("silu", silu, 1),
+    METHOD("silu_bwd", silu_bwd, 2), METHOD("cross_entropy", cross_entropy, 3), METHOD("embedding_bwd", embedding_bwd, 3),
     {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_seco_ext", "native half of the binding", -1, methods, nullptr, nullptr, nullptr, nullptr};
 

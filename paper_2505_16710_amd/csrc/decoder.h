@@ -1,0 +1,27 @@
+// Row kernels of the decoder around the attention (chunk_loop.py): launched through these C functions by the extension
+// module of the binding.  All tensors are contiguous; dtype is a seco_dtype; the functions return a seco_status.
+#pragma once
+#include <stdint.h>
+
+#ifdef __cplusplus
+extern "C" {
+#endif
+// x_out = x + y (y NULL: x_out is not written), h = round(x_out * rstd) * gain, rstd = 1 / sqrt(mean(x_out^2) + 1e-6)
+int dec_add_rmsnorm(int dtype, const void* x, const void* y, const void* gain, void* x_out, void* h, float* rstd,
+                    int64_t rows, int64_t d, void* stream);
+// d_x = d_in + gradient of the norm at x (d_in NULL: the gradient alone; d_x may be d_in or d_h);
+// gain_part[blocks, d] fp32 += per-workgroup sums of the gain's gradient, blocks = DEC_GAIN_BLOCKS
+#define DEC_GAIN_BLOCKS 256
+int dec_rmsnorm_bwd(int dtype, const void* x, const void* gain, const float* rstd, const void* d_h, const void* d_in,
+                    void* d_x, float* gain_part, int64_t rows, int64_t d, void* stream);
+int dec_silu(int dtype, const void* u, void* a, int64_t n, void* stream);
+int dec_silu_bwd(int dtype, const void* u, void* d_a, int64_t n, void* stream);   // d_a <- d_a * silu'(u)
+// loss[r] = logsumexp(logits[r]) - logits[r][target[r]] (loss non-NULL), or logits <- softmax - onehot (loss NULL);
+// a target of -100 gives loss 0 and gradient 0, any other target outside [0, v) NaN
+int dec_cross_entropy(int dtype, void* logits, const int64_t* target, float* loss, int64_t rows, int64_t v, void* stream);
+// grad[token[r]] += d_x[r] for every row r; the rows of one token are added in ascending order by one workgroup
+int dec_embedding_bwd(int dtype, const void* d_x, const int64_t* token, void* grad, int64_t rows, int64_t d, int64_t v,
+                      void* stream);
+#ifdef __cplusplus
+}
+#endif

@@ -1,0 +1,350 @@
+// Row kernels of the decoder around the attention: residual add + RMSNorm, its backward, SiLU, cross-entropy and the
+// embedding gradient.  All are bound by memory at large sizes and by the number of launches at the sizes of a chunk:
+// written as separate framework operators a norm was six launches forward and about twelve backward (convert, square,
+// mean, rsqrt, two products ...), and a two-layer training step spent 9 of its 14 ms of GPU time and nearly all of its
+// 27 ms of host time on them.  Here each is one launch: a workgroup per row, 16-byte accesses where the row
+// length allows, the row kept in registers between the two passes up to kKeep * 256 * V elements.  Sums are fp32 in a
+// fixed order (reproducible); rounding follows the operators' (the normalised row is rounded before the gain).
+#include "decoder.h"
+
+#include <hip/hip_runtime.h>
+
+#include "seco.h"
+
+namespace {
+
+constexpr int kThreads = 256, kKeep = 4;
+
+template <typename T, int V> struct alignas(sizeof(T) * V) Vec {
+  T v[V];
+  __device__ void get(float* f) const {
+#pragma unroll
+    for (int j = 0; j < V; ++j) f[j] = (float)v[j];
+  }
+  __device__ void set(const float* f) {
+#pragma unroll
+    for (int j = 0; j < V; ++j) v[j] = (T)f[j];
+  }
+};
+template <typename T, int V> __device__ __forceinline__ void load(const T* p, float* f) {
+  reinterpret_cast<const Vec<T, V>*>(p)->get(f);
+}
+template <typename T, int V> __device__ __forceinline__ void store(T* p, const float* f) {
+  Vec<T, V> x;
+  x.set(f);
+  *reinterpret_cast<Vec<T, V>*>(p) = x;
+}
+
+struct Sum {
+  __device__ static float of(float a, float b) { return a + b; }
+};
+struct Max {
+  __device__ static float of(float a, float b) { return fmaxf(a, b); }
+};
+// over the workgroup; every thread gets the result.  The barrier at the end frees the scratch for the next call.
+template <typename Op> __device__ __forceinline__ float block_reduce(float x) {
+  __shared__ float sh[kThreads / 64];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) x = Op::of(x, __shfl_xor(x, o));
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = x;
+  __syncthreads();
+  x = sh[0];
+#pragma unroll
+  for (int i = 1; i < kThreads / 64; ++i) x = Op::of(x, sh[i]);
+  __syncthreads();
+  return x;
+}
+
+template <typename T, int V>
+__global__ __launch_bounds__(kThreads) void add_rmsnorm_kernel(const T* x, const T* y, const T* gain, T* x_out, T* h,
+                                                               float* rstd, int64_t d) {   // (x_out may be x)
+  const int64_t row = (int64_t)blockIdx.x * d;
+  float kept[kKeep][V], sum = 0.f;
+  auto value = [&](int64_t c, float* f) {                 // first pass: the row, with y added (and rounded) to it
+    load<T, V>(x + row + c, f);
+    if (y) {
+      float g[V];
+      load<T, V>(y + row + c, g);
+#pragma unroll
+      for (int j = 0; j < V; ++j) f[j] = (float)(T)(f[j] + g[j]);
+      store<T, V>(x_out + row + c, f);
+    }
+#pragma unroll
+    for (int j = 0; j < V; ++j) sum += f[j] * f[j];
+  };
+#pragma unroll
+  for (int k = 0; k < kKeep; ++k) {
+    const int64_t c = ((int64_t)k * kThreads + threadIdx.x) * V;
+    if (c < d) value(c, kept[k]);
+  }
+  for (int64_t c = ((int64_t)kKeep * kThreads + threadIdx.x) * V; c < d; c += kThreads * V) {
+    float f[V];
+    value(c, f);
+  }
+  const float r = rsqrtf(block_reduce<Sum>(sum) / (float)d + 1e-6f);
+  if (threadIdx.x == 0) rstd[blockIdx.x] = r;
+  auto scale = [&](int64_t c, float* f) {
+    float g[V];
+    load<T, V>(gain + c, g);
+#pragma unroll
+    for (int j = 0; j < V; ++j) f[j] = (float)(T)(f[j] * r) * g[j];
+    store<T, V>(h + row + c, f);
+  };
+#pragma unroll
+  for (int k = 0; k < kKeep; ++k) {
+    const int64_t c = ((int64_t)k * kThreads + threadIdx.x) * V;
+    if (c < d) scale(c, kept[k]);
+  }
+  for (int64_t c = ((int64_t)kKeep * kThreads + threadIdx.x) * V; c < d; c += kThreads * V) {
+    float f[V];
+    load<T, V>((y ? x_out : x) + row + c, f);             // this thread's own words
+    scale(c, f);
+  }
+}
+
+// With n = x rstd and e = d_h gain:  d_x = d_in + rstd (e - n mean(e n)),  d_gain = sum over rows of d_h round(n).
+// A workgroup takes every DEC_GAIN_BLOCKS-th row and adds its share of d_gain to its own row of gain_part.
+template <typename T, int V>
+__global__ __launch_bounds__(kThreads) void rmsnorm_bwd_kernel(const T* x, const T* gain, const float* rstd, const T* d_h,
+                                                               const T* d_in, T* d_x, float* gain_part, int64_t rows,
+                                                               int64_t d) {
+  float dg[kKeep][V];
+#pragma unroll
+  for (int k = 0; k < kKeep; ++k)
+#pragma unroll
+    for (int j = 0; j < V; ++j) dg[k][j] = 0.f;
+  float* part = gain_part + (int64_t)blockIdx.x * d;
+  for (int64_t rr = blockIdx.x; rr < rows; rr += DEC_GAIN_BLOCKS) {
+    const int64_t row = rr * d;
+    const float r = rstd[rr];
+    float n[kKeep][V], e[kKeep][V], sum = 0.f;
+    auto first = [&](int64_t c, float* nn, float* ee, float* gg) {
+      float g[V];
+      load<T, V>(x + row + c, nn);
+      load<T, V>(d_h + row + c, ee);
+      load<T, V>(gain + c, g);
+#pragma unroll
+      for (int j = 0; j < V; ++j) {
+        nn[j] *= r;
+        if (gg) gg[j] += ee[j] * (float)(T)nn[j];
+        ee[j] *= g[j];
+        sum += ee[j] * nn[j];
+      }
+    };
+#pragma unroll
+    for (int k = 0; k < kKeep; ++k) {
+      const int64_t c = ((int64_t)k * kThreads + threadIdx.x) * V;
+      if (c < d) first(c, n[k], e[k], dg[k]);
+    }
+    for (int64_t c = ((int64_t)kKeep * kThreads + threadIdx.x) * V; c < d; c += kThreads * V) {
+      float nn[V], ee[V], gg[V];
+      load<float, V>(part + c, gg);
+      first(c, nn, ee, gg);
+      store<float, V>(part + c, gg);
+    }
+    const float mean = block_reduce<Sum>(sum) / (float)d;
+    auto second = [&](int64_t c, const float* nn, const float* ee) {
+      float f[V];
+#pragma unroll
+      for (int j = 0; j < V; ++j) f[j] = 0.f;
+      if (d_in) load<T, V>(d_in + row + c, f);
+#pragma unroll
+      for (int j = 0; j < V; ++j) f[j] += r * (ee[j] - nn[j] * mean);
+      store<T, V>(d_x + row + c, f);
+    };
+#pragma unroll
+    for (int k = 0; k < kKeep; ++k) {
+      const int64_t c = ((int64_t)k * kThreads + threadIdx.x) * V;
+      if (c < d) second(c, n[k], e[k]);
+    }
+    for (int64_t c = ((int64_t)kKeep * kThreads + threadIdx.x) * V; c < d; c += kThreads * V) {
+      float nn[V], ee[V];
+      first(c, nn, ee, nullptr);
+      second(c, nn, ee);
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < kKeep; ++k) {
+    const int64_t c = ((int64_t)k * kThreads + threadIdx.x) * V;
+    if (c < d) {
+      float f[V];
+      load<float, V>(part + c, f);
+#pragma unroll
+      for (int j = 0; j < V; ++j) f[j] += dg[k][j];
+      store<float, V>(part + c, f);
+    }
+  }
+}
+
+template <typename T, int V, bool BWD>
+__global__ __launch_bounds__(kThreads) void silu_kernel(const T* u, T* a, int64_t n) {   // BWD: a is d_a, in and out
+  for (int64_t i = ((int64_t)blockIdx.x * kThreads + threadIdx.x) * V; i < n; i += (int64_t)gridDim.x * kThreads * V) {
+    float f[V], g[V];
+    load<T, V>(u + i, f);
+    if (BWD) load<T, V>(a + i, g);
+#pragma unroll
+    for (int j = 0; j < V; ++j) {
+      const float s = 1.f / (1.f + __expf(-f[j]));
+      f[j] = BWD ? g[j] * (s * (1.f + f[j] * (1.f - s))) : f[j] * s;
+    }
+    store<T, V>(a + i, f);
+  }
+}
+
+template <typename T, int V>
+__global__ __launch_bounds__(kThreads) void cross_entropy_kernel(T* logits, const int64_t* target, float* loss, int64_t v) {
+  const int64_t row = (int64_t)blockIdx.x * v, t = target[blockIdx.x];
+  T* l = logits + row;
+  float m = -INFINITY;
+  for (int64_t c = threadIdx.x * V; c < v; c += kThreads * V) {
+    float f[V];
+    load<T, V>(l + c, f);
+#pragma unroll
+    for (int j = 0; j < V; ++j) m = fmaxf(m, f[j]);
+  }
+  m = block_reduce<Max>(m);
+  float sum = 0.f;
+  for (int64_t c = threadIdx.x * V; c < v; c += kThreads * V) {
+    float f[V];
+    load<T, V>(l + c, f);
+#pragma unroll
+    for (int j = 0; j < V; ++j) sum += __expf(f[j] - m);
+  }
+  sum = block_reduce<Sum>(sum);
+  const bool bad = t != -100 && (t < 0 || t >= v);
+  if (loss) {
+    if (threadIdx.x == 0) loss[blockIdx.x] = t == -100 ? 0.f : bad ? NAN : m + __logf(sum) - (float)l[t];
+    return;
+  }
+  const float inv = t == -100 ? 0.f : bad ? NAN : 1.f / sum;
+  for (int64_t c = threadIdx.x * V; c < v; c += kThreads * V) {
+    float f[V];
+    load<T, V>(l + c, f);
+#pragma unroll
+    for (int j = 0; j < V; ++j) f[j] = __expf(f[j] - m) * inv - (c + j == t ? 1.f : 0.f);
+    store<T, V>(l + c, f);
+  }
+}
+
+// One workgroup per row r; the one of a token's first row adds up all of the token's rows, in order, the others leave.
+// A wavefront compares 64 tokens at a time and walks the matches by the bits of the result.
+template <typename T, int V>
+__global__ __launch_bounds__(kThreads) void embedding_bwd_kernel(const T* d_x, const int64_t* token, T* grad, int64_t rows,
+                                                                 int64_t d, int64_t v) {
+  auto index = [&](int64_t i) { return token[i] < 0 ? token[i] + v : token[i]; };   // negative: counted from the end
+  const int64_t r = blockIdx.x, t = index(r);
+  if (t < 0 || t >= v) return;
+  float earlier = 0.f;
+  for (int64_t i = threadIdx.x; i < r; i += kThreads)
+    if (index(i) == t) earlier = 1.f;
+  if (block_reduce<Sum>(earlier) != 0.f) return;
+  const int lane = threadIdx.x & 63;
+  T* out = grad + t * d;
+  for (int64_t c0 = 0; c0 < d; c0 += kThreads * V) {      // (every lane takes part in the comparisons)
+    const int64_t c = c0 + threadIdx.x * V;
+    float f[V], x[V];
+#pragma unroll
+    for (int j = 0; j < V; ++j) f[j] = 0.f;
+    for (int64_t i0 = r; i0 < rows; i0 += 64) {
+      uint64_t hit = __builtin_amdgcn_ballot_w64(i0 + lane < rows && index(i0 + lane < rows ? i0 + lane : r) == t);
+      for (; hit; hit &= hit - 1) {
+        if (c < d) {
+          load<T, V>(d_x + (i0 + __builtin_ctzll(hit)) * d + c, x);
+#pragma unroll
+          for (int j = 0; j < V; ++j) f[j] += x[j];
+        }
+      }
+    }
+    if (c < d) {
+      load<T, V>(out + c, x);
+#pragma unroll
+      for (int j = 0; j < V; ++j) f[j] += x[j];
+      store<T, V>(out + c, f);
+    }
+  }
+}
+
+int status() { return hipGetLastError() == hipSuccess ? SECO_OK : SECO_ERR_LAUNCH; }
+bool sizes_ok(int dtype, int64_t rows, int64_t d) {
+  return (dtype == SECO_BF16 || dtype == SECO_F32) && rows >= 0 && rows < ((int64_t)1 << 31) && d >= 1;
+}
+template <typename... P> bool words(P... p) { return (((reinterpret_cast<uintptr_t>(p) & 15u) == 0) && ...); }
+
+}  // namespace
+
+// 16-byte accesses when every row starts on a 16-byte boundary, else element by element
+#define DEC_DISPATCH(d, aligned, LAUNCH)                                        \
+  if (dtype == SECO_BF16) {                                                     \
+    if ((d) % 8 == 0 && (aligned)) { LAUNCH(__bf16, 8); }                       \
+    else { LAUNCH(__bf16, 1); }                                                 \
+  } else {                                                                      \
+    if ((d) % 4 == 0 && (aligned)) { LAUNCH(float, 4); }                        \
+    else { LAUNCH(float, 1); }                                                  \
+  }
+
+extern "C" int dec_add_rmsnorm(int dtype, const void* x, const void* y, const void* gain, void* x_out, void* h, float* rstd,
+                               int64_t rows, int64_t d, void* stream) {
+  if (!sizes_ok(dtype, rows, d)) return SECO_ERR_SHAPE;
+  if (rows == 0) return SECO_OK;
+#define L(T, V)                                                                                                      \
+  hipLaunchKernelGGL((add_rmsnorm_kernel<T, V>), dim3((unsigned)rows), dim3(kThreads), 0, (hipStream_t)stream, (const T*)x, \
+                     (const T*)y, (const T*)gain, (T*)x_out, (T*)h, rstd, d)
+  DEC_DISPATCH(d, words(x, y, gain, x_out, h), L)
+#undef L
+  return status();
+}
+
+extern "C" int dec_rmsnorm_bwd(int dtype, const void* x, const void* gain, const float* rstd, const void* d_h,
+                               const void* d_in, void* d_x, float* gain_part, int64_t rows, int64_t d, void* stream) {
+  if (!sizes_ok(dtype, rows, d)) return SECO_ERR_SHAPE;
+  if (rows == 0) return SECO_OK;
+  const unsigned blocks = rows < DEC_GAIN_BLOCKS ? (unsigned)rows : DEC_GAIN_BLOCKS;
+#define L(T, V)                                                                                                        \
+  hipLaunchKernelGGL((rmsnorm_bwd_kernel<T, V>), dim3(blocks), dim3(kThreads), 0, (hipStream_t)stream, (const T*)x,     \
+                     (const T*)gain, rstd, (const T*)d_h, (const T*)d_in, (T*)d_x, gain_part, rows, d)
+  DEC_DISPATCH(d, words(x, gain, d_h, d_in, d_x, gain_part), L)
+#undef L
+  return status();
+}
+
+template <bool BWD> static int silu(int dtype, const void* u, void* a, int64_t n, void* stream) {
+  if ((dtype != SECO_BF16 && dtype != SECO_F32) || n < 0) return SECO_ERR_SHAPE;
+  if (n == 0) return SECO_OK;
+#define L(T, V)                                                                                                        \
+  {                                                                                                                    \
+    const int64_t blocks = (n + kThreads * V - 1) / (kThreads * V);                                                    \
+    hipLaunchKernelGGL((silu_kernel<T, V, BWD>), dim3((unsigned)(blocks < 65536 ? blocks : 65536)), dim3(kThreads), 0,  \
+                       (hipStream_t)stream, (const T*)u, (T*)a, n);                                                    \
+  }
+  DEC_DISPATCH(n, words(u, a), L)
+#undef L
+  return status();
+}
+extern "C" int dec_silu(int dtype, const void* u, void* a, int64_t n, void* stream) { return silu<false>(dtype, u, a, n, stream); }
+extern "C" int dec_silu_bwd(int dtype, const void* u, void* d_a, int64_t n, void* stream) {
+  return silu<true>(dtype, u, d_a, n, stream);
+}
+
+extern "C" int dec_cross_entropy(int dtype, void* logits, const int64_t* target, float* loss, int64_t rows, int64_t v,
+                                 void* stream) {
+  if (!sizes_ok(dtype, rows, v)) return SECO_ERR_SHAPE;
+  if (rows == 0) return SECO_OK;
+#define L(T, V)                                                                                                     \
+  hipLaunchKernelGGL((cross_entropy_kernel<T, V>), dim3((unsigned)rows), dim3(kThreads), 0, (hipStream_t)stream,    \
+                     (T*)logits, target, loss, v)
+  DEC_DISPATCH(v, words(logits), L)
+#undef L
+  return status();
+}
+
+extern "C" int dec_embedding_bwd(int dtype, const void* d_x, const int64_t* token, void* grad, int64_t rows, int64_t d,
+                                 int64_t v, void* stream) {
+  if (!sizes_ok(dtype, rows, d)) return SECO_ERR_SHAPE;
+  if (rows == 0) return SECO_OK;
+#define L(T, V)                                                                                                     \
+  hipLaunchKernelGGL((embedding_bwd_kernel<T, V>), dim3((unsigned)rows), dim3(kThreads), 0, (hipStream_t)stream,    \
+                     (const T*)d_x, token, (T*)grad, rows, d, v)
+  DEC_DISPATCH(d, words(d_x, grad), L)
+#undef L
+  return status();
+}
