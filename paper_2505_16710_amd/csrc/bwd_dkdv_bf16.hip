@@ -130,11 +130,8 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
   const int n0 = c0 + cb * 32;     // first cache row of this wavefront
   const int col = n0 + l32;        // this lane's cache row in the score tile
   // role A holds K^T fragments, role B holds V^T fragments
-  const __bf16* fptr = static_cast<const __bf16*>(role == 0 ? p.k : p.v) + b * p.kvs[0] + kvh * p.kvs[1] +
-                       (int64_t)min(col, kv_len - 1) * p.kvs[2];
-  bf16x8 frag[8];
-#pragma unroll
-  for (int t = 0; t < 8; ++t) frag[t] = *reinterpret_cast<const bf16x8*>(fptr + 16 * t + 8 * g);
+  bf16x8 frag[8], fr[8];
+  load_rows32(fr, static_cast<const __bf16*>(role == 0 ? p.k : p.v) + b * p.kvs[0] + kvh * p.kvs[1], p.kvs[2], n0, kv_len - 1, lane);
   // Role A starts its MFMA chains from -LSE / s instead of zero, so that a chain delivers q.k - LSE / s and
   // P = exp2(c * that) with c = s * log2(e): one multiply per score, in fp32.  (Folding c into the K^T fragments
   // would save that multiply but round K a second time, to bf16: with scores far from zero, as with the outlier
@@ -318,8 +315,10 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
       copy_stat(nxt, 1, s1);
     }
   }
-#pragma unroll
-  for (int t = 0; t < 8; ++t) settle(frag[t]);
+  // (through the third slot's Q and dO tiles and the P buffers, which are empty until the barriers below)
+  rows32_to_frags(frag, fr, wave < 4 ? smem + (wave < 2 ? 0 : kDoRegion) + 2 * kTileBytes + (wave & 1) * 8192
+                                     : pbuf + (wave - 4) * 8192, lane);
+  settle8(frag);
   dma_wait_all();
   __syncthreads();
   if constexpr (role == 0) {
@@ -502,44 +501,57 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
     slot = slot1;
   }
 
-  // The lane-dependent indices of the epilogue are derived again from the thread index (through an empty asm, so
-  // that the compiler does not keep the ones computed before the loop alive across it: the loop uses every register).
+  // The sums leave through LDS (each wavefront turns its 32 x 128 tile in 16.5 KiB of its own), so that gK/gV and the
+  // partial sums are accessed in whole 512-byte rows, 1 KiB per instruction: in the accumulators' layout an
+  // instruction covers 128 bytes of two rows, and a workgroup's 1024 such accesses keep the address unit busy for
+  // longer than the data takes.
+  // (The lane-dependent indices are derived again from the thread index, through an empty asm, so that the compiler
+  // does not keep the ones computed before the loop alive across it: the loop uses every register.)
   int tid_e = threadIdx.x;
   asm volatile("" : "+v"(tid_e));
-  const int l32_e = tid_e & 31, g_e = (tid_e >> 5) & 1, n0_e = c0 + ((tid_e >> 6) % NCB) * 32;
+  typedef float f32x4 __attribute__((ext_vector_type(4)));
+  const int lane_e = tid_e & 63, l32_e = tid_e & 31, g_e = (tid_e >> 5) & 1, wave_e = tid_e >> 6;
+  const int n0_e = c0 + (wave_e % NCB) * 32;
+  constexpr int kTurnRow = 528;                                          // bytes; 16 of padding
+  static_assert(2 * NCB * 32 * kTurnRow <= Cfg::kSmemBytes, "the turned tiles fit the ring's LDS");
+  lds_char* own = smem + wave_e * (32 * kTurnRow);
+  auto turn_in = [&]() {
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+#pragma unroll
+      for (int db = 0; db < 4; ++db)
+        *reinterpret_cast<SECO_LDS float*>(own + (8 * (r >> 2) + 4 * g_e + (r & 3)) * kTurnRow + (32 * db + l32_e) * 4) = acc[db][r];
+  };
+  auto turned = [&](int j) {                                             // row 2 j + lane / 32, columns 4 (lane % 32) ..
+    return *reinterpret_cast<SECO_LDS f32x4*>(own + (2 * j + (lane_e >> 5)) * kTurnRow + l32_e * 16);
+  };
   if (divided) {
-    // a share of the heads: plain stores of the unweighted sums, all 32 rows (the merge drops rows past the tile's end)
+    // a share of the tile: plain stores of the unweighted sums, all 32 rows (the merge drops rows past the tile's end)
     float* pb = ts.part + ((((int64_t)unit * ts.n_tiles + (tile - n_whole)) * ts.hs + share) * 2 + role) *
-                              (int64_t)(Cfg::kCols * 128) + (cb * 32) * 128 + l32_e;
+                              (int64_t)(Cfg::kCols * 128) + (wave_e % NCB) * 32 * 128 + lane_e * 4;
+    turn_in();
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      float* pr = pb + (8 * (r >> 2) + 4 * g_e + (r & 3)) * 128;
-#pragma unroll
-      for (int db = 0; db < 4; ++db) pr[32 * db] = acc[db][r];
-    }
+    for (int j = 0; j < 16; ++j) *reinterpret_cast<f32x4*>(pb + j * 256) = turned(j);
     return;
   }
-  // exclusive read-modify-write of this workgroup's gK/gV rows: role A adds dV, role B adds s * dK
-  float* gbase = (role == 0 ? p.gv : p.gk) + b * p.gs[0] + kvh * p.gs[1];
+  // exclusive read-modify-write of this workgroup's gK/gV rows: role A adds dV, role B adds s * dK.  All old values
+  // are requested before the tile is turned (rows past the tile's end read a clamped address and are not written
+  // back): one memory round trip, under the LDS work.
+  float* gbase = (role == 0 ? p.gv : p.gk) + b * p.gs[0] + kvh * p.gs[1] + l32_e * 4;
   const float wf = role == 0 ? weight : weight * p.scale;
-  // All 64 old values are requested before the first one is used (rows past the tile's end read a clamped
-  // address and are not written back): one memory round trip instead of one per group of rows.
-  float old[16][4];
+  f32x4 old[16];
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int kvrow = min(n0_e + 8 * (r >> 2) + 4 * g_e + (r & 3), c_end - 1);
-    const float* gr = gbase + (int64_t)kvrow * p.gs[2] + l32_e;
+  for (int j = 0; j < 16; ++j)
+    old[j] = *reinterpret_cast<const f32x4*>(gbase + (int64_t)min(n0_e + 2 * j + (lane_e >> 5), c_end - 1) * p.gs[2]);
+  turn_in();
 #pragma unroll
-    for (int db = 0; db < 4; ++db) old[r][db] = gr[32 * db];
-  }
+  for (int j = 0; j < 16; ++j) {
+    const int row = n0_e + 2 * j + (lane_e >> 5);
+    const f32x4 x = turned(j);
+    f32x4 v;
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int kvrow = n0_e + 8 * (r >> 2) + 4 * g_e + (r & 3);
-    if (kvrow < c_end) {
-      float* gr = gbase + (int64_t)kvrow * p.gs[2] + l32_e;
-#pragma unroll
-      for (int db = 0; db < 4; ++db) gr[32 * db] = old[r][db] + wf * acc[db][r];
-    }
+    for (int i = 0; i < 4; ++i) v[i] = old[j][i] + wf * x[i];
+    if (row < c_end) *reinterpret_cast<f32x4*>(gbase + (int64_t)row * p.gs[2]) = v;
   }
 }
 

@@ -77,36 +77,17 @@ __global__ __launch_bounds__(256 * KH, 2) void dq_bf16_kernel(AttnParams p, SegT
   const int row = m0 + l32;
   const int crow = min(row, p.C - 1);
   const int qpos = p.q_start + row;
-  const __bf16* qptr = static_cast<const __bf16*>(p.q) + b * p.qs[0] + h * p.qs[1] + (int64_t)crow * p.qs[2];
-  const __bf16* doptr = static_cast<const __bf16*>(p.d_o) + b * p.os[0] + h * p.os[1] + (int64_t)crow * p.os[2];
-  bf16x8 qf[8], dof[8];
-#pragma unroll
-  for (int t = 0; t < 8; ++t) {
-    qf[t] = *reinterpret_cast<const bf16x8*>(qptr + 16 * t + 8 * g);
-    dof[t] = *reinterpret_cast<const bf16x8*>(doptr + 16 * t + 8 * g);
+  // Q, dO, O, the row's LSE and (below) the first K/V tile are all requested before the first of them is waited for:
+  // a workgroup starts with one memory round trip
+  bf16x8 qr[8], dor[8], orow[8];
+  {
+    const int64_t ob = b * p.os[0] + h * p.os[1];
+    load_rows32(qr, static_cast<const __bf16*>(p.q) + b * p.qs[0] + h * p.qs[1], p.qs[2], m0, p.C - 1, lane);
+    load_rows32(dor, static_cast<const __bf16*>(p.d_o) + ob, p.os[2], m0, p.C - 1, lane);
+    load_rows32(orow, static_cast<const __bf16*>(p.o) + ob, p.os[2], m0, p.C - 1, lane);
   }
   const int64_t stat = ((int64_t)b * p.Hq + h) * p.C + crow;
-  const float lse_c = p.lse[stat] * kLog2e;
-  // delta = rowsum(dO * O) is computed here, from the dO fragments already in registers and the matching O
-  // fragments: a lane holds half of its row's head_dim (the other half is in lane ^ 32).  It is also written to
-  // the workspace for the dK/dV kernel that follows on the same stream, negated, together with -LSE / s (the
-  // log-sum-exp in units of the unscaled dot product): the two values that kernel starts its MFMA chains from.
-  float delta = 0.f;
-  {
-    const __bf16* optr = static_cast<const __bf16*>(p.o) + b * p.os[0] + h * p.os[1] + (int64_t)crow * p.os[2];
-#pragma unroll
-    for (int t = 0; t < 8; ++t) {
-      const bf16x8 of = *reinterpret_cast<const bf16x8*>(optr + 16 * t + 8 * g);
-#pragma unroll
-      for (int i = 0; i < 8; ++i) delta = __builtin_fmaf((float)of[i], (float)dof[t][i], delta);
-    }
-    delta += __shfl_xor(delta, 32);
-    if (kh == 0 && sp == 0 && g == 0 && row < p.C) {
-      const int64_t kept = ((int64_t)b * p.Hq + h) * p.stat_stride + p.stat_off + crow;
-      p.delta[kept] = -delta;
-      p.nlse2[kept] = -p.lse[stat] / p.scale;
-    }
-  }
+  const float lse = p.lse[stat];
   const float c = p.scale * kLog2e;
 
   const __bf16* kbase = static_cast<const __bf16*>(p.k) + b * p.kvs[0] + kvh * p.kvs[1];
@@ -206,10 +187,30 @@ __global__ __launch_bounds__(256 * KH, 2) void dq_bf16_kernel(AttnParams p, SegT
   }
   Cur nxt = cur;
   if (n_begin < n_end) copy_tile(cur.col, 0);
+  bf16x8 qf[8], dof[8], of[8];
+  lds_char* own = smem + 2 * kTileBytes + wave * 8192;      // of the second tile buffer, which is empty until the loop
+  rows32_to_frags(qf, qr, own, lane);
+  rows32_to_frags(dof, dor, own, lane);
+  rows32_to_frags(of, orow, own, lane);
+  const float lse_c = lse * kLog2e;
+  // delta = rowsum(dO * O), from the dO fragments and the matching O fragments: a lane holds half of its row's
+  // head_dim (the other half is in lane ^ 32).  It is also written to the workspace for the dK/dV kernel that follows
+  // on the same stream, negated, together with -LSE / s (the log-sum-exp in units of the unscaled dot product): the
+  // two values that kernel starts its MFMA chains from.
+  float delta;
+  {
+    float part[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int t = 0; t < 8; ++t) {
-    settle(qf[t]);
-    settle(dof[t]);
+    for (int t = 0; t < 8; ++t)
+#pragma unroll
+      for (int i = 0; i < 8; ++i) part[i & 3] = __builtin_fmaf((float)of[t][i], (float)dof[t][i], part[i & 3]);
+    delta = (part[0] + part[1]) + (part[2] + part[3]);
+    delta += __shfl_xor(delta, 32);
+    if (kh == 0 && sp == 0 && g == 0 && row < p.C) {
+      const int64_t kept = ((int64_t)b * p.Hq + h) * p.stat_stride + p.stat_off + crow;
+      p.delta[kept] = -delta;
+      p.nlse2[kept] = -lse / p.scale;
+    }
   }
   dma_wait_all();
   __syncthreads();
@@ -249,7 +250,7 @@ __global__ __launch_bounds__(256 * KH, 2) void dq_bf16_kernel(AttnParams p, SegT
         }
     }
     __syncthreads();
-    if (kh == 1) return;
+    if (kh == 1 || m0 >= p.C) return;
 #pragma unroll
     for (int db = 0; db < 4; ++db)
 #pragma unroll
@@ -275,18 +276,9 @@ __global__ __launch_bounds__(256 * KH, 2) void dq_bf16_kernel(AttnParams p, SegT
     return;
   }
 
-  if (row < p.C) {
-    __bf16* out = static_cast<__bf16*>(p.d_q) + b * p.qs[0] + h * p.qs[1] + (int64_t)row * p.qs[2];
-#pragma unroll
-    for (int db = 0; db < 4; ++db)
-#pragma unroll
-      for (int r4 = 0; r4 < 4; ++r4) {
-        bf16x4 v;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = (__bf16)(dq[db][4 * r4 + i] * p.scale);
-        *reinterpret_cast<bf16x4*>(out + 32 * db + 8 * r4 + 4 * g) = v;
-      }
-  }
+  store_rows32([&](int db, int r) { return dq[db][r] * p.scale; },
+               static_cast<__bf16*>(p.d_q) + b * p.qs[0] + h * p.qs[1], p.qs[2], m0, p.C,
+               KH == 2 ? smem + rb * (16 * 1024) : smem + wave * 8192);
 }
 
 template <int KH, bool SPLIT, bool SPARSE>

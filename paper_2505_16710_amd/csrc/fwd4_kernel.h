@@ -73,10 +73,8 @@ __global__ __launch_bounds__(256, 2) void fwd4_bf16_kernel(AttnParams p, int n_m
   const int kv_len = p.q_start + p.C;
   const int row = m0 + l32;                    // this lane's row
   const int qpos = p.q_start + row;            // its global position
-  const __bf16* qptr = static_cast<const __bf16*>(p.q) + b * p.qs[0] + h * p.qs[1] + (int64_t)min(row, p.C - 1) * p.qs[2];
-  bf16x8 qf[8];
-#pragma unroll
-  for (int t = 0; t < 8; ++t) qf[t] = *reinterpret_cast<const bf16x8*>(qptr + 16 * t + 8 * g);
+  bf16x8 qr[8];
+  load_rows32(qr, static_cast<const __bf16*>(p.q) + b * p.qs[0] + h * p.qs[1], p.qs[2], m0, p.C - 1, lane);
 
   const __bf16* kbase = static_cast<const __bf16*>(p.k) + b * p.kvs[0] + kvh * p.kvs[1];
   const __bf16* vbase = static_cast<const __bf16*>(p.v) + b * p.kvs[0] + kvh * p.kvs[1];
@@ -141,6 +139,7 @@ __global__ __launch_bounds__(256, 2) void fwd4_bf16_kernel(AttnParams p, int n_m
     }
   };
 
+  bf16x8 qf[8];                                // (filled below, while the first tiles are on their way)
   f32x16 o[4];
 #pragma unroll
   for (int db = 0; db < 4; ++db)
@@ -266,8 +265,9 @@ __global__ __launch_bounds__(256, 2) void fwd4_bf16_kernel(AttnParams p, int n_m
   copy_ring(kbase, n_begin, 0);
   copy_ring(vbase, n_begin, kKSlots);
   if (n_begin + 1 < n_end) copy_ring(kbase, n_begin + 1, 1);
-#pragma unroll
-  for (int t = 0; t < 8; ++t) settle(qf[t]);
+  // (through the third K slot and the second V slot, which are empty until the loop)
+  rows32_to_frags(qf, qr, smem + (wave < 2 ? 2 : 4) * kTileBytes + (wave & 1) * 8192, lane);
+  settle8(qf);
   dma_wait_all();
   __syncthreads();
 
@@ -305,22 +305,11 @@ __global__ __launch_bounds__(256, 2) void fwd4_bf16_kernel(AttnParams p, int n_m
     return;
   }
 
-  if (row < p.C) {
-    const float inv = 1.f / l_tot;
-    __bf16* optr = static_cast<__bf16*>(p.o_out) + b * p.os[0] + h * p.os[1] + (int64_t)row * p.os[2];
-#pragma unroll
-    for (int db = 0; db < 4; ++db)
-#pragma unroll
-      for (int r4 = 0; r4 < 4; ++r4) {
-        bf16x4 v;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = (__bf16)(o[db][4 * r4 + i] * inv);
-        *reinterpret_cast<bf16x4*>(optr + 32 * db + 8 * r4 + 4 * g) = v;
-      }
-    if (g == 0) p.lse[((int64_t)b * p.Hq + h) * p.C + row] = (m_run + __log2f(l_tot)) * kLn2;
-  }
+  const float inv = 1.f / l_tot;
+  store_rows32([&](int db, int r) { return o[db][r] * inv; },
+               static_cast<__bf16*>(p.o_out) + b * p.os[0] + h * p.os[1], p.os[2], m0, p.C, smem + wave * 8192);
+  if (row < p.C && g == 0) p.lse[((int64_t)b * p.Hq + h) * p.C + row] = (m_run + __log2f(l_tot)) * kLn2;
 }
-
 
 template <bool SPLIT>
 int launch_fwd4(const AttnParams& p, int n_mtiles, int total, hipStream_t s) {

@@ -54,10 +54,8 @@ __global__ __launch_bounds__(512, 2) void fwd8_bf16_kernel(AttnParams p, int n_m
   const int kv_len = p.q_start + p.C;
   const int row = m0 + l32;                    // this lane's row
   const int qpos = p.q_start + row;            // its global position
-  const __bf16* qptr = static_cast<const __bf16*>(p.q) + b * p.qs[0] + h * p.qs[1] + (int64_t)min(row, p.C - 1) * p.qs[2];
-  bf16x8 qf[8];
-#pragma unroll
-  for (int t = 0; t < 8; ++t) qf[t] = *reinterpret_cast<const bf16x8*>(qptr + 16 * t + 8 * g);
+  bf16x8 qr[8];
+  load_rows32(qr, static_cast<const __bf16*>(p.q) + b * p.qs[0] + h * p.qs[1], p.qs[2], m0, p.C - 1, lane);
 
   const __bf16* kbase = static_cast<const __bf16*>(p.k) + b * p.kvs[0] + kvh * p.kvs[1];
   const __bf16* vbase = static_cast<const __bf16*>(p.v) + b * p.kvs[0] + kvh * p.kvs[1];
@@ -105,9 +103,22 @@ __global__ __launch_bounds__(512, 2) void fwd8_bf16_kernel(AttnParams p, int n_m
   float m_run = -INFINITY, l_run = 0.f;
   const float c = p.scale * kLog2e;
 
-  copy_tile(n_begin, 0);
+  // lane-dependent parts of the LDS operand addresses (constant for the whole kernel)
+  int r_off[8];
+  TrOff t_off[4];
 #pragma unroll
-  for (int t = 0; t < 8; ++t) settle(qf[t]);
+  for (int t = 0; t < 8; ++t) r_off[t] = row8_lane_off(l32, 2 * t + g) + kh * BNW * kRowBytes;
+#pragma unroll
+  for (int db = 0; db < 4; ++db) {
+    t_off[db] = tr8_lane_off(db, lane);
+    t_off[db].lo += kh * BNW * kRowBytes + kTileBytes;
+    t_off[db].hi += kh * BNW * kRowBytes + kTileBytes;
+  }
+
+  copy_tile(n_begin, 0);
+  bf16x8 qf[8];
+  rows32_to_frags(qf, qr, smem + 2 * kTileBytes + wave * 8192, lane);   // (the second tile buffer is empty until the loop)
+  settle8(qf);
   dma_wait_all();
   __syncthreads();
 
@@ -116,15 +127,14 @@ __global__ __launch_bounds__(512, 2) void fwd8_bf16_kernel(AttnParams p, int n_m
     if (n + 1 < n_end) copy_tile(n + 1, buf ^ 1);
     const int col0 = n * BN + kh * BNW;        // first cache row of this wavefront's part of the tile
     if (col0 < wave_kv_end) {
-      lds_char* kt = smem + buf * 2 * kTileBytes + kh * BNW * kRowBytes;
-      lds_char* vt = kt + kTileBytes;
+      lds_char* kt = smem + buf * 2 * kTileBytes;
       f32x16 s[2];
 #pragma unroll
       for (int kvb = 0; kvb < 2; ++kvb) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) s[kvb][r] = 0.f;
 #pragma unroll
-        for (int t = 0; t < 8; ++t) s[kvb] = mfma(lds_row8(kt, kvb * 32 + l32, 2 * t + g), qf[t], s[kvb]);
+        for (int t = 0; t < 8; ++t) s[kvb] = mfma(lds_row8_at(kt + r_off[t], kvb * 32), qf[t], s[kvb]);
       }
       if (col0 + BNW - 1 > p.q_start + m0) {  // reaches past this wavefront's first row: causal mask
 #pragma unroll
@@ -195,7 +205,7 @@ __global__ __launch_bounds__(512, 2) void fwd8_bf16_kernel(AttnParams p, int n_m
         for (int t = 0; t < 2; ++t) {
           const bf16x8 pb = pack8(s[kvb], t);
 #pragma unroll
-          for (int db = 0; db < 4; ++db) o[db] = mfma(lds_tr8(vt, kvb * 32 + 16 * t, db, lane), pb, o[db]);
+          for (int db = 0; db < 4; ++db) o[db] = mfma(lds_tr8_at(kt, t_off[db], kvb * 32 + 16 * t), pb, o[db]);
         }
     }
     dma_wait_all();
@@ -219,13 +229,16 @@ __global__ __launch_bounds__(512, 2) void fwd8_bf16_kernel(AttnParams p, int n_m
       *reinterpret_cast<SECO_LDS float*>(slot + 16384 + 256 + lane * 4) = l_tot;
     }
     __syncthreads();
-    if (kh == 1) return;
+    if (kh == 1 || m0 >= p.C) return;
     const float m1 = *reinterpret_cast<SECO_LDS float*>(slot + 16384 + lane * 4);
     const float l1 = *reinterpret_cast<SECO_LDS float*>(slot + 16384 + 256 + lane * 4);
     const float m = fmaxf(m_run, m1);               // finite: half 0 always sees column 0
-    const float a0 = fast_exp2(m_run - m), a1 = fast_exp2(m1 - m);
+    float a0 = fast_exp2(m_run - m), a1 = fast_exp2(m1 - m);
     l_tot = l_tot * a0 + l1 * a1;
     m_run = m;
+    const float inv = 1.f / l_tot;
+    a0 *= inv;
+    a1 *= inv;
 #pragma unroll
     for (int db = 0; db < 4; ++db)
 #pragma unroll
@@ -236,20 +249,9 @@ __global__ __launch_bounds__(512, 2) void fwd8_bf16_kernel(AttnParams p, int n_m
       }
   }
 
-  if (row < p.C) {
-    const float inv = 1.f / l_tot;
-    __bf16* optr = static_cast<__bf16*>(p.o_out) + b * p.os[0] + h * p.os[1] + (int64_t)row * p.os[2];
-#pragma unroll
-    for (int db = 0; db < 4; ++db)
-#pragma unroll
-      for (int r4 = 0; r4 < 4; ++r4) {
-        bf16x4 v;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = (__bf16)(o[db][4 * r4 + i] * inv);
-        *reinterpret_cast<bf16x4*>(optr + 32 * db + 8 * r4 + 4 * g) = v;
-      }
-    if (g == 0) p.lse[((int64_t)b * p.Hq + h) * p.C + row] = (m_run + __log2f(l_tot)) * kLn2;
-  }
+  store_rows32([&](int db, int r) { return o[db][r]; },
+               static_cast<__bf16*>(p.o_out) + b * p.os[0] + h * p.os[1], p.os[2], m0, p.C, smem + rb * (17 * 1024));
+  if (row < p.C && g == 0) p.lse[((int64_t)b * p.Hq + h) * p.C + row] = (m_run + __log2f(l_tot)) * kLn2;
 }
 
 int launch_fwd8(const AttnParams& p, int n_mtiles, int total, hipStream_t s) {

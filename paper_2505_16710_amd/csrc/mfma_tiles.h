@@ -152,6 +152,49 @@ __device__ __forceinline__ void dma_wait_all() { asm volatile("s_waitcnt vmcnt(0
 // loaded once before a loop: otherwise the first use inside the loop carries a conservative vmcnt wait
 // on every iteration, which would also wait for the asynchronous tile copies issued in the loop.
 __device__ __forceinline__ void settle(const bf16x8& v) { asm volatile("" : : "v"(v)); }
+// ... for eight of them at once: all eight loads are in flight before the first one is waited for
+__device__ __forceinline__ void settle8(const bf16x8 (&v)[8]) {
+  asm volatile("" : : "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "v"(v[4]), "v"(v[5]), "v"(v[6]), "v"(v[7]));
+}
+
+// Fragments of 32 rows (lane: row l % 32, chunks 2 t + l / 32), taken from memory with whole 256-byte rows per 16 lanes
+// and turned through 8 KiB of LDS that belong to the wavefront (no barrier: a wavefront's LDS accesses are in order).
+// Loaded straight into their layout the fragments are 32 bytes of each of 32 rows per instruction, which the address
+// unit takes one cache line at a time: about 57 cycles per instruction and CU, 11e3 cycles before a dQ workgroup of
+// 8 wavefronts could start; whole rows take 16.
+__device__ __forceinline__ void load_rows32(bf16x8 (&x)[8], const __bf16* base, int64_t stride, int row0, int last_row, int lane) {
+#pragma unroll
+  for (int j = 0; j < 8; ++j)
+    x[j] = *reinterpret_cast<const bf16x8*>(base + (int64_t)min(row0 + 4 * j + (lane >> 4), last_row) * stride + (lane & 15) * 8);
+}
+__device__ __forceinline__ void rows32_to_frags(bf16x8 (&f)[8], const bf16x8 (&x)[8], lds_char* own8k, int lane) {
+#pragma unroll
+  for (int j = 0; j < 8; ++j) lds_store16(own8k, 4 * j + (lane >> 4), lane & 15, x[j]);
+#pragma unroll
+  for (int t = 0; t < 8; ++t) f[t] = lds_row8(own8k, lane & 31, 2 * t + (lane >> 5));
+}
+// The way back: a 128 x 32 accumulator whose lanes own rows (lane: row l % 32, register 4 r4 + i of block db: column
+// 32 db + 8 r4 + 4 (l / 32) + i) as bf16 to rows of memory, whole rows at a time.
+template <typename F>
+__device__ __forceinline__ void store_rows32(const F& value, __bf16* base, int64_t stride, int row0, int n_rows,
+                                             lds_char* own8k) {   // value(db, register): the element
+  int lane = threadIdx.x & 63;
+  asm volatile("" : "+v"(lane));        // (derived again here, so that no address is kept in registers across the main loop)
+#pragma unroll
+  for (int db = 0; db < 4; ++db)
+#pragma unroll
+    for (int r4 = 0; r4 < 4; ++r4) {
+      bf16x4 v;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i] = (__bf16)value(db, 4 * r4 + i);
+      *reinterpret_cast<SECO_LDS bf16x4*>(own8k + tile_off(lane & 31, 4 * db + r4) + 8 * (lane >> 5)) = v;
+    }
+  const int r0 = row0 + (lane >> 4);
+  __bf16* dst = base + (int64_t)r0 * stride + (lane & 15) * 8;
+#pragma unroll
+  for (int j = 0; j < 8; ++j, dst += 4 * stride)
+    if (r0 + 4 * j < n_rows) *reinterpret_cast<bf16x8*>(dst) = lds_row8(own8k, 4 * j + (lane >> 4), lane & 15);
+}
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
