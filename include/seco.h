@@ -367,6 +367,10 @@ int seco_profile_read(double* total_ms_host, int64_t* launches_host);
  * and with it this size, counts workgroups against the number of compute units of the device that is current when
  * the library is first used (256, an MI355X's, when no device can be asked): ask on the device the call will run on. */
 size_t seco_workspace_bytes(const seco_desc* desc, int op);
+/* Workspace bytes with which the entry point runs fastest (at least seco_workspace_bytes): without grouped query heads
+ * the bf16 backward can do without room for partial sums, but then leaves compute units idle when a call has few
+ * cache tiles. */
+size_t seco_workspace_bytes_preferred(const seco_desc* desc, int op);
 
 /*
  * How the bf16 kernels would be launched for this desc (host arithmetic only, nothing is launched; for tests and
@@ -376,6 +380,7 @@ size_t seco_workspace_bytes(const seco_desc* desc, int op);
  *   [1] row tiles of the forward / dQ pass (work items before that division)
  *   [2] cache tiles per (batch, KV head), counted from the last, that the dK/dV pass shares out by query head
  *   [3] workgroups per such tile (1: none); [2] * [3] * batch * n_kv_heads never exceeds the device's compute units
+ * A call whose tiles still leave compute units idle shares them out further, by query rows.
  * Returns SECO_OK, or the status of an invalid desc; SECO_ERR_DTYPE for fp32 (its kernels have one shape).
  */
 int seco_launch_plan(const seco_desc* desc, int32_t n_col_tiles, int32_t* plan_host);

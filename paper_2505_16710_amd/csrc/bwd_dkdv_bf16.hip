@@ -78,12 +78,11 @@ struct DkdvCfg {
   static constexpr int kCols = NCB * 32;                                // cache rows per workgroup
 };
 
-// The last n_tiles column tiles of every (batch, KV head) are each divided among hs workgroups by query head;
-// their sums go to part[split tile][head share][dV, dK][cache row of the tile][128] instead of gK/gV.
+// The column tiles at the end of every (batch, KV head) that are shared out among several workgroups (share_plan): a
+// share's sums go to part[unit][workgroup of the list][dV, dK][cache row of the tile][128] instead of gK/gV.
 struct TailSplit {
-  int n_tiles;
-  int hs;
   float* part;
+  SharePlan plan;
 };
 
 // (RB is fixed to 2 by the hand-pipelined main loop.)
@@ -109,16 +108,19 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
   const int l32 = lane & 31, g = lane >> 5;
   constexpr int role = ROLE;
   const int cb = wave % NCB;
-  // item -> (batch, kv head, column tile, share of the query heads); the divided tiles come last in a unit
+  // item -> (batch, kv head, column tile, share of the tile's iterations); the listed tiles come last in a unit
   const int n_ctiles = seg.tile_begin[seg.n];
-  const int n_whole = n_ctiles - ts.n_tiles;
-  const int per_unit = n_whole + ts.n_tiles * ts.hs;
+  const int n_whole = n_ctiles - ts.plan.n_tiles;
+  const int per_unit = n_whole + ts.plan.n_entries;
   const int unit = item / per_unit, in_unit = item % per_unit;
-  const bool divided = in_unit >= n_whole;
-  const int tile = divided ? n_whole + (in_unit - n_whole) / ts.hs : in_unit;
-  const int share = divided ? (in_unit - n_whole) % ts.hs : 0;
-  const int n_heads = divided ? p.G / ts.hs : p.G;   // query heads of the group handled here, from head0 on
-  const int head0 = share * n_heads;
+  int tile = in_unit, share = 0, n_shares = 1;
+  if (in_unit >= n_whole) {
+    const int entry = in_unit - n_whole, pos = ts.plan.tile_of[entry];
+    tile = n_whole + pos;
+    share = entry - ts.plan.first[pos];
+    n_shares = ts.plan.first[pos + 1] - ts.plan.first[pos];
+  }
+  const bool divided = n_shares > 1;
   const int kvh = unit % p.Hkv, b = unit / p.Hkv;
   int si = 0;
   while (si + 1 < seg.n && tile >= seg.tile_begin[si + 1]) ++si;
@@ -153,7 +155,10 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
   } else {
     n_rt = (p.C + BQ - 1) / BQ - rt0;
   }
-  const int n_iter = n_rt * n_heads;
+  // this workgroup's share of the tile's iterations: [it0, it0 + n_iter)
+  const int n_all = n_rt * p.G;
+  const int it0 = divided ? (int)((int64_t)share * n_all / n_shares) : 0;
+  const int n_iter = (divided ? (int)((int64_t)(share + 1) * n_all / n_shares) : n_all) - it0;
   // rows [x.r0, row_limit(x)) of a stage exist; the others are masked
   auto row_limit = [&](Pos x) { return ROWS ? rr.end[x.ri] : p.C; };
   auto advance = [&](Pos x) {
@@ -304,7 +309,15 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
     *reinterpret_cast<SECO_LDS bf16x8*>(pb + 1024) = pack8(s, 1);
   };
 
-  Pos cur{head0, first_r0, first_ri};
+  Pos cur{0, first_r0, first_ri};
+  if (it0 > 0) {
+    cur.hg = it0 / n_rt;
+    int skip = it0 - cur.hg * n_rt;
+    if constexpr (ROWS) {
+      for (int len; skip >= (len = (rr.end[cur.ri] - cur.r0 + BQ - 1) / BQ); skip -= len) cur.r0 = rr.begin[++cur.ri];
+    }
+    cur.r0 += skip * BQ;
+  }
   Pos nxt = advance(cur);
   {
     const Src s0 = src_of(cur), s1 = src_of(nxt);
@@ -527,8 +540,9 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
   };
   if (divided) {
     // a share of the tile: plain stores of the unweighted sums, all 32 rows (the merge drops rows past the tile's end)
-    float* pb = ts.part + ((((int64_t)unit * ts.n_tiles + (tile - n_whole)) * ts.hs + share) * 2 + role) *
-                              (int64_t)(Cfg::kCols * 128) + (wave_e % NCB) * 32 * 128 + lane_e * 4;
+    const int n_slots = ts.plan.first[ts.plan.n_shared];
+    float* pb = ts.part + (((int64_t)unit * n_slots + (in_unit - n_whole)) * 2 + role) * (int64_t)(Cfg::kCols * 128) +
+                (wave_e % NCB) * 32 * 128 + lane_e * 4;
     turn_in();
 #pragma unroll
     for (int j = 0; j < 16; ++j) *reinterpret_cast<f32x4*>(pb + j * 256) = turned(j);
@@ -568,36 +582,36 @@ __global__ __launch_bounds__(NCB * 128, 2) void dkdv_bf16_kernel(AttnParams p, S
     dkdv_bf16_body<NCB, RB, ROWS, 1>(p, seg, ts, rr, total_items, smem);
 }
 
-// gK/gV of the divided column tiles: g += w * (sum of the head shares, in head order).  One thread per four
-// consecutive elements of a (tile, dV or dK) pair.
+// gK/gV of the shared-out column tiles: g += w * (sum of the shares, in order).  One thread per four consecutive
+// elements of a (tile, dV or dK) pair.
 template <int COLS>
 __global__ __launch_bounds__(256) void dkdv_tail_merge_kernel(AttnParams p, SegTable seg, TailSplit ts, int n_units) {
-  constexpr int kQuads = COLS * 128 / 4;
-  const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int quad = (int)(gid % kQuads);
-  const int64_t pair = gid / kQuads;
-  const int role = (int)(pair & 1);
-  const int64_t st = pair >> 1;                       // divided tile, counted over all units
-  if (st >= (int64_t)n_units * ts.n_tiles) return;
-  const int unit = (int)(st / ts.n_tiles);
-  const int n_ctiles = seg.tile_begin[seg.n];
-  const int tile = n_ctiles - ts.n_tiles + (int)(st % ts.n_tiles);
+  constexpr int kBlocks = COLS * 128 / 4 / 256;       // workgroups per (tile, dV or dK)
+  typedef float f32x4 __attribute__((ext_vector_type(4)));
+  const int quad = (blockIdx.x % kBlocks) * 256 + threadIdx.x, role = (blockIdx.x / kBlocks) & 1;
+  const int st = blockIdx.x / (2 * kBlocks);          // shared tile, counted over all units
+  const int unit = st / ts.plan.n_shared, pos = st - unit * ts.plan.n_shared;
+  const int tile = seg.tile_begin[seg.n] - ts.plan.n_tiles + pos;
   int si = 0;
   while (si + 1 < seg.n && tile >= seg.tile_begin[si + 1]) ++si;
   const int row = seg.col_begin[si] + (tile - seg.tile_begin[si]) * COLS + quad / 32;
   if (row >= seg.col_end[si]) return;
   const float wf = role == 0 ? seg.weight[si] : seg.weight[si] * p.scale;
-  const float* src = ts.part + (st * ts.hs * 2 + role) * (int64_t)(COLS * 128) + (int64_t)quad * 4;
-  float4 sum = *reinterpret_cast<const float4*>(src);
-  for (int h = 1; h < ts.hs; ++h) {
-    const float4 x = *reinterpret_cast<const float4*>(src + (int64_t)h * 2 * COLS * 128);
-    sum.x += x.x; sum.y += x.y; sum.z += x.z; sum.w += x.w;
-  }
   const int kvh = unit % p.Hkv, b = unit / p.Hkv;
   float* g = (role == 0 ? p.gv : p.gk) + b * p.gs[0] + kvh * p.gs[1] + (int64_t)row * p.gs[2] + (quad % 32) * 4;
-  float4 old = *reinterpret_cast<float4*>(g);
-  old.x += wf * sum.x; old.y += wf * sum.y; old.z += wf * sum.z; old.w += wf * sum.w;
-  *reinterpret_cast<float4*>(g) = old;
+  const f32x4 old = *reinterpret_cast<const f32x4*>(g);
+  const int n_slots = ts.plan.first[ts.plan.n_shared], slot = ts.plan.first[pos], hs = ts.plan.first[pos + 1] - slot;
+  const float* src = ts.part + (((int64_t)unit * n_slots + slot) * 2 + role) * (int64_t)(COLS * 128) + (int64_t)quad * 4;
+  f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+  for (int h = 0; h < hs; h += 4) {                   // four shares in flight; past the last one: its address again, dropped
+    f32x4 x[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) x[i] = *reinterpret_cast<const f32x4*>(src + (int64_t)min(h + i, hs - 1) * 2 * COLS * 128);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (h + i < hs) sum += x[i];
+  }
+  *reinterpret_cast<f32x4*>(g) = old + wf * sum;
 }
 
 }  // namespace
@@ -606,29 +620,36 @@ template <int NCB, int RB, bool ROWS>
 int launch_cfg(const AttnParams& p, const SegTable& seg, const RowRuns& rr, hipStream_t s) {
   using Cfg = DkdvCfg<NCB, RB>;
   const int n_units = p.Hkv * p.B, n_ctiles = seg.tile_begin[seg.n];
-  TailSplit ts{0, 1, p.tail_part};
   int n_rows = p.C;
   if (ROWS) {
     n_rows = 0;
     for (int i = 0; i < rr.n; ++i) n_rows += rr.end[i] - rr.begin[i];
   }
-  const TailPlan tp = tail_plan(n_units, n_ctiles, p.G, n_rows);
-  if (p.tail_part && tp.hs > 1) {
-    ts.n_tiles = tp.n_tiles;
-    ts.hs = tp.hs;
-  }
-  const int total = n_units * (n_ctiles - ts.n_tiles + ts.n_tiles * ts.hs);
+  // iterations of a column tile (as the kernel counts them)
+  auto iters = [&](int tile) {
+    int si = 0;
+    while (si + 1 < seg.n && tile >= seg.tile_begin[si + 1]) ++si;
+    const int c0 = seg.col_begin[si] + (tile - seg.tile_begin[si]) * Cfg::kCols;
+    const int r0 = (c0 > p.q_start ? c0 - p.q_start : 0) / Cfg::kBQ * Cfg::kBQ;
+    if (!ROWS) return ((p.C - r0 + Cfg::kBQ - 1) / Cfg::kBQ) * p.G;
+    int n = 0;
+    for (int i = 0; i < rr.n; ++i)
+      if (rr.end[i] > r0) n += (rr.end[i] - (rr.begin[i] > r0 ? rr.begin[i] : r0) + Cfg::kBQ - 1) / Cfg::kBQ;
+    return n * p.G;
+  };
+  TailSplit ts;
+  ts.part = p.tail_part;
+  ts.plan = share_plan(n_units, n_ctiles, p.G, n_rows, p.tail_part ? p.tail_slots : 0, iters);
+  const int total = n_units * (n_ctiles - ts.plan.n_tiles + ts.plan.n_entries);
   auto kern = dkdv_bf16_kernel<NCB, RB, ROWS>;
   static std::atomic<uint64_t> ready{0};
   if (!allow_lds(ready, reinterpret_cast<const void*>(kern), Cfg::kSmemBytes)) return SECO_ERR_LAUNCH;
   {
     ProfScope prof(kKernelDkdv, s);   // the merge of the divided tiles counts as part of the dK/dV pass
     hipLaunchKernelGGL(kern, dim3(xcd_grid(total)), dim3(Cfg::kThreads), Cfg::kSmemBytes, s, p, seg, ts, rr, total);
-    if (ts.n_tiles > 0) {
-      const int64_t threads = (int64_t)n_units * ts.n_tiles * 2 * (Cfg::kCols * 128 / 4);
-      hipLaunchKernelGGL(dkdv_tail_merge_kernel<Cfg::kCols>, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, p,
-                         seg, ts, n_units);
-    }
+    if (ts.plan.n_shared > 0)
+      hipLaunchKernelGGL(dkdv_tail_merge_kernel<Cfg::kCols>, dim3((unsigned)(n_units * ts.plan.n_shared * 2 * (Cfg::kCols / 8))),
+                         dim3(256), 0, s, p, seg, ts, n_units);
   }
   return launch_status();
 }

@@ -105,13 +105,21 @@ int splits_for(const seco_desc* d) {
   return split_count(pl, d->q_start + d->chunk_len);
 }
 
-// workspace of the dK/dV pass for the column tiles it divides by query head (bf16, grouped heads only)
+// workspace of the dK/dV pass for the column tiles it shares out: at most one share per CU (share_plan).  With
+// grouped heads the call insists on it; without, it is used if it is there.
+constexpr size_t kSlotBytes = (size_t)2 * kColTileBf16 * 128 * sizeof(float);
 size_t tail_part_bytes(const seco_desc* d) {
   if (d->dtype != SECO_BF16 || d->n_q_heads / d->n_kv_heads < 2) return 0;
-  return (size_t)device_cus() * 2 * kColTileBf16 * 128 * sizeof(float);   // at most one share per CU (tail_plan)
+  return (size_t)device_cus() * kSlotBytes;
 }
 // the partial dQ of the split path and the divided dK/dV tiles are never live together: they share one region
 size_t bwd_part_bytes(const seco_desc* d) { return std::max(split_part_bytes(d), tail_part_bytes(d)); }
+
+void use_tail_part(AttnParams& p, const seco_desc* d, size_t ws_bytes) {
+  const size_t slots = d->dtype == SECO_BF16 ? (ws_bytes - delta_bytes(d)) / kSlotBytes : 0;
+  p.tail_slots = (int)std::min(slots, (size_t)device_cus());
+  p.tail_part = p.tail_slots > 0 ? p.part : nullptr;
+}
 
 int check_fwd_like(const seco_desc* d) {
   int rc = check_desc(d);
@@ -183,7 +191,7 @@ int backward(const seco_desc* d, const void* q, const void* k, const void* v, co
   p.n_splits = splits_for(d);
   p.Cpad = (d->chunk_len + 31) / 32 * 32;
   p.part = reinterpret_cast<float*>(static_cast<char*>(ws) + delta_bytes(d));
-  p.tail_part = tail_part_bytes(d) ? p.part : nullptr;
+  use_tail_part(p, d, ws_bytes);
   hipStream_t s = static_cast<hipStream_t>(stream);
   const bool bf16 = d->dtype == SECO_BF16;
   // delta = rowsum(dO * O): the bf16 dQ kernel computes it in its prologue (and stores it for the dK/dV kernel)
@@ -290,7 +298,7 @@ int backward_gather(const seco_desc* d, const void* q_rows, const void* k, const
   p.n_splits = splits_for(d);
   p.Cpad = (d->chunk_len + 31) / 32 * 32;
   p.part = reinterpret_cast<float*>(static_cast<char*>(ws) + delta_bytes(d));
-  p.tail_part = tail_part_bytes(d) ? p.part : nullptr;
+  use_tail_part(p, d, ws_bytes);
   hipStream_t s = static_cast<hipStream_t>(stream);
   if ((rc = launch_dq_bf16(p, nullptr, s))) return rc;
   // dK/dV: the query rows are the chunk's and the later ones, the cache rows the chunk's own
@@ -390,6 +398,12 @@ extern "C" size_t seco_workspace_bytes(const seco_desc* desc, int op) {
   if (op == SECO_OP_FWD) return split_part_bytes(desc) + split_ml_bytes(desc);
   if (op == SECO_OP_BWD) return delta_bytes(desc) + bwd_part_bytes(desc);
   return (size_t)-1;
+}
+
+extern "C" size_t seco_workspace_bytes_preferred(const seco_desc* desc, int op) {
+  const size_t n = seco_workspace_bytes(desc, op);
+  if (n == (size_t)-1 || op != SECO_OP_BWD || desc->dtype != SECO_BF16) return n;
+  return std::max(n, delta_bytes(desc) + (size_t)device_cus() * kSlotBytes);
 }
 
 extern "C" int seco_launch_plan(const seco_desc* desc, int32_t n_col_tiles, int32_t* plan_host) {

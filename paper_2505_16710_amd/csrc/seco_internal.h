@@ -24,7 +24,8 @@ struct AttnParams {
   float* gv;
   float* part;       // split path: partial O (forward) or partial dQ (backward), fp32 [n_splits, B, Hq, C, D]
   float* part_ml;    // split path, forward: (reference max in log2 units, sum) per partial row, [n_splits, B, Hq, C, 2]
-  float* tail_part;  // dK/dV pass: sums of the column tiles divided by query head (workspace), or NULL
+  float* tail_part;  // dK/dV pass: sums of the column tiles shared out among several workgroups (workspace), or NULL
+  int tail_slots;    // shares that fit there (2 x 128 x 128 floats each)
   int n_splits;      // > 1 selects the split path
   int Cpad;          // C rounded up to 32: rows per head in the packed row space of the split path
   int B, Hq, Hkv, D, C, q_start, G;
@@ -111,6 +112,76 @@ inline TailPlan tail_plan(int n_units, int n_ctiles, int G, int C) {
     break;
   }
   return tp;
+}
+
+// What the dK/dV launcher makes of that: the list of column tiles that end a (batch, KV head)'s work, each with the
+// number of workgroups that share its iterations (an iteration: 64 query rows of one head).  The last round's tiles as
+// above, or, when all tiles fit one round, all of them; an iteration range may cut through heads, so that any number
+// of shares is possible, and tiles on the diagonal, which have fewer iterations, get fewer shares.
+constexpr int kMaxEntries = 256;
+struct SharePlan {
+  int n_tiles;                        // column tiles in the list, the last ones of every (batch, KV head)
+  int n_shared;                       // of these, how many are shared out: the first ones (they see the most rows)
+  int n_entries;                      // workgroups per (batch, KV head) for the list
+  uint8_t tile_of[kMaxEntries];       // list position of a workgroup's tile
+  uint16_t first[kMaxEntries + 1];    // first workgroup of a list position; shared tiles come first, so for them it is
+};                                    // also the first slot of partial sums
+
+// Iterations of list position i: iters(i), not increasing.  Times in microseconds, as measured: a workgroup takes
+// 9 + 1.2 per iteration when the chip is not full, a merge 4 + 0.03 per slot.
+template <typename F>
+inline SharePlan share_plan(int n_units, int n_ctiles, int G, int n_rows, int slots, const F& iters) {
+  SharePlan sp;
+  sp.n_tiles = sp.n_shared = sp.n_entries = 0;
+  const int round = device_cus();
+  const TailPlan tp = tail_plan(n_units, n_ctiles, G, n_rows);
+  const int tail = (int)((int64_t)n_units * n_ctiles % round);
+  if (tail == 0 || slots < 2 * n_units) return sp;
+  const int n = tp.hs > 1 ? tp.n_tiles : ((int64_t)n_units * n_ctiles < round ? n_ctiles : (tail + n_units - 1) / n_units);
+  if (n > kMaxEntries) return sp;
+  const float kWg = 9.f, kIter = 1.2f, kMerge = 4.f, kSlot = 0.03f;
+  const int most = iters(n_ctiles - n);
+  int best = 0;
+  float best_t = 0.f;
+  static const int ways[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32};
+  auto shares = [&](int i, int per) { return (iters(n_ctiles - n + i) + per - 1) / per; };
+  for (int w : ways) {
+    if (w < tp.hs) continue;
+    const int per = (most + w - 1) / w;
+    if (per < 2 && w > 1) break;
+    int entries = 0, shared = 0, n_over = 0;
+    float sum = 0.f, longest = 0.f;
+    for (int i = 0; i < n; ++i) {
+      int k = shares(i, per);
+      if (k < 1) k = 1;
+      if (k > 1) shared += k, ++n_over;
+      entries += k;
+      const int it = iters(n_ctiles - n + i);
+      sum += k * kWg + it * kIter;
+      const float t = kWg + (it + k - 1) / k * kIter;
+      if (t > longest) longest = t;
+    }
+    if (entries > kMaxEntries || shared * n_units > slots) break;
+    const float even = sum * n_units / round;
+    float t = entries * n_units <= round ? longest : even + 0.5f * longest > longest + kWg ? even + 0.5f * longest : longest + kWg;
+    if (n_over > 0) t += kMerge + kSlot * shared * n_units;
+    if (best == 0 || t < best_t) {
+      best = w;
+      best_t = t;
+    }
+  }
+  if (best < 2) return sp;
+  const int per = (most + best - 1) / best;
+  sp.n_tiles = n;
+  for (int i = 0; i < n; ++i) {
+    int k = shares(i, per);
+    if (k < 1) k = 1;
+    if (k > 1) sp.n_shared = i + 1;
+    sp.first[i] = (uint16_t)sp.n_entries;
+    for (int j = 0; j < k; ++j) sp.tile_of[sp.n_entries++] = (uint8_t)i;
+  }
+  sp.first[n] = (uint16_t)sp.n_entries;
+  return sp;
 }
 
 // fp32 kernels (any head_dim that is a multiple of 4, up to 256)

@@ -121,6 +121,27 @@ def test_bf16_last_round_divided_by_query_head(B, Hq, Hkv, N, C, sel):
     assert np.array_equal(got["gk"], again["gk"]) and np.array_equal(got["gv"], again["gv"])
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,N,C,sel", [
+    (1, 2, 2, 2500, 2500, None),         # one head per KV head, tiles of the diagonal with 1 .. 40 iterations, ragged rows
+    (1, 3, 1, 3001, 1500, None),         # shares that cut through heads; last call of one row
+    (2, 8, 1, 1290, 430, [2, 0]),        # weights, a column tile that ends inside its run
+])
+def test_bf16_column_tiles_shared_out_by_query_rows(B, Hq, Hkv, N, C, sel):
+    """dK/dV pass with few column tiles: a tile's (head, row) iterations divided among workgroups, merged in order."""
+    x = small_layer(22, B, Hq, Hkv, N, 128, "bf16")
+    s = 1 / np.sqrt(128)
+    lam = float(np.float32(3 / 2))
+    kw = {} if sel is None else {"selected": sel, "factor": lam}
+    got = run_layer(x, C, s, "bf16", **kw)
+    if sel is None:
+        ref = A.seco_layer(x["q"], x["k"], x["v"], x["do"], C, s)
+    else:
+        ref = A.spaco_layer(x["q"], x["k"], x["v"], x["do"], C, s, sel, lam)
+    check(got, ref, "bf16", f"shared by rows {B,Hq,Hkv,N,C,sel}")
+    again = run_layer(x, C, s, "bf16", **kw)
+    assert np.array_equal(got["gk"], again["gk"]) and np.array_equal(got["gv"], again["gv"])
+
+
 def _one_call(dtype, D, N, C, j, weights=None, seed=40):
     x = small_layer(seed, 1, 4, 2, N, D, dtype)
     q, k, v, do = (to_dev(x[n], dtype) for n in ("q", "k", "v", "do"))
