@@ -27,6 +27,7 @@ SOURCES = [
     "bwd_dq_bf16.hip",
     "bwd_dkdv_bf16.hip",
     "decoder.hip",
+    "gemm_bf16.hip",
 ]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -86,7 +87,7 @@ def build_extension(verbose=True):
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I", INCLUDE,
            "-I", CSRC, "-isystem", os.path.join(troot, "include"), "-isystem", os.path.join(troot, "include", "torch", "csrc", "api", "include"),
            "-isystem", sysconfig.get_paths()["include"], "-isystem", os.path.join(os.path.dirname(os.path.dirname(HIPCC)), "include"),
-           os.path.join(CSRC, "binding_ext.cpp"), "-o", out, "-L", os.path.join(troot, "lib"),
+           os.path.join(CSRC, "binding_ext.cpp"), os.path.join(CSRC, "chunk_step_ext.cpp"), "-o", out, "-L", os.path.join(troot, "lib"),
            "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip", "-ldl"]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:

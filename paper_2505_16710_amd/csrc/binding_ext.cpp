@@ -5,119 +5,11 @@
 // 13 - 20 us of host time, more than most of the kernels of a short chunk; this one costs 3 - 5 us, of which the
 // kernel launch is the largest part.  The entry points are looked up in the library that the Python side has
 // loaded (seco_init gets its path), so there is one copy of libseco_hip.so in the process.
-#include <Python.h>
-#include <dlfcn.h>
-
-#include <cmath>
-#include <vector>
-
-#include <ATen/ATen.h>
-#include <c10/hip/HIPStream.h>
-#include <torch/csrc/Exceptions.h>
-#include <torch/csrc/autograd/python_variable.h>
-
-#include "decoder.h"
-#include "seco.h"
+#include "binding_common.h"
 
 namespace {
 
-using at::Tensor;
-
-#define SECO_ENTRIES(X)                                                                                             \
-  X(seco_chunk_attn_fwd) X(seco_chunk_attn_bwd) X(seco_chunk_attn_bwd_noalloc) X(spaco_chunk_attn_bwd)              \
-  X(spaco_chunk_attn_bwd_sparse_dq) X(seco_chunk_attn_bwd_gather) X(spaco_chunk_attn_bwd_gather)                    \
-  X(seco_workspace_bytes) X(seco_workspace_bytes_preferred) X(kvgrad_zero) X(kvgrad_accumulate) X(kv_append) X(kvgrad_readout) X(kv_append_rope)      \
-  X(kvgrad_readout_rope) X(rope_rotate) X(dec_add_rmsnorm) X(dec_rmsnorm_bwd) X(dec_silu) X(dec_silu_bwd)             \
-  X(dec_cross_entropy) X(dec_embedding_bwd)
-struct Lib {
-#define X(name) decltype(&::name) name = nullptr;
-  SECO_ENTRIES(X)
-#undef X
-} lib;
-PyObject* g_error = nullptr;   // SecoError(status, where)
-
-// an error that is already set in the interpreter
-struct Raised {};
-[[noreturn]] void raise(PyObject* type, const char* msg) {
-  PyErr_SetString(type, msg);
-  throw Raised{};
-}
-void check(int status, const char* where) {
-  if (status == SECO_OK) return;
-  PyObject* e = PyObject_CallFunction(g_error, "is", status, where);
-  if (e) {
-    PyErr_SetObject(g_error, e);
-    Py_DECREF(e);
-  }
-  throw Raised{};
-}
-
-const Tensor& tensor(PyObject* o) {
-  if (!THPVariable_Check(o)) raise(PyExc_TypeError, "expected a torch tensor");
-  return THPVariable_Unpack(o);
-}
-const Tensor* opt_tensor(PyObject* o) { return o == Py_None ? nullptr : &tensor(o); }
-int64_t integer(PyObject* o) {
-  if (PyLong_Check(o)) {
-    const int64_t v = PyLong_AsLongLong(o);
-    if (v == -1 && PyErr_Occurred()) throw Raised{};
-    return v;
-  }
-  PyObject* n = PyNumber_Long(o);
-  if (!n) throw Raised{};
-  const int64_t v = PyLong_AsLongLong(n);
-  Py_DECREF(n);
-  if (v == -1 && PyErr_Occurred()) throw Raised{};
-  return v;
-}
-int32_t int32(PyObject* o) { return (int32_t)integer(o); }
-double real(PyObject* o) {
-  const double v = PyFloat_AsDouble(o);
-  if (v == -1.0 && PyErr_Occurred()) throw Raised{};
-  return v;
-}
-std::vector<float> floats(PyObject* o) {
-  PyObject* s = PySequence_Fast(o, "expected a sequence of floats");
-  if (!s) throw Raised{};
-  std::vector<float> v((size_t)PySequence_Fast_GET_SIZE(s));
-  for (size_t i = 0; i < v.size(); ++i) {
-    v[i] = (float)PyFloat_AsDouble(PySequence_Fast_GET_ITEM(s, (Py_ssize_t)i));
-    if (PyErr_Occurred()) {
-      Py_DECREF(s);
-      throw Raised{};
-    }
-  }
-  Py_DECREF(s);
-  return v;
-}
-void* stream(PyObject* o) {
-  if (o == Py_None) return c10::hip::getCurrentHIPStream().stream();
-  PyObject* n = PyObject_HasAttrString(o, "cuda_stream") ? PyObject_GetAttrString(o, "cuda_stream") : PyNumber_Long(o);
-  if (!n) throw Raised{};
-  void* s = PyLong_AsVoidPtr(n);
-  Py_DECREF(n);
-  if (!s && PyErr_Occurred()) throw Raised{};
-  return s;
-}
-
-int dtype_code(const Tensor& t) {
-  if (t.scalar_type() == at::kBFloat16) return SECO_BF16;
-  if (t.scalar_type() == at::kFloat) return SECO_F32;
-  raise(PyExc_TypeError, "unsupported dtype: expected bfloat16 or float32");
-}
-void strides3(const Tensor& t, int64_t out[3]) {
-  if (t.dim() != 4 || t.stride(3) != 1)
-    raise(PyExc_ValueError, "expected a [batch, head, row, head_dim] tensor with contiguous head_dim");
-  for (int i = 0; i < 3; ++i) out[i] = t.stride(i);
-}
-void* ptr(const Tensor* t) { return t ? t->data_ptr() : nullptr; }
-void* ptr(const Tensor& t) { return t.data_ptr(); }
-float* fptr(const Tensor* t) { return static_cast<float*>(ptr(t)); }
-float* fptr(const Tensor& t) { return static_cast<float*>(t.data_ptr()); }
-
-Tensor like(const Tensor& t) { return at::empty_strided(t.sizes(), t.strides(), t.options().requires_grad(false)); }
-Tensor bytes(int64_t n, const Tensor& t) { return at::empty({n}, t.options().dtype(at::kByte).requires_grad(false)); }
-size_t nbytes(const Tensor& t) { return (size_t)t.numel() * t.element_size(); }
+using namespace seco_ext;
 
 seco_desc chunk_desc(const Tensor& q, const Tensor& k, PyObject* q_start, PyObject* scale, const Tensor& o, const Tensor* g) {
   seco_desc d;
@@ -146,11 +38,6 @@ seco_desc rows_desc(const Tensor& t, int64_t rows, int64_t q_start, int dtype) {
   d.dtype = dtype;
   d.softmax_scale = 1.f;
   return d;
-}
-size_t workspace(const seco_desc& d, int op) {
-  const size_t n = lib.seco_workspace_bytes_preferred(&d, op);
-  if (n == (size_t)-1) check(SECO_ERR_SHAPE, "seco_workspace_bytes");
-  return n;
 }
 bool same_layout(const Tensor& a, const Tensor& b) { return a.sizes() == b.sizes() && a.strides() == b.strides(); }
 
@@ -351,89 +238,6 @@ PyObject* rotate(PyObject* const* a) {
   return a[4] == Py_None ? THPVariable_Wrap(out) : (Py_INCREF(a[4]), a[4]);
 }
 
-// ---- row kernels of the decoder (decoder.h); tensors are contiguous [rows, d] ----
-const Tensor& rows2(PyObject* o) {
-  const Tensor& t = tensor(o);
-  if (t.dim() != 2 || !t.is_contiguous()) raise(PyExc_ValueError, "expected a contiguous [rows, d] tensor");
-  return t;
-}
-void same_as(const Tensor& t, const Tensor& x) {
-  if (t.sizes() != x.sizes() || t.scalar_type() != x.scalar_type() || !t.is_contiguous())
-    raise(PyExc_ValueError, "tensors must share shape and dtype and be contiguous");
-}
-void gain_of(const Tensor& g, const Tensor& x) {
-  if (g.dim() != 1 || g.size(0) != x.size(1) || g.scalar_type() != x.scalar_type() || !g.is_contiguous())
-    raise(PyExc_ValueError, "the gain must be a contiguous [d] tensor of the rows' dtype");
-}
-
-// (x, y or None, gain, x_out or None) -> (x_out, h, rstd): x_out = x + y, h = its RMSNorm; x_out is x when y is None
-PyObject* add_rmsnorm(PyObject* const* a) {
-  const Tensor& x = rows2(a[0]);
-  const Tensor *y = opt_tensor(a[1]), &g = tensor(a[2]);
-  if (y) same_as(*y, x);
-  gain_of(g, x);
-  const Tensor xo = !y ? x : a[3] == Py_None ? like(x) : tensor(a[3]);
-  if (y) same_as(xo, x);
-  const Tensor h = like(x), rstd = at::empty({x.size(0)}, x.options().dtype(at::kFloat).requires_grad(false));
-  check(lib.dec_add_rmsnorm(dtype_code(x), ptr(x), ptr(y), ptr(g), ptr(xo), ptr(h), fptr(rstd), x.size(0), x.size(1),
-                            stream(Py_None)), "dec_add_rmsnorm");
-  return Py_BuildValue("NNN", THPVariable_Wrap(xo), THPVariable_Wrap(h), THPVariable_Wrap(rstd));
-}
-
-// (x, gain, rstd, d_h, d_in or None, gain_part): d_in += gradient at x (or d_h <- it, without d_in); returns that tensor
-PyObject* rmsnorm_bwd(PyObject* const* a) {
-  const Tensor &x = rows2(a[0]), &g = tensor(a[1]), &rstd = tensor(a[2]), &dh = tensor(a[3]), &part = tensor(a[5]);
-  const Tensor* din = opt_tensor(a[4]);
-  same_as(dh, x);
-  if (din) same_as(*din, x);
-  gain_of(g, x);
-  if (rstd.scalar_type() != at::kFloat || rstd.numel() != x.size(0) || part.scalar_type() != at::kFloat ||
-      part.dim() != 2 || part.size(0) != DEC_GAIN_BLOCKS || part.size(1) != x.size(1) || !part.is_contiguous())
-    raise(PyExc_ValueError, "rstd: fp32 [rows]; gain_part: contiguous fp32 [256, d]");
-  PyObject* out = din ? a[4] : a[3];
-  check(lib.dec_rmsnorm_bwd(dtype_code(x), ptr(x), ptr(g), fptr(rstd), ptr(dh), ptr(din), ptr(tensor(out)), fptr(part),
-                            x.size(0), x.size(1), stream(Py_None)), "dec_rmsnorm_bwd");
-  return Py_INCREF(out), out;
-}
-
-// (u) -> silu(u)
-PyObject* silu(PyObject* const* a) {
-  const Tensor& u = rows2(a[0]);
-  const Tensor out = like(u);
-  check(lib.dec_silu(dtype_code(u), ptr(u), ptr(out), u.numel(), stream(Py_None)), "dec_silu");
-  return THPVariable_Wrap(out);
-}
-// (u, d_a): d_a <- d_a * silu'(u)
-PyObject* silu_bwd(PyObject* const* a) {
-  const Tensor &u = rows2(a[0]), &da = tensor(a[1]);
-  same_as(da, u);
-  check(lib.dec_silu_bwd(dtype_code(u), ptr(u), ptr(da), u.numel(), stream(Py_None)), "dec_silu_bwd");
-  return Py_INCREF(a[1]), a[1];
-}
-
-// (logits, target int64 [rows], loss fp32 [rows] or None): with loss the rows' losses, without it logits <- gradient
-PyObject* cross_entropy(PyObject* const* a) {
-  const Tensor &l = rows2(a[0]), &t = tensor(a[1]);
-  const Tensor* loss = opt_tensor(a[2]);
-  if (t.scalar_type() != at::kLong || t.numel() != l.size(0) || !t.is_contiguous() ||
-      (loss && (loss->scalar_type() != at::kFloat || loss->numel() != l.size(0) || !loss->is_contiguous())))
-    raise(PyExc_ValueError, "targets: contiguous int64 [rows]; loss: contiguous float32 [rows]");
-  check(lib.dec_cross_entropy(dtype_code(l), ptr(l), static_cast<const int64_t*>(ptr(t)), fptr(loss), l.size(0), l.size(1),
-                              stream(Py_None)), "dec_cross_entropy");
-  Py_RETURN_NONE;
-}
-
-// (d_x, token int64 [rows], grad [v, d]): grad[token[r]] += d_x[r]
-PyObject* embedding_bwd(PyObject* const* a) {
-  const Tensor &dx = rows2(a[0]), &t = tensor(a[1]), &g = rows2(a[2]);
-  if (t.scalar_type() != at::kLong || t.numel() != dx.size(0) || !t.is_contiguous() || g.size(1) != dx.size(1) ||
-      g.scalar_type() != dx.scalar_type())
-    raise(PyExc_ValueError, "tokens: contiguous int64 [rows]; grad: [v, d] of the rows' dtype");
-  check(lib.dec_embedding_bwd(dtype_code(dx), ptr(dx), static_cast<const int64_t*>(ptr(t)), ptr(g), dx.size(0), dx.size(1),
-                              g.size(0), stream(Py_None)), "dec_embedding_bwd");
-  Py_RETURN_NONE;
-}
-
 // (library path, SecoError)
 PyObject* init(PyObject* const* a) {
   const char* path = PyUnicode_AsUTF8(a[0]);
@@ -450,30 +254,17 @@ PyObject* init(PyObject* const* a) {
   Py_RETURN_NONE;
 }
 
-template <PyObject* (*F)(PyObject* const*), int N>
-PyObject* entry(PyObject*, PyObject* const* args, Py_ssize_t n) {
-  HANDLE_TH_ERRORS
-  if (n != N) {
-    PyErr_Format(PyExc_TypeError, "expected %d arguments, got %zd", N, n);
-    return nullptr;
-  }
-  try {
-    return F(args);
-  } catch (const Raised&) {
-    return nullptr;
-  }
-  END_HANDLE_TH_ERRORS
-}
-#define METHOD(name, f, n) {name, reinterpret_cast<PyCFunction>(reinterpret_cast<void*>(&entry<f, n>)), METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {
-    METHOD("init", init, 2), METHOD("fwd", fwd, 9), METHOD("bwd", bwd, 16), METHOD("bwd_noalloc", bwd_noalloc, 12),
-    METHOD("bwd_gather", bwd_gather, 17), METHOD("zero", zero, 5), METHOD("accumulate", accumulate, 8),
-    METHOD("append", append, 7), METHOD("readout", readout, 10), METHOD("rotate", rotate, 6),
-    METHOD("add_rmsnorm", add_rmsnorm, 4), METHOD("rmsnorm_bwd", rmsnorm_bwd, 6), METHOD("silu", silu, 1),
-    METHOD("silu_bwd", silu_bwd, 2), METHOD("cross_entropy", cross_entropy, 3), METHOD("embedding_bwd", embedding_bwd, 3),
+    SECO_METHOD("init", init, 2), SECO_METHOD("fwd", fwd, 9), SECO_METHOD("bwd", bwd, 16), SECO_METHOD("bwd_noalloc", bwd_noalloc, 12),
+    SECO_METHOD("bwd_gather", bwd_gather, 17), SECO_METHOD("zero", zero, 5), SECO_METHOD("accumulate", accumulate, 8),
+    SECO_METHOD("append", append, 7), SECO_METHOD("readout", readout, 10), SECO_METHOD("rotate", rotate, 6),
     {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_seco_ext", "native half of the binding", -1, methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__seco_ext() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__seco_ext() {
+  PyObject* m = PyModule_Create(&module);
+  if (m && PyModule_AddFunctions(m, seco_ext::step_methods) < 0) Py_CLEAR(m);
+  return m;
+}

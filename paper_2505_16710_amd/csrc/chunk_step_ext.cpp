@@ -1,0 +1,531 @@
+// The training step of chunk_loop.py, one chunk at a time, on the host side: what is launched, in which order, on which
+// buffers.  Second source of the extension module of the binding.
+//
+// A chunk of the step is about 90 launches of a few microseconds each.  Driven from Python, with the matrix products
+// through the framework (17 - 19 us of host time per call), a two-layer step over 4096 tokens in chunks of 512 took
+// 9.1 ms, of which the GPU worked 6.7; here a launch costs 2 - 4 us of host time, activations are carved from two
+// blocks allocated once per step, and the products are the library's own (gemm_bf16.hip) where type and alignment allow.
+#include <map>
+#include <memory>
+
+#include "binding_common.h"
+
+namespace seco_ext {
+namespace {
+
+// A block of device memory handed out front to back; `mark` / `reset` free everything taken since.
+struct Arena {
+  Tensor buf;
+  size_t used = 0;
+  void create(size_t bytes_total, const Tensor& like_t) { buf = bytes((int64_t)bytes_total, like_t); }
+  void* take(size_t n) {
+    if (used + n > nbytes(buf)) raise(PyExc_RuntimeError, "activation block too small");
+    void* p = static_cast<char*>(buf.data_ptr()) + used;
+    used += (n + 255) & ~(size_t)255;
+    return p;
+  }
+};
+
+struct Param {
+  Tensor w;              // contiguous
+  bool wanted = false;
+  Tensor grad;           // undefined until the first chunk adds to it
+};
+
+struct Layer {
+  Param norm1, norm2, wqkv, wo, w1, w2;
+  float *part1 = nullptr, *part2 = nullptr;      // partial sums of the gains' gradients
+  Tensor k, v, gk, gv;                           // KV cache and KV-gradient buffers, [B, Hkv, N, D]
+  std::map<int64_t, std::pair<Tensor, Tensor>> kept;   // q_start -> (O rows [B, C, Hq, D], LSE) of stage 1
+  Tensor q_all, do_all, o_all, dq_all, stats;    // transposed backward order only
+};
+
+// What the backward of a layer needs of a chunk's forward; C rows per sequence.
+struct Saved {
+  void *x1, *h1, *qkv, *o, *x2, *h2, *u, *a;
+  float *r1, *lse, *r2;
+  Tensor keep_o, keep_lse;                       // O and LSE taken back from stage 1
+};
+
+enum Keep { kCompute = 0, kStore = 1, kReuse = 2 };
+
+struct Step {
+  int64_t L, Hq, Hkv, D, B, N, dm, ff, V, W, HD;   // W: columns of the joint projection
+  double scale, rope_base;                         // rope_base 0: no rotary embedding
+  int dtype;
+  size_t e;                                        // bytes per element
+  Param emb, head, norm_f;
+  float* part_f = nullptr;
+  Tensor parts;
+  std::vector<Layer> layers;
+  Arena stage1, stage2;
+  void* s = nullptr;                               // stream of the current call
+  bool trained = false;                            // a chunk has been back-propagated
+
+  at::TensorOptions opts() const { return emb.w.options().requires_grad(false); }
+  Tensor view(void* p, at::IntArrayRef sizes) { return at::from_blob(p, sizes, opts()); }
+
+  // ---- matrix products: the library's own kernel where it takes the operands, the framework's otherwise
+  bool own(int form, int64_t M, int64_t N_, int64_t K, int64_t lda, int64_t ldb, int64_t ldc) const {
+    return dtype == SECO_BF16 && lib.dec_gemm_supported(form, M, N_, K, lda, ldb, ldc);
+  }
+  // c[M, n] = a[M, K] w[K, n]
+  void mm(void* c, void* a, const Param& w, int64_t M) {
+    const int64_t K = w.w.size(0), n = w.w.size(1);
+    if (own(DEC_GEMM_NN, M, n, K, K, n, n)) {
+      check(lib.dec_gemm(DEC_GEMM_NN, DEC_GEMM_STORE, a, ptr(w.w), c, nullptr, M, n, K, K, n, n, s), "dec_gemm");
+    } else {
+      Tensor out = view(c, {M, n});
+      at::mm_out(out, view(a, {M, K}), w.w);
+    }
+  }
+  // u = h w, a = silu(u)
+  void mm_silu(void* u, void* a, void* h, const Param& w, int64_t M) {
+    const int64_t K = w.w.size(0), n = w.w.size(1);
+    if (own(DEC_GEMM_NN, M, n, K, K, n, n)) {
+      check(lib.dec_gemm(DEC_GEMM_NN, DEC_GEMM_SILU, h, ptr(w.w), u, a, M, n, K, K, n, n, s), "dec_gemm");
+    } else {
+      mm(u, h, w, M);
+      check(lib.dec_silu(dtype, u, a, M * n, s), "dec_silu");
+    }
+  }
+  // d_x[M, K] = d_y[M, n] w[K, n]^T; u non-NULL: times silu'(u)
+  void mm_bwd(void* dx, void* dy, const Param& w, int64_t M, void* u = nullptr) {
+    const int64_t K = w.w.size(0), n = w.w.size(1);
+    if (own(DEC_GEMM_NT, M, K, n, n, n, K)) {
+      check(lib.dec_gemm(DEC_GEMM_NT, u ? DEC_GEMM_SILU_BWD : DEC_GEMM_STORE, dy, ptr(w.w), dx, u, M, K, n, n, n, K, s), "dec_gemm");
+    } else {
+      Tensor out = view(dx, {M, K});
+      at::mm_out(out, view(dy, {M, n}), w.w.t());
+      if (u) check(lib.dec_silu_bwd(dtype, u, dx, M * K, s), "dec_silu_bwd");
+    }
+  }
+  // grad[K, n] += x[M, K]^T d_y[M, n] (fp32 inside the product, rounded once per chunk)
+  void add(Param& w, void* x, void* dy, int64_t M) {
+    if (!w.wanted) return;
+    const int64_t K = w.w.size(0), n = w.w.size(1);
+    const bool first = !w.grad.defined();
+    if (first) w.grad = at::empty({K, n}, opts());
+    if (own(DEC_GEMM_TN, K, n, M, K, n, n)) {
+      check(lib.dec_gemm(DEC_GEMM_TN, first ? DEC_GEMM_STORE : DEC_GEMM_ADD, x, dy, ptr(w.grad), nullptr, K, n, M, K, n, n, s), "dec_gemm");
+    } else if (first) {
+      at::mm_out(w.grad, view(x, {M, K}).t(), view(dy, {M, n}));
+    } else {
+      w.grad.addmm_(view(x, {M, K}).t(), view(dy, {M, n}));
+    }
+  }
+
+  // ---- attention
+  seco_desc desc(int64_t C, int64_t q_start, const Layer& l) const {
+    seco_desc d;
+    const int64_t q[3] = {C * W, D, W}, o[3] = {C * HD, D, HD};
+    for (int i = 0; i < 3; ++i) {
+      d.q_stride[i] = q[i];
+      d.o_stride[i] = o[i];
+      d.kv_stride[i] = l.k.stride(i);
+      d.g_stride[i] = l.gk.stride(i);
+    }
+    d.batch = (int32_t)B;
+    d.n_q_heads = (int32_t)Hq;
+    d.n_kv_heads = (int32_t)Hkv;
+    d.head_dim = (int32_t)D;
+    d.chunk_len = (int32_t)C;
+    d.q_start = (int32_t)q_start;
+    d.dtype = dtype;
+    d.softmax_scale = (float)scale;
+    return d;
+  }
+  char* at_col(void* qkv, int64_t col) const { return static_cast<char*>(qkv) + col * (int64_t)e; }
+  void rotate(void* qkv, int64_t C, int64_t q_start, bool inverse) {
+    if (rope_base == 0.0) return;
+    seco_desc d = desc(C, 0, layers[0]);
+    d.n_kv_heads = d.n_q_heads;
+    const int64_t st[3] = {C * W, D, W};
+    for (int64_t* x : {d.q_stride, d.o_stride, d.kv_stride, d.g_stride}) std::copy(st, st + 3, x);
+    check(lib.rope_rotate(&d, (int32_t)Hq, qkv, qkv, q_start, (float)rope_base, inverse, s), "rope_rotate");
+  }
+  void append(Layer& l, void* qkv, int64_t C, int64_t q_start) {
+    seco_desc d = desc(C, q_start, l);
+    std::copy(d.q_stride, d.q_stride + 3, d.o_stride);
+    std::copy(d.q_stride, d.q_stride + 3, d.g_stride);
+    d.n_q_heads = d.n_kv_heads;
+    d.softmax_scale = 1.f;
+    void *k = at_col(qkv, HD), *v = at_col(qkv, HD + Hkv * D);
+    if (rope_base != 0.0)
+      check(lib.kv_append_rope(&d, k, v, ptr(l.k), ptr(l.v), (float)rope_base, s), "kv_append_rope");
+    else
+      check(lib.kv_append(&d, k, v, ptr(l.k), ptr(l.v), s), "kv_append");
+  }
+  void readout(Layer& l, void* d_qkv, int64_t C, int64_t q_start) {
+    seco_desc d = desc(C, q_start, l);
+    std::copy(d.q_stride, d.q_stride + 3, d.o_stride);
+    std::copy(d.q_stride, d.q_stride + 3, d.kv_stride);
+    d.n_q_heads = d.n_kv_heads;
+    d.softmax_scale = 1.f;
+    void *dk = at_col(d_qkv, HD), *dv = at_col(d_qkv, HD + Hkv * D);
+    if (rope_base != 0.0)
+      check(lib.kvgrad_readout_rope(&d, fptr(l.gk), fptr(l.gv), dk, dv, 1.f, (float)rope_base, s), "kvgrad_readout_rope");
+    else
+      check(lib.kvgrad_readout(&d, fptr(l.gk), fptr(l.gv), dk, dv, 1.f, s), "kvgrad_readout");
+  }
+  // O and LSE of the chunk; its k / v enter the cache.  (kReuse: the rebuilt chunk has the same inputs and the kernels are
+  // deterministic, so the values are identical and the cache rows already hold this chunk's K/V.)
+  void attention(Layer& l, Saved& sv, int64_t C, int64_t q_start, Keep keep, Arena& mem) {
+    if (keep == kReuse) {
+      // the span of stage 1 that holds this chunk's rows (the chunk itself, or a longer span to cut from)
+      auto it = l.kept.upper_bound(q_start);
+      if (it == l.kept.begin()) raise(PyExc_RuntimeError, "no kept attention output");
+      --it;
+      const int64_t a = q_start - it->first;
+      sv.keep_o = it->second.first;
+      sv.keep_lse = it->second.second;
+      if (a != 0 || C != sv.keep_o.size(1)) {
+        sv.keep_o = sv.keep_o.slice(1, a, a + C).contiguous();
+        sv.keep_lse = sv.keep_lse.slice(2, a, a + C).contiguous();
+      }
+      sv.o = ptr(sv.keep_o);
+      sv.lse = fptr(sv.keep_lse);
+      return;
+    }
+    append(l, sv.qkv, C, q_start);
+    if (keep == kStore) {
+      sv.keep_o = at::empty({B, C, Hq, D}, opts());
+      sv.keep_lse = at::empty({B, Hq, C}, opts().dtype(at::kFloat));
+      l.kept[q_start] = {sv.keep_o, sv.keep_lse};
+      sv.o = ptr(sv.keep_o);
+      sv.lse = fptr(sv.keep_lse);
+    } else {
+      sv.o = mem.take(B * C * HD * e);
+      sv.lse = static_cast<float*>(mem.take(B * Hq * C * 4));
+    }
+    const seco_desc d = desc(C, q_start, l);
+    const size_t n = workspace(d, SECO_OP_FWD);
+    Tensor ws;
+    if (n > 0) ws = bytes((int64_t)n, emb.w);
+    check(lib.seco_chunk_attn_fwd(&d, sv.qkv, ptr(l.k), ptr(l.v), sv.o, sv.lse, n ? ptr(ws) : nullptr, n, s), "seco_chunk_attn_fwd");
+  }
+  void attention_bwd(Layer& l, const Saved& sv, void* d_o, void* d_qkv, int64_t C, int64_t q_start, const std::vector<float>& w,
+                     const std::vector<float>& wq, int64_t wlen) {
+    seco_desc d = desc(C, q_start, l);
+    const Tensor ws = bytes((int64_t)std::max<size_t>(workspace(d, SECO_OP_BWD), 256), emb.w);
+    const size_t nw = nbytes(ws);
+    if (l.q_all.defined()) {
+      // transposed order: this chunk's finished gK/gV rows from its own and every later chunk's query rows, whose Q and
+      // dO the layer has kept; nothing is added to earlier rows.  w: weights of the row chunks under Alg. 2
+      auto heads = [&](void* p, int64_t row) { return at::from_blob(p, {B, Hq, C, D}, {C * row, D, row, 1}, opts()); };
+      l.q_all.slice(2, q_start, q_start + C).copy_(heads(sv.qkv, W));
+      l.do_all.slice(2, q_start, q_start + C).copy_(heads(d_o, HD));
+      l.o_all.slice(2, q_start, q_start + C).copy_(heads(sv.o, HD));
+      Tensor dq = l.dq_all.slice(2, q_start, q_start + C);
+      for (int i = 0; i < 3; ++i) d.q_stride[i] = d.o_stride[i] = l.q_all.stride(i);
+      auto row = [&](const Tensor& t) { return static_cast<char*>(ptr(t)) + q_start * t.stride(2) * (int64_t)e; };
+      const int32_t later = (int32_t)(N - q_start - C);
+      if (w.empty())
+        check(lib.seco_chunk_attn_bwd_gather(&d, row(l.q_all), ptr(l.k), ptr(l.v), row(l.o_all), sv.lse, row(l.do_all), ptr(dq),
+                                             fptr(l.gk), fptr(l.gv), fptr(l.stats), l.stats.size(3), later, ptr(ws), nw, s),
+              "seco_chunk_attn_bwd_gather");
+      else
+        check(lib.spaco_chunk_attn_bwd_gather(&d, row(l.q_all), ptr(l.k), ptr(l.v), row(l.o_all), sv.lse, row(l.do_all), ptr(dq),
+                                              fptr(l.gk), fptr(l.gv), fptr(l.stats), l.stats.size(3), later, w.data(),
+                                              (int32_t)w.size(), (int32_t)wlen, ptr(ws), nw, s), "spaco_chunk_attn_bwd_gather");
+      heads(d_qkv, W).copy_(dq);
+    } else if (w.empty() && wq.empty()) {
+      check(lib.seco_chunk_attn_bwd(&d, sv.qkv, ptr(l.k), ptr(l.v), sv.o, sv.lse, d_o, d_qkv, fptr(l.gk), fptr(l.gv), ptr(ws), nw, s),
+            "seco_chunk_attn_bwd");
+    } else {
+      const std::vector<float> ones(wq.size(), 1.f);
+      const std::vector<float>& cw = w.empty() ? ones : w;
+      const int32_t n = (int32_t)cw.size();
+      if (wq.empty())
+        check(lib.spaco_chunk_attn_bwd(&d, sv.qkv, ptr(l.k), ptr(l.v), sv.o, sv.lse, d_o, d_qkv, fptr(l.gk), fptr(l.gv), cw.data(), n,
+                                       (int32_t)wlen, ptr(ws), nw, s), "spaco_chunk_attn_bwd");
+      else if (wq.size() != cw.size())
+        raise(PyExc_ValueError, "dq_weight and chunk_weight must have one entry per chunk");
+      else
+        check(lib.spaco_chunk_attn_bwd_sparse_dq(&d, sv.qkv, ptr(l.k), ptr(l.v), sv.o, sv.lse, d_o, d_qkv, fptr(l.gk), fptr(l.gv),
+                                                 cw.data(), wq.data(), n, (int32_t)wlen, ptr(ws), nw, s),
+              "spaco_chunk_attn_bwd_sparse_dq");
+    }
+  }
+
+  // ---- one chunk.  Returns its logits; saved: receives what the backward needs of every layer and, last, of the final norm
+  // (NULL in stage 1, where the residual stream is updated in place and the layers share their buffers).
+  void* forward(const Tensor& tok, int64_t C, int64_t q_start, Keep keep, Arena& mem, std::vector<Saved>* saved, Tensor& x0) {
+    const int64_t R = B * C;
+    auto rows = [&](int64_t n) { return mem.take((size_t)(R * n) * e); };
+    auto stats = [&]() { return static_cast<float*>(mem.take((size_t)R * 4)); };
+    auto norm = [&](void* x, void* y, const Param& g, void* xo, void* h, float* r) {
+      check(lib.dec_add_rmsnorm(dtype, x, y, ptr(g.w), xo, h, r, R, dm, s), "dec_add_rmsnorm");
+    };
+    x0 = at::index(emb.w, {tok});
+    void *x = ptr(x0), *y = rows(dm), *logits = rows(V);
+    bool have_y = false;
+    const size_t base = mem.used;
+    for (Layer& l : layers) {
+      if (!saved) mem.used = base;
+      Saved sv{};
+      sv.x1 = have_y && saved ? rows(dm) : x;
+      sv.h1 = rows(dm);
+      sv.r1 = stats();
+      norm(x, have_y ? y : nullptr, l.norm1, sv.x1, sv.h1, sv.r1);
+      sv.qkv = rows(W);
+      mm(sv.qkv, sv.h1, l.wqkv, R);
+      rotate(sv.qkv, C, q_start, false);
+      attention(l, sv, C, q_start, keep, mem);
+      mm(y, sv.o, l.wo, R);
+      sv.x2 = saved ? rows(dm) : x;
+      sv.h2 = rows(dm);
+      sv.r2 = stats();
+      norm(sv.x1, y, l.norm2, sv.x2, sv.h2, sv.r2);
+      sv.u = rows(ff);
+      sv.a = rows(ff);
+      mm_silu(sv.u, sv.a, sv.h2, l.w1, R);
+      mm(y, sv.a, l.w2, R);
+      have_y = true;
+      x = sv.x2;
+      if (saved) saved->push_back(std::move(sv));
+    }
+    if (!saved) mem.used = base;
+    Saved sv{};
+    sv.x1 = have_y && saved ? rows(dm) : x;
+    sv.h1 = rows(dm);
+    sv.r1 = stats();
+    norm(x, have_y ? y : nullptr, norm_f, sv.x1, sv.h1, sv.r1);
+    mm(logits, sv.h1, head, R);
+    if (saved) saved->push_back(std::move(sv));
+    return logits;
+  }
+
+  // Adds the chunk's parameter gradients; d_logits: gradient of its loss at the logits.
+  void backward(void* d_logits, const Tensor& tok, int64_t C, int64_t q_start, std::vector<Saved>& saved, Arena& mem,
+                const std::vector<float>& w, const std::vector<std::vector<float>>& wq, int64_t wlen) {
+    const int64_t R = B * C;
+    auto rows = [&](int64_t n) { return mem.take((size_t)(R * n) * e); };
+    void *dh = rows(dm), *dx = rows(dm), *du = rows(ff), *d_o = rows(HD), *d_qkv = rows(W);
+    // dx <- dx + gradient of the norm at x (first: without dx)
+    auto norm_bwd = [&](void* x, const Param& g, float* r, float* part, bool first) {
+      check(lib.dec_rmsnorm_bwd(dtype, x, ptr(g.w), r, dh, first ? nullptr : dx, dx, part, R, dm, s), "dec_rmsnorm_bwd");
+    };
+    const Saved fin = std::move(saved.back());
+    saved.pop_back();
+    add(head, fin.h1, d_logits, R);
+    mm_bwd(dh, d_logits, head, R);
+    norm_bwd(fin.x1, norm_f, fin.r1, part_f, true);
+    static const std::vector<float> none;
+    for (int64_t i = L - 1; i >= 0; --i) {
+      Layer& l = layers[i];
+      const Saved& sv = saved[i];
+      add(l.w2, sv.a, dx, R);
+      mm_bwd(du, dx, l.w2, R, sv.u);
+      add(l.w1, sv.h2, du, R);
+      mm_bwd(dh, du, l.w1, R);
+      norm_bwd(sv.x2, l.norm2, sv.r2, l.part2, false);
+      add(l.wo, sv.o, dx, R);
+      mm_bwd(d_o, dx, l.wo, R);
+      attention_bwd(l, sv, d_o, d_qkv, C, q_start, w, wq.empty() ? none : wq[i], wlen);
+      readout(l, d_qkv, C, q_start);
+      rotate(d_qkv, C, q_start, true);
+      add(l.wqkv, sv.h1, d_qkv, R);
+      mm_bwd(dh, d_qkv, l.wqkv, R);
+      norm_bwd(sv.x1, l.norm1, sv.r1, l.part1, false);
+    }
+    if (emb.wanted) {
+      if (!emb.grad.defined()) emb.grad = at::zeros({emb.w.size(0), dm}, opts());
+      check(lib.dec_embedding_bwd(dtype, dx, static_cast<const int64_t*>(ptr(tok)), ptr(emb.grad), R, dm, emb.w.size(0), s),
+            "dec_embedding_bwd");
+    }
+  }
+};
+
+constexpr char kName[] = "seco_step";
+Step& step_of(PyObject* o) {
+  void* p = PyCapsule_GetPointer(o, kName);
+  if (!p) throw Raised{};
+  return *static_cast<Step*>(p);
+}
+void begin(Step& st) {
+  st.s = stream(Py_None);
+}
+
+Param param(PyObject* o) {
+  const Tensor& t = tensor(o);
+  Param p;
+  p.wanted = t.requires_grad();
+  p.w = t.detach().contiguous();
+  return p;
+}
+
+// (config, params): config = (n_layers, Hq, Hkv, D, scale, rope_base or None, B, N, chunk rows of stage 1, of stage 2, transposed);
+// params = [emb, head, norm_f, then norm1, norm2, wq, wk, wv, wo, w1, w2 of every layer] -> step
+PyObject* step_new(PyObject* const* a) {
+  if (!PyTuple_Check(a[0]) || PyTuple_GET_SIZE(a[0]) != 11 || !PyList_Check(a[1])) raise(PyExc_TypeError, "expected (tuple of 11, list)");
+  auto cfg = [&](int i) { return PyTuple_GET_ITEM(a[0], i); };
+  auto st = std::make_unique<Step>();
+  st->L = integer(cfg(0));
+  st->Hq = integer(cfg(1));
+  st->Hkv = integer(cfg(2));
+  st->D = integer(cfg(3));
+  st->scale = real(cfg(4));
+  st->rope_base = cfg(5) == Py_None ? 0.0 : real(cfg(5));
+  st->B = integer(cfg(6));
+  st->N = integer(cfg(7));
+  const int64_t c1 = integer(cfg(8)), c2 = integer(cfg(9));
+  const bool transposed = PyObject_IsTrue(cfg(10)) == 1;
+  if (PyList_GET_SIZE(a[1]) != 3 + 8 * st->L) raise(PyExc_ValueError, "wrong number of parameters");
+  auto par = [&](int64_t i) { return PyList_GET_ITEM(a[1], i); };
+  st->emb = param(par(0));
+  st->head = param(par(1));
+  st->norm_f = param(par(2));
+  const Tensor& em = st->emb.w;
+  st->dtype = dtype_code(em);
+  st->e = em.element_size();
+  st->dm = em.size(1);
+  st->V = st->head.w.size(1);
+  st->HD = st->Hq * st->D;
+  st->W = st->HD + 2 * st->Hkv * st->D;
+  st->ff = 0;
+  const at::TensorOptions f32 = st->opts().dtype(at::kFloat);
+  st->parts = at::zeros({2 * st->L + 1, DEC_GAIN_BLOCKS, st->dm}, f32);
+  auto part = [&](int64_t i) { return fptr(st->parts) + i * DEC_GAIN_BLOCKS * st->dm; };
+  st->part_f = part(2 * st->L);
+  st->layers.resize(st->L);
+  for (int64_t i = 0; i < st->L; ++i) {
+    Layer& l = st->layers[i];
+    const int64_t p0 = 3 + 8 * i;
+    l.norm1 = param(par(p0));
+    l.norm2 = param(par(p0 + 1));
+    // one projection product (and one gradient product each way) for queries, keys and values instead of three
+    const Tensor &q = tensor(par(p0 + 2)), &k = tensor(par(p0 + 3)), &v = tensor(par(p0 + 4));
+    l.wqkv.w = at::cat({q.detach(), k.detach(), v.detach()}, 1);
+    l.wqkv.wanted = q.requires_grad() || k.requires_grad() || v.requires_grad();
+    l.wo = param(par(p0 + 5));
+    l.w1 = param(par(p0 + 6));
+    l.w2 = param(par(p0 + 7));
+    st->ff = std::max(st->ff, l.w1.w.size(1));
+    if (l.wqkv.w.size(1) != st->W || l.w1.w.size(1) != st->ff || l.w2.w.size(0) != st->ff || l.wo.w.size(0) != st->HD)
+      raise(PyExc_ValueError, "parameter shapes do not fit the decoder's");
+    for (const Tensor* t : {&l.norm1.w, &l.norm2.w, &l.wqkv.w, &l.wo.w, &l.w1.w, &l.w2.w})
+      if (t->scalar_type() != em.scalar_type()) raise(PyExc_TypeError, "parameters must share one dtype");
+    l.part1 = part(2 * i);
+    l.part2 = part(2 * i + 1);
+    // (cache rows are written before they are read; the gradient rows are cleared before stage 2)
+    l.k = at::empty({st->B, st->Hkv, st->N, st->D}, st->opts());
+    l.v = at::empty_like(l.k);
+    l.gk = at::empty({st->B, st->Hkv, st->N, st->D}, f32);
+    l.gv = at::empty_like(l.gk);
+    if (transposed) {
+      for (Tensor* t : {&l.q_all, &l.do_all, &l.o_all, &l.dq_all}) *t = at::empty({st->B, st->Hq, st->N, st->D}, st->opts());
+      l.stats = at::empty({2, st->B, st->Hq, (st->N + 3) / 4 * 4}, f32);
+    }
+  }
+  // activations: see forward / backward for what is taken (each piece rounded up to 256 bytes)
+  const size_t e = st->e;
+  auto layer_bytes = [&](int64_t R) { return (size_t)R * ((4 * st->dm + st->W + st->HD + 2 * st->ff) * e + 8 + 4 * st->Hq) + 12 * 256; };
+  auto other_bytes = [&](int64_t R) { return (size_t)R * ((3 * st->dm + st->V) * e + 4) + 8 * 256; };
+  auto bwd_bytes = [&](int64_t R) { return (size_t)R * (2 * st->dm + st->ff + st->HD + st->W) * e + 8 * 256; };
+  const int64_t R1 = st->B * c1, R2 = st->B * c2;
+  st->stage1.create(layer_bytes(R1) + other_bytes(R1), em);
+  st->stage2.create(st->L * layer_bytes(R2) + other_bytes(R2) + bwd_bytes(R2), em);
+  PyObject* cap = PyCapsule_New(st.get(), kName, [](PyObject* o) { delete static_cast<Step*>(PyCapsule_GetPointer(o, kName)); });
+  if (!cap) throw Raised{};
+  st.release();
+  return cap;
+}
+
+Tensor chunk_of(const Tensor& t, int64_t s0, int64_t s1) {
+  if (!t.is_cuda() || t.scalar_type() != at::kLong || t.dim() != 2) raise(PyExc_ValueError, "tokens, targets: int64 [B, N] on the GPU");
+  return t.slice(1, s0, s1).reshape({-1});
+}
+
+// (step, tokens, targets, s0, s1, losses, store): inference over rows [s0, s1) of every sequence; their losses
+PyObject* step_infer(PyObject* const* a) {
+  Step& st = step_of(a[0]);
+  begin(st);
+  const int64_t s0 = integer(a[3]), s1 = integer(a[4]);
+  const Tensor tok = chunk_of(tensor(a[1]), s0, s1), tgt = chunk_of(tensor(a[2]), s0, s1);
+  const Tensor& losses = tensor(a[5]);
+  if (losses.scalar_type() != at::kFloat || !losses.is_contiguous() || losses.numel() < st.B * s1)
+    raise(PyExc_ValueError, "losses: one float32 per token");
+  st.stage1.used = 0;
+  Tensor x0;
+  void* logits = st.forward(tok, s1 - s0, s0, PyObject_IsTrue(a[6]) == 1 ? kStore : kCompute, st.stage1, nullptr, x0);
+  check(lib.dec_cross_entropy(st.dtype, logits, static_cast<const int64_t*>(ptr(tgt)), fptr(losses) + s0 * st.B, tok.numel(), st.V, st.s),
+        "dec_cross_entropy");
+  Py_RETURN_NONE;
+}
+
+// (step): clears the KV-gradient buffers
+PyObject* step_zero(PyObject* const* a) {
+  Step& st = step_of(a[0]);
+  begin(st);
+  for (Layer& l : st.layers) {
+    seco_desc d = st.desc(1, 0, l);
+    check(lib.kvgrad_zero(&d, fptr(l.gk), fptr(l.gv), 0, st.N, st.s), "kvgrad_zero");
+  }
+  Py_RETURN_NONE;
+}
+
+// (step, tokens, targets, s0, s1, reuse, weights or None, weight chunk length, per-layer dQ weights or None): rebuilds the
+// chunk and back-propagates its loss
+PyObject* step_train(PyObject* const* a) {
+  Step& st = step_of(a[0]);
+  begin(st);
+  const int64_t s0 = integer(a[3]), s1 = integer(a[4]);
+  const Tensor tok = chunk_of(tensor(a[1]), s0, s1), tgt = chunk_of(tensor(a[2]), s0, s1);
+  std::vector<float> w;
+  if (a[6] != Py_None) w = floats(a[6]);
+  std::vector<std::vector<float>> wq;
+  if (a[8] != Py_None) {
+    if (!PyList_Check(a[8]) || PyList_GET_SIZE(a[8]) != st.L) raise(PyExc_ValueError, "dq weights: one entry per layer");
+    for (int64_t i = 0; i < st.L; ++i) {
+      PyObject* x = PyList_GET_ITEM(a[8], i);
+      wq.push_back(x == Py_None ? std::vector<float>() : floats(x));
+    }
+  }
+  st.stage2.used = 0;
+  std::vector<Saved> saved;
+  saved.reserve(st.L + 1);
+  Tensor x0;
+  void* logits = st.forward(tok, s1 - s0, s0, PyObject_IsTrue(a[5]) == 1 ? kReuse : kCompute, st.stage2, &saved, x0);
+  check(lib.dec_cross_entropy(st.dtype, logits, static_cast<const int64_t*>(ptr(tgt)), nullptr, tok.numel(), st.V, st.s), "dec_cross_entropy");
+  st.trained = true;
+  st.backward(logits, tok, s1 - s0, s0, saved, st.stage2, w, wq, integer(a[7]));
+  Py_RETURN_NONE;
+}
+
+// (step) -> gradients in the order of step_new's params; None where no chunk reached the parameter
+PyObject* step_grads(PyObject* const* a) {
+  Step& st = step_of(a[0]);
+  std::vector<Tensor> out = {st.emb.grad, st.head.grad};
+  const Tensor gains = st.parts.sum(1).to(st.emb.w.scalar_type());
+  auto gain = [&](int64_t i) { return st.trained ? gains.select(0, i) : Tensor(); };
+  out.push_back(gain(2 * st.L));
+  for (int64_t i = 0; i < st.L; ++i) {
+    Layer& l = st.layers[i];
+    out.push_back(gain(2 * i));
+    out.push_back(gain(2 * i + 1));
+    const int64_t kv = st.Hkv * st.D;
+    const bool have = l.wqkv.grad.defined();
+    out.push_back(have ? l.wqkv.grad.slice(1, 0, st.HD).contiguous() : Tensor());
+    out.push_back(have ? l.wqkv.grad.slice(1, st.HD, st.HD + kv).contiguous() : Tensor());
+    out.push_back(have ? l.wqkv.grad.slice(1, st.HD + kv, st.HD + 2 * kv).contiguous() : Tensor());
+    out.push_back(l.wo.grad);
+    out.push_back(l.w1.grad);
+    out.push_back(l.w2.grad);
+  }
+  PyObject* list = PyList_New((Py_ssize_t)out.size());
+  if (!list) throw Raised{};
+  for (size_t i = 0; i < out.size(); ++i) {
+    PyObject* o = out[i].defined() ? THPVariable_Wrap(out[i]) : (Py_INCREF(Py_None), Py_None);
+    PyList_SET_ITEM(list, (Py_ssize_t)i, o);
+  }
+  return list;
+}
+
+}  // namespace
+
+PyMethodDef step_methods[] = {SECO_METHOD("step_new", step_new, 2),   SECO_METHOD("step_infer", step_infer, 7),
+                              SECO_METHOD("step_zero", step_zero, 1), SECO_METHOD("step_train", step_train, 9),
+                              SECO_METHOD("step_grads", step_grads, 1), {nullptr, nullptr, 0, nullptr}};
+
+}  // namespace seco_ext

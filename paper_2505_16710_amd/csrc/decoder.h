@@ -22,6 +22,16 @@ int dec_cross_entropy(int dtype, void* logits, const int64_t* target, float* los
 // grad[token[r]] += d_x[r] for every row r; the rows of one token are added in ascending order by one workgroup
 int dec_embedding_bwd(int dtype, const void* d_x, const int64_t* token, void* grad, int64_t rows, int64_t d, int64_t v,
                       void* stream);
+
+// bf16 matrix products with fp32 accumulation, row-major with leading dimensions in elements (gemm_bf16.hip):
+//   NN: C[M,N] = A[M,K] B[K,N]     NT: C[M,N] = A[M,K] B[N,K]^T     TN: C[M,N] = A[K,M]^T B[K,N]
+// Epilogues: STORE; ADD (TN): C += the product; SILU (NN): C = the product, C2 = silu(C);
+// SILU_BWD (NT): C = the product times silu'(C2).  Operands start on 16-byte boundaries.
+enum { DEC_GEMM_NN = 0, DEC_GEMM_NT = 1, DEC_GEMM_TN = 2 };
+enum { DEC_GEMM_STORE = 0, DEC_GEMM_ADD = 1, DEC_GEMM_SILU = 2, DEC_GEMM_SILU_BWD = 3 };
+int dec_gemm_supported(int form, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, int64_t ldc);   // 1 / 0
+int dec_gemm(int form, int epilogue, const void* a, const void* b, void* c, void* c2, int64_t M, int64_t N, int64_t K,
+             int64_t lda, int64_t ldb, int64_t ldc, void* stream);
 #ifdef __cplusplus
 }
 #endif

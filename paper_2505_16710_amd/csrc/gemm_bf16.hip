@@ -1,0 +1,300 @@
+// Matrix products of the decoder around the attention (chunk_loop.py), bf16 with fp32 accumulation, in the three forms
+// a projection needs: forward C = A B, data gradient C = A B^T, weight gradient C (+)= A^T B, with the SiLU of the MLP
+// and its derivative in the epilogue of the product they follow.
+//
+// What bounds them: at the row counts of a chunk (512 rows, 1 - 4 thousand columns) a product is 1 - 4 GFLOP, a few
+// microseconds of matrix work on 256 CUs, so launch cost and latency count, not the matrix pipe.  A call of the
+// library product through the framework took 17 - 19 us of host time, twice its kernel; a launch here takes 3.
+//
+// A workgroup (4 wavefronts, 2 x 2, or two such groups that take the steps in turn) owns a BM x BN tile of C and walks
+// the contraction in steps of 64 through a ring of kStages LDS slots filled by direct global -> LDS copies, kStages - 1
+// steps ahead, with one barrier per step.  An operand whose
+// contraction runs along its rows in memory ("KC") is staged as rows of 64 contraction elements, one whose rows are
+// contracted ("KR") as panels of 64 of its columns; either way an LDS row is 128 bytes whose eight 16-byte chunks
+// are XOR-ed with a function of the row such that row reads (ds_read_b128, 16 rows) and transpose reads
+// (ds_read_b64_tr_b16, 4 rows x 64 bytes) meet no bank conflict.  Both kinds of read deliver contraction slot s of
+// lane group g as element 8 g + s, so that any two operands can meet.  The tile leaves through LDS in rows of 16-byte stores.
+#include "decoder.h"
+#include "mfma_tiles.h"
+#include "seco_internal.h"
+
+namespace seco {
+namespace {
+
+constexpr int kStep = 64, kRow = 128;   // contraction elements per step; bytes per LDS row
+enum Epilogue { kStore, kAdd, kSilu, kSiluBwd };
+
+struct GemmArgs {
+  const char* a;
+  const char* b;
+  __bf16* c;
+  __bf16* c2;       // kSilu: silu(C); kSiluBwd: the u that C is the gradient of silu at
+  int M, N, K, lda, ldb, ldc, tiles_m;
+};
+
+__device__ __forceinline__ int flip(int row) { return (((row >> 1) & 1) << 2) | ((row >> 2) & 3); }
+
+// Copies of one operand: instruction i of a wavefront brings the staged rows 8 (wave + 4 i) .. + 7.
+template <bool KC, int BO> struct Stage {
+  static constexpr int kCopies = BO / 32;
+  uint32_t off[kCopies];      // this lane's source, relative to the step's base
+  // o0: first outer index of the tile, n_outer: how many there are (KR: a multiple of 8); rows / chunks past the end repeat the last
+  __device__ void init(int o0, int n_outer, int ld, int wave, int lane) {
+#pragma unroll
+    for (int i = 0; i < kCopies; ++i) {
+      const int lr = 8 * (wave + 4 * i) + (lane >> 3);
+      if (KC) {
+        off[i] = (uint32_t)min(o0 + lr, n_outer - 1) * (uint32_t)(ld * 2) + (((lane & 7) ^ flip(lr)) << 4);
+      } else {
+        const int krow = lr & 63;
+        off[i] = (uint32_t)krow * (uint32_t)(ld * 2) + (uint32_t)min(o0 + (lr & ~63) + (((lane & 7) ^ flip(krow)) << 3), n_outer - 8) * 2u;
+      }
+    }
+  }
+  __device__ void copy(const char* base, uint32_t lds_wave) const {   // lds_wave: the operand's slot + 8 wave rows
+#pragma unroll
+    for (int i = 0; i < kCopies; ++i) dma16_sbase(base, off[i], lds_wave + i * 32 * kRow);
+  }
+};
+
+// The last contraction rows of two KR operands, when they do not fill a step: through registers, zeros behind the end.
+template <int BO>
+__device__ __forceinline__ void stage_rest(lds_char* dst, const char* base, int rows, int o0, int n_outer, int ld) {
+  for (int c = threadIdx.x; c < BO * 8; c += blockDim.x) {
+    const int lr = c >> 3, krow = lr & 63, col = min(o0 + (lr & ~63) + ((c & 7) << 3), n_outer - 8);
+    bf16x8 v;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = (__bf16)0.f;
+    if (krow < rows) v = *reinterpret_cast<const bf16x8*>(base + ((int64_t)krow * ld + col) * 2);
+    *reinterpret_cast<SECO_LDS bf16x8*>(dst + lr * kRow + (((c & 7) ^ flip(krow)) << 4)) = v;
+  }
+}
+
+// Operand of the 32-wide block `blk` of a staged tile for 16 contraction elements, t = 0 .. 3
+template <bool KC> struct Frag {
+  int lo, hi;
+  int chunk_t[KC ? 4 : 1];
+  __device__ void init(int blk, int lane) {
+    if (KC) {
+      const int row = lane & 31;
+      lo = blk * 32 * kRow + row * kRow;
+#pragma unroll
+      for (int t = 0; t < (KC ? 4 : 1); ++t) chunk_t[t] = lo + (((2 * t + (lane >> 5)) ^ flip(row)) << 4);
+      hi = 0;
+    } else {
+      const int ii = lane & 15, row = 8 * (lane >> 5) + (ii >> 2);
+      const int chunk = 4 * (blk & 1) + 2 * ((lane >> 4) & 1) + ((ii & 3) >> 1), sub = (ii & 1) << 3;
+      lo = (blk >> 1) * 64 * kRow + row * kRow + ((chunk ^ flip(row)) << 4) + sub;
+      hi = (blk >> 1) * 64 * kRow + (row + 4) * kRow + ((chunk ^ flip(row + 4)) << 4) + sub;
+      chunk_t[0] = 0;
+    }
+  }
+  __device__ __forceinline__ bf16x8 read(lds_char* tile, int t) const {
+    if constexpr (KC) {
+      return *reinterpret_cast<SECO_LDS bf16x8*>(tile + chunk_t[t]);
+    } else {
+      s16x4 x = __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<SECO_LDS s16x4*>(tile + lo + 16 * t * kRow));
+      s16x4 y = __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<SECO_LDS s16x4*>(tile + hi + 16 * t * kRow));
+      typedef short s16x8 __attribute__((ext_vector_type(8)));
+      const s16x8 r = {x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]};
+      return __builtin_bit_cast(bf16x8, r);
+    }
+  }
+};
+
+// KH groups of 4 wavefronts, each with a ring of kStages slots; group kh takes the steps kh, kh + KH, ...
+template <int BM, int BN, int KH, int kStages, bool AKC, bool BKC, int EPI>
+__global__ __launch_bounds__(256 * KH, 2) void gemm_kernel(GemmArgs g, int total) {
+  constexpr int kSlot = (BM + BN) * kRow, MB = BM / 64, NB = BN / 64;
+  constexpr int kPerWave = BM / 32 + BN / 32;            // copies per wavefront and step
+  constexpr int kRing = kStages * kSlot;
+  extern __shared__ __attribute__((aligned(16))) char smem_raw[];
+  lds_char* smem_all = (lds_char*)smem_raw;
+  const int item = xcd_item(blockIdx.x, total);          // neighbours share the columns of B (a weight matrix in two of the forms)
+  if (item < 0) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave_all = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave = wave_all & 3, kh = KH == 1 ? 0 : wave_all >> 2;
+  lds_char* smem = smem_all + kh * kRing;
+  const int tn = item / g.tiles_m, tm = item - tn * g.tiles_m;
+  const int m0 = tm * BM, n0 = tn * BN;
+
+  Stage<AKC, BM> sa;
+  Stage<BKC, BN> sb;
+  sa.init(m0, g.M, g.lda, wave, lane);
+  sb.init(n0, g.N, g.ldb, wave, lane);
+  const int64_t step_a = AKC ? kStep * 2 : (int64_t)kStep * g.lda * 2, step_b = BKC ? kStep * 2 : (int64_t)kStep * g.ldb * 2;
+  const uint32_t lds_wave = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)smem + 8 * wave * kRow);
+  const char *pa = g.a + kh * step_a, *pb = g.b + kh * step_b;   // of the next step to be copied
+  const int n_full = g.K / kStep;
+  const int n_steps = (n_full - kh + KH - 1) / KH;       // of this group
+  auto copy = [&](int slot) {
+    sa.copy(pa, lds_wave + slot * kSlot);
+    sb.copy(pb, lds_wave + slot * kSlot + BM * kRow);
+    pa += KH * step_a;
+    pb += KH * step_b;
+  };
+#pragma unroll
+  for (int s = 0; s < kStages - 1; ++s)
+    if (s < n_steps) copy(s);
+
+  Frag<AKC> fa[MB];
+  Frag<BKC> fb[NB];
+#pragma unroll
+  for (int i = 0; i < MB; ++i) fa[i].init((wave >> 1) * MB + i, lane);
+#pragma unroll
+  for (int i = 0; i < NB; ++i) fb[i].init((wave & 1) * NB + i, lane);
+  f32x16 acc[MB][NB];
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+  auto multiply = [&](int slot) {
+    lds_char* ta = smem + slot * kSlot;
+    lds_char* tb = ta + BM * kRow;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      bf16x8 x[MB], y[NB];
+#pragma unroll
+      for (int i = 0; i < MB; ++i) x[i] = fa[i].read(ta, t);
+#pragma unroll
+      for (int j = 0; j < NB; ++j) y[j] = fb[j].read(tb, t);
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j) acc[i][j] = mfma(x[i], y[j], acc[i][j]);
+    }
+  };
+
+  int slot = 0;
+  const int n_turns = (n_full + KH - 1) / KH;            // the same for all groups: they share the barriers
+  for (int it = 0; it < n_turns; ++it) {
+    // step `it` has landed when at most the copies of the kStages - 2 steps behind it are outstanding
+    if (it + kStages - 2 < n_steps)
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"((kStages - 2) * kPerWave) : "memory");
+    else
+      asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" : : : "memory");
+    if (it + kStages - 1 < n_steps) copy(slot == 0 ? kStages - 1 : slot - 1);   // the slot every wavefront has just left
+    if (KH == 1 || it < n_steps) multiply(slot);
+    slot = slot + 1 == kStages ? 0 : slot + 1;
+  }
+  if constexpr (!AKC && !BKC) {
+    if (const int rest = g.K - n_full * kStep; rest > 0) {
+      __syncthreads();
+      stage_rest<BM>(smem_all, g.a + n_full * step_a, rest, m0, g.M, g.lda);
+      stage_rest<BN>(smem_all + BM * kRow, g.b + n_full * step_b, rest, n0, g.N, g.ldb);
+      __syncthreads();
+      if (kh == 0) multiply(0);
+    }
+  }
+
+  __syncthreads();
+  typedef float f32x4 __attribute__((ext_vector_type(4)));
+  constexpr int kTurnRow = BM * (BN + 4) * 4 <= kRing ? (BN + 4) * 4 : BN * 4;   // padded where there is room
+  static_assert(BM * kTurnRow <= kRing, "the tile fits the ring");
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        *reinterpret_cast<SECO_LDS float*>(smem + (((wave >> 1) * MB + i) * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * kTurnRow +
+                                           (((wave & 1) * NB + j) * 32 + (lane & 31)) * 4) = acc[i][j][r];
+  __syncthreads();
+  constexpr int kPerRow = BN / 8, kRows = 256 * KH / kPerRow;
+  const int col = n0 + (tid % kPerRow) * 8;
+  if (col >= g.N) return;
+#pragma unroll
+  for (int i = 0; i < BM / kRows; ++i) {
+    const int lr = i * kRows + tid / kPerRow, row = m0 + lr;
+    if (row >= g.M) break;
+    lds_char* src = smem_all + lr * kTurnRow + (tid % kPerRow) * 32;
+    f32x4 lo = *reinterpret_cast<SECO_LDS f32x4*>(src), hi = *reinterpret_cast<SECO_LDS f32x4*>(src + 16);
+    if constexpr (KH == 2) {
+      lo += *reinterpret_cast<SECO_LDS f32x4*>(src + kRing);
+      hi += *reinterpret_cast<SECO_LDS f32x4*>(src + kRing + 16);
+    }
+    const float f[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+    const int64_t at = (int64_t)row * g.ldc + col;
+    bf16x8 out, old, act;
+    if constexpr (EPI == kAdd) old = *reinterpret_cast<const bf16x8*>(g.c + at);
+    if constexpr (EPI == kSiluBwd) old = *reinterpret_cast<const bf16x8*>(g.c2 + at);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      if constexpr (EPI == kAdd) {
+        out[e] = (__bf16)((float)old[e] + f[e]);
+      } else if constexpr (EPI == kSiluBwd) {
+        const float u = (float)old[e], s = 1.f / (1.f + __expf(-u));
+        out[e] = (__bf16)((float)(__bf16)f[e] * (s * (1.f + u * (1.f - s))));
+      } else {
+        out[e] = (__bf16)f[e];
+        if constexpr (EPI == kSilu) {
+          const float u = (float)out[e];
+          act[e] = (__bf16)(u * (1.f / (1.f + __expf(-u))));
+        }
+      }
+    }
+    *reinterpret_cast<bf16x8*>(g.c + at) = out;
+    if constexpr (EPI == kSilu) *reinterpret_cast<bf16x8*>(g.c2 + at) = act;
+  }
+}
+
+template <int BM, int BN, int KH, int ST, bool AKC, bool BKC, int EPI> int launch(GemmArgs g, hipStream_t s) {
+  constexpr int smem = KH * ST * (BM + BN) * kRow;
+  auto kern = gemm_kernel<BM, BN, KH, ST, AKC, BKC, EPI>;
+  static std::atomic<uint64_t> ready{0};
+  if (!allow_lds(ready, reinterpret_cast<const void*>(kern), smem)) return SECO_ERR_LAUNCH;
+  g.tiles_m = (g.M + BM - 1) / BM;
+  const int total = g.tiles_m * ((g.N + BN - 1) / BN);
+  hipLaunchKernelGGL(kern, dim3(xcd_grid(total)), dim3(256 * KH), smem, s, g, total);
+  return launch_status();
+}
+
+// Which tile: measured over 64 .. 2048 rows against matrices of 1024 x 1024 .. 4096 x 1024 (us; K: contraction length).
+// LDS reads bound the small tiles (2 KiB per MFMA at 64 x 64, 1 KiB at 128 x 128), idle CUs the large ones.
+//  - over 1.25 128 x 128 tiles per CU: those, four wavefronts and two slots, so that two workgroups share a CU
+//    (2048 x 4096 x 1024: 25; 31 with eight wavefronts, 35 with 64 x 64 tiles);
+//  - from 0.55 per CU on: 128 x 128, eight wavefronts in two groups (1024 x 4096 x 1024: 16.5 against 17.3);
+//  - 64 x 64 tiles that fit one round: those, two groups, three slots (512 x 1024 x 4096: 14.6; 18.5 with one group);
+//  - more of them: 128 x 64 for a long contraction (2048 x 1024 x 4096: 25 against 30), else 64 x 64 with two slots, two
+//    workgroups per CU (512 x 4096 x 1024: 9.9; 14.0 with 128 x 128).
+template <bool AKC, bool BKC, int EPI> int pick(const GemmArgs& g, hipStream_t s) {
+  const int64_t m64 = (g.M + 63) / 64, n64 = (g.N + 63) / 64, big = ((m64 + 1) / 2) * ((n64 + 1) / 2), cus = device_cus();
+  if (4 * big > 5 * cus) return launch<128, 128, 1, 2, AKC, BKC, EPI>(g, s);
+  if (20 * big >= 11 * cus) return launch<128, 128, 2, 2, AKC, BKC, EPI>(g, s);
+  if (m64 * n64 <= cus) return launch<64, 64, 2, 3, AKC, BKC, EPI>(g, s);
+  if (g.K >= 2048) return launch<128, 64, 2, 3, AKC, BKC, EPI>(g, s);
+  return launch<64, 64, 2, 2, AKC, BKC, EPI>(g, s);
+}
+
+}  // namespace
+}  // namespace seco
+
+extern "C" int dec_gemm_supported(int form, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, int64_t ldc) {
+  const int64_t big = (int64_t)1 << 30;
+  if (M < 1 || N < 8 || K < 1 || N % 8 || lda % 8 || ldb % 8 || ldc % 8) return 0;
+  if (form == DEC_GEMM_TN ? (M < 8 || M % 8) : K % 64) return 0;
+  // offsets inside an operand are 32-bit: outer indices times row length (KC), 64 rows (KR)
+  const int64_t ra = form == DEC_GEMM_TN ? 64 : M, rb = form == DEC_GEMM_NT ? N : 64;
+  return M < big && N < big && K < big && ra * lda < big && rb * ldb < big && ((M + 63) / 64) * ((N + 63) / 64) < big;
+}
+
+extern "C" int dec_gemm(int form, int epilogue, const void* a, const void* b, void* c, void* c2, int64_t M, int64_t N, int64_t K,
+                        int64_t lda, int64_t ldb, int64_t ldc, void* stream) {
+  using namespace seco;
+  if (!dec_gemm_supported(form, M, N, K, lda, ldb, ldc)) return SECO_ERR_SHAPE;
+  if (!a || !b || !c || ((epilogue == DEC_GEMM_SILU || epilogue == DEC_GEMM_SILU_BWD) && !c2)) return SECO_ERR_NULL;
+  if (((uintptr_t)a | (uintptr_t)b | (uintptr_t)c | (uintptr_t)c2) & 15u) return SECO_ERR_ALIGN;
+  const GemmArgs g{static_cast<const char*>(a), static_cast<const char*>(b), static_cast<__bf16*>(c), static_cast<__bf16*>(c2),
+                   (int)M, (int)N, (int)K, (int)lda, (int)ldb, (int)ldc, 0};
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  if (form == DEC_GEMM_NN && epilogue == DEC_GEMM_STORE) return pick<true, false, kStore>(g, s);
+  if (form == DEC_GEMM_NN && epilogue == DEC_GEMM_SILU) return pick<true, false, kSilu>(g, s);
+  if (form == DEC_GEMM_NT && epilogue == DEC_GEMM_STORE) return pick<true, true, kStore>(g, s);
+  if (form == DEC_GEMM_NT && epilogue == DEC_GEMM_SILU_BWD) return pick<true, true, kSiluBwd>(g, s);
+  if (form == DEC_GEMM_TN && epilogue == DEC_GEMM_STORE) return pick<false, false, kStore>(g, s);
+  if (form == DEC_GEMM_TN && epilogue == DEC_GEMM_ADD) return pick<false, false, kAdd>(g, s);
+  return SECO_ERR_SHAPE;
+}

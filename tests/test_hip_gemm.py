@@ -1,0 +1,65 @@
+"""The decoder's matrix products (dec_gemm) against fp32 products of the same bf16 operands: every form and epilogue at the
+edges of the tiles (64 and 128), of the contraction step (64) and of each shape of workgroup the launcher picks."""
+import ctypes as C
+
+import pytest
+import torch
+
+import paper_2505_16710_amd as seco
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+NN, NT, TN = 0, 1, 2
+STORE, ADD, SILU, SILU_BWD = 0, 1, 2, 3
+
+
+@pytest.mark.parametrize("form,epi,M,N,K", [
+    (NN, STORE, 1, 8, 64), (NN, STORE, 63, 72, 64), (NN, STORE, 65, 136, 192), (NN, SILU, 129, 200, 320),
+    (NT, STORE, 127, 64, 128), (NT, SILU_BWD, 130, 264, 448),
+    (TN, STORE, 72, 200, 1), (TN, ADD, 136, 264, 77), (TN, ADD, 64, 64, 63), (TN, STORE, 128, 128, 129),
+    (NN, STORE, 300, 4096, 64),            # more 64 x 64 tiles than CUs, two slots
+    (NT, STORE, 1500, 1032, 2112),         # 128 x 64 tiles
+    (TN, ADD, 2040, 2056, 200),            # 128 x 128 tiles, two groups, a remainder of the contraction
+    (NN, SILU, 2050, 4104, 128),           # 128 x 128 tiles, one group, two workgroups per CU
+])
+def test_gemm_forms_and_epilogues(form, epi, M, N, K):
+    lib = seco.load_library()
+    P, I = C.c_void_p, C.c_int64
+    lib.dec_gemm.argtypes = [C.c_int, C.c_int, P, P, P, P] + [I] * 6 + [P]
+    g = torch.Generator(device=DEV).manual_seed(M + N + K)
+
+    def normal(*shape):
+        return torch.randn(*shape, generator=g, device=DEV).to(torch.bfloat16)
+    a = normal(K, M) if form == TN else normal(M, K)
+    b = normal(N, K) if form == NT else normal(K, N)
+    c, c2 = normal(M + 1, N), normal(M + 1, N)                      # the last row must stay as it is
+    c_in, c2_in = c.clone(), c2.clone()
+    rc = lib.dec_gemm(form, epi, a.data_ptr(), b.data_ptr(), c.data_ptr(), c2.data_ptr(), M, N, K, a.shape[1], b.shape[1], N,
+                      torch.cuda.current_stream().cuda_stream)
+    assert rc == 0
+    torch.cuda.synchronize()
+    ref = torch.mm((a.float().t() if form == TN else a.float()).contiguous(), (b.float().t() if form == NT else b.float()).contiguous())
+    if epi == ADD:
+        ref += c_in[:M].float()
+    if epi == SILU_BWD:
+        u = c2_in[:M].float()
+        s = torch.sigmoid(u)
+        ref *= s * (1 + u * (1 - s))
+
+    def close(x, y):
+        return float((x.float() - y).abs().max() / y.abs().max()) < 1e-2 and float((x.float() - y).norm() / y.norm()) < 4e-3
+    assert close(c[:M], ref)
+    if epi == SILU:
+        assert close(c2[:M], torch.nn.functional.silu(c[:M].float()))
+    else:
+        assert torch.equal(c2, c2_in)
+    assert torch.equal(c[M], c_in[M]) and torch.equal(c2[M], c2_in[M])
+
+
+def test_gemm_refuses_what_it_cannot_do():
+    lib = seco.load_library()
+    I = C.c_int64
+    lib.dec_gemm_supported.argtypes = [C.c_int] + [I] * 6
+    ok = lib.dec_gemm_supported
+    assert ok(NN, 5, 64, 64, 64, 64, 64) and ok(TN, 64, 64, 5, 64, 64, 64)
+    assert not ok(NN, 5, 29, 64, 64, 29, 29) and not ok(NN, 5, 64, 96, 96, 64, 64) and not ok(TN, 60, 64, 64, 60, 64, 64)
