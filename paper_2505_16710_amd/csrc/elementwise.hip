@@ -63,44 +63,6 @@ __global__ __launch_bounds__(256) void kvgrad_kernel(float* __restrict__ dst_a, 
   });
 }
 
-__device__ inline float bf16_lo(uint32_t u) { return __uint_as_float(u << 16); }
-__device__ inline float bf16_hi(uint32_t u) { return __uint_as_float(u & 0xffff0000u); }
-
-// One wavefront per row; 16-byte loads; fp32 accumulation; cross-lane tree reduction.
-template <bool kBf16>
-__global__ __launch_bounds__(256) void delta_kernel(AttnParams p) {
-  const int lane = threadIdx.x & 63;
-  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int64_t nrows = (int64_t)p.B * p.Hq * p.C;
-  if (row >= nrows) return;
-  const int r = row % p.C;
-  const int h = (row / p.C) % p.Hq;
-  const int b = row / ((int64_t)p.C * p.Hq);
-  const int64_t off = b * p.os[0] + h * p.os[1] + (int64_t)r * p.os[2];
-  float acc = 0.f;
-  if (kBf16) {
-    const uint4* o = reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(p.o) + off);
-    const uint4* g = reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(p.d_o) + off);
-    for (int i = lane; i < p.D / 8; i += 64) {
-      const uint4 a = o[i], c = g[i];
-      acc += bf16_lo(a.x) * bf16_lo(c.x) + bf16_hi(a.x) * bf16_hi(c.x);
-      acc += bf16_lo(a.y) * bf16_lo(c.y) + bf16_hi(a.y) * bf16_hi(c.y);
-      acc += bf16_lo(a.z) * bf16_lo(c.z) + bf16_hi(a.z) * bf16_hi(c.z);
-      acc += bf16_lo(a.w) * bf16_lo(c.w) + bf16_hi(a.w) * bf16_hi(c.w);
-    }
-  } else {
-    const float4* o = reinterpret_cast<const float4*>(static_cast<const float*>(p.o) + off);
-    const float4* g = reinterpret_cast<const float4*>(static_cast<const float*>(p.d_o) + off);
-    for (int i = lane; i < p.D / 4; i += 64) {
-      const float4 a = o[i], c = g[i];
-      acc += a.x * c.x + a.y * c.y + a.z * c.z + a.w * c.w;
-    }
-  }
-#pragma unroll
-  for (int s = 32; s > 0; s >>= 1) acc += __shfl_xor(acc, s);
-  if (lane == 0) p.delta[row] = acc;
-}
-
 // Merge of the partial rows of the split kernels (n_splits <= 64 of 128 fp32 each).  GP groups of 32 threads (a thread:
 // 4 consecutive head_dim elements) share a row, each taking the splits sp = group, group + GP, .., at most 8 of them, so
 // that all its loads are in flight at once; the groups' sums meet in LDS and are added in group order (fixed order:
@@ -496,21 +458,5 @@ int launch_dq_merge(const AttnParams& p, hipStream_t s) {
   return launch_status();
 }
 #undef SECO_MERGE_LAUNCH
-
-int launch_delta(const AttnParams& p, int dtype, hipStream_t s) {
-  const int64_t nrows = (int64_t)p.B * p.Hq * p.C;
-  const unsigned blocks = (unsigned)((nrows + 3) / 4);
-  if (dtype == SECO_BF16)
-    {
-    ProfScope prof(kKernelDelta, s);
-    hipLaunchKernelGGL(delta_kernel<true>, dim3(blocks), dim3(256), 0, s, p);
-  }
-  else
-    {
-    ProfScope prof(kKernelDelta, s);
-    hipLaunchKernelGGL(delta_kernel<false>, dim3(blocks), dim3(256), 0, s, p);
-  }
-  return launch_status();
-}
 
 }  // namespace seco

@@ -194,6 +194,8 @@ int backward(const seco_desc* d, const void* q, const void* k, const void* v, co
   use_tail_part(p, d, ws_bytes);
   hipStream_t s = static_cast<hipStream_t>(stream);
   const bool bf16 = d->dtype == SECO_BF16;
+  F32Pending pending;
+  p.f32 = &pending;
   // delta = rowsum(dO * O): the bf16 dQ kernel computes it in its prologue (and stores it for the dK/dV kernel)
   if (!bf16 && (rc = launch_delta(p, d->dtype, s))) return rc;
   const SegTable* runs_arg = sparse_dq ? &dq_runs : nullptr;
@@ -234,7 +236,7 @@ int backward(const seco_desc* d, const void* q, const void* k, const void* v, co
     }
   }
   if ((rc = flush())) return rc;
-  return SECO_OK;
+  return pending.dq ? launch_dkdv_f32(p, seg, s) : SECO_OK;   // (fp32 without a cache row to cover: dQ alone)
 }
 
 

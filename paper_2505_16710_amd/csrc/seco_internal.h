@@ -6,6 +6,8 @@
 
 namespace seco {
 
+struct F32Pending;
+
 // Everything a kernel needs to know about one chunk call (validated by the host side).
 struct AttnParams {
   const void* q;
@@ -31,6 +33,7 @@ struct AttnParams {
   int B, Hq, Hkv, D, C, q_start, G;
   float scale;
   int64_t qs[3], os[3], kvs[3], gs[3];
+  F32Pending* f32;   // fp32 backward, host side: passes announced but not launched yet
 };
 
 // Column segments of the dK/dV pass: a run of cache rows that share one weight.
@@ -43,6 +46,12 @@ struct SegTable {
   int col_end[kMaxSegments];
   float weight[kMaxSegments];
   int tile_begin[kMaxSegments + 1];  // prefix sum of column tiles, in units of the launcher's tile width
+};
+
+// What launch_dq_f32 leaves for launch_dkdv_f32
+struct F32Pending {
+  bool dq = false;
+  SegTable runs;
 };
 
 // Runs of query rows of the dK/dV pass in the transposed order: rows [begin, end) relative to the call's first
@@ -206,7 +215,7 @@ int launch_dkdv_rows_bf16(const AttnParams& p, const SegTable& seg, const RowRun
 #endif
 constexpr int kColTileBf16 = SECO_DKDV_COLS;  // columns per workgroup in launch_dkdv_bf16
 
-// delta[r] = sum_d dO[r,d] * O[r,d]
+// announces delta[r] = sum_d dO[r,d] * O[r,d] of the fp32 backward
 int launch_delta(const AttnParams& p, int dtype, hipStream_t s);
 
 // Bandwidth-bound helpers; each takes a pair of tensors (gK and gV, keys and values) handled by one launch,
