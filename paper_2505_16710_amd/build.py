@@ -24,6 +24,7 @@ SOURCES = [
     "fwd_bf16.hip",
     "fwd4_bf16.hip",
     "fwd4_split_bf16.hip",
+    "fwd_small_bf16.hip",
     "bwd_dq_bf16.hip",
     "bwd_dkdv_bf16.hip",
     "decoder.hip",

@@ -268,6 +268,7 @@ int launch_fwd8(const AttnParams& p, int n_mtiles, int total, hipStream_t s) {
 }  // namespace
 
 int launch_fwd_bf16(const AttnParams& p, hipStream_t s) {
+  if (p.G * p.C <= 32) return launch_fwd_small_bf16(p, p.part ? split_plan(p.B, p.Hkv, p.G, p.C).max_splits : 1, s);
   if (p.n_splits > 1) {
     const SplitPlan plan = split_plan(p.B, p.Hkv, p.G, p.C);
     int rc = launch_fwd4_bf16(p, true, plan.n_mtiles, plan.items * p.n_splits, s);

@@ -1,0 +1,217 @@
+// Forward of a chunk with at most 32 query rows per KV head (C rows times the G query heads that share it): a few tokens
+// at the end of a cache.
+//
+// What bounds it is reading the cache once, or, where that is short, the latency of one pass through memory: the row tiles
+// of the other kernels would be mostly padding (a wavefront per head, four heads per workgroup, all on the same tile of
+// the cache, one tile after the other).  Here all rows of a KV head are one 32-row tile that every wavefront holds, and
+// the wavefronts divide the cache: each takes blocks of 32 cache rows on its own, K and V copied into its own 16 KiB of
+// LDS, no barrier in the loop.  Eight wavefronts keep 128 KiB in flight per CU.  Their sums meet in LDS; a long cache is
+// divided among n_splits workgroups whose partial results fwd_merge_kernel combines.
+// Kernel times with the merge: 2 rows x 8 heads against 1101 cache rows 14.9 -> 10.0 us, 1 row x 32 heads (8 KV heads)
+// against 600 / 8828 15.8 -> 8.9 / 16.7 -> 13.8 us; 8 rows x 32 heads against 32008 rows 30.7 -> 28.1 us (4.7 TB/s).
+#include <algorithm>
+
+#include "mfma_tiles.h"
+#include "seco_internal.h"
+
+namespace seco {
+namespace {
+
+constexpr int kWaves = 8, kBlock = 32;
+constexpr int kTurnStep = 1040;                          // bytes between the 64-lane groups of a turned tile (16 of padding)
+constexpr int kOwn = 16 * kTurnStep;                     // a wavefront's LDS: K and V blocks, then its partial O
+constexpr int kQTile = kWaves * kOwn, kMl = kQTile + 8192, kSmem = kMl + kWaves * 32 * 2 * 4;
+static_assert(kOwn >= 2 * kBlock * kRowBytes && kOwn % 256 == 0, "a K and a V block");
+
+__global__ __launch_bounds__(kWaves * 64, 2) void fwd_small_bf16_kernel(AttnParams p, int total_items) {
+  typedef float f32x4 __attribute__((ext_vector_type(4)));
+  extern __shared__ __attribute__((aligned(16))) char smem_raw[];
+  lds_char* smem = (lds_char*)smem_raw;
+  const int item = xcd_item(blockIdx.x, total_items);
+  if (item < 0) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, g = lane >> 5;
+  const int unit = item / p.n_splits, sp = item - unit * p.n_splits, b = unit / p.Hkv, kvh = unit - b * p.Hkv;
+  const int n_rows = p.G * p.C, kv_len = p.q_start + p.C;
+  const __bf16* kbase = static_cast<const __bf16*>(p.k) + b * p.kvs[0] + kvh * p.kvs[1];
+  const __bf16* vbase = static_cast<const __bf16*>(p.v) + b * p.kvs[0] + kvh * p.kvs[1];
+  // blocks of this workgroup: [first, last), dealt to the wavefronts in turn
+  const int n_blocks = (kv_len + kBlock - 1) / kBlock, per = (n_blocks + p.n_splits - 1) / p.n_splits;
+  const int first = sp * per, last = min(n_blocks, first + per);
+  lds_char* kt = smem + wave * kOwn;
+  lds_char* vt = kt + kBlock * kRowBytes;
+  uint32_t lane_off[4];                                  // of rows 4 i .. 4 i + 3, by i % 4 (the chunk's XOR), without 4 i rows
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    lane_off[i] = (uint32_t)((lane >> 4) * (p.kvs[2] * 2)) + (uint32_t)(((lane & 15) ^ swz(4 * i + (lane >> 4))) << 4);
+  // eight copies of four rows each: one block of K (dst kt) or V (dst vt)
+  auto copy_block = [&](const __bf16* base, lds_char* dst, int blk) {
+    if ((blk + 1) * kBlock <= kv_len) {
+      const uint32_t d = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)dst);
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        dma16_sbase(base + (int64_t)(blk * kBlock + 4 * i) * p.kvs[2], lane_off[i & 3], d + i * 4 * kRowBytes);
+    } else {
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        dma4rows(dst, 4 * i, base + (int64_t)min(blk * kBlock + 4 * i + (lane >> 4), kv_len - 1) * p.kvs[2], lane);
+    }
+  };
+  // packed row r: head r / C of the group, chunk row r % C; rows past the last repeat it and are not stored
+  {
+    const int r = min(4 * wave + (lane >> 4), n_rows - 1), hg = r / p.C;
+    dma4rows(smem + kQTile, 4 * wave, static_cast<const __bf16*>(p.q) + b * p.qs[0] + (kvh * p.G + hg) * p.qs[1] +
+                                          (int64_t)(r - hg * p.C) * p.qs[2], lane);
+  }
+  int blk = first + wave;
+  if (blk < last) {
+    copy_block(kbase, kt, blk);
+    copy_block(vbase, vt, blk);
+  }
+  const int my_row = min(l32, n_rows - 1), qpos = p.q_start + my_row % p.C;
+  const float c = p.scale * kLog2e;
+  f32x16 o[4];
+#pragma unroll
+  for (int db = 0; db < 4; ++db)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) o[db][r] = 0.f;
+  float m = -INFINITY, l = 0.f;
+  dma_wait_all();
+  __syncthreads();
+  bf16x8 qf[8];
+#pragma unroll
+  for (int t = 0; t < 8; ++t) qf[t] = lds_row8(smem + kQTile, l32, 2 * t + g);
+
+  for (; blk < last; blk += kWaves) {
+    f32x16 s;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[r] = 0.f;
+#pragma unroll
+    for (int t = 0; t < 8; ++t) s = mfma(lds_row8(kt, l32, 2 * t + g), qf[t], s);
+    // The next block's K goes into the place of this one's as soon as its rows have been read, its V behind the second
+    // product: copies land in order, so "at most 8 outstanding" means that the older of the two has arrived.
+    const bool more = blk + kWaves < last;
+    if (more) {
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      copy_block(kbase, kt, blk + kWaves);
+    }
+    const int col0 = blk * kBlock;
+    if (col0 + kBlock - 1 > p.q_start) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        if (col0 + 8 * (r >> 2) + 4 * g + (r & 3) > qpos) s[r] = -INFINITY;
+    }
+    float mx = s[0];
+#pragma unroll
+    for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
+    mx = fmaxf(m, fmaxf(mx, __shfl_xor(mx, 32)) * c);
+    const float ref = mx == -INFINITY ? 0.f : mx;                   // a row that has seen nothing yet
+    if (__builtin_amdgcn_ballot_w64(mx > m) != 0) {
+      const float alpha = fast_exp2(m - ref);
+      l *= alpha;
+#pragma unroll
+      for (int db = 0; db < 4; ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
+      m = mx;
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      s[r] = fast_exp2(__builtin_fmaf(s[r], c, -ref));
+      l += s[r];
+    }
+    if (more)
+      asm volatile("s_waitcnt vmcnt(8)" ::: "memory");              // V of this block
+    else
+      dma_wait_all();
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const bf16x8 pb = pack8(s, t);
+#pragma unroll
+      for (int db = 0; db < 4; ++db) o[db] = mfma(lds_tr8(vt, 16 * t, db, lane), pb, o[db]);
+    }
+    if (more) {
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      copy_block(vbase, vt, blk + kWaves);
+      asm volatile("s_waitcnt vmcnt(8)" ::: "memory");              // K of the next block
+    }
+  }
+  l += __shfl_xor(l, 32);
+
+  // the wavefronts' sums, relative to their common reference
+  SECO_LDS float* ml = reinterpret_cast<SECO_LDS float*>(smem + kMl);
+  if (g == 0) {
+    ml[2 * (wave * 32 + l32)] = m;
+    ml[2 * (wave * 32 + l32) + 1] = l;
+  }
+  __syncthreads();
+  float M = -INFINITY;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) M = fmaxf(M, ml[2 * (w * 32 + l32)]);
+  const float a = M == -INFINITY ? 0.f : fast_exp2(m - M);
+#pragma unroll
+  for (int db = 0; db < 4; ++db)
+#pragma unroll
+    for (int r4 = 0; r4 < 4; ++r4) {
+      const f32x4 v = {o[db][4 * r4] * a, o[db][4 * r4 + 1] * a, o[db][4 * r4 + 2] * a, o[db][4 * r4 + 3] * a};
+      *reinterpret_cast<SECO_LDS f32x4*>(kt + (4 * db + r4) * kTurnStep + lane * 16) = v;
+    }
+  __syncthreads();
+  // thread: four consecutive head_dim elements of rows tid / 32 and tid / 32 + 16
+  const int q = tid & 31;
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const int r = (tid >> 5) + 16 * k;
+    if (r >= n_rows) break;
+    float rm = -INFINITY, rl = 0.f;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) rm = fmaxf(rm, ml[2 * (w * 32 + r)]);
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      const float mw = ml[2 * (w * 32 + r)];
+      rl += mw == -INFINITY ? 0.f : ml[2 * (w * 32 + r) + 1] * fast_exp2(mw - rm);
+    }
+    f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w)
+      sum += *reinterpret_cast<SECO_LDS f32x4*>(smem + w * kOwn + (q >> 1) * kTurnStep + ((q & 1) * 32 + r) * 16);
+    const int hg = r / p.C, row = r - hg * p.C, h = kvh * p.G + hg;
+    const int64_t rowid = ((int64_t)b * p.Hq + h) * p.C + row;
+    if (p.n_splits > 1) {
+      const int64_t part_row = (int64_t)sp * p.B * p.Hq * p.C + rowid;
+      *reinterpret_cast<f32x4*>(p.part + part_row * kHeadDim + 4 * q) = sum;
+      if (q == 0) {
+        p.part_ml[2 * part_row] = rm;
+        p.part_ml[2 * part_row + 1] = rl;
+      }
+    } else {
+      const float inv = 1.f / rl;
+      const bf16x4 v = {(__bf16)(sum[0] * inv), (__bf16)(sum[1] * inv), (__bf16)(sum[2] * inv), (__bf16)(sum[3] * inv)};
+      *reinterpret_cast<bf16x4*>(static_cast<__bf16*>(p.o_out) + b * p.os[0] + h * p.os[1] + (int64_t)row * p.os[2] + 4 * q) = v;
+      if (q == 0) p.lse[rowid] = (rm + __log2f(rl)) * kLn2;
+    }
+  }
+}
+
+}  // namespace
+
+int launch_fwd_small_bf16(AttnParams p, int max_splits, hipStream_t s) {
+  // A workgroup takes about 1.3 us per round of 8 blocks; dividing the cache costs a merge of about 4 us.  At most one
+  // workgroup per CU.
+  const int units = p.B * p.Hkv, rounds = ((p.q_start + p.C + kBlock - 1) / kBlock + kWaves - 1) / kWaves;
+  int n = std::min(std::max(device_cus() / units, 1), max_splits);
+  const int each = (rounds + n - 1) / n;
+  n = (rounds + each - 1) / each;
+  p.n_splits = 13 * (rounds - each) > 40 ? n : 1;
+  const int total = units * p.n_splits;
+  static std::atomic<uint64_t> ready{0};
+  if (!allow_lds(ready, reinterpret_cast<const void*>(fwd_small_bf16_kernel), kSmem)) return SECO_ERR_LAUNCH;
+  {
+    ProfScope prof(kKernelFwd, s);
+    hipLaunchKernelGGL(fwd_small_bf16_kernel, dim3(xcd_grid(total)), dim3(kWaves * 64), kSmem, s, p, total);
+  }
+  const int rc = launch_status();
+  return rc || p.n_splits == 1 ? rc : launch_fwd_merge(p, s);
+}
+
+}  // namespace seco

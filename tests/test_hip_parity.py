@@ -571,6 +571,27 @@ def test_short_chunk_forward_with_and_without_workspace():
         assert max_rel(to_host(l), ref_l) <= 1e-2
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,C,q_start", [
+    (1, 8, 8, 1, 0),         # one row that sees itself
+    (2, 8, 2, 8, 23),        # 32 packed rows, one ragged block of cache rows
+    (1, 4, 1, 3, 1024),      # heads of three rows each; fewer blocks in the last round than wavefronts
+    (1, 4, 4, 32, 1000),     # the diagonal inside two blocks
+    (1, 16, 2, 4, 9001),     # divided cache, the last share short
+])
+def test_bf16_forward_of_a_few_rows(B, Hq, Hkv, C, q_start):
+    """At most 32 rows per KV head: the kernel whose wavefronts divide the cache; with a cache of a larger row stride."""
+    N, s = q_start + C, 1 / np.sqrt(128)
+    x = small_layer(63, B, Hq, Hkv, N, 128, "bf16")
+    q = to_dev(np.ascontiguousarray(x["q"][:, :, q_start:]), "bf16")
+    k, v = (torch.empty(B, Hkv, N, 136, dtype=torch.bfloat16, device=DEV)[..., :128] for _ in range(2))
+    k.copy_(to_dev(x["k"], "bf16"))
+    v.copy_(to_dev(x["v"], "bf16"))
+    ref_o, ref_lse = A.chunk_attn_fwd(x["q"][:, :, q_start:], x["k"], x["v"], q_start, s)
+    for ws in (None, False):                        # divided or not
+        o, lse = seco.seco_chunk_attn_fwd(q, k, v, q_start, s, ws=ws)
+        assert max_rel(to_host(o), ref_o) <= TOL["bf16"]["o"] and max_rel(to_host(lse), ref_lse) <= TOL["bf16"]["lse"]
+
+
 @pytest.mark.parametrize("order", ["accumulating", "transposed"])
 def test_step_captured_in_a_hip_graph_replays_identically(order):
     """The library allocates nothing, never synchronises and clears gK/gV with a kernel, so a whole SeCO step can be
