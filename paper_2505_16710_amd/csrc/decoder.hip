@@ -55,12 +55,45 @@ template <typename Op> __device__ __forceinline__ float block_reduce(float x) {
   return x;
 }
 
-template <typename T, int V>
+// Block k of a row, this thread's words: loads are issued for every lane (past the row's end: its last words, dropped), all
+// of a row's before the first is used.  Behind a per-lane condition the compiler waits for each load before the next,
+// which made a norm three to six memory latencies long.
+// KB: blocks of a row kept in registers, as many as the row has, at most kKeep.
+template <typename T, int V> __device__ __forceinline__ Vec<T, V> fetch(const T* row, int64_t c, int64_t d) {
+  return *reinterpret_cast<const Vec<T, V>*>(row + (c < d ? c : d - V));
+}
+
+template <typename T, int V, int KB>
 __global__ __launch_bounds__(kThreads) void add_rmsnorm_kernel(const T* x, const T* y, const T* gain, T* x_out, T* h,
                                                                float* rstd, int64_t d) {   // (x_out may be x)
   const int64_t row = (int64_t)blockIdx.x * d;
-  float kept[kKeep][V], sum = 0.f;
-  auto value = [&](int64_t c, float* f) {                 // first pass: the row, with y added (and rounded) to it
+  float kept[KB][V], sum = 0.f;
+  Vec<T, V> xv[KB], yv[KB], gv[KB];
+#pragma unroll
+  for (int k = 0; k < KB; ++k) {
+    const int64_t c = ((int64_t)k * kThreads + threadIdx.x) * V;
+    xv[k] = fetch<T, V>(x + row, c, d);
+    yv[k] = fetch<T, V>((y ? y : x) + row, c, d);
+    gv[k] = fetch<T, V>(gain, c, d);
+  }
+#pragma unroll
+  for (int k = 0; k < KB; ++k) {                       // first pass: the row, with y added (and rounded) to it
+    const int64_t c = ((int64_t)k * kThreads + threadIdx.x) * V;
+    if (c < d) {
+      xv[k].get(kept[k]);
+      if (y) {
+        float g[V];
+        yv[k].get(g);
+#pragma unroll
+        for (int j = 0; j < V; ++j) kept[k][j] = (float)(T)(kept[k][j] + g[j]);
+        store<T, V>(x_out + row + c, kept[k]);
+      }
+#pragma unroll
+      for (int j = 0; j < V; ++j) sum += kept[k][j] * kept[k][j];
+    }
+  }
+  for (int64_t c = ((int64_t)KB * kThreads + threadIdx.x) * V; c < d; c += kThreads * V) {
+    float f[V];
     load<T, V>(x + row + c, f);
     if (y) {
       float g[V];
@@ -71,58 +104,61 @@ __global__ __launch_bounds__(kThreads) void add_rmsnorm_kernel(const T* x, const
     }
 #pragma unroll
     for (int j = 0; j < V; ++j) sum += f[j] * f[j];
-  };
-#pragma unroll
-  for (int k = 0; k < kKeep; ++k) {
-    const int64_t c = ((int64_t)k * kThreads + threadIdx.x) * V;
-    if (c < d) value(c, kept[k]);
-  }
-  for (int64_t c = ((int64_t)kKeep * kThreads + threadIdx.x) * V; c < d; c += kThreads * V) {
-    float f[V];
-    value(c, f);
   }
   const float r = rsqrtf(block_reduce<Sum>(sum) / (float)d + 1e-6f);
   if (threadIdx.x == 0) rstd[blockIdx.x] = r;
-  auto scale = [&](int64_t c, float* f) {
-    float g[V];
+#pragma unroll
+  for (int k = 0; k < KB; ++k) {
+    const int64_t c = ((int64_t)k * kThreads + threadIdx.x) * V;
+    if (c < d) {
+      float g[V];
+      gv[k].get(g);
+#pragma unroll
+      for (int j = 0; j < V; ++j) kept[k][j] = (float)(T)(kept[k][j] * r) * g[j];
+      store<T, V>(h + row + c, kept[k]);
+    }
+  }
+  for (int64_t c = ((int64_t)KB * kThreads + threadIdx.x) * V; c < d; c += kThreads * V) {
+    float f[V], g[V];
+    load<T, V>((y ? x_out : x) + row + c, f);             // this thread's own words
     load<T, V>(gain + c, g);
 #pragma unroll
     for (int j = 0; j < V; ++j) f[j] = (float)(T)(f[j] * r) * g[j];
     store<T, V>(h + row + c, f);
-  };
-#pragma unroll
-  for (int k = 0; k < kKeep; ++k) {
-    const int64_t c = ((int64_t)k * kThreads + threadIdx.x) * V;
-    if (c < d) scale(c, kept[k]);
-  }
-  for (int64_t c = ((int64_t)kKeep * kThreads + threadIdx.x) * V; c < d; c += kThreads * V) {
-    float f[V];
-    load<T, V>((y ? x_out : x) + row + c, f);             // this thread's own words
-    scale(c, f);
   }
 }
 
 // With n = x rstd and e = d_h gain:  d_x = d_in + rstd (e - n mean(e n)),  d_gain = sum over rows of d_h round(n).
 // A workgroup takes every DEC_GAIN_BLOCKS-th row and adds its share of d_gain to its own row of gain_part.
-template <typename T, int V>
+template <typename T, int V, int KB>
 __global__ __launch_bounds__(kThreads) void rmsnorm_bwd_kernel(const T* x, const T* gain, const float* rstd, const T* d_h,
                                                                const T* d_in, T* d_x, float* gain_part, int64_t rows,
                                                                int64_t d) {
-  float dg[kKeep][V];
+  float dg[KB][V];
+  Vec<T, V> gv[KB];
+  Vec<float, V> old[KB];
+  float* part = gain_part + (int64_t)blockIdx.x * d;
 #pragma unroll
-  for (int k = 0; k < kKeep; ++k)
+  for (int k = 0; k < KB; ++k) {
+    const int64_t c = ((int64_t)k * kThreads + threadIdx.x) * V;
+    gv[k] = fetch<T, V>(gain, c, d);
+    old[k] = fetch<float, V>(part, c, d);
 #pragma unroll
     for (int j = 0; j < V; ++j) dg[k][j] = 0.f;
-  float* part = gain_part + (int64_t)blockIdx.x * d;
+  }
   for (int64_t rr = blockIdx.x; rr < rows; rr += DEC_GAIN_BLOCKS) {
     const int64_t row = rr * d;
     const float r = rstd[rr];
-    float n[kKeep][V], e[kKeep][V], sum = 0.f;
-    auto first = [&](int64_t c, float* nn, float* ee, float* gg) {
-      float g[V];
-      load<T, V>(x + row + c, nn);
-      load<T, V>(d_h + row + c, ee);
-      load<T, V>(gain + c, g);
+    float n[KB][V], e[KB][V], sum = 0.f;
+    Vec<T, V> xv[KB], hv[KB], iv[KB];
+#pragma unroll
+    for (int k = 0; k < KB; ++k) {
+      const int64_t c = ((int64_t)k * kThreads + threadIdx.x) * V;
+      xv[k] = fetch<T, V>(x + row, c, d);
+      hv[k] = fetch<T, V>(d_h + row, c, d);
+      iv[k] = fetch<T, V>((d_in ? d_in : x) + row, c, d);  // (d_x may be d_in: this thread's own words)
+    }
+    auto terms = [&](float* nn, float* ee, const float* g, float* gg) {   // nn = x, ee = d_h on entry
 #pragma unroll
       for (int j = 0; j < V; ++j) {
         nn[j] *= r;
@@ -132,43 +168,60 @@ __global__ __launch_bounds__(kThreads) void rmsnorm_bwd_kernel(const T* x, const
       }
     };
 #pragma unroll
-    for (int k = 0; k < kKeep; ++k) {
+    for (int k = 0; k < KB; ++k) {
       const int64_t c = ((int64_t)k * kThreads + threadIdx.x) * V;
-      if (c < d) first(c, n[k], e[k], dg[k]);
+      if (c < d) {
+        float g[V];
+        xv[k].get(n[k]);
+        hv[k].get(e[k]);
+        gv[k].get(g);
+        terms(n[k], e[k], g, dg[k]);
+      }
     }
-    for (int64_t c = ((int64_t)kKeep * kThreads + threadIdx.x) * V; c < d; c += kThreads * V) {
+    auto far = [&](int64_t c, float* nn, float* ee, float* gg) {           // past what is kept in registers
+      float g[V];
+      load<T, V>(x + row + c, nn);
+      load<T, V>(d_h + row + c, ee);
+      load<T, V>(gain + c, g);
+      terms(nn, ee, g, gg);
+    };
+    for (int64_t c = ((int64_t)KB * kThreads + threadIdx.x) * V; c < d; c += kThreads * V) {
       float nn[V], ee[V], gg[V];
       load<float, V>(part + c, gg);
-      first(c, nn, ee, gg);
+      far(c, nn, ee, gg);
       store<float, V>(part + c, gg);
     }
     const float mean = block_reduce<Sum>(sum) / (float)d;
-    auto second = [&](int64_t c, const float* nn, const float* ee) {
-      float f[V];
+#pragma unroll
+    for (int k = 0; k < KB; ++k) {
+      const int64_t c = ((int64_t)k * kThreads + threadIdx.x) * V;
+      if (c < d) {
+        float f[V];
+#pragma unroll
+        for (int j = 0; j < V; ++j) f[j] = 0.f;
+        if (d_in) iv[k].get(f);
+#pragma unroll
+        for (int j = 0; j < V; ++j) f[j] += r * (e[k][j] - n[k][j] * mean);
+        store<T, V>(d_x + row + c, f);
+      }
+    }
+    for (int64_t c = ((int64_t)KB * kThreads + threadIdx.x) * V; c < d; c += kThreads * V) {
+      float nn[V], ee[V], f[V];
+      far(c, nn, ee, nullptr);
 #pragma unroll
       for (int j = 0; j < V; ++j) f[j] = 0.f;
       if (d_in) load<T, V>(d_in + row + c, f);
 #pragma unroll
       for (int j = 0; j < V; ++j) f[j] += r * (ee[j] - nn[j] * mean);
       store<T, V>(d_x + row + c, f);
-    };
-#pragma unroll
-    for (int k = 0; k < kKeep; ++k) {
-      const int64_t c = ((int64_t)k * kThreads + threadIdx.x) * V;
-      if (c < d) second(c, n[k], e[k]);
-    }
-    for (int64_t c = ((int64_t)kKeep * kThreads + threadIdx.x) * V; c < d; c += kThreads * V) {
-      float nn[V], ee[V];
-      first(c, nn, ee, nullptr);
-      second(c, nn, ee);
     }
   }
 #pragma unroll
-  for (int k = 0; k < kKeep; ++k) {
+  for (int k = 0; k < KB; ++k) {
     const int64_t c = ((int64_t)k * kThreads + threadIdx.x) * V;
     if (c < d) {
       float f[V];
-      load<float, V>(part + c, f);
+      old[k].get(f);
 #pragma unroll
       for (int j = 0; j < V; ++j) f[j] += dg[k][j];
       store<float, V>(part + c, f);
@@ -282,13 +335,20 @@ template <typename... P> bool words(P... p) { return (((reinterpret_cast<uintptr
     else { LAUNCH(float, 1); }                                                  \
   }
 
+#define DEC_BLOCKS(kernel, T, V, grid, ...)                                                                                \
+  if (d <= kThreads * V)                                                                                                  \
+    hipLaunchKernelGGL((kernel<T, V, 1>), dim3(grid), dim3(kThreads), 0, (hipStream_t)stream, __VA_ARGS__);               \
+  else if (d <= 2 * kThreads * V)                                                                                         \
+    hipLaunchKernelGGL((kernel<T, V, 2>), dim3(grid), dim3(kThreads), 0, (hipStream_t)stream, __VA_ARGS__);               \
+  else                                                                                                                    \
+    hipLaunchKernelGGL((kernel<T, V, kKeep>), dim3(grid), dim3(kThreads), 0, (hipStream_t)stream, __VA_ARGS__)
+
 extern "C" int dec_add_rmsnorm(int dtype, const void* x, const void* y, const void* gain, void* x_out, void* h, float* rstd,
                                int64_t rows, int64_t d, void* stream) {
   if (!sizes_ok(dtype, rows, d)) return SECO_ERR_SHAPE;
   if (rows == 0) return SECO_OK;
 #define L(T, V)                                                                                                      \
-  hipLaunchKernelGGL((add_rmsnorm_kernel<T, V>), dim3((unsigned)rows), dim3(kThreads), 0, (hipStream_t)stream, (const T*)x, \
-                     (const T*)y, (const T*)gain, (T*)x_out, (T*)h, rstd, d)
+  DEC_BLOCKS(add_rmsnorm_kernel, T, V, (unsigned)rows, (const T*)x, (const T*)y, (const T*)gain, (T*)x_out, (T*)h, rstd, d)
   DEC_DISPATCH(d, words(x, y, gain, x_out, h), L)
 #undef L
   return status();
@@ -300,8 +360,8 @@ extern "C" int dec_rmsnorm_bwd(int dtype, const void* x, const void* gain, const
   if (rows == 0) return SECO_OK;
   const unsigned blocks = rows < DEC_GAIN_BLOCKS ? (unsigned)rows : DEC_GAIN_BLOCKS;
 #define L(T, V)                                                                                                        \
-  hipLaunchKernelGGL((rmsnorm_bwd_kernel<T, V>), dim3(blocks), dim3(kThreads), 0, (hipStream_t)stream, (const T*)x,     \
-                     (const T*)gain, rstd, (const T*)d_h, (const T*)d_in, (T*)d_x, gain_part, rows, d)
+  DEC_BLOCKS(rmsnorm_bwd_kernel, T, V, blocks, (const T*)x, (const T*)gain, rstd, (const T*)d_h, (const T*)d_in, (T*)d_x,  \
+             gain_part, rows, d)
   DEC_DISPATCH(d, words(x, gain, d_h, d_in, d_x, gain_part), L)
 #undef L
   return status();

@@ -68,24 +68,29 @@ __global__ __launch_bounds__(256) void kvgrad_kernel(float* __restrict__ dst_a, 
 // that all its loads are in flight at once; the groups' sums meet in LDS and are added in group order (fixed order:
 // reproducible).  What bounds it is the partials' traffic (33 MB for a 32-row chunk of 32 heads in 64 splits): with one
 // group per row and a loop over the splits every load waited for the one before, 23 us for that chunk; now 8.
-// Launchers choose GP = the power of two from which a group has at most 8 splits.
-template <int GP, typename Weight>
-__device__ __forceinline__ bool merge_partials(const float* part, int n_splits, int64_t R, int64_t rowid, int group, int d4,
-                                               Weight weight, float4& acc) {
-  __shared__ float4 sh[GP > 1 ? 256 : 1];
-  float4 x[8];
+// Launchers choose GP = the power of two from which a group has at most K = 8 splits (K less for the fewest splits).
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+// requests the group's partials (clamped, never behind a condition that differs over the lanes: the compiler would wait for
+// each load before the next one)
+template <int GP, int K>
+__device__ __forceinline__ void load_partials(const float* part, int n_splits, int64_t R, int64_t rowid, int group, int d4,
+                                              f32x4 (&x)[K]) {
 #pragma unroll
-  for (int k = 0; k < 8; ++k)
-    if (group + k * GP < n_splits) x[k] = *reinterpret_cast<const float4*>(part + ((group + k * GP) * R + rowid) * 128 + 4 * d4);
+  for (int k = 0; k < K; ++k)
+    x[k] = *reinterpret_cast<const f32x4*>(part + (min(group + k * GP, n_splits - 1) * R + rowid) * 128 + 4 * d4);
+}
+template <int GP, int K, typename Weight>
+__device__ __forceinline__ bool merge_partials(const f32x4 (&x)[K], int n_splits, int group, Weight weight, float4& acc) {
+  __shared__ float4 sh[GP > 1 ? 256 : 1];
   acc = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-  for (int k = 0; k < 8; ++k) {
+  for (int k = 0; k < K; ++k) {
     const float w = weight(k);                     // (a cross-lane read: every lane takes part)
     if (group + k * GP < n_splits && w != 0.f) {   // weight 0: an empty partial, never written
-      acc.x += w * x[k].x;
-      acc.y += w * x[k].y;
-      acc.z += w * x[k].z;
-      acc.w += w * x[k].w;
+      acc.x += w * x[k][0];
+      acc.y += w * x[k][1];
+      acc.z += w * x[k][2];
+      acc.w += w * x[k][3];
     }
   }
   if (GP == 1) return true;
@@ -112,31 +117,30 @@ typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 //   M = max m_s,  L = sum l_s 2^(m_s - M),  O = sum o_s 2^(m_s - M) / L,  LSE = (M + log2 L) ln 2.
 // Lane i of a group loads (m, l) of splits i and i + 32 once; max, sum and the per-split weights then travel by
 // cross-lane shuffles.
-template <int GP>
+template <int GP, int K>
 __global__ __launch_bounds__(256) void fwd_merge_kernel(AttnParams p) {
   const int64_t R = (int64_t)p.B * p.Hq * p.C;
   const int group = (threadIdx.x >> 5) % GP, l32 = threadIdx.x & 31;
   const int64_t mine = (int64_t)blockIdx.x * (8 / GP) + (threadIdx.x >> 5) / GP;
   const int64_t rowid = min(mine, R - 1);          // surplus threads of the last block repeat the last row, no store
-  float m0 = -INFINITY, m1 = -INFINITY, s0 = 0.f, s1 = 0.f;
-  if (l32 < p.n_splits) {
-    m0 = p.part_ml[2 * (l32 * R + rowid)];
-    s0 = p.part_ml[2 * (l32 * R + rowid) + 1];
-  }
-  if (l32 + 32 < p.n_splits) {
-    m1 = p.part_ml[2 * ((l32 + 32) * R + rowid)];
-    s1 = p.part_ml[2 * ((l32 + 32) * R + rowid) + 1];
-  }
+  // (m, l) of splits l32 and l32 + 32, then the partials, all in flight together
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  const f32x2* ml = reinterpret_cast<const f32x2*>(p.part_ml) + rowid;
+  const f32x2 a0 = ml[min(l32, p.n_splits - 1) * R], a1 = ml[min(l32 + 32, p.n_splits - 1) * R];
+  f32x4 x[K];
+  load_partials<GP, K>(p.part, p.n_splits, R, rowid, group, l32, x);
+  const float m0 = l32 < p.n_splits ? a0[0] : -INFINITY, s0 = l32 < p.n_splits ? a0[1] : 0.f;
+  const float m1 = l32 + 32 < p.n_splits ? a1[0] : -INFINITY, s1 = l32 + 32 < p.n_splits ? a1[1] : 0.f;
   float M = fmaxf(m0, m1);
 #pragma unroll
   for (int sh = 16; sh > 0; sh >>= 1) M = fmaxf(M, __shfl_xor(M, sh, 32));
-  const float w0 = m0 == -INFINITY ? 0.f : exp2f(m0 - M);
-  const float w1 = m1 == -INFINITY ? 0.f : exp2f(m1 - M);
+  const float w0 = m0 == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m0 - M);
+  const float w1 = m1 == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m1 - M);
   float L = w0 * s0 + w1 * s1;
 #pragma unroll
   for (int sh = 16; sh > 0; sh >>= 1) L += __shfl_xor(L, sh, 32);
   float4 acc;
-  const bool store = merge_partials<GP>(p.part, p.n_splits, R, rowid, group, l32, [&](int k) {
+  const bool store = merge_partials<GP, K>(x, p.n_splits, group, [&](int k) {
     const int sp = group + k * GP;
     return __shfl(sp < 32 ? w0 : w1, sp & 31, 32);
   }, acc);
@@ -144,40 +148,45 @@ __global__ __launch_bounds__(256) void fwd_merge_kernel(AttnParams p) {
   const float inv = 1.f / L;
   const bf16x4 v = {(__bf16)(acc.x * inv), (__bf16)(acc.y * inv), (__bf16)(acc.z * inv), (__bf16)(acc.w * inv)};
   *reinterpret_cast<bf16x4*>(static_cast<__bf16*>(p.o_out) + row_offset(p, rowid, p.os) + 4 * l32) = v;
-  if (l32 == 0) p.lse[rowid] = (M + log2f(L)) * 0.6931471805599453f;
+  if (l32 == 0) p.lse[rowid] = (M + __builtin_amdgcn_logf(L)) * 0.6931471805599453f;
 }
 
 // Merge of the split dQ: dQ = scale * (sum of the partials), rounded to bf16.
-template <int GP>
+template <int GP, int K>
 __global__ __launch_bounds__(256) void dq_merge_kernel(AttnParams p) {
   const int64_t R = (int64_t)p.B * p.Hq * p.C;
   const int group = (threadIdx.x >> 5) % GP, l32 = threadIdx.x & 31;
   const int64_t mine = (int64_t)blockIdx.x * (8 / GP) + (threadIdx.x >> 5) / GP;
   const int64_t rowid = min(mine, R - 1);
+  f32x4 x[K];
+  load_partials<GP, K>(p.part, p.n_splits, R, rowid, group, l32, x);
   float4 acc;
-  const bool store = merge_partials<GP>(p.part, p.n_splits, R, rowid, group, l32, [](int) { return 1.f; }, acc);
+  const bool store = merge_partials<GP, K>(x, p.n_splits, group, [](int) { return 1.f; }, acc);
   if (!store || mine >= R) return;
   const bf16x4 v = {(__bf16)(acc.x * p.scale), (__bf16)(acc.y * p.scale), (__bf16)(acc.z * p.scale), (__bf16)(acc.w * p.scale)};
   *reinterpret_cast<bf16x4*>(static_cast<__bf16*>(p.d_q) + row_offset(p, rowid, p.qs) + 4 * l32) = v;
 }
 
+// (Loads without a condition, on a clamped row: with one the compiler waited for each before it issued the next, 18.7 us
+// for 2 x 4 MiB.)
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // Row-range copy into the cache, 16 bytes per thread and row.  Strides arrive in units of 16 bytes.
-__global__ __launch_bounds__(256) void rows_copy_kernel(uint4* __restrict__ dst_a, uint4* __restrict__ dst_b,
-                                                        const uint4* __restrict__ src_a, const uint4* __restrict__ src_b,
+__global__ __launch_bounds__(256) void rows_copy_kernel(u32x4* __restrict__ dst_a, u32x4* __restrict__ dst_b,
+                                                        const u32x4* __restrict__ src_a, const u32x4* __restrict__ src_b,
                                                         int n_bh, int H, int C, int v16, int64_t ds0, int64_t ds1,
                                                         int64_t ds2, int64_t ss0, int64_t ss1, int64_t ss2, int64_t r0) {
-  uint4* __restrict__ dst = blockIdx.z ? dst_b : dst_a;
-  const uint4* __restrict__ src = blockIdx.z ? src_b : src_a;
+  u32x4* __restrict__ dst = blockIdx.z ? dst_b : dst_a;
+  const u32x4* __restrict__ src = blockIdx.z ? src_b : src_a;
   int64_t to = 0, from = 0;
   for_rows(n_bh, v16, C, [&](int bh) {
     const int b = bh / H, h = bh % H;
     to = b * ds0 + h * ds1 + r0 * ds2;
     from = b * ss0 + h * ss1;
   }, [&](int64_t row, int rpb, int c) {
-    uint4 x[kRowUnroll];
+    u32x4 x[kRowUnroll];
 #pragma unroll
     for (int k = 0; k < kRowUnroll; ++k)
-      if (row + k * rpb < C) x[k] = src[from + (row + k * rpb) * ss2 + c];
+      x[k] = src[from + min(row + k * rpb, (int64_t)C - 1) * ss2 + c];
 #pragma unroll
     for (int k = 0; k < kRowUnroll; ++k)
       if (row + k * rpb < C) dst[to + (row + k * rpb) * ds2 + c] = x[k];
@@ -270,8 +279,8 @@ int launch_rows_copy(void* da, void* db, const void* sa, const void* sb, int eb,
   if (!da) return SECO_OK;
   {
     ProfScope prof(kKernelKvgrad, s);
-    hipLaunchKernelGGL(rows_copy_kernel, rows_grid(C, v16, B * H, db ? 2 : 1), dim3(256), 0, s, static_cast<uint4*>(da),
-                       static_cast<uint4*>(db), static_cast<const uint4*>(sa), static_cast<const uint4*>(sb), B * H, H, C,
+    hipLaunchKernelGGL(rows_copy_kernel, rows_grid(C, v16, B * H, db ? 2 : 1), dim3(256), 0, s, static_cast<u32x4*>(da),
+                       static_cast<u32x4*>(db), static_cast<const u32x4*>(sa), static_cast<const u32x4*>(sb), B * H, H, C,
                        v16, dst_s[0] / per16, dst_s[1] / per16, dst_s[2] / per16, src_s[0] / per16, src_s[1] / per16,
                        src_s[2] / per16, r0);
   }
@@ -347,12 +356,17 @@ template <> struct Quad<__bf16> {
 // as blockIdx.z == 1: the same rows, scaled and converted but not rotated, so that keys and values take one pass and
 // one launch.
 constexpr int kRopeHeads = 4;
+// base^(-2 i / D) for i = 4 grp + j is a product of powers the host has computed: pow[k] = base^(-8 2^k / D) for bit k of
+// grp, and step = base^(-2 / D), j times (an fp64 exp2 per element pair was half of the kernel's arithmetic).
+struct RopePowers {
+  double pow[6], step;
+};
 template <typename TIn, typename TOut>
 __global__ __launch_bounds__(256) void rope_rows_kernel(TOut* out, const TIn* in, TOut* plain_out, const TIn* plain_in,
                                                         int B, int H, int C,   // (out may be in)
                                                         int D, int64_t os0, int64_t os1, int64_t os2, int64_t is0,
                                                         int64_t is1, int64_t is2, int64_t out_r0, int64_t in_r0,
-                                                        int64_t pos0, double log2_base, float sign, float scale,
+                                                        int64_t pos0, RopePowers powers, float sign, float scale,
                                                         int plain_from) {
   const int q4 = D / 8;                                   // groups of 4 pairs per row
   const bool plain = (int)blockIdx.z >= plain_from;       // plain_from: 1 with a rotated pair present, else 0
@@ -384,11 +398,14 @@ __global__ __launch_bounds__(256) void rope_rows_kernel(TOut* out, const TIn* in
   load(y);                                                // in flight during the fp64 arithmetic
   double sn[4], cs[4];
   if (!plain) {                                           // (uniform over the workgroup)
-    const double pos = (double)(pos0 + row);
+    double theta = (double)(pos0 + row);
+#pragma unroll
+    for (int k = 0; k < 6; ++k) theta *= grp >> k & 1 ? powers.pow[k] : 1.0;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      sincos_f64(pos * exp2(-2.0 * (double)(grp * 4 + j) / (double)D * log2_base), sn[j], cs[j]);
+      sincos_f64(theta, sn[j], cs[j]);
       sn[j] *= (double)sign;
+      theta *= powers.step;
     }
   }
   while (true) {
@@ -419,7 +436,9 @@ int launch_rope_rows(void* out, const void* in, void* plain_out, const void* pla
                      int H, int C, int D, const int64_t out_s[3], const int64_t in_s[3], int64_t out_r0, int64_t in_r0,
                      int64_t pos0, float base, bool inverse, float scale, hipStream_t s) {
   if (!out && !plain_out) return SECO_OK;
-  const double l2b = log2((double)base);
+  RopePowers powers;
+  powers.step = exp2(-2.0 / D * log2((double)base));
+  for (int k = 0; k < 6; ++k) powers.pow[k] = exp2(-8.0 * (1 << k) / D * log2((double)base));
   const float sign = inverse ? -1.f : 1.f;
   {
     ProfScope prof(kKernelKvgrad, s);
@@ -430,7 +449,7 @@ int launch_rope_rows(void* out, const void* in, void* plain_out, const void* pla
 #define SECO_ROPE_LAUNCH(TI, TO)                                                                                       \
   hipLaunchKernelGGL((rope_rows_kernel<TI, TO>), grid, dim3(256), 0, s, static_cast<TO*>(out),                         \
                      static_cast<const TI*>(in), static_cast<TO*>(plain_out), static_cast<const TI*>(plain_in), B, H,   \
-                     C, D, out_s[0], out_s[1], out_s[2], in_s[0], in_s[1], in_s[2], out_r0, in_r0, pos0, l2b, sign,     \
+                     C, D, out_s[0], out_s[1], out_s[2], in_s[0], in_s[1], in_s[2], out_r0, in_r0, pos0, powers, sign,     \
                      scale, plain_from)
     if (in_kind == SECO_BF16 && out_kind == SECO_BF16) SECO_ROPE_LAUNCH(__bf16, __bf16);
     else if (in_kind == SECO_F32 && out_kind == SECO_BF16) SECO_ROPE_LAUNCH(float, __bf16);
@@ -443,10 +462,13 @@ int launch_rope_rows(void* out, const void* in, void* plain_out, const void* pla
 #define SECO_MERGE_LAUNCH(kernel)                                                                             \
   const int64_t R = (int64_t)p.B * p.Hq * p.C;                                                                \
   ProfScope prof(kKernelMerge, s);                                                                            \
-  if (p.n_splits <= 8) hipLaunchKernelGGL(kernel<1>, dim3((unsigned)((R + 7) / 8)), dim3(256), 0, s, p);      \
-  else if (p.n_splits <= 16) hipLaunchKernelGGL(kernel<2>, dim3((unsigned)((R + 3) / 4)), dim3(256), 0, s, p); \
-  else if (p.n_splits <= 32) hipLaunchKernelGGL(kernel<4>, dim3((unsigned)((R + 1) / 2)), dim3(256), 0, s, p); \
-  else hipLaunchKernelGGL(kernel<8>, dim3((unsigned)R), dim3(256), 0, s, p);
+  const dim3 tpb(256);                                                                                        \
+  if (p.n_splits <= 2) hipLaunchKernelGGL((kernel<1, 2>), dim3((unsigned)((R + 7) / 8)), tpb, 0, s, p);       \
+  else if (p.n_splits <= 4) hipLaunchKernelGGL((kernel<1, 4>), dim3((unsigned)((R + 7) / 8)), tpb, 0, s, p);  \
+  else if (p.n_splits <= 8) hipLaunchKernelGGL((kernel<1, 8>), dim3((unsigned)((R + 7) / 8)), tpb, 0, s, p);  \
+  else if (p.n_splits <= 16) hipLaunchKernelGGL((kernel<2, 8>), dim3((unsigned)((R + 3) / 4)), tpb, 0, s, p); \
+  else if (p.n_splits <= 32) hipLaunchKernelGGL((kernel<4, 8>), dim3((unsigned)((R + 1) / 2)), tpb, 0, s, p); \
+  else hipLaunchKernelGGL((kernel<8, 8>), dim3((unsigned)R), tpb, 0, s, p);
 
 int launch_fwd_merge(const AttnParams& p, hipStream_t s) {
   SECO_MERGE_LAUNCH(fwd_merge_kernel)
