@@ -40,10 +40,10 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-I", INCLUDE, "
 # tried on every matrix-core kernel): keeping memory (LDS) instructions in clauses is 3 % faster than the default
 # on the 4-wavefront forward and at least as good on the dK/dV kernel; the dQ kernels and the 8-wavefront forward are
 # 3 % faster with the iterative ILP scheduler.
-SCHED = {"bwd_dq_bf16.hip": "iterative-ilp", "fwd_bf16.hip": "iterative-ilp"}
+SCHED = {"bwd_dq_bf16.hip": "iterative-ilp", "fwd_bf16.hip": "iterative-ilp", "fwd4_split_bf16.hip": "iterative-ilp"}
 SCHED_DEFAULT = "max-memory-clause"
 # the 4-wavefront forward, whose source interleaves two instruction streams by hand, is 2 % faster when the
-# scheduler does not cluster memory operations (its split instantiation would spill registers with that option)
+# scheduler does not cluster memory operations
 PER_FILE = {"fwd4_bf16.hip": ["-mllvm", "-misched-cluster=false"]}
 
 

@@ -33,7 +33,7 @@ constexpr int BNW = 64;   // cache rows per wavefront and tile
 template <int KH, bool SPLIT, bool SPARSE>
 __global__ __launch_bounds__(256 * KH, 2) void dq_bf16_kernel(AttnParams p, SegTable seg, int n_mtiles,
                                                               int total_items) {
-  static_assert(!SPLIT || KH == 1, "the split variant uses the 4-wavefront shape");
+  static_assert(!SPLIT || KH == 2, "the split variant uses the 8-wavefront shape");
   constexpr int BN = BNW * KH;
   constexpr int kTileBytes = BN * kRowBytes;
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];   // 4 * kTileBytes: [buf][K|V]
@@ -239,7 +239,7 @@ __global__ __launch_bounds__(256 * KH, 2) void dq_bf16_kernel(AttnParams p, SegT
   if (KH == 2) {
     // add the partial dQ of the two column halves of each row block through LDS
     typedef float f32x4 __attribute__((ext_vector_type(4)));
-    lds_char* slot = smem + rb * (16 * 1024);
+    lds_char* slot = smem + rb * (17 * 1024);
     if (kh == 1) {
 #pragma unroll
       for (int db = 0; db < 4; ++db)
@@ -262,23 +262,14 @@ __global__ __launch_bounds__(256 * KH, 2) void dq_bf16_kernel(AttnParams p, SegT
   }
 
   if constexpr (SPLIT) {
-    if (row < p.C) {
-      typedef float f32x4 __attribute__((ext_vector_type(4)));
-      float* po = p.part + ((int64_t)sp * p.B * p.Hq * p.C + stat) * kHeadDim;   // row < C: stat is this row's index
-#pragma unroll
-      for (int db = 0; db < 4; ++db)
-#pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4) {
-          const f32x4 v = {dq[db][4 * r4], dq[db][4 * r4 + 1], dq[db][4 * r4 + 2], dq[db][4 * r4 + 3]};
-          *reinterpret_cast<f32x4*>(po + 32 * db + 8 * r4 + 4 * g) = v;
-        }
-    }
+    float* po = p.part + ((int64_t)sp * p.B * p.Hq * p.C + ((int64_t)b * p.Hq + h) * p.C + m0) * kHeadDim;
+    store_part32(dq, po, p.C - m0, smem + rb * (17 * 1024));
     return;
   }
 
   store_rows32([&](int db, int r) { return dq[db][r] * p.scale; },
                static_cast<__bf16*>(p.d_q) + b * p.qs[0] + h * p.qs[1], p.qs[2], m0, p.C,
-               KH == 2 ? smem + rb * (16 * 1024) : smem + wave * 8192);
+               KH == 2 ? smem + rb * (17 * 1024) : smem + wave * 8192);
 }
 
 template <int KH, bool SPLIT, bool SPARSE>
@@ -303,8 +294,8 @@ int launch_dq_bf16(const AttnParams& p, const SegTable* runs, hipStream_t s) {
   if (p.n_splits > 1) {
     const SplitPlan plan = split_plan(p.B, p.Hkv, p.G, p.C);
     const int total = plan.items * p.n_splits;
-    int rc = runs ? launch_kh<1, true, true>(p, seg, plan.n_mtiles, total, s)
-                  : launch_kh<1, true, false>(p, seg, plan.n_mtiles, total, s);
+    int rc = runs ? launch_kh<2, true, true>(p, seg, plan.n_mtiles, total, s)
+                  : launch_kh<2, true, false>(p, seg, plan.n_mtiles, total, s);
     return rc ? rc : launch_dq_merge(p, s);
   }
   const int n_mtiles = (p.C + BM - 1) / BM;

@@ -196,6 +196,27 @@ __device__ __forceinline__ void store_rows32(const F& value, __bf16* base, int64
     if (r0 + 4 * j < n_rows) *reinterpret_cast<bf16x8*>(dst) = lds_row8(own8k, 4 * j + (lane >> 4), lane & 15);
 }
 
+// The same accumulator, fp32 and unscaled, to consecutive 512-byte rows (16.5 KiB of LDS)
+__device__ __forceinline__ void store_part32(const f32x16 (&acc)[4], float* base, int n_rows, lds_char* own) {
+  typedef float f32x4 __attribute__((ext_vector_type(4)));
+  constexpr int kRow = 528;             // bytes; 16 of padding
+  int lane = threadIdx.x & 63;
+  asm volatile("" : "+v"(lane));
+#pragma unroll
+  for (int db = 0; db < 4; ++db)
+#pragma unroll
+    for (int r4 = 0; r4 < 4; ++r4) {
+      const f32x4 v = {acc[db][4 * r4], acc[db][4 * r4 + 1], acc[db][4 * r4 + 2], acc[db][4 * r4 + 3]};
+      *reinterpret_cast<SECO_LDS f32x4*>(own + (lane & 31) * kRow + (32 * db + 8 * r4 + 4 * (lane >> 5)) * 4) = v;
+    }
+#pragma unroll
+  for (int j = 0; j < 16; ++j) {
+    const int r = 2 * j + (lane >> 5);
+    const f32x4 v = *reinterpret_cast<SECO_LDS f32x4*>(own + r * kRow + (lane & 31) * 16);
+    if (r < n_rows) *reinterpret_cast<f32x4*>(base + r * kHeadDim + (lane & 31) * 4) = v;
+  }
+}
+
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // XCD-aware work mapping: consecutive workgroup ids go round-robin over the 8 XCDs, each

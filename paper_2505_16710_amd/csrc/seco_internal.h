@@ -88,11 +88,21 @@ inline SplitPlan split_plan(int B, int Hkv, int G, int C) {
   if (pl.max_splits > 64) pl.max_splits = 64;
   return pl;
 }
-// number of splits for a call that sees kv_len cache rows: every split gets at least 4 tiles of 64 rows
+// Number of splits for a call that sees kv_len cache rows: the one with the least estimated time, in units of 0.1 us as
+// measured: a round of one workgroup per CU takes 60 plus 17 per 128-row tile of its share, a merge 40 plus 0.3 per share.
 inline int split_count(const SplitPlan& pl, int kv_len) {
-  const int by_len = (kv_len + 63) / 64 / 4;
-  const int n = pl.max_splits < by_len ? pl.max_splits : by_len;
-  return n < 2 ? 1 : n;
+  const int tiles = (kv_len + 127) / 128, cus = device_cus();
+  const int most = pl.max_splits < tiles ? pl.max_splits : tiles;
+  int best = 1, best_t = 0;
+  for (int n = 1; n <= most; ++n) {
+    const int wgs = pl.items * n, rounds = (wgs + cus - 1) / cus;
+    const int t = rounds * (60 + 17 * ((tiles + n - 1) / n)) + (n > 1 ? 40 + 3 * wgs / 10 : 0);
+    if (n == 1 || t < best_t) {
+      best = n;
+      best_t = t;
+    }
+  }
+  return best;
 }
 int launch_fwd_merge(const AttnParams& p, hipStream_t s);   // O, LSE from the partials
 int launch_dq_merge(const AttnParams& p, hipStream_t s);    // dQ = scale * sum of the partials, in split order
@@ -201,11 +211,12 @@ constexpr int kColTileF32 = 16;    // columns per workgroup in launch_dkdv_f32
 
 // bf16 matrix-core kernels (head_dim 128)
 int launch_fwd_bf16(const AttnParams& p, hipStream_t s);
-// the 4-wavefront forward kernel (its own translation unit); split: the short-chunk variant that writes partials
-int launch_fwd4_bf16(const AttnParams& p, bool split, int n_mtiles, int total, hipStream_t s);
+// the 4-wavefront forward kernel (its own translation unit)
+int launch_fwd4_bf16(const AttnParams& p, int n_mtiles, int total, hipStream_t s);
+// the 8-wavefront forward kernel's short-chunk variant, which writes partials (likewise)
+int launch_fwd8_split_bf16(const AttnParams& p, int n_mtiles, int total, hipStream_t s);
 // at most 32 query rows per KV head; max_splits: how many partial results the workspace holds (1: there is none)
 int launch_fwd_small_bf16(AttnParams p, int max_splits, hipStream_t s);
-int launch_fwd4_split_bf16(const AttnParams& p, int n_mtiles, int total, hipStream_t s);
 // dq_runs: NULL for all visible cache rows with weight 1; else runs of cache rows (ascending, disjoint), each with
 // a positive weight (tile_begin is not used)
 int launch_dq_bf16(const AttnParams& p, const SegTable* dq_runs, hipStream_t s);
