@@ -406,27 +406,27 @@ int bwd_nt(const AttnParams& p, const SegTable& dq_runs, const SegTable& seg, bo
 
 int launch_fwd_f32(const AttnParams& p, hipStream_t s) { SECO_F32_DISPATCH(fwd_nt, p, s) }
 
-// The three passes of the fp32 backward are one launch: the first two are noted in p.f32 and go out with the third
+// The three passes of the fp32 backward are one launch: the first two are noted in p.pending and go out with the third
 // (launch_dkdv_f32; with an empty table when there are no cache rows to cover).
 int launch_delta(const AttnParams&, int, hipStream_t) { return SECO_OK; }   // taken from O and dO where it is used
 
 int launch_dq_f32(const AttnParams& p, const SegTable* dq_runs, hipStream_t) {
-  SegTable& runs = p.f32->runs;
+  SegTable& runs = p.pending->runs;
   runs = SegTable{};
   runs.n = 1;
   runs.col_end[0] = p.q_start + p.C;
   runs.weight[0] = 1.f;
   if (dq_runs) runs = *dq_runs;
-  p.f32->dq = true;
+  p.pending->dq = true;
   return SECO_OK;
 }
 
 int launch_dkdv_f32(const AttnParams& p, const SegTable& seg, hipStream_t s) {
   static_assert(kColTileF32 == kRows, "one workgroup per column tile");
-  const bool dq = p.f32->dq;
-  p.f32->dq = false;
+  const bool dq = p.pending->dq;
+  p.pending->dq = false;
   if (!dq && seg.tile_begin[seg.n] == 0) return SECO_OK;
-  SECO_F32_DISPATCH(bwd_nt, p, p.f32->runs, seg, dq, s)
+  SECO_F32_DISPATCH(bwd_nt, p, p.pending->runs, seg, dq, s)
 }
 
 }  // namespace seco

@@ -20,6 +20,7 @@
 #include <stdint.h>
 
 #include <atomic>
+#include <type_traits>
 
 namespace seco {
 
@@ -215,6 +216,19 @@ __device__ __forceinline__ void store_part32(const f32x16 (&acc)[4], float* base
     const f32x4 v = *reinterpret_cast<SECO_LDS f32x4*>(own + r * kRow + (lane & 31) * 16);
     if (r < n_rows) *reinterpret_cast<f32x4*>(base + r * kHeadDim + (lane & 31) * 4) = v;
   }
+}
+
+// Sum over the 16 lanes of a row, by lane bits 3, 2, 1, 0; every lane gets it.  (Cross-lane reads of the vector ALU: rotations
+// by 8 and 4 equal exchanges of those bits once the sums repeat with that period.)
+__device__ __forceinline__ float row16_sum(float x) {
+  auto other = [](float v, auto ctrl) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), decltype(ctrl)::value, 0xf, 0xf, true));
+  };
+  x += other(x, std::integral_constant<int, 0x128>{});   // row_ror:8
+  x += other(x, std::integral_constant<int, 0x124>{});   // row_ror:4
+  x += other(x, std::integral_constant<int, 0x4e>{});    // quad_perm:[2,3,0,1]
+  x += other(x, std::integral_constant<int, 0xb1>{});    // quad_perm:[1,0,3,2]
+  return x;
 }
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }

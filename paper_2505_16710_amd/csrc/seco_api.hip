@@ -112,13 +112,15 @@ size_t tail_part_bytes(const seco_desc* d) {
   if (d->dtype != SECO_BF16 || d->n_q_heads / d->n_kv_heads < 2) return 0;
   return (size_t)device_cus() * kSlotBytes;
 }
-// the partial dQ of the split path and the divided dK/dV tiles are never live together: they share one region
 size_t bwd_part_bytes(const seco_desc* d) { return std::max(split_part_bytes(d), tail_part_bytes(d)); }
 
+// partial dQ first, then the shared-out column tiles (p.n_splits is set)
 void use_tail_part(AttnParams& p, const seco_desc* d, size_t ws_bytes) {
-  const size_t slots = d->dtype == SECO_BF16 ? (ws_bytes - delta_bytes(d)) / kSlotBytes : 0;
-  p.tail_slots = (int)std::min(slots, (size_t)device_cus());
-  p.tail_part = p.tail_slots > 0 ? p.part : nullptr;
+  if (d->dtype != SECO_BF16) return;
+  const size_t room = std::min(ws_bytes - delta_bytes(d), kPartBytes);
+  const size_t dq = p.n_splits > 1 ? round256((size_t)p.n_splits * d->batch * d->n_q_heads * d->chunk_len * d->head_dim * sizeof(float)) : 0;
+  p.tail_slots = room > dq ? (int)std::min((room - dq) / kSlotBytes, (size_t)device_cus()) : 0;
+  p.tail_part = p.tail_slots > 0 ? p.part + dq / sizeof(float) : nullptr;
 }
 
 int check_fwd_like(const seco_desc* d) {
@@ -194,8 +196,8 @@ int backward(const seco_desc* d, const void* q, const void* k, const void* v, co
   use_tail_part(p, d, ws_bytes);
   hipStream_t s = static_cast<hipStream_t>(stream);
   const bool bf16 = d->dtype == SECO_BF16;
-  F32Pending pending;
-  p.f32 = &pending;
+  PendingDq pending;     // where both fit, the dQ and dK/dV passes are one launch
+  p.pending = &pending;
   // delta = rowsum(dO * O): the bf16 dQ kernel computes it in its prologue (and stores it for the dK/dV kernel)
   if (!bf16 && (rc = launch_delta(p, d->dtype, s))) return rc;
   const SegTable* runs_arg = sparse_dq ? &dq_runs : nullptr;
@@ -236,7 +238,8 @@ int backward(const seco_desc* d, const void* q, const void* k, const void* v, co
     }
   }
   if ((rc = flush())) return rc;
-  return pending.dq ? launch_dkdv_f32(p, seg, s) : SECO_OK;   // (fp32 without a cache row to cover: dQ alone)
+  if (!pending.dq) return SECO_OK;                            // (else: no cache row to cover, dQ alone)
+  return bf16 ? launch_dkdv_bf16(p, seg, s) : launch_dkdv_f32(p, seg, s);
 }
 
 
@@ -405,7 +408,7 @@ extern "C" size_t seco_workspace_bytes(const seco_desc* desc, int op) {
 extern "C" size_t seco_workspace_bytes_preferred(const seco_desc* desc, int op) {
   const size_t n = seco_workspace_bytes(desc, op);
   if (n == (size_t)-1 || op != SECO_OP_BWD || desc->dtype != SECO_BF16) return n;
-  return std::max(n, delta_bytes(desc) + (size_t)device_cus() * kSlotBytes);
+  return std::max(n, delta_bytes(desc) + kPartBytes);
 }
 
 extern "C" int seco_launch_plan(const seco_desc* desc, int32_t n_col_tiles, int32_t* plan_host) {

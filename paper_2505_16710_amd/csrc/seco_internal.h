@@ -6,7 +6,7 @@
 
 namespace seco {
 
-struct F32Pending;
+struct PendingDq;
 
 // Everything a kernel needs to know about one chunk call (validated by the host side).
 struct AttnParams {
@@ -33,7 +33,7 @@ struct AttnParams {
   int B, Hq, Hkv, D, C, q_start, G;
   float scale;
   int64_t qs[3], os[3], kvs[3], gs[3];
-  F32Pending* f32;   // fp32 backward, host side: passes announced but not launched yet
+  PendingDq* pending;   // backward, host side: a dQ pass that is announced but not launched yet
 };
 
 // Column segments of the dK/dV pass: a run of cache rows that share one weight.
@@ -48,10 +48,10 @@ struct SegTable {
   int tile_begin[kMaxSegments + 1];  // prefix sum of column tiles, in units of the launcher's tile width
 };
 
-// What launch_dq_f32 leaves for launch_dkdv_f32
-struct F32Pending {
+// What launch_dq_f32 / launch_dq_bf16 leave for the dK/dV launcher that follows
+struct PendingDq {
   bool dq = false;
-  SegTable runs;
+  SegTable runs;   // fp32 only
 };
 
 // Runs of query rows of the dK/dV pass in the transposed order: rows [begin, end) relative to the call's first
@@ -147,7 +147,7 @@ struct SharePlan {
 };                                    // also the first slot of partial sums
 
 // Iterations of list position i: iters(i), not increasing.  Times in microseconds, as measured: a workgroup takes
-// 9 + 1.2 per iteration when the chip is not full, a merge 4 + 0.03 per slot.
+// 8 + 1.6 per iteration, a merge 4 + 0.03 per slot.
 template <typename F>
 inline SharePlan share_plan(int n_units, int n_ctiles, int G, int n_rows, int slots, const F& iters) {
   SharePlan sp;
@@ -158,7 +158,7 @@ inline SharePlan share_plan(int n_units, int n_ctiles, int G, int n_rows, int sl
   if (tail == 0 || slots < 2 * n_units) return sp;
   const int n = tp.hs > 1 ? tp.n_tiles : ((int64_t)n_units * n_ctiles < round ? n_ctiles : (tail + n_units - 1) / n_units);
   if (n > kMaxEntries) return sp;
-  const float kWg = 9.f, kIter = 1.2f, kMerge = 4.f, kSlot = 0.03f;
+  const float kWg = 8.f, kIter = 1.6f, kMerge = 4.f, kSlot = 0.03f;
   const int most = iters(n_ctiles - n);
   int best = 0;
   float best_t = 0.f;
@@ -203,6 +203,13 @@ inline SharePlan share_plan(int n_units, int n_ctiles, int G, int n_rows, int sl
   return sp;
 }
 
+// Partial results of a backward call (partial dQ, shared-out column tiles): no more than this is used, whatever the workspace
+// holds, so that a call's plan, and with it the order of its sums, does not depend on the workspace.
+constexpr size_t kPartBytes = (size_t)38 << 20;
+
+// gK/gV of the shared-out column tiles from their partial sums
+void launch_tail_merge(const AttnParams& p, const SegTable& seg, float* part, const SharePlan& plan, hipStream_t s);
+
 // fp32 kernels (any head_dim that is a multiple of 4, up to 256)
 int launch_fwd_f32(const AttnParams& p, hipStream_t s);
 int launch_dq_f32(const AttnParams& p, const SegTable* dq_runs, hipStream_t s);   // dq_runs as in launch_dq_bf16
@@ -221,6 +228,9 @@ int launch_fwd_small_bf16(AttnParams p, int max_splits, hipStream_t s);
 // a positive weight (tile_begin is not used)
 int launch_dq_bf16(const AttnParams& p, const SegTable* dq_runs, hipStream_t s);
 int launch_dkdv_bf16(const AttnParams& p, const SegTable& seg, hipStream_t s);
+// dQ and dK/dV in one launch, where that is the faster way (launched says whether it was)
+int launch_bwd_fused_bf16(const AttnParams& p, const SegTable& seg, bool& launched, hipStream_t s);
+int launch_dq_bf16_now(const AttnParams& p, const SegTable* dq_runs, hipStream_t s);
 // the same with the query rows taken from runs (p.C: number of rows that may be addressed from p.q / p.d_o)
 int launch_dkdv_rows_bf16(const AttnParams& p, const SegTable& seg, const RowRuns& rr, hipStream_t s);
 #ifndef SECO_DKDV_COLS

@@ -142,6 +142,26 @@ def test_bf16_column_tiles_shared_out_by_query_rows(B, Hq, Hkv, N, C, sel):
     assert np.array_equal(got["gk"], again["gk"]) and np.array_equal(got["gv"], again["gv"])
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,N,C,sel", [
+    (1, 1, 1, 3, 2, None),             # two rows, then one against three columns
+    (1, 8, 8, 65, 33, None),           # a second stage of one row; ragged second chunk
+    (2, 8, 1, 257, 129, None),         # G = 8, two row tiles, one column behind a tile's edge
+    (1, 16, 2, 920, 184, None),        # tiles shared out by rows, row tiles divided by columns
+    (1, 32, 8, 1152, 128, [8, 3, 0]),  # chunk weights, segments that end inside a stage
+])
+def test_bf16_backward_of_a_short_call_in_one_launch(B, Hq, Hkv, N, C, sel):
+    """dQ and dK/dV workgroups in one grid, row statistics computed by both."""
+    x = small_layer(61, B, Hq, Hkv, N, 128, "bf16")
+    s = 1 / np.sqrt(128)
+    lam = float(np.float32(4 / 2))
+    if sel is None:
+        got, ref = run_layer(x, C, s, "bf16"), A.seco_layer(x["q"], x["k"], x["v"], x["do"], C, s)
+    else:
+        got = run_layer(x, C, s, "bf16", selected=sel, factor=lam)
+        ref = A.spaco_layer(x["q"], x["k"], x["v"], x["do"], C, s, sel, lam)
+    check(got, ref, "bf16", f"one launch {B,Hq,Hkv,N,C,sel}")
+
+
 def _one_call(dtype, D, N, C, j, weights=None, seed=40):
     x = small_layer(seed, 1, 4, 2, N, D, dtype)
     q, k, v, do = (to_dev(x[n], dtype) for n in ("q", "k", "v", "do"))
