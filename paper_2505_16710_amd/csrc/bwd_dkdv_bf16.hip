@@ -1,5 +1,8 @@
 // dK/dV of one chunk, bf16: the launch of the kernel in bwd_dkdv_body.h and the merge of shared-out column tiles.
+#include <algorithm>
+
 #include "bwd_dkdv_body.h"
+#include "merge_body.h"
 
 namespace seco {
 namespace {
@@ -19,83 +22,109 @@ __global__ __launch_bounds__(NCB * 128, 2) void dkdv_bf16_kernel(AttnParams p, S
     dkdv_bf16_body<NCB, RB, ROWS, 1>(p, seg, ts, rr, item, smem);
 }
 
-// gK/gV of the shared-out column tiles: g += w * (sum of the shares, in order).  One thread per four consecutive
-// elements of a (tile, dV or dK) pair.
 template <int COLS>
-__global__ __launch_bounds__(256) void dkdv_tail_merge_kernel(AttnParams p, SegTable seg, TailSplit ts, int n_units) {
-  constexpr int kBlocks = COLS * 128 / 4 / 256;       // workgroups per (tile, dV or dK)
-  typedef float f32x4 __attribute__((ext_vector_type(4)));
-  const int quad = (blockIdx.x % kBlocks) * 256 + threadIdx.x, role = (blockIdx.x / kBlocks) & 1;
-  const int st = blockIdx.x / (2 * kBlocks);          // shared tile, counted over all units
-  const int unit = st / ts.plan.n_shared, pos = st - unit * ts.plan.n_shared;
-  const int tile = seg.tile_begin[seg.n] - ts.plan.n_tiles + pos;
-  int si = 0;
-  while (si + 1 < seg.n && tile >= seg.tile_begin[si + 1]) ++si;
-  const int row = seg.col_begin[si] + (tile - seg.tile_begin[si]) * COLS + quad / 32;
-  if (row >= seg.col_end[si]) return;
-  const float wf = role == 0 ? seg.weight[si] : seg.weight[si] * p.scale;
-  const int kvh = unit % p.Hkv, b = unit / p.Hkv;
-  float* g = (role == 0 ? p.gv : p.gk) + b * p.gs[0] + kvh * p.gs[1] + (int64_t)row * p.gs[2] + (quad % 32) * 4;
-  const f32x4 old = *reinterpret_cast<const f32x4*>(g);
-  const int n_slots = ts.plan.first[ts.plan.n_shared], slot = ts.plan.first[pos], hs = ts.plan.first[pos + 1] - slot;
-  const float* src = ts.part + (((int64_t)unit * n_slots + slot) * 2 + role) * (int64_t)(COLS * 128) + (int64_t)quad * 4;
-  f32x4 sum = {0.f, 0.f, 0.f, 0.f};
-  for (int h = 0; h < hs; h += 4) {                   // four shares in flight; past the last one: its address again, dropped
-    f32x4 x[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) x[i] = *reinterpret_cast<const f32x4*>(src + (int64_t)min(h + i, hs - 1) * 2 * COLS * 128);
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      if (h + i < hs) sum += x[i];
-  }
-  *reinterpret_cast<f32x4*>(g) = old + wf * sum;
+__global__ __launch_bounds__(256) void dkdv_tail_merge_kernel(AttnParams p, SegTable seg, TailSplit ts) {
+  tail_merge_body<COLS>(p, seg, ts, blockIdx.x);
 }
 
-}  // namespace
+using Cfg = DkdvCfg<kColTileBf16 / 32, SECO_DKDV_RB>;
+constexpr size_t kSlotBytes = (size_t)2 * kColTileBf16 * 128 * sizeof(float);
+int slots_in(size_t bytes) { return (int)std::min(bytes / kSlotBytes, (size_t)device_cus()); }
 
-void launch_tail_merge(const AttnParams& p, const SegTable& seg, float* part, const SharePlan& plan, hipStream_t s) {
-  const int n_units = p.Hkv * p.B;
-  TailSplit ts;
-  ts.part = part;
-  ts.plan = plan;
-  hipLaunchKernelGGL(dkdv_tail_merge_kernel<kColTileBf16>, dim3((unsigned)(n_units * plan.n_shared * 2 * (kColTileBf16 / 8))),
-                     dim3(256), 0, s, p, seg, ts, n_units);
-}
-
-template <int NCB, int RB, bool ROWS>
-int launch_cfg(const AttnParams& p, const SegTable& seg, const RowRuns& rr, hipStream_t s) {
-  using Cfg = DkdvCfg<NCB, RB>;
-  const int n_units = p.Hkv * p.B, n_ctiles = seg.tile_begin[seg.n];
-  const TailSplit ts = tail_split<Cfg, ROWS>(p, seg, rr, n_units, p.tail_part, p.tail_slots);
-  const int total = n_units * (n_ctiles - ts.plan.n_tiles + ts.plan.n_entries);
-  auto kern = dkdv_bf16_kernel<NCB, RB, ROWS>;
+template <bool ROWS>
+int launch(const AttnParams& p, const SegTable& seg, const TailSplit& ts, const RowRuns& rr, hipStream_t s) {
+  const int total = p.Hkv * p.B * (seg.tile_begin[seg.n] - ts.plan.n_tiles + ts.plan.n_entries);
+  auto kern = dkdv_bf16_kernel<kColTileBf16 / 32, SECO_DKDV_RB, ROWS>;
   static std::atomic<uint64_t> ready{0};
   if (!allow_lds(ready, reinterpret_cast<const void*>(kern), Cfg::kSmemBytes)) return SECO_ERR_LAUNCH;
   {
     ProfScope prof(kKernelDkdv, s);   // the merge of the divided tiles counts as part of the dK/dV pass
     hipLaunchKernelGGL(kern, dim3(xcd_grid(total)), dim3(Cfg::kThreads), Cfg::kSmemBytes, s, p, seg, ts, rr, total);
-    if (ts.plan.n_shared > 0) launch_tail_merge(p, seg, ts.part, ts.plan, s);
+    if (ts.plan.n_shared > 0)
+      hipLaunchKernelGGL(dkdv_tail_merge_kernel<kColTileBf16>, dim3(tail_merge_grid<kColTileBf16>(p, ts)), dim3(256), 0, s, p, seg, ts);
   }
   return launch_status();
 }
 
-int launch_dkdv_bf16(const AttnParams& p, const SegTable& seg, hipStream_t s) {
-  if (p.pending && p.pending->dq) {
-    p.pending->dq = false;
-    bool launched = false;
-    int rc = launch_bwd_fused_bf16(p, seg, launched, s);
-    if (rc || launched) return rc;
-    if ((rc = launch_dq_bf16_now(p, nullptr, s))) return rc;
-  }
-  if (seg.tile_begin[seg.n] == 0) return SECO_OK;
+// Both passes of a dense call: in one launch with dq_splits workgroups per row tile for dQ (0: one after the other), and
+// the column tiles that are shared out.
+struct BwdPlan {
+  int dq_splits;
+  bool kv_first;
+  TailSplit ts;
+};
+// One launch is taken when all workgroups of both passes fit the chip at one per CU and the longer pass, with the extra
+// work, is expected to end before the two would one after the other: with more workgroups than CUs the two halves of
+// the grid would queue behind each other on some CUs (16/2 heads, chunk 704 at 5632: 7% slower in one launch).  The passes
+// divide the CUs: for every number of shares of a dQ row tile the column tiles are shared out over the rest.  Times in
+// microseconds as measured: a dQ workgroup 7.5 + 2.5 per tile of 128 cache rows, a dK/dV workgroup that computes its row
+// statistics 8.5 + 1.8 per iteration.
+BwdPlan plan_bwd(const AttnParams& p, const SegTable& seg) {
+  const int cus = device_cus(), n_units = p.B * p.Hkv, n_ctiles = seg.tile_begin[seg.n];
   RowRuns none;
   none.n = 0;
-  return launch_cfg<kColTileBf16 / 32, SECO_DKDV_RB, false>(p, seg, none, s);
+  const IterRuns runs = tile_iterations<Cfg, false>(p, seg, none);
+  BwdPlan best;
+  best.dq_splits = 0;
+  best.kv_first = true;
+  best.ts.part = p.tail_part;
+  float kv_alone = 0.f;
+  best.ts.plan = share_plan(runs, n_units, n_ctiles, p.G, p.C, slots_in(p.tail_bytes), kv_alone);
+  const SplitPlan sp = split_plan(p.B, p.Hkv, p.G, p.C);
+  if (!p.pending || (int64_t)n_units * n_ctiles >= cus || sp.items >= cus) return best;
+  const int tiles = (p.q_start + p.C + 127) / 128;
+  auto dq_wgs = [&](int n) { return n > 1 ? sp.items * n : p.B * p.Hq * ((p.C + 127) / 128); };
+  auto dq_time = [&](int n) { return 7.5f + 2.5f * ((tiles + n - 1) / n); };
+  auto merge_time = [&](int n) { return n > 1 ? 4.f + 0.02f * dq_wgs(n) : 0.f; };
+  float best_t = (dq_wgs(p.n_splits) + cus - 1) / cus * dq_time(p.n_splits) + merge_time(p.n_splits) + kv_alone + 2.f;
+  int per = 0;
+  const size_t dq_bytes = (size_t)p.B * p.Hq * p.C * 128 * sizeof(float);
+  for (int n = 1; n <= p.n_splits && dq_wgs(n) + n_units * n_ctiles <= cus; ++n) {
+    const size_t used = n > 1 ? (n * dq_bytes + 255) / 256 * 256 : 0;
+    if (used > p.tail_bytes) break;
+    const ShareChoice c = choose_shares(runs, n_ctiles, n_units, cus - dq_wgs(n), slots_in(p.tail_bytes - used), 1, true, 8.5f, 1.8f);
+    // (both merges are one launch)
+    const float t = std::max(dq_time(n), c.longest) + (c.time - c.longest) + (n > 1 ? merge_time(n) - (c.per ? 4.f : 0.f) : 0.f);
+    if (c.time >= 0.f && t < best_t) {
+      best_t = t;
+      best.dq_splits = n;
+      best.kv_first = c.longest >= dq_time(n);
+      best.ts.part = p.tail_part + used / sizeof(float);
+      per = c.per;
+    }
+  }
+  if (best.dq_splits > 0) best.ts.plan = make_shares(runs, n_ctiles, per);
+  return best;
+}
+
+}  // namespace
+
+int launch_dkdv_bf16(const AttnParams& p, const SegTable& seg, hipStream_t s) {
+  const bool dq = p.pending && p.pending->dq;
+  if (dq) p.pending->dq = false;
+  if (seg.tile_begin[seg.n] == 0) return dq ? launch_dq_bf16_now(p, nullptr, s) : SECO_OK;
+  // (where dQ ran already, over selected columns, the sums are still divided as they would be with it)
+  const BwdPlan plan = plan_bwd(p, seg);
+  if (dq && plan.dq_splits > 0) {
+    AttnParams pf = p;
+    pf.n_splits = plan.dq_splits;
+    return launch_bwd_fused_bf16(pf, seg, plan.ts, plan.kv_first, s);
+  }
+  int rc = dq ? launch_dq_bf16_now(p, nullptr, s) : SECO_OK;
+  RowRuns none;
+  none.n = 0;
+  return rc ? rc : launch<false>(p, seg, plan.ts, none, s);
 }
 
 int launch_dkdv_rows_bf16(const AttnParams& p, const SegTable& seg, const RowRuns& rr, hipStream_t s) {
   if (seg.tile_begin[seg.n] == 0 || rr.n == 0) return SECO_OK;
-  return launch_cfg<kColTileBf16 / 32, SECO_DKDV_RB, true>(p, seg, rr, s);
+  int n_rows = 0;
+  for (int i = 0; i < rr.n; ++i) n_rows += rr.end[i] - rr.begin[i];
+  TailSplit ts;
+  ts.part = p.tail_part;
+  float time;
+  ts.plan = share_plan(tile_iterations<Cfg, true>(p, seg, rr), p.B * p.Hkv, seg.tile_begin[seg.n], p.G, n_rows, slots_in(p.tail_bytes), time);
+  return launch<true>(p, seg, ts, rr, s);
 }
 
 }  // namespace seco

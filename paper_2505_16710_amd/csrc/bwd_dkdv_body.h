@@ -79,13 +79,6 @@ struct DkdvCfg {
   static constexpr int kCols = NCB * 32;                                // cache rows per workgroup
 };
 
-// The column tiles at the end of every (batch, KV head) that are shared out among several workgroups (share_plan): a
-// share's sums go to part[unit][workgroup of the list][dV, dK][cache row of the tile][128] instead of gK/gV.
-struct TailSplit {
-  float* part;
-  SharePlan plan;
-};
-
 // (RB is fixed to 2 by the hand-pipelined main loop.)
 // ROWS: the query rows are taken from a table of runs (rows relative to p.q_start, each run with one weight whose
 // log2 is added to -LSE, i.e. its probabilities are scaled by the weight) instead of being all p.C rows with weight 1.
@@ -613,14 +606,9 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
   }
 }
 
-// Host side: which column tiles of a call are shared out, given room for `slots` partial sums at `part`
+// Host side: iterations of the last column tiles
 template <typename Cfg, bool ROWS>
-TailSplit tail_split(const AttnParams& p, const SegTable& seg, const RowRuns& rr, int n_units, float* part, int slots) {
-  int n_rows = p.C;
-  if (ROWS) {
-    n_rows = 0;
-    for (int i = 0; i < rr.n; ++i) n_rows += rr.end[i] - rr.begin[i];
-  }
+IterRuns tile_iterations(const AttnParams& p, const SegTable& seg, const RowRuns& rr) {
   // iterations of a column tile (as the kernel counts them)
   auto iters = [&](int tile) {
     int si = 0;
@@ -633,10 +621,7 @@ TailSplit tail_split(const AttnParams& p, const SegTable& seg, const RowRuns& rr
       if (rr.end[i] > r0) n += (rr.end[i] - (rr.begin[i] > r0 ? rr.begin[i] : r0) + Cfg::kBQ - 1) / Cfg::kBQ;
     return n * p.G;
   };
-  TailSplit ts;
-  ts.part = part;
-  ts.plan = share_plan(n_units, seg.tile_begin[seg.n], p.G, n_rows, slots, iters);
-  return ts;
+  return iter_runs(seg.tile_begin[seg.n], iters);
 }
 
 }  // namespace

@@ -1,6 +1,7 @@
 // Bandwidth-bound helpers: KV-gradient buffer zero / axpy (the gradient relay of the
 // paper's appendix listing, "grad + base * scaler") and the softmax-gradient row term
 // delta = rowsum(dO * O); and the merge steps of the split forward / dQ kernels (short chunks).
+#include "merge_body.h"
 #include "seco_internal.h"
 
 namespace seco {
@@ -63,57 +64,6 @@ __global__ __launch_bounds__(256) void kvgrad_kernel(float* __restrict__ dst_a, 
   });
 }
 
-// Merge of the partial rows of the split kernels (n_splits <= 64 of 128 fp32 each).  GP groups of 32 threads (a thread:
-// 4 consecutive head_dim elements) share a row, each taking the splits sp = group, group + GP, .., at most 8 of them, so
-// that all its loads are in flight at once; the groups' sums meet in LDS and are added in group order (fixed order:
-// reproducible).  What bounds it is the partials' traffic (33 MB for a 32-row chunk of 32 heads in 64 splits): with one
-// group per row and a loop over the splits every load waited for the one before, 23 us for that chunk; now 8.
-// Launchers choose GP = the power of two from which a group has at most K = 8 splits (K less for the fewest splits).
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-// requests the group's partials (clamped, never behind a condition that differs over the lanes: the compiler would wait for
-// each load before the next one)
-template <int GP, int K>
-__device__ __forceinline__ void load_partials(const float* part, int n_splits, int64_t R, int64_t rowid, int group, int d4,
-                                              f32x4 (&x)[K]) {
-#pragma unroll
-  for (int k = 0; k < K; ++k)
-    x[k] = *reinterpret_cast<const f32x4*>(part + (min(group + k * GP, n_splits - 1) * R + rowid) * 128 + 4 * d4);
-}
-template <int GP, int K, typename Weight>
-__device__ __forceinline__ bool merge_partials(const f32x4 (&x)[K], int n_splits, int group, Weight weight, float4& acc) {
-  __shared__ float4 sh[GP > 1 ? 256 : 1];
-  acc = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-  for (int k = 0; k < K; ++k) {
-    const float w = weight(k);                     // (a cross-lane read: every lane takes part)
-    if (group + k * GP < n_splits && w != 0.f) {   // weight 0: an empty partial, never written
-      acc.x += w * x[k][0];
-      acc.y += w * x[k][1];
-      acc.z += w * x[k][2];
-      acc.w += w * x[k][3];
-    }
-  }
-  if (GP == 1) return true;
-  sh[threadIdx.x] = acc;
-  __syncthreads();
-  if (group != 0) return false;
-#pragma unroll
-  for (int k = 1; k < GP; ++k) {
-    const float4 y = sh[threadIdx.x + 32 * k];     // the groups of a row are adjacent in the workgroup
-    acc.x += y.x;
-    acc.y += y.y;
-    acc.z += y.z;
-    acc.w += y.w;
-  }
-  return true;
-}
-// element offset of row `rowid` = (b * Hq + h) * C + row of a strided [B, Hq, C, 128] tensor
-__device__ __forceinline__ int64_t row_offset(const AttnParams& p, int64_t rowid, const int64_t s[3]) {
-  const int bh = (int)(rowid / p.C), row = (int)(rowid - (int64_t)bh * p.C), b = bh / p.Hq;
-  return b * s[0] + (bh - b * p.Hq) * s[1] + (int64_t)row * s[2];
-}
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-
 //   M = max m_s,  L = sum l_s 2^(m_s - M),  O = sum o_s 2^(m_s - M) / L,  LSE = (M + log2 L) ln 2.
 // Lane i of a group loads (m, l) of splits i and i + 32 once; max, sum and the per-split weights then travel by
 // cross-lane shuffles.
@@ -151,21 +101,8 @@ __global__ __launch_bounds__(256) void fwd_merge_kernel(AttnParams p) {
   if (l32 == 0) p.lse[rowid] = (M + __builtin_amdgcn_logf(L)) * 0.6931471805599453f;
 }
 
-// Merge of the split dQ: dQ = scale * (sum of the partials), rounded to bf16.
 template <int GP, int K>
-__global__ __launch_bounds__(256) void dq_merge_kernel(AttnParams p) {
-  const int64_t R = (int64_t)p.B * p.Hq * p.C;
-  const int group = (threadIdx.x >> 5) % GP, l32 = threadIdx.x & 31;
-  const int64_t mine = (int64_t)blockIdx.x * (8 / GP) + (threadIdx.x >> 5) / GP;
-  const int64_t rowid = min(mine, R - 1);
-  f32x4 x[K];
-  load_partials<GP, K>(p.part, p.n_splits, R, rowid, group, l32, x);
-  float4 acc;
-  const bool store = merge_partials<GP, K>(x, p.n_splits, group, [](int) { return 1.f; }, acc);
-  if (!store || mine >= R) return;
-  const bf16x4 v = {(__bf16)(acc.x * p.scale), (__bf16)(acc.y * p.scale), (__bf16)(acc.z * p.scale), (__bf16)(acc.w * p.scale)};
-  *reinterpret_cast<bf16x4*>(static_cast<__bf16*>(p.d_q) + row_offset(p, rowid, p.qs) + 4 * l32) = v;
-}
+__global__ __launch_bounds__(256) void dq_merge_kernel(AttnParams p) { dq_merge_body<GP, K>(p, blockIdx.x); }
 
 // (Loads without a condition, on a clamped row: with one the compiler waited for each before it issued the next, 18.7 us
 // for 2 x 4 MiB.)

@@ -114,13 +114,10 @@ size_t tail_part_bytes(const seco_desc* d) {
 }
 size_t bwd_part_bytes(const seco_desc* d) { return std::max(split_part_bytes(d), tail_part_bytes(d)); }
 
-// partial dQ first, then the shared-out column tiles (p.n_splits is set)
 void use_tail_part(AttnParams& p, const seco_desc* d, size_t ws_bytes) {
   if (d->dtype != SECO_BF16) return;
-  const size_t room = std::min(ws_bytes - delta_bytes(d), kPartBytes);
-  const size_t dq = p.n_splits > 1 ? round256((size_t)p.n_splits * d->batch * d->n_q_heads * d->chunk_len * d->head_dim * sizeof(float)) : 0;
-  p.tail_slots = room > dq ? (int)std::min((room - dq) / kSlotBytes, (size_t)device_cus()) : 0;
-  p.tail_part = p.tail_slots > 0 ? p.part + dq / sizeof(float) : nullptr;
+  p.tail_bytes = std::min(ws_bytes - delta_bytes(d), kPartBytes);
+  p.tail_part = p.part;
 }
 
 int check_fwd_like(const seco_desc* d) {

@@ -27,7 +27,7 @@ struct AttnParams {
   float* part;       // split path: partial O (forward) or partial dQ (backward), fp32 [n_splits, B, Hq, C, D]
   float* part_ml;    // split path, forward: (reference max in log2 units, sum) per partial row, [n_splits, B, Hq, C, 2]
   float* tail_part;  // dK/dV pass: sums of the column tiles shared out among several workgroups (workspace), or NULL
-  int tail_slots;    // shares that fit there (2 x 128 x 128 floats each)
+  size_t tail_bytes; // room there
   int n_splits;      // > 1 selects the split path
   int Cpad;          // C rounded up to 32: rows per head in the packed row space of the split path
   int B, Hq, Hkv, D, C, q_start, G;
@@ -146,69 +146,111 @@ struct SharePlan {
   uint16_t first[kMaxEntries + 1];    // first workgroup of a list position; shared tiles come first, so for them it is
 };                                    // also the first slot of partial sums
 
-// Iterations of list position i: iters(i), not increasing.  Times in microseconds, as measured: a workgroup takes
-// 8 + 1.6 per iteration, a merge 4 + 0.03 per slot.
+// Iterations of the last n_tiles (at most kMaxEntries) column tiles of a (batch, KV head), as runs of equal numbers; they do
+// not increase (a tile behind the chunk's first row sees fewer rows), so there are few runs.
+struct IterRuns {
+  int n_tiles, n;
+  int iters[kMaxEntries], count[kMaxEntries];
+};
 template <typename F>
-inline SharePlan share_plan(int n_units, int n_ctiles, int G, int n_rows, int slots, const F& iters) {
-  SharePlan sp;
-  sp.n_tiles = sp.n_shared = sp.n_entries = 0;
-  const int round = device_cus();
-  const TailPlan tp = tail_plan(n_units, n_ctiles, G, n_rows);
-  const int tail = (int)((int64_t)n_units * n_ctiles % round);
-  if (tail == 0 || slots < 2 * n_units) return sp;
-  const int n = tp.hs > 1 ? tp.n_tiles : ((int64_t)n_units * n_ctiles < round ? n_ctiles : (tail + n_units - 1) / n_units);
-  if (n > kMaxEntries) return sp;
-  const float kWg = 8.f, kIter = 1.6f, kMerge = 4.f, kSlot = 0.03f;
-  const int most = iters(n_ctiles - n);
-  int best = 0;
-  float best_t = 0.f;
+inline IterRuns iter_runs(int n_ctiles, const F& iters) {
+  IterRuns r;
+  r.n_tiles = n_ctiles < kMaxEntries ? n_ctiles : kMaxEntries;
+  r.n = 0;
+  for (int i = 0; i < r.n_tiles; ++i) {
+    const int it = iters(n_ctiles - r.n_tiles + i);
+    if (r.n > 0 && r.iters[r.n - 1] == it) {
+      ++r.count[r.n - 1];
+    } else {
+      r.iters[r.n] = it;
+      r.count[r.n++] = 1;
+    }
+  }
+  return r;
+}
+// f(iterations, tiles with that many) over the last n tiles
+template <typename F>
+inline void for_last(const IterRuns& r, int n, const F& f) {
+  int skip = r.n_tiles - n;
+  for (int i = 0; i < r.n; ++i) {
+    const int c = r.count[i] - (skip < r.count[i] ? skip : r.count[i]);
+    skip -= r.count[i] - c;
+    if (c > 0) f(r.iters[i], c);
+  }
+}
+
+// How to share out the last n tiles of every unit: the most iterations a workgroup gets (0: nothing is shared out), the
+// time that is expected to take and how much of it the longest workgroup takes.  Times in microseconds, as measured: a
+// workgroup takes wg + iter per iteration; partial sums 4 + 0.03 per share (written and read again) + 0.02 per tile.
+// fit: all workgroups of the list must run at once, on `cus` compute units.
+struct ShareChoice { int per; float time, longest; };
+inline ShareChoice choose_shares(const IterRuns& r, int n, int n_units, int cus, int slots, int min_ways, bool fit, float wg, float iter) {
   static const int ways[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32};
-  auto shares = [&](int i, int per) { return (iters(n_ctiles - n + i) + per - 1) / per; };
+  int most = 0;
+  for_last(r, n, [&](int it, int) { most = it > most ? it : most; });
+  ShareChoice best{0, -1.f, 0.f};
   for (int w : ways) {
-    if (w < tp.hs) continue;
+    if (w < min_ways) continue;
     const int per = (most + w - 1) / w;
     if (per < 2 && w > 1) break;
-    int entries = 0, shared = 0, n_over = 0;
+    int entries = 0, shared = 0, tiles = 0;
     float sum = 0.f, longest = 0.f;
-    for (int i = 0; i < n; ++i) {
-      int k = shares(i, per);
-      if (k < 1) k = 1;
-      if (k > 1) shared += k, ++n_over;
-      entries += k;
-      const int it = iters(n_ctiles - n + i);
-      sum += k * kWg + it * kIter;
-      const float t = kWg + (it + k - 1) / k * kIter;
+    for_last(r, n, [&](int it, int count) {
+      const int k = it > per ? (it + per - 1) / per : 1;
+      if (k > 1) shared += k * count, tiles += count;
+      entries += k * count;
+      sum += count * (k * wg + it * iter);
+      const float t = wg + (it + k - 1) / k * iter;
       if (t > longest) longest = t;
-    }
-    if (entries > kMaxEntries || shared * n_units > slots) break;
-    const float even = sum * n_units / round;
-    float t = entries * n_units <= round ? longest : even + 0.5f * longest > longest + kWg ? even + 0.5f * longest : longest + kWg;
-    if (n_over > 0) t += kMerge + kSlot * shared * n_units;
-    if (best == 0 || t < best_t) {
-      best = w;
-      best_t = t;
-    }
+    });
+    if (entries > kMaxEntries || shared * n_units > slots || (fit && entries * n_units > cus)) break;
+    const float even = sum * n_units / cus;
+    float t = entries * n_units <= cus ? longest : even + 0.5f * longest > longest + wg ? even + 0.5f * longest : longest + wg;
+    if (shared > 0) t += 4.f + (0.03f * shared + 0.02f * tiles) * n_units;
+    if (best.time < 0.f || t < best.time) best = ShareChoice{w > 1 ? per : 0, t, longest};
   }
-  if (best < 2) return sp;
-  const int per = (most + best - 1) / best;
-  sp.n_tiles = n;
-  for (int i = 0; i < n; ++i) {
-    int k = shares(i, per);
-    if (k < 1) k = 1;
-    if (k > 1) sp.n_shared = i + 1;
-    sp.first[i] = (uint16_t)sp.n_entries;
-    for (int j = 0; j < k; ++j) sp.tile_of[sp.n_entries++] = (uint8_t)i;
-  }
+  return best;
+}
+inline SharePlan make_shares(const IterRuns& r, int n, int per) {
+  SharePlan sp;
+  sp.n_tiles = sp.n_shared = sp.n_entries = 0;
+  if (per == 0) return sp;
+  for_last(r, n, [&](int it, int count) {
+    const int k = it > per ? (it + per - 1) / per : 1;
+    for (int c = 0; c < count; ++c) {
+      const int i = sp.n_tiles++;
+      if (k > 1) sp.n_shared = i + 1;
+      sp.first[i] = (uint16_t)sp.n_entries;
+      for (int j = 0; j < k; ++j) sp.tile_of[sp.n_entries++] = (uint8_t)i;
+    }
+  });
   sp.first[n] = (uint16_t)sp.n_entries;
   return sp;
+}
+// The column tiles at the end of every (batch, KV head) that are shared out among several workgroups: a share's sums go
+// to part[unit][workgroup of the list][dV, dK][cache row of the tile][128] instead of gK/gV.
+struct TailSplit {
+  float* part;
+  SharePlan plan;
+};
+constexpr float kDkdvWg = 8.f, kDkdvIter = 1.6f;
+// For a dK/dV pass that has the chip to itself; time: what it is expected to take from its last full round on
+inline SharePlan share_plan(const IterRuns& r, int n_units, int n_ctiles, int G, int n_rows, int slots, float& time) {
+  const int cus = device_cus();
+  const int64_t items = (int64_t)n_units * n_ctiles;
+  const int tail = (int)(items % cus);
+  const TailPlan tp = tail_plan(n_units, n_ctiles, G, n_rows);
+  const int n = tp.hs > 1 ? tp.n_tiles : items < cus ? n_ctiles : (tail + n_units - 1) / n_units;
+  time = kDkdvWg + kDkdvIter * r.iters[0];
+  if (tail == 0 || slots < 2 * n_units || n > r.n_tiles) return make_shares(r, 0, 0);
+  const ShareChoice c = choose_shares(r, n, n_units, cus, slots, tp.hs > 1 ? tp.hs : 1, false, kDkdvWg, kDkdvIter);
+  if (c.time >= 0.f) time = c.time;
+  return make_shares(r, n, c.per);
 }
 
 // Partial results of a backward call (partial dQ, shared-out column tiles): no more than this is used, whatever the workspace
 // holds, so that a call's plan, and with it the order of its sums, does not depend on the workspace.
 constexpr size_t kPartBytes = (size_t)38 << 20;
-
-// gK/gV of the shared-out column tiles from their partial sums
-void launch_tail_merge(const AttnParams& p, const SegTable& seg, float* part, const SharePlan& plan, hipStream_t s);
 
 // fp32 kernels (any head_dim that is a multiple of 4, up to 256)
 int launch_fwd_f32(const AttnParams& p, hipStream_t s);
@@ -228,8 +270,8 @@ int launch_fwd_small_bf16(AttnParams p, int max_splits, hipStream_t s);
 // a positive weight (tile_begin is not used)
 int launch_dq_bf16(const AttnParams& p, const SegTable* dq_runs, hipStream_t s);
 int launch_dkdv_bf16(const AttnParams& p, const SegTable& seg, hipStream_t s);
-// dQ and dK/dV in one launch, where that is the faster way (launched says whether it was)
-int launch_bwd_fused_bf16(const AttnParams& p, const SegTable& seg, bool& launched, hipStream_t s);
+// dQ (p.n_splits workgroups per row tile) and dK/dV in one launch
+int launch_bwd_fused_bf16(const AttnParams& p, const SegTable& seg, const TailSplit& ts, bool kv_first, hipStream_t s);
 int launch_dq_bf16_now(const AttnParams& p, const SegTable* dq_runs, hipStream_t s);
 // the same with the query rows taken from runs (p.C: number of rows that may be addressed from p.q / p.d_o)
 int launch_dkdv_rows_bf16(const AttnParams& p, const SegTable& seg, const RowRuns& rr, hipStream_t s);

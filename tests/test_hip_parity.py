@@ -147,6 +147,7 @@ def test_bf16_column_tiles_shared_out_by_query_rows(B, Hq, Hkv, N, C, sel):
     (1, 8, 8, 65, 33, None),           # a second stage of one row; ragged second chunk
     (2, 8, 1, 257, 129, None),         # G = 8, two row tiles, one column behind a tile's edge
     (1, 16, 2, 920, 184, None),        # tiles shared out by rows, row tiles divided by columns
+    (1, 8, 2, 1089, 512, None),        # the same, the last chunk one stage and one row
     (1, 32, 8, 1152, 128, [8, 3, 0]),  # chunk weights, segments that end inside a stage
 ])
 def test_bf16_backward_of_a_short_call_in_one_launch(B, Hq, Hkv, N, C, sel):
