@@ -34,6 +34,7 @@ struct Param {
 
 struct Layer {
   Param norm1, norm2, wqkv, wo, w1, w2;
+  int64_t ff = 0;                                // width of this layer's MLP
   float *part1 = nullptr, *part2 = nullptr;      // partial sums of the gains' gradients
   Tensor k, v, gk, gv;                           // KV cache and KV-gradient buffers, [B, Hkv, N, D]
   std::map<int64_t, std::pair<Tensor, Tensor>> kept;   // q_start -> (O rows [B, C, Hq, D], LSE) of stage 1
@@ -50,7 +51,7 @@ struct Saved {
 enum Keep { kCompute = 0, kStore = 1, kReuse = 2 };
 
 struct Step {
-  int64_t L, Hq, Hkv, D, B, N, dm, ff, V, W, HD;   // W: columns of the joint projection
+  int64_t L, Hq, Hkv, D, B, N, dm, ff, V, W, HD;   // ff: the widest MLP; W: columns of the joint projection
   double scale, rope_base;                         // rope_base 0: no rotary embedding
   int dtype;
   size_t e;                                        // bytes per element
@@ -277,8 +278,8 @@ struct Step {
       sv.h2 = rows(dm);
       sv.r2 = stats();
       norm(sv.x1, y, l.norm2, sv.x2, sv.h2, sv.r2);
-      sv.u = rows(ff);
-      sv.a = rows(ff);
+      sv.u = rows(l.ff);
+      sv.a = rows(l.ff);
       mm_silu(sv.u, sv.a, sv.h2, l.w1, R);
       mm(y, sv.a, l.w2, R);
       have_y = true;
@@ -401,8 +402,9 @@ PyObject* step_new(PyObject* const* a) {
     l.wo = param(par(p0 + 5));
     l.w1 = param(par(p0 + 6));
     l.w2 = param(par(p0 + 7));
-    st->ff = std::max(st->ff, l.w1.w.size(1));
-    if (l.wqkv.w.size(1) != st->W || l.w1.w.size(1) != st->ff || l.w2.w.size(0) != st->ff || l.wo.w.size(0) != st->HD)
+    l.ff = l.w1.w.size(1);
+    st->ff = std::max(st->ff, l.ff);
+    if (l.wqkv.w.size(1) != st->W || l.w2.w.size(0) != l.ff || l.wo.w.size(0) != st->HD)
       raise(PyExc_ValueError, "parameter shapes do not fit the decoder's");
     for (const Tensor* t : {&l.norm1.w, &l.norm2.w, &l.wqkv.w, &l.wo.w, &l.w1.w, &l.w2.w})
       if (t->scalar_type() != em.scalar_type()) raise(PyExc_TypeError, "parameters must share one dtype");

@@ -175,3 +175,16 @@ def test_spaco_step_with_the_transposed_backward_order_matches_oracle():
     _, g_ref = om.spaco_grads(cfg, p64, tok, tgt, C, sel, f)
     _, g = dec.step(tok.to(DEV), tgt.to(DEV), C, selected=sel, factor=f, transposed_backward=True)
     _compare(g_ref, g, tol)
+
+
+@pytest.mark.parametrize("widths", [(96, 160, 64), (160, 64, 96)])
+def test_step_with_mlp_widths_that_differ_between_layers(widths):
+    p64, dec, tok, tgt = _setup(F32_CFG, 29, 1, 64, torch.float32)
+    g = torch.Generator().manual_seed(30)
+    for l, ff in enumerate(widths):
+        for n, shape in ((f"l{l}.w1", (F32_CFG.d_model, ff)), (f"l{l}.w2", (ff, F32_CFG.d_model))):
+            p64[n] = (torch.randn(shape, generator=g, dtype=torch.float64) * shape[0] ** -0.5).requires_grad_()
+            dec.p[n] = p64[n].detach().to(torch.float32).to(DEV).requires_grad_()
+    _, g_ref = om.monolithic_grads(F32_CFG, p64, tok, tgt)
+    _, g = dec.step(tok.to(DEV), tgt.to(DEV), 24)
+    _compare(g_ref, g, 5e-4)
