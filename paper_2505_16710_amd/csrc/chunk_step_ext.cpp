@@ -356,6 +356,16 @@ Param param(PyObject* o) {
   return p;
 }
 
+// The kernels take sizes from the first parameters and addresses on trust, so every matrix is compared with what will be
+// assumed of it before anything is allocated or launched.  rows, cols: -1 leaves that size free (at least `least`).
+void check_matrix(const Tensor& t, const char* name, int64_t rows, int64_t cols, int64_t least = 1) {
+  auto fits = [&](int i, int64_t n) { return n < 0 ? t.size(i) >= least : t.size(i) == n; };
+  if (t.dim() == 2 && fits(0, rows) && fits(1, cols)) return;
+  PyErr_Format(PyExc_ValueError, "the shape of %s does not fit the decoder's: expected [%lld, %lld] (-1: any size)", name,
+               (long long)rows, (long long)cols);
+  throw Raised{};
+}
+
 // (config, params): config = (n_layers, Hq, Hkv, D, scale, rope_base or None, B, N, chunk rows of stage 1, of stage 2, transposed);
 // params = [emb, head, norm_f, then norm1, norm2, wq, wk, wv, wo, w1, w2 of every layer] -> step
 PyObject* step_new(PyObject* const* a) {
@@ -373,17 +383,30 @@ PyObject* step_new(PyObject* const* a) {
   const int64_t c1 = integer(cfg(8)), c2 = integer(cfg(9));
   const bool transposed = PyObject_IsTrue(cfg(10)) == 1;
   if (PyList_GET_SIZE(a[1]) != 3 + 8 * st->L) raise(PyExc_ValueError, "wrong number of parameters");
+  if (st->L < 0 || st->Hq < 1 || st->Hkv < 1 || st->D < 1 || st->B < 1 || st->N < 1 || c1 < 1 || c2 < 1)
+    raise(PyExc_ValueError, "sizes must be positive");
+  st->HD = st->Hq * st->D;
+  st->W = st->HD + 2 * st->Hkv * st->D;
   auto par = [&](int64_t i) { return PyList_GET_ITEM(a[1], i); };
+  check_matrix(tensor(par(0)), "emb", -1, -1);
+  st->dm = tensor(par(0)).size(1);
+  check_matrix(tensor(par(1)), "head", st->dm, -1);
+  for (int64_t i = 0; i < st->L; ++i) {
+    auto matrix = [&](int64_t k) -> const Tensor& { return tensor(par(3 + 8 * i + k)); };
+    check_matrix(matrix(2), "wq", st->dm, st->HD);
+    check_matrix(matrix(3), "wk", st->dm, st->Hkv * st->D);
+    check_matrix(matrix(4), "wv", st->dm, st->Hkv * st->D);
+    check_matrix(matrix(5), "wo", st->HD, st->dm);
+    check_matrix(matrix(6), "w1", st->dm, -1, 0);
+    check_matrix(matrix(7), "w2", matrix(6).size(1), st->dm);
+  }
   st->emb = param(par(0));
   st->head = param(par(1));
   st->norm_f = param(par(2));
   const Tensor& em = st->emb.w;
   st->dtype = dtype_code(em);
   st->e = em.element_size();
-  st->dm = em.size(1);
   st->V = st->head.w.size(1);
-  st->HD = st->Hq * st->D;
-  st->W = st->HD + 2 * st->Hkv * st->D;
   st->ff = 0;
   const at::TensorOptions f32 = st->opts().dtype(at::kFloat);
   st->parts = at::zeros({2 * st->L + 1, DEC_GAIN_BLOCKS, st->dm}, f32);
@@ -404,8 +427,6 @@ PyObject* step_new(PyObject* const* a) {
     l.w2 = param(par(p0 + 7));
     l.ff = l.w1.w.size(1);
     st->ff = std::max(st->ff, l.ff);
-    if (l.wqkv.w.size(1) != st->W || l.w2.w.size(0) != l.ff || l.wo.w.size(0) != st->HD)
-      raise(PyExc_ValueError, "parameter shapes do not fit the decoder's");
     for (const Tensor* t : {&l.norm1.w, &l.norm2.w, &l.wqkv.w, &l.wo.w, &l.w1.w, &l.w2.w})
       if (t->scalar_type() != em.scalar_type()) raise(PyExc_TypeError, "parameters must share one dtype");
     l.part1 = part(2 * i);

@@ -1,0 +1,54 @@
+"""What the training step refuses before it allocates or launches anything: its kernels take sizes and addresses on trust.
+Every call here gets host tensors and fails (no GPU needed)."""
+import pytest
+import torch
+
+from paper_2505_16710_amd import binding as B
+
+DM, V, HQ, HKV, D, FF = 64, 40, 2, 1, 128, (96, 160, 64)
+MATRICES = {"wq": (DM, HQ * D), "wk": (DM, HKV * D), "wv": (DM, HKV * D), "wo": (HQ * D, DM)}
+LAYER = ("norm1", "norm2", "wq", "wk", "wv", "wo", "w1", "w2")
+
+
+def _params(**replaced):
+    """[emb, head, norm_f, then the layers'] as step_new takes them; replaced: l1_wo=..., head=..."""
+    p = {"emb": torch.zeros(V, DM), "head": torch.zeros(DM, V), "norm_f": torch.ones(DM)}
+    for l, ff in enumerate(FF):
+        shapes = {"norm1": (DM,), "norm2": (DM,), **MATRICES, "w1": (DM, ff), "w2": (ff, DM)}
+        p.update({f"l{l}_{n}": torch.zeros(shapes[n]) for n in LAYER})
+    p = {n: t.to(torch.bfloat16) for n, t in p.items()}
+    assert set(replaced) <= set(p)
+    p.update(replaced)
+    return list(p.values())
+
+
+def _new(params, layers=3, tokens=64, chunk=32):
+    ext = B._ext or B._load_ext()
+    return ext.step_new((layers, HQ, HKV, D, D ** -0.5, None, 1, tokens, chunk, chunk, False), params)
+
+
+@pytest.mark.parametrize("name,shape", [
+    ("l1_wo", (HQ * D, DM + 8)), ("l1_wo", (HQ * D - 8, DM)), ("l2_w2", (FF[2], DM - 8)), ("l2_w2", (FF[2] + 8, DM)),
+    ("l0_w1", (DM + 8, FF[0])), ("l1_w1", (DM, FF[1] + 8)), ("l1_wq", (DM, HQ * D + 8)), ("l1_wk", (DM, HKV * D - 8)),
+    ("l0_wv", (DM - 8, HKV * D)), ("head", (DM + 8, V)), ("head", (DM,)), ("emb", (V, DM, 1)), ("emb", (V, DM - 8)),
+    ("l0_wq", (1, DM, HQ * D)), ("head", (DM, 0)), ("emb", (V, 0)),
+])
+def test_matrices_of_another_shape_are_refused(name, shape):
+    with pytest.raises(ValueError, match="shape of"):
+        _new(_params(**{name: torch.zeros(shape, dtype=torch.bfloat16)}))
+
+
+def test_projections_whose_widths_only_add_up_are_refused():
+    """wq narrower and wk wider by as much: the joint projection has the right width, its columns the wrong meaning."""
+    with pytest.raises(ValueError, match="shape of wq"):
+        _new(_params(l1_wq=torch.zeros(DM, HQ * D - 8, dtype=torch.bfloat16),
+                     l1_wk=torch.zeros(DM, HKV * D + 8, dtype=torch.bfloat16)))
+
+
+def test_sizes_that_are_not_positive_are_refused():
+    with pytest.raises(ValueError, match="positive"):
+        _new(_params(), chunk=0)
+    with pytest.raises(ValueError, match="positive"):
+        _new(_params(), tokens=0)
+    with pytest.raises(ValueError, match="number of parameters"):
+        _new(_params()[:-1])
