@@ -30,6 +30,8 @@ struct Param {
   Tensor w;              // contiguous
   bool wanted = false;
   Tensor grad;           // undefined until the first chunk adds to it
+  std::vector<int64_t> sizes;                    // gains: the parameter's own shape and type (w: dm elements, in the
+  at::ScalarType type = at::kFloat;              // type the norm computes its rows in)
 };
 
 struct Layer {
@@ -366,6 +368,26 @@ void check_matrix(const Tensor& t, const char* name, int64_t rows, int64_t cols,
   throw Raised{};
 }
 
+// The gain of a norm over rows of dm elements.  As it multiplies the rows by broadcasting, it may hold dm elements or
+// one, behind any number of leading ones, and be of a narrower type than the rows.
+Param gain(PyObject* o, const char* name, int64_t dm, at::ScalarType rows) {
+  const Tensor& t = tensor(o);
+  if ((t.numel() != dm && t.numel() != 1) || (t.dim() > 0 && t.size(-1) != t.numel())) {
+    PyErr_Format(PyExc_ValueError, "the shape of %s does not fit the decoder's: expected [%lld] or one element", name, (long long)dm);
+    throw Raised{};
+  }
+  if (at::promote_types(t.scalar_type(), rows) != rows) {
+    PyErr_Format(PyExc_TypeError, "parameters must share one dtype: %s is wider than the rows it multiplies", name);
+    throw Raised{};
+  }
+  Param p;
+  p.wanted = t.requires_grad();
+  p.sizes = t.sizes().vec();
+  p.type = t.scalar_type();
+  p.w = t.detach().to(rows).reshape({-1}).expand({dm}).contiguous();
+  return p;
+}
+
 // (config, params): config = (n_layers, Hq, Hkv, D, scale, rope_base or None, B, N, chunk rows of stage 1, of stage 2, transposed);
 // params = [emb, head, norm_f, then norm1, norm2, wq, wk, wv, wo, w1, w2 of every layer] -> step
 PyObject* step_new(PyObject* const* a) {
@@ -402,8 +424,8 @@ PyObject* step_new(PyObject* const* a) {
   }
   st->emb = param(par(0));
   st->head = param(par(1));
-  st->norm_f = param(par(2));
   const Tensor& em = st->emb.w;
+  st->norm_f = gain(par(2), "norm_f", st->dm, em.scalar_type());
   st->dtype = dtype_code(em);
   st->e = em.element_size();
   st->V = st->head.w.size(1);
@@ -416,8 +438,8 @@ PyObject* step_new(PyObject* const* a) {
   for (int64_t i = 0; i < st->L; ++i) {
     Layer& l = st->layers[i];
     const int64_t p0 = 3 + 8 * i;
-    l.norm1 = param(par(p0));
-    l.norm2 = param(par(p0 + 1));
+    l.norm1 = gain(par(p0), "norm1", st->dm, em.scalar_type());
+    l.norm2 = gain(par(p0 + 1), "norm2", st->dm, em.scalar_type());
     // one projection product (and one gradient product each way) for queries, keys and values instead of three
     const Tensor &q = tensor(par(p0 + 2)), &k = tensor(par(p0 + 3)), &v = tensor(par(p0 + 4));
     l.wqkv.w = at::cat({q.detach(), k.detach(), v.detach()}, 1);
@@ -520,13 +542,21 @@ PyObject* step_train(PyObject* const* a) {
 PyObject* step_grads(PyObject* const* a) {
   Step& st = step_of(a[0]);
   std::vector<Tensor> out = {st.emb.grad, st.head.grad};
-  const Tensor gains = st.parts.sum(1).to(st.emb.w.scalar_type());
-  auto gain = [&](int64_t i) { return st.trained ? gains.select(0, i) : Tensor(); };
-  out.push_back(gain(2 * st.L));
+  const Tensor sums = st.parts.sum(1), gains = sums.to(st.emb.w.scalar_type());
+  auto gain = [&](int64_t i, const Param& p) {
+    if (!st.trained) return Tensor();
+    if (p.type == gains.scalar_type() && p.sizes.size() == 1 && p.sizes[0] == st.dm) return gains.select(0, i);
+    Tensor g = sums.select(0, i);
+    int64_t n = 1;
+    for (int64_t x : p.sizes) n *= x;
+    if (n != st.dm) g = g.sum();
+    return g.to(p.type).reshape(p.sizes);
+  };
+  out.push_back(gain(2 * st.L, st.norm_f));
   for (int64_t i = 0; i < st.L; ++i) {
     Layer& l = st.layers[i];
-    out.push_back(gain(2 * i));
-    out.push_back(gain(2 * i + 1));
+    out.push_back(gain(2 * i, l.norm1));
+    out.push_back(gain(2 * i + 1, l.norm2));
     const int64_t kv = st.Hkv * st.D;
     const bool have = l.wqkv.grad.defined();
     out.push_back(have ? l.wqkv.grad.slice(1, 0, st.HD).contiguous() : Tensor());

@@ -52,3 +52,10 @@ def test_sizes_that_are_not_positive_are_refused():
         _new(_params(), tokens=0)
     with pytest.raises(ValueError, match="number of parameters"):
         _new(_params()[:-1])
+
+
+@pytest.mark.parametrize("name", ["l1_norm1", "l2_norm2", "norm_f"])
+@pytest.mark.parametrize("shape", [(DM - 1,), (DM + 8,), (2, DM), (DM, 1), (0,)])
+def test_gains_of_another_shape_are_refused(name, shape):
+    with pytest.raises(ValueError, match="shape of"):
+        _new(_params(**{name: torch.ones(shape, dtype=torch.bfloat16)}))

@@ -188,3 +188,19 @@ def test_step_with_mlp_widths_that_differ_between_layers(widths):
     _, g_ref = om.monolithic_grads(F32_CFG, p64, tok, tgt)
     _, g = dec.step(tok.to(DEV), tgt.to(DEV), 24)
     _compare(g_ref, g, 5e-4)
+
+
+def test_step_with_gains_of_one_element_or_a_narrower_type():
+    """A gain multiplies its rows by broadcasting: one element, leading ones and (in fp32) bf16 values are gains too."""
+    p64, dec, tok, tgt = _setup(F32_CFG, 31, 1, 64, torch.float32)
+    gains = {"l0.norm1": torch.tensor([0.75]), "l1.norm2": torch.tensor(1.25), "norm_f": torch.tensor([[[1.5]]]),
+             "l2.norm1": (1 + torch.arange(64) / 64).to(torch.bfloat16), "l0.norm2": (1 + torch.arange(64) / 64)[None, None]}
+    for n, t in gains.items():
+        p64[n] = t.to(torch.float64).requires_grad_()
+        dec.p[n] = t.to(DEV).requires_grad_()
+    _, g_ref = om.monolithic_grads(F32_CFG, p64, tok, tgt)
+    _, g = dec.step(tok.to(DEV), tgt.to(DEV), 24)
+    for n, t in gains.items():
+        assert g[n].shape == t.shape and g[n].dtype == t.dtype
+    _compare({n: t for n, t in g_ref.items() if n != "l2.norm1"}, g, 5e-4)
+    _compare({"l2.norm1": g_ref["l2.norm1"]}, g, 5e-4 + 2.0 ** -8)     # rounded to bf16 once more
