@@ -47,7 +47,7 @@ struct Layer {
 struct Saved {
   void *x1, *h1, *qkv, *o, *x2, *h2, *u, *a;
   float *r1, *lse, *r2;
-  Tensor keep_o, keep_lse;                       // O and LSE taken back from stage 1
+  Tensor keep_o, keep_lse;                       // O and LSE taken back from stage 1; wide tail: x1 and h1 of the final norm
 };
 
 enum Keep { kCompute = 0, kStore = 1, kReuse = 2 };
@@ -57,6 +57,8 @@ struct Step {
   double scale, rope_base;                         // rope_base 0: no rotary embedding
   int dtype;
   size_t e;                                        // bytes per element
+  int tail;                                        // type of the final norm's result, the head and the logits: dtype, or
+                                                   // fp32 behind a bf16 body when both parameters are fp32
   Param emb, head, norm_f;
   float* part_f = nullptr;
   Tensor parts;
@@ -67,25 +69,27 @@ struct Step {
 
   at::TensorOptions opts() const { return emb.w.options().requires_grad(false); }
   Tensor view(void* p, at::IntArrayRef sizes) { return at::from_blob(p, sizes, opts()); }
+  Tensor view(void* p, at::IntArrayRef sizes, const Param& w) { return at::from_blob(p, sizes, w.w.options().requires_grad(false)); }
 
   // ---- matrix products: the library's own kernel where it takes the operands, the framework's otherwise
-  bool own(int form, int64_t M, int64_t N_, int64_t K, int64_t lda, int64_t ldb, int64_t ldc) const {
-    return dtype == SECO_BF16 && lib.dec_gemm_supported(form, M, N_, K, lda, ldb, ldc);
+  // (operands have the type of the matrix)
+  static bool own(const Param& w, int form, int64_t M, int64_t N_, int64_t K, int64_t lda, int64_t ldb, int64_t ldc) {
+    return w.w.scalar_type() == at::kBFloat16 && lib.dec_gemm_supported(form, M, N_, K, lda, ldb, ldc);
   }
   // c[M, n] = a[M, K] w[K, n]
   void mm(void* c, void* a, const Param& w, int64_t M) {
     const int64_t K = w.w.size(0), n = w.w.size(1);
-    if (own(DEC_GEMM_NN, M, n, K, K, n, n)) {
+    if (own(w, DEC_GEMM_NN, M, n, K, K, n, n)) {
       check(lib.dec_gemm(DEC_GEMM_NN, DEC_GEMM_STORE, a, ptr(w.w), c, nullptr, M, n, K, K, n, n, s), "dec_gemm");
     } else {
-      Tensor out = view(c, {M, n});
-      at::mm_out(out, view(a, {M, K}), w.w);
+      Tensor out = view(c, {M, n}, w);
+      at::mm_out(out, view(a, {M, K}, w), w.w);
     }
   }
   // u = h w, a = silu(u)
   void mm_silu(void* u, void* a, void* h, const Param& w, int64_t M) {
     const int64_t K = w.w.size(0), n = w.w.size(1);
-    if (own(DEC_GEMM_NN, M, n, K, K, n, n)) {
+    if (own(w, DEC_GEMM_NN, M, n, K, K, n, n)) {
       check(lib.dec_gemm(DEC_GEMM_NN, DEC_GEMM_SILU, h, ptr(w.w), u, a, M, n, K, K, n, n, s), "dec_gemm");
     } else {
       mm(u, h, w, M);
@@ -95,11 +99,11 @@ struct Step {
   // d_x[M, K] = d_y[M, n] w[K, n]^T; u non-NULL: times silu'(u)
   void mm_bwd(void* dx, void* dy, const Param& w, int64_t M, void* u = nullptr) {
     const int64_t K = w.w.size(0), n = w.w.size(1);
-    if (own(DEC_GEMM_NT, M, K, n, n, n, K)) {
+    if (own(w, DEC_GEMM_NT, M, K, n, n, n, K)) {
       check(lib.dec_gemm(DEC_GEMM_NT, u ? DEC_GEMM_SILU_BWD : DEC_GEMM_STORE, dy, ptr(w.w), dx, u, M, K, n, n, n, K, s), "dec_gemm");
     } else {
-      Tensor out = view(dx, {M, K});
-      at::mm_out(out, view(dy, {M, n}), w.w.t());
+      Tensor out = view(dx, {M, K}, w);
+      at::mm_out(out, view(dy, {M, n}, w), w.w.t());
       if (u) check(lib.dec_silu_bwd(dtype, u, dx, M * K, s), "dec_silu_bwd");
     }
   }
@@ -108,13 +112,13 @@ struct Step {
     if (!w.wanted) return;
     const int64_t K = w.w.size(0), n = w.w.size(1);
     const bool first = !w.grad.defined();
-    if (first) w.grad = at::empty({K, n}, opts());
-    if (own(DEC_GEMM_TN, K, n, M, K, n, n)) {
+    if (first) w.grad = at::empty({K, n}, w.w.options().requires_grad(false));
+    if (own(w, DEC_GEMM_TN, K, n, M, K, n, n)) {
       check(lib.dec_gemm(DEC_GEMM_TN, first ? DEC_GEMM_STORE : DEC_GEMM_ADD, x, dy, ptr(w.grad), nullptr, K, n, M, K, n, n, s), "dec_gemm");
     } else if (first) {
-      at::mm_out(w.grad, view(x, {M, K}).t(), view(dy, {M, n}));
+      at::mm_out(w.grad, view(x, {M, K}, w).t(), view(dy, {M, n}, w));
     } else {
-      w.grad.addmm_(view(x, {M, K}).t(), view(dy, {M, n}));
+      w.grad.addmm_(view(x, {M, K}, w).t(), view(dy, {M, n}, w));
     }
   }
 
@@ -261,7 +265,7 @@ struct Step {
       check(lib.dec_add_rmsnorm(dtype, x, y, ptr(g.w), xo, h, r, R, dm, s), "dec_add_rmsnorm");
     };
     x0 = at::index(emb.w, {tok});
-    void *x = ptr(x0), *y = rows(dm), *logits = rows(V);
+    void *x = ptr(x0), *y = rows(dm), *logits = mem.take((size_t)(R * V) * head.w.element_size());
     bool have_y = false;
     const size_t base = mem.used;
     for (Layer& l : layers) {
@@ -290,10 +294,19 @@ struct Step {
     }
     if (!saved) mem.used = base;
     Saved sv{};
-    sv.x1 = have_y && saved ? rows(dm) : x;
-    sv.h1 = rows(dm);
     sv.r1 = stats();
-    norm(x, have_y ? y : nullptr, norm_f, sv.x1, sv.h1, sv.r1);
+    if (tail == dtype) {
+      sv.x1 = have_y && saved ? rows(dm) : x;
+      sv.h1 = rows(dm);
+      norm(x, have_y ? y : nullptr, norm_f, sv.x1, sv.h1, sv.r1);
+    } else {
+      const Tensor xr = view(x, {R, dm});
+      sv.keep_o = (have_y ? xr + view(y, {R, dm}) : xr).to(at::kFloat);   // (the residual sum rounds to the body's type)
+      sv.keep_lse = at::empty_like(sv.keep_o);
+      sv.x1 = ptr(sv.keep_o);
+      sv.h1 = ptr(sv.keep_lse);
+      check(lib.dec_add_rmsnorm(tail, sv.x1, nullptr, ptr(norm_f.w), nullptr, sv.h1, sv.r1, R, dm, s), "dec_add_rmsnorm");
+    }
     mm(logits, sv.h1, head, R);
     if (saved) saved->push_back(std::move(sv));
     return logits;
@@ -312,8 +325,15 @@ struct Step {
     const Saved fin = std::move(saved.back());
     saved.pop_back();
     add(head, fin.h1, d_logits, R);
-    mm_bwd(dh, d_logits, head, R);
-    norm_bwd(fin.x1, norm_f, fin.r1, part_f, true);
+    if (tail == dtype) {
+      mm_bwd(dh, d_logits, head, R);
+      norm_bwd(fin.x1, norm_f, fin.r1, part_f, true);
+    } else {
+      const Tensor dh_f = at::empty_like(fin.keep_o), dx_f = at::empty_like(fin.keep_o);
+      mm_bwd(ptr(dh_f), d_logits, head, R);
+      check(lib.dec_rmsnorm_bwd(tail, fin.x1, ptr(norm_f.w), fin.r1, ptr(dh_f), nullptr, ptr(dx_f), part_f, R, dm, s), "dec_rmsnorm_bwd");
+      view(dx, {R, dm}).copy_(dx_f);
+    }
     static const std::vector<float> none;
     for (int64_t i = L - 1; i >= 0; --i) {
       Layer& l = layers[i];
@@ -425,7 +445,12 @@ PyObject* step_new(PyObject* const* a) {
   st->emb = param(par(0));
   st->head = param(par(1));
   const Tensor& em = st->emb.w;
-  st->norm_f = gain(par(2), "norm_f", st->dm, em.scalar_type());
+  // (a wider gain makes the rows behind it wider)
+  const at::ScalarType tail = at::promote_types(em.scalar_type(), tensor(par(2)).scalar_type());
+  st->norm_f = gain(par(2), "norm_f", st->dm, tail);
+  if (st->head.w.scalar_type() != tail)
+    raise(PyExc_TypeError, "head must have the dtype of the rows of the final norm: the wider one of emb's and norm_f's");
+  st->tail = dtype_code(st->head.w);
   st->dtype = dtype_code(em);
   st->e = em.element_size();
   st->V = st->head.w.size(1);
@@ -466,7 +491,7 @@ PyObject* step_new(PyObject* const* a) {
   // activations: see forward / backward for what is taken (each piece rounded up to 256 bytes)
   const size_t e = st->e;
   auto layer_bytes = [&](int64_t R) { return (size_t)R * ((4 * st->dm + st->W + st->HD + 2 * st->ff) * e + 8 + 4 * st->Hq) + 12 * 256; };
-  auto other_bytes = [&](int64_t R) { return (size_t)R * ((3 * st->dm + st->V) * e + 4) + 8 * 256; };
+  auto other_bytes = [&](int64_t R) { return (size_t)R * (3 * st->dm * e + st->V * st->head.w.element_size() + 4) + 8 * 256; };
   auto bwd_bytes = [&](int64_t R) { return (size_t)R * (2 * st->dm + st->ff + st->HD + st->W) * e + 8 * 256; };
   const int64_t R1 = st->B * c1, R2 = st->B * c2;
   st->stage1.create(layer_bytes(R1) + other_bytes(R1), em);
@@ -494,7 +519,7 @@ PyObject* step_infer(PyObject* const* a) {
   st.stage1.used = 0;
   Tensor x0;
   void* logits = st.forward(tok, s1 - s0, s0, PyObject_IsTrue(a[6]) == 1 ? kStore : kCompute, st.stage1, nullptr, x0);
-  check(lib.dec_cross_entropy(st.dtype, logits, static_cast<const int64_t*>(ptr(tgt)), fptr(losses) + s0 * st.B, tok.numel(), st.V, st.s),
+  check(lib.dec_cross_entropy(st.tail, logits, static_cast<const int64_t*>(ptr(tgt)), fptr(losses) + s0 * st.B, tok.numel(), st.V, st.s),
         "dec_cross_entropy");
   Py_RETURN_NONE;
 }
@@ -532,7 +557,7 @@ PyObject* step_train(PyObject* const* a) {
   saved.reserve(st.L + 1);
   Tensor x0;
   void* logits = st.forward(tok, s1 - s0, s0, PyObject_IsTrue(a[5]) == 1 ? kReuse : kCompute, st.stage2, &saved, x0);
-  check(lib.dec_cross_entropy(st.dtype, logits, static_cast<const int64_t*>(ptr(tgt)), nullptr, tok.numel(), st.V, st.s), "dec_cross_entropy");
+  check(lib.dec_cross_entropy(st.tail, logits, static_cast<const int64_t*>(ptr(tgt)), nullptr, tok.numel(), st.V, st.s), "dec_cross_entropy");
   st.trained = true;
   st.backward(logits, tok, s1 - s0, s0, saved, st.stage2, w, wq, integer(a[7]));
   Py_RETURN_NONE;

@@ -59,3 +59,15 @@ def test_sizes_that_are_not_positive_are_refused():
 def test_gains_of_another_shape_are_refused(name, shape):
     with pytest.raises(ValueError, match="shape of"):
         _new(_params(**{name: torch.ones(shape, dtype=torch.bfloat16)}))
+
+
+@pytest.mark.parametrize("changed", [
+    {"head": torch.float32}, {"norm_f": torch.float32}, {"l1_norm1": torch.float32}, {"l0_wo": torch.float32},
+    {"l2_w2": torch.float32}, {"emb": torch.float32}, {"head": torch.float64, "norm_f": torch.float64},
+    {"l1_wq": torch.float32}, {"l1_wv": torch.float32},
+])
+def test_dtypes_that_the_products_cannot_mix_are_refused(changed):
+    names = ["emb", "head", "norm_f"] + [f"l{l}_{n}" for l in range(3) for n in LAYER]
+    p = dict(zip(names, _params()))
+    with pytest.raises(TypeError):
+        _new(_params(**{n: p[n].to(dt) for n, dt in changed.items()}))

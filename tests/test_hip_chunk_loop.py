@@ -204,3 +204,15 @@ def test_step_with_gains_of_one_element_or_a_narrower_type():
         assert g[n].shape == t.shape and g[n].dtype == t.dtype
     _compare({n: t for n, t in g_ref.items() if n != "l2.norm1"}, g, 5e-4)
     _compare({"l2.norm1": g_ref["l2.norm1"]}, g, 5e-4 + 2.0 ** -8)     # rounded to bf16 once more
+
+
+def test_step_with_an_fp32_final_norm_and_head_behind_a_bf16_body():
+    p64, dec, tok, tgt = _setup(BF16_CFG, 33, 2, 192, torch.bfloat16)
+    for n in ("norm_f", "head"):
+        p64[n] = om.init_params(BF16_CFG, 34)[n].detach().to(torch.float32).to(torch.float64).requires_grad_()
+        dec.p[n] = p64[n].detach().to(torch.float32).to(DEV).requires_grad_()
+    loss_ref, g_ref = om.monolithic_grads(BF16_CFG, p64, tok, tgt)
+    loss, g = dec.step(tok.to(DEV), tgt.to(DEV), 64)
+    assert g["head"].dtype == g["norm_f"].dtype == torch.float32
+    assert abs(loss - float(loss_ref)) < 1e-2 * abs(float(loss_ref))
+    _compare(g_ref, g, 6e-2)
