@@ -390,8 +390,7 @@ void check_matrix(const Tensor& t, const char* name, int64_t rows, int64_t cols,
 
 // The gain of a norm over rows of dm elements.  As it multiplies the rows by broadcasting, it may hold dm elements or
 // one, behind any number of leading ones, and be of a narrower type than the rows.
-Param gain(PyObject* o, const char* name, int64_t dm, at::ScalarType rows) {
-  const Tensor& t = tensor(o);
+void check_gain(const Tensor& t, const char* name, int64_t dm, at::ScalarType rows) {
   if ((t.numel() != dm && t.numel() != 1) || (t.dim() > 0 && t.size(-1) != t.numel())) {
     PyErr_Format(PyExc_ValueError, "the shape of %s does not fit the decoder's: expected [%lld] or one element", name, (long long)dm);
     throw Raised{};
@@ -400,6 +399,9 @@ Param gain(PyObject* o, const char* name, int64_t dm, at::ScalarType rows) {
     PyErr_Format(PyExc_TypeError, "parameters must share one dtype: %s is wider than the rows it multiplies", name);
     throw Raised{};
   }
+}
+Param gain(PyObject* o, int64_t dm, at::ScalarType rows) {
+  const Tensor& t = tensor(o);
   Param p;
   p.wanted = t.requires_grad();
   p.sizes = t.sizes().vec();
@@ -430,28 +432,38 @@ PyObject* step_new(PyObject* const* a) {
   st->HD = st->Hq * st->D;
   st->W = st->HD + 2 * st->Hkv * st->D;
   auto par = [&](int64_t i) { return PyList_GET_ITEM(a[1], i); };
-  check_matrix(tensor(par(0)), "emb", -1, -1);
-  st->dm = tensor(par(0)).size(1);
+  const Tensor& first = tensor(par(0));
+  const at::ScalarType body = first.scalar_type();
+  st->dtype = dtype_code(first);
+  check_matrix(first, "emb", -1, -1);
+  st->dm = first.size(1);
   check_matrix(tensor(par(1)), "head", st->dm, -1);
+  // (a wider gain makes the rows behind it wider)
+  const at::ScalarType tail = at::promote_types(body, tensor(par(2)).scalar_type());
+  check_gain(tensor(par(2)), "norm_f", st->dm, tail);
+  if (tensor(par(1)).scalar_type() != tail)
+    raise(PyExc_TypeError, "head must have the dtype of the rows of the final norm: the wider one of emb's and norm_f's");
+  st->tail = dtype_code(tensor(par(1)));
   for (int64_t i = 0; i < st->L; ++i) {
-    auto matrix = [&](int64_t k) -> const Tensor& { return tensor(par(3 + 8 * i + k)); };
-    check_matrix(matrix(2), "wq", st->dm, st->HD);
-    check_matrix(matrix(3), "wk", st->dm, st->Hkv * st->D);
-    check_matrix(matrix(4), "wv", st->dm, st->Hkv * st->D);
-    check_matrix(matrix(5), "wo", st->HD, st->dm);
-    check_matrix(matrix(6), "w1", st->dm, -1, 0);
-    check_matrix(matrix(7), "w2", matrix(6).size(1), st->dm);
+    auto at_layer = [&](int64_t k) -> const Tensor& { return tensor(par(3 + 8 * i + k)); };
+    check_gain(at_layer(0), "norm1", st->dm, body);
+    check_gain(at_layer(1), "norm2", st->dm, body);
+    check_matrix(at_layer(2), "wq", st->dm, st->HD);
+    check_matrix(at_layer(3), "wk", st->dm, st->Hkv * st->D);
+    check_matrix(at_layer(4), "wv", st->dm, st->Hkv * st->D);
+    check_matrix(at_layer(5), "wo", st->HD, st->dm);
+    check_matrix(at_layer(6), "w1", st->dm, -1, 0);
+    check_matrix(at_layer(7), "w2", at_layer(6).size(1), st->dm);
+    for (int64_t k = 2; k < 8; ++k)
+      if (at_layer(k).scalar_type() != body) raise(PyExc_TypeError, "parameters must share one dtype");
   }
+  for (int64_t i = 0; i < 3 + 8 * st->L; ++i)
+    if (!tensor(par(i)).is_cuda() || tensor(par(i)).device() != first.device())
+      raise(PyExc_ValueError, "parameters must be on one GPU");
   st->emb = param(par(0));
   st->head = param(par(1));
+  st->norm_f = gain(par(2), st->dm, tail);
   const Tensor& em = st->emb.w;
-  // (a wider gain makes the rows behind it wider)
-  const at::ScalarType tail = at::promote_types(em.scalar_type(), tensor(par(2)).scalar_type());
-  st->norm_f = gain(par(2), "norm_f", st->dm, tail);
-  if (st->head.w.scalar_type() != tail)
-    raise(PyExc_TypeError, "head must have the dtype of the rows of the final norm: the wider one of emb's and norm_f's");
-  st->tail = dtype_code(st->head.w);
-  st->dtype = dtype_code(em);
   st->e = em.element_size();
   st->V = st->head.w.size(1);
   st->ff = 0;
@@ -463,8 +475,8 @@ PyObject* step_new(PyObject* const* a) {
   for (int64_t i = 0; i < st->L; ++i) {
     Layer& l = st->layers[i];
     const int64_t p0 = 3 + 8 * i;
-    l.norm1 = gain(par(p0), "norm1", st->dm, em.scalar_type());
-    l.norm2 = gain(par(p0 + 1), "norm2", st->dm, em.scalar_type());
+    l.norm1 = gain(par(p0), st->dm, body);
+    l.norm2 = gain(par(p0 + 1), st->dm, body);
     // one projection product (and one gradient product each way) for queries, keys and values instead of three
     const Tensor &q = tensor(par(p0 + 2)), &k = tensor(par(p0 + 3)), &v = tensor(par(p0 + 4));
     l.wqkv.w = at::cat({q.detach(), k.detach(), v.detach()}, 1);
@@ -474,8 +486,6 @@ PyObject* step_new(PyObject* const* a) {
     l.w2 = param(par(p0 + 7));
     l.ff = l.w1.w.size(1);
     st->ff = std::max(st->ff, l.ff);
-    for (const Tensor* t : {&l.norm1.w, &l.norm2.w, &l.wqkv.w, &l.wo.w, &l.w1.w, &l.w2.w})
-      if (t->scalar_type() != em.scalar_type()) raise(PyExc_TypeError, "parameters must share one dtype");
     l.part1 = part(2 * i);
     l.part2 = part(2 * i + 1);
     // (cache rows are written before they are read; the gradient rows are cleared before stage 2)

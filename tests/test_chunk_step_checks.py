@@ -71,3 +71,12 @@ def test_dtypes_that_the_products_cannot_mix_are_refused(changed):
     p = dict(zip(names, _params()))
     with pytest.raises(TypeError):
         _new(_params(**{n: p[n].to(dt) for n, dt in changed.items()}))
+
+
+def test_host_tensors_are_refused():
+    """Parameters that are in order otherwise (the refusals above are not refusals of the device)."""
+    with pytest.raises(ValueError, match="on one GPU"):
+        _new(_params())
+    with pytest.raises(ValueError, match="on one GPU"):      # ... nor are the mixtures that are accepted
+        p = _params()
+        _new([p[0], p[1].float(), p[2].float()] + p[3:])
