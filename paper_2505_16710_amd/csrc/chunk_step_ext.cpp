@@ -370,11 +370,16 @@ void begin(Step& st) {
   st.s = stream(Py_None);
 }
 
+// contiguous from a 16-byte boundary on, which a piece of a larger buffer need not be
+Tensor laid_out(const Tensor& t) {
+  const Tensor c = t.contiguous();
+  return reinterpret_cast<uintptr_t>(c.data_ptr()) & 15u ? c.clone() : c;
+}
 Param param(PyObject* o) {
   const Tensor& t = tensor(o);
   Param p;
   p.wanted = t.requires_grad();
-  p.w = t.detach().contiguous();
+  p.w = laid_out(t.detach());
   return p;
 }
 
@@ -406,7 +411,7 @@ Param gain(PyObject* o, int64_t dm, at::ScalarType rows) {
   p.wanted = t.requires_grad();
   p.sizes = t.sizes().vec();
   p.type = t.scalar_type();
-  p.w = t.detach().to(rows).reshape({-1}).expand({dm}).contiguous();
+  p.w = laid_out(t.detach().to(rows).reshape({-1}).expand({dm}));
   return p;
 }
 

@@ -216,3 +216,21 @@ def test_step_with_an_fp32_final_norm_and_head_behind_a_bf16_body():
     assert g["head"].dtype == g["norm_f"].dtype == torch.float32
     assert abs(loss - float(loss_ref)) < 1e-2 * abs(float(loss_ref))
     _compare(g_ref, g, 6e-2)
+
+
+@pytest.mark.parametrize("dtype,cfg", [(torch.float32, F32_CFG), (torch.bfloat16, BF16_CFG)])
+def test_step_with_parameters_at_any_address(dtype, cfg):
+    """Parameters that are pieces of one buffer start on no 16-byte boundary; the gradients do not change."""
+    _, dec, tok, tgt = _setup(cfg, 35, 1, 128, dtype)
+    _, g_ref = dec.step(tok.to(DEV), tgt.to(DEV), 64)
+    flat = torch.zeros(1 + sum(t.numel() + -t.numel() % 8 for t in dec.p.values()), dtype=dtype, device=DEV)
+    at = 1
+    for n, t in list(dec.p.items()):
+        piece = flat[at:at + t.numel()].view(t.shape)
+        piece.copy_(t.detach())
+        dec.p[n] = piece.requires_grad_()
+        assert piece.data_ptr() % 16 != 0
+        at += t.numel() + -t.numel() % 8
+    _, g = dec.step(tok.to(DEV), tgt.to(DEV), 64)
+    for n in g_ref:
+        assert torch.equal(g[n], g_ref[n]), n
