@@ -61,6 +61,13 @@ class ChunkedDecoder:
         p = self.p
         B, N = tokens.shape
         dtype, dev = p["emb"].dtype, p["emb"].device
+        for t in (tokens, targets):
+            if t.dim() != 2 or t.shape[0] != B or t.shape[1] < N:
+                raise ValueError("tokens and targets must be [batch, tokens], one target per token")
+            if t.dtype.is_floating_point or t.dtype.is_complex or t.dtype == torch.bool:
+                raise TypeError("tokens and targets must be integers")
+            if t.device != dev:
+                raise ValueError("tokens and targets must be on the parameters' device")
         starts = list(range(0, N, chunk_len))
         if transposed_backward:
             if dq_weights is not None or dtype != torch.bfloat16:

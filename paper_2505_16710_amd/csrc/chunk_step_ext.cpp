@@ -517,8 +517,11 @@ PyObject* step_new(PyObject* const* a) {
   return cap;
 }
 
-Tensor chunk_of(const Tensor& t, int64_t s0, int64_t s1) {
-  if (!t.is_cuda() || t.scalar_type() != at::kLong || t.dim() != 2) raise(PyExc_ValueError, "tokens, targets: int64 [B, N] on the GPU");
+// rows [s0, s1) of every sequence; the kernels read as many entries as the chunk has tokens
+Tensor chunk_of(const Step& st, const Tensor& t, int64_t s0, int64_t s1) {
+  if (t.device() != st.emb.w.device() || t.scalar_type() != at::kLong || t.dim() != 2 || t.size(0) != st.B || t.size(1) < s1)
+    raise(PyExc_ValueError, "tokens, targets: int64 [B, N] on the parameters' GPU");
+  if (s0 < 0 || s1 <= s0 || s1 > st.N) raise(PyExc_ValueError, "chunk outside the sequence");
   return t.slice(1, s0, s1).reshape({-1});
 }
 
@@ -527,9 +530,9 @@ PyObject* step_infer(PyObject* const* a) {
   Step& st = step_of(a[0]);
   begin(st);
   const int64_t s0 = integer(a[3]), s1 = integer(a[4]);
-  const Tensor tok = chunk_of(tensor(a[1]), s0, s1), tgt = chunk_of(tensor(a[2]), s0, s1);
+  const Tensor tok = chunk_of(st, tensor(a[1]), s0, s1), tgt = chunk_of(st, tensor(a[2]), s0, s1);
   const Tensor& losses = tensor(a[5]);
-  if (losses.scalar_type() != at::kFloat || !losses.is_contiguous() || losses.numel() < st.B * s1)
+  if (losses.device() != st.emb.w.device() || losses.scalar_type() != at::kFloat || !losses.is_contiguous() || losses.numel() < st.B * s1)
     raise(PyExc_ValueError, "losses: one float32 per token");
   st.stage1.used = 0;
   Tensor x0;
@@ -556,7 +559,7 @@ PyObject* step_train(PyObject* const* a) {
   Step& st = step_of(a[0]);
   begin(st);
   const int64_t s0 = integer(a[3]), s1 = integer(a[4]);
-  const Tensor tok = chunk_of(tensor(a[1]), s0, s1), tgt = chunk_of(tensor(a[2]), s0, s1);
+  const Tensor tok = chunk_of(st, tensor(a[1]), s0, s1), tgt = chunk_of(st, tensor(a[2]), s0, s1);
   std::vector<float> w;
   if (a[6] != Py_None) w = floats(a[6]);
   std::vector<std::vector<float>> wq;

@@ -80,3 +80,29 @@ def test_host_tensors_are_refused():
     with pytest.raises(ValueError, match="on one GPU"):      # ... nor are the mixtures that are accepted
         p = _params()
         _new([p[0], p[1].float(), p[2].float()] + p[3:])
+
+
+def _decoder():
+    from paper_2505_16710_amd.chunk_loop import ChunkedDecoder
+    names = ["emb", "head", "norm_f"] + [f"l{l}.{n}" for l in range(3) for n in LAYER]
+    return ChunkedDecoder(dict(zip(names, _params())), 3, HQ, HKV, D)
+
+
+@pytest.mark.parametrize("tokens,targets,error", [
+    ((1, 64), (1, 63), ValueError), ((2, 64), (1, 64), ValueError), ((2, 64), (1, 128), ValueError),
+    ((64,), (64,), ValueError), ((1, 64), (1, 64, 1), ValueError),
+])
+def test_targets_that_do_not_cover_the_tokens_are_refused(tokens, targets, error):
+    with pytest.raises(error, match="not enough values|one target per token"):
+        _decoder().step(torch.zeros(tokens, dtype=torch.int64), torch.zeros(targets, dtype=torch.int64), 32)
+
+
+def test_tokens_and_targets_of_another_kind_are_refused():
+    ints = torch.zeros(1, 64, dtype=torch.int64)
+    for other in (ints.float(), ints.bool()):
+        with pytest.raises(TypeError, match="integers"):
+            _decoder().step(other, ints, 32)
+        with pytest.raises(TypeError, match="integers"):
+            _decoder().step(ints, other, 32)
+    with pytest.raises(ValueError, match="device"):
+        _decoder().step(ints, ints.to("meta"), 32)
