@@ -79,6 +79,8 @@ class ChunkedDecoder:
         c1 = stage1_chunk_len or chunk_len
         picked = None if selected is None else {int(i) for i in selected}
         order = range(len(starts) - 1, -1, -1) if selected is None else sorted(picked, reverse=True)
+        if keep_attention_outputs and any(starts[j] // c1 != (min(starts[j] + chunk_len, N) - 1) // c1 for j in order):
+            raise ValueError("kept attention outputs: every chunk must lie within one chunk of stage 1")
         names = ["emb", "head", "norm_f"] + [f"l{l}.{n}" for l in range(self.n_layers)
                                              for n in ("norm1", "norm2", "wq", "wk", "wv", "wo", "w1", "w2")]
         ext = _b._ext or _b._load_ext()

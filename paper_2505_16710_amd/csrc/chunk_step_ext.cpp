@@ -184,6 +184,7 @@ struct Step {
       if (it == l.kept.begin()) raise(PyExc_RuntimeError, "no kept attention output");
       --it;
       const int64_t a = q_start - it->first;
+      if (a + C > it->second.first.size(1)) raise(PyExc_ValueError, "the chunk's kept attention outputs are in two spans of stage 1");
       sv.keep_o = it->second.first;
       sv.keep_lse = it->second.second;
       if (a != 0 || C != sv.keep_o.size(1)) {

@@ -106,3 +106,13 @@ def test_tokens_and_targets_of_another_kind_are_refused():
             _decoder().step(ints, other, 32)
     with pytest.raises(ValueError, match="device"):
         _decoder().step(ints, ints.to("meta"), 32)
+
+
+def test_chunks_that_straddle_two_kept_spans_are_refused():
+    ints = torch.zeros(1, 192, dtype=torch.int64)
+    with pytest.raises(ValueError, match="kept attention outputs"):
+        _decoder().step(ints, ints, 64, keep_attention_outputs=True, stage1_chunk_len=96)
+    with pytest.raises(ValueError, match="on one GPU"):      # the chunks in use lie within one span each
+        _decoder().step(ints, ints, 64, selected=[2, 0], keep_attention_outputs=True, stage1_chunk_len=96)
+    with pytest.raises(ValueError, match="on one GPU"):      # not kept: the two lengths need not fit
+        _decoder().step(ints, ints, 64, stage1_chunk_len=96)
