@@ -35,6 +35,11 @@ template <typename T, int V> __device__ __forceinline__ void store(T* p, const f
   *reinterpret_cast<Vec<T, V>*>(p) = x;
 }
 
+// Rows in bf16 take the hardware's exponential and logarithm, whose argument is first multiplied by log2(e) in fp32: a
+// relative error of about |x| 2^-24, far below the rounding to bf16.  fp32 rows take the full-precision functions.
+template <typename T> __device__ __forceinline__ float exp_of(float x) { return sizeof(T) == 4 ? expf(x) : __expf(x); }
+template <typename T> __device__ __forceinline__ float log_of(float x) { return sizeof(T) == 4 ? logf(x) : __logf(x); }
+
 struct Sum {
   __device__ static float of(float a, float b) { return a + b; }
 };
@@ -237,7 +242,7 @@ __global__ __launch_bounds__(kThreads) void silu_kernel(const T* u, T* a, int64_
     if (BWD) load<T, V>(a + i, g);
 #pragma unroll
     for (int j = 0; j < V; ++j) {
-      const float s = 1.f / (1.f + __expf(-f[j]));
+      const float s = 1.f / (1.f + exp_of<T>(-f[j]));
       f[j] = BWD ? g[j] * (s * (1.f + f[j] * (1.f - s))) : f[j] * s;
     }
     store<T, V>(a + i, f);
@@ -261,12 +266,12 @@ __global__ __launch_bounds__(kThreads) void cross_entropy_kernel(T* logits, cons
     float f[V];
     load<T, V>(l + c, f);
 #pragma unroll
-    for (int j = 0; j < V; ++j) sum += __expf(f[j] - m);
+    for (int j = 0; j < V; ++j) sum += exp_of<T>(f[j] - m);
   }
   sum = block_reduce<Sum>(sum);
   const bool bad = t != -100 && (t < 0 || t >= v);
   if (loss) {
-    if (threadIdx.x == 0) loss[blockIdx.x] = t == -100 ? 0.f : bad ? NAN : m + __logf(sum) - (float)l[t];
+    if (threadIdx.x == 0) loss[blockIdx.x] = t == -100 ? 0.f : bad ? NAN : m + log_of<T>(sum) - (float)l[t];
     return;
   }
   const float inv = t == -100 ? 0.f : bad ? NAN : 1.f / sum;
@@ -274,7 +279,7 @@ __global__ __launch_bounds__(kThreads) void cross_entropy_kernel(T* logits, cons
     float f[V];
     load<T, V>(l + c, f);
 #pragma unroll
-    for (int j = 0; j < V; ++j) f[j] = __expf(f[j] - m) * inv - (c + j == t ? 1.f : 0.f);
+    for (int j = 0; j < V; ++j) f[j] = exp_of<T>(f[j] - m) * inv - (c + j == t ? 1.f : 0.f);
     store<T, V>(l + c, f);
   }
 }
