@@ -110,10 +110,11 @@ int seco_chunk_attn_fwd(const seco_desc* desc, const void* q, const void* k_cach
  * same desc; d_o has o's layout.
  * ws: seco_workspace_bytes(desc, SECO_OP_BWD) bytes, 256-byte aligned: one fp32 value per query row (delta; bf16:
  *     two, delta and the log-sum-exp in the form the dK/dV kernel consumes), plus one region shared by the
- *     partial dQ of the short-chunk path described at seco_chunk_attn_fwd and, for bf16 with grouped heads, the
- *     sums of the cache-row tiles whose query heads the dK/dV pass shares out among several workgroups when its
- *     last round of workgroups would be less than half full (at most 32 MiB; merged in head order, so gk/gv
- *     stay bit-reproducible).  SECO_ERR_WORKSPACE if NULL, misaligned or smaller.
+ *     partial dQ of the short-chunk path described at seco_chunk_attn_fwd and the sums of the cache-row tiles that
+ *     the dK/dV pass shares out among several workgroups when its workgroups would leave compute units idle (bf16;
+ *     32 MiB with grouped heads, without them only what the partial dQ takes; merged in a fixed order, so gk/gv
+ *     stay bit-reproducible).  A larger workspace changes nothing: the results are the same bit for bit.
+ *     SECO_ERR_WORKSPACE if NULL, misaligned or smaller.
  */
 int seco_chunk_attn_bwd(const seco_desc* desc, const void* q, const void* k_cache, const void* v_cache,
                         const void* o, const float* lse, const void* d_o,
@@ -367,9 +368,8 @@ int seco_profile_read(double* total_ms_host, int64_t* launches_host);
  * and with it this size, counts workgroups against the number of compute units of the device that is current when
  * the library is first used (256, an MI355X's, when no device can be asked): ask on the device the call will run on. */
 size_t seco_workspace_bytes(const seco_desc* desc, int op);
-/* Workspace bytes with which the entry point runs fastest (at least seco_workspace_bytes): without grouped query heads
- * the bf16 backward can do without room for partial sums, but then leaves compute units idle when a call has few
- * cache tiles. */
+/* The same number: a backward call's launch plan, and with it the order of its sums, depends on the descriptor alone,
+ * so no workspace is faster than one of seco_workspace_bytes. */
 size_t seco_workspace_bytes_preferred(const seco_desc* desc, int op);
 
 /*

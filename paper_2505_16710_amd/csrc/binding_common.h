@@ -22,7 +22,7 @@ using at::Tensor;
 #define SECO_ENTRIES(X)                                                                                             \
   X(seco_chunk_attn_fwd) X(seco_chunk_attn_bwd) X(seco_chunk_attn_bwd_noalloc) X(spaco_chunk_attn_bwd)              \
   X(spaco_chunk_attn_bwd_sparse_dq) X(seco_chunk_attn_bwd_gather) X(spaco_chunk_attn_bwd_gather)                    \
-  X(seco_workspace_bytes) X(seco_workspace_bytes_preferred) X(kvgrad_zero) X(kvgrad_accumulate) X(kv_append) X(kvgrad_readout) X(kv_append_rope)      \
+  X(seco_workspace_bytes) X(kvgrad_zero) X(kvgrad_accumulate) X(kv_append) X(kvgrad_readout) X(kv_append_rope)      \
   X(kvgrad_readout_rope) X(rope_rotate) X(dec_add_rmsnorm) X(dec_rmsnorm_bwd) X(dec_silu) X(dec_silu_bwd)             \
   X(dec_cross_entropy) X(dec_embedding_bwd) X(dec_gemm_supported) X(dec_gemm)
 struct Lib {
@@ -117,7 +117,7 @@ inline Tensor bytes(int64_t n, const Tensor& t) { return at::empty({n}, t.option
 inline size_t nbytes(const Tensor& t) { return (size_t)t.numel() * t.element_size(); }
 
 inline size_t workspace(const seco_desc& d, int op) {
-  const size_t n = lib.seco_workspace_bytes_preferred(&d, op);
+  const size_t n = lib.seco_workspace_bytes(&d, op);
   if (n == (size_t)-1) check(SECO_ERR_SHAPE, "seco_workspace_bytes");
   return n;
 }

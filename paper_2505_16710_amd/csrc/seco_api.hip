@@ -105,8 +105,8 @@ int splits_for(const seco_desc* d) {
   return split_count(pl, d->q_start + d->chunk_len);
 }
 
-// workspace of the dK/dV pass for the column tiles it shares out: at most one share per CU (share_plan).  With
-// grouped heads the call insists on it; without, it is used if it is there.
+// workspace of the dK/dV pass for the column tiles it shares out: at most one share per CU (share_plan); none without
+// grouped heads, where the pass uses what the partial dQ of a short chunk needs anyway.
 constexpr size_t kSlotBytes = (size_t)2 * kColTileBf16 * 128 * sizeof(float);
 size_t tail_part_bytes(const seco_desc* d) {
   if (d->dtype != SECO_BF16 || d->n_q_heads / d->n_kv_heads < 2) return 0;
@@ -114,9 +114,10 @@ size_t tail_part_bytes(const seco_desc* d) {
 }
 size_t bwd_part_bytes(const seco_desc* d) { return std::max(split_part_bytes(d), tail_part_bytes(d)); }
 
-void use_tail_part(AttnParams& p, const seco_desc* d, size_t ws_bytes) {
-  if (d->dtype != SECO_BF16) return;
-  p.tail_bytes = std::min(ws_bytes - delta_bytes(d), kPartBytes);
+// The room for partial results is what every call must bring and no more, however large the workspace is: a call's plan,
+// and with it the order of its sums, depends on the descriptor alone.
+void use_tail_part(AttnParams& p, const seco_desc* d) {
+  p.tail_bytes = bwd_part_bytes(d);
   p.tail_part = p.part;
 }
 
@@ -190,7 +191,7 @@ int backward(const seco_desc* d, const void* q, const void* k, const void* v, co
   p.n_splits = splits_for(d);
   p.Cpad = (d->chunk_len + 31) / 32 * 32;
   p.part = reinterpret_cast<float*>(static_cast<char*>(ws) + delta_bytes(d));
-  use_tail_part(p, d, ws_bytes);
+  use_tail_part(p, d);
   hipStream_t s = static_cast<hipStream_t>(stream);
   const bool bf16 = d->dtype == SECO_BF16;
   PendingDq pending;     // where both fit, the dQ and dK/dV passes are one launch
@@ -300,7 +301,7 @@ int backward_gather(const seco_desc* d, const void* q_rows, const void* k, const
   p.n_splits = splits_for(d);
   p.Cpad = (d->chunk_len + 31) / 32 * 32;
   p.part = reinterpret_cast<float*>(static_cast<char*>(ws) + delta_bytes(d));
-  use_tail_part(p, d, ws_bytes);
+  use_tail_part(p, d);
   hipStream_t s = static_cast<hipStream_t>(stream);
   if ((rc = launch_dq_bf16(p, nullptr, s))) return rc;
   // dK/dV: the query rows are the chunk's and the later ones, the cache rows the chunk's own
@@ -403,9 +404,7 @@ extern "C" size_t seco_workspace_bytes(const seco_desc* desc, int op) {
 }
 
 extern "C" size_t seco_workspace_bytes_preferred(const seco_desc* desc, int op) {
-  const size_t n = seco_workspace_bytes(desc, op);
-  if (n == (size_t)-1 || op != SECO_OP_BWD || desc->dtype != SECO_BF16) return n;
-  return std::max(n, delta_bytes(desc) + kPartBytes);
+  return seco_workspace_bytes(desc, op);
 }
 
 extern "C" int seco_launch_plan(const seco_desc* desc, int32_t n_col_tiles, int32_t* plan_host) {

@@ -27,7 +27,7 @@ struct AttnParams {
   float* part;       // split path: partial O (forward) or partial dQ (backward), fp32 [n_splits, B, Hq, C, D]
   float* part_ml;    // split path, forward: (reference max in log2 units, sum) per partial row, [n_splits, B, Hq, C, 2]
   float* tail_part;  // dK/dV pass: sums of the column tiles shared out among several workgroups (workspace), or NULL
-  size_t tail_bytes; // room there
+  size_t tail_bytes; // room there; a function of the descriptor, not of the workspace that was passed
   int n_splits;      // > 1 selects the split path
   int Cpad;          // C rounded up to 32: rows per head in the packed row space of the split path
   int B, Hq, Hkv, D, C, q_start, G;
@@ -247,10 +247,6 @@ inline SharePlan share_plan(const IterRuns& r, int n_units, int n_ctiles, int G,
   if (c.time >= 0.f) time = c.time;
   return make_shares(r, n, c.per);
 }
-
-// Partial results of a backward call (partial dQ, shared-out column tiles): no more than this is used, whatever the workspace
-// holds, so that a call's plan, and with it the order of its sums, does not depend on the workspace.
-constexpr size_t kPartBytes = (size_t)38 << 20;
 
 // fp32 kernels (any head_dim that is a multiple of 4, up to 256)
 int launch_fwd_f32(const AttnParams& p, hipStream_t s);

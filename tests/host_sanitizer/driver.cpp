@@ -88,6 +88,21 @@ int main() {
     CHECK(seco_workspace_bytes(&big, SECO_OP_BWD) > SECO_STATIC_SCRATCH_BYTES);
     CHECK(seco_chunk_attn_bwd_noalloc(&big, FAKE, FAKE, FAKE, FAKE, FAKEF, FAKE, FAKE, FAKEF, FAKEF, nullptr) ==
           SECO_ERR_TOO_LARGE);
+    // the plan does not depend on how much workspace there is: with and without grouped heads, few rows and many
+    for (int hkv : {2, 8})
+      for (int c : {256, hkv == 2 ? 1000 : 3976}) {
+        const seco_desc e = desc(SECO_BF16, c, 512, 8, hkv);
+        const size_t need = seco_workspace_bytes(&e, SECO_OP_BWD);
+        CHECK(seco_workspace_bytes_preferred(&e, SECO_OP_BWD) == need);
+        size_t room[4];
+        for (int i = 0; i < 3; ++i) {
+          CHECK(seco_chunk_attn_bwd(&e, FAKE, FAKE, FAKE, FAKE, FAKEF, FAKE, FAKE, FAKEF, FAKEF, FAKE, need + ((size_t)i << 24), nullptr) == SECO_OK);
+          room[i] = g_stub.last.tail_bytes;
+        }
+        CHECK(seco_chunk_attn_bwd_noalloc(&e, FAKE, FAKE, FAKE, FAKE, FAKEF, FAKE, FAKE, FAKEF, FAKEF, nullptr) == SECO_OK);
+        room[3] = g_stub.last.tail_bytes;
+        for (int i = 1; i < 4; ++i) CHECK(room[i] == room[0] && room[0] <= need);
+      }
     // fp32: the delta launch comes first
     seco_desc f = desc(SECO_F32, 100, 200, 4, 4, 64);
     g_stub.clear();
