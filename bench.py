@@ -201,13 +201,29 @@ def main():
             torch.cuda.synchronize()
             prof = seco.seco_profile_read()
             seco.seco_profile_enable(False)
-            alg = {"fwd": 4, "dq": 6, "dkdv": 4}
+            # (dQ and dK/dV of a short or fp32 call are one launch)
+            alg = {"fwd": 4, "bwd": 10} if prof["bwd"][1] else {"fwd": 4, "dq": 6, "dkdv": 4}
             per_call[str(j)] = {k: {"avg_ms": round(prof[k][0] / args.steps, 5),
                                     "tflops": round(f * pairs(j, C) * per_pair * args.steps / (prof[k][0] * 1e-3) / 1e12, 1)}
                                 for k, f in alg.items()}
         print(json.dumps({"metric": "per_call_kernel_times", "config": {"workload": cfg.name, "chunk_len": C,
                                                                        "seq_len": N}, "per_call": per_call}))
         return
+
+    def kernel_work(Lx, calls, pairs_dkdv, weights=lambda j: None):
+        """FLOPs of a step per kernel kind.  Whether a call's backward is one launch (kind "bwd") or two ("dq", "dkdv") is
+        asked of the library, by running each call once with its launches recorded."""
+        pp = Lx.cx.head_dim * Lx.cx.n_q_heads * Lx.cx.batch
+        alg = {"fwd": 0, "bwd": 0, "dq": 0, "dkdv": 0}
+        for j in calls:
+            seco.seco_profile_enable(True)
+            Lx.bwd(j, weights(j))
+            one_launch = seco.seco_profile_read()["bwd"][1] > 0
+            alg["fwd"] += 4 * pairs(j, Lx.C) * pp
+            alg["bwd" if one_launch else "dq"] += 6 * pairs(j, Lx.C) * pp
+            alg["bwd" if one_launch else "dkdv"] += 4 * pairs_dkdv(j) * pp
+        seco.seco_profile_enable(False)
+        return {kind: f for kind, f in alg.items() if f}
 
     run_step = step
     if args.graph:
@@ -229,11 +245,10 @@ def main():
 
     def roofline_of(name, kind, alg_flops, ms, n, n_steps, where):
         """Roofline object of one kernel kind: algorithmic FLOPs of its launches / their summed event durations.
-        bf16 kernels are dense MFMA contractions (2500 TFLOP/s); the fp32 parity kernels use the vector ALU only
-        (256 CUs x 128 lanes x 2 FLOP x 2.4 GHz = 157.3 TFLOP/s)."""
+        All are dense MFMA contractions: bf16 2500 TFLOP/s, fp32 157.3 TFLOP/s (256 CUs x 256 FLOP x 2.4 GHz)."""
         achieved = alg_flops * n_steps / (ms * 1e-3) / 1e12
-        twice = 2.0 if (bf16 and kind == "dkdv") else 1.0       # dK/dV computes S and dP a second time
-        return {"bound": "mfma" if bf16 else "alu", "kernel": kind + ("_bf16_kernel" if bf16 else "_f32_kernel"),
+        twice = {"dkdv": 2.0, "bwd": 1.4}.get(kind, 1.0)        # dK/dV computes S and dP a second time
+        return {"bound": "mfma", "kernel": kind + ("_fused" if bf16 and kind == "bwd" else "") + ("_bf16_kernel" if bf16 else "_f32_kernel"),
                 "achieved": round(achieved, 2), "peak": peak, "unit": "TFLOP/s", "frac": round(achieved / peak, 4),
                 "traffic": hbm_traffic_per_launch(name, kind),
                 "avg_launch_ms": round(ms / n, 5), "launches": int(n),
@@ -269,11 +284,13 @@ def main():
     dom = None
     prof_kinds = None
     if not args.no_profile and warm_prof is not None:
-        dom = max(("fwd", "dq", "dkdv"), key=lambda kd: warm_prof[kd][0])
+        dom = max(("fwd", "bwd", "dq", "dkdv"), key=lambda kd: warm_prof[kd][0])
         prof_kinds = [dom]
     PROF_EVERY = 5
     n_prof_steps = 0
+    alg = None
     if not args.no_profile:
+        alg = kernel_work(L, range(k_chunks), lambda j: pairs(j, C))
         seco.seco_profile_enable(False)             # also drops any earlier records
     marks = [torch.cuda.Event(enable_timing=True) for _ in range(args.steps + 1)]
     t0 = time.perf_counter()
@@ -320,7 +337,6 @@ def main():
                      "bf16_peak_from_device_tflops": round(cus * 4096 * clock_khz * 1e3 / 1e12, 1)}
 
     if prof is not None:
-        alg = {"fwd": flops_fwd, "dq": flops_dq, "dkdv": flops_dkdv}
         kprof, ksteps = (warm_prof, 1) if warm_prof is not None else (prof, n_prof_steps)
         kern = kernel_table(kprof, alg, ksteps)
         kern["measured_in"] = "last warm-up step (every launch bracketed by events)" if warm_prof is not None else "timed steps"
@@ -358,15 +374,17 @@ def main():
                 return pairs(j, Cx)
             return sum(Cx * Cx for i in selected if i < j) + Cx * (Cx + 1) // 2
 
-        alg = {"fwd": sum(4 * pairs(j, Cx) for j in calls) * pp, "dq": sum(6 * pairs(j, Cx) for j in calls) * pp,
-               "dkdv": sum(4 * sel_pairs(j) for j in calls) * pp}
-        total = sum(alg.values())
+        def weights(j):
+            return None if selected is None else seco.spaco_chunk_weights(selected, j, lam)
 
         def stepx():
             seco.kvgrad_zero(Lx.gk, Lx.gv)
             for j in calls:
                 Lx.fwd(j)
-                Lx.bwd(j, None if selected is None else seco.spaco_chunk_weights(selected, j, lam))
+                Lx.bwd(j, weights(j))
+
+        total = sum(10 * pairs(j, Cx) + 4 * sel_pairs(j) for j in calls) * pp
+        alg = kernel_work(Lx, calls, sel_pairs, weights)
 
         for _ in range(warmup):
             stepx()

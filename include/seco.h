@@ -349,11 +349,14 @@ int spaco_gather_row_weights(const int32_t* selected_host, int32_t n_selected, i
  */
 typedef enum seco_profile_kind {
   SECO_PROFILE_FWD = 0,     /* forward kernel */
-  SECO_PROFILE_DELTA = 1,   /* delta = rowsum(dO * O) */
+  SECO_PROFILE_BWD = 1,     /* dQ and dK/dV in one launch: every fp32 backward, bf16 calls with few rows and few cache
+                               tiles; such a call has no SECO_PROFILE_DQ or _DKDV launch (delta = rowsum(dO * O), which
+                               had this entry once, is no launch of its own on any path) */
   SECO_PROFILE_DQ = 2,      /* dQ kernel */
-  SECO_PROFILE_DKDV = 3,    /* dK/dV kernel with the gK/gV accumulation */
+  SECO_PROFILE_DKDV = 3,    /* dK/dV kernel with the gK/gV accumulation, and the merge of shared-out cache tiles */
   SECO_PROFILE_KVGRAD = 4,  /* kvgrad_zero / kvgrad_accumulate */
-  SECO_PROFILE_MERGE = 5,   /* merge of partial O / dQ on the short-chunk path */
+  SECO_PROFILE_MERGE = 5,   /* merge of partial O / dQ on the short-chunk path; behind a SECO_PROFILE_BWD launch it adds
+                               up shared-out cache tiles too */
   SECO_PROFILE_KINDS = 6
 } seco_profile_kind;
 int seco_profile_enable(int on);                    /* all kinds on / off; forgets recorded events */

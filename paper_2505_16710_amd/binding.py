@@ -283,7 +283,13 @@ def spaco_gather_row_weights(selected, i, k, factor):
     return list(w)
 
 
-PROFILE_KINDS = ("fwd", "delta", "dq", "dkdv", "kvgrad", "merge")
+# "bwd": dQ and dK/dV in one launch (fp32, short bf16 calls), which then has no "dq" or "dkdv"
+PROFILE_KINDS = ("fwd", "bwd", "dq", "dkdv", "kvgrad", "merge")
+
+
+def _profile_mask(kinds):
+    """Bits of the named kinds.  "delta" (rowsum(dO * O), once a kernel) is still taken: nothing is timed for it."""
+    return sum(1 << PROFILE_KINDS.index(k) for k in set(kinds) if k != "delta")
 
 
 def seco_launch_plan(desc, n_col_tiles):
@@ -303,19 +309,14 @@ def seco_device_info():
 def seco_profile_enable(on=True, kinds=None):
     """Time every kernel launch (on=True), none (False), or only the named kinds (subset of PROFILE_KINDS)."""
     if kinds is not None:
-        mask = 0
-        for k in kinds:
-            mask |= 1 << PROFILE_KINDS.index(k)
-        _check(load_library().seco_profile_enable_kinds(mask), "seco_profile_enable_kinds")
+        _check(load_library().seco_profile_enable_kinds(_profile_mask(kinds)), "seco_profile_enable_kinds")
     else:
         _check(load_library().seco_profile_enable(1 if on else 0), "seco_profile_enable")
 
 
 def seco_profile_set(kinds=None):
     """Change which kinds are timed (None: all, []: none) without dropping what has been recorded."""
-    mask = 0
-    for k in (PROFILE_KINDS if kinds is None else kinds):
-        mask |= 1 << PROFILE_KINDS.index(k)
+    mask = _profile_mask(PROFILE_KINDS if kinds is None else kinds)
     _check(load_library().seco_profile_set_kinds(mask), "seco_profile_set_kinds")
 
 
@@ -324,4 +325,4 @@ def seco_profile_read():
     ms = (C.c_double * len(PROFILE_KINDS))()
     n = (C.c_int64 * len(PROFILE_KINDS))()
     _check(load_library().seco_profile_read(ms, n), "seco_profile_read")
-    return {k: (ms[i], n[i]) for i, k in enumerate(PROFILE_KINDS)}
+    return {**{k: (ms[i], n[i]) for i, k in enumerate(PROFILE_KINDS)}, "delta": (0.0, 0)}

@@ -78,7 +78,7 @@ int launch(const AttnParams& p, const SegTable& seg, const TailSplit& ts, int n_
   if (!allow_lds(ready, reinterpret_cast<const void*>(kern), kSmem)) return SECO_ERR_LAUNCH;
   const int first = xcd_grid(kv_first ? kv_total : dq_total), second = xcd_grid(kv_first ? dq_total : kv_total);
   {
-    ProfScope prof(kKernelDkdv, s);
+    ProfScope prof(kKernelBwd, s);
     hipLaunchKernelGGL(kern, dim3(first + second), dim3(512), kSmem, s, p, seg, ts, n_mtiles, kv_total, dq_total, first,
                        kv_first ? 1 : 0);
   }

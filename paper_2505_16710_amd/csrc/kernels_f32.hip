@@ -386,7 +386,7 @@ int bwd_nt(const AttnParams& p, const SegTable& dq_runs, const SegTable& seg, bo
   const int64_t n_dq = dq ? (int64_t)((p.C + kRows - 1) / kRows) * p.Hq * p.B : 0;
   const int64_t total = n_dq + (int64_t)seg.tile_begin[seg.n] * p.Hkv * p.B;
   if (total > 0x7fffffff) return SECO_ERR_TOO_LARGE;
-  ProfScope prof(seg.tile_begin[seg.n] ? kKernelDkdv : kKernelDq, s);
+  ProfScope prof(n_dq == 0 ? kKernelDkdv : seg.tile_begin[seg.n] ? kKernelBwd : kKernelDq, s);
   hipLaunchKernelGGL(kern, dim3((unsigned)total), dim3(NW * 64), smem, s, p, dq_runs, seg, (int)n_dq);
   return launch_status();
 }

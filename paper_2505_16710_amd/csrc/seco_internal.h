@@ -303,7 +303,7 @@ int launch_rope_rows(void* out, const void* in, void* plain_out, const void* pla
 
 // Optional per-kernel timing (seco_profile_enable): a scope brackets one launch with HIP events
 // on the launch stream.  Disabled by default; then a scope costs one branch.
-enum KernelKind { kKernelFwd = 0, kKernelDelta, kKernelDq, kKernelDkdv, kKernelKvgrad, kKernelMerge, kKernelKinds };
+enum KernelKind { kKernelFwd = 0, kKernelBwd, kKernelDq, kKernelDkdv, kKernelKvgrad, kKernelMerge, kKernelKinds };
 struct ProfScope {
   ProfScope(KernelKind kind, hipStream_t s);
   ~ProfScope();

@@ -951,3 +951,23 @@ def test_rope_append_readout_and_rotate(dtype):
     close(to_host(rot), R._to_storage(R.rope_rotate(q, r0, base), dtype), "rotate")
     back = seco.rope_rotate(rot, r0, base, inverse=True, out=rot)                  # in place
     assert np.abs(to_host(back) - q).max() <= 3 * ulp * np.abs(q).max()
+
+
+@pytest.mark.parametrize("dtype,D,C,q_start,Hq,Hkv,kinds", [
+    ("bf16", 128, 64, 128, 8, 2, {"bwd"}),              # a short call: both passes in one launch
+    ("bf16", 128, 1024, 7168, 32, 8, {"dq", "dkdv"}),   # as many cache tiles as compute units: one after the other
+    ("f32", 64, 64, 64, 4, 4, {"bwd"}),
+])
+def test_profile_books_one_launch_backwards_under_a_kind_of_their_own(dtype, D, C, q_start, Hq, Hkv, kinds):
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    gen = torch.Generator(device=DEV).manual_seed(5)
+    mk = lambda h, n: torch.randn(1, h, n, D, generator=gen, device=DEV).to(dt)
+    q, do, k, v = mk(Hq, C), mk(Hq, C), mk(Hkv, q_start + C), mk(Hkv, q_start + C)
+    o, lse = seco.seco_chunk_attn_fwd(q, k, v, q_start, D ** -0.5)
+    gk, gv = (torch.zeros(1, Hkv, q_start + C, D, device=DEV) for _ in range(2))
+    seco.seco_profile_enable(True)
+    seco.seco_chunk_attn_bwd(q, k, v, o, lse, do, gk, gv, q_start, D ** -0.5)
+    prof = seco.seco_profile_read()
+    seco.seco_profile_enable(False)
+    assert {n for n in ("fwd", "bwd", "dq", "dkdv", "kvgrad") if prof[n][1]} == kinds
+    assert all(prof[n][1] == 1 and prof[n][0] > 0 for n in kinds)
