@@ -406,10 +406,8 @@ int bwd_nt(const AttnParams& p, const SegTable& dq_runs, const SegTable& seg, bo
 
 int launch_fwd_f32(const AttnParams& p, hipStream_t s) { SECO_F32_DISPATCH(fwd_nt, p, s) }
 
-// The three passes of the fp32 backward are one launch: the first two are noted in p.pending and go out with the third
-// (launch_dkdv_f32; with an empty table when there are no cache rows to cover).
-int launch_delta(const AttnParams&, int, hipStream_t) { return SECO_OK; }   // taken from O and dO where it is used
-
+// Both passes of the fp32 backward are one launch: dQ is noted in p.pending and goes out with dK/dV (launch_dkdv_f32;
+// with an empty table when there are no cache rows to cover).  rowsum(dO * O) is taken from O and dO where it is used.
 int launch_dq_f32(const AttnParams& p, const SegTable* dq_runs, hipStream_t) {
   SegTable& runs = p.pending->runs;
   runs = SegTable{};

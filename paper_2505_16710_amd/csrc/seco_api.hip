@@ -77,7 +77,9 @@ AttnParams make_params(const seco_desc* d) {
   return p;
 }
 
-// one fp32 value per query row: delta; the bf16 path keeps a second array (LSE in the form its dK/dV kernel uses)
+// Row statistics, fp32 per query row: the bf16 dQ kernel writes -delta = -rowsum(dO * O) and -LSE / scale for the dK/dV
+// kernel.  (fp32: one value per row is demanded as ever, so that sizes that callers keep stay right; nothing is
+// written there, both passes compute delta from O and dO.)
 size_t row_stat_bytes(const seco_desc* d) {
   const size_t n = (size_t)d->batch * d->n_q_heads * d->chunk_len * sizeof(float);
   return (n + 255) & ~(size_t)255;
@@ -196,8 +198,6 @@ int backward(const seco_desc* d, const void* q, const void* k, const void* v, co
   const bool bf16 = d->dtype == SECO_BF16;
   PendingDq pending;     // where both fit, the dQ and dK/dV passes are one launch
   p.pending = &pending;
-  // delta = rowsum(dO * O): the bf16 dQ kernel computes it in its prologue (and stores it for the dK/dV kernel)
-  if (!bf16 && (rc = launch_delta(p, d->dtype, s))) return rc;
   const SegTable* runs_arg = sparse_dq ? &dq_runs : nullptr;
   if ((rc = bf16 ? launch_dq_bf16(p, runs_arg, s) : launch_dq_f32(p, runs_arg, s))) return rc;
   // dK/dV pass: one launch per table of at most kMaxSegments runs (no host allocation: a table is launched as soon

@@ -18,8 +18,8 @@ struct AttnParams {
   void* o_out;
   void* d_q;
   float* lse;        // [B, Hq, C] contiguous
-  float* delta;      // [B, Hq, stat_stride], backward only: rowsum(dO * O); NEGATED on the bf16 path
-  float* nlse2;      // bf16 backward: -LSE / scale, [B, Hq, stat_stride], written by the dQ kernel for the dK/dV kernel
+  float* delta;      // bf16 backward: -rowsum(dO * O), [B, Hq, stat_stride], written by the dQ kernel for the dK/dV kernel
+  float* nlse2;      // bf16 backward: -LSE / scale, likewise
   int stat_stride;   // rows per (batch, head) of delta / nlse2: C (workspace of one call), or the length of
   int stat_off;      // arrays kept for the whole sequence, in which this call's first query row sits at stat_off
   float* gk;
@@ -275,9 +275,6 @@ int launch_dkdv_rows_bf16(const AttnParams& p, const SegTable& seg, const RowRun
 #define SECO_DKDV_COLS 128
 #endif
 constexpr int kColTileBf16 = SECO_DKDV_COLS;  // columns per workgroup in launch_dkdv_bf16
-
-// announces delta[r] = sum_d dO[r,d] * O[r,d] of the fp32 backward
-int launch_delta(const AttnParams& p, int dtype, hipStream_t s);
 
 // Bandwidth-bound helpers; each takes a pair of tensors (gK and gV, keys and values) handled by one launch,
 // a NULL member of the pair is skipped.

@@ -69,7 +69,7 @@ int main() {
     CHECK(ws != (size_t)-1 && ws > 0);
     g_stub.clear();
     CHECK(seco_chunk_attn_bwd(&d, FAKE, FAKE, FAKE, FAKE, FAKEF, FAKE, FAKE, FAKEF, FAKEF, FAKE, ws, nullptr) == SECO_OK);
-    CHECK(g_stub.dq == 1 && g_stub.dkdv == 1 && g_stub.delta == 0 && g_stub.dq_tables.empty());
+    CHECK(g_stub.dq == 1 && g_stub.dkdv == 1 && g_stub.dq_tables.empty());
     const seco::SegTable& t = g_stub.dkdv_tables[0];
     CHECK(t.n == 1 && t.col_begin[0] == 0 && t.col_end[0] == 1024 && t.weight[0] == 1.f && t.tile_begin[1] == 8);
     CHECK(g_stub.last.n_splits > 1);                        // a short chunk: the cache range is divided
@@ -103,12 +103,12 @@ int main() {
         room[3] = g_stub.last.tail_bytes;
         for (int i = 1; i < 4; ++i) CHECK(room[i] == room[0] && room[0] <= need);
       }
-    // fp32: the delta launch comes first
+    // fp32
     seco_desc f = desc(SECO_F32, 100, 200, 4, 4, 64);
     g_stub.clear();
     CHECK(seco_chunk_attn_bwd(&f, FAKE, FAKE, FAKE, FAKE, FAKEF, FAKE, FAKE, FAKEF, FAKEF, FAKE,
                               seco_workspace_bytes(&f, SECO_OP_BWD), nullptr) == SECO_OK);
-    CHECK(g_stub.delta == 1 && g_stub.dq == 1 && g_stub.dkdv == 1);
+    CHECK(g_stub.dq == 1 && g_stub.dkdv == 1);
     CHECK(g_stub.dkdv_tables[0].tile_begin[1] == (300 + seco::kColTileF32 - 1) / seco::kColTileF32);
   }
   // ---- weights: merged runs, zero chunks skipped, ragged last chunk, more runs than one table holds ----

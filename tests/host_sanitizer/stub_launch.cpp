@@ -22,7 +22,6 @@ int launch_dkdv_bf16(const AttnParams& p, const SegTable& seg, hipStream_t) {
 int launch_dkdv_rows_bf16(const AttnParams& p, const SegTable& seg, const RowRuns& rr, hipStream_t) {
   g_stub.dkdv++; g_stub.last = p; g_stub.dkdv_tables.push_back(seg); g_stub.row_runs.push_back(rr); return SECO_OK;
 }
-int launch_delta(const AttnParams&, int, hipStream_t) { g_stub.delta++; return SECO_OK; }
 int launch_kvgrad_zero(float*, float*, int, int, int, const int64_t*, int64_t, int64_t, hipStream_t) {
   g_stub.zero++; return SECO_OK;
 }

@@ -113,7 +113,7 @@ def test_kvgrad_validation_and_workspace_size():
     assert lib.kvgrad_accumulate(C.byref(d), FAKE, None, FAKE, None, 1.0, 0, 4, None) == -8   # dst aliases src
     assert lib.kvgrad_zero(C.byref(d), None, None, 0, 4, None) == 0                           # nothing to do
     # long chunks (enough row tiles to fill the GPU): no forward workspace; the backward takes two values per query
-    # row (delta and the log-sum-exp in the form the dK/dV kernel starts from; fp32: delta only) plus the sums
+    # row (delta and the log-sum-exp in the form the dK/dV kernel starts from; fp32: one value) plus the sums
     # of the column tiles that the dK/dV pass divides by query head (at most 256 shares of 2 x 128 x 128 floats)
     big = desc(n_q_heads=32, n_kv_heads=8, chunk_len=1024)
     assert seco.seco_workspace_bytes(big, B.SECO_OP_FWD) == 0
