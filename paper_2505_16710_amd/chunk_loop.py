@@ -29,6 +29,102 @@ import torch
 from . import binding as _b
 
 
+# ---- the attention of one layer as an autograd function, for models whose other parts are framework operators ----------
+# (ChunkedDecoder drives the same calls natively.)
+
+class LayerState:
+    """KV cache (storage dtype) and fp32 KV-gradient buffers of one layer, [B, Hkv, N, D]."""
+
+    def __init__(self, B, Hkv, N, D, dtype, device):
+        self.k = torch.zeros(B, Hkv, N, D, dtype=dtype, device=device)
+        self.v = torch.zeros_like(self.k)
+        self.gk = torch.empty(B, Hkv, N, D, dtype=torch.float32, device=device)
+        self.gv = torch.empty_like(self.gk)
+        self.kept = {}      # q_start -> (O, LSE) of stage 1, when attention outputs are kept for stage 2
+        self.gather = None  # transposed backward order: (Q, dO, O, dQ of the layer, row statistics)
+        self.gather_rows = None   # ... under Alg. 2: (selected chunks, factor, chunk length, number of chunks)
+
+    def enable_gather(self, B, Hq, N, D, dtype, device):
+        """Buffers of the transposed backward order: the layer's Q, dO, O and dQ over the whole sequence,
+        [B, Hq, N, D] each (a call takes row ranges of them, so all share one set of strides), and the per-row
+        statistics the dK/dV kernel reads, fp32 [2, B, Hq, N rounded up to 4]."""
+        self.gather = tuple(torch.empty(B, Hq, N, D, dtype=dtype, device=device) for _ in range(4)) + (
+            torch.empty(2, B, Hq, (N + 3) // 4 * 4, dtype=torch.float32, device=device),)
+
+
+class ChunkAttention(torch.autograd.Function):
+    """Attention of one chunk against a layer's cache; backward deposits into the layer's KV-gradient buffers."""
+
+    @staticmethod
+    def forward(ctx, q, k_new, v_new, state, q_start, scale, weights, weight_chunk_len, keep, dq_weights=None,
+                rope_base=None):
+        # keep: None = always compute; "store" = stage 1, remember (O, LSE); "reuse" = stage 2, take them back
+        # (the rebuilt chunk has the same inputs and the kernels are deterministic, so the values are identical and
+        # the cache rows already hold this chunk's K/V)
+        if keep == "reuse":
+            # the span of stage 1 that holds this chunk's rows (the chunk itself, or a longer span to cut from)
+            s0, (o_all, lse_all) = max((kv for kv in state.kept.items() if kv[0] <= q_start), key=lambda kv: kv[0])
+            a, b = q_start - s0, q_start - s0 + q.shape[2]
+            if a == 0 and b == o_all.shape[2]:
+                o, lse = o_all, lse_all
+            else:
+                o, lse = o_all[:, :, a:b].contiguous(), lse_all[:, :, a:b].contiguous()
+        else:
+            _b.kv_append(k_new, v_new, state.k, state.v, q_start, rope_base=rope_base)   # keys are cached rotated
+            o, lse = _b.seco_chunk_attn_fwd(q, state.k, state.v, q_start, scale,
+                                            o=torch.empty(q.shape, dtype=q.dtype, device=q.device))
+            if keep == "store":
+                state.kept[q_start] = (o, lse)
+        ctx.save_for_backward(q, o, lse)
+        ctx.state, ctx.q_start, ctx.scale, ctx.weights, ctx.wlen = state, q_start, scale, weights, weight_chunk_len
+        ctx.dq_weights, ctx.rope_base = dq_weights, rope_base
+        return o
+
+    @staticmethod
+    def backward(ctx, d_o):
+        q, o, lse = ctx.saved_tensors
+        st, s0, C = ctx.state, ctx.q_start, q.shape[2]
+        d_o = d_o.contiguous()
+        if st.gather is not None:
+            # transposed order (Alg. 1 only): this chunk's finished gK/gV rows from its own and every later chunk's
+            # query rows, whose Q and dO the layer has kept; nothing is added to earlier rows
+            q_all, do_all, o_all, dq_all, stats = st.gather
+            q_all[:, :, s0:s0 + C] = q
+            do_all[:, :, s0:s0 + C] = d_o
+            o_all[:, :, s0:s0 + C] = o
+            row_w, wlen = None, None
+            if st.gather_rows is not None:      # Alg. 2: 1 on the chunk's own rows, the factor on later selected chunks
+                sel, factor, wlen, k = st.gather_rows
+                j = s0 // wlen
+                row_w = _b.spaco_gather_row_weights(sel, j, k, factor)
+            d_q = _b.seco_chunk_attn_bwd_gather(q_all[:, :, s0:], st.k, st.v, o_all[:, :, s0:s0 + C], lse,
+                                                do_all[:, :, s0:], st.gk, st.gv, s0, ctx.scale, C, stats,
+                                                d_q=dq_all[:, :, s0:s0 + C], row_weight=row_w,
+                                                weight_chunk_len=wlen).contiguous()
+        elif ctx.weights is None and ctx.dq_weights is None:
+            d_q = _b.seco_chunk_attn_bwd(q, st.k, st.v, o, lse, d_o, st.gk, st.gv, s0, ctx.scale)
+        else:
+            n_chunks = len(ctx.dq_weights) if ctx.weights is None else len(ctx.weights)
+            w = [1.0] * n_chunks if ctx.weights is None else ctx.weights
+            d_q = _b.spaco_chunk_attn_bwd(q, st.k, st.v, o, lse, d_o, st.gk, st.gv, s0, ctx.scale,
+                                          w, ctx.wlen, dq_weight=ctx.dq_weights)
+        d_k, d_v = _b.kvgrad_readout(st.gk, st.gv, s0, C, q.dtype, rope_base=ctx.rope_base)
+        return d_q, d_k, d_v, None, None, None, None, None, None, None, None
+
+
+class Rope(torch.autograd.Function):
+    """Rotary position embedding of the chunk's queries (rope_rotate); the gradient is turned back."""
+
+    @staticmethod
+    def forward(ctx, x, pos_start, base):
+        ctx.pos_start, ctx.base = pos_start, base
+        return _b.rope_rotate(x.contiguous(), pos_start, base)
+
+    @staticmethod
+    def backward(ctx, d_out):
+        return _b.rope_rotate(d_out.contiguous(), ctx.pos_start, ctx.base, inverse=True), None, None
+
+
 class ChunkedDecoder:
     """Holds the parameters (dict name -> leaf tensor on the GPU) and runs SeCO / SpaCO steps."""
 

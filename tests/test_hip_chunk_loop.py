@@ -234,3 +234,51 @@ def test_step_with_parameters_at_any_address(dtype, cfg):
     _, g = dec.step(tok.to(DEV), tgt.to(DEV), 64)
     for n in g_ref:
         assert torch.equal(g[n], g_ref[n]), n
+
+
+@pytest.mark.parametrize("transposed", [False, True])
+@pytest.mark.parametrize("rope", [False, True])
+def test_chunk_attention_composes_with_autograd(rope, transposed):
+    """LayerState, Rope and ChunkAttention between framework operators: Alg. 1 over one layer (projections, attention, a
+    loss of the outputs) leaves the gradients of whole-sequence attention at the weights and at the inputs."""
+    from paper_2505_16710_amd.chunk_loop import ChunkAttention, LayerState, Rope
+    B_, N, C, Hq, Hkv, D, dm, base = 1, 160, 64, 2, 1, 128, 64, 10000.0
+    scale = D ** -0.5
+    gen = torch.Generator().manual_seed(41)
+    rnd = lambda *s: torch.randn(*s, generator=gen, dtype=torch.float64).to(torch.bfloat16).double()
+    x, t = rnd(B_, N, dm), rnd(B_, N, Hq * D)
+    w = {n: rnd(dm, h * D) * dm ** -0.5 for n, h in (("q", Hq), ("k", Hkv), ("v", Hkv))}
+    w = {n: v.to(torch.bfloat16).double() for n, v in w.items()}
+
+    def heads(y, h):
+        return y.view(B_, -1, h, D).transpose(1, 2)
+    ref = {n: v.clone().requires_grad_() for n, v in {**w, "x": x}.items()}
+    q, k, v = (heads(ref["x"] @ ref[n], h) for n, h in (("q", Hq), ("k", Hkv), ("v", Hkv)))
+    if rope:
+        q, k = om._rope(q, 0, base), om._rope(k, 0, base)
+    (om._attend(q, k, v, 0, scale).transpose(1, 2).reshape(B_, N, -1) * t).sum().backward()
+
+    gpu = {n: v.to(torch.bfloat16).to(DEV).requires_grad_() for n, v in {**w, "x": x}.items()}
+    tg, hooked = t.to(torch.bfloat16).to(DEV), []
+    gpu["q"].register_hook(lambda g: hooked.append(g.shape))
+    st = LayerState(B_, Hkv, N, D, torch.bfloat16, DEV)
+    if transposed:
+        st.enable_gather(B_, Hq, N, D, torch.bfloat16, DEV)
+
+    def chunk(s0):
+        xc = gpu["x"][:, s0:s0 + C]
+        qc, kc, vc = (heads(xc @ gpu[n], h) for n, h in (("q", Hq), ("k", Hkv), ("v", Hkv)))
+        if rope:
+            qc = Rope.apply(qc, s0, base)
+        o = ChunkAttention.apply(qc, kc, vc, st, s0, scale, None, 0, None, None, base if rope else None)
+        return (o.transpose(1, 2).reshape(B_, xc.shape[1], -1) * tg[:, s0:s0 + C]).float().sum()
+    from paper_2505_16710_amd import kvgrad_zero
+    starts = list(range(0, N, C))
+    with torch.no_grad():
+        for s0 in starts:
+            chunk(s0)
+    kvgrad_zero(st.gk, st.gv)
+    for s0 in reversed(starts):
+        chunk(s0).backward()
+    assert len(hooked) == len(starts)
+    _compare({n: v.grad for n, v in ref.items()}, {n: v.grad for n, v in gpu.items()}, 6e-2)
