@@ -125,6 +125,37 @@ class Rope(torch.autograd.Function):
         return _b.rope_rotate(d_out.contiguous(), ctx.pos_start, ctx.base, inverse=True), None, None
 
 
+def hand_over(params, grads):
+    """Leaves every parameter's gradient in .grad (None there if no chunk reached it) and returns {name: gradient}, zeros
+    for those.  A tensor under several names gets the sum over them.  A parameter that something waits for (hooks of
+    the tensor, post-accumulate hooks, hooks of its accumulation node) receives its gradient through autograd, which
+    runs them: once per step, with the step's gradient.
+    So does a parameter that is computed from others."""
+    has_grad_hooks = (_b._ext or _b._load_ext()).has_grad_hooks
+    total = {}                                  # id -> gradient
+    for n, t in params.items():
+        g = grads.get(n)
+        if g is not None and t.requires_grad:
+            total[id(t)] = total[id(t)] + g if id(t) in total else g
+    done = set()
+    for t in params.values():
+        g = total.get(id(t))
+        if g is None or id(t) in done:
+            continue
+        done.add(id(t))
+        if t.is_leaf and not has_grad_hooks(t):
+            t.grad = g
+        else:
+            torch.autograd.backward(t, g)
+    out = {}
+    for n, t in params.items():
+        g = total.get(id(t))
+        if g is not None and t.is_leaf:
+            g = t.grad                          # (a hook may have changed or taken it)
+        out[n] = torch.zeros_like(t) if g is None else g
+    return out
+
+
 class ChunkedDecoder:
     """Holds the parameters (dict name -> leaf tensor on the GPU) and runs SeCO / SpaCO steps."""
 
@@ -139,6 +170,9 @@ class ChunkedDecoder:
              stage1_chunk_len=None, dq_weights=None, transposed_backward=False):
         """One SeCO step (selected is None: Alg. 1) or SpaCO step (Alg. 2, `selected` chunk indices,
         relay factor `factor`).  Returns (sum of the chunk losses from stage 1, {name: gradient}).
+
+        The derivatives are written out, not recorded: hooks of the parameters run once per step, with its gradient
+        (hand_over), not once per chunk, and saved-tensor hooks have nothing to see.
 
         keep_attention_outputs: stage 1 keeps every layer's O and LSE (2 + 4/D bytes per query element: with 288 GB
         of HBM that is cheap), and the rebuilt chunks of stage 2 take them back instead of running the attention
@@ -200,12 +234,4 @@ class ChunkedDecoder:
                 ext.step_train(run, tokens, targets, starts[j], min(starts[j] + chunk_len, N), keep_attention_outputs, w,
                                chunk_len, wq)
             total, grads = float(losses.sum()), dict(zip(names, ext.step_grads(run)))
-        # every parameter's gradient, also left in .grad (None there if no chunk reached it)
-        out = {}
-        for n, t in p.items():
-            g = grads.get(n)
-            if g is not None and t.requires_grad:
-                t.grad = out[n] = g
-            else:
-                out[n] = torch.zeros_like(t)
-        return total, out
+        return total, hand_over(p, grads)

@@ -8,6 +8,9 @@
 #include <map>
 #include <memory>
 
+#include <torch/csrc/autograd/function.h>
+#include <torch/csrc/autograd/variable.h>
+
 #include "binding_common.h"
 
 namespace seco_ext {
@@ -619,10 +622,20 @@ PyObject* step_grads(PyObject* const* a) {
   return list;
 }
 
+// (tensor) -> whether anything waits for a gradient to arrive at this leaf: hooks of the tensor, or of the node that
+// accumulates into its .grad
+PyObject* has_grad_hooks(PyObject* const* a) {
+  const Tensor& t = tensor(a[0]);
+  bool any = !torch::autograd::impl::hooks(t).empty() || torch::autograd::impl::post_acc_grad_hooks(t) != nullptr;
+  if (const auto node = torch::autograd::impl::try_get_grad_accumulator(t))
+    any = any || !node->pre_hooks().empty() || !node->post_hooks().empty() || !node->tensor_pre_hooks().empty();
+  return PyBool_FromLong(any);
+}
+
 }  // namespace
 
 PyMethodDef step_methods[] = {SECO_METHOD("step_new", step_new, 2),   SECO_METHOD("step_infer", step_infer, 7),
                               SECO_METHOD("step_zero", step_zero, 1), SECO_METHOD("step_train", step_train, 9),
-                              SECO_METHOD("step_grads", step_grads, 1), {nullptr, nullptr, 0, nullptr}};
+                              SECO_METHOD("step_grads", step_grads, 1), SECO_METHOD("has_grad_hooks", has_grad_hooks, 1), {nullptr, nullptr, 0, nullptr}};
 
 }  // namespace seco_ext
