@@ -9,6 +9,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "seco.h"
 
 namespace {
@@ -285,10 +287,15 @@ __global__ __launch_bounds__(kThreads) void cross_entropy_kernel(T* logits, cons
 }
 
 // One workgroup per row r; the one of a token's first row adds up all of the token's rows, in order, the others leave.
-// A wavefront compares 64 tokens at a time and walks the matches by the bits of the result.
+// What bounds it is the token that occurs most often (padding, a frequent word): one workgroup adds up all of its rows.
+// So the rows are first listed, kScan tokens at a time, and then taken kAhead at a time, their loads in flight
+// together.  Measured at 1024 columns of bf16, walked one by one, each load behind the last -> here: 4096 rows of one token
+// 1275 -> 257 us, of which 5 % are one token 52 -> 21, uniform tokens 17 -> 15; 512 rows 85 -> 33, 8.7 -> 7.2, 4.8 -> 4.9.
 template <typename T, int V>
 __global__ __launch_bounds__(kThreads) void embedding_bwd_kernel(const T* d_x, const int64_t* token, T* grad, int64_t rows,
                                                                  int64_t d, int64_t v) {
+  constexpr int kWaves = kThreads / 64, kTurns = 8, kScan = kTurns * kThreads, kAhead = 16;
+  __shared__ int list[kScan], found[kTurns * kWaves];
   auto index = [&](int64_t i) { return token[i] < 0 ? token[i] + v : token[i]; };   // negative: counted from the end
   const int64_t r = blockIdx.x, t = index(r);
   if (t < 0 || t >= v) return;
@@ -296,22 +303,53 @@ __global__ __launch_bounds__(kThreads) void embedding_bwd_kernel(const T* d_x, c
   for (int64_t i = threadIdx.x; i < r; i += kThreads)
     if (index(i) == t) earlier = 1.f;
   if (block_reduce<Sum>(earlier) != 0.f) return;
-  const int lane = threadIdx.x & 63;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   T* out = grad + t * d;
-  for (int64_t c0 = 0; c0 < d; c0 += kThreads * V) {      // (every lane takes part in the comparisons)
+  for (int64_t c0 = 0; c0 < d; c0 += kThreads * V) {
     const int64_t c = c0 + threadIdx.x * V;
     float f[V], x[V];
 #pragma unroll
     for (int j = 0; j < V; ++j) f[j] = 0.f;
-    for (int64_t i0 = r; i0 < rows; i0 += 64) {
-      uint64_t hit = __builtin_amdgcn_ballot_w64(i0 + lane < rows && index(i0 + lane < rows ? i0 + lane : r) == t);
-      for (; hit; hit &= hit - 1) {
-        if (c < d) {
-          load<T, V>(d_x + (i0 + __builtin_ctzll(hit)) * d + c, x);
+    for (int64_t i0 = r; i0 < rows; i0 += kScan) {
+      uint64_t hit[kTurns];
 #pragma unroll
-          for (int j = 0; j < V; ++j) f[j] += x[j];
-        }
+      for (int u = 0; u < kTurns; ++u) {
+        const int64_t i = i0 + u * kThreads + threadIdx.x;
+        hit[u] = __builtin_amdgcn_ballot_w64(i < rows && index(i < rows ? i : r) == t);
+        if (lane == 0) found[u * kWaves + wave] = __builtin_popcountll(hit[u]);
       }
+      __syncthreads();
+      int n = 0, mine[kTurns];
+#pragma unroll
+      for (int k = 0; k < kTurns * kWaves; ++k) {        // positions in ascending order of the rows
+        if (k % kWaves == wave) mine[k / kWaves] = n;
+        n += found[k];
+      }
+#pragma unroll
+      for (int u = 0; u < kTurns; ++u)
+        if (hit[u] >> lane & 1)
+          list[mine[u] + __builtin_popcountll(hit[u] & (((uint64_t)1 << lane) - 1))] = u * kThreads + threadIdx.x;
+      __syncthreads();
+      n = __builtin_amdgcn_readfirstlane(n);
+      const int64_t at = c < d ? c : d - V;
+      auto add = [&](auto ahead, int k0, int there) {     // there: how many are left (uniform, like the row numbers)
+        constexpr int A = decltype(ahead)::value;
+        Vec<T, V> w[A];
+#pragma unroll
+        for (int k = 0; k < A; ++k)
+          w[k] = *reinterpret_cast<const Vec<T, V>*>(d_x + (i0 + __builtin_amdgcn_readfirstlane(list[k0 + (k < there ? k : 0)])) * d + at);
+#pragma unroll
+        for (int k = 0; k < A; ++k)
+          if (k < there) {
+            w[k].get(x);
+#pragma unroll
+            for (int j = 0; j < V; ++j) f[j] += x[j];
+          }
+      };
+      int k0 = 0;
+      for (; n - k0 >= kAhead; k0 += kAhead) add(std::integral_constant<int, kAhead>{}, k0, kAhead);
+      for (; k0 < n; k0 += 2) add(std::integral_constant<int, 2>{}, k0, n - k0);
+      __syncthreads();                                   // the list and the counts are free again
     }
     if (c < d) {
       load<T, V>(out + c, x);

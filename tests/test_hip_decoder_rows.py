@@ -65,3 +65,32 @@ def test_cross_entropy_in_fp32_keeps_fp32_precision(v):
     assert float(((dev.cpu().double() - p).abs() / p)[off].max()) < 24 * U
     on = dev.cpu().double().gather(1, target[:, None]) - (p.gather(1, target[:, None]) - 1)
     assert float(on.abs().max()) < 24 * U
+
+
+@pytest.mark.parametrize("dtype", [F32, BF16])
+@pytest.mark.parametrize("rows,d,v,kind", [
+    (1, 8, 1, "uniform"), (300, 64, 29, "uniform"), (257, 29, 5, "uniform"), (64, 2056, 7, "negative"),
+    (2049, 40, 3, "same"), (2500, 1032, 1000, "same"), (4500, 16, 900, "frequent"), (2048, 1027, 2, "frequent"),
+])
+def test_embedding_gradient(dtype, rows, d, v, kind):
+    """Rows of a token are added in fp32, in order: within (n + 1) U of the sum of their magnitudes, and one rounding."""
+    gen = torch.Generator().manual_seed(rows + d)
+    dt = torch.float32 if dtype == F32 else torch.bfloat16
+    x = torch.randn(rows, d, generator=gen).to(dt)
+    base = torch.randn(v + 1, d, generator=gen).to(dt)          # the last row lies behind the table
+    tok = torch.randint(0, v, (rows,), generator=gen)
+    if kind == "negative":
+        tok = torch.where(torch.rand(rows, generator=gen) < 0.5, tok - v, tok)
+    elif kind == "same":
+        tok[:] = v - 1
+    elif kind == "frequent":
+        tok[torch.rand(rows, generator=gen) < 0.4] = 0
+    grad = base.to(DEV)
+    _call("embedding_bwd", dtype, x.to(DEV), tok.to(DEV), grad, rows, d, v)
+    at = torch.where(tok < 0, tok + v, tok)
+    ref = base.double().index_add(0, at, x.double())
+    size = base.double().abs().index_add(0, at, x.double().abs())
+    n = torch.bincount(at, minlength=v + 1)[:, None].double()
+    bound = (n + 1) * U * size + (2.0 ** -8 * ref.abs() if dtype == BF16 else 0)
+    assert torch.equal(grad[v].cpu(), base[v])
+    assert ((grad.cpu().double() - ref).abs() <= bound).all()
