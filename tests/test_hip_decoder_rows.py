@@ -94,3 +94,113 @@ def test_embedding_gradient(dtype, rows, d, v, kind):
     bound = (n + 1) * U * size + (2.0 ** -8 * ref.abs() if dtype == BF16 else 0)
     assert torch.equal(grad[v].cpu(), base[v])
     assert ((grad.cpu().double() - ref).abs() <= bound).all()
+
+
+# Row lengths: the blocks of a row kept in registers are 1, 2 or 4 of 256 words (a word: 8 bf16 or 4 fp32 where the rows
+# start on 16-byte boundaries, else one element), what is left of a longer row is read twice.
+LENGTHS = [(BF16, 8), (BF16, 2048), (BF16, 2056), (BF16, 4096), (BF16, 4104), (BF16, 8192), (BF16, 10248),
+           (F32, 4), (F32, 1024), (F32, 1028), (F32, 2052), (F32, 4096), (F32, 5000),
+           (BF16, 1), (BF16, 255), (BF16, 257), (BF16, 513), (BF16, 1025), (F32, 1023), (F32, 2047)]
+
+
+def _rows(dtype, seed, *shape):
+    x = torch.randn(*shape, generator=torch.Generator().manual_seed(seed))
+    return x.to(torch.float32 if dtype == F32 else torch.bfloat16)
+
+
+def _norm64(x, gain):
+    r = torch.rsqrt((x * x).mean(1, keepdim=True) + 1e-6)
+    return r, x * r, x * r * gain
+
+
+@pytest.mark.parametrize("residual", ["none", "in place", "apart"])
+@pytest.mark.parametrize("dtype,d", LENGTHS)
+def test_add_rmsnorm(dtype, d, residual):
+    """Sums of d squares and a reciprocal root in fp32 (64 U), then a rounding of the row and one of the product."""
+    rows = 5
+    x, y, gain = _rows(dtype, d, rows, d), _rows(dtype, d + 1, rows, d), _rows(dtype, d + 2, d) + 1
+    dx, dy = x.to(DEV), None if residual == "none" else y.to(DEV)
+    out = None if residual == "none" else dx if residual == "in place" else torch.empty_like(dx)
+    h, r = torch.empty_like(dx), torch.empty(rows, device=DEV)
+    _call("add_rmsnorm", dtype, dx, dy, gain.to(DEV), out, h, r, rows, d)
+    s = x if dy is None else (x.float() + y.float()).to(x.dtype)
+    if out is not None:
+        assert torch.equal(out.cpu(), s)
+    if residual != "in place":
+        assert torch.equal(dx.cpu(), x)
+    r64, _, h64 = _norm64(s.double(), gain.double())
+    eps = 64 * U + (2.0 ** -7 + 2.0 ** -16 if dtype == BF16 else 0)     # (two roundings to 8 bits, 2^-8 each)
+    assert ((r.cpu().double()[:, None] - r64).abs() <= 64 * U * r64).all()
+    assert ((h.cpu().double() - h64).abs() <= eps * h64.abs()).all()
+
+
+@pytest.mark.parametrize("rows,d_in", [(1, "none"), (7, "in place"), (300, "apart"), (300, "none")])
+@pytest.mark.parametrize("dtype,d", LENGTHS)
+def test_rmsnorm_backward(dtype, d, rows, d_in):
+    """Terms and sums in fp32, 64 U of the magnitudes added up; in bf16 one rounding of d_x, and the normalised row of the
+    gain's gradient rounded first."""
+    x, dh, extra = (_rows(dtype, d + i, rows, d) for i in (3, 4, 5))
+    gain, r = _rows(dtype, d + 6, d) + 1, None
+    r64, n64, _ = _norm64(x.double(), gain.double())
+    r = r64[:, 0].float()
+    n64 = x.double() * r.double()[:, None]
+    part = torch.randn(256, d, generator=torch.Generator().manual_seed(d + 7))
+    dev = {"x": x.to(DEV), "dh": dh.to(DEV), "in": extra.to(DEV), "part": part.to(DEV)}
+    out = dev["in"] if d_in == "in place" else torch.empty_like(dev["x"])
+    _call("rmsnorm_bwd", dtype, dev["x"], gain.to(DEV), r.to(DEV), dev["dh"], None if d_in == "none" else dev["in"], out,
+          dev["part"], rows, d)
+    e = dh.double() * gain.double()
+    mean, mean_abs = (e * n64).mean(1, keepdim=True), (e * n64).abs().mean(1, keepdim=True)
+    base = torch.zeros_like(e) if d_in == "none" else extra.double()
+    r64 = r.double()[:, None]
+    ref = base + r64 * (e - n64 * mean)
+    size = base.abs() + r64 * (e.abs() + n64.abs() * mean_abs)
+    eps = 2.0 ** -8 if dtype == BF16 else 0.0
+    assert ((out.cpu().double() - ref).abs() <= 64 * U * size + eps * ref.abs()).all()
+    got = dev["part"].cpu().double().sum(0) - part.double().sum(0)
+    want = (dh.double() * n64).sum(0)
+    size = part.double().abs().sum(0) + (dh.double() * n64).abs().sum(0)
+    assert ((got - want).abs() <= 64 * U * size + eps * (dh.double() * n64).abs().sum(0)).all()
+    if rows < 256:
+        assert torch.equal(dev["part"].cpu()[rows:], part[rows:])
+
+
+@pytest.mark.parametrize("dtype", [F32, BF16])
+@pytest.mark.parametrize("v", [1, 29, 2048, 4104, 10000])
+def test_cross_entropy_targets(dtype, v):
+    """Targets inside, -100 (no loss, no gradient) and outside (NaN in that row alone)."""
+    rows = 8
+    logits = 4 * _rows(dtype, v, rows, v).float()
+    logits = logits.to(torch.float32 if dtype == F32 else torch.bfloat16)
+    target = torch.randint(0, v, (rows,), generator=torch.Generator().manual_seed(v))
+    target[1], target[3], target[4], target[6] = -100, v, -1, v - 1
+    dev, loss = logits.to(DEV), torch.empty(rows, device=DEV)
+    _call("cross_entropy", dtype, dev, target.to(DEV), loss, rows, v)
+    assert torch.equal(dev.cpu(), logits)
+    good = torch.tensor([0, 2, 5, 6, 7])
+    lse = torch.logsumexp(logits.double(), 1)
+    ref = lse[good] - logits.double()[good, target[good]]
+    assert float((loss.cpu().double()[good] - ref).abs().max()) < 64 * U * max(1.0, float(lse.abs().max()))
+    assert float(loss[1]) == 0.0 and torch.isnan(loss[3:5]).all()
+    _call("cross_entropy", dtype, dev, target.to(DEV), None, rows, v)
+    got = dev.cpu().double()
+    p = torch.softmax(logits.double(), 1)
+    ref = p.clone()
+    ref[good, target[good]] -= 1
+    eps = 256 * U + (2.0 ** -8 if dtype == BF16 else 0)                 # bf16 rows: exp is off by |x| U, |x| < 64
+    assert ((got - ref)[good].abs() <= eps * (ref[good].abs() + 256 * U)).all()
+    assert not got[1].any() and torch.isnan(got[3:5]).all()
+
+
+@pytest.mark.parametrize("dtype,n", [(BF16, 8), (BF16, 9), (BF16, 65536 * 2048 + 2048 * 3), (F32, 4), (F32, 1023)])
+def test_silu_lengths(dtype, n):
+    """The shortest and odd lengths, and one that the largest grid walks more than once."""
+    u = _rows(dtype, 1, min(n, 1 << 20)).repeat(-(-n // (1 << 20)))[:n].contiguous()
+    dev = u.to(DEV)
+    out = torch.zeros(n + 8, dtype=u.dtype, device=DEV)
+    _call("silu", dtype, dev, out, n)
+    assert not out[n:].any()
+    f = dev.float()
+    ref = f * torch.sigmoid(f)
+    eps = 16 * U + (2.0 ** -8 if dtype == BF16 else 0)
+    assert ((out[:n].float() - ref).abs() <= eps * ref.abs()).all()
