@@ -75,9 +75,25 @@ struct Step {
   Tensor view(void* p, at::IntArrayRef sizes, const Param& w) { return at::from_blob(p, sizes, w.w.options().requires_grad(false)); }
 
   // ---- matrix products: the library's own kernel where it takes the operands, the framework's otherwise
+  // Small products are bound by their launch, which costs 17 - 19 us of host time through the framework and 3 here; of large
+  // ones the framework's kernels are faster, by up to 1.8 times at 8192 rows.  The line between them, in multiply-adds and
+  // by the rows of the chunk (R; gradients: of the matrix), lies where the two meet.  Measured with epilogue against
+  // product and row pass, in us, own / framework, R x K -> N:
+  //   forward     2048 x 4096 -> 1024  29 / 36     1024 x 4096 -> 4096  41 / 45     2048 x 2048 -> 8192  78 / 71
+  //               4096 x 1024 -> 1024  18 / 22     8192 x 1024 -> 1024  29 / 30     4096 x 4096 -> 1024  51 / 44
+  //   backward    2048 x 2048 <- 2048  26 / 27     1024 x 4096 <- 4096  41 / 41     2048 x 4096 <- 4096  74 / 67
+  //               4096 x 1024 <- 1024  18 / 23     8192 x 1024 <- 1024  29 / 30     4096 x 1024 <- 4096  50 / 42
+  //   gradient    512: 4096 x 1024  12 / 18     8192: 4096 x 4096  236 / 255     512: 8192 x 2048  39 / 28
+  //               2048: 4096 x 14336  267 / 273     8192: 4096 x 14336  1054 / 1010     2048: 14336 x 4096  297 / 273
+  static bool worth(int form, int64_t M, int64_t N_, int64_t K) {
+    const double work = (double)M * N_ * K;
+    if (form == DEC_GEMM_NN) return work <= (M <= 2048 ? 0x1p34 : 0x1p33);
+    if (form == DEC_GEMM_NT) return work <= (M <= 2048 ? 0x1p33 : 0x1p32);
+    return M <= 4096 && work < 0x1p38;
+  }
   // (operands have the type of the matrix)
   static bool own(const Param& w, int form, int64_t M, int64_t N_, int64_t K, int64_t lda, int64_t ldb, int64_t ldc) {
-    return w.w.scalar_type() == at::kBFloat16 && lib.dec_gemm_supported(form, M, N_, K, lda, ldb, ldc);
+    return w.w.scalar_type() == at::kBFloat16 && worth(form, M, N_, K) && lib.dec_gemm_supported(form, M, N_, K, lda, ldb, ldc);
   }
   // c[M, n] = a[M, K] w[K, n]
   void mm(void* c, void* a, const Param& w, int64_t M) {

@@ -4,7 +4,8 @@
 //
 // What bounds them: at the row counts of a chunk (512 rows, 1 - 4 thousand columns) a product is 1 - 4 GFLOP, a few
 // microseconds of matrix work on 256 CUs, so launch cost and latency count, not the matrix pipe.  A call of the
-// library product through the framework took 17 - 19 us of host time, twice its kernel; a launch here takes 3.
+// library product through the framework took 17 - 19 us of host time, twice its kernel; a launch here takes 3.  Above
+// about 10 GMAC the framework's kernels are faster, and the training step takes those (worth() in chunk_step_ext.cpp).
 //
 // A workgroup (4 wavefronts, 2 x 2, or two such groups that take the steps in turn) owns a BM x BN tile of C and walks
 // the contraction in steps of 64 through a ring of kStages LDS slots filled by direct global -> LDS copies, kStages - 1

@@ -282,3 +282,21 @@ def test_chunk_attention_composes_with_autograd(rope, transposed):
         chunk(s0).backward()
     assert len(hooked) == len(starts)
     _compare({n: v.grad for n, v in ref.items()}, {n: v.grad for n, v in gpu.items()}, 6e-2)
+
+
+def test_step_whose_products_are_partly_the_frameworks():
+    """An MLP 8192 wide: the gradient of w2 is taller than the library's own product is used for, the others are not; with
+    more rows, forward and backward products cross the line too, and agree with those of shorter chunks to rounding."""
+    import dataclasses
+    cfg = dataclasses.replace(BF16_CFG, n_layers=1, d_model=512, d_ff=8192, vocab=64)
+    p64, dec, tok, tgt = _setup(cfg, 37, 1, 128, torch.bfloat16)
+    _, g_ref = om.monolithic_grads(cfg, p64, tok, tgt)
+    _, g = dec.step(tok.to(DEV), tgt.to(DEV), 64)
+    _compare(g_ref, g, 6e-2)
+    gen = torch.Generator().manual_seed(38)
+    tok, tgt = (torch.randint(0, cfg.vocab, (1, 4608), generator=gen).to(DEV) for _ in range(2))
+    loss_a, g_a = dec.step(tok, tgt, 4608)      # 4608 x 512 x 8192 multiply-adds
+    loss_b, g_b = dec.step(tok, tgt, 512)
+    assert abs(loss_a - loss_b) < 1e-3 * loss_b
+    for n in g_a:
+        assert float((g_a[n].float() - g_b[n].float()).norm() / g_b[n].float().norm()) < 2e-2, n
