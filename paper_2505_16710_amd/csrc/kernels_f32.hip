@@ -27,6 +27,8 @@ namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int kRows = 16;   // rows a workgroup owns
+// blocks of 16 that every head_dim that NT blocks are used for (SECO_F32_DISPATCH) fills; past head_dim lie later ones
+template <int NT> constexpr int kWhole = NT <= 2 ? 0 : NT <= 4 ? 2 : NT <= 5 ? 4 : NT <= 8 ? 5 : NT <= 12 ? 8 : 12;
 
 __device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
@@ -293,22 +295,36 @@ __device__ __forceinline__ void dkdv_f32(const AttnParams& p, const SegTable& se
   f32x4 dk[ND][4], dv[ND][4];
   clear<ND>(dk);
   clear<ND>(dv);
+  // the group's first head (per-head products of 64-bit strides in the loop would cost scalar registers that are not there)
+  const int h0 = kvh * p.G;
+  const float* q_group = static_cast<const float*>(p.q) + b * p.qs[0] + h0 * p.qs[1];
+  const float* do_group = static_cast<const float*>(p.d_o) + b * p.os[0] + h0 * p.os[1];
+  const float* o_group = static_cast<const float*>(p.o) + b * p.os[0] + h0 * p.os[1];
+  const float* lse_group = p.lse + ((int64_t)b * p.Hq + h0) * p.C;
   const int rb0 = max(0, c0 - p.q_start) / kRows, n_rb = (p.C + kRows - 1) / kRows - rb0;   // row blocks that see the tile
   for (int it = w; it < n_rb * p.G; it += NW) {
-    const int hg = it / n_rb, q0 = (rb0 + it - hg * n_rb) * kRows, h = kvh * p.G + hg, row = min(q0 + i, p.C - 1);
-    const int64_t orow = b * p.os[0] + h * p.os[1] + (int64_t)row * p.os[2];
+    const int hg = it / n_rb, q0 = (rb0 + it - hg * n_rb) * kRows, row = min(q0 + i, p.C - 1);
+    const int64_t orow = hg * p.os[1] + (int64_t)row * p.os[2];
     f32x4 pr, ds, x[4][ND], qx[NT], dox[NT];
-    load_rows<NT>(static_cast<const float*>(p.q) + b * p.qs[0] + h * p.qs[1] + (int64_t)row * p.qs[2], D, g, qx);
-    load_rows<NT>(static_cast<const float*>(p.d_o) + orow, D, g, dox);
-    const float lse = p.lse[((int64_t)b * p.Hq + h) * p.C + row] * kLog2e;
+    // (the longest rows: Q is requested when O is no longer needed; with all three in registers beside K, V and both
+    // sums 31 of them went to memory, in every iteration)
+    constexpr bool kLate = NT > 12;
+    const float* qrow = q_group + hg * p.qs[1] + (int64_t)row * p.qs[2];
+    if (!kLate) load_rows<NT>(qrow, D, g, qx);
+    load_rows<NT>(do_group + orow, D, g, dox);
+    const float lse = lse_group[(int64_t)hg * p.C + row] * kLog2e;
     float delta = 0.f;                                  // of row i
     {
       f32x4 ox[NT];
-      load_rows<NT>(static_cast<const float*>(p.o) + orow, D, g, ox);
+      load_rows<NT>(o_group + orow, D, g, ox);
 #pragma unroll
       for (int t = 0; t < NT; ++t)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) delta += 16 * t + 4 * g < D ? ox[t][j] * dox[t][j] : 0.f;
+        for (int j = 0; j < 4; ++j) delta += t < kWhole<NT> || 16 * t + 4 * g < D ? ox[t][j] * dox[t][j] : 0.f;
+    }
+    if (kLate) {
+      asm volatile("" : "+v"(delta) : : "memory");
+      load_rows<NT>(qrow, D, g, qx);
     }
     delta += __shfl_xor(delta, 16);
     delta += __shfl_xor(delta, 32);

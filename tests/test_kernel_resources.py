@@ -1,5 +1,7 @@
 """Compile-time resource check of the matrix-core kernels (no GPU needed: hipcc cross-compiles): none may spill
-registers, and each must leave room for two wavefronts per SIMD, which their latency hiding is built on."""
+registers, and each must leave room for two wavefronts per SIMD, which their latency hiding is built on.  (fp32 kernels
+for the longer rows excepted: a wavefront that holds 16 rows of K and V and both sums of a head_dim over 80 needs more
+than half a SIMD's registers, and every row of a stage it holds besides saves a second read.)"""
 import os
 import re
 import subprocess
@@ -10,7 +12,15 @@ import pytest
 
 from paper_2505_16710_amd import build as B
 
-KERNEL_FILES = ["fwd_bf16.hip", "fwd4_bf16.hip", "fwd4_split_bf16.hip", "bwd_dq_bf16.hip", "bwd_dkdv_bf16.hip"]
+KERNEL_FILES = ["fwd_bf16.hip", "fwd4_bf16.hip", "fwd4_split_bf16.hip", "bwd_dq_bf16.hip", "bwd_dkdv_bf16.hip", "fwd_small_bf16.hip",
+                "gemm_bf16.hip", "kernels_f32.hip"]
+# blocks of 16 of the head_dim from which on one wavefront per SIMD is taken
+ONE_WAVE = {"fwd_f32_kernel": 16, "bwd_f32_kernel": 8}
+
+
+def _least_waves(name):
+    m = re.search(r"(fwd_f32_kernel|bwd_f32_kernel)ILi(\d+)E", name)
+    return 1 if m and int(m.group(2)) >= ONE_WAVE[m.group(1)] else 2
 
 
 def _usage(src):
@@ -67,7 +77,7 @@ def test_matrix_core_kernels_do_not_spill():
             # parks launch constants that way - as long as none of it happens inside a loop (checked below)
             assert sspill <= 24, (src, name, sspill)
             spilling.add(src if sspill else None)
-            assert occ is not None and occ >= 2, (src, name, occ)
-    assert seen >= 10                    # 1 + 2 forward, 6 dQ, 1 dK/dV instantiations
+            assert occ is not None and occ >= _least_waves(name), (src, name, occ)
+    assert seen >= 54                    # 5 forward, 6 dQ, 1 dK/dV, 30 product, 12 fp32 instantiations at least
     for src in sorted(x for x in spilling if x):
         assert _lane_moves_in_loops(src) == [], src
