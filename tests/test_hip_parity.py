@@ -51,7 +51,7 @@ def test_fp32_shapes(B, Hq, Hkv, N, D, C):
     check(got, ref, "f32", f"f32 {B,Hq,Hkv,N,D,C}")
 
 
-@pytest.mark.parametrize("D", [4, 60, 68, 128, 132, 192, 196, 252])
+@pytest.mark.parametrize("D", [4, 36, 60, 68, 84, 128, 132, 192, 196, 252])
 @pytest.mark.parametrize("N,C", [(17, 17), (49, 16), (95, 31), (290, 145)])
 def test_fp32_tile_edges(D, N, C):
     """16-row tiles, head_dim in blocks of 64: chunk lengths and head dims on both sides of the edges, G = 3, with
