@@ -197,9 +197,10 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
     if (x.r0 + BQ <= row_limit(x)) {
       const __bf16* q_src = src.q;
       const __bf16* do_src = src.d_o;
+      const uint32_t lds = OWN ? opaque(lds_wave) : lds_wave;
 #pragma unroll
       for (int i = 0; i < kCopies; ++i) {
-        const uint32_t dst = lds_wave + slot * kTileBytes + i * (4 * NW * kRowBytes);
+        const uint32_t dst = lds + slot * kTileBytes + i * (4 * NW * kRowBytes);
         dma16_sbase(q_src, q_lane_off[i], dst);
         dma16_sbase(do_src, do_lane_off[i], dst + kDoRegion);
       }

@@ -32,7 +32,8 @@ constexpr int BNW = 64;   // cache rows per wavefront and tile
 
 // seg (SPARSE only): runs of cache rows in ascending order, each with a positive weight
 // smem: 4 * kTileBytes, [buf][K|V]
-template <int KH, bool SPLIT, bool SPARSE>
+// FUSED: inside the kernel that holds dK/dV too, where scalar registers are short (opaque)
+template <int KH, bool SPLIT, bool SPARSE, bool FUSED = false>
 __device__ __forceinline__ void dq_bf16_body(const AttnParams& p, const SegTable& seg, int n_mtiles, int item, lds_char* smem) {
   static_assert(!SPLIT || KH == 2, "the split variant uses the 8-wavefront shape");
   constexpr int BN = BNW * KH;
@@ -136,9 +137,10 @@ __device__ __forceinline__ void dq_bf16_body(const AttnParams& p, const SegTable
     if (col + BN <= kv_len) {
       const __bf16* kt_src = kbase + (int64_t)col * p.kvs[2];
       const __bf16* vt_src = vbase + (int64_t)col * p.kvs[2];
+      const uint32_t lds = FUSED ? opaque(lds_wave) : lds_wave;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const uint32_t dst = lds_wave + buf * 2 * kTileBytes + i * (16 * KH * kRowBytes);
+        const uint32_t dst = lds + buf * 2 * kTileBytes + i * (16 * KH * kRowBytes);
         dma16_sbase(kt_src, lane_off[i], dst);
         dma16_sbase(vt_src, lane_off[i], dst + kTileBytes);
       }

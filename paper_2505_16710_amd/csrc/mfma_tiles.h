@@ -147,6 +147,13 @@ __device__ __forceinline__ uint32_t dma_lane_offset(int r, int64_t row_stride_by
   const int row = r + (lane >> 4);
   return (uint32_t)(row * row_stride_bytes) + (uint32_t)((((lane & 15) ^ swz(row))) << 4);
 }
+// The same value to the compiler's eyes a new one: destinations derived from it are added up where they are used instead
+// of being kept, one scalar register each, over a whole loop (where scalar registers run out, in the kernel that holds
+// both passes of the backward).
+__device__ __forceinline__ uint32_t opaque(uint32_t scalar) {
+  asm volatile("" : "+s"(scalar));
+  return scalar;
+}
 __device__ __forceinline__ void dma_wait_all() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // Make the compiler wait, here, for the load that produces `v`.  Used on operand fragments that are
