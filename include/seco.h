@@ -376,14 +376,19 @@ size_t seco_workspace_bytes(const seco_desc* desc, int op);
 size_t seco_workspace_bytes_preferred(const seco_desc* desc, int op);
 
 /*
- * How the bf16 kernels would be launched for this desc (host arithmetic only, nothing is launched; for tests and
- * tuning).  n_col_tiles: number of 128-row cache tiles the dK/dV pass of the call covers (rows with non-zero
- * weight, each run of equal weight rounded up to whole tiles).  plan_host receives four values:
+ * The two general planning rules of the bf16 kernels for this desc (host arithmetic only, nothing is launched; for
+ * tests and tuning).  n_col_tiles: number of 128-row cache tiles the dK/dV pass of the call covers (rows with
+ * non-zero weight, each run of equal weight rounded up to whole tiles).  plan_host receives four values:
  *   [0] workgroups that share the cache rows of one row tile in the forward / dQ pass (1: no division)
  *   [1] row tiles of the forward / dQ pass (work items before that division)
- *   [2] cache tiles per (batch, KV head), counted from the last, that the dK/dV pass shares out by query head
- *   [3] workgroups per such tile (1: none); [2] * [3] * batch * n_kv_heads never exceeds the device's compute units
- * A call whose tiles still leave compute units idle shares them out further, by query rows.
+ *   [2] cache tiles per (batch, KV head), counted from the last, that the dK/dV pass shares out because its last round
+ *       of workgroups would be at most half full
+ *   [3] workgroups per such tile, at least (1: none); [2] * [3] * batch * n_kv_heads never exceeds the device's
+ *       compute units
+ * Three things they do not cover: a forward of at most 32 query rows per KV head (chunk_len * n_q_heads / n_kv_heads)
+ * divides the cache by a rule of its own; a backward that runs in one launch (SECO_PROFILE_BWD) chooses its own number
+ * of shares for both passes; a dK/dV pass whose tiles all fit one round, or whose estimated time falls, shares tiles
+ * out further, by query rows.
  * Returns SECO_OK, or the status of an invalid desc; SECO_ERR_DTYPE for fp32 (its kernels have one shape).
  */
 int seco_launch_plan(const seco_desc* desc, int32_t n_col_tiles, int32_t* plan_host);

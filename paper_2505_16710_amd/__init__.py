@@ -1,8 +1,8 @@
 """MI355X-native chunk-wise attention for SeCO / SpaCO (thin binding over libseco_hip.so).
 
-The package holds the HIP sources (csrc/), the build script and a ctypes binding whose
-functions carry the names of the C ABI in include/seco.h.  Every step of the path runs in
-the HIP kernels; PyTorch is used only for device memory and streams.  There is no CPU or
+The package holds the HIP sources (csrc/), the build script and a binding (an extension module for the calls
+that take tensors, ctypes for the host-only ones) whose functions carry the names of the C ABI in
+include/seco.h.  Every step of the path runs in the HIP kernels; PyTorch is used only for device memory and streams.  There is no CPU or
 PyTorch fallback: if the library has not been built, importing the binding raises.
 """
 from .binding import (  # noqa: F401

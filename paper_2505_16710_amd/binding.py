@@ -293,7 +293,8 @@ def _profile_mask(kinds):
 
 
 def seco_launch_plan(desc, n_col_tiles):
-    """(splits per row tile, row tiles, shared-out cache tiles per (batch, KV head), workgroups per such tile)."""
+    """(splits per row tile, row tiles, shared-out cache tiles per (batch, KV head), workgroups per such tile) by the general
+    planning rules; include/seco.h says which calls follow rules of their own."""
     out = (C.c_int32 * 4)()
     _check(load_library().seco_launch_plan(C.byref(desc), int(n_col_tiles), out), "seco_launch_plan")
     return tuple(out)

@@ -6,16 +6,22 @@ forward of a chunk is `seco_chunk_attn_fwd` against the cache, its backward is `
 `spaco_chunk_attn_bwd`, which deposits the chunk's dK/dV on every visible cache row, and the gradient
 handed to the chunk's own recomputed K/V is simply the chunk's rows of those buffers (they hold what
 the later chunks deposited plus the chunk's own diagonal block: the relay of Alg. 1, `m_i.grad <-
-m'_i.grad`), read out by `kvgrad_readout`; new keys / values enter the cache through `kv_append`.  Under SpaCO the deposits on earlier selected chunks carry the compensation
-factor, so a chain through p caches is scaled by factor^p (Sec. 5).
+m'_i.grad`), read out by `kvgrad_readout`; new keys / values enter the cache through `kv_append`.  Under
+SpaCO the deposits on earlier selected chunks carry the compensation factor, so a chain through p caches is
+scaled by factor^p (Sec. 5).
 
 The projections and the MLP, the residual adds, norms, SiLU, loss and embedding gradient around the attention are
 kernels of the library too (gemm_bf16.hip, decoder.hip), the derivatives are written out instead of being recorded, and
 a chunk is launched by one call of the binding's extension module (chunk_step_ext.cpp): at the row counts of a chunk a
 step is bound by the number of launches and the host time behind each (with autograd and framework operators, 27 ms for
-two layers over 4096 tokens in chunks of 512, of which the GPU worked 14).  Products whose type or alignment the
-library's kernel does not take (fp32, row lengths that are not multiples of 8) go through the framework's.  Only one
-chunk's activations are alive at a time, as in the paper.  There is no CPU path.
+two layers over 4096 tokens in chunks of 512, of which the GPU worked 14; 4.8 now).  Products whose type or alignment
+the library's kernel does not take (fp32, row lengths that are not multiples of 8) and large ones, which the framework's
+kernels do faster, go through the framework's.  Only one chunk's activations are alive at a time, as in the paper.
+There is no CPU path.  (LayerState, ChunkAttention and Rope are the same attention as autograd functions.)
+
+Parameters are bf16 or fp32 tensors on one GPU, all of one type, with two exceptions: gains may be of a narrower one, and
+behind a bf16 body norm_f and head may both be fp32.  Anything else that does not fit is refused before it reaches a
+kernel.
 
 Model (fixed here so that a checker can build the same function): pre-norm decoder, RMSNorm with
 eps 1e-6, grouped-query causal attention (optionally with rotary position embedding), MLP x + silu(h W1) W2, final

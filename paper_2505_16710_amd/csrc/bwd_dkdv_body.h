@@ -37,10 +37,11 @@
 // one non-zero weight); SpaCO's unselected chunks simply have no tiles.
 //
 // A workgroup occupies a whole CU, so a launch runs in rounds of 256 column tiles and a last round with few
-// tiles costs as much as a full one.  When the last round would hold at most 128 tiles, the last column tiles
-// of every (batch, KV head) are therefore divided among 2 or 4 workgroups by query head: each writes its
-// fp32 sums to the workspace and dkdv_tail_merge_kernel adds them to gK/gV in head order (still one writer
-// per element and a fixed summation order, so results stay reproducible).
+// tiles costs as much as a full one.  The last column tiles of every (batch, KV head) are therefore shared out
+// where that is expected to pay (share_plan in seco_internal.h): a share is a run of the tile's iterations (64 query rows
+// of one head each, cut through heads where the number of shares asks for it), its fp32 sums go to the workspace, and
+// a merge adds them to gK/gV in the order of the shares (still one writer per element and a fixed summation order, so
+// results stay reproducible).
 //
 // The same kernel serves the transposed order of the backward pass (seco_chunk_attn_bwd_gather): there the column
 // run is one chunk and the query rows are that chunk's and every later one's, p.C of them from p.q_start on, with

@@ -4,11 +4,11 @@
 // and each with 6 - 9 us before its first product and behind its last.  The passes do not need each other's results: all
 // that dK/dV takes from dQ are the row statistics, which are cheap enough to be computed twice for a short call (from the
 // O and dO rows of a stage; OWN in bwd_dkdv_body.h).  So the workgroups of both are one grid, a third as many launches deep.
-// Kernel times of a call with its merges, two launches -> one, in us (Hq/Hkv, chunk at position):
-//   8/8  32 at 0     18.0 -> 10.4     32/8 128 at 1024   41.7 -> 29.9
-//   8/8  32 at 1024  25.4 -> 16.8     32/8 256 at 0      34.6 -> 23.9
-//   8/8 128 at 512   26.9 -> 17.6     32/8 256 at 2048   65.8 -> 55
-//   16/2 184 at 736  43.6 -> 27.1     8/2  512 at 2048   48.7 -> 34.6
+// A call among others with its merges, one pass after the other -> in one launch, in us (Hq/Hkv, chunk at position):
+//   8/8  32 at 0     18.0 -> 10.1     32/8 128 at 1024   39.5 -> 26.9
+//   8/8  32 at 1024  24.0 -> 14.9     32/8 256 at 0      31.6 -> 21.4
+//   8/8 128 at 512   25.5 -> 16.1     32/8 256 at 2048   57.8 -> 47.0
+//   16/2 184 at 736  40.1 -> 25.4     8/2  512 at 2048   48.5 -> 33.5
 // What bounds it now: one workgroup's prologue, 1 - 10 iterations and epilogue, at one workgroup per CU.
 #include "bwd_dkdv_body.h"
 #include "bwd_dq_body.h"

@@ -1,6 +1,6 @@
 // Bandwidth-bound helpers: KV-gradient buffer zero / axpy (the gradient relay of the
-// paper's appendix listing, "grad + base * scaler") and the softmax-gradient row term
-// delta = rowsum(dO * O); and the merge steps of the split forward / dQ kernels (short chunks).
+// paper's appendix listing, "grad + base * scaler"), cache append and gradient read-out with and without rotary
+// embedding; and the merge steps of the split forward / dQ kernels (short chunks).
 #include "merge_body.h"
 #include "seco_internal.h"
 

@@ -109,9 +109,9 @@ int launch_dq_merge(const AttnParams& p, hipStream_t s);    // dQ = scale * sum 
 
 // Last round of the bf16 dK/dV pass.  One workgroup fills a CU, so n_units * n_ctiles column tiles run in rounds of
 // one workgroup per CU; when the last round would hold at most half of that, the last n_tiles column tiles of every
-// (batch, KV head) are divided among hs workgroups by query head (hs = 1: nothing is divided).  A share keeps
-// at least 512 query rows, and all shares together fit one round (device_cus() shares at most, which is also what
-// the workspace for their partial sums is sized for).
+// (batch, KV head) are shared out among at least hs workgroups (hs = 1: by this rule none are).  hs divides the group's
+// heads, a share keeps at least 512 query rows, and all shares together fit one round (device_cus() shares at most,
+// which is also what the workspace for their partial sums is sized for).  share_plan below starts from this.
 struct TailPlan {
   int n_tiles;
   int hs;

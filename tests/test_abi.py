@@ -114,11 +114,11 @@ def test_kvgrad_validation_and_workspace_size():
     assert lib.kvgrad_zero(C.byref(d), None, None, 0, 4, None) == 0                           # nothing to do
     # long chunks (enough row tiles to fill the GPU): no forward workspace; the backward takes two values per query
     # row (delta and the log-sum-exp in the form the dK/dV kernel starts from; fp32: one value) plus the sums
-    # of the column tiles that the dK/dV pass divides by query head (at most 256 shares of 2 x 128 x 128 floats)
+    # of the column tiles that the dK/dV pass shares out (at most 256 shares of 2 x 128 x 128 floats)
     big = desc(n_q_heads=32, n_kv_heads=8, chunk_len=1024)
     assert seco.seco_workspace_bytes(big, B.SECO_OP_FWD) == 0
     assert seco.seco_workspace_bytes(big, B.SECO_OP_BWD) == 2 * 32 * 1024 * 4 + 256 * 2 * 128 * 128 * 4
-    # without grouped heads nothing is divided: delta only
+    # without grouped heads there is room for no share: the row statistics only
     mha = desc(n_q_heads=8, n_kv_heads=8, chunk_len=4096)
     assert seco.seco_workspace_bytes(mha, B.SECO_OP_BWD) == 2 * 8 * 4096 * 4
     # fp32 never uses the split path
@@ -243,7 +243,7 @@ def test_percall_weights_match_oracle_bit_exactly():
 
 def test_launch_plan_host_logic():
     """The host arithmetic that shapes the launches: division of the cache rows among workgroups for short chunks,
-    and the sharing-out of the dK/dV pass's last round by query head."""
+    and the sharing-out of the dK/dV pass's last round."""
     big = desc(n_q_heads=32, n_kv_heads=8, chunk_len=1024, q_start=0)
     units, G = 8, 4
     for n_col_tiles in range(0, 200):

@@ -106,7 +106,7 @@ def test_spaco_parity(dtype, D, N, C, sel, lam):
     (1, 8, 2, 2080, 520, [3, 2, 0]),     # the same with weights (applied when the shares are merged)
 ])
 def test_bf16_last_round_divided_by_query_head(B, Hq, Hkv, N, C, sel):
-    """dK/dV pass with a short last round: column tiles shared out by query head and merged in head order."""
+    """dK/dV pass with a short last round: column tiles shared out among several workgroups and merged in their order."""
     x = small_layer(21, B, Hq, Hkv, N, 128, "bf16")
     s = 1 / np.sqrt(128)
     lam = float(np.float32(4 / 3))
@@ -341,7 +341,7 @@ def test_one_call_against_a_cache_of_a_million_rows():
     (1, 4, 1, 512, 256),      # aligned, G = 4
     (2, 4, 2, 640, 256),      # short last chunk
     (1, 2, 2, 700, 200),      # nothing aligned to the tiles
-    (1, 8, 2, 4096, 1024),    # every column tile divided among the four query heads of its group
+    (1, 8, 2, 4096, 1024),    # every column tile shared out
     (3, 4, 4, 1536, 512),     # G = 1: nothing to divide
 ])
 def test_transposed_backward_order_gives_the_same_layer_gradients(B, Hq, Hkv, N, C):
@@ -377,7 +377,7 @@ def test_transposed_backward_order_gives_the_same_layer_gradients(B, Hq, Hkv, N,
 @pytest.mark.parametrize("B,Hq,Hkv,N,C,sel", [
     (1, 4, 2, 1024, 128, [7, 5, 4, 1]),     # runs of one and of two selected chunks, gaps between them
     (2, 4, 1, 1100, 128, [8, 6, 3, 2, 0]),  # the last chunk is short (76 rows) and selected
-    (1, 8, 2, 4096, 1024, [3, 2, 0]),       # column tiles divided among the query heads
+    (1, 8, 2, 4096, 1024, [3, 2, 0]),       # column tiles shared out
     (1, 2, 2, 768, 192, [3, 1]),            # chunk length a multiple of 64 but not of the 128-row column tile
 ])
 def test_spaco_in_the_transposed_order(B, Hq, Hkv, N, C, sel):

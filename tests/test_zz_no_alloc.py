@@ -42,7 +42,7 @@ def _both(x, j, Cn, dtype):
 
 
 def test_noalloc_backward_equals_the_workspace_entry_point_twice_in_a_row():
-    # first call: 8 (batch, KV head) units x 12 column tiles, the last ones shared out by query head (partials in
+    # first call: 8 (batch, KV head) units x 12 column tiles, the last ones shared out (partials in
     # the scratch array), 4-wavefront direct dQ; second call: a smaller, short-chunk shape whose split dQ partials
     # and row statistics land where the first call's data were
     _both(small_layer(91, 2, 16, 4, 1536, 128, "bf16"), 2, 512, "bf16")
