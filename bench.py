@@ -527,6 +527,8 @@ def main():
                          (f"spaco_t{tx}_prefill_kept_outputs_transposed", spaco_layer_transposed),
                          (f"spaco_percall_t{tx}", spaco_percall_layer),
                          (f"spaco_last_call_t{tx}", spaco_last_call)):
+            if fn is spaco_layer_transposed and Lx.C % 64 != 0:      # (the row weights' chunks must be whole 64-row stages)
+                continue
             fn()
             torch.cuda.synchronize()
             best = 1e9
