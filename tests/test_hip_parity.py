@@ -65,6 +65,24 @@ def test_fp32_tile_edges(D, N, C):
           A.spaco_layer(x["q"], x["k"], x["v"], x["do"], C, s, sel, lam), "f32", f"f32 spaco {D,N,C}")
 
 
+@pytest.mark.parametrize("D", [8, 32, 64, 80, 112, 128, 176, 256])
+@pytest.mark.parametrize("rising", [True, False])
+def test_fp32_reference_moves_along_the_cache(D, rising):
+    """Scores that climb (or fall) by up to 70 over the cache: the forward's exponent reference, which follows only when a
+    score lies 2^32 above it, moves several times within a wavefront's blocks and differs between wavefronts.  Scores of
+    70 carry an fp32 rounding of about 70 * 2^-24 * 4 = 1.7e-5, a relative error of as much in every probability.  dQ sums
+    dS K, in which a component shared by all keys cancels but not its rounding: it is held to 70 / (32 s) < 36, by a
+    large component of the queries (the other components of K and dS are of order 1, |dQ| of order 1 to 10: 1.7e-5 * 36 / 10
+    at most; with 99 instead of 12 in K at head_dim 32 dQ was off by 1.06e-4)."""
+    N, C, s = 700, 90, 1 / np.sqrt(D)
+    x = small_layer(12, 1, 2, 1, N, D, "f32")
+    ramp = 70 * np.floor(np.arange(N) / 50)[None, None, :] / ((N - 1) // 50)
+    x["q"][..., 0] = 32.0
+    x["k"][..., 0] = (ramp if rising else 70 - ramp) / (32.0 * s)
+    got = run_layer(x, C, s, "f32")
+    check(got, A.seco_layer(x["q"], x["k"], x["v"], x["do"], C, s), "f32", f"f32 ramp {D,rising}")
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,N,C", [
     (1, 4, 1, 512, 256),     # aligned, G = 4
     (2, 4, 2, 640, 256),     # short last chunk (128 rows)
