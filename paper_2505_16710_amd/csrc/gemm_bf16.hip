@@ -35,15 +35,15 @@ struct GemmArgs {
 
 __device__ __forceinline__ int flip(int row) { return (((row >> 1) & 1) << 2) | ((row >> 2) & 3); }
 
-// Copies of one operand: instruction i of a wavefront brings the staged rows 8 (wave + 4 i) .. + 7.
-template <bool KC, int BO> struct Stage {
-  static constexpr int kCopies = BO / 32;
+// Copies of one operand by W wavefronts: instruction i of a wavefront brings the staged rows 8 (wave + W i) .. + 7.
+template <bool KC, int BO, int W = 4> struct Stage {
+  static constexpr int kCopies = BO / (8 * W);
   uint32_t off[kCopies];      // this lane's source, relative to the step's base
   // o0: first outer index of the tile, n_outer: how many there are (KR: a multiple of 8); rows / chunks past the end repeat the last
   __device__ void init(int o0, int n_outer, int ld, int wave, int lane) {
 #pragma unroll
     for (int i = 0; i < kCopies; ++i) {
-      const int lr = 8 * (wave + 4 * i) + (lane >> 3);
+      const int lr = 8 * (wave + W * i) + (lane >> 3);
       if (KC) {
         off[i] = (uint32_t)min(o0 + lr, n_outer - 1) * (uint32_t)(ld * 2) + (((lane & 7) ^ flip(lr)) << 4);
       } else {
@@ -54,7 +54,7 @@ template <bool KC, int BO> struct Stage {
   }
   __device__ void copy(const char* base, uint32_t lds_wave) const {   // lds_wave: the operand's slot + 8 wave rows
 #pragma unroll
-    for (int i = 0; i < kCopies; ++i) dma16_sbase(base, off[i], lds_wave + i * 32 * kRow);
+    for (int i = 0; i < kCopies; ++i) dma16_sbase(base, off[i], lds_wave + i * 8 * W * kRow);
   }
 };
 
@@ -102,6 +102,32 @@ template <bool KC> struct Frag {
     }
   }
 };
+
+// eight sums to C, from element `at` on
+template <int EPI, typename F4>
+__device__ __forceinline__ void emit(const GemmArgs& g, int64_t at, const F4& lo, const F4& hi) {
+  const float f[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+  bf16x8 out, old, act;
+  if constexpr (EPI == kAdd) old = *reinterpret_cast<const bf16x8*>(g.c + at);
+  if constexpr (EPI == kSiluBwd) old = *reinterpret_cast<const bf16x8*>(g.c2 + at);
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    if constexpr (EPI == kAdd) {
+      out[e] = (__bf16)((float)old[e] + f[e]);
+    } else if constexpr (EPI == kSiluBwd) {
+      const float u = (float)old[e], s = 1.f / (1.f + __expf(-u));
+      out[e] = (__bf16)((float)(__bf16)f[e] * (s * (1.f + u * (1.f - s))));
+    } else {
+      out[e] = (__bf16)f[e];
+      if constexpr (EPI == kSilu) {
+        const float u = (float)out[e];
+        act[e] = (__bf16)(u * (1.f / (1.f + __expf(-u))));
+      }
+    }
+  }
+  *reinterpret_cast<bf16x8*>(g.c + at) = out;
+  if constexpr (EPI == kSilu) *reinterpret_cast<bf16x8*>(g.c2 + at) = act;
+}
 
 // KH groups of 4 wavefronts, each with a ring of kStages slots; group kh takes the steps kh, kh + KH, ...
 template <int BM, int BN, int KH, int kStages, bool AKC, bool BKC, int EPI>
@@ -217,29 +243,88 @@ __global__ __launch_bounds__(256 * KH, 2) void gemm_kernel(GemmArgs g, int total
       lo += *reinterpret_cast<SECO_LDS f32x4*>(src + kRing);
       hi += *reinterpret_cast<SECO_LDS f32x4*>(src + kRing + 16);
     }
-    const float f[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-    const int64_t at = (int64_t)row * g.ldc + col;
-    bf16x8 out, old, act;
-    if constexpr (EPI == kAdd) old = *reinterpret_cast<const bf16x8*>(g.c + at);
-    if constexpr (EPI == kSiluBwd) old = *reinterpret_cast<const bf16x8*>(g.c2 + at);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      if constexpr (EPI == kAdd) {
-        out[e] = (__bf16)((float)old[e] + f[e]);
-      } else if constexpr (EPI == kSiluBwd) {
-        const float u = (float)old[e], s = 1.f / (1.f + __expf(-u));
-        out[e] = (__bf16)((float)(__bf16)f[e] * (s * (1.f + u * (1.f - s))));
-      } else {
-        out[e] = (__bf16)f[e];
-        if constexpr (EPI == kSilu) {
-          const float u = (float)out[e];
-          act[e] = (__bf16)(u * (1.f / (1.f + __expf(-u))));
-        }
-      }
-    }
-    *reinterpret_cast<bf16x8*>(g.c + at) = out;
-    if constexpr (EPI == kSilu) *reinterpret_cast<bf16x8*>(g.c2 + at) = act;
+    emit<EPI>(g, (int64_t)row * g.ldc + col, lo, hi);
   }
+}
+
+// A product with few tiles and, often, a long contraction (the projections back to the residual stream: 512 x 1024 x 4096):
+// tiles of 32 x 64, and every wavefront takes steps of the contraction for the whole tile, w, w + NW, .., on its own, in LDS
+// of its own: no barrier before the sums of the wavefronts meet.  What bounds 64 x 64 tiles there is LDS (2 KiB read per
+// MFMA) on half of the CUs; here an operand is read from LDS once (1.5 KiB per MFMA), twice the CUs work, and the copies of
+// all wavefronts are in flight at once.
+template <int NW, bool AKC, bool BKC, int EPI>
+__global__ __launch_bounds__(64 * NW, 2) void gemm_k_kernel(GemmArgs g, int total) {
+  constexpr int BM = 32, BN = 64, kSlot = (BM + BN) * kRow;
+  extern __shared__ __attribute__((aligned(16))) char smem_raw[];
+  lds_char* smem_all = (lds_char*)smem_raw;
+  const int item = xcd_item(blockIdx.x, total);
+  if (item < 0) return;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  lds_char* smem = smem_all + w * kSlot;
+  const int tn = item / g.tiles_m, tm = item - tn * g.tiles_m;
+  const int m0 = tm * BM, n0 = tn * BN;
+  Stage<AKC, BM, 1> sa;
+  Stage<BKC, BN, 1> sb;
+  sa.init(m0, g.M, g.lda, 0, lane);
+  sb.init(n0, g.N, g.ldb, 0, lane);
+  const int64_t step_a = AKC ? kStep * 2 : (int64_t)kStep * g.lda * 2, step_b = BKC ? kStep * 2 : (int64_t)kStep * g.ldb * 2;
+  const uint32_t lds = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)smem);
+  const char *pa = g.a + w * step_a, *pb = g.b + w * step_b;
+  const int n_steps = g.K / kStep;
+  auto copy = [&]() {
+    sa.copy(pa, lds);
+    sb.copy(pb, lds + BM * kRow);
+    pa += NW * step_a;
+    pb += NW * step_b;
+  };
+  if (w < n_steps) copy();
+  Frag<AKC> fa;
+  Frag<BKC> fb[2];
+  fa.init(0, lane);
+  fb[0].init(0, lane);
+  fb[1].init(1, lane);
+  f32x16 acc[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
+  for (int it = w; it < n_steps; it += NW) {
+    dma_wait_all();
+    bf16x8 x[4], y[2][4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      x[t] = fa.read(smem, t);
+      y[0][t] = fb[0].read(smem + BM * kRow, t);
+      y[1][t] = fb[1].read(smem + BM * kRow, t);
+    }
+    // (all operands are in registers before the next copy overwrites them)
+    asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]), "+v"(y[0][0]), "+v"(y[0][1]), "+v"(y[0][2]),
+                 "+v"(y[0][3]), "+v"(y[1][0]), "+v"(y[1][1]), "+v"(y[1][2]), "+v"(y[1][3]) : : "memory");
+    if (it + NW < n_steps) copy();
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) acc[j] = mfma(x[t], y[j][t], acc[j]);
+  }
+  constexpr int kTurnRow = (BN + 4) * 4;
+  static_assert(BM * kTurnRow <= kSlot, "a wavefront's sums fit its slot");
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+      *reinterpret_cast<SECO_LDS float*>(smem + (8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * kTurnRow + (j * 32 + (lane & 31)) * 4) = acc[j][r];
+  __syncthreads();
+  const int lr = threadIdx.x >> 3, col = n0 + (threadIdx.x & 7) * 8;
+  if (lr >= BM || m0 + lr >= g.M || col >= g.N) return;
+  typedef float f32x4 __attribute__((ext_vector_type(4)));
+  f32x4 lo = {0.f, 0.f, 0.f, 0.f}, hi = lo;
+#pragma unroll
+  for (int v = 0; v < NW; ++v) {
+    lds_char* src = smem_all + v * kSlot + lr * kTurnRow + (threadIdx.x & 7) * 32;
+    lo += *reinterpret_cast<SECO_LDS f32x4*>(src);
+    hi += *reinterpret_cast<SECO_LDS f32x4*>(src + 16);
+  }
+  emit<EPI>(g, (int64_t)(m0 + lr) * g.ldc + col, lo, hi);
 }
 
 template <int BM, int BN, int KH, int ST, bool AKC, bool BKC, int EPI> int launch(GemmArgs g, hipStream_t s) {
@@ -253,8 +338,23 @@ template <int BM, int BN, int KH, int ST, bool AKC, bool BKC, int EPI> int launc
   return launch_status();
 }
 
+template <int NW, bool AKC, bool BKC, int EPI> int launch_k(GemmArgs g, hipStream_t s) {
+  constexpr int smem = NW * 96 * kRow;
+  auto kern = gemm_k_kernel<NW, AKC, BKC, EPI>;
+  static std::atomic<uint64_t> ready{0};
+  if (!allow_lds(ready, reinterpret_cast<const void*>(kern), smem)) return SECO_ERR_LAUNCH;
+  g.tiles_m = (g.M + 31) / 32;
+  const int total = g.tiles_m * ((g.N + 63) / 64);
+  hipLaunchKernelGGL(kern, dim3(xcd_grid(total)), dim3(64 * NW), smem, s, g, total);
+  return launch_status();
+}
+
 // Which tile: measured over 64 .. 2048 rows against matrices of 1024 x 1024 .. 4096 x 1024 (us; K: contraction length).
 // LDS reads bound the small tiles (2 KiB per MFMA at 64 x 64, 1 KiB at 128 x 128), idle CUs the large ones.
+//  - forward and data gradient whose 32 x 64 tiles fit one round: those, the contraction divided among eight wavefronts (512 x
+//    1024 x 4096: 11.3 against 14.5 with 64 x 64 tiles, 512 x 1024 x 1024: 5.2 / 5.8, 320 x 1536 x 1024: 5.1 / 5.8; in two rounds
+//    they lose: 640 x 1024 x 1024 8.2 / 5.8; twelve wavefronts 11.6 and 5.5.  What bounds the long one now is what the L2s
+//    deliver: 196 MB in 8.5 us);
 //  - over 1.25 128 x 128 tiles per CU: those, four wavefronts and two slots, so that two workgroups share a CU
 //    (2048 x 4096 x 1024: 25; 31 with eight wavefronts, 35 with 64 x 64 tiles);
 //  - from 0.55 per CU on: 128 x 128, eight wavefronts in two groups (1024 x 4096 x 1024: 16.5 against 17.3);
@@ -263,6 +363,8 @@ template <int BM, int BN, int KH, int ST, bool AKC, bool BKC, int EPI> int launc
 //    workgroups per CU (512 x 4096 x 1024: 9.9; 14.0 with 128 x 128).
 template <bool AKC, bool BKC, int EPI> int pick(const GemmArgs& g, hipStream_t s) {
   const int64_t m64 = (g.M + 63) / 64, n64 = (g.N + 63) / 64, big = ((m64 + 1) / 2) * ((n64 + 1) / 2), cus = device_cus();
+  if constexpr (AKC)
+    if ((g.M + 31) / 32 * n64 <= cus) return launch_k<8, AKC, BKC, EPI>(g, s);
   if (4 * big > 5 * cus) return launch<128, 128, 1, 2, AKC, BKC, EPI>(g, s);
   if (20 * big >= 11 * cus) return launch<128, 128, 2, 2, AKC, BKC, EPI>(g, s);
   if (m64 * n64 <= cus) return launch<64, 64, 2, 3, AKC, BKC, EPI>(g, s);

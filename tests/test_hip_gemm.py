@@ -17,6 +17,10 @@ STORE, ADD, SILU, SILU_BWD = 0, 1, 2, 3
     (NN, STORE, 1, 8, 64), (NN, STORE, 63, 72, 64), (NN, STORE, 65, 136, 192), (NN, SILU, 129, 200, 320),
     (NT, STORE, 127, 64, 128), (NT, SILU_BWD, 130, 264, 448),
     (TN, STORE, 72, 200, 1), (TN, ADD, 136, 264, 77), (TN, ADD, 64, 64, 63), (TN, STORE, 128, 128, 129),
+    # the contraction divided among the wavefronts of 32 x 64 tiles: fewer steps than wavefronts, one more, all in one round
+    (NN, STORE, 31, 64, 448), (NN, SILU, 33, 72, 576), (NN, STORE, 500, 1024, 4096), (NT, STORE, 32, 8, 512),
+    (NT, SILU_BWD, 65, 128, 640), (NT, STORE, 512, 1024, 1536),
+    (NN, STORE, 640, 1024, 320), (NT, SILU_BWD, 700, 1000, 512),   # 64 x 64 tiles that fit one round, 32 x 64 do not
     (NN, STORE, 300, 4096, 64),            # more 64 x 64 tiles than CUs, two slots
     (NT, STORE, 1500, 1032, 2112),         # 128 x 64 tiles
     (TN, ADD, 2040, 2056, 200),            # 128 x 128 tiles, two groups, a remainder of the contraction
