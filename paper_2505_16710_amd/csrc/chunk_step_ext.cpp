@@ -171,7 +171,20 @@ struct Step {
     for (int64_t* x : {d.q_stride, d.o_stride, d.kv_stride, d.g_stride}) std::copy(st, st + 3, x);
     check(lib.rope_rotate(&d, (int32_t)Hq, qkv, qkv, q_start, (float)rope_base, inverse, s), "rope_rotate");
   }
+  // queries turned in place, keys (turned) and values to the cache; or, on the way back, the queries' gradient turned back and
+  // the key and value gradients from gK / gV: one launch where the library's call takes the sizes
+  bool rope_qkv(Layer& l, void* qkv, int64_t C, int64_t q_start, bool inverse) {
+    if (rope_base == 0.0) return false;
+    const Tensor &k = inverse ? l.gk : l.k, &v = inverse ? l.gv : l.v;
+    const int64_t st[3] = {k.stride(0), k.stride(1), k.stride(2)};
+    const int rc = lib.dec_rope_qkv(dtype, inverse, qkv, ptr(k), ptr(v), st, B, Hq, Hkv, C, D, q_start, (float)rope_base, s);
+    if (rc == SECO_ERR_TOO_LARGE) return false;
+    check(rc, "dec_rope_qkv");
+    return true;
+  }
   void append(Layer& l, void* qkv, int64_t C, int64_t q_start) {
+    if (rope_qkv(l, qkv, C, q_start, false)) return;
+    rotate(qkv, C, q_start, false);
     seco_desc d = desc(C, q_start, l);
     std::copy(d.q_stride, d.q_stride + 3, d.o_stride);
     std::copy(d.q_stride, d.q_stride + 3, d.g_stride);
@@ -184,6 +197,8 @@ struct Step {
       check(lib.kv_append(&d, k, v, ptr(l.k), ptr(l.v), s), "kv_append");
   }
   void readout(Layer& l, void* d_qkv, int64_t C, int64_t q_start) {
+    if (rope_qkv(l, d_qkv, C, q_start, true)) return;
+    rotate(d_qkv, C, q_start, true);
     seco_desc d = desc(C, q_start, l);
     std::copy(d.q_stride, d.q_stride + 3, d.o_stride);
     std::copy(d.q_stride, d.q_stride + 3, d.kv_stride);
@@ -199,6 +214,7 @@ struct Step {
   // deterministic, so the values are identical and the cache rows already hold this chunk's K/V.)
   void attention(Layer& l, Saved& sv, int64_t C, int64_t q_start, Keep keep, Arena& mem) {
     if (keep == kReuse) {
+      rotate(sv.qkv, C, q_start, false);
       // the span of stage 1 that holds this chunk's rows (the chunk itself, or a longer span to cut from)
       auto it = l.kept.upper_bound(q_start);
       if (it == l.kept.begin()) raise(PyExc_RuntimeError, "no kept attention output");
@@ -298,7 +314,6 @@ struct Step {
       norm(x, have_y ? y : nullptr, l.norm1, sv.x1, sv.h1, sv.r1);
       sv.qkv = rows(W);
       mm(sv.qkv, sv.h1, l.wqkv, R);
-      rotate(sv.qkv, C, q_start, false);
       attention(l, sv, C, q_start, keep, mem);
       mm(y, sv.o, l.wo, R);
       sv.x2 = saved ? rows(dm) : x;
@@ -368,7 +383,6 @@ struct Step {
       mm_bwd(d_o, dx, l.wo, R);
       attention_bwd(l, sv, d_o, d_qkv, C, q_start, w, wq.empty() ? none : wq[i], wlen);
       readout(l, d_qkv, C, q_start);
-      rotate(d_qkv, C, q_start, true);
       add(l.wqkv, sv.h1, d_qkv, R);
       mm_bwd(dh, d_qkv, l.wqkv, R);
       norm_bwd(sv.x1, l.norm1, sv.r1, l.part1, false);

@@ -22,6 +22,12 @@ int dec_cross_entropy(int dtype, void* logits, const int64_t* target, float* los
 // grad[token[r]] += d_x[r] for every row r; the rows of one token are added in ascending order by one workgroup
 int dec_embedding_bwd(int dtype, const void* d_x, const int64_t* token, void* grad, int64_t rows, int64_t d, int64_t v,
                       void* stream);
+// A layer's joint projection qkv [B, C, (Hq + 2 Hkv) D] and rows row0 .. row0 + C of its cache (k, v: the type of qkv) or, with
+// `inverse`, of its fp32 gradient buffers, both [B, Hkv, *, D] with kv_stride: queries rotated (back) in place, keys rotated and
+// values copied to the cache, or gK (rotated back) and gV to the key and value columns; what rope_rotate with
+// kv_append_rope, or kvgrad_readout_rope with rope_rotate, compute, bit for bit, in one launch.  D as there: bf16 128, fp32 a multiple of 8 up to 256
+int dec_rope_qkv(int dtype, int inverse, void* qkv, void* k, void* v, const int64_t* kv_stride, int64_t B, int64_t Hq, int64_t Hkv,
+                 int64_t C, int64_t D, int64_t row0, float base, void* stream);
 
 // bf16 matrix products with fp32 accumulation, row-major with leading dimensions in elements (gemm_bf16.hip):
 //   NN: C[M,N] = A[M,K] B[K,N]     NT: C[M,N] = A[M,K] B[N,K]^T     TN: C[M,N] = A[K,M]^T B[K,N]

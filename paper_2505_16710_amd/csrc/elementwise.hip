@@ -2,6 +2,7 @@
 // paper's appendix listing, "grad + base * scaler"), cache append and gradient read-out with and without rotary
 // embedding; and the merge steps of the split forward / dQ kernels (short chunks).
 #include "merge_body.h"
+#include "decoder.h"
 #include "seco_internal.h"
 
 namespace seco {
@@ -369,13 +370,88 @@ __global__ __launch_bounds__(256) void rope_rows_kernel(TOut* out, const TIn* in
   }
 }
 
+// What a decoder layer does between its joint projection and the attention, in one launch: the query heads of qkv [B, C, (Hq + 2
+// Hkv) D] rotated in place, the key heads rotated and the value heads copied to rows row0 .. of the cache; or, on the way
+// back (INV), the query gradients turned back in place and the rows of gK (turned back) and gV to the key and value
+// columns.  blockIdx.y: head groups of the queries, then of the keys, then of the values.  (As two launches, queries and
+// cache, 512 rows of 8/2 heads take 4 us each, of which 3 are the launch and the first loads.)
+// One head group of one row: this thread's four pairs of kRopeHeads heads.
+template <typename TIn, typename TOut>
+__device__ __forceinline__ void rope_group(TOut* dst, const TIn* src, int64_t os1, int64_t is1, int heads, int D, int grp, double theta,
+                                           const RopePowers& powers, double sign, bool plain) {
+  Quad<TIn> x[kRopeHeads][2];
+#pragma unroll
+  for (int k = 0; k < kRopeHeads; ++k)
+    if (k < heads) {
+      x[k][0] = *reinterpret_cast<const Quad<TIn>*>(src + k * is1);
+      x[k][1] = *reinterpret_cast<const Quad<TIn>*>(src + k * is1 + D / 2);
+    }
+  double sn[4], cs[4];
+  if (!plain) {
+#pragma unroll
+    for (int k = 0; k < 6; ++k) theta *= grp >> k & 1 ? powers.pow[k] : 1.0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      sincos_f64(theta, sn[j], cs[j]);
+      sn[j] *= sign;
+      theta *= powers.step;
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < kRopeHeads; ++k)
+    if (k < heads) {
+      float lo[4], hi[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        lo[j] = x[k][0].get(j);
+        hi[j] = x[k][1].get(j);
+        if (!plain) {
+          const double a = (double)lo[j], c = (double)hi[j];
+          lo[j] = (float)(a * cs[j] - c * sn[j]);
+          hi[j] = (float)(c * cs[j] + a * sn[j]);
+          // (rounded to fp32 and then to the storage type, as rope_rows_kernel does: the compiler would take the two steps
+          // as one, and two of 524288 elements differ)
+          asm("" : "+v"(lo[j]), "+v"(hi[j]));
+        }
+      }
+      *reinterpret_cast<Quad<TOut>*>(dst + k * os1) = Quad<TOut>::of(lo);
+      *reinterpret_cast<Quad<TOut>*>(dst + k * os1 + D / 2) = Quad<TOut>::of(hi);
+    }
+}
+template <typename T, typename TG, bool INV>
+__global__ __launch_bounds__(256) void rope_qkv_kernel(T* qkv, TG* k, TG* v, int Hq, int Hkv, int C, int D, int64_t ks0, int64_t ks1,
+                                                       int64_t ks2, int64_t row0, RopePowers powers, int n_q, int n_kv) {
+  const int q4 = D / 8, rpb = 256 / q4, lr = threadIdx.x / q4, grp = threadIdx.x - lr * q4, row = blockIdx.x * rpb + lr;
+  if (lr >= rpb || row >= C) return;
+  const bool is_q = (int)blockIdx.y < n_q, plain = (int)blockIdx.y >= n_q + n_kv;
+  const int y = is_q ? blockIdx.y : (int)blockIdx.y - n_q - (plain ? n_kv : 0);
+  const int H = is_q ? Hq : Hkv, groups = (H + kRopeHeads - 1) / kRopeHeads, b = y / groups, h0 = (y - b * groups) * kRopeHeads;
+  const int heads = min(kRopeHeads, H - h0);
+  const double theta = (double)(row0 + row), sign = INV ? -1.0 : 1.0;
+  T* here = qkv + ((int64_t)b * C + row) * ((int64_t)(Hq + 2 * Hkv) * D) + (int64_t)(h0 + (is_q ? 0 : plain ? Hq + Hkv : Hq)) * D + grp * 4;
+  if (is_q) {
+    rope_group(here, (const T*)here, D, D, heads, D, grp, theta, powers, sign, false);
+  } else {
+    TG* there = (plain ? v : k) + b * ks0 + h0 * ks1 + (row0 + row) * ks2 + grp * 4;
+    if constexpr (INV)
+      rope_group(here, (const TG*)there, D, ks1, heads, D, grp, theta, powers, sign, plain);
+    else
+      rope_group(there, (const T*)here, ks1, D, heads, D, grp, theta, powers, sign, plain);
+  }
+}
+
+RopePowers rope_powers(int D, float base) {
+  RopePowers powers;
+  powers.step = exp2(-2.0 / D * log2((double)base));
+  for (int k = 0; k < 6; ++k) powers.pow[k] = exp2(-8.0 * (1 << k) / D * log2((double)base));
+  return powers;
+}
+
 int launch_rope_rows(void* out, const void* in, void* plain_out, const void* plain_in, int in_kind, int out_kind, int B,
                      int H, int C, int D, const int64_t out_s[3], const int64_t in_s[3], int64_t out_r0, int64_t in_r0,
                      int64_t pos0, float base, bool inverse, float scale, hipStream_t s) {
   if (!out && !plain_out) return SECO_OK;
-  RopePowers powers;
-  powers.step = exp2(-2.0 / D * log2((double)base));
-  for (int k = 0; k < 6; ++k) powers.pow[k] = exp2(-8.0 * (1 << k) / D * log2((double)base));
+  const RopePowers powers = rope_powers(D, base);
   const float sign = inverse ? -1.f : 1.f;
   {
     ProfScope prof(kKernelKvgrad, s);
@@ -395,6 +471,44 @@ int launch_rope_rows(void* out, const void* in, void* plain_out, const void* pla
   }
   return launch_status();
 }
+
+}  // namespace seco
+
+extern "C" int dec_rope_qkv(int dtype, int inverse, void* qkv, void* k, void* v, const int64_t* kv_stride, int64_t B, int64_t Hq,
+                            int64_t Hkv, int64_t C, int64_t D, int64_t row0, float base, void* stream) {
+  using namespace seco;
+  if (!qkv || !k || !v || !kv_stride) return SECO_ERR_NULL;
+  if (dtype != SECO_F32 && dtype != SECO_BF16) return SECO_ERR_DTYPE;
+  const int64_t n_q = B * ((Hq + kRopeHeads - 1) / kRopeHeads), n_kv = B * ((Hkv + kRopeHeads - 1) / kRopeHeads);
+  if (B < 1 || Hq < 1 || Hkv < 1 || C < 1 || D < 8 || row0 < 0) return SECO_ERR_SHAPE;
+  if (dtype == SECO_BF16 ? D != 128 : D % 8 != 0 || D > 256) return SECO_ERR_HEAD_DIM;
+  if (!(base > 1.f) || !std::isfinite(base)) return SECO_ERR_RANGE;
+  if (n_q + 2 * n_kv > 65535 || C > (int64_t)1 << 30 || B > 65535) return SECO_ERR_TOO_LARGE;
+  const int64_t per = dtype == SECO_BF16 && !inverse ? 8 : 4;       // elements per 16 bytes of a cache or gradient row
+  for (int i = 0; i < 3; ++i)
+    if (kv_stride[i] < 0 || kv_stride[i] % per != 0) return SECO_ERR_ALIGN;
+  if (((uintptr_t)qkv | (uintptr_t)k | (uintptr_t)v) & 15u) return SECO_ERR_ALIGN;
+  const int rpb = 256 / (int)(D / 8);
+  const dim3 grid((unsigned)((C + rpb - 1) / rpb), (unsigned)(n_q + 2 * n_kv));
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  const RopePowers powers = rope_powers((int)D, base);
+#define SECO_QKV_LAUNCH(T, TG, INV)                                                                                              \
+  hipLaunchKernelGGL((rope_qkv_kernel<T, TG, INV>), grid, dim3(256), 0, s, static_cast<T*>(qkv), static_cast<TG*>(k),              \
+                     static_cast<TG*>(v), (int)Hq, (int)Hkv, (int)C, (int)D, kv_stride[0], kv_stride[1], kv_stride[2], row0, powers, \
+                     (int)n_q, (int)n_kv)
+  ProfScope prof(kKernelKvgrad, s);
+  if (dtype == SECO_BF16) {
+    if (inverse) SECO_QKV_LAUNCH(__bf16, float, true);
+    else SECO_QKV_LAUNCH(__bf16, __bf16, false);
+  } else {
+    if (inverse) SECO_QKV_LAUNCH(float, float, true);
+    else SECO_QKV_LAUNCH(float, float, false);
+  }
+#undef SECO_QKV_LAUNCH
+  return launch_status();
+}
+
+namespace seco {
 
 #define SECO_MERGE_LAUNCH(kernel)                                                                             \
   const int64_t R = (int64_t)p.B * p.Hq * p.C;                                                                \

@@ -204,3 +204,41 @@ def test_silu_lengths(dtype, n):
     ref = f * torch.sigmoid(f)
     eps = 16 * U + (2.0 ** -8 if dtype == BF16 else 0)
     assert ((out[:n].float() - ref).abs() <= eps * ref.abs()).all()
+
+
+@pytest.mark.parametrize("dtype,B,Hq,Hkv,n,D,row0", [
+    (BF16, 1, 8, 2, 512, 128, 1024), (BF16, 2, 3, 1, 17, 128, 0), (BF16, 1, 9, 9, 1, 128, 5),
+    (F32, 2, 3, 1, 17, 128, 0), (F32, 2, 5, 5, 33, 80, 7), (F32, 1, 4, 4, 1, 8, 3), (F32, 1, 6, 3, 40, 256, 100),
+])
+def test_rotated_projection_in_one_launch(dtype, B, Hq, Hkv, n, D, row0):
+    """dec_rope_qkv against the public calls it stands for: the same bits, and nothing else of the cache is written."""
+    base, N, dt = 500000.0, row0 + n + 5, torch.bfloat16 if dtype == BF16 else torch.float32
+    gen = torch.Generator(device=DEV).manual_seed(n + D)
+    qkv = torch.randn(B, n, Hq + 2 * Hkv, D, generator=gen, device=DEV).to(dt)
+    k, v = (torch.randn(B, Hkv, N, D, generator=gen, device=DEV).to(dt) for _ in range(2))
+    gk, gv = (torch.randn(B, Hkv, N, D, generator=gen, device=DEV) for _ in range(2))
+
+    def parts(x):
+        x = x.transpose(1, 2)
+        return x[:, :Hq], x[:, Hq:Hq + Hkv], x[:, Hq + Hkv:]
+
+    def call(inverse, t, kk, vv):
+        fn = seco.load_library().dec_rope_qkv
+        st = (C.c_int64 * 3)(*kk.stride()[:3])
+        rc = fn(dtype, inverse, C.c_void_p(t.data_ptr()), C.c_void_p(kk.data_ptr()), C.c_void_p(vv.data_ptr()), st,
+                *(C.c_int64(x) for x in (B, Hq, Hkv, n, D, row0)), C.c_float(base), C.c_void_p(torch.cuda.current_stream().cuda_stream))
+        assert rc == 0
+        torch.cuda.synchronize()
+    x, kk, vv = qkv.clone(), k.clone(), v.clone()
+    call(0, x, kk, vv)
+    q, kn, vn = parts(qkv)
+    want_k, want_v = k.clone(), v.clone()
+    seco.kv_append(kn.contiguous(), vn.contiguous(), want_k, want_v, row0, rope_base=base)
+    assert torch.equal(kk, want_k) and torch.equal(vv, want_v)
+    assert torch.equal(parts(x)[0], seco.rope_rotate(q.contiguous(), row0, base))
+    assert torch.equal(x[:, :, Hq:], qkv[:, :, Hq:])
+    x, kk, vv = qkv.clone(), gk.clone(), gv.clone()
+    call(1, x, kk, vv)
+    dk, dv = seco.kvgrad_readout(gk, gv, row0, n, dt, rope_base=base)
+    assert torch.equal(parts(x)[0], seco.rope_rotate(q.contiguous(), row0, base, inverse=True))
+    assert torch.equal(parts(x)[1], dk) and torch.equal(parts(x)[2], dv) and torch.equal(kk, gk) and torch.equal(vv, gv)
