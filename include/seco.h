@@ -92,9 +92,11 @@ typedef struct seco_desc {
  * lse      out  fp32 [B, Hq, C] contiguous (no strides are taken for it: a sliced view is not accepted), overwritten
  * ws       optional workspace, 256-byte aligned.  seco_workspace_bytes(desc, SECO_OP_FWD) is non-zero only for
  *          bf16 calls with so few query rows that the row tiles cannot fill the GPU (short chunks, as in the
- *          chunk-size study of Sec. 6.3); given at least that many bytes, the visible cache rows are divided
- *          among several workgroups whose partial results are merged in a fixed order.  With ws NULL or smaller
- *          the call computes the same O and LSE (to rounding) without the division, only slower.
+ *          chunk-size study of Sec. 6.3), or with more of them than fill it once but not twice (at most 32.5 MiB
+ *          then); given at least that many bytes, the visible cache rows - there only those of the row tiles beyond
+ *          the first round - are divided among several workgroups whose partial results are merged in a fixed order.
+ *          With ws NULL or smaller the call computes the same O and LSE (to rounding) without the division, only
+ *          slower.
  */
 int seco_chunk_attn_fwd(const seco_desc* desc, const void* q, const void* k_cache, const void* v_cache,
                         void* o, float* lse, void* ws, size_t ws_bytes, void* hip_stream);
@@ -110,7 +112,7 @@ int seco_chunk_attn_fwd(const seco_desc* desc, const void* q, const void* k_cach
  * same desc; d_o has o's layout.
  * ws: seco_workspace_bytes(desc, SECO_OP_BWD) bytes, 256-byte aligned: bf16, two fp32 values per query row (delta and
  *     the log-sum-exp in the form the dK/dV kernel consumes; fp32: one, which its kernels leave unused), plus one region shared by the
- *     partial dQ of the short-chunk path described at seco_chunk_attn_fwd and the sums of the cache-row tiles that
+ *     partial dQ of the divided row tiles described at seco_chunk_attn_fwd and the sums of the cache-row tiles that
  *     the dK/dV pass shares out among several workgroups when its workgroups would leave compute units idle (bf16;
  *     32 MiB with grouped heads, without them only what the partial dQ takes; merged in a fixed order, so gk/gv
  *     stay bit-reproducible).  A larger workspace changes nothing: the results are the same bit for bit.

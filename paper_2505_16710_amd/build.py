@@ -24,6 +24,7 @@ SOURCES = [
     "fwd_bf16.hip",
     "fwd4_bf16.hip",
     "fwd4_split_bf16.hip",
+    "fwd8_shares_bf16.hip",
     "fwd_small_bf16.hip",
     "bwd_dq_bf16.hip",
     "bwd_dkdv_bf16.hip",
@@ -41,7 +42,8 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-I", INCLUDE, "
 # tried on every matrix-core kernel): keeping memory (LDS) instructions in clauses is 3 % faster than the default
 # on the 4-wavefront forward and at least as good on the dK/dV kernel; the dQ kernels and the 8-wavefront forward are
 # 3 % faster with the iterative ILP scheduler.
-SCHED = {"bwd_dq_bf16.hip": "iterative-ilp", "fwd_bf16.hip": "iterative-ilp", "fwd4_split_bf16.hip": "iterative-ilp"}
+SCHED = {"bwd_dq_bf16.hip": "iterative-ilp", "fwd_bf16.hip": "iterative-ilp", "fwd4_split_bf16.hip": "iterative-ilp",
+         "fwd8_shares_bf16.hip": "iterative-ilp"}
 SCHED_DEFAULT = "max-memory-clause"
 # the 4-wavefront forward, whose source interleaves two instruction streams by hand, is 2 % faster when the
 # scheduler does not cluster memory operations

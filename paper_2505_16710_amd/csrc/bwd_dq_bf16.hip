@@ -4,15 +4,15 @@
 namespace seco {
 namespace {
 
-template <int KH, bool SPLIT, bool SPARSE>
+template <int KH, int SPLIT, bool SPARSE>
 __global__ __launch_bounds__(256 * KH, 2) void dq_bf16_kernel(AttnParams p, SegTable seg, int n_mtiles, int total_items) {
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];
-  const int item = xcd_item(blockIdx.x, total_items);
+  const int item = SPLIT == kShares ? shares_item(blockIdx.x, p.B * p.Hkv * p.rows_whole, total_items) : xcd_item(blockIdx.x, total_items);
   if (item < 0) return;
   dq_bf16_body<KH, SPLIT, SPARSE>(p, seg, n_mtiles, item, (lds_char*)smem_raw);
 }
 
-template <int KH, bool SPLIT, bool SPARSE>
+template <int KH, int SPLIT, bool SPARSE>
 int launch_kh(const AttnParams& p, const SegTable& seg, int n_mtiles, int total, hipStream_t s) {
   constexpr int smem = 4 * BNW * KH * kRowBytes;
   auto kern = dq_bf16_kernel<KH, SPLIT, SPARSE>;
@@ -20,9 +20,28 @@ int launch_kh(const AttnParams& p, const SegTable& seg, int n_mtiles, int total,
   if (!allow_lds(ready, reinterpret_cast<const void*>(kern), smem)) return SECO_ERR_LAUNCH;
   {
     ProfScope prof(kKernelDq, s);
-    hipLaunchKernelGGL(kern, dim3(xcd_grid(total)), dim3(256 * KH), smem, s, p, seg, n_mtiles, total);
+    const int first = SPLIT == kShares ? p.B * p.Hkv * p.rows_whole : 0;
+    hipLaunchKernelGGL(kern, dim3(xcd_grid(first) + xcd_grid(total - first)), dim3(256 * KH), smem, s, p, seg, n_mtiles, total);
   }
   return launch_status();
+}
+
+// Row tiles that were divided (kShares): dQ = scale * (sum of the shares, in order).  A thread: four elements of a row.
+__global__ __launch_bounds__(256) void dq_shares_merge_kernel(AttnParams p, int n_cut) {
+  typedef float f32x4 __attribute__((ext_vector_type(4)));
+  const int tile = blockIdx.x >> 4, unit = tile / n_cut, pos = tile - unit * n_cut, lr = (blockIdx.x & 15) * 8 + (threadIdx.x >> 5);
+  const int v = (n_cut - 1 - pos) * BM + lr, hg = v / p.Cpad, row = v - hg * p.Cpad, d = (threadIdx.x & 31) * 4;
+  if (hg >= p.G || row >= p.C) return;
+  const float* src = p.part + ((int64_t)tile * p.n_splits * BM + lr) * kHeadDim + d;
+  f32x4 x[kMaxRowShares], sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int k = 0; k < kMaxRowShares; ++k) x[k] = *reinterpret_cast<const f32x4*>(src + (int64_t)min(k, p.n_splits - 1) * BM * kHeadDim);
+#pragma unroll
+  for (int k = 0; k < kMaxRowShares; ++k)
+    if (k < p.n_splits) sum += x[k];
+  const int kvh = unit % p.Hkv, b = unit / p.Hkv;
+  const bf16x4 out = {(__bf16)(sum[0] * p.scale), (__bf16)(sum[1] * p.scale), (__bf16)(sum[2] * p.scale), (__bf16)(sum[3] * p.scale)};
+  *reinterpret_cast<bf16x4*>(static_cast<__bf16*>(p.d_q) + b * p.qs[0] + (int64_t)(kvh * p.G + hg) * p.qs[1] + row * p.qs[2] + d) = out;
 }
 
 }  // namespace
@@ -43,15 +62,31 @@ int launch_dq_bf16_now(const AttnParams& p, const SegTable* runs, hipStream_t s)
   if (p.n_splits > 1) {
     const SplitPlan plan = split_plan(p.B, p.Hkv, p.G, p.C);
     const int total = plan.items * p.n_splits;
-    int rc = runs ? launch_kh<2, true, true>(p, seg, plan.n_mtiles, total, s)
-                  : launch_kh<2, true, false>(p, seg, plan.n_mtiles, total, s);
+    int rc = runs ? launch_kh<2, kDivided, true>(p, seg, plan.n_mtiles, total, s)
+                  : launch_kh<2, kDivided, false>(p, seg, plan.n_mtiles, total, s);
     return rc ? rc : launch_dq_merge(p, s);
   }
   const int n_mtiles = (p.C + BM - 1) / BM;
   const int total = p.B * p.Hq * n_mtiles;
+  if (!runs) {
+    const SplitPlan plan = split_plan(p.B, p.Hkv, p.G, p.C);
+    const RowShares rs = row_shares(p.B * p.Hkv, plan.n_mtiles, total, p.q_start, p.C, p.tail_bytes / (BM * kHeadDim * sizeof(float)), 7.5f, 2.7f);
+    if (rs.shares > 1) {
+      AttnParams ps = p;
+      ps.rows_whole = rs.whole;
+      ps.n_splits = rs.shares;
+      ps.part = p.tail_part;
+      const int n_cut = plan.n_mtiles - rs.whole;
+      const int rc = launch_kh<2, kShares, false>(ps, seg, plan.n_mtiles, p.B * p.Hkv * (rs.whole + n_cut * rs.shares), s);
+      if (rc) return rc;
+      ProfScope prof(kKernelMerge, s);
+      hipLaunchKernelGGL(dq_shares_merge_kernel, dim3(p.B * p.Hkv * n_cut * 16), dim3(256), 0, s, ps, n_cut);
+      return launch_status();
+    }
+  }
   if (total < 2 * device_cus())
-    return runs ? launch_kh<2, false, true>(p, seg, n_mtiles, total, s) : launch_kh<2, false, false>(p, seg, n_mtiles, total, s);
-  return runs ? launch_kh<1, false, true>(p, seg, n_mtiles, total, s) : launch_kh<1, false, false>(p, seg, n_mtiles, total, s);
+    return runs ? launch_kh<2, kWholeTiles, true>(p, seg, n_mtiles, total, s) : launch_kh<2, kWholeTiles, false>(p, seg, n_mtiles, total, s);
+  return runs ? launch_kh<1, kWholeTiles, true>(p, seg, n_mtiles, total, s) : launch_kh<1, kWholeTiles, false>(p, seg, n_mtiles, total, s);
 }
 
 }  // namespace seco

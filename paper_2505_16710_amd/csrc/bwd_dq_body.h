@@ -17,9 +17,12 @@
 // tile.  With every chunk sampled with probability pi and weighted 1 / pi this is an unbiased estimate of dQ
 // whose cost does not grow with the number of unvisited rows.
 //
-// Short chunks (SPLIT = true): as in the forward, the rows of the G heads of a KV head are packed into one row
+// Short chunks (SPLIT = kDivided): as in the forward, the rows of the G heads of a KV head are packed into one row
 // space and the visible cache rows of a row tile are divided among n_splits workgroups; each writes its partial
 // dQ (fp32, unscaled) to the workspace and dq_merge_kernel adds the partials in split order.
+//
+// Between one and two rounds of workgroups (SPLIT = kShares): packed row tiles too, but only those beyond the first round
+// are divided (row_shares in seco_internal.h); the others are written as they are.
 #pragma once
 #include "mfma_tiles.h"
 #include "seco_internal.h"
@@ -33,7 +36,7 @@ constexpr int BNW = 64;   // cache rows per wavefront and tile
 // seg (SPARSE only): runs of cache rows in ascending order, each with a positive weight
 // smem: 4 * kTileBytes, [buf][K|V]
 // FUSED: inside the kernel that holds dK/dV too, where scalar registers are short (opaque)
-template <int KH, bool SPLIT, bool SPARSE, bool FUSED = false>
+template <int KH, int SPLIT, bool SPARSE, bool FUSED = false>
 __device__ __forceinline__ void dq_bf16_body(const AttnParams& p, const SegTable& seg, int n_mtiles, int item, lds_char* smem) {
   static_assert(!SPLIT || KH == 2, "the split variant uses the 8-wavefront shape");
   constexpr int BN = BNW * KH;
@@ -44,11 +47,29 @@ __device__ __forceinline__ void dq_bf16_body(const AttnParams& p, const SegTable
   const int l32 = lane & 31, g = lane >> 5;
   const int rb = wave & 3, kh = (KH == 1 && !SPARSE) ? 0 : wave >> 2;
   int b, kvh, h, mt, m0, sp = 0;              // m0: first chunk-local row of this wavefront
+  int n_sp = 1, slot = 0;                     // shares of this row tile; kShares: where this one's sums go
   if constexpr (SPLIT) {
-    sp = item % p.n_splits;
-    int rest = item / p.n_splits;
-    mt = n_mtiles - 1 - rest % n_mtiles;
-    rest /= n_mtiles;
+    int rest;
+    if constexpr (SPLIT == kDivided) {
+      n_sp = p.n_splits;
+      sp = item % n_sp;
+      rest = item / n_sp;
+      mt = n_mtiles - 1 - rest % n_mtiles;
+      rest /= n_mtiles;
+    } else {
+      const int n_cut = n_mtiles - p.rows_whole, n_first = p.B * p.Hkv * p.rows_whole;   // (the whole tiles come first)
+      if (item < n_first) {
+        rest = item / p.rows_whole;
+        mt = n_mtiles - 1 - (item - rest * p.rows_whole);
+      } else {
+        n_sp = p.n_splits;
+        slot = item - n_first;
+        rest = slot / (n_cut * n_sp);
+        const int e = slot - rest * (n_cut * n_sp);
+        sp = e % n_sp;
+        mt = n_cut - 1 - e / n_sp;
+      }
+    }
     kvh = rest % p.Hkv;
     b = rest / p.Hkv;
     const int v0 = mt * BM + rb * 32;          // packed row: head v0 / Cpad of the group, row v0 % Cpad
@@ -121,9 +142,13 @@ __device__ __forceinline__ void dq_bf16_body(const AttnParams& p, const SegTable
   const int wave_kv_end = m0 < p.C ? p.q_start + min(m0 + 32, p.C) : 0;
   int n_begin = 0, n_end = n_tiles;            // tiles of this workgroup
   if constexpr (SPLIT) {
-    const int per = (n_tiles + p.n_splits - 1) / p.n_splits;
+    const int per = (n_tiles + n_sp - 1) / n_sp;
     n_begin = sp * per;
     n_end = min(n_tiles, n_begin + per);       // may be empty: the partial written below is then all zero
+    if constexpr (SPLIT == kShares) {          // (never empty: there are at least as many tiles as shares)
+      n_begin = sp * n_tiles / n_sp;
+      n_end = (sp + 1) * n_tiles / n_sp;
+    }
   }
 
   // asynchronous global -> LDS copy of one K and one V tile: each wavefront copies 4 groups of 4 rows of each.
@@ -261,7 +286,13 @@ __device__ __forceinline__ void dq_bf16_body(const AttnParams& p, const SegTable
       }
   }
 
-  if constexpr (SPLIT) {
+  if constexpr (SPLIT == kShares) {
+    if (n_sp > 1) {                            // all 32 rows: the merge takes those that exist
+      store_part32(dq, p.part + ((int64_t)slot * BM + rb * 32) * kHeadDim, 32, smem + rb * (17 * 1024));
+      return;
+    }
+  }
+  if constexpr (SPLIT == kDivided) {
     float* po = p.part + ((int64_t)sp * p.B * p.Hq * p.C + ((int64_t)b * p.Hq + h) * p.C + m0) * kHeadDim;
     store_part32(dq, po, p.C - m0, smem + rb * (17 * 1024));
     return;

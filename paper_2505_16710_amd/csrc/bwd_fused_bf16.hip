@@ -39,7 +39,7 @@ __global__ __launch_bounds__(512, 2) void bwd_fused_bf16_kernel(AttnParams p, Se
     else
       dkdv_bf16_body<kNcb, SECO_DKDV_RB, false, 1, true>(p, seg, ts, none, item, smem);
   } else {
-    dq_bf16_body<2, SPLIT, false, true>(p, seg, n_mtiles, item, smem);
+    dq_bf16_body<2, SPLIT ? kDivided : kWholeTiles, false, true>(p, seg, n_mtiles, item, smem);
   }
 }
 

@@ -4,6 +4,6 @@
 
 namespace seco {
 
-int launch_fwd8_split_bf16(const AttnParams& p, int n_mtiles, int total, hipStream_t s) { return launch_fwd8<true>(p, n_mtiles, total, s); }
+int launch_fwd8_split_bf16(const AttnParams& p, int n_mtiles, int total, hipStream_t s) { return launch_fwd8<kDivided>(p, n_mtiles, total, s); }
 
 }  // namespace seco

@@ -14,7 +14,7 @@
 //       SIMD, which is what calls with few row tiles need (a 1024-row chunk of a 32-head layer has only 256
 //       row tiles for 256 CUs).
 //
-// Short chunks (SPLIT = true).  With chunks of 32 .. 512 rows (the sizes of the paper's chunk-size study,
+// Short chunks (SPLIT = kDivided).  With chunks of 32 .. 512 rows (the sizes of the paper's chunk-size study,
 // Sec. 6.3) a call has far fewer row tiles than the GPU has CUs and every tile would stream the whole cache
 // alone.  The split variant therefore (a) packs the rows of the G query heads that share a KV head into one row
 // space of G * roundup(C, 32) rows, so that a workgroup's K/V tiles serve several heads, and (b) divides the
@@ -22,6 +22,9 @@
 // its reference maximum and sum (fp32) to the workspace, and fwd_merge_kernel combines the partials in split order.
 // (With the 4-wavefront kernel here twice as many partials were written and merged: 32 rows x 32 heads against 16K cache
 // rows 32.1 us, now 24.2; 256 rows against 2304 29.1, now 24.6.)
+//
+// Between one and two rounds of workgroups (SPLIT = kShares): packed row tiles too, but only those beyond the first round are
+// divided (row_shares in seco_internal.h); the others are written as they are.
 //
 // The score tile is computed transposed, S^T = K Q^T, so that a lane owns one query row
 // (C layout: lane = column): row max / row sum are in-lane reductions plus one exchange with
@@ -40,7 +43,7 @@ constexpr int BNW = 64;  // cache rows per wavefront and tile
 constexpr float kBig = 1099511627776.f;   // 2^40: a tile's exponentials may sum to this before the reference moves
 
 // 8-wavefront shape (see the head of the file)
-template <bool SPLIT>
+template <int SPLIT>
 __global__ __launch_bounds__(512, 2) void fwd8_bf16_kernel(AttnParams p, int n_mtiles, int total_items) {
   constexpr int KH = 2;
   constexpr int BN = BNW * KH;                 // cache rows per tile
@@ -48,18 +51,36 @@ __global__ __launch_bounds__(512, 2) void fwd8_bf16_kernel(AttnParams p, int n_m
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];   // 4 * kTileBytes: [buf][K|V]
   lds_char* smem = (lds_char*)smem_raw;
 
-  const int item = xcd_item(blockIdx.x, total_items);
+  const int item = SPLIT == kShares ? shares_item(blockIdx.x, p.B * p.Hkv * p.rows_whole, total_items) : xcd_item(blockIdx.x, total_items);
   if (item < 0) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int l32 = lane & 31, g = lane >> 5;
   const int rb = wave & 3, kh = wave >> 2;
   int b, kvh, h, mt, m0, sp = 0;              // m0: first chunk-local row of this wavefront
+  int n_sp = 1, share_slot = 0;                // shares of this row tile; kShares: where this one's sums go
   if constexpr (SPLIT) {
     // item -> (batch, kv head, row tile of the packed row space, split)
-    sp = item % p.n_splits;
-    int rest = item / p.n_splits;
-    mt = n_mtiles - 1 - rest % n_mtiles;
-    rest /= n_mtiles;
+    int rest;
+    if constexpr (SPLIT == kDivided) {
+      n_sp = p.n_splits;
+      sp = item % n_sp;
+      rest = item / n_sp;
+      mt = n_mtiles - 1 - rest % n_mtiles;
+      rest /= n_mtiles;
+    } else {
+      const int n_cut = n_mtiles - p.rows_whole, n_first = p.B * p.Hkv * p.rows_whole;   // (the whole tiles come first)
+      if (item < n_first) {
+        rest = item / p.rows_whole;
+        mt = n_mtiles - 1 - (item - rest * p.rows_whole);
+      } else {
+        n_sp = p.n_splits;
+        share_slot = item - n_first;
+        rest = share_slot / (n_cut * n_sp);
+        const int e = share_slot - rest * (n_cut * n_sp);
+        sp = e % n_sp;
+        mt = n_cut - 1 - e / n_sp;
+      }
+    }
     kvh = rest % p.Hkv;
     b = rest / p.Hkv;
     const int v0 = mt * BM + rb * 32;          // packed row: head v0 / Cpad of the group, row v0 % Cpad
@@ -107,7 +128,11 @@ __global__ __launch_bounds__(512, 2) void fwd8_bf16_kernel(AttnParams p, int n_m
   const int wave_kv_end = m0 < p.C ? p.q_start + min(m0 + 32, p.C) : 0;  // columns this wavefront sees
   int n_begin = 0, n_end = n_tiles;            // tiles of this workgroup
   auto part_row_of = [&]() { return (int64_t)sp * p.B * p.Hq * p.C + ((int64_t)b * p.Hq + h) * p.C + row; };
-  if constexpr (SPLIT) {
+  if constexpr (SPLIT == kShares) {            // (never empty: there are at least as many tiles as shares)
+    n_begin = sp * n_tiles / n_sp;
+    n_end = (sp + 1) * n_tiles / n_sp;
+  }
+  if constexpr (SPLIT == kDivided) {
     const int per = (n_tiles + p.n_splits - 1) / p.n_splits;
     n_begin = sp * per;
     n_end = min(n_tiles, n_begin + per);
@@ -293,7 +318,7 @@ __global__ __launch_bounds__(512, 2) void fwd8_bf16_kernel(AttnParams p, int n_m
     float a0 = fast_exp2(m_run - m_sub), a1 = fast_exp2(m1 - m_sub);
     l_tot = l_tot * a0 + l1 * a1;
     m_run = m;
-    if constexpr (!SPLIT) {
+    if (SPLIT != kDivided && (SPLIT == kWholeTiles || n_sp == 1)) {
       const float inv = 1.f / l_tot;
       a0 *= inv;
       a1 *= inv;
@@ -308,7 +333,18 @@ __global__ __launch_bounds__(512, 2) void fwd8_bf16_kernel(AttnParams p, int n_m
       }
   }
 
-  if constexpr (SPLIT) {
+  if constexpr (SPLIT == kShares) {
+    if (n_sp > 1) {                            // all 32 rows: the merge takes those that exist
+      const int64_t part_row = (int64_t)share_slot * BM + rb * 32;
+      store_part32(o, p.part + part_row * kHeadDim, 32, smem + rb * (17 * 1024));
+      if (g == 0) {
+        p.part_ml[2 * (part_row + l32)] = m_run;
+        p.part_ml[2 * (part_row + l32) + 1] = l_tot;
+      }
+      return;
+    }
+  }
+  if constexpr (SPLIT == kDivided) {
     // un-normalised partial O (relative to the reference m_run), fp32, plus (m_run, sum)
     const int64_t part_row = part_row_of();
     store_part32(o, p.part + (part_row - l32) * kHeadDim, p.C - m0, smem + rb * (17 * 1024));
@@ -323,7 +359,7 @@ __global__ __launch_bounds__(512, 2) void fwd8_bf16_kernel(AttnParams p, int n_m
   if (row < p.C && g == 0) p.lse[((int64_t)b * p.Hq + h) * p.C + row] = (m_run + __log2f(l_tot)) * kLn2;
 }
 
-template <bool SPLIT>
+template <int SPLIT>
 int launch_fwd8(const AttnParams& p, int n_mtiles, int total, hipStream_t s) {
   constexpr int smem = 4 * BNW * 2 * kRowBytes;
   auto kern = fwd8_bf16_kernel<SPLIT>;
@@ -331,7 +367,8 @@ int launch_fwd8(const AttnParams& p, int n_mtiles, int total, hipStream_t s) {
   if (!allow_lds(ready, reinterpret_cast<const void*>(kern), smem)) return SECO_ERR_LAUNCH;
   {
     ProfScope prof(kKernelFwd, s);
-    hipLaunchKernelGGL(kern, dim3(xcd_grid(total)), dim3(512), smem, s, p, n_mtiles, total);
+    const int first = SPLIT == kShares ? p.B * p.Hkv * p.rows_whole : 0;
+    hipLaunchKernelGGL(kern, dim3(xcd_grid(first) + xcd_grid(total - first)), dim3(512), smem, s, p, n_mtiles, total);
   }
   return launch_status();
 }

@@ -12,8 +12,18 @@ int launch_fwd_bf16(const AttnParams& p, hipStream_t s) {
   }
   const int n_mtiles = (p.C + BM - 1) / BM;
   const int total = p.B * p.Hq * n_mtiles;
+  if (p.tail_bytes > 0) {
+    const SplitPlan plan = split_plan(p.B, p.Hkv, p.G, p.C);
+    const RowShares rs = row_shares(p.B * p.Hkv, plan.n_mtiles, total, p.q_start, p.C, p.tail_bytes / (BM * kHeadDim * sizeof(float)), 6.f, 1.8f);
+    if (rs.shares > 1) {
+      AttnParams ps = p;
+      ps.rows_whole = rs.whole;
+      ps.n_splits = rs.shares;
+      return launch_fwd8_shares_bf16(ps, plan.n_mtiles, s);
+    }
+  }
   // fewer row tiles than two per CU: use the 8-wavefront shape so that every SIMD still has two wavefronts
-  return total < 2 * device_cus() ? launch_fwd8<false>(p, n_mtiles, total, s) : launch_fwd4_bf16(p, n_mtiles, total, s);
+  return total < 2 * device_cus() ? launch_fwd8<kWholeTiles>(p, n_mtiles, total, s) : launch_fwd4_bf16(p, n_mtiles, total, s);
 }
 
 }  // namespace seco

@@ -249,5 +249,15 @@ __device__ __forceinline__ int xcd_item(int block, int total_items) {
   return item < total_items ? item : -1;
 }
 inline int xcd_grid(int total_items) { return ((total_items + 7) / 8) * 8; }
+// How a kernel that owns row tiles divides them among workgroups: not at all; every packed row tile into p.n_splits; only
+// those beyond the first round (row_shares)
+enum { kWholeTiles = 0, kDivided = 1, kShares = 2 };
+// The first n_first items, then the others: each part divided evenly among the XCDs (grid: the two parts' together).
+__device__ __forceinline__ int shares_item(int block, int n_first, int total_items) {
+  const int grid = (n_first + 7) / 8 * 8;
+  if (block < grid) return xcd_item(block, n_first);
+  const int i = xcd_item(block - grid, total_items - n_first);
+  return i < 0 ? -1 : n_first + i;
+}
 
 }  // namespace seco

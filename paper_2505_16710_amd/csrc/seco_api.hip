@@ -100,6 +100,12 @@ size_t split_ml_bytes(const seco_desc* d) {     // (max, sum) of the forward par
   const SplitPlan pl = split_plan(d->batch, d->n_kv_heads, d->n_q_heads / d->n_kv_heads, d->chunk_len);
   return round256((size_t)pl.max_splits * d->batch * d->n_q_heads * d->chunk_len * 2 * sizeof(float));
 }
+// forward, row tiles beyond the first round: partial tiles, then (max, sum) per row
+size_t share_part_bytes(const seco_desc* d) {
+  if (d->dtype != SECO_BF16) return 0;
+  return (size_t)fwd_share_slots(d->batch, d->n_q_heads, d->n_kv_heads, d->chunk_len) * 128 * 128 * sizeof(float);
+}
+size_t share_ml_bytes(const seco_desc* d) { return share_part_bytes(d) / 128 * 2; }
 // number of splits of this call (1: direct path)
 int splits_for(const seco_desc* d) {
   if (split_part_bytes(d) == 0) return 1;
@@ -400,7 +406,8 @@ extern "C" int seco_device_info(int32_t* compute_units_host, int32_t* max_clock_
 
 extern "C" size_t seco_workspace_bytes(const seco_desc* desc, int op) {
   if (check_desc(desc) != SECO_OK) return (size_t)-1;
-  if (op == SECO_OP_FWD) return split_part_bytes(desc) + split_ml_bytes(desc);
+  // (a shape has the one or the other: short chunks, or between one and two rounds of row tiles)
+  if (op == SECO_OP_FWD) return split_part_bytes(desc) + split_ml_bytes(desc) + share_part_bytes(desc) + share_ml_bytes(desc);
   if (op == SECO_OP_BWD) return delta_bytes(desc) + bwd_part_bytes(desc);
   return (size_t)-1;
 }
@@ -442,6 +449,12 @@ extern "C" int seco_chunk_attn_fwd(const seco_desc* desc, const void* q, const v
     p.n_splits = splits_for(desc);
     p.part = static_cast<float*>(ws);
     p.part_ml = reinterpret_cast<float*>(static_cast<char*>(ws) + part_bytes);
+  }
+  const size_t share_bytes = share_part_bytes(desc);
+  if (share_bytes && ws && !(reinterpret_cast<uintptr_t>(ws) & 255u) && ws_bytes >= share_bytes + share_ml_bytes(desc)) {
+    p.part = static_cast<float*>(ws);
+    p.part_ml = reinterpret_cast<float*>(static_cast<char*>(ws) + share_bytes);
+    p.tail_bytes = share_bytes;
   }
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   return desc->dtype == SECO_BF16 ? launch_fwd_bf16(p, s) : launch_fwd_f32(p, s);

@@ -26,7 +26,8 @@ struct AttnParams {
   float* gv;
   float* part;       // split path: partial O (forward) or partial dQ (backward), fp32 [n_splits, B, Hq, C, D]
   float* part_ml;    // split path, forward: (reference max in log2 units, sum) per partial row, [n_splits, B, Hq, C, 2]
-  float* tail_part;  // dK/dV pass: sums of the column tiles shared out among several workgroups (workspace), or NULL
+  float* tail_part;  // workspace, or NULL: dQ pass: sums of the row tiles beyond the first round (row_shares); dK/dV pass,
+                     // after it: of the column tiles shared out among several workgroups
   size_t tail_bytes; // room there; a function of the descriptor, not of the workspace that was passed
   int n_splits;      // > 1 selects the split path
   int Cpad;          // C rounded up to 32: rows per head in the packed row space of the split path
@@ -34,6 +35,7 @@ struct AttnParams {
   float scale;
   int64_t qs[3], os[3], kvs[3], gs[3];
   PendingDq* pending;   // backward, host side: a dQ pass that is announced but not launched yet
+  int rows_whole;       // row tiles beyond the first round divided: how many of a (batch, KV head)'s are not
 };
 
 // Column segments of the dK/dV pass: a run of cache rows that share one weight.
@@ -103,6 +105,44 @@ inline int split_count(const SplitPlan& pl, int kv_len) {
     }
   }
   return best;
+}
+// Row tiles between one and two rounds of workgroups, one per CU: the second round, which would be as long as the first
+// however few tiles it has, is divided.  Of every (batch, KV head)'s packed row tiles the first `whole` (together one round)
+// stay whole, the others have their cache rows divided among `shares` workgroups each, which run in short rounds of their
+// own; shares 1: nothing is divided.  slots: partial tiles that the workspace holds; n_plain: workgroups without packing,
+// the alternative.  Times in microseconds: wg + tile per 128 cache rows, a merge 5 + 0.03 per share; forward 6 + 1.8, dQ
+// 7.5 + 2.7 (in dense calls of one round).  Chosen where that comes out 5 % below the undivided call, and only where the
+// tiles are about equally long (a chunk of at most half of what precedes it: the rounds' lengths are those of the mean).
+// Microseconds before -> after, 32 heads on 8, batch 1:
+//   rows @ preceding    1100 @ 9000   1500 @ 9000   1300 @ 3000   1060 @ 30000   1900 @ 9000 (undivided by the rule)
+//   forward              268 -> 196    281 -> 265    106 -> 100    878 -> 597     328 -> 327
+//   backward, both passes 690 -> 586   805 -> 772    292 -> 280   2083 -> 1692   1004 -> 1004
+// and 16 heads on 2, 2500 @ 9000: 308 -> 234, 842 -> 738; 8 on 8, 4500 @ 12000: 372 -> 290.
+constexpr int kMaxRowShares = 8;
+struct RowShares { int whole, shares; };
+inline RowShares row_shares(int n_units, int n_mtiles, int n_plain, int q_start, int C, size_t slots, float wg, float tile) {
+  const int cus = device_cus(), whole = cus / n_units, n_cut = n_mtiles - whole, tiles = (q_start + C / 2 + 127) / 128;
+  RowShares best{0, 1};
+  if (whole < 1 || n_cut < 1 || n_plain >= 2 * cus || q_start < 2 * C) return best;
+  const float one = wg + tile * tiles;
+  float best_t = 0.95f * ((n_plain + cus - 1) / cus) * one;
+  for (int k = 2; k <= kMaxRowShares && k <= q_start / 128; ++k) {
+    const int64_t n = (int64_t)n_units * n_cut * k;
+    if ((size_t)n > slots) break;
+    const float t = one + (n + cus - 1) / cus * (wg + tile * ((tiles + k - 1) / k)) + 5.f + 0.03f * n;
+    if (t < best_t) {
+      best_t = t;
+      best = RowShares{whole, k};
+    }
+  }
+  return best;
+}
+// Partial tiles that a forward's workspace holds for that (0: the shape never divides them); by the shape alone
+inline int fwd_share_slots(int B, int Hq, int Hkv, int C) {
+  const int cus = device_cus(), units = B * Hkv, n_mtiles = split_plan(B, Hkv, Hq / Hkv, C).n_mtiles;
+  if (units > cus || (int64_t)units * n_mtiles <= cus || (int64_t)B * Hq * ((C + 127) / 128) >= 2 * cus) return 0;
+  const int n = units * (n_mtiles - cus / units) * kMaxRowShares;
+  return n < 2 * cus ? n : 2 * cus;
 }
 int launch_fwd_merge(const AttnParams& p, hipStream_t s);   // O, LSE from the partials
 int launch_dq_merge(const AttnParams& p, hipStream_t s);    // dQ = scale * sum of the partials, in split order
@@ -260,6 +300,8 @@ int launch_fwd_bf16(const AttnParams& p, hipStream_t s);
 int launch_fwd4_bf16(const AttnParams& p, int n_mtiles, int total, hipStream_t s);
 // the 8-wavefront forward kernel's short-chunk variant, which writes partials (likewise)
 int launch_fwd8_split_bf16(const AttnParams& p, int n_mtiles, int total, hipStream_t s);
+// ... and its variant that divides the row tiles beyond the first round, with the merge behind it
+int launch_fwd8_shares_bf16(const AttnParams& p, int n_mtiles, hipStream_t s);
 // at most 32 query rows per KV head; max_splits: how many partial results the workspace holds (1: there is none)
 int launch_fwd_small_bf16(AttnParams p, int max_splits, hipStream_t s);
 // dq_runs: NULL for all visible cache rows with weight 1; else runs of cache rows (ascending, disjoint), each with

@@ -103,6 +103,20 @@ def test_spaco_weight_validation():
     assert sparse([1.0] * 128, [float(i % 4 == 0) for i in range(128)], 128, 4) == -6   # 32 runs fit
 
 
+@pytest.mark.parametrize("Hq,Hkv,C,tiles", [
+    (32, 8, 1024, 0),        # one round of row tiles on 256 CUs
+    (32, 8, 1025, 8 * 1),    # packed: 4 heads of 1056 rows are 33 tiles, 32 of them one round
+    (32, 8, 1920, 64),       # 60 tiles: 28 divided, as many shares as two rounds hold (512 partial tiles)
+    (32, 8, 1921, 0),        # two full rounds
+    (8, 8, 4097, 8 * 1),
+    (16, 2, 2500, 60),       # 158 packed tiles per KV head, 30 of them divided
+])
+def test_forward_workspace_between_one_and_two_rounds(Hq, Hkv, C, tiles):
+    """Row tiles beyond the first round are divided among up to 8 workgroups each: partial rows and (max, sum)."""
+    n = seco.seco_workspace_bytes(desc(n_q_heads=Hq, n_kv_heads=Hkv, chunk_len=C), B.SECO_OP_FWD)
+    assert n == tiles * 8 * 128 * (128 + 2) * 4
+
+
 def test_kvgrad_validation_and_workspace_size():
     lib = seco.load_library()
     d = desc()

@@ -181,6 +181,43 @@ def test_bf16_backward_of_a_short_call_in_one_launch(B, Hq, Hkv, N, C, sel):
     check(got, ref, "bf16", f"one launch {B,Hq,Hkv,N,C,sel}")
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,C,q_start", [
+    (1, 64, 8, 513, 1500),     # 256 tiles whole, 8 in shares: the last packed tile holds 96 padding rows
+    (1, 8, 8, 4100, 8300),     # one head per KV head, padding within the shares' rows
+    (3, 12, 4, 850, 1701),     # 252 whole tiles on 256 CUs; rows that see nothing of the last share
+    (1, 48, 16, 700, 2900),    # three heads of a group in one tile
+])
+def test_bf16_row_tiles_beyond_one_round_divided(B, Hq, Hkv, C, q_start):
+    """Between one and two rounds of row tiles the second round's cache rows are divided (forward with a workspace, dQ);
+    caches with a larger row stride, heads of Q and O interleaved by row.  The direct forward against the same reference."""
+    N, s = q_start + C, 1 / np.sqrt(128)
+    g = torch.Generator(device=DEV).manual_seed(64)
+    rand = lambda *shape: torch.randn(*shape, device=DEV, generator=g).to(torch.bfloat16)
+    k, v = rand(B, Hkv, N, 136)[..., :128], rand(B, Hkv, N, 136)[..., :128]
+    q, do = (rand(B, C, Hq, 128).transpose(1, 2) for _ in range(2))
+    d = seco.binding.make_desc(q, k, q_start, s)
+    assert seco.seco_workspace_bytes(d, seco.binding.SECO_OP_FWD) > 0
+    outs = [seco.seco_chunk_attn_fwd(q, k, v, q_start, s, ws=ws) for ws in (None, None, False)]
+    o, lse = outs[0]
+    gk, gv = (torch.zeros(B, Hkv, N, 128, device=DEV) for _ in range(2))
+    dqs = [seco.seco_chunk_attn_bwd(q, k, v, o, lse, do, gk, gv, q_start, s) for _ in range(2)]
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(outs[0], outs[1])) and torch.equal(*dqs)
+    rows = torch.arange(C, device=DEV)[:, None] + q_start
+    for b in range(B):
+        for h in range(Hq):                          # fp32 on the device, one head at a time
+            kf, vf, qf, dof = k[b, h * Hkv // Hq].float(), v[b, h * Hkv // Hq].float(), q[b, h].float(), do[b, h].float()
+            z = (qf @ kf.t() * s).masked_fill(torch.arange(N, device=DEV)[None, :] > rows, float("-inf"))
+            ref_l = z.logsumexp(-1)
+            p = torch.exp(z - ref_l[:, None])
+            ref_o = p @ vf
+            ref_dq = s * (p * (dof @ vf.t() - (dof * ref_o).sum(-1, keepdim=True))) @ kf
+            for oo, ll in outs:
+                assert max_rel(to_host(oo[b, h]), to_host(ref_o)) <= TOL["bf16"]["o"], (b, h)
+                assert max_rel(to_host(ll[b, h]), to_host(ref_l)) <= TOL["bf16"]["lse"], (b, h)
+            assert max_rel(to_host(dqs[0][b, h]), to_host(ref_dq)) <= TOL["bf16"]["dq"], (b, h)
+
+
 def _one_call(dtype, D, N, C, j, weights=None, seed=40):
     x = small_layer(seed, 1, 4, 2, N, D, dtype)
     q, k, v, do = (to_dev(x[n], dtype) for n in ("q", "k", "v", "do"))
