@@ -175,7 +175,7 @@ class ChunkedDecoder:
     def step(self, tokens, targets, chunk_len, selected=None, factor=1.0, keep_attention_outputs=False,
              stage1_chunk_len=None, dq_weights=None, transposed_backward=False):
         """One SeCO step (selected is None: Alg. 1) or SpaCO step (Alg. 2, `selected` chunk indices,
-        relay factor `factor`).  Returns (sum of the chunk losses from stage 1, {name: gradient}).
+        relay factor `factor`).  Returns (sum of the chunk losses, as stage 1 runs them, {name: gradient}).
 
         The derivatives are written out, not recorded: hooks of the parameters run once per step, with its gradient
         (hand_over), not once per chunk, and saved-tensor hooks have nothing to see.
@@ -225,8 +225,12 @@ class ChunkedDecoder:
                                 min(chunk_len, N), transposed_backward), [p[n] for n in names])
             tokens, targets = tokens.to(torch.int64), targets.to(torch.int64)
             losses = torch.empty(N * B, dtype=torch.float32, device=dev)        # one per token, in stage-1 order
+            # stage 2 rebuilds every chunk as stage 1 ran it, launch for launch: the losses come from there, and stage 1 ends
+            # at the last layer's cache rows (of a two-layer step over 4096 tokens an eighth of the time, mostly that
+            # layer's attention and MLP, the final norm and the head)
+            rebuilt = c1 == chunk_len and set(order) == set(range(len(starts)))
             for s0 in range(0, N, c1):                                      # stage 1: inference over all chunks
-                ext.step_infer(run, tokens, targets, s0, min(s0 + c1, N), losses, keep_attention_outputs)
+                ext.step_infer(run, tokens, targets, s0, min(s0 + c1, N), None if rebuilt else losses, keep_attention_outputs)
             ext.step_zero(run)
             for j in order:                                                 # stage 2: rebuild + back-propagate
                 w = wq = None
@@ -238,6 +242,6 @@ class ChunkedDecoder:
                 if dq_weights is not None:
                     wq = [dq_weights(j, l) for l in range(self.n_layers)]
                 ext.step_train(run, tokens, targets, starts[j], min(starts[j] + chunk_len, N), keep_attention_outputs, w,
-                               chunk_len, wq)
+                               chunk_len, wq, losses if rebuilt else None)
             total, grads = float(losses.sum()), dict(zip(names, ext.step_grads(run)))
         return total, hand_over(p, grads)

@@ -294,7 +294,9 @@ struct Step {
 
   // ---- one chunk.  Returns its logits; saved: receives what the backward needs of every layer and, last, of the final norm
   // (NULL in stage 1, where the residual stream is updated in place and the layers share their buffers).
-  void* forward(const Tensor& tok, int64_t C, int64_t q_start, Keep keep, Arena& mem, std::vector<Saved>* saved, Tensor& x0) {
+  // to_cache: only as far as the last layer's cache rows (and, kept, its attention output); returns NULL
+  void* forward(const Tensor& tok, int64_t C, int64_t q_start, Keep keep, Arena& mem, std::vector<Saved>* saved, Tensor& x0,
+                bool to_cache = false) {
     const int64_t R = B * C;
     auto rows = [&](int64_t n) { return mem.take((size_t)(R * n) * e); };
     auto stats = [&]() { return static_cast<float*>(mem.take((size_t)R * 4)); };
@@ -314,7 +316,12 @@ struct Step {
       norm(x, have_y ? y : nullptr, l.norm1, sv.x1, sv.h1, sv.r1);
       sv.qkv = rows(W);
       mm(sv.qkv, sv.h1, l.wqkv, R);
+      if (to_cache && &l == &layers.back() && keep == kCompute) {
+        append(l, sv.qkv, C, q_start);
+        return nullptr;
+      }
       attention(l, sv, C, q_start, keep, mem);
+      if (to_cache && &l == &layers.back()) return nullptr;
       mm(y, sv.o, l.wo, R);
       sv.x2 = saved ? rows(dm) : x;
       sv.h2 = rows(dm);
@@ -560,20 +567,27 @@ Tensor chunk_of(const Step& st, const Tensor& t, int64_t s0, int64_t s1) {
   return t.slice(1, s0, s1).reshape({-1});
 }
 
-// (step, tokens, targets, s0, s1, losses, store): inference over rows [s0, s1) of every sequence; their losses
+// where the losses of rows [s0, s1) of every sequence go
+float* losses_at(const Step& st, const Tensor& losses, int64_t s0, int64_t s1) {
+  if (losses.device() != st.emb.w.device() || losses.scalar_type() != at::kFloat || !losses.is_contiguous() || losses.numel() < st.B * s1)
+    raise(PyExc_ValueError, "losses: one float32 per token");
+  return fptr(losses) + s0 * st.B;
+}
+
+// (step, tokens, targets, s0, s1, losses, store): inference over rows [s0, s1) of every sequence; their losses (None: the
+// chunk is rebuilt later with the same launches, which then give the losses; here it ends at the last layer's cache rows)
 PyObject* step_infer(PyObject* const* a) {
   Step& st = step_of(a[0]);
   begin(st);
   const int64_t s0 = integer(a[3]), s1 = integer(a[4]);
   const Tensor tok = chunk_of(st, tensor(a[1]), s0, s1), tgt = chunk_of(st, tensor(a[2]), s0, s1);
-  const Tensor& losses = tensor(a[5]);
-  if (losses.device() != st.emb.w.device() || losses.scalar_type() != at::kFloat || !losses.is_contiguous() || losses.numel() < st.B * s1)
-    raise(PyExc_ValueError, "losses: one float32 per token");
+  const bool to_cache = a[5] == Py_None;
+  float* losses = to_cache ? nullptr : losses_at(st, tensor(a[5]), s0, s1);
   st.stage1.used = 0;
   Tensor x0;
-  void* logits = st.forward(tok, s1 - s0, s0, PyObject_IsTrue(a[6]) == 1 ? kStore : kCompute, st.stage1, nullptr, x0);
-  check(lib.dec_cross_entropy(st.tail, logits, static_cast<const int64_t*>(ptr(tgt)), fptr(losses) + s0 * st.B, tok.numel(), st.V, st.s),
-        "dec_cross_entropy");
+  void* logits = st.forward(tok, s1 - s0, s0, PyObject_IsTrue(a[6]) == 1 ? kStore : kCompute, st.stage1, nullptr, x0, to_cache);
+  if (!to_cache)
+    check(lib.dec_cross_entropy(st.tail, logits, static_cast<const int64_t*>(ptr(tgt)), losses, tok.numel(), st.V, st.s), "dec_cross_entropy");
   Py_RETURN_NONE;
 }
 
@@ -588,8 +602,8 @@ PyObject* step_zero(PyObject* const* a) {
   Py_RETURN_NONE;
 }
 
-// (step, tokens, targets, s0, s1, reuse, weights or None, weight chunk length, per-layer dQ weights or None): rebuilds the
-// chunk and back-propagates its loss
+// (step, tokens, targets, s0, s1, reuse, weights or None, weight chunk length, per-layer dQ weights or None, losses or None):
+// rebuilds the chunk and back-propagates its loss
 PyObject* step_train(PyObject* const* a) {
   Step& st = step_of(a[0]);
   begin(st);
@@ -605,12 +619,17 @@ PyObject* step_train(PyObject* const* a) {
       wq.push_back(x == Py_None ? std::vector<float>() : floats(x));
     }
   }
+  float* losses = a[9] == Py_None ? nullptr : losses_at(st, tensor(a[9]), s0, s1);
   st.stage2.used = 0;
   std::vector<Saved> saved;
   saved.reserve(st.L + 1);
   Tensor x0;
   void* logits = st.forward(tok, s1 - s0, s0, PyObject_IsTrue(a[5]) == 1 ? kReuse : kCompute, st.stage2, &saved, x0);
-  check(lib.dec_cross_entropy(st.tail, logits, static_cast<const int64_t*>(ptr(tgt)), nullptr, tok.numel(), st.V, st.s), "dec_cross_entropy");
+  const int64_t* target = static_cast<const int64_t*>(ptr(tgt));
+  if (losses)
+    check(lib.dec_cross_entropy_both(st.tail, logits, target, losses, tok.numel(), st.V, st.s), "dec_cross_entropy_both");
+  else
+    check(lib.dec_cross_entropy(st.tail, logits, target, nullptr, tok.numel(), st.V, st.s), "dec_cross_entropy");
   st.trained = true;
   st.backward(logits, tok, s1 - s0, s0, saved, st.stage2, w, wq, integer(a[7]));
   Py_RETURN_NONE;
@@ -666,7 +685,7 @@ PyObject* has_grad_hooks(PyObject* const* a) {
 }  // namespace
 
 PyMethodDef step_methods[] = {SECO_METHOD("step_new", step_new, 2),   SECO_METHOD("step_infer", step_infer, 7),
-                              SECO_METHOD("step_zero", step_zero, 1), SECO_METHOD("step_train", step_train, 9),
+                              SECO_METHOD("step_zero", step_zero, 1), SECO_METHOD("step_train", step_train, 10),
                               SECO_METHOD("step_grads", step_grads, 1), SECO_METHOD("has_grad_hooks", has_grad_hooks, 1), {nullptr, nullptr, 0, nullptr}};
 
 }  // namespace seco_ext

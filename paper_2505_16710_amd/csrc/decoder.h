@@ -19,6 +19,8 @@ int dec_silu_bwd(int dtype, const void* u, void* d_a, int64_t n, void* stream); 
 // loss[r] = logsumexp(logits[r]) - logits[r][target[r]] (loss non-NULL), or logits <- softmax - onehot (loss NULL);
 // a target of -100 gives loss 0 and gradient 0, any other target outside [0, v) NaN
 int dec_cross_entropy(int dtype, void* logits, const int64_t* target, float* loss, int64_t rows, int64_t v, void* stream);
+// both: the loss (loss non-NULL), and logits <- softmax - onehot; the same values
+int dec_cross_entropy_both(int dtype, void* logits, const int64_t* target, float* loss, int64_t rows, int64_t v, void* stream);
 // grad[token[r]] += d_x[r] for every row r; the rows of one token are added in ascending order by one workgroup
 int dec_embedding_bwd(int dtype, const void* d_x, const int64_t* token, void* grad, int64_t rows, int64_t d, int64_t v,
                       void* stream);

@@ -252,7 +252,7 @@ __global__ __launch_bounds__(kThreads) void silu_kernel(const T* u, T* a, int64_
 }
 
 template <typename T, int V>
-__global__ __launch_bounds__(kThreads) void cross_entropy_kernel(T* logits, const int64_t* target, float* loss, int64_t v) {
+__global__ __launch_bounds__(kThreads) void cross_entropy_kernel(T* logits, const int64_t* target, float* loss, bool grad, int64_t v) {
   const int64_t row = (int64_t)blockIdx.x * v, t = target[blockIdx.x];
   T* l = logits + row;
   float m = -INFINITY;
@@ -270,12 +270,12 @@ __global__ __launch_bounds__(kThreads) void cross_entropy_kernel(T* logits, cons
 #pragma unroll
     for (int j = 0; j < V; ++j) sum += exp_of<T>(f[j] - m);
   }
-  sum = block_reduce<Sum>(sum);
   const bool bad = t != -100 && (t < 0 || t >= v);
-  if (loss) {
-    if (threadIdx.x == 0) loss[blockIdx.x] = t == -100 ? 0.f : bad ? NAN : m + log_of<T>(sum) - (float)l[t];
-    return;
-  }
+  float at_target = 0.f;                       // read in front of the barriers behind which the row is overwritten
+  if (loss && threadIdx.x == 0 && t != -100 && !bad) at_target = (float)l[t];
+  sum = block_reduce<Sum>(sum);
+  if (loss && threadIdx.x == 0) loss[blockIdx.x] = t == -100 ? 0.f : bad ? NAN : m + log_of<T>(sum) - at_target;
+  if (!grad) return;
   const float inv = t == -100 ? 0.f : bad ? NAN : 1.f / sum;
   for (int64_t c = threadIdx.x * V; c < v; c += kThreads * V) {
     float f[V];
@@ -428,16 +428,23 @@ extern "C" int dec_silu_bwd(int dtype, const void* u, void* d_a, int64_t n, void
   return silu<true>(dtype, u, d_a, n, stream);
 }
 
-extern "C" int dec_cross_entropy(int dtype, void* logits, const int64_t* target, float* loss, int64_t rows, int64_t v,
-                                 void* stream) {
+static int cross_entropy(int dtype, void* logits, const int64_t* target, float* loss, bool grad, int64_t rows, int64_t v, void* stream) {
   if (!sizes_ok(dtype, rows, v)) return SECO_ERR_SHAPE;
   if (rows == 0) return SECO_OK;
 #define L(T, V)                                                                                                     \
   hipLaunchKernelGGL((cross_entropy_kernel<T, V>), dim3((unsigned)rows), dim3(kThreads), 0, (hipStream_t)stream,    \
-                     (T*)logits, target, loss, v)
+                     (T*)logits, target, loss, grad, v)
   DEC_DISPATCH(v, words(logits), L)
 #undef L
   return status();
+}
+extern "C" int dec_cross_entropy(int dtype, void* logits, const int64_t* target, float* loss, int64_t rows, int64_t v,
+                                 void* stream) {
+  return cross_entropy(dtype, logits, target, loss, !loss, rows, v, stream);
+}
+extern "C" int dec_cross_entropy_both(int dtype, void* logits, const int64_t* target, float* loss, int64_t rows, int64_t v,
+                                      void* stream) {
+  return cross_entropy(dtype, logits, target, loss, true, rows, v, stream);
 }
 
 extern "C" int dec_embedding_bwd(int dtype, const void* d_x, const int64_t* token, void* grad, int64_t rows, int64_t d,

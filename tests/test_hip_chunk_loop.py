@@ -93,6 +93,18 @@ def test_keeping_attention_outputs_gives_identical_gradients(dtype, cfg):
             assert torch.equal(g_a[n], g_b[n]), n
 
 
+@pytest.mark.parametrize("dtype,cfg,N", [(torch.float32, F32_CFG, 200), (torch.bfloat16, BF16_CFG, 256)])
+@pytest.mark.parametrize("kw", [{}, {"keep_attention_outputs": True}])
+def test_losses_of_a_step_that_visits_every_chunk(dtype, cfg, N, kw):
+    """They come from stage 2; with a chunk left out, from stage 1: the same bits (same launches on the same inputs)."""
+    _, dec, tok, tgt = _setup(cfg, 17, 1, N, dtype)
+    tok, tgt = tok.to(DEV), tgt.to(DEV)
+    every, _ = dec.step(tok, tgt, 64, **kw)
+    picked, _ = dec.step(tok, tgt, 64, selected=[0, 1, 2, 3], factor=1.0, **kw)
+    some, _ = dec.step(tok, tgt, 64, selected=[3, 1, 0], factor=4 / 3, **kw)
+    assert every == picked == some
+
+
 def test_whole_sequence_stage1_with_kept_outputs_matches_oracle():
     """Stage 1 as one plain forward over the whole sequence, stage 2 from its kept O / LSE: same gradients as the
     oracle's Alg. 1 / Alg. 2 (to the usual tolerance; the launches differ in shape from the chunked stage 1)."""

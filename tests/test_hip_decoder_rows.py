@@ -192,6 +192,23 @@ def test_cross_entropy_targets(dtype, v):
     assert not got[1].any() and torch.isnan(got[3:5]).all()
 
 
+@pytest.mark.parametrize("dtype", [F32, BF16])
+@pytest.mark.parametrize("v", [1, 29, 2048, 10000])
+def test_cross_entropy_loss_and_gradient_in_one_launch(dtype, v):
+    """The same bits as the two calls, whichever thread holds the target."""
+    rows = 300
+    logits = 4 * _rows(dtype, v, rows, v).float()
+    logits = logits.to(torch.float32 if dtype == F32 else torch.bfloat16).to(DEV)
+    target = torch.randint(0, v, (rows,), generator=torch.Generator().manual_seed(v)).to(DEV)
+    target[1], target[3], target[4], target[6], target[7] = -100, v, -1, v - 1, 0
+    one, two, loss1, loss2 = logits.clone(), logits.clone(), torch.empty(rows, device=DEV), torch.empty(rows, device=DEV)
+    _call("cross_entropy", dtype, one, target, loss1, rows, v)
+    _call("cross_entropy", dtype, one, target, None, rows, v)
+    _call("cross_entropy_both", dtype, two, target, loss2, rows, v)
+    bits = torch.int32 if dtype == F32 else torch.int16
+    assert torch.equal(one.view(bits), two.view(bits)) and torch.equal(loss1.view(torch.int32), loss2.view(torch.int32))
+
+
 @pytest.mark.parametrize("dtype,n", [(BF16, 8), (BF16, 9), (BF16, 65536 * 2048 + 2048 * 3), (F32, 4), (F32, 1023)])
 def test_silu_lengths(dtype, n):
     """The shortest and odd lengths, and one that the largest grid walks more than once."""
