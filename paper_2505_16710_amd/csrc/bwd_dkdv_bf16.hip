@@ -53,12 +53,35 @@ struct BwdPlan {
   bool kv_first;
   TailSplit ts;
 };
-// One launch is taken when all workgroups of both passes fit the chip at one per CU and the longer pass, with the extra
-// work, is expected to end before the two would one after the other: with more workgroups than CUs the two halves of
-// the grid would queue behind each other on some CUs (16/2 heads, chunk 704 at 5632: 7% slower in one launch).  The passes
-// divide the CUs: for every number of shares of a dQ row tile the column tiles are shared out over the rest.  Times in
-// microseconds as measured: a dQ workgroup 7.5 + 2.5 per tile of 128 cache rows, a dK/dV workgroup that computes its row
-// statistics 8.5 + 1.8 per iteration.
+// Column tiles for a round or more (n_kv of them, iters iterations each): in how many shares a row tile of dQ joins them
+// in one launch, dQ first; 0: not.  The column tiles of a round all start together and reach the read-modify-write of
+// gK / gV together, and the last round is seldom full; dQ's workgroups, of another length, fill it and put them out of step.
+// Shares: the fewest that end within 0.9 of the time the column tiles take (few workgroups, few partial sums).  Against it
+// stand the row statistics, computed anew in every iteration: beyond 12 iterations, or with a single full round of more than
+// 4, some shapes lost 3 - 10 %.  Both sides in microseconds as fitted to shapes of 16 - 1000 rows on 256 - 2560 tiles (4 % off);
+// one launch where it comes out 3 % ahead: 210 of 345 shapes, 1.14 times as fast, none more than 1.3 % slower.  Two -> one, us:
+//   32/8 heads  32 at 16256: 126 -> 110   64 at 8000: 75 -> 62   128 at 4000: 66 -> 53   128 at 16256: 175 (not taken: 177)
+//   8/8  128 at 4000: 43 -> 32            16/8  256 at 4000: 68 -> 55                    16/2  64 at 32000: 105 -> 92
+template <typename F>
+int rounds_in_one_launch(int n_kv, int iters, int items, int tiles, int max_splits, const F& dq_wgs) {
+  const float cus = (float)device_cus(), kv = n_kv / cus;
+  if (iters > (n_kv <= device_cus() ? 4 : 12)) return 0;
+  int n = 1;
+  while (n < max_splits && 8.f + 2.7f * ((tiles + n - 1) / n) > 0.9f * kv * (14.f + 2.f * iters)) ++n;
+  const int full = n_kv / device_cus();
+  const float tail = kv - full;
+  const float rest = tail > 0.f ? 9.2f + 0.6f * iters + tail * (5.6f + 1.7f * iters) : 0.f;
+  const float apart = 12.2f + full * (15.2f + 2.2f * iters) + rest + 1.7f * items * tiles / cus;
+  const float one = 5.3f + 2.3f * dq_wgs(n) * tiles / (n * cus) + kv * (14.f + 2.2f * iters) + 0.6f * iters;
+  return 1.03f * one < apart ? n : 0;
+}
+
+// With column tiles for less than a round, one launch is taken when all workgroups of both passes fit the chip at one per
+// CU and the longer pass, with the extra work, is expected to end before the two would one after the other: with more
+// workgroups than CUs the two halves of the grid would queue behind each other on some CUs (16/2 heads, chunk 704 at 5632:
+// 7% slower in one launch).  The passes divide the CUs: for every number of shares of a dQ row tile the column tiles are
+// shared out over the rest.  Times in microseconds as measured: a dQ workgroup 7.5 + 2.5 per tile of 128 cache rows, a
+// dK/dV workgroup that computes its row statistics 8.5 + 1.8 per iteration.
 BwdPlan plan_bwd(const AttnParams& p, const SegTable& seg) {
   const int cus = device_cus(), n_units = p.B * p.Hkv, n_ctiles = seg.tile_begin[seg.n];
   RowRuns none;
@@ -71,16 +94,27 @@ BwdPlan plan_bwd(const AttnParams& p, const SegTable& seg) {
   float kv_alone = 0.f;
   best.ts.plan = share_plan(runs, n_units, n_ctiles, p.G, p.C, slots_in(p.tail_bytes), kv_alone);
   const SplitPlan sp = split_plan(p.B, p.Hkv, p.G, p.C);
-  if (!p.pending || (int64_t)n_units * n_ctiles >= cus || sp.items >= cus) return best;
+  if (!p.pending || sp.items >= cus) return best;
   const int tiles = (p.q_start + p.C + 127) / 128;
+  const size_t dq_bytes = (size_t)p.B * p.Hq * p.C * 128 * sizeof(float);
   auto dq_wgs = [&](int n) { return n > 1 ? sp.items * n : p.B * p.Hq * ((p.C + 127) / 128); };
+  auto dq_part = [&](int n) { return n > 1 ? (n * dq_bytes + 255) / 256 * 256 : (size_t)0; };
+  if ((int64_t)n_units * n_ctiles >= cus) {
+    const int n = rounds_in_one_launch(n_units * n_ctiles, runs.iters[0], sp.items, tiles, p.n_splits, dq_wgs);
+    if (n > 0 && dq_part(n) <= p.tail_bytes) {
+      best.dq_splits = n;
+      best.kv_first = false;
+      best.ts.part = p.tail_part + dq_part(n) / sizeof(float);
+      best.ts.plan = share_plan(runs, n_units, n_ctiles, p.G, p.C, slots_in(p.tail_bytes - dq_part(n)), kv_alone);
+    }
+    return best;
+  }
   auto dq_time = [&](int n) { return 7.5f + 2.5f * ((tiles + n - 1) / n); };
   auto merge_time = [&](int n) { return n > 1 ? 4.f + 0.02f * dq_wgs(n) : 0.f; };
   float best_t = (dq_wgs(p.n_splits) + cus - 1) / cus * dq_time(p.n_splits) + merge_time(p.n_splits) + kv_alone + 2.f;
   int per = 0;
-  const size_t dq_bytes = (size_t)p.B * p.Hq * p.C * 128 * sizeof(float);
   for (int n = 1; n <= p.n_splits && dq_wgs(n) + n_units * n_ctiles <= cus; ++n) {
-    const size_t used = n > 1 ? (n * dq_bytes + 255) / 256 * 256 : 0;
+    const size_t used = dq_part(n);
     if (used > p.tail_bytes) break;
     const ShareChoice c = choose_shares(runs, n_ctiles, n_units, cus - dq_wgs(n), slots_in(p.tail_bytes - used), 1, true, 8.5f, 1.8f);
     // (both merges are one launch)

@@ -9,7 +9,9 @@
 //   8/8  32 at 1024  24.0 -> 14.9     32/8 256 at 0      31.6 -> 21.4
 //   8/8 128 at 512   25.5 -> 16.1     32/8 256 at 2048   57.8 -> 47.0
 //   16/2 184 at 736  40.1 -> 25.4     8/2  512 at 2048   48.5 -> 33.5
-// What bounds it now: one workgroup's prologue, 1 - 10 iterations and epilogue, at one workgroup per CU.
+// What bounds it now: one workgroup's prologue, 1 - 10 iterations and epilogue, at one workgroup per CU.  With a round or more
+// of column tiles one launch pays by what rounds_in_one_launch weighs (8/8 heads, 128 rows at 16256: 112 -> 95): bound then by
+// the read-modify-write of gK and gV (with the reads of K and V 2.5 KiB per cache row and KV head, at 3.6 TB/s).
 #include "bwd_dkdv_body.h"
 #include "bwd_dq_body.h"
 #include "merge_body.h"

@@ -181,6 +181,53 @@ def test_bf16_backward_of_a_short_call_in_one_launch(B, Hq, Hkv, N, C, sel):
     check(got, ref, "bf16", f"one launch {B,Hq,Hkv,N,C,sel}")
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,C,q_start,apart", [
+    (1, 8, 8, 70, 4050, False),       # 264 column tiles; one head per KV head: no tile is shared out
+    (1, 32, 8, 33, 4130, False),      # the eight of the second round are
+    (1, 16, 2, 48, 17000, False),     # many shares of few row tiles
+    (2, 16, 8, 250, 2200, False),     # row tiles of two heads, chunk's end and its diagonal inside column tiles
+    (1, 8, 8, 64, 6400, False),
+    (1, 32, 8, 128, 16256, True),     # not taken: four rounds of eight iterations
+    (1, 16, 2, 60, 16300, True),      # nor one full round of eight
+])
+def test_bf16_backward_of_several_rounds_in_one_launch(B, Hq, Hkv, C, q_start, apart):
+    """dQ's workgroups in front of a round or more of column tiles, and what the rule leaves in two launches: dQ and the
+    gradients added to what the buffers hold, against fp32 on the device; reruns and unit weights give the same bits."""
+    N, s, G = q_start + C, 1 / np.sqrt(128), Hq // Hkv
+    g = torch.Generator(device=DEV).manual_seed(65)
+    rand = lambda *shape: torch.randn(*shape, device=DEV, generator=g).to(torch.bfloat16)
+    q, do, k, v = rand(B, Hq, C, 128), rand(B, Hq, C, 128), rand(B, Hkv, N, 136)[..., :128], rand(B, Hkv, N, 136)[..., :128]
+    o, lse = seco.seco_chunk_attn_fwd(q, k, v, q_start, s)
+    def run(call):
+        gk, gv = torch.full((B, Hkv, N, 128), 0.5, device=DEV), torch.full((B, Hkv, N, 128), -0.25, device=DEV)
+        return call(gk, gv), gk, gv
+    seco.seco_profile_enable(True)
+    got = run(lambda gk, gv: seco.seco_chunk_attn_bwd(q, k, v, o, lse, do, gk, gv, q_start, s))
+    prof = seco.seco_profile_read()
+    seco.seco_profile_enable(False)
+    assert (prof["dkdv"][1] == 1) == apart and (prof["bwd"][1] == 1) == (not apart)
+    again = run(lambda gk, gv: seco.seco_chunk_attn_bwd(q, k, v, o, lse, do, gk, gv, q_start, s))
+    assert all(torch.equal(a, b) for a, b in zip(got, again))
+    if q_start % C == 0:
+        n = q_start // C + 1
+        if n <= 128:
+            unit = run(lambda gk, gv: seco.spaco_chunk_attn_bwd(q, k, v, o, lse, do, gk, gv, q_start, s, [1.0] * n, C))
+            assert all(torch.equal(a, b) for a, b in zip(got, unit))
+    rows = torch.arange(C, device=DEV)[:, None] + q_start
+    for b in range(B):
+        for kh in range(Hkv):
+            kf, vf, rk, rv = k[b, kh].float(), v[b, kh].float(), 0.5, -0.25
+            for h in range(kh * G, kh * G + G):
+                qf, dof, of = q[b, h].float(), do[b, h].float(), o[b, h].float()
+                z = (qf @ kf.t() * s).masked_fill(torch.arange(N, device=DEV)[None, :] > rows, float("-inf"))
+                p = torch.exp(z - lse[b, h][:, None])
+                ds = p * (dof @ vf.t() - (dof * of).sum(-1, keepdim=True))
+                assert max_rel(to_host(got[0][b, h]), to_host(s * ds @ kf)) <= TOL["bf16"]["dq"], (b, h)
+                rk, rv = rk + s * ds.t() @ qf, rv + p.t() @ dof
+            assert max_rel(to_host(got[1][b, kh]), to_host(rk)) <= TOL["bf16"]["gk"], (b, kh)
+            assert max_rel(to_host(got[2][b, kh]), to_host(rv)) <= TOL["bf16"]["gv"], (b, kh)
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,C,q_start", [
     (1, 64, 8, 513, 1500),     # 256 tiles whole, 8 in shares: the last packed tile holds 96 padding rows
     (1, 8, 8, 4100, 8300),     # one head per KV head, padding within the shares' rows
