@@ -131,20 +131,30 @@ BwdPlan plan_bwd(const AttnParams& p, const SegTable& seg) {
   return best;
 }
 
+// dQ over selected columns takes the place of n shares per row tile of the dense pass: as many as keep a share's length,
+// and whole row tiles only where those are no more workgroups
+int sparse_shares(const AttnParams& p, const SegTable& runs, int n) {
+  const int tiles = (p.q_start + p.C + 127) / 128, m = std::max(1, (visited_tiles(p, runs) * n + tiles - 1) / tiles);
+  if (n == 1 || m > 1) return std::min(m, n);
+  return p.B * p.Hq * ((p.C + 127) / 128) <= n * split_plan(p.B, p.Hkv, p.G, p.C).items ? 1 : 2;
+}
+
 }  // namespace
 
 int launch_dkdv_bf16(const AttnParams& p, const SegTable& seg, hipStream_t s) {
   const bool dq = p.pending && p.pending->dq;
   if (dq) p.pending->dq = false;
-  if (seg.tile_begin[seg.n] == 0) return dq ? launch_dq_bf16_now(p, nullptr, s) : SECO_OK;
-  // (where dQ ran already, over selected columns, the sums are still divided as they would be with it)
+  const SegTable* runs = dq && p.pending->sparse ? &p.pending->runs : nullptr;
+  if (seg.tile_begin[seg.n] == 0) return dq ? launch_dq_bf16_now(p, runs, s) : SECO_OK;
+  // (over selected columns, or where dQ ran with an earlier table, the sums of gK / gV are divided as they would be with
+  // all columns: the same bits)
   const BwdPlan plan = plan_bwd(p, seg);
   if (dq && plan.dq_splits > 0) {
     AttnParams pf = p;
-    pf.n_splits = plan.dq_splits;
-    return launch_bwd_fused_bf16(pf, seg, plan.ts, plan.kv_first, s);
+    pf.n_splits = runs ? sparse_shares(p, *runs, plan.dq_splits) : plan.dq_splits;
+    return launch_bwd_fused_bf16(pf, seg, plan.ts, plan.kv_first, runs, s);
   }
-  int rc = dq ? launch_dq_bf16_now(p, nullptr, s) : SECO_OK;
+  int rc = dq ? launch_dq_bf16_now(p, runs, s) : SECO_OK;
   RowRuns none;
   none.n = 0;
   return rc ? rc : launch<false>(p, seg, plan.ts, none, s);

@@ -1,4 +1,6 @@
 // dQ of one chunk, bf16: the launch shapes of the kernel in bwd_dq_body.h.
+#include <algorithm>
+
 #include "bwd_dq_body.h"
 
 namespace seco {
@@ -46,25 +48,29 @@ __global__ __launch_bounds__(256) void dq_shares_merge_kernel(AttnParams p, int 
 
 }  // namespace
 
-// runs == nullptr: all visible cache rows, weight 1.  A small dense pass is left for the dK/dV launcher, which may be able
-// to run both at once.
+// runs == nullptr: all visible cache rows, weight 1.  The pass is left for the dK/dV launcher, which may be able to run
+// both at once.
 int launch_dq_bf16(const AttnParams& p, const SegTable* runs, hipStream_t s) {
-  if (p.pending && !runs) {
-    p.pending->dq = true;
-    return SECO_OK;
-  }
-  return launch_dq_bf16_now(p, runs, s);
+  if (!p.pending) return launch_dq_bf16_now(p, runs, s);
+  p.pending->dq = true;
+  p.pending->sparse = runs != nullptr;
+  if (runs) p.pending->runs = *runs;
+  return SECO_OK;
 }
 
 int launch_dq_bf16_now(const AttnParams& p, const SegTable* runs, hipStream_t s) {
   SegTable none = {};
   const SegTable& seg = runs ? *runs : none;
-  if (p.n_splits > 1) {
+  // (over selected columns: as many shares as those are worth, not the whole cache)
+  const int n_splits = runs && p.n_splits > 1 ? std::min(p.n_splits, split_count(split_plan(p.B, p.Hkv, p.G, p.C), visited_tiles(p, *runs) * 128)) : p.n_splits;
+  if (n_splits > 1) {
     const SplitPlan plan = split_plan(p.B, p.Hkv, p.G, p.C);
-    const int total = plan.items * p.n_splits;
-    int rc = runs ? launch_kh<2, kDivided, true>(p, seg, plan.n_mtiles, total, s)
-                  : launch_kh<2, kDivided, false>(p, seg, plan.n_mtiles, total, s);
-    return rc ? rc : launch_dq_merge(p, s);
+    AttnParams ps = p;
+    ps.n_splits = n_splits;
+    const int total = plan.items * n_splits;
+    int rc = runs ? launch_kh<2, kDivided, true>(ps, seg, plan.n_mtiles, total, s)
+                  : launch_kh<2, kDivided, false>(ps, seg, plan.n_mtiles, total, s);
+    return rc ? rc : launch_dq_merge(ps, s);
   }
   const int n_mtiles = (p.C + BM - 1) / BM;
   const int total = p.B * p.Hq * n_mtiles;

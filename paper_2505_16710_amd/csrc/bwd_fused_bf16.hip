@@ -12,6 +12,13 @@
 // What bounds it now: one workgroup's prologue, 1 - 10 iterations and epilogue, at one workgroup per CU.  With a round or more
 // of column tiles one launch pays by what rounds_in_one_launch weighs (8/8 heads, 128 rows at 16256: 112 -> 95): bound then by
 // the read-modify-write of gK and gV (with the reads of K and V 2.5 KiB per cache row and KV head, at 3.6 TB/s).
+// dQ over selected columns (spaco_chunk_attn_bwd_sparse_dq) joins in wherever the dense pass would, in fewer shares; us, two launches
+// of which dQ's was divided as for the whole cache -> one (Hq/Hkv, rows, chunks selected of all):
+//   16/8 x 2  29, 2 of 64  24.5 -> 14.8     16/2 188, 8 of 35  51 -> 38
+//   32/8  32, 2 of 64      28.1 -> 15.8     32/8 128, 4 of 32  41 -> 23
+//   32/8 256, 4 of 16      51 -> 38         8/8   64, 8 of 64  25.4 -> 15.2
+#include <type_traits>
+
 #include "bwd_dkdv_body.h"
 #include "bwd_dq_body.h"
 #include "merge_body.h"
@@ -25,8 +32,10 @@ constexpr int kSmem = Cfg::kSmemBytes > kDqSmem ? Cfg::kSmemBytes : kDqSmem;
 static_assert(Cfg::kThreads == 512, "both passes in workgroups of 8 wavefronts");
 
 // The first first_grid workgroups are those of dK/dV (kv_first: the pass with the longer workgroups) or of dQ; both numbers are rounded up to whole XCD rounds.
-template <bool SPLIT>
-__global__ __launch_bounds__(512, 2) void bwd_fused_bf16_kernel(AttnParams p, SegTable seg, TailSplit ts, int n_mtiles,
+// RUNS: nothing, or the SegTable of dQ over selected columns
+struct AllColumns {};
+template <bool SPLIT, typename RUNS>
+__global__ __launch_bounds__(512, 2) void bwd_fused_bf16_kernel(AttnParams p, SegTable seg, TailSplit ts, RUNS runs, int n_mtiles,
                                                                 int kv_total, int dq_total, int first_grid, int kv_first) {
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];
   lds_char* smem = (lds_char*)smem_raw;
@@ -41,7 +50,11 @@ __global__ __launch_bounds__(512, 2) void bwd_fused_bf16_kernel(AttnParams p, Se
     else
       dkdv_bf16_body<kNcb, SECO_DKDV_RB, false, 1, true>(p, seg, ts, none, item, smem);
   } else {
-    dq_bf16_body<2, SPLIT ? kDivided : kWholeTiles, false, true>(p, seg, n_mtiles, item, smem);
+    constexpr int kSplit = SPLIT ? kDivided : kWholeTiles;
+    if constexpr (std::is_same_v<RUNS, SegTable>)
+      dq_bf16_body<2, kSplit, true, true>(p, runs, n_mtiles, item, smem);
+    else
+      dq_bf16_body<2, kSplit, false, true>(p, seg, n_mtiles, item, smem);
   }
 }
 
@@ -72,29 +85,33 @@ int launch_merges(const AttnParams& p, const SegTable& seg, const TailSplit& ts,
   return launch_status();
 }
 
-template <bool SPLIT>
-int launch(const AttnParams& p, const SegTable& seg, const TailSplit& ts, int n_mtiles, int kv_total, int dq_total, bool kv_first,
-           hipStream_t s) {
-  auto kern = bwd_fused_bf16_kernel<SPLIT>;
+template <bool SPLIT, typename RUNS>
+int launch(const AttnParams& p, const SegTable& seg, const TailSplit& ts, const RUNS& runs, int n_mtiles, int kv_total, int dq_total,
+           bool kv_first, hipStream_t s) {
+  auto kern = bwd_fused_bf16_kernel<SPLIT, RUNS>;
   static std::atomic<uint64_t> ready{0};
   if (!allow_lds(ready, reinterpret_cast<const void*>(kern), kSmem)) return SECO_ERR_LAUNCH;
   const int first = xcd_grid(kv_first ? kv_total : dq_total), second = xcd_grid(kv_first ? dq_total : kv_total);
   {
     ProfScope prof(kKernelBwd, s);
-    hipLaunchKernelGGL(kern, dim3(first + second), dim3(512), kSmem, s, p, seg, ts, n_mtiles, kv_total, dq_total, first,
-                       kv_first ? 1 : 0);
+    hipLaunchKernelGGL(kern, dim3(first + second), dim3(512), kSmem, s, p, seg, ts, runs, n_mtiles, kv_total, dq_total,
+                       first, kv_first ? 1 : 0);
   }
   return launch_status();
 }
 
 }  // namespace
 
-int launch_bwd_fused_bf16(const AttnParams& p, const SegTable& seg, const TailSplit& ts, bool kv_first, hipStream_t s) {
+int launch_bwd_fused_bf16(const AttnParams& p, const SegTable& seg, const TailSplit& ts, bool kv_first, const SegTable* runs, hipStream_t s) {
   const int kv_total = p.B * p.Hkv * (seg.tile_begin[seg.n] - ts.plan.n_tiles + ts.plan.n_entries);
   const SplitPlan plan = split_plan(p.B, p.Hkv, p.G, p.C);
   const int mtiles = (p.C + BM - 1) / BM;
-  const int rc = p.n_splits == 1 ? launch<false>(p, seg, ts, mtiles, kv_total, p.B * p.Hq * mtiles, kv_first, s)
-                                 : launch<true>(p, seg, ts, plan.n_mtiles, kv_total, plan.items * p.n_splits, kv_first, s);
+  const AllColumns all;
+  const int whole = p.B * p.Hq * mtiles, divided = plan.items * p.n_splits;
+  const int rc = p.n_splits == 1 ? (runs ? launch<false>(p, seg, ts, *runs, mtiles, kv_total, whole, kv_first, s)
+                                         : launch<false>(p, seg, ts, all, mtiles, kv_total, whole, kv_first, s))
+                                 : (runs ? launch<true>(p, seg, ts, *runs, plan.n_mtiles, kv_total, divided, kv_first, s)
+                                         : launch<true>(p, seg, ts, all, plan.n_mtiles, kv_total, divided, kv_first, s));
   return rc ? rc : launch_merges(p, seg, ts, s);
 }
 

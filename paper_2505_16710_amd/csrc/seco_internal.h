@@ -53,7 +53,8 @@ struct SegTable {
 // What launch_dq_f32 / launch_dq_bf16 leave for the dK/dV launcher that follows
 struct PendingDq {
   bool dq = false;
-  SegTable runs;   // fp32 only
+  bool sparse = false;   // bf16: dQ visits `runs` only (fp32 always has them)
+  SegTable runs;
 };
 
 // Runs of query rows of the dK/dV pass in the transposed order: rows [begin, end) relative to the call's first
@@ -143,6 +144,15 @@ inline int fwd_share_slots(int B, int Hq, int Hkv, int C) {
   if (units > cus || (int64_t)units * n_mtiles <= cus || (int64_t)B * Hq * ((C + 127) / 128) >= 2 * cus) return 0;
   const int n = units * (n_mtiles - cus / units) * kMaxRowShares;
   return n < 2 * cus ? n : 2 * cus;
+}
+// Tiles of 128 cache rows that dQ over a table of runs visits (the chunk's last rows; no run starts behind them)
+inline int visited_tiles(const AttnParams& p, const SegTable& runs) {
+  int n = 0;
+  for (int i = 0; i < runs.n; ++i) {
+    const int end = runs.col_end[i] < p.q_start + p.C ? runs.col_end[i] : p.q_start + p.C;
+    n += (end - runs.col_begin[i] + 127) / 128;
+  }
+  return n;
 }
 int launch_fwd_merge(const AttnParams& p, hipStream_t s);   // O, LSE from the partials
 int launch_dq_merge(const AttnParams& p, hipStream_t s);    // dQ = scale * sum of the partials, in split order
@@ -308,8 +318,8 @@ int launch_fwd_small_bf16(AttnParams p, int max_splits, hipStream_t s);
 // a positive weight (tile_begin is not used)
 int launch_dq_bf16(const AttnParams& p, const SegTable* dq_runs, hipStream_t s);
 int launch_dkdv_bf16(const AttnParams& p, const SegTable& seg, hipStream_t s);
-// dQ (p.n_splits workgroups per row tile) and dK/dV in one launch
-int launch_bwd_fused_bf16(const AttnParams& p, const SegTable& seg, const TailSplit& ts, bool kv_first, hipStream_t s);
+// dQ (p.n_splits workgroups per row tile; runs as for launch_dq_bf16) and dK/dV in one launch
+int launch_bwd_fused_bf16(const AttnParams& p, const SegTable& seg, const TailSplit& ts, bool kv_first, const SegTable* runs, hipStream_t s);
 int launch_dq_bf16_now(const AttnParams& p, const SegTable* dq_runs, hipStream_t s);
 // the same with the query rows taken from runs (p.C: number of rows that may be addressed from p.q / p.d_o)
 int launch_dkdv_rows_bf16(const AttnParams& p, const SegTable& seg, const RowRuns& rr, hipStream_t s);

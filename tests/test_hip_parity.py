@@ -228,6 +228,37 @@ def test_bf16_backward_of_several_rounds_in_one_launch(B, Hq, Hkv, C, q_start, a
             assert max_rel(to_host(got[2][b, kh]), to_host(rv)) <= TOL["bf16"]["gv"], (b, kh)
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,C,k,picked", [
+    (1, 8, 2, 40, 30, [3, 29]),              # two tiles: whole row tiles, no merge of dQ
+    (1, 32, 8, 33, 40, [0, 7, 8, 20, 39]),   # runs of one and two chunks that end inside a tile
+    (2, 8, 1, 129, 9, [1, 2, 3, 6, 8]),      # row tiles of one row
+    (1, 8, 8, 64, 90, [5, 50, 89]),          # column tiles for more than one round behind dQ's
+    (1, 16, 2, 300, 30, [0, 28, 29]),        # two launches
+])
+def test_bf16_dq_over_selected_columns_with_dkdv_in_one_launch(B, Hq, Hkv, C, k, picked):
+    """dQ against fp32 on the device; gK and gV have the bits of the call whose dQ sees all columns."""
+    N, s, G, j = k * C, 1 / np.sqrt(128), Hq // Hkv, (k - 1) * C
+    g = torch.Generator(device=DEV).manual_seed(66)
+    rand = lambda *shape: torch.randn(*shape, device=DEV, generator=g).to(torch.bfloat16)
+    q, do, kc, vc = rand(B, Hq, C, 128), rand(B, Hq, C, 128), rand(B, Hkv, N, 128), rand(B, Hkv, N, 128)
+    o, lse = seco.seco_chunk_attn_fwd(q, kc, vc, j, s)
+    wq = [2.0 if i in picked else 0.0 for i in range(k - 1)] + [1.0]
+    def run(dq_weight):
+        gk, gv = (torch.zeros(B, Hkv, N, 128, device=DEV) for _ in range(2))
+        return seco.spaco_chunk_attn_bwd(q, kc, vc, o, lse, do, gk, gv, j, s, [1.0] * k, C, dq_weight=dq_weight), gk, gv
+    got, again, dense = run(wq), run(wq), run(None)
+    assert all(torch.equal(a, b) for a, b in zip(got, again))
+    assert torch.equal(got[1], dense[1]) and torch.equal(got[2], dense[2])
+    rows = torch.arange(C, device=DEV)[:, None] + j
+    col_w = torch.tensor(wq, device=DEV).repeat_interleave(C)
+    for b in range(B):
+        for h in range(Hq):
+            kf, vf, qf, dof, of = (t.float() for t in (kc[b, h // G], vc[b, h // G], q[b, h], do[b, h], o[b, h]))
+            z = (qf @ kf.t() * s).masked_fill(torch.arange(N, device=DEV)[None, :] > rows, float("-inf"))
+            ds = torch.exp(z - lse[b, h][:, None]) * (dof @ vf.t() - (dof * of).sum(-1, keepdim=True))
+            assert max_rel(to_host(got[0][b, h]), to_host(s * (ds * col_w) @ kf)) <= TOL["bf16"]["dq"], (b, h)
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,C,q_start", [
     (1, 64, 8, 513, 1500),     # 256 tiles whole, 8 in shares: the last packed tile holds 96 padding rows
     (1, 8, 8, 4100, 8300),     # one head per KV head, padding within the shares' rows
