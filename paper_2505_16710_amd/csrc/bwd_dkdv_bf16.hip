@@ -76,6 +76,105 @@ int rounds_in_one_launch(int n_kv, int iters, int items, int tiles, int max_spli
   return 1.03f * one < apart ? n : 0;
 }
 
+// When the last of a row of workgroups ends on `places` that take them in order: the places by the time they are free at, those
+// within a quarter of a microsecond as one.
+class Schedule {
+ public:
+  static constexpr int kMost = 64;
+  explicit Schedule(int places) : n_(1) { at_[0] = 0.f, of_[0] = places; }
+  void run(float time, int count) {
+    while (count > 0) {
+      const int k = std::min(of_[0], count);
+      const float t = at_[0] + time;
+      count -= k;
+      if ((of_[0] -= k) == 0) {
+        --n_;
+        std::copy(at_ + 1, at_ + 1 + n_, at_);
+        std::copy(of_ + 1, of_ + 1 + n_, of_);
+      }
+      int i = n_;
+      while (i > 0 && at_[i - 1] > t + 0.25f) --i;
+      if (i > 0 && at_[i - 1] >= t - 0.25f) {
+        of_[i - 1] += k;
+      } else {
+        std::copy_backward(at_ + i, at_ + n_, at_ + n_ + 1);
+        std::copy_backward(of_ + i, of_ + n_, of_ + n_ + 1);
+        at_[i] = t, of_[i] = k;
+        ++n_;
+      }
+    }
+  }
+  float end() const { return at_[n_ - 1]; }
+
+ private:
+  float at_[kMost + 1];
+  int of_[kMost + 1], n_;
+};
+
+// Fewer column tiles than a round, but more workgroups in all than fit at once: the plan of sharing out the column tiles with
+// which both passes in one launch, dK/dV first, dQ in whole row tiles behind it, are expected to end before the two would
+// one after the other; false: none.  Both are laid out workgroup by workgroup on the compute units of an XCD (whole units
+// of a batch and KV head each, in the order of the items).  The times, in microseconds, are fitted to 74 shapes of 130 - 3200
+// rows (3 - 4 % off); one launch where it comes out 5 % ahead, and below 200 us, from where gains and errors were both about 3 %.
+// Of 400 other random shapes with less than a round of column tiles it takes 76, 1.13 times as fast, none more than 1 %
+// slower; two -> one, us:
+//   32/8  745 at 0: 50.9 -> 39.1   873 at 0: 55.9 -> 43.2   1482 at 445: 134.5 -> 131   16/8  1174 at 0: 58 -> 45
+//   8/8  2156 at 5: 84.9 -> 63.9   x 2  1011 at 96: 58.6 -> 40.9
+bool one_launch_behind_column_tiles(const AttnParams& p, const IterRuns& runs, int n_ctiles, int slots, const SharePlan& apart_plan,
+                                    SharePlan& one_plan) {
+  const int n_units = p.B * p.Hkv, places = device_cus() / 8, mtiles = (p.C + 127) / 128, heads = p.B * p.Hq / 8;
+  const int row_wgs = p.B * p.Hq * mtiles;
+  if (n_units % 8 != 0 || places > Schedule::kMost || row_wgs >= 2 * device_cus()) return false;
+  if (row_wgs > device_cus() && p.q_start >= 2 * p.C) return false;      // (row_shares divides dQ's second round)
+  auto column_tiles = [&](Schedule& sc, const SharePlan& plan, float wg, float iter) {
+    for (int u = 0; u < n_units / 8; ++u) {
+      int tile = 0, i = 0;
+      for (int r = 0; r < runs.n; ++r)
+        for (int c = 0; c < runs.count[r]; ++c, ++tile) {
+          const bool listed = tile >= n_ctiles - plan.n_tiles;
+          const int k = listed ? plan.first[i + 1] - plan.first[i] : 1;
+          if (listed) ++i;
+          sc.run(wg + iter * runs.iters[r] / k, k);
+        }
+    }
+  };
+  auto row_tiles = [&](Schedule& sc, float wg, float tile) {
+    for (int mt = mtiles; mt > 0; --mt) sc.run(wg + tile * ((p.q_start + std::min(mt * 128, p.C) + 127) / 128), heads);
+  };
+  auto merge = [&](const SharePlan& plan, float each) { return plan.n_shared > 0 ? 4.f + each * plan.first[plan.n_shared] * n_units : 0.f; };
+  Schedule kv(places);
+  column_tiles(kv, apart_plan, 14.9f, 1.7f);
+  float apart = kv.end() + merge(apart_plan, 0.03f) - 1.6f;
+  if (p.n_splits > 1) {
+    const int wgs = split_plan(p.B, p.Hkv, p.G, p.C).items * p.n_splits, tiles = (p.q_start + p.C + 127) / 128;
+    apart += (wgs + device_cus() - 1) / device_cus() * (7.1f + 1.7f * ((tiles + p.n_splits - 1) / p.n_splits)) + 4.f + 0.02f * wgs;
+  } else {
+    Schedule dq(places);
+    row_tiles(dq, 7.1f, 1.7f);
+    apart += dq.end();
+  }
+  if (apart > 200.f) return false;
+  float best = apart / 1.05f;
+  int last = -1;
+  bool found = false;
+  for (int cus : {96, 160, 256}) {
+    const ShareChoice c = choose_shares(runs, n_ctiles, n_units, cus * device_cus() / 256, slots, 1, false, 8.5f, 1.8f);
+    if (c.time < 0.f || c.per == last) continue;
+    last = c.per;
+    const SharePlan plan = make_shares(runs, n_ctiles, c.per);
+    Schedule both(places);
+    column_tiles(both, plan, 15.7f, 1.8f);
+    row_tiles(both, 8.2f, 2.4f);
+    const float t = both.end() + merge(plan, 0.024f) - 4.7f;
+    if (t < best) {
+      best = t;
+      one_plan = plan;
+      found = true;
+    }
+  }
+  return found;
+}
+
 // With column tiles for less than a round, one launch is taken when all workgroups of both passes fit the chip at one per
 // CU and the longer pass, with the extra work, is expected to end before the two would one after the other: with more
 // workgroups than CUs the two halves of the grid would queue behind each other on some CUs (16/2 heads, chunk 704 at 5632:
@@ -94,12 +193,13 @@ BwdPlan plan_bwd(const AttnParams& p, const SegTable& seg) {
   float kv_alone = 0.f;
   best.ts.plan = share_plan(runs, n_units, n_ctiles, p.G, p.C, slots_in(p.tail_bytes), kv_alone);
   const SplitPlan sp = split_plan(p.B, p.Hkv, p.G, p.C);
-  if (!p.pending || sp.items >= cus) return best;
+  if (!p.pending) return best;
   const int tiles = (p.q_start + p.C + 127) / 128;
   const size_t dq_bytes = (size_t)p.B * p.Hq * p.C * 128 * sizeof(float);
   auto dq_wgs = [&](int n) { return n > 1 ? sp.items * n : p.B * p.Hq * ((p.C + 127) / 128); };
   auto dq_part = [&](int n) { return n > 1 ? (n * dq_bytes + 255) / 256 * 256 : (size_t)0; };
   if ((int64_t)n_units * n_ctiles >= cus) {
+    if (sp.items >= cus) return best;
     const int n = rounds_in_one_launch(n_units * n_ctiles, runs.iters[0], sp.items, tiles, p.n_splits, dq_wgs);
     if (n > 0 && dq_part(n) <= p.tail_bytes) {
       best.dq_splits = n;
@@ -127,7 +227,12 @@ BwdPlan plan_bwd(const AttnParams& p, const SegTable& seg) {
       per = c.per;
     }
   }
-  if (best.dq_splits > 0) best.ts.plan = make_shares(runs, n_ctiles, per);
+  if (best.dq_splits > 0) {
+    best.ts.plan = make_shares(runs, n_ctiles, per);
+  } else if (SharePlan plan; n_ctiles <= runs.n_tiles && one_launch_behind_column_tiles(p, runs, n_ctiles, slots_in(p.tail_bytes), best.ts.plan, plan)) {
+    best.dq_splits = 1;
+    best.ts.plan = plan;
+  }
   return best;
 }
 

@@ -189,10 +189,14 @@ def test_bf16_backward_of_a_short_call_in_one_launch(B, Hq, Hkv, N, C, sel):
     (1, 8, 8, 64, 6400, False),
     (1, 32, 8, 128, 16256, True),     # not taken: four rounds of eight iterations
     (1, 16, 2, 60, 16300, True),      # nor one full round of eight
+    (1, 32, 8, 745, 0, False),        # less than a round of column tiles, shared out, whole row tiles behind them
+    (2, 8, 8, 1040, 193, False),      # one head per KV head: none is shared out
+    (1, 16, 8, 1421, 247, False),
+    (1, 32, 8, 1838, 1322, True),     # longer than where one launch is looked for
 ])
 def test_bf16_backward_of_several_rounds_in_one_launch(B, Hq, Hkv, C, q_start, apart):
-    """dQ's workgroups in front of a round or more of column tiles, and what the rule leaves in two launches: dQ and the
-    gradients added to what the buffers hold, against fp32 on the device; reruns and unit weights give the same bits."""
+    """dQ's workgroups in front of a round or more of column tiles, or behind less than a round, and what the rules leave in
+    two launches: dQ and the gradients added to what the buffers hold, against fp32 on the device; reruns and unit weights give the same bits."""
     N, s, G = q_start + C, 1 / np.sqrt(128), Hq // Hkv
     g = torch.Generator(device=DEV).manual_seed(65)
     rand = lambda *shape: torch.randn(*shape, device=DEV, generator=g).to(torch.bfloat16)
