@@ -7,9 +7,9 @@
 // library product through the framework took 17 - 19 us of host time, twice its kernel; a launch here takes 3.  Above
 // about 10 GMAC the framework's kernels are faster, and the training step takes those (worth() in chunk_step_ext.cpp).
 //
-// A workgroup (4 wavefronts, 2 x 2, or two such groups that take the steps in turn) owns a BM x BN tile of C and walks
-// the contraction in steps of 64 through a ring of kStages LDS slots filled by direct global -> LDS copies, kStages - 1
-// steps ahead, with one barrier per step.  An operand whose
+// A workgroup (2 x 2 or 2 x 4 wavefronts, or two groups of the former that take the steps in turn) owns a BM x BN tile of C
+// and walks the contraction in steps of 64 through a ring of kStages LDS slots filled by direct global -> LDS copies,
+// kStages - 1 steps ahead, with one barrier per step.  An operand whose
 // contraction runs along its rows in memory ("KC") is staged as rows of 64 contraction elements, one whose rows are
 // contracted ("KR") as panels of 64 of its columns; either way an LDS row is 128 bytes whose eight 16-byte chunks
 // are XOR-ed with a function of the row such that row reads (ds_read_b128, 16 rows) and transpose reads
@@ -103,13 +103,18 @@ template <bool KC> struct Frag {
   }
 };
 
-// eight sums to C, from element `at` on
-template <int EPI, typename F4>
-__device__ __forceinline__ void emit(const GemmArgs& g, int64_t at, const F4& lo, const F4& hi) {
-  const float f[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-  bf16x8 out, old, act;
+// what eight sums from element `at` of C on meet there: C itself, or u
+template <int EPI> __device__ __forceinline__ bf16x8 met(const GemmArgs& g, int64_t at) {
+  bf16x8 old = {};
   if constexpr (EPI == kAdd) old = *reinterpret_cast<const bf16x8*>(g.c + at);
   if constexpr (EPI == kSiluBwd) old = *reinterpret_cast<const bf16x8*>(g.c2 + at);
+  return old;
+}
+// eight sums to C, from element `at` on
+template <int EPI, typename F4>
+__device__ __forceinline__ void emit(const GemmArgs& g, int64_t at, const F4& lo, const F4& hi, const bf16x8& old) {
+  const float f[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+  bf16x8 out, act;
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     if constexpr (EPI == kAdd) {
@@ -129,24 +134,24 @@ __device__ __forceinline__ void emit(const GemmArgs& g, int64_t at, const F4& lo
   if constexpr (EPI == kSilu) *reinterpret_cast<bf16x8*>(g.c2 + at) = act;
 }
 
-// KH groups of 4 wavefronts, each with a ring of kStages slots; group kh takes the steps kh, kh + KH, ...
-template <int BM, int BN, int KH, int kStages, bool AKC, bool BKC, int EPI>
-__global__ __launch_bounds__(256 * KH, 2) void gemm_kernel(GemmArgs g, int total) {
-  constexpr int kSlot = (BM + BN) * kRow, MB = BM / 64, NB = BN / 64;
-  constexpr int kPerWave = BM / 32 + BN / 32;            // copies per wavefront and step
+// KH groups of 2 x WN wavefronts, each with a ring of kStages slots; group kh takes the steps kh, kh + KH, ...
+template <int BM, int BN, int KH, int kStages, int WN, bool AKC, bool BKC, int EPI>
+__global__ __launch_bounds__(128 * WN * KH, 2) void gemm_kernel(GemmArgs g, int total) {
+  constexpr int kSlot = (BM + BN) * kRow, GW = 2 * WN, MB = BM / 64, NB = BN / (32 * WN);
+  constexpr int kPerWave = BM / (8 * GW) + BN / (8 * GW);            // copies per wavefront and step
   constexpr int kRing = kStages * kSlot;
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];
   lds_char* smem_all = (lds_char*)smem_raw;
   const int item = xcd_item(blockIdx.x, total);          // neighbours share the columns of B (a weight matrix in two of the forms)
   if (item < 0) return;
   const int tid = threadIdx.x, lane = tid & 63, wave_all = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wave = wave_all & 3, kh = KH == 1 ? 0 : wave_all >> 2;
+  const int wave = wave_all % GW, kh = KH == 1 ? 0 : wave_all / GW;
   lds_char* smem = smem_all + kh * kRing;
   const int tn = item / g.tiles_m, tm = item - tn * g.tiles_m;
   const int m0 = tm * BM, n0 = tn * BN;
 
-  Stage<AKC, BM> sa;
-  Stage<BKC, BN> sb;
+  Stage<AKC, BM, GW> sa;
+  Stage<BKC, BN, GW> sb;
   sa.init(m0, g.M, g.lda, wave, lane);
   sb.init(n0, g.N, g.ldb, wave, lane);
   const int64_t step_a = AKC ? kStep * 2 : (int64_t)kStep * g.lda * 2, step_b = BKC ? kStep * 2 : (int64_t)kStep * g.ldb * 2;
@@ -167,9 +172,9 @@ __global__ __launch_bounds__(256 * KH, 2) void gemm_kernel(GemmArgs g, int total
   Frag<AKC> fa[MB];
   Frag<BKC> fb[NB];
 #pragma unroll
-  for (int i = 0; i < MB; ++i) fa[i].init((wave >> 1) * MB + i, lane);
+  for (int i = 0; i < MB; ++i) fa[i].init(wave / WN * MB + i, lane);
 #pragma unroll
-  for (int i = 0; i < NB; ++i) fb[i].init((wave & 1) * NB + i, lane);
+  for (int i = 0; i < NB; ++i) fb[i].init(wave % WN * NB + i, lane);
   f32x16 acc[MB][NB];
 #pragma unroll
   for (int i = 0; i < MB; ++i)
@@ -195,17 +200,38 @@ __global__ __launch_bounds__(256 * KH, 2) void gemm_kernel(GemmArgs g, int total
     }
   };
 
+  // where this thread's part of the tile leaves, and what it meets there: requested behind the last wait for operands, in
+  // front of the last step's products
+  constexpr int kPerRow = BN / 8, kRows = 64 * GW * KH / kPerRow;
+  const int col = n0 + (tid % kPerRow) * 8;
+  bf16x8 old[BM / kRows];
+  auto request_old = [&]() {
+#pragma unroll
+    for (int i = 0; i < BM / kRows; ++i) {
+      const int row = min(m0 + i * kRows + tid / kPerRow, g.M - 1);
+      old[i] = met<EPI>(g, (int64_t)row * g.ldc + min(col, g.N - 8));
+    }
+  };
   int slot = 0;
   const int n_turns = (n_full + KH - 1) / KH;            // the same for all groups: they share the barriers
-  for (int it = 0; it < n_turns; ++it) {
+  auto wait = [&](int it) {
     // step `it` has landed when at most the copies of the kStages - 2 steps behind it are outstanding
     if (it + kStages - 2 < n_steps)
       asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"((kStages - 2) * kPerWave) : "memory");
     else
       asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" : : : "memory");
+  };
+  constexpr bool kMeets = EPI == kAdd || (EPI == kSiluBwd && BM == 128);
+  for (int it = 0; it < n_turns - (kMeets ? 1 : 0); ++it) {
+    wait(it);
     if (it + kStages - 1 < n_steps) copy(slot == 0 ? kStages - 1 : slot - 1);   // the slot every wavefront has just left
     if (KH == 1 || it < n_steps) multiply(slot);
     slot = slot + 1 == kStages ? 0 : slot + 1;
+  }
+  if constexpr (kMeets) {
+    if (n_turns > 0) wait(n_turns - 1);
+    request_old();
+    if (n_turns > 0 && (KH == 1 || n_turns - 1 < n_steps)) multiply(slot);
   }
   if constexpr (!AKC && !BKC) {
     if (const int rest = g.K - n_full * kStep; rest > 0) {
@@ -227,11 +253,9 @@ __global__ __launch_bounds__(256 * KH, 2) void gemm_kernel(GemmArgs g, int total
     for (int j = 0; j < NB; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r)
-        *reinterpret_cast<SECO_LDS float*>(smem + (((wave >> 1) * MB + i) * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * kTurnRow +
-                                           (((wave & 1) * NB + j) * 32 + (lane & 31)) * 4) = acc[i][j][r];
+        *reinterpret_cast<SECO_LDS float*>(smem + ((wave / WN * MB + i) * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * kTurnRow +
+                                           ((wave % WN * NB + j) * 32 + (lane & 31)) * 4) = acc[i][j][r];
   __syncthreads();
-  constexpr int kPerRow = BN / 8, kRows = 256 * KH / kPerRow;
-  const int col = n0 + (tid % kPerRow) * 8;
   if (col >= g.N) return;
 #pragma unroll
   for (int i = 0; i < BM / kRows; ++i) {
@@ -243,7 +267,8 @@ __global__ __launch_bounds__(256 * KH, 2) void gemm_kernel(GemmArgs g, int total
       lo += *reinterpret_cast<SECO_LDS f32x4*>(src + kRing);
       hi += *reinterpret_cast<SECO_LDS f32x4*>(src + kRing + 16);
     }
-    emit<EPI>(g, (int64_t)row * g.ldc + col, lo, hi);
+    const int64_t at = (int64_t)row * g.ldc + col;
+    emit<EPI>(g, at, lo, hi, kMeets ? old[i] : met<EPI>(g, at));
   }
 }
 
@@ -324,17 +349,18 @@ __global__ __launch_bounds__(64 * NW, 2) void gemm_k_kernel(GemmArgs g, int tota
     lo += *reinterpret_cast<SECO_LDS f32x4*>(src);
     hi += *reinterpret_cast<SECO_LDS f32x4*>(src + 16);
   }
-  emit<EPI>(g, (int64_t)(m0 + lr) * g.ldc + col, lo, hi);
+  const int64_t at = (int64_t)(m0 + lr) * g.ldc + col;
+  emit<EPI>(g, at, lo, hi, met<EPI>(g, at));
 }
 
-template <int BM, int BN, int KH, int ST, bool AKC, bool BKC, int EPI> int launch(GemmArgs g, hipStream_t s) {
+template <int BM, int BN, int KH, int ST, int WN, bool AKC, bool BKC, int EPI> int launch(GemmArgs g, hipStream_t s) {
   constexpr int smem = KH * ST * (BM + BN) * kRow;
-  auto kern = gemm_kernel<BM, BN, KH, ST, AKC, BKC, EPI>;
+  auto kern = gemm_kernel<BM, BN, KH, ST, WN, AKC, BKC, EPI>;
   static std::atomic<uint64_t> ready{0};
   if (!allow_lds(ready, reinterpret_cast<const void*>(kern), smem)) return SECO_ERR_LAUNCH;
   g.tiles_m = (g.M + BM - 1) / BM;
   const int total = g.tiles_m * ((g.N + BN - 1) / BN);
-  hipLaunchKernelGGL(kern, dim3(xcd_grid(total)), dim3(256 * KH), smem, s, g, total);
+  hipLaunchKernelGGL(kern, dim3(xcd_grid(total)), dim3(128 * WN * KH), smem, s, g, total);
   return launch_status();
 }
 
@@ -357,19 +383,27 @@ template <int NW, bool AKC, bool BKC, int EPI> int launch_k(GemmArgs g, hipStrea
 //    deliver: 196 MB in 8.5 us);
 //  - over 1.25 128 x 128 tiles per CU: those, four wavefronts and two slots, so that two workgroups share a CU
 //    (2048 x 4096 x 1024: 25; 31 with eight wavefronts, 35 with 64 x 64 tiles);
-//  - from 0.55 per CU on: 128 x 128, eight wavefronts in two groups (1024 x 4096 x 1024: 16.5 against 17.3);
+//  - from 0.55 per CU on: 128 x 128, eight wavefronts side by side, three slots (added to a 4096 x 1024 product over 512 rows:
+//    9.5; in two groups with two slots, which turn and add twice the sums through LDS, 10.5, and 11.4 while what the sums
+//    are added to was only requested when they were there);
 //  - 64 x 64 tiles that fit one round: those, two groups, three slots (512 x 1024 x 4096: 14.6; 18.5 with one group);
-//  - more of them: 128 x 64 for a long contraction (2048 x 1024 x 4096: 25 against 30), else 64 x 64 with two slots, two
-//    workgroups per CU (512 x 4096 x 1024: 9.9; 14.0 with 128 x 128).
+//  - more of them: 128 x 64 for a long contraction of rows of A (2048 x 1024 x 4096: 25 against 27 with 64 x 128); else, where
+//    the rows of B are contracted, 64 x 128, eight wavefronts side by side, three slots: a third less from L2 than 64 x 64 with two
+//    slots and two workgroups per CU (1024 x 1536 over 512 rows: 5.7 against 6.3, 512 x 4096 x 1024 with the SiLU: 9.9 / 10.4;
+//    2048 x 1024 over 2048: 13.7 / 14.9 with 128 x 64); else those (512 x 4096 x 1024 back through the SiLU: 9.5; 10.2 with 64 x 128).
 template <bool AKC, bool BKC, int EPI> int pick(const GemmArgs& g, hipStream_t s) {
   const int64_t m64 = (g.M + 63) / 64, n64 = (g.N + 63) / 64, big = ((m64 + 1) / 2) * ((n64 + 1) / 2), cus = device_cus();
   if constexpr (AKC)
     if ((g.M + 31) / 32 * n64 <= cus) return launch_k<8, AKC, BKC, EPI>(g, s);
-  if (4 * big > 5 * cus) return launch<128, 128, 1, 2, AKC, BKC, EPI>(g, s);
-  if (20 * big >= 11 * cus) return launch<128, 128, 2, 2, AKC, BKC, EPI>(g, s);
-  if (m64 * n64 <= cus) return launch<64, 64, 2, 3, AKC, BKC, EPI>(g, s);
-  if (g.K >= 2048) return launch<128, 64, 2, 3, AKC, BKC, EPI>(g, s);
-  return launch<64, 64, 2, 2, AKC, BKC, EPI>(g, s);
+  if (4 * big > 5 * cus) return launch<128, 128, 1, 2, 2, AKC, BKC, EPI>(g, s);
+  if (20 * big >= 11 * cus) return launch<128, 128, 1, 3, 4, AKC, BKC, EPI>(g, s);
+  if (m64 * n64 <= cus) return launch<64, 64, 2, 3, 2, AKC, BKC, EPI>(g, s);
+  if constexpr (AKC)
+    if (g.K >= 2048) return launch<128, 64, 2, 3, 2, AKC, BKC, EPI>(g, s);
+  if constexpr (!BKC)
+    return launch<64, 128, 1, 3, 4, AKC, BKC, EPI>(g, s);
+  else
+    return launch<64, 64, 2, 2, 2, AKC, BKC, EPI>(g, s);
 }
 
 }  // namespace

@@ -25,6 +25,9 @@ STORE, ADD, SILU, SILU_BWD = 0, 1, 2, 3
     (NT, STORE, 1500, 1032, 2112),         # 128 x 64 tiles
     (TN, ADD, 2040, 2056, 200),            # 128 x 128 tiles, two groups, a remainder of the contraction
     (NN, SILU, 2050, 4104, 128),           # 128 x 128 tiles, one group, two workgroups per CU
+    (NN, SILU, 500, 4000, 192), (TN, ADD, 1000, 1544, 200), (TN, STORE, 1000, 1544, 128),   # 64 x 128 tiles
+    (NT, SILU_BWD, 1030, 4104, 128),       # 128 x 128 tiles, side by side: u requested early
+    (TN, ADD, 2040, 2056, 40), (TN, ADD, 2040, 2056, 64),   # ... no whole step, one
 ])
 def test_gemm_forms_and_epilogues(form, epi, M, N, K):
     lib = seco.load_library()
