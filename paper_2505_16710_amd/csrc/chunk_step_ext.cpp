@@ -142,6 +142,17 @@ struct Step {
     }
   }
 
+  // both gradients of y = x w: grad[K, n] += x[M, K]^T d_y[M, n], d_x[M, K] = d_y w^T (u non-NULL: times silu'(u))
+  void grads(Param& w, void* x, void* dx, void* dy, int64_t M, void* u = nullptr) {
+    const int64_t K = w.w.size(0), n = w.w.size(1);
+    if (w.wanted && w.grad.defined() && own(w, DEC_GEMM_TN, K, n, M, K, n, n) && own(w, DEC_GEMM_NT, M, K, n, n, n, K)) {
+      check(lib.dec_gemm_grads(dy, ptr(w.w), dx, u, x, ptr(w.grad), M, K, n, s), "dec_gemm_grads");
+    } else {
+      add(w, x, dy, M);
+      mm_bwd(dx, dy, w, M, u);
+    }
+  }
+
   // ---- attention
   seco_desc desc(int64_t C, int64_t q_start, const Layer& l) const {
     seco_desc d;
@@ -367,13 +378,12 @@ struct Step {
     };
     const Saved fin = std::move(saved.back());
     saved.pop_back();
-    add(head, fin.h1, d_logits, R);
     if (tail == dtype) {
-      mm_bwd(dh, d_logits, head, R);
+      grads(head, fin.h1, dh, d_logits, R);
       norm_bwd(fin.x1, norm_f, fin.r1, part_f, true);
     } else {
       const Tensor dh_f = at::empty_like(fin.keep_o), dx_f = at::empty_like(fin.keep_o);
-      mm_bwd(ptr(dh_f), d_logits, head, R);
+      grads(head, fin.h1, ptr(dh_f), d_logits, R);
       check(lib.dec_rmsnorm_bwd(tail, fin.x1, ptr(norm_f.w), fin.r1, ptr(dh_f), nullptr, ptr(dx_f), part_f, R, dm, s), "dec_rmsnorm_bwd");
       view(dx, {R, dm}).copy_(dx_f);
     }
@@ -381,17 +391,13 @@ struct Step {
     for (int64_t i = L - 1; i >= 0; --i) {
       Layer& l = layers[i];
       const Saved& sv = saved[i];
-      add(l.w2, sv.a, dx, R);
-      mm_bwd(du, dx, l.w2, R, sv.u);
-      add(l.w1, sv.h2, du, R);
-      mm_bwd(dh, du, l.w1, R);
+      grads(l.w2, sv.a, du, dx, R, sv.u);
+      grads(l.w1, sv.h2, dh, du, R);
       norm_bwd(sv.x2, l.norm2, sv.r2, l.part2, false);
-      add(l.wo, sv.o, dx, R);
-      mm_bwd(d_o, dx, l.wo, R);
+      grads(l.wo, sv.o, d_o, dx, R);
       attention_bwd(l, sv, d_o, d_qkv, C, q_start, w, wq.empty() ? none : wq[i], wlen);
       readout(l, d_qkv, C, q_start);
-      add(l.wqkv, sv.h1, d_qkv, R);
-      mm_bwd(dh, d_qkv, l.wqkv, R);
+      grads(l.wqkv, sv.h1, dh, d_qkv, R);
       norm_bwd(sv.x1, l.norm1, sv.r1, l.part1, false);
     }
     if (emb.wanted) {

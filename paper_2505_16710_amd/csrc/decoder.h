@@ -40,6 +40,9 @@ enum { DEC_GEMM_STORE = 0, DEC_GEMM_ADD = 1, DEC_GEMM_SILU = 2, DEC_GEMM_SILU_BW
 int dec_gemm_supported(int form, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, int64_t ldc);   // 1 / 0
 int dec_gemm(int form, int epilogue, const void* a, const void* b, void* c, void* c2, int64_t M, int64_t N, int64_t K,
              int64_t lda, int64_t ldb, int64_t ldc, void* stream);
+// Both gradients of y[M,n] = x[M,K] w[K,n], contiguous: dx[M,K] = dy w^T (u non-NULL: times silu'(u)), dw += x^T dy; what
+// dec_gemm computes for either, bit for bit, in one launch where that pays.  No output may overlap an operand of the other.
+int dec_gemm_grads(const void* dy, const void* w, void* dx, void* u, const void* x, void* dw, int64_t M, int64_t K, int64_t n, void* stream);
 #ifdef __cplusplus
 }
 #endif

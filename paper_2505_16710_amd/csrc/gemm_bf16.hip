@@ -15,6 +15,8 @@
 // are XOR-ed with a function of the row such that row reads (ds_read_b128, 16 rows) and transpose reads
 // (ds_read_b64_tr_b16, 4 rows x 64 bytes) meet no bank conflict.  Both kinds of read deliver contraction slot s of
 // lane group g as element 8 g + s, so that any two operands can meet.  The tile leaves through LDS in rows of 16-byte stores.
+#include <type_traits>
+
 #include "decoder.h"
 #include "mfma_tiles.h"
 #include "seco_internal.h"
@@ -136,14 +138,10 @@ __device__ __forceinline__ void emit(const GemmArgs& g, int64_t at, const F4& lo
 
 // KH groups of 2 x WN wavefronts, each with a ring of kStages slots; group kh takes the steps kh, kh + KH, ...
 template <int BM, int BN, int KH, int kStages, int WN, bool AKC, bool BKC, int EPI>
-__global__ __launch_bounds__(128 * WN * KH, 2) void gemm_kernel(GemmArgs g, int total) {
+__device__ __forceinline__ void ring_tile(const GemmArgs& g, int item, lds_char* smem_all) {
   constexpr int kSlot = (BM + BN) * kRow, GW = 2 * WN, MB = BM / 64, NB = BN / (32 * WN);
   constexpr int kPerWave = BM / (8 * GW) + BN / (8 * GW);            // copies per wavefront and step
   constexpr int kRing = kStages * kSlot;
-  extern __shared__ __attribute__((aligned(16))) char smem_raw[];
-  lds_char* smem_all = (lds_char*)smem_raw;
-  const int item = xcd_item(blockIdx.x, total);          // neighbours share the columns of B (a weight matrix in two of the forms)
-  if (item < 0) return;
   const int tid = threadIdx.x, lane = tid & 63, wave_all = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wave = wave_all % GW, kh = KH == 1 ? 0 : wave_all / GW;
   lds_char* smem = smem_all + kh * kRing;
@@ -278,12 +276,8 @@ __global__ __launch_bounds__(128 * WN * KH, 2) void gemm_kernel(GemmArgs g, int 
 // MFMA) on half of the CUs; here an operand is read from LDS once (1.5 KiB per MFMA), twice the CUs work, and the copies of
 // all wavefronts are in flight at once.
 template <int NW, bool AKC, bool BKC, int EPI>
-__global__ __launch_bounds__(64 * NW, 2) void gemm_k_kernel(GemmArgs g, int total) {
+__device__ __forceinline__ void k_tile(const GemmArgs& g, int item, lds_char* smem_all) {
   constexpr int BM = 32, BN = 64, kSlot = (BM + BN) * kRow;
-  extern __shared__ __attribute__((aligned(16))) char smem_raw[];
-  lds_char* smem_all = (lds_char*)smem_raw;
-  const int item = xcd_item(blockIdx.x, total);
-  if (item < 0) return;
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   lds_char* smem = smem_all + w * kSlot;
   const int tn = item / g.tiles_m, tm = item - tn * g.tiles_m;
@@ -353,28 +347,36 @@ __global__ __launch_bounds__(64 * NW, 2) void gemm_k_kernel(GemmArgs g, int tota
   emit<EPI>(g, at, lo, hi, met<EPI>(g, at));
 }
 
-template <int BM, int BN, int KH, int ST, int WN, bool AKC, bool BKC, int EPI> int launch(GemmArgs g, hipStream_t s) {
-  constexpr int smem = KH * ST * (BM + BN) * kRow;
-  auto kern = gemm_kernel<BM, BN, KH, ST, WN, AKC, BKC, EPI>;
-  static std::atomic<uint64_t> ready{0};
-  if (!allow_lds(ready, reinterpret_cast<const void*>(kern), smem)) return SECO_ERR_LAUNCH;
-  g.tiles_m = (g.M + BM - 1) / BM;
-  const int total = g.tiles_m * ((g.N + BN - 1) / BN);
-  hipLaunchKernelGGL(kern, dim3(xcd_grid(total)), dim3(128 * WN * KH), smem, s, g, total);
-  return launch_status();
+// A way to work a product: workgroups of kThreads with kSmem bytes of LDS, one per item
+template <int BM, int BN, int KH, int ST, int WN, bool AKC, bool BKC, int EPI> struct Ring {
+  static constexpr int kThreads = 128 * WN * KH, kSmem = KH * ST * (BM + BN) * kRow, kBM = BM, kBN = BN;
+  static __device__ __forceinline__ void run(const GemmArgs& g, int item, lds_char* smem) {
+    ring_tile<BM, BN, KH, ST, WN, AKC, BKC, EPI>(g, item, smem);
+  }
+};
+template <int NW, bool AKC, bool BKC, int EPI> struct ByK {
+  static constexpr int kThreads = 64 * NW, kSmem = NW * 96 * kRow, kBM = 32, kBN = 64;
+  static __device__ __forceinline__ void run(const GemmArgs& g, int item, lds_char* smem) { k_tile<NW, AKC, BKC, EPI>(g, item, smem); }
+};
+template <typename T> int items_of(GemmArgs& g) {
+  g.tiles_m = (g.M + T::kBM - 1) / T::kBM;
+  return g.tiles_m * ((g.N + T::kBN - 1) / T::kBN);
 }
 
-template <int NW, bool AKC, bool BKC, int EPI> int launch_k(GemmArgs g, hipStream_t s) {
-  constexpr int smem = NW * 96 * kRow;
-  auto kern = gemm_k_kernel<NW, AKC, BKC, EPI>;
+template <typename T>
+__global__ __launch_bounds__(T::kThreads, 2) void gemm_kernel(GemmArgs g, int total) {
+  extern __shared__ __attribute__((aligned(16))) char smem_raw[];
+  const int item = xcd_item(blockIdx.x, total);          // neighbours share the columns of B (a weight matrix in two of the forms)
+  if (item >= 0) T::run(g, item, (lds_char*)smem_raw);
+}
+template <typename T> int launch(GemmArgs g, hipStream_t s) {
+  auto kern = gemm_kernel<T>;
   static std::atomic<uint64_t> ready{0};
-  if (!allow_lds(ready, reinterpret_cast<const void*>(kern), smem)) return SECO_ERR_LAUNCH;
-  g.tiles_m = (g.M + 31) / 32;
-  const int total = g.tiles_m * ((g.N + 63) / 64);
-  hipLaunchKernelGGL(kern, dim3(xcd_grid(total)), dim3(64 * NW), smem, s, g, total);
+  if (!allow_lds(ready, reinterpret_cast<const void*>(kern), T::kSmem)) return SECO_ERR_LAUNCH;
+  const int total = items_of<T>(g);
+  hipLaunchKernelGGL(kern, dim3(xcd_grid(total)), dim3(T::kThreads), T::kSmem, s, g, total);
   return launch_status();
 }
-
 // Which tile: measured over 64 .. 2048 rows against matrices of 1024 x 1024 .. 4096 x 1024 (us; K: contraction length).
 // LDS reads bound the small tiles (2 KiB per MFMA at 64 x 64, 1 KiB at 128 x 128), idle CUs the large ones.
 //  - forward and data gradient whose 32 x 64 tiles fit one round: those, the contraction divided among eight wavefronts (512 x
@@ -391,19 +393,76 @@ template <int NW, bool AKC, bool BKC, int EPI> int launch_k(GemmArgs g, hipStrea
 //    the rows of B are contracted, 64 x 128, eight wavefronts side by side, three slots: a third less from L2 than 64 x 64 with two
 //    slots and two workgroups per CU (1024 x 1536 over 512 rows: 5.7 against 6.3, 512 x 4096 x 1024 with the SiLU: 9.9 / 10.4;
 //    2048 x 1024 over 2048: 13.7 / 14.9 with 128 x 64); else those (512 x 4096 x 1024 back through the SiLU: 9.5; 10.2 with 64 x 128).
-template <bool AKC, bool BKC, int EPI> int pick(const GemmArgs& g, hipStream_t s) {
+template <typename T> struct Way { using type = T; };
+template <bool AKC, bool BKC, int EPI, typename F> int with_way(const GemmArgs& g, const F& f) {
   const int64_t m64 = (g.M + 63) / 64, n64 = (g.N + 63) / 64, big = ((m64 + 1) / 2) * ((n64 + 1) / 2), cus = device_cus();
   if constexpr (AKC)
-    if ((g.M + 31) / 32 * n64 <= cus) return launch_k<8, AKC, BKC, EPI>(g, s);
-  if (4 * big > 5 * cus) return launch<128, 128, 1, 2, 2, AKC, BKC, EPI>(g, s);
-  if (20 * big >= 11 * cus) return launch<128, 128, 1, 3, 4, AKC, BKC, EPI>(g, s);
-  if (m64 * n64 <= cus) return launch<64, 64, 2, 3, 2, AKC, BKC, EPI>(g, s);
+    if ((g.M + 31) / 32 * n64 <= cus) return f(Way<ByK<8, AKC, BKC, EPI>>());
+  if (4 * big > 5 * cus) return f(Way<Ring<128, 128, 1, 2, 2, AKC, BKC, EPI>>());
+  if (20 * big >= 11 * cus) return f(Way<Ring<128, 128, 1, 3, 4, AKC, BKC, EPI>>());
+  if (m64 * n64 <= cus) return f(Way<Ring<64, 64, 2, 3, 2, AKC, BKC, EPI>>());
   if constexpr (AKC)
-    if (g.K >= 2048) return launch<128, 64, 2, 3, 2, AKC, BKC, EPI>(g, s);
+    if (g.K >= 2048) return f(Way<Ring<128, 64, 2, 3, 2, AKC, BKC, EPI>>());
   if constexpr (!BKC)
-    return launch<64, 128, 1, 3, 4, AKC, BKC, EPI>(g, s);
+    return f(Way<Ring<64, 128, 1, 3, 4, AKC, BKC, EPI>>());
   else
-    return launch<64, 64, 2, 2, 2, AKC, BKC, EPI>(g, s);
+    return f(Way<Ring<64, 64, 2, 2, 2, AKC, BKC, EPI>>());
+}
+template <bool AKC, bool BKC, int EPI> int pick(const GemmArgs& g, hipStream_t s) {
+  return with_way<AKC, BKC, EPI>(g, [&](auto way) { return launch<typename decltype(way)::type>(g, s); });
+}
+
+// Both gradients of a layer's product in one launch.  Each fills the chip once or less for a few microseconds: what is saved is
+// the end of the one and the start of the other, 1.5 - 3 us.  512 rows, apart -> together: 1024 x 4096 19.5 -> 17.7, 4096 x 1024
+// with the SiLU's derivative 18.9 -> 17.6, 1024 x 1536 12.1 -> 10.3, 1024 x 1024 10.1 -> 8.6; 320 rows 17.5 -> 14.5, 16.6 -> 14.0,
+// -, 9.5 -> 7.7.
+// weight_first: which workgroups go in front.  Those of the weight gradient take rows / 64 steps, the others' time does not
+// depend on the rows: the longer ones first (512 rows, 4096 x 1024: 17.6 against 18.8; 320: 15.1 against 14.0).
+template <typename A, typename B>
+__global__ __launch_bounds__(512, 2) void gemm_pair_kernel(GemmArgs a, GemmArgs b, int total_a, int total_b, int first_grid, int weight_first) {
+  extern __shared__ __attribute__((aligned(16))) char smem_raw[];
+  const bool first = (int)blockIdx.x < first_grid, weight = first == (weight_first != 0);
+  const int item = xcd_item(first ? blockIdx.x : blockIdx.x - first_grid, weight ? total_b : total_a);
+  if (item < 0) return;
+  if (weight)
+    B::run(b, item, (lds_char*)smem_raw);
+  else
+    A::run(a, item, (lds_char*)smem_raw);
+}
+template <typename A, typename B> int launch_pair(GemmArgs a, GemmArgs b, hipStream_t s) {
+  static_assert(A::kThreads == 512 && B::kThreads == 512, "workgroups of one size");
+  constexpr int smem = A::kSmem > B::kSmem ? A::kSmem : B::kSmem;
+  auto kern = gemm_pair_kernel<A, B>;
+  static std::atomic<uint64_t> ready{0};
+  if (!allow_lds(ready, reinterpret_cast<const void*>(kern), smem)) return SECO_ERR_LAUNCH;
+  const int ta = items_of<A>(a), tb = items_of<B>(b), weight_first = b.K >= 448;
+  const int ga = xcd_grid(ta), gb = xcd_grid(tb);
+  hipLaunchKernelGGL(kern, dim3(ga + gb), dim3(512), smem, s, a, b, ta, tb, weight_first ? gb : ga, weight_first);
+  return launch_status();
+}
+// In one launch where the data gradient takes one of the small tiles and as many of its workgroups share a CU as by itself
+// (64 x 64 tiles with two slots: two; larger products would gain less than 5 %).  -1: not
+template <int EPI> int pair(const GemmArgs& a, const GemmArgs& b, hipStream_t s) {
+  using Wide = Ring<128, 128, 1, 3, 4, false, false, kAdd>;
+  using Two = Ring<64, 64, 2, 2, 2, true, true, EPI>;
+  return with_way<true, true, EPI>(a, [&](auto way_a) {
+    using A = typename decltype(way_a)::type;
+    if constexpr (A::kThreads == 512 && A::kBM <= 64) {
+      return with_way<false, false, kAdd>(b, [&](auto way_b) {
+        using B = typename decltype(way_b)::type;
+        if constexpr (!std::is_same_v<A, Two> && B::kThreads == 512)
+          return launch_pair<A, B>(a, b, s);
+        else if constexpr (std::is_same_v<A, Two> && std::is_same_v<B, Wide>)
+          return launch_pair<A, Ring<128, 128, 1, 2, 4, false, false, kAdd>>(a, b, s);     // (the same sums)
+        else if constexpr (std::is_same_v<A, Two> && 2 * B::kSmem <= 160 * 1024 && B::kThreads == 512)
+          return launch_pair<A, B>(a, b, s);
+        else
+          return -1;
+      });
+    } else {
+      return -1;
+    }
+  });
 }
 
 }  // namespace
@@ -434,4 +493,21 @@ extern "C" int dec_gemm(int form, int epilogue, const void* a, const void* b, vo
   if (form == DEC_GEMM_TN && epilogue == DEC_GEMM_STORE) return pick<false, false, kStore>(g, s);
   if (form == DEC_GEMM_TN && epilogue == DEC_GEMM_ADD) return pick<false, false, kAdd>(g, s);
   return SECO_ERR_SHAPE;
+}
+
+extern "C" int dec_gemm_grads(const void* dy, const void* w, void* dx, void* u, const void* x, void* dw, int64_t M, int64_t K, int64_t n,
+                              void* stream) {
+  using namespace seco;
+  if (!dec_gemm_supported(DEC_GEMM_NT, M, K, n, n, n, K) || !dec_gemm_supported(DEC_GEMM_TN, K, n, M, K, n, n)) return SECO_ERR_SHAPE;
+  if (!dy || !w || !dx || !x || !dw) return SECO_ERR_NULL;
+  if (((uintptr_t)dy | (uintptr_t)w | (uintptr_t)dx | (uintptr_t)u | (uintptr_t)x | (uintptr_t)dw) & 15u) return SECO_ERR_ALIGN;
+  const GemmArgs a{static_cast<const char*>(dy), static_cast<const char*>(w), static_cast<__bf16*>(dx), static_cast<__bf16*>(u),
+                   (int)M, (int)K, (int)n, (int)n, (int)n, (int)K, 0};
+  const GemmArgs b{static_cast<const char*>(x), static_cast<const char*>(dy), static_cast<__bf16*>(dw), nullptr,
+                   (int)K, (int)n, (int)M, (int)K, (int)n, (int)n, 0};
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  int rc = u ? pair<kSiluBwd>(a, b, s) : pair<kStore>(a, b, s);
+  if (rc != -1) return rc;
+  rc = u ? pick<true, true, kSiluBwd>(a, s) : pick<true, true, kStore>(a, s);
+  return rc ? rc : pick<false, false, kAdd>(b, s);
 }

@@ -63,6 +63,32 @@ def test_gemm_forms_and_epilogues(form, epi, M, N, K):
     assert torch.equal(c[M], c_in[M]) and torch.equal(c2[M], c2_in[M])
 
 
+@pytest.mark.parametrize("M,K,n,silu", [
+    (512, 1024, 4096, False), (512, 4096, 1024, True), (448, 1024, 1536, False), (447, 1024, 1024, False), (1, 64, 64, False),
+    (33, 72, 128, True), (200, 1000, 1536, False), (250, 4104, 1088, True), (320, 4096, 1024, True), (500, 4000, 512, True),
+    (640, 1024, 1024, False), (300, 2048, 192, True), (1024, 4096, 1024, True), (2050, 1024, 4096, False),
+])
+def test_both_gradients_in_one_launch(M, K, n, silu):
+    """The bits of the two products, and nothing behind their last rows: tiles of every kind for either, in both orders."""
+    lib = seco.load_library()
+    P, I = C.c_void_p, C.c_int64
+    lib.dec_gemm.argtypes = [C.c_int, C.c_int, P, P, P, P] + [I] * 6 + [P]
+    lib.dec_gemm_grads.argtypes = [P] * 6 + [I] * 3 + [P]
+    g = torch.Generator(device=DEV).manual_seed(M + K + n)
+
+    def normal(*shape):
+        return torch.randn(*shape, generator=g, device=DEV).to(torch.bfloat16)
+    dy, w, x, u = normal(M, n), normal(K, n), normal(M, K), normal(M, K)
+    dx, dw = normal(M + 1, K), normal(K + 1, n)
+    dx2, dw2, s = dx.clone(), dw.clone(), torch.cuda.current_stream().cuda_stream
+    ptr = lambda t: t.data_ptr()
+    assert lib.dec_gemm(TN, ADD, ptr(x), ptr(dy), ptr(dw), None, K, n, M, K, n, n, s) == 0
+    assert lib.dec_gemm(NT, SILU_BWD if silu else STORE, ptr(dy), ptr(w), ptr(dx), ptr(u) if silu else None, M, K, n, n, n, K, s) == 0
+    assert lib.dec_gemm_grads(ptr(dy), ptr(w), ptr(dx2), ptr(u) if silu else None, ptr(x), ptr(dw2), M, K, n, s) == 0
+    torch.cuda.synchronize()
+    assert torch.equal(dx, dx2) and torch.equal(dw, dw2)
+
+
 def test_gemm_refuses_what_it_cannot_do():
     lib = seco.load_library()
     I = C.c_int64
