@@ -1,11 +1,11 @@
 // The training step of chunk_loop.py, one chunk at a time, on the host side: what is launched, in which order, on which
 // buffers.  Second source of the extension module of the binding.
 //
-// A chunk of the step is about 90 launches of a few microseconds each.  Driven from Python, with the matrix products
+// A chunk of the step is about 60 launches of a few microseconds each.  Driven from Python, with the matrix products
 // through the framework (17 - 19 us of host time per call), a two-layer step over 4096 tokens in chunks of 512 took
 // 9.1 ms, of which the GPU worked 6.7; here a launch costs 2 - 4 us of host time, activations are carved from two
 // blocks allocated once per step, and the products are the library's own (gemm_bf16.hip) where type, alignment and size
-// allow: 4.8 ms, in which the GPU is busy throughout.
+// allow: 3.8 ms, in which the GPU is busy throughout.
 #include <map>
 #include <memory>
 
