@@ -195,38 +195,41 @@ template <int NT> struct Acc {
   }
 };
 // sum over the wavefronts, in order, of row i's elements d .. d + 3
-template <int NT, int NW>
+template <int NT, int NO, int NW>
 __device__ __forceinline__ f32x4 sum_part(const float* part, int i, int d) {
   f32x4 s = zero4();
 #pragma unroll
-  for (int w = 0; w < NW; ++w) s += load4(part + w * kPart<NT> + i * kPartRow<NT> + d);
+  for (int w = 0; w < NW; ++w) s += load4(part + w * kPart<NT> + i * kPartRow<NO> + d);
   return s;
 }
 
-// O = softmax(s Q K^T) V and LSE.  The next block's K and V are requested before the present one is worked on.
-template <int NT, int NW>
+// O = softmax(s Q K^T) V and LSE, of O the columns of NO of the NT blocks (fwd_nt).  The next block's K and V are requested before the present one is worked on.
+template <int NT, int NO, int NW>
 __global__ __launch_bounds__(NW * 64, NT <= 12 ? 2 : 1) void fwd_f32_kernel(AttnParams p) {
+  constexpr int kParts = (NT + NO - 1) / NO;
   constexpr bool kAhead = NT <= 8;                      // (longer rows do not leave the registers)
   extern __shared__ float part[];                       // an image per wavefront; then its (reference, sum) per row
   float* ml = part + NW * kPart<NT>;
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), i = lane & 15, g = lane >> 4;
-  const int r0 = (gridDim.x - 1 - blockIdx.x) * kRows, h = blockIdx.y, b = blockIdx.z, D = p.D;
+  const int turn = gridDim.x - 1 - blockIdx.x, r0 = turn / kParts * kRows, h = blockIdx.y, b = blockIdx.z, D = p.D;
+  const int o0 = turn % kParts * (16 * NO), n_o = min(D - o0, 16 * NO);   // this workgroup's columns of O
+  if (n_o <= 0) return;
   const float* K = static_cast<const float*>(p.k) + b * p.kvs[0] + (h / p.G) * p.kvs[1];
-  const float* V = static_cast<const float*>(p.v) + b * p.kvs[0] + (h / p.G) * p.kvs[1];
+  const float* V = static_cast<const float*>(p.v) + b * p.kvs[0] + (h / p.G) * p.kvs[1] + o0;
   const int64_t row = p.kvs[2];
   const int qpos = p.q_start + r0 + i, kv_end = p.q_start + min(r0 + kRows, p.C);
   float* own = part + w * kPart<NT>;
   Block<NT> kb;
-  Cols<NT> vx;
+  Cols<NO> vx;
   const Pieces<NT> pk(lane, row, D);
   const uint32_t v_off = (uint32_t)(4 * g) * (uint32_t)row;   // elements
   auto load_k = [&](int c0) { pk.load(kb, K + c0 * row, row, kv_end - c0); };
   auto load_v = [&](int c0) {
     const float* from = V + c0 * row;
     if (c0 + kRows <= kv_end)
-      vx.load([&](int r) { return from + r * row + v_off; }, D, i);
+      vx.load([&](int r) { return from + r * row + v_off; }, n_o, i);
     else
-      vx.load([&](int r) { return V + min(c0 + 4 * g + r, kv_end - 1) * row; }, D, i);
+      vx.load([&](int r) { return V + min(c0 + 4 * g + r, kv_end - 1) * row; }, n_o, i);
   };
   f32x4 qf[NT];
   {
@@ -246,7 +249,7 @@ __global__ __launch_bounds__(NW * 64, NT <= 12 ? 2 : 1) void fwd_f32_kernel(Attn
   // 15.5 us, 14.8 without.)
   constexpr float kSlack = 32.f;
   float m = -INFINITY, ref = 0.f, l = 0.f;
-  Acc<NT> o;
+  Acc<NO> o;
   o.clear();
 #pragma unroll 1
   for (int c0 = w * 16; c0 < kv_end; c0 += NW * 16) {
@@ -309,21 +312,21 @@ __global__ __launch_bounds__(NW * 64, NT <= 12 ? 2 : 1) void fwd_f32_kernel(Attn
     }
     L += __shfl_xor(L, 16);
     L += __shfl_xor(L, 32);
-    float* out = static_cast<float*>(p.o_out) + b * p.os[0] + h * p.os[1] + (r0 + r) * p.os[2];
+    float* out = static_cast<float*>(p.o_out) + b * p.os[0] + h * p.os[1] + (r0 + r) * p.os[2] + o0;
 #pragma unroll
-    for (int d0 = 0; d0 < 16 * NT; d0 += 64) {
+    for (int d0 = 0; d0 < 16 * NO; d0 += 64) {
       const int d = d0 + 4 * i;
       f32x4 acc = zero4();
 #pragma unroll
-      for (int v = 0; v < NW / 4; ++v) acc += a[v] * load4(part + (g * (NW / 4) + v) * kPart<NT> + r * kPartRow<NT> + min(d, 16 * NT - 4));
+      for (int v = 0; v < NW / 4; ++v) acc += a[v] * load4(part + (g * (NW / 4) + v) * kPart<NT> + r * kPartRow<NO> + min(d, 16 * NO - 4));
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         acc[j] += __shfl_xor(acc[j], 16);
         acc[j] += __shfl_xor(acc[j], 32);
       }
-      if (g == 0 && d < D) *reinterpret_cast<f32x4*>(out + d) = acc * (1.f / L);
+      if (g == 0 && d < n_o) *reinterpret_cast<f32x4*>(out + d) = acc * (1.f / L);
     }
-    if (lane == 0) p.lse[((int64_t)b * p.Hq + h) * p.C + r0 + r] = (M + __log2f(L)) * kLn2;
+    if (lane == 0 && o0 == 0) p.lse[((int64_t)b * p.Hq + h) * p.C + r0 + r] = (M + __log2f(L)) * kLn2;
   }
 }
 
@@ -350,9 +353,13 @@ __device__ __forceinline__ OneRun tile_at(const SegTable& t, int tile) {
 }
 __device__ __forceinline__ OneRun tile_at(const OneRun& t, int tile) { return {t.begin + tile * kRows, t.end, t.weight}; }
 
-// dQ = s * sum over the runs of cache rows of w * dS K (one run with weight 1 over all visible rows: the exact dQ)
-template <int NT, int NW, typename Runs>
-__device__ __forceinline__ void dq_f32(const AttnParams& p, const Runs& runs, int item, float* part) {
+// dQ = s * sum over the runs of cache rows of w * dS K (one run with weight 1 over all visible rows: the exact dQ); of dQ the
+// columns of NO of the NT blocks
+template <int NT, int NO, int NW, typename Runs>
+__device__ __forceinline__ void dq_f32(const AttnParams& p, const Runs& runs, int item_part, float* part) {
+  constexpr int kParts = (NT + NO - 1) / NO;
+  const int item = item_part / kParts, o0 = item_part % kParts * (16 * NO), n_o = kParts == 1 ? p.D : min(p.D - o0, 16 * NO);
+  if (kParts > 1 && n_o <= 0) return;
   constexpr bool kAhead = NT <= 5;                      // (longer rows do not leave the registers)
   constexpr bool kTable = std::is_same<Runs, SegTable>::value;
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), i = lane & 15, g = lane >> 4;
@@ -401,7 +408,7 @@ __device__ __forceinline__ void dq_f32(const AttnParams& p, const Runs& runs, in
     __syncthreads();
   }
   const float lse = p.lse[((int64_t)b * p.Hq + h) * p.C + min(r0 + i, p.C - 1)] * kLog2e, c = p.scale * kLog2e;
-  Acc<NT> dq;
+  Acc<NO> dq;
   dq.clear();
   int next = w;                                         // blocks of all runs are dealt to the wavefronts in turn
   for (int si = 0; si < runs_of(runs); ++si) {
@@ -428,8 +435,9 @@ __device__ __forceinline__ void dq_f32(const AttnParams& p, const Runs& runs, in
         rows_of<NT>(own2, i, g, x);
         dp = score<NT>(x, dof);
       }
-      Cols<NT> kc;
-      kc.of(own, i, g);
+      Cols<NO> kc;
+      kc.load([&](int r) { return own + (4 * g + r) * kPartRow<NT> + o0; }, min(16 * NO, 16 * NT - o0), i);
+      asm volatile("" : : : "memory");
 #pragma unroll
       for (int r = 0; r < 4; ++r) ds[r] = fast_exp2(__builtin_fmaf(s[r], c, -lse)) * (dp[r] - delta);
       if (kTable) ds *= run.weight;                     // (of a single run: with the scale, at the end)
@@ -443,11 +451,11 @@ __device__ __forceinline__ void dq_f32(const AttnParams& p, const Runs& runs, in
   }
   dq.store(own, i, g);
   __syncthreads();
-  for (int e = threadIdx.x; e < kRows * NT * 4; e += NW * 64) {
-    const int rr = e / (NT * 4), d = 4 * (e % (NT * 4));
-    if (r0 + rr >= p.C || d >= D) continue;
-    float* out = static_cast<float*>(p.d_q) + b * p.qs[0] + h * p.qs[1] + (r0 + rr) * p.qs[2] + d;
-    *reinterpret_cast<f32x4*>(out) = (kTable ? p.scale : p.scale * run_at(runs, 0).weight) * sum_part<NT, NW>(part, rr, d);
+  for (int e = threadIdx.x; e < kRows * NO * 4; e += NW * 64) {
+    const int rr = e / (NO * 4), d = 4 * (e % (NO * 4));
+    if (r0 + rr >= p.C || d >= n_o) continue;
+    float* out = static_cast<float*>(p.d_q) + b * p.qs[0] + h * p.qs[1] + (r0 + rr) * p.qs[2] + o0 + d;
+    *reinterpret_cast<f32x4*>(out) = (kTable ? p.scale : p.scale * run_at(runs, 0).weight) * sum_part<NT, NO, NW>(part, rr, d);
   }
 }
 
@@ -585,15 +593,15 @@ __device__ __forceinline__ void dkdv_f32(const AttnParams& p, const Runs& runs, 
     const int e = threadIdx.x + k * NW * 64;
     float *q, wt;
     if (!target(e, q, wt)) continue;
-    *reinterpret_cast<f32x4*>(q) = old[k] + wt * sum_part<NT, NW>(part + e / kQuads * (NW * kPart<NT>), (e % kQuads) / (NT * 4), 4 * (e % (NT * 4)));
+    *reinterpret_cast<f32x4*>(q) = old[k] + wt * sum_part<NT, NT, NW>(part + e / kQuads * (NW * kPart<NT>), (e % kQuads) / (NT * 4), 4 * (e % (NT * 4)));
   }
 }
 
-template <int NT, int NW, typename Runs>
+template <int NT, int NO, int NW, typename Runs>
 __global__ __launch_bounds__(NW * 64) void bwd_f32_kernel(AttnParams p, Runs dq_runs, Runs seg, int n_dq) {
   extern __shared__ float part[];                       // two images per wavefront
   if ((int)blockIdx.x < n_dq)
-    dq_f32<NT, NW>(p, dq_runs, blockIdx.x, part);
+    dq_f32<NT, NO, NW>(p, dq_runs, blockIdx.x, part);
   else
     dkdv_f32<NT, NW>(p, seg, blockIdx.x - n_dq, part);
 }
@@ -602,20 +610,34 @@ __global__ __launch_bounds__(NW * 64) void bwd_f32_kernel(AttnParams p, Runs dq_
 template <int NT> constexpr int kFwdWaves = NT <= 4 ? 16 : NT <= 8 ? 8 : 4;
 template <int NT> constexpr int kBwdWaves = NT <= 8 ? 8 : 4;
 
-template <int NT>
-int fwd_nt(const AttnParams& p, hipStream_t s) {
+template <int NT, int NO>
+int fwd_launch(const AttnParams& p, hipStream_t s) {
   constexpr int NW = kFwdWaves<NT>, smem = NW * (kPart<NT> + 2 * kRows) * 4;
-  auto kern = fwd_f32_kernel<NT, NW>;
+  auto kern = fwd_f32_kernel<NT, NO, NW>;
   static std::atomic<uint64_t> ready{0};
   if (!allow_lds(ready, reinterpret_cast<const void*>(kern), smem)) return SECO_ERR_LAUNCH;
   ProfScope prof(kKernelFwd, s);
-  hipLaunchKernelGGL(kern, dim3((p.C + kRows - 1) / kRows, p.Hq, p.B), dim3(NW * 64), smem, s, p);
+  hipLaunchKernelGGL(kern, dim3((p.C + kRows - 1) / kRows * ((NT + NO - 1) / NO), p.Hq, p.B), dim3(NW * 64), smem, s, p);
   return launch_status();
 }
-template <int NT, typename Runs>
+// Few row tiles: two or four workgroups for each, on CUs that had none, which all compute its scores but only a part of the
+// columns of O (or dQ), whose products are half of the work (a third).  As long as that leaves every workgroup a CU: beyond, the
+// scores computed again cost more than they save (88 tiles of head_dim 64 by four: 24 us, by two 17.3, whole 18.7).  Forward of 4
+// heads of 64, 256 rows at 768: 14.9 -> 11.7 us; 3 heads of 128, 76 rows at 560: 18.2 -> 13.8; 4 of 256, 200 at 400: 37.5 -> 25.0.
+// Backward: 64 + 128 tiles of head_dim 64 10.9 -> 10.1 us; 15 + 120 of 128 23.3 -> 19.1 (four); 28 + 252 of 64 18.1 -> 16.5 (two: the
+// others' CUs may be shared a little, 64 + 256 gain nothing); 120 + 120 of 128 by two 26.2 -> 28.1.
+template <int NT>
+int fwd_nt(const AttnParams& p, hipStream_t s) {
+  const int64_t n = (int64_t)((p.C + kRows - 1) / kRows) * p.Hq * p.B, cus = device_cus();
+  if (n * 4 <= cus) return fwd_launch<NT, (NT + 3) / 4>(p, s);
+  if (n * 2 <= cus) return fwd_launch<NT, (NT + 1) / 2>(p, s);
+  return fwd_launch<NT, NT>(p, s);
+}
+template <int NT, int NO, typename Runs>
 int bwd_launch(const AttnParams& p, const Runs& dq_runs, const Runs& seg, int64_t n_dq, int64_t n_kv, hipStream_t s) {
   constexpr int NW = kBwdWaves<NT>, smem = 2 * NW * kPart<NT> * 4;
-  auto kern = bwd_f32_kernel<NT, NW, Runs>;
+  auto kern = bwd_f32_kernel<NT, NO, NW, Runs>;
+  n_dq *= (NT + NO - 1) / NO;
   static std::atomic<uint64_t> ready{0};
   if (!allow_lds(ready, reinterpret_cast<const void*>(kern), smem)) return SECO_ERR_LAUNCH;
   if (n_dq + n_kv > 0x7fffffff) return SECO_ERR_TOO_LARGE;
@@ -623,15 +645,24 @@ int bwd_launch(const AttnParams& p, const Runs& dq_runs, const Runs& seg, int64_
   hipLaunchKernelGGL(kern, dim3((unsigned)(n_dq + n_kv)), dim3(NW * 64), smem, s, p, dq_runs, seg, (int)n_dq);
   return launch_status();
 }
+template <int NT, typename Runs>
+int bwd_parts(const AttnParams& p, const Runs& dq_runs, const Runs& seg, int64_t n_dq, int64_t n_kv, hipStream_t s) {
+  const int64_t cus = device_cus();
+  if constexpr (NT < 16 || std::is_same<Runs, OneRun>::value) {    // (with the table scalar registers are short at the longest rows)
+    if (n_dq * 4 + n_kv <= cus) return bwd_launch<NT, (NT + 3) / 4>(p, dq_runs, seg, n_dq, n_kv, s);
+    if (n_dq * 2 + n_kv <= cus + cus / 4) return bwd_launch<NT, (NT + 1) / 2>(p, dq_runs, seg, n_dq, n_kv, s);
+  }
+  return bwd_launch<NT, NT>(p, dq_runs, seg, n_dq, n_kv, s);
+}
 template <int NT>
 int bwd_nt(const AttnParams& p, const SegTable& dq_runs, const SegTable& seg, bool dq, hipStream_t s) {
   const int64_t n_dq = dq ? (int64_t)((p.C + kRows - 1) / kRows) * p.Hq * p.B : 0;
   const int64_t n_kv = (int64_t)seg.tile_begin[seg.n] * p.Hkv * p.B;
   if (dq_runs.n == 1 && seg.n == 1) {
     const OneRun d{dq_runs.col_begin[0], dq_runs.col_end[0], dq_runs.weight[0]}, k{seg.col_begin[0], seg.col_end[0], seg.weight[0]};
-    return bwd_launch<NT, OneRun>(p, d, k, n_dq, n_kv, s);
+    return bwd_parts<NT>(p, d, k, n_dq, n_kv, s);
   }
-  return bwd_launch<NT, SegTable>(p, dq_runs, seg, n_dq, n_kv, s);
+  return bwd_parts<NT>(p, dq_runs, seg, n_dq, n_kv, s);
 }
 
 }  // namespace

@@ -65,6 +65,39 @@ def test_fp32_tile_edges(D, N, C):
           A.spaco_layer(x["q"], x["k"], x["v"], x["do"], C, s, sel, lam), "f32", f"f32 spaco {D,N,C}")
 
 
+@pytest.mark.parametrize("D", [4, 20, 32, 36, 52, 64, 68, 80, 84, 128, 132, 180, 196, 228, 256])
+@pytest.mark.parametrize("Hq,C,q_start", [(4, 256, 0), (4, 257, 40), (8, 250, 100), (2, 500, 4), (3, 33, 200)])
+def test_fp32_row_tiles_with_several_workgroups(D, Hq, C, q_start):
+    """Four, two and one workgroup per 16 query rows on both sides of the rules' lines (256 CUs: 64 and 65 tiles, 128 and 129), parts of
+    the columns that are partly or wholly past head_dim; strided inputs, weights in the second run."""
+    N, s = q_start + C, 1 / np.sqrt(D)
+    x = small_layer(13, 1, Hq, 1, N, D, "f32")
+    dev = {}
+    for n, t in x.items():                              # rows 16 bytes longer than head_dim
+        wide = torch.full((*t.shape[:3], t.shape[3] + 4), float("nan"), device=DEV)
+        wide[..., :D] = to_dev(t, "f32")
+        dev[n] = wide[..., :D]
+    q, do = dev["q"][:, :, q_start:], dev["do"][:, :, q_start:]
+    o = torch.full((1, Hq, N, D + 4), float("nan"), device=DEV)[:, :, q_start:, :D]
+    _, lse = seco.seco_chunk_attn_fwd(q, dev["k"], dev["v"], q_start, s, o=o)
+    xq, xdo = x["q"][:, :, q_start:], x["do"][:, :, q_start:]
+    ref_o, ref_lse = A.chunk_attn_fwd(xq, x["k"], x["v"], q_start, s)
+    ref = A.chunk_attn_bwd(xq, x["k"], x["v"], ref_o, ref_lse, xdo, q_start, s)
+    assert max_rel(to_host(o), ref_o) <= 1e-4 and max_rel(to_host(lse), ref_lse) <= 1e-4
+    for w in (None, [0.5, 2.0]):
+        gk, gv = (torch.zeros(1, 1, N, D, device=DEV) for _ in range(2))
+        args = (q, dev["k"], dev["v"], o, lse, do, gk, gv, q_start, s)
+        if w is None:
+            dq = seco.seco_chunk_attn_bwd(*args)
+        elif q_start % C or q_start == 0:
+            continue
+        else:
+            dq = seco.spaco_chunk_attn_bwd(*args, w, C)
+        factor = np.ones(N)[:, None] if w is None else np.repeat(w, C)[:N, None]
+        assert max_rel(to_host(dq), ref[0]) <= 1e-4
+        assert max_rel(to_host(gk), ref[1] * factor) <= 1e-4 and max_rel(to_host(gv), ref[2] * factor) <= 1e-4
+
+
 @pytest.mark.parametrize("D", [8, 32, 64, 80, 112, 128, 176, 256])
 @pytest.mark.parametrize("rising", [True, False])
 def test_fp32_reference_moves_along_the_cache(D, rising):
