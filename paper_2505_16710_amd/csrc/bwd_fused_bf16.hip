@@ -35,8 +35,8 @@ static_assert(Cfg::kThreads == 512, "both passes in workgroups of 8 wavefronts")
 // RUNS: nothing, or the SegTable of dQ over selected columns
 struct AllColumns {};
 template <bool SPLIT, typename RUNS>
-__global__ __launch_bounds__(512, 2) void bwd_fused_bf16_kernel(AttnParams p, SegTable seg, TailSplit ts, RUNS runs, int n_mtiles,
-                                                                int kv_total, int dq_total, int first_grid, int kv_first) {
+__global__ __launch_bounds__(512, 2) void bwd_fused_bf16_kernel(AttnParams p, SegTable seg, TailSplit ts, int n_mtiles,
+                                                                int kv_total, int dq_total, int first_grid, int kv_first, RUNS runs) {
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];
   lds_char* smem = (lds_char*)smem_raw;
   const bool first = (int)blockIdx.x < first_grid, kv = first == (kv_first != 0);
@@ -94,8 +94,8 @@ int launch(const AttnParams& p, const SegTable& seg, const TailSplit& ts, const 
   const int first = xcd_grid(kv_first ? kv_total : dq_total), second = xcd_grid(kv_first ? dq_total : kv_total);
   {
     ProfScope prof(kKernelBwd, s);
-    hipLaunchKernelGGL(kern, dim3(first + second), dim3(512), kSmem, s, p, seg, ts, runs, n_mtiles, kv_total, dq_total,
-                       first, kv_first ? 1 : 0);
+    hipLaunchKernelGGL(kern, dim3(first + second), dim3(512), kSmem, s, p, seg, ts, n_mtiles, kv_total, dq_total, first,
+                       kv_first ? 1 : 0, runs);
   }
   return launch_status();
 }

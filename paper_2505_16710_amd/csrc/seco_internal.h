@@ -28,14 +28,14 @@ struct AttnParams {
   float* part_ml;    // split path, forward: (reference max in log2 units, sum) per partial row, [n_splits, B, Hq, C, 2]
   float* tail_part;  // workspace, or NULL: dQ pass: sums of the row tiles beyond the first round (row_shares); dK/dV pass,
                      // after it: of the column tiles shared out among several workgroups
-  size_t tail_bytes; // room there; a function of the descriptor, not of the workspace that was passed
+  uint32_t tail_bytes; // room there (under 64 MiB); a function of the descriptor, not of the workspace that was passed
+  int rows_whole;    // row tiles beyond the first round divided: how many of a (batch, KV head)'s are not
   int n_splits;      // > 1 selects the split path
   int Cpad;          // C rounded up to 32: rows per head in the packed row space of the split path
   int B, Hq, Hkv, D, C, q_start, G;
   float scale;
   int64_t qs[3], os[3], kvs[3], gs[3];
   PendingDq* pending;   // backward, host side: a dQ pass that is announced but not launched yet
-  int rows_whole;       // row tiles beyond the first round divided: how many of a (batch, KV head)'s are not
 };
 
 // Column segments of the dK/dV pass: a run of cache rows that share one weight.
