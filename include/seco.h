@@ -351,8 +351,8 @@ int spaco_gather_row_weights(const int32_t* selected_host, int32_t n_selected, i
  */
 typedef enum seco_profile_kind {
   SECO_PROFILE_FWD = 0,     /* forward kernel */
-  SECO_PROFILE_BWD = 1,     /* dQ and dK/dV in one launch: every fp32 backward, bf16 calls with few rows and few cache
-                               tiles; such a call has no SECO_PROFILE_DQ or _DKDV launch (delta = rowsum(dO * O), which
+  SECO_PROFILE_BWD = 1,     /* dQ and dK/dV in one launch: every fp32 backward, bf16 calls of short chunks or with few
+                               cache tiles where that is expected to pay; such a call has no SECO_PROFILE_DQ or _DKDV launch (delta = rowsum(dO * O), which
                                had this entry once, is no launch of its own on any path) */
   SECO_PROFILE_DQ = 2,      /* dQ kernel */
   SECO_PROFILE_DKDV = 3,    /* dK/dV kernel with the gK/gV accumulation, and the merge of shared-out cache tiles */
@@ -387,8 +387,9 @@ size_t seco_workspace_bytes_preferred(const seco_desc* desc, int op);
  *       of workgroups would be at most half full
  *   [3] workgroups per such tile, at least (1: none); [2] * [3] * batch * n_kv_heads never exceeds the device's
  *       compute units
- * Three things they do not cover: a forward of at most 32 query rows per KV head (chunk_len * n_q_heads / n_kv_heads)
- * divides the cache by a rule of its own; a backward that runs in one launch (SECO_PROFILE_BWD) chooses its own number
+ * Four things they do not cover: a forward of at most 32 query rows per KV head (chunk_len * n_q_heads / n_kv_heads)
+ * divides the cache by a rule of its own; a forward or dQ pass with between one and two rounds of row tiles divides those
+ * beyond the first; a backward that runs in one launch (SECO_PROFILE_BWD) chooses its own number
  * of shares for both passes; a dK/dV pass whose tiles all fit one round, or whose estimated time falls, shares tiles
  * out further, by query rows.
  * Returns SECO_OK, or the status of an invalid desc; SECO_ERR_DTYPE for fp32 (its kernels have one shape).
