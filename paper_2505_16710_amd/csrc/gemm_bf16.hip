@@ -440,8 +440,9 @@ template <typename A, typename B> int launch_pair(GemmArgs a, GemmArgs b, hipStr
   hipLaunchKernelGGL(kern, dim3(ga + gb), dim3(512), smem, s, a, b, ta, tb, weight_first ? gb : ga, weight_first);
   return launch_status();
 }
+constexpr int kApart = 1;           // (no seco_status)
 // In one launch where the data gradient takes one of the small tiles and as many of its workgroups share a CU as by itself
-// (64 x 64 tiles with two slots: two; larger products would gain less than 5 %).  -1: not
+// (64 x 64 tiles with two slots: two; larger products would gain less than 5 %).  kApart: not
 template <int EPI> int pair(const GemmArgs& a, const GemmArgs& b, hipStream_t s) {
   using Wide = Ring<128, 128, 1, 3, 4, false, false, kAdd>;
   using Two = Ring<64, 64, 2, 2, 2, true, true, EPI>;
@@ -457,10 +458,10 @@ template <int EPI> int pair(const GemmArgs& a, const GemmArgs& b, hipStream_t s)
         else if constexpr (std::is_same_v<A, Two> && 2 * B::kSmem <= 160 * 1024 && B::kThreads == 512)
           return launch_pair<A, B>(a, b, s);
         else
-          return -1;
+          return kApart;
       });
     } else {
-      return -1;
+      return kApart;
     }
   });
 }
@@ -507,7 +508,7 @@ extern "C" int dec_gemm_grads(const void* dy, const void* w, void* dx, void* u, 
                    (int)K, (int)n, (int)M, (int)K, (int)n, (int)n, 0};
   hipStream_t s = static_cast<hipStream_t>(stream);
   int rc = u ? pair<kSiluBwd>(a, b, s) : pair<kStore>(a, b, s);
-  if (rc != -1) return rc;
+  if (rc != kApart) return rc;
   rc = u ? pick<true, true, kSiluBwd>(a, s) : pick<true, true, kStore>(a, s);
   return rc ? rc : pick<false, false, kAdd>(b, s);
 }
