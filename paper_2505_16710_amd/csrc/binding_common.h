@@ -117,6 +117,20 @@ inline Tensor like(const Tensor& t) { return at::empty_strided(t.sizes(), t.stri
 inline Tensor bytes(int64_t n, const Tensor& t) { return at::empty({n}, t.options().dtype(at::kByte).requires_grad(false)); }
 inline size_t nbytes(const Tensor& t) { return (size_t)t.numel() * t.element_size(); }
 
+// Scratch of one call, which works on it in stream s: taken from that stream's memory, whatever stream is current, since it
+// is given back as soon as the call is enqueued.
+inline Tensor scratch(int64_t n, const Tensor& t, void* s) {
+  const auto device = t.device().index();
+  if (!t.is_cuda() || s == c10::hip::getCurrentHIPStream(device).stream()) return bytes(n, t);
+  struct Back {
+    c10::hip::HIPStream to;
+    ~Back() { c10::hip::setCurrentHIPStream(to); }
+  } back{c10::hip::getCurrentHIPStream(device)};
+  c10::hip::setCurrentHIPStream(s ? c10::hip::getStreamFromExternal(static_cast<hipStream_t>(s), device)
+                                  : c10::hip::getDefaultHIPStream(device));
+  return bytes(n, t);
+}
+
 inline size_t workspace(const seco_desc& d, int op) {
   const size_t n = lib.seco_workspace_bytes(&d, op);
   if (n == (size_t)-1) check(SECO_ERR_SHAPE, "seco_workspace_bytes");

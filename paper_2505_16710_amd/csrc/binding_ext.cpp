@@ -61,15 +61,16 @@ PyObject* fwd(PyObject* const* a) {
   if (q.dim() != 4 || lse.sizes() != q.sizes().slice(0, 3)) raise(PyExc_ValueError, "lse must have shape [B, Hq, C]");
   check_shared(k, v, nullptr, nullptr, lse);
   const seco_desc d = chunk_desc(q, k, a[3], a[4], o, nullptr);
+  void* s = stream(a[7]);
   Tensor ws;
   if (a[8] == Py_None) {
     const size_t n = workspace(d, SECO_OP_FWD);
-    if (n > 0) ws = bytes((int64_t)n, q);
+    if (n > 0) ws = scratch((int64_t)n, q, s);
   } else if (a[8] != Py_False) {
     ws = tensor(a[8]);
   }
   check(lib.seco_chunk_attn_fwd(&d, ptr(q), ptr(k), ptr(v), ptr(o), fptr(lse), ws.defined() ? ptr(ws) : nullptr,
-                                ws.defined() ? nbytes(ws) : 0, stream(a[7])), "seco_chunk_attn_fwd");
+                                ws.defined() ? nbytes(ws) : 0, s), "seco_chunk_attn_fwd");
   PyObject* po = a[5] == Py_None ? THPVariable_Wrap(o) : (Py_INCREF(a[5]), a[5]);
   PyObject* pl = a[6] == Py_None ? THPVariable_Wrap(lse) : (Py_INCREF(a[6]), a[6]);
   return Py_BuildValue("NN", po, pl);
@@ -84,8 +85,8 @@ PyObject* bwd(PyObject* const* a) {
     raise(PyExc_ValueError, "o/d_o and q/d_q must share strides");
   check_shared(k, v, &gk, &gv, lse);
   const seco_desc d = chunk_desc(q, k, a[8], a[9], o, &gk);
-  const Tensor ws = a[11] == Py_None ? bytes((int64_t)std::max<size_t>(workspace(d, SECO_OP_BWD), 256), q) : tensor(a[11]);
   void* s = stream(a[12]);
+  const Tensor ws = a[11] == Py_None ? scratch((int64_t)std::max<size_t>(workspace(d, SECO_OP_BWD), 256), q, s) : tensor(a[11]);
   if (a[13] == Py_None) {
     check(lib.seco_chunk_attn_bwd(&d, ptr(q), ptr(k), ptr(v), ptr(o), fptr(lse), ptr(d_o), ptr(dq), fptr(gk), fptr(gv),
                                   ptr(ws), nbytes(ws), s), "seco_chunk_attn_bwd");
@@ -134,8 +135,8 @@ PyObject* bwd_gather(PyObject* const* a) {
   if (stats.scalar_type() != at::kFloat || !stats.is_contiguous() || stats.dim() != 4)
     raise(PyExc_ValueError, "row_stats must be a contiguous fp32 [2, B, Hq, stat_rows] tensor");
   const seco_desc d = chunk_desc(qc, k, a[8], a[9], o, &gk);
-  const Tensor ws = a[13] == Py_None ? bytes((int64_t)std::max<size_t>(workspace(d, SECO_OP_BWD), 256), qc) : tensor(a[13]);
   void* s = stream(a[14]);
+  const Tensor ws = a[13] == Py_None ? scratch((int64_t)std::max<size_t>(workspace(d, SECO_OP_BWD), 256), qc, s) : tensor(a[13]);
   const int32_t later = (int32_t)(q_rows.size(2) - C);
   if (a[15] != Py_None) {
     const std::vector<float> w = floats(a[15]);

@@ -1042,6 +1042,32 @@ def test_sparse_dq_many_runs_and_extreme_weights():
         assert err <= TOL["bf16"]["dq"]
 
 
+def test_scratch_of_a_call_on_another_stream_is_that_streams():
+    """A call takes its workspace for itself and gives it back when it is enqueued: from the memory of the stream it works on, or
+    the current stream's next tensor, and what that stream still does in memory freed before, would share it."""
+    g = torch.Generator(device=DEV).manual_seed(67)
+    rand = lambda *shape: torch.randn(*shape, device=DEV, generator=g).to(torch.bfloat16)
+    C, q_start, s = 1100, 2300, 128 ** -0.5
+    q, k, v, do = rand(1, 32, C, 128), rand(1, 8, q_start + C, 128), rand(1, 8, q_start + C, 128), rand(1, 32, C, 128)
+    gk, gv = (torch.zeros(1, 8, q_start + C, 128, device=DEV) for _ in range(2))
+    o, lse = seco.seco_chunk_attn_fwd(q, k, v, q_start, s)
+    dq = seco.seco_chunk_attn_bwd(q, k, v, o, lse, do, gk, gv, q_start, s)
+    need = seco.seco_workspace_bytes(seco.binding.make_desc(q, k, q_start, s), seco.binding.SECO_OP_FWD)
+    assert need > 0
+    torch.cuda.synchronize()
+    for call in (lambda st: seco.seco_chunk_attn_fwd(q, k, v, q_start, s, o=torch.empty_like(q), lse=torch.empty_like(lse), stream=st),
+                 lambda st: (seco.seco_chunk_attn_bwd(q, k, v, o, lse, do, gk.clone(), gv.clone(), q_start, s, d_q=torch.empty_like(q), stream=st), None)):
+        torch.cuda.synchronize()
+        torch.cuda.empty_cache()
+        side = torch.cuda.Stream()
+        side.wait_stream(torch.cuda.current_stream())
+        got, got_lse = call(side)
+        assert any(x["stream"] == side.cuda_stream and x["total_size"] >= need for x in torch.cuda.memory_snapshot())
+        assert torch.cuda.current_stream() != side
+        torch.cuda.synchronize()
+        assert torch.equal(got, dq) if got_lse is None else torch.equal(got, o) and torch.equal(got_lse, lse)
+
+
 @pytest.mark.parametrize("seed", range(12))
 def test_random_shapes_and_weights(seed):
     """Seeded random small configurations through every entry point of the backward: shapes that are not multiples
