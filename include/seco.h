@@ -88,7 +88,8 @@ typedef struct seco_desc {
  *   O = softmax_row(S) V;   LSE[r] = ln sum_c exp(S[r,c])  (natural log of the scaled scores).
  * q        in   [B, Hq, C, D]   (q_stride)
  * k_cache  in   [B, Hkv, >= q_start + C, D]   (kv_stride); v_cache alike
- * o        out  [B, Hq, C, D]   (o_stride), overwritten
+ * o        out  [B, Hq, C, D]   (o_stride), overwritten; may be q itself (o_stride equal to q_stride), and may overlap no
+ *          other input
  * lse      out  fp32 [B, Hq, C] contiguous (no strides are taken for it: a sliced view is not accepted), overwritten
  * ws       optional workspace, 256-byte aligned.  seco_workspace_bytes(desc, SECO_OP_FWD) is non-zero only for
  *          bf16 calls with so few query rows that the row tiles cannot fill the GPU (short chunks, as in the

@@ -626,9 +626,11 @@ int fwd_launch(const AttnParams& p, hipStream_t s) {
 // heads of 64, 256 rows at 768: 14.9 -> 11.7 us; 3 heads of 128, 76 rows at 560: 18.2 -> 13.8; 4 of 256, 200 at 400: 37.5 -> 25.0.
 // Backward: 64 + 128 tiles of head_dim 64 10.9 -> 10.1 us; 15 + 120 of 128 23.3 -> 19.1 (four); 28 + 252 of 64 18.1 -> 16.5 (two: the
 // others' CUs may be shared a little, 64 + 256 gain nothing); 120 + 120 of 128 by two 26.2 -> 28.1.
+// Not where O is written over an input: each of them would read query rows that another has overwritten.
 template <int NT>
 int fwd_nt(const AttnParams& p, hipStream_t s) {
   const int64_t n = (int64_t)((p.C + kRows - 1) / kRows) * p.Hq * p.B, cus = device_cus();
+  if (o_over_inputs(p, sizeof(float))) return fwd_launch<NT, NT>(p, s);
   if (n * 4 <= cus) return fwd_launch<NT, (NT + 3) / 4>(p, s);
   if (n * 2 <= cus) return fwd_launch<NT, (NT + 1) / 2>(p, s);
   return fwd_launch<NT, NT>(p, s);

@@ -38,6 +38,23 @@ struct AttnParams {
   PendingDq* pending;   // backward, host side: a dQ pass that is announced but not launched yet
 };
 
+// Memory that a [B, H, rows, D] tensor lies in, first byte to last (strides in elements, none negative).
+struct Span { uintptr_t begin, end; };
+inline Span span_of(const void* t, const int64_t st[3], int B, int H, int rows, int D, int elem_bytes) {
+  const uintptr_t last = (uintptr_t)(B - 1) * st[0] + (uintptr_t)(H - 1) * st[1] + (uintptr_t)(rows - 1) * st[2] + D;
+  return Span{reinterpret_cast<uintptr_t>(t), reinterpret_cast<uintptr_t>(t) + last * elem_bytes};
+}
+inline bool overlap(Span a, Span b) { return a.begin < b.end && b.begin < a.end; }
+// O may be written over Q: a workgroup that owns its rows reads Q before it writes O.  Several workgroups for the same rows
+// would read what another has written, so a forward that has such a form asks here first (spans, not elements: interleaved
+// tensors count as overlapping and only lose that form).
+inline bool o_over_inputs(const AttnParams& p, int elem_bytes) {
+  const Span o = span_of(p.o_out, p.os, p.B, p.Hq, p.C, p.D, elem_bytes);
+  return overlap(o, span_of(p.q, p.qs, p.B, p.Hq, p.C, p.D, elem_bytes)) ||
+         overlap(o, span_of(p.k, p.kvs, p.B, p.Hkv, p.q_start + p.C, p.D, elem_bytes)) ||
+         overlap(o, span_of(p.v, p.kvs, p.B, p.Hkv, p.q_start + p.C, p.D, elem_bytes));
+}
+
 // Column segments of the dK/dV pass: a run of cache rows that share one weight.
 // The table travels by value in the kernel arguments, so no device memory or
 // host-to-device copy is needed for SpaCO's selection.

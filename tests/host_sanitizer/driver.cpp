@@ -242,6 +242,32 @@ int main() {
     CHECK(rope_rotate(&d, 0, FAKE, FAKE, 0, 10000.f, 0, nullptr) == SECO_ERR_RANGE);
     CHECK(kvgrad_readout(&d, FAKEF, FAKEF, FAKE, FAKE, INFINITY, nullptr) == SECO_ERR_RANGE);
   }
+  // ---- where an output lies over an input ----
+  {
+    static char mem[1 << 20];
+    seco::AttnParams p;
+    std::memset(&p, 0, sizeof(p));
+    p.B = 2; p.Hq = 4; p.Hkv = 2; p.D = 64; p.C = 20; p.q_start = 30;
+    const int64_t packed[3] = {4 * 20 * 64, 20 * 64, 64}, kv[3] = {2 * 50 * 64, 50 * 64, 64};
+    for (int i = 0; i < 3; ++i) p.qs[i] = p.os[i] = packed[i], p.kvs[i] = kv[i];
+    const int q_bytes = 2 * 4 * 20 * 64 * 4, kv_bytes = 2 * 2 * 50 * 64 * 4;
+    p.q = mem; p.k = mem + q_bytes; p.v = mem + q_bytes + kv_bytes;
+    for (const int at : {q_bytes + 2 * kv_bytes, q_bytes + 2 * kv_bytes + 4096}) {      // behind all of them
+      p.o_out = mem + at;
+      CHECK(!seco::o_over_inputs(p, 4));
+    }
+    for (const int at : {0, 16, q_bytes - 16, q_bytes, q_bytes + kv_bytes, q_bytes + 2 * kv_bytes - 16}) {
+      p.o_out = mem + at;
+      CHECK(seco::o_over_inputs(p, 4));
+    }
+    p.q = mem + (1 << 19); p.o_out = mem + (1 << 19) - q_bytes;                        // right before q
+    CHECK(!seco::o_over_inputs(p, 4));
+    p.os[1] += 4;                                                                       // heads 16 bytes further apart
+    CHECK(seco::o_over_inputs(p, 4));
+    p.C = 1; p.B = p.Hq = 1;                                                            // (strides that reach no row do not count)
+    p.os[0] = p.os[1] = (int64_t)1 << 61;
+    CHECK(!seco::o_over_inputs(p, 4));
+  }
   std::puts("host sanitizer run: all checks passed");
   return 0;
 }

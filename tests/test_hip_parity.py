@@ -98,6 +98,27 @@ def test_fp32_row_tiles_with_several_workgroups(D, Hq, C, q_start):
         assert max_rel(to_host(gk), ref[1] * factor) <= 1e-4 and max_rel(to_host(gv), ref[2] * factor) <= 1e-4
 
 
+@pytest.mark.parametrize("dtype,D,Hq,Hkv,C,q_start", [
+    ("f32", 64, 4, 4, 256, 768),        # 64 row tiles: four workgroups for each where O lies elsewhere
+    ("f32", 128, 8, 2, 250, 100),       # 128: two
+    ("f32", 256, 3, 3, 76, 560),
+    ("bf16", 128, 8, 2, 4, 900),        # at most 32 rows per KV head
+    ("bf16", 128, 8, 2, 100, 3000),     # the cache divided, merged
+    ("bf16", 128, 64, 8, 513, 1500),    # row tiles beyond one round divided
+    ("bf16", 128, 32, 8, 1000, 1000),   # 8 and 4 wavefronts, whole row tiles
+    ("bf16", 128, 32, 8, 2100, 0),
+])
+def test_forward_with_o_written_over_q(dtype, D, Hq, Hkv, C, q_start):
+    """The same bits as into a buffer of its own (fp32: the same sums, in whole row tiles)."""
+    g = torch.Generator(device=DEV).manual_seed(14)
+    t = torch.float32 if dtype == "f32" else torch.bfloat16
+    rand = lambda *shape: torch.randn(*shape, device=DEV, generator=g).to(t)
+    q, k, v = rand(1, C, Hq, D).transpose(1, 2), rand(1, Hkv, q_start + C, D), rand(1, Hkv, q_start + C, D)
+    o, lse = seco.seco_chunk_attn_fwd(q, k, v, q_start, D ** -0.5, o=torch.empty_like(q))
+    over, lse_over = seco.seco_chunk_attn_fwd(q, k, v, q_start, D ** -0.5, o=q)
+    assert over is q and torch.equal(o, q) and torch.equal(lse, lse_over)
+
+
 @pytest.mark.parametrize("D", [8, 32, 64, 80, 112, 128, 176, 256])
 @pytest.mark.parametrize("rising", [True, False])
 def test_fp32_reference_moves_along_the_cache(D, rising):
