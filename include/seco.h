@@ -105,7 +105,8 @@ int seco_chunk_attn_fwd(const seco_desc* desc, const void* q, const void* k_cach
 /*
  * Backward of one chunk for SeCO (Alg. 1, "backprop(J_i)" at the attention layer).
  * With P = exp(S - LSE), delta = rowsum(dO * O), dS = P * (dO V^T - delta):
- *   d_q  out  [B, Hq, C, D] (q_stride), overwritten:  dQ = s * dS K          (all visible columns)
+ *   d_q  out  [B, Hq, C, D] (q_stride), overwritten:  dQ = s * dS K          (all visible columns); may be o itself
+ *             (o_stride equal to q_stride; the passes are then never one launch), and may overlap no other input
  *   gk   i/o  fp32 [B, Hkv, >= q_start + C, D] (g_stride): gK[c] += s * sum_{heads of group} dS^T Q
  *   gv   i/o  same:                                        gV[c] += sum_{heads of group} P^T dO
  * for every visible cache row c.  gk/gv are accumulated into, never overwritten; rows at or

@@ -651,6 +651,7 @@ template <int NT, typename Runs>
 int bwd_parts(const AttnParams& p, const Runs& dq_runs, const Runs& seg, int64_t n_dq, int64_t n_kv, hipStream_t s) {
   const int64_t cus = device_cus();
   if constexpr (NT < 16 || std::is_same<Runs, OneRun>::value) {    // (with the table scalar registers are short at the longest rows)
+    if (dq_over_inputs(p, sizeof(float))) return bwd_launch<NT, NT>(p, dq_runs, seg, n_dq, n_kv, s);
     if (n_dq * 4 + n_kv <= cus) return bwd_launch<NT, (NT + 3) / 4>(p, dq_runs, seg, n_dq, n_kv, s);
     if (n_dq * 2 + n_kv <= cus + cus / 4) return bwd_launch<NT, (NT + 1) / 2>(p, dq_runs, seg, n_dq, n_kv, s);
   }
@@ -683,7 +684,8 @@ int bwd_nt(const AttnParams& p, const SegTable& dq_runs, const SegTable& seg, bo
 int launch_fwd_f32(const AttnParams& p, hipStream_t s) { SECO_F32_DISPATCH(fwd_nt, p, s) }
 
 // Both passes of the fp32 backward are one launch: dQ is noted in p.pending and goes out with dK/dV (launch_dkdv_f32;
-// with an empty table when there are no cache rows to cover).  rowsum(dO * O) is taken from O and dO where it is used.
+// with an empty table when there are no cache rows to cover).  rowsum(dO * O) is taken from O and dO where it is used, so a
+// dQ that lies over one of them goes out behind the last dK/dV table, in a launch of its own.
 int launch_dq_f32(const AttnParams& p, const SegTable* dq_runs, hipStream_t) {
   SegTable& runs = p.pending->runs;
   runs = SegTable{};
@@ -697,9 +699,9 @@ int launch_dq_f32(const AttnParams& p, const SegTable* dq_runs, hipStream_t) {
 
 int launch_dkdv_f32(const AttnParams& p, const SegTable& seg, hipStream_t s) {
   static_assert(kColTileF32 == kRows, "one workgroup per column tile");
-  const bool dq = p.pending->dq;
-  p.pending->dq = false;
-  if (!dq && seg.tile_begin[seg.n] == 0) return SECO_OK;
+  const bool rows = seg.tile_begin[seg.n] > 0, dq = p.pending->dq && !(rows && dq_over_inputs(p, sizeof(float)));
+  if (dq) p.pending->dq = false;
+  if (!dq && !rows) return SECO_OK;
   SECO_F32_DISPATCH(bwd_nt, p, p.pending->runs, seg, dq, s)
 }
 

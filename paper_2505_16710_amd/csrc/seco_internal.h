@@ -54,6 +54,16 @@ inline bool o_over_inputs(const AttnParams& p, int elem_bytes) {
          overlap(o, span_of(p.k, p.kvs, p.B, p.Hkv, p.q_start + p.C, p.D, elem_bytes)) ||
          overlap(o, span_of(p.v, p.kvs, p.B, p.Hkv, p.q_start + p.C, p.D, elem_bytes));
 }
+// Likewise dQ, which may be written over O: the dK/dV workgroups that run beside it in one launch read O too (as do several
+// workgroups for the same rows).
+inline bool dq_over_inputs(const AttnParams& p, int elem_bytes) {
+  const Span dq = span_of(p.d_q, p.qs, p.B, p.Hq, p.C, p.D, elem_bytes);
+  return overlap(dq, span_of(p.q, p.qs, p.B, p.Hq, p.C, p.D, elem_bytes)) ||
+         overlap(dq, span_of(p.o, p.os, p.B, p.Hq, p.C, p.D, elem_bytes)) ||
+         overlap(dq, span_of(p.d_o, p.os, p.B, p.Hq, p.C, p.D, elem_bytes)) ||
+         overlap(dq, span_of(p.k, p.kvs, p.B, p.Hkv, p.q_start + p.C, p.D, elem_bytes)) ||
+         overlap(dq, span_of(p.v, p.kvs, p.B, p.Hkv, p.q_start + p.C, p.D, elem_bytes));
+}
 
 // Column segments of the dK/dV pass: a run of cache rows that share one weight.
 // The table travels by value in the kernel arguments, so no device memory or

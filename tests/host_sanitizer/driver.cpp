@@ -260,6 +260,15 @@ int main() {
       p.o_out = mem + at;
       CHECK(seco::o_over_inputs(p, 4));
     }
+    p.o = mem + (1 << 18); p.d_o = mem + (1 << 19);
+    for (const int at : {q_bytes + 2 * kv_bytes, (1 << 18) - q_bytes, (1 << 18) + q_bytes, (1 << 19) - q_bytes, (1 << 19) + q_bytes}) {
+      p.d_q = mem + at;
+      CHECK(!seco::dq_over_inputs(p, 4));
+    }
+    for (const int at : {0, q_bytes, q_bytes + kv_bytes, 1 << 18, (1 << 18) + q_bytes - 16, 1 << 19, (1 << 19) - q_bytes + 16}) {
+      p.d_q = mem + at;
+      CHECK(seco::dq_over_inputs(p, 4));
+    }
     p.q = mem + (1 << 19); p.o_out = mem + (1 << 19) - q_bytes;                        // right before q
     CHECK(!seco::o_over_inputs(p, 4));
     p.os[1] += 4;                                                                       // heads 16 bytes further apart

@@ -119,6 +119,44 @@ def test_forward_with_o_written_over_q(dtype, D, Hq, Hkv, C, q_start):
     assert over is q and torch.equal(o, q) and torch.equal(lse, lse_over)
 
 
+@pytest.mark.parametrize("dtype,D,Hq,Hkv,C,k,weights", [
+    ("f32", 64, 4, 2, 256, 4, "none"),       # both passes in one launch where dQ lies elsewhere, dQ in parts
+    ("f32", 128, 3, 3, 33, 7, "some"),
+    ("f32", 32, 2, 1, 16, 110, "runs"),      # 56 runs of weights: two tables
+    ("f32", 32, 4, 4, 64, 5, "zero"),        # dQ alone
+    ("bf16", 128, 32, 8, 745, 1, "none"),    # one launch: whole row tiles behind the column tiles
+    ("bf16", 128, 8, 8, 32, 1, "none"),      # short
+    ("bf16", 128, 8, 8, 64, 101, "none"),    # in front of several rounds
+    ("bf16", 128, 8, 2, 40, 30, "sparse"),
+    ("bf16", 128, 2, 1, 32, 110, "runs"),
+    ("bf16", 128, 32, 8, 1024, 4, "none"),   # two launches
+])
+def test_backward_with_dq_written_over_o(dtype, D, Hq, Hkv, C, k, weights):
+    """gK and gV have the bits of the call with a dQ of its own, dQ too in fp32; in bf16 it may be summed in other shares: two
+    fp32 sums that differ by their order, each rounded once, and one bf16 step (2^-7 of the element) apart where they straddle a tie."""
+    g = torch.Generator(device=DEV).manual_seed(15)
+    t = torch.float32 if dtype == "f32" else torch.bfloat16
+    rand = lambda *shape: torch.randn(*shape, device=DEV, generator=g).to(t)
+    N, s0, s = k * C, (k - 1) * C, D ** -0.5
+    q, do, kc, vc = rand(1, Hq, C, D), rand(1, Hq, C, D), rand(1, Hkv, N, D), rand(1, Hkv, N, D)
+    o, lse = seco.seco_chunk_attn_fwd(q, kc, vc, s0, s)
+    w = {"some": [float(i % 3) for i in range(k)], "runs": [0.0 if i % 2 else 1.0 + 0.05 * i for i in range(k)],
+         "zero": [0.0] * k, "sparse": [1.0] * k}.get(weights)
+    wq = [2.0 if i % 10 == 3 else 0.0 for i in range(k - 1)] + [1.0] if weights == "sparse" else None
+    def run(o, d_q):
+        gk, gv = (torch.zeros(1, Hkv, N, D, device=DEV) for _ in range(2))
+        args = (q, kc, vc, o, lse, do, gk, gv, s0, s)
+        dq = seco.seco_chunk_attn_bwd(*args, d_q=d_q) if w is None else seco.spaco_chunk_attn_bwd(*args, w, C, d_q=d_q, dq_weight=wq)
+        return dq, gk, gv
+    apart = run(o, None)
+    over = run(o, o)
+    assert over[0] is o and torch.equal(apart[1], over[1]) and torch.equal(apart[2], over[2])
+    if dtype == "f32":
+        assert torch.equal(apart[0], over[0])
+    else:
+        assert max_rel(to_host(over[0]), to_host(apart[0])) <= 2 ** -7
+
+
 @pytest.mark.parametrize("D", [8, 32, 64, 80, 112, 128, 176, 256])
 @pytest.mark.parametrize("rising", [True, False])
 def test_fp32_reference_moves_along_the_cache(D, rising):
