@@ -91,6 +91,9 @@ typedef struct seco_desc {
  * o        out  [B, Hq, C, D]   (o_stride), overwritten; may be q itself (o_stride equal to q_stride), and may overlap no
  *          other input
  * lse      out  fp32 [B, Hq, C] contiguous (no strides are taken for it: a sliced view is not accepted), overwritten
+ * Range of V: un-normalised sums of exponentials times V are kept in fp32.  fp32 calls give finite results while (visible
+ * rows) * max |V| < 2^128.  bf16 calls let exponentials grow to 2^40 per tile before they rescale, so they need
+ * (visible rows) * max |V| < 2^92; beyond, O may come out infinite or NaN.
  * ws       optional workspace, 256-byte aligned.  seco_workspace_bytes(desc, SECO_OP_FWD) is non-zero only for
  *          bf16 calls with so few query rows that the row tiles cannot fill the GPU (short chunks, as in the
  *          chunk-size study of Sec. 6.3), or with more of them than fill it once but not twice (at most 32.5 MiB

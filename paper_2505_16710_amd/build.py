@@ -20,6 +20,7 @@ SOURCES = [
     "seco_api.hip",
     "seco_select.cpp",
     "elementwise.hip",
+    "fwd_f32.hip",
     "kernels_f32.hip",
     "fwd_bf16.hip",
     "fwd4_bf16.hip",

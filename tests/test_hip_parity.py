@@ -175,6 +175,22 @@ def test_fp32_reference_moves_along_the_cache(D, rising):
     check(got, A.seco_layer(x["q"], x["k"], x["v"], x["do"], C, s), "f32", f"f32 ramp {D,rising}")
 
 
+@pytest.mark.parametrize("D", [8, 32, 64, 80, 112, 128, 176, 256])
+@pytest.mark.parametrize("Hq", [1, 2, 4])       # four, two workgroups and one for a row tile
+def test_fp32_forward_of_values_near_the_end_of_the_range(D, Hq):
+    """Scores that climb by 40 in log2 units, most of it below where the reference moves: weights of up to 2^32 on values of
+    2^100, whose sums leave fp32 although O does not.  Rows 0 .. 699 in one call, and O as exact as with small values."""
+    N, s = 700, 1 / np.sqrt(D)
+    x = small_layer(16, 1, Hq, 1, N, D, "f32")
+    x["q"][..., 0] = 32.0
+    x["k"][..., 0] = 40 * np.log(2) * np.arange(N) / (N - 1) / (32.0 * s)
+    x["v"] = x["v"] * np.float32(2.0 ** 100)
+    o, lse = seco.seco_chunk_attn_fwd(*(to_dev(x[n], "f32") for n in ("q", "k", "v")), 0, s)
+    ref_o, ref_lse = A.chunk_attn_fwd(x["q"], x["k"], x["v"], 0, s)
+    assert np.isfinite(to_host(o)).all()
+    assert max_rel(to_host(o), ref_o) <= 1e-4 and max_rel(to_host(lse), ref_lse) <= 1e-4
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,N,C", [
     (1, 4, 1, 512, 256),     # aligned, G = 4
     (2, 4, 2, 640, 256),     # short last chunk (128 rows)

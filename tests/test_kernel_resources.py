@@ -13,7 +13,8 @@ import pytest
 from paper_2505_16710_amd import build as B
 
 KERNEL_FILES = ["fwd_bf16.hip", "fwd4_bf16.hip", "fwd4_split_bf16.hip", "fwd8_shares_bf16.hip", "bwd_dq_bf16.hip", "bwd_dkdv_bf16.hip", "bwd_fused_bf16.hip",
-                "fwd_small_bf16.hip", "gemm_bf16.hip", "kernels_f32.hip"]
+                "fwd_small_bf16.hip", "gemm_bf16.hip", "fwd_f32.hip",
+                "kernels_f32.hip"]
 # blocks of 16 of the head_dim from which on one wavefront per SIMD is taken
 ONE_WAVE = {"fwd_f32_kernel": 16, "bwd_f32_kernel": 8}
 
