@@ -608,23 +608,5 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
   }
 }
 
-// Host side: iterations of the last column tiles
-template <typename Cfg, bool ROWS>
-IterRuns tile_iterations(const AttnParams& p, const SegTable& seg, const RowRuns& rr) {
-  // iterations of a column tile (as the kernel counts them)
-  auto iters = [&](int tile) {
-    int si = 0;
-    while (si + 1 < seg.n && tile >= seg.tile_begin[si + 1]) ++si;
-    const int c0 = seg.col_begin[si] + (tile - seg.tile_begin[si]) * Cfg::kCols;
-    const int r0 = (c0 > p.q_start ? c0 - p.q_start : 0) / Cfg::kBQ * Cfg::kBQ;
-    if (!ROWS) return ((p.C - r0 + Cfg::kBQ - 1) / Cfg::kBQ) * p.G;
-    int n = 0;
-    for (int i = 0; i < rr.n; ++i)
-      if (rr.end[i] > r0) n += (rr.end[i] - (rr.begin[i] > r0 ? rr.begin[i] : r0) + Cfg::kBQ - 1) / Cfg::kBQ;
-    return n * p.G;
-  };
-  return iter_runs(seg.tile_begin[seg.n], iters);
-}
-
 }  // namespace
 }  // namespace seco

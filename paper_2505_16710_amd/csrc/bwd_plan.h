@@ -1,0 +1,232 @@
+// How a bf16 backward call is laid out (host arithmetic only): whether dQ and dK/dV run in one launch, in how many shares a row
+// tile of dQ goes, and which column tiles of dK/dV are shared out.
+#pragma once
+#include <algorithm>
+
+#include "seco_internal.h"
+
+namespace seco {
+namespace {
+
+constexpr size_t kSlotBytes = (size_t)2 * kColTileBf16 * 128 * sizeof(float);
+int slots_in(size_t bytes) { return (int)std::min(bytes / kSlotBytes, (size_t)device_cus()); }
+
+// Iterations of the last column tiles
+template <typename Cfg, bool ROWS>
+IterRuns tile_iterations(const AttnParams& p, const SegTable& seg, const RowRuns& rr) {
+  // iterations of a column tile (as the kernel counts them)
+  auto iters = [&](int tile) {
+    int si = 0;
+    while (si + 1 < seg.n && tile >= seg.tile_begin[si + 1]) ++si;
+    const int c0 = seg.col_begin[si] + (tile - seg.tile_begin[si]) * Cfg::kCols;
+    const int r0 = (c0 > p.q_start ? c0 - p.q_start : 0) / Cfg::kBQ * Cfg::kBQ;
+    if (!ROWS) return ((p.C - r0 + Cfg::kBQ - 1) / Cfg::kBQ) * p.G;
+    int n = 0;
+    for (int i = 0; i < rr.n; ++i)
+      if (rr.end[i] > r0) n += (rr.end[i] - (rr.begin[i] > r0 ? rr.begin[i] : r0) + Cfg::kBQ - 1) / Cfg::kBQ;
+    return n * p.G;
+  };
+  return iter_runs(seg.tile_begin[seg.n], iters);
+}
+
+// Both passes of a dense call: in one launch with dq_splits workgroups per row tile for dQ (0: one after the other), and
+// the column tiles that are shared out.
+struct BwdPlan {
+  int dq_splits;
+  bool kv_first;
+  TailSplit ts;
+};
+// Column tiles for a round or more (n_kv of them, iters iterations each): in how many shares a row tile of dQ joins them
+// in one launch, dQ first; 0: not.  The column tiles of a round all start together and reach the read-modify-write of
+// gK / gV together, and the last round is seldom full; dQ's workgroups, of another length, fill it and put them out of step.
+// Shares: the fewest that end within 0.9 of the time the column tiles take (few workgroups, few partial sums).  Against it
+// stand the row statistics, computed anew in every iteration: beyond 12 iterations, or with a single full round of more than
+// 4, some shapes lost 3 - 10 %.  Both sides in microseconds as fitted to shapes of 16 - 1000 rows on 256 - 2560 tiles (4 % off);
+// one launch where it comes out 3 % ahead: 210 of 345 shapes, 1.14 times as fast, none more than 1.3 % slower.  Two -> one, us:
+//   32/8 heads  32 at 16256: 126 -> 110   64 at 8000: 75 -> 62   128 at 4000: 66 -> 53   128 at 16256: 175 (not taken: 177)
+//   8/8  128 at 4000: 43 -> 32            16/8  256 at 4000: 68 -> 55                    16/2  64 at 32000: 105 -> 92
+template <typename F>
+int rounds_in_one_launch(int n_kv, int iters, int items, int tiles, int max_splits, const F& dq_wgs) {
+  const float cus = (float)device_cus(), kv = n_kv / cus;
+  if (iters > (n_kv <= device_cus() ? 4 : 12)) return 0;
+  int n = 1;
+  while (n < max_splits && 8.f + 2.7f * ((tiles + n - 1) / n) > 0.9f * kv * (14.f + 2.f * iters)) ++n;
+  const int full = n_kv / device_cus();
+  const float tail = kv - full;
+  const float rest = tail > 0.f ? 9.2f + 0.6f * iters + tail * (5.6f + 1.7f * iters) : 0.f;
+  const float apart = 12.2f + full * (15.2f + 2.2f * iters) + rest + 1.7f * items * tiles / cus;
+  const float one = 5.3f + 2.3f * dq_wgs(n) * tiles / (n * cus) + kv * (14.f + 2.2f * iters) + 0.6f * iters;
+  return 1.03f * one < apart ? n : 0;
+}
+
+// When the last of a row of workgroups ends on `places` that take them in order: the places by the time they are free at, those
+// within a quarter of a microsecond as one.
+class Schedule {
+ public:
+  static constexpr int kMost = 64;
+  explicit Schedule(int places) : n_(1) { at_[0] = 0.f, of_[0] = places; }
+  void run(float time, int count) {
+    while (count > 0) {
+      const int k = std::min(of_[0], count);
+      const float t = at_[0] + time;
+      count -= k;
+      if ((of_[0] -= k) == 0) {
+        --n_;
+        std::copy(at_ + 1, at_ + 1 + n_, at_);
+        std::copy(of_ + 1, of_ + 1 + n_, of_);
+      }
+      int i = n_;
+      while (i > 0 && at_[i - 1] > t + 0.25f) --i;
+      if (i > 0 && at_[i - 1] >= t - 0.25f) {
+        of_[i - 1] += k;
+      } else {
+        std::copy_backward(at_ + i, at_ + n_, at_ + n_ + 1);
+        std::copy_backward(of_ + i, of_ + n_, of_ + n_ + 1);
+        at_[i] = t, of_[i] = k;
+        ++n_;
+      }
+    }
+  }
+  float end() const { return at_[n_ - 1]; }
+
+ private:
+  float at_[kMost + 1];
+  int of_[kMost + 1], n_;
+};
+
+// Fewer column tiles than a round, but more workgroups in all than fit at once: the plan of sharing out the column tiles with
+// which both passes in one launch, dK/dV first, dQ in whole row tiles behind it, are expected to end before the two would
+// one after the other; false: none.  Both are laid out workgroup by workgroup on the compute units of an XCD (whole units
+// of a batch and KV head each, in the order of the items).  The times, in microseconds, are fitted to 74 shapes of 130 - 3200
+// rows (3 - 4 % off); one launch where it comes out 5 % ahead, and below 200 us, from where gains and errors were both about 3 %.
+// Of 400 other random shapes with less than a round of column tiles it takes 76, 1.13 times as fast, none more than 1 %
+// slower; two -> one, us:
+//   32/8  745 at 0: 50.9 -> 39.1   873 at 0: 55.9 -> 43.2   1482 at 445: 134.5 -> 131   16/8  1174 at 0: 58 -> 45
+//   8/8  2156 at 5: 84.9 -> 63.9   x 2  1011 at 96: 58.6 -> 40.9
+bool one_launch_behind_column_tiles(const AttnParams& p, const IterRuns& runs, int n_ctiles, int slots, const SharePlan& apart_plan,
+                                    SharePlan& one_plan) {
+  const int n_units = p.B * p.Hkv, places = device_cus() / 8, mtiles = (p.C + 127) / 128, heads = p.B * p.Hq / 8;
+  const int row_wgs = p.B * p.Hq * mtiles;
+  if (n_units % 8 != 0 || places > Schedule::kMost || row_wgs >= 2 * device_cus()) return false;
+  if (row_wgs > device_cus() && p.q_start >= 2 * p.C) return false;      // (row_shares divides dQ's second round)
+  auto column_tiles = [&](Schedule& sc, const SharePlan& plan, float wg, float iter) {
+    for (int u = 0; u < n_units / 8; ++u) {
+      int tile = 0, i = 0;
+      for (int r = 0; r < runs.n; ++r)
+        for (int c = 0; c < runs.count[r]; ++c, ++tile) {
+          const bool listed = tile >= n_ctiles - plan.n_tiles;
+          const int k = listed ? plan.first[i + 1] - plan.first[i] : 1;
+          if (listed) ++i;
+          sc.run(wg + iter * runs.iters[r] / k, k);
+        }
+    }
+  };
+  auto row_tiles = [&](Schedule& sc, float wg, float tile) {
+    for (int mt = mtiles; mt > 0; --mt) sc.run(wg + tile * ((p.q_start + std::min(mt * 128, p.C) + 127) / 128), heads);
+  };
+  auto merge = [&](const SharePlan& plan, float each) { return plan.n_shared > 0 ? 4.f + each * plan.first[plan.n_shared] * n_units : 0.f; };
+  Schedule kv(places);
+  column_tiles(kv, apart_plan, 14.9f, 1.7f);
+  float apart = kv.end() + merge(apart_plan, 0.03f) - 1.6f;
+  if (p.n_splits > 1) {
+    const int wgs = split_plan(p.B, p.Hkv, p.G, p.C).items * p.n_splits, tiles = (p.q_start + p.C + 127) / 128;
+    apart += (wgs + device_cus() - 1) / device_cus() * (7.1f + 1.7f * ((tiles + p.n_splits - 1) / p.n_splits)) + 4.f + 0.02f * wgs;
+  } else {
+    Schedule dq(places);
+    row_tiles(dq, 7.1f, 1.7f);
+    apart += dq.end();
+  }
+  if (apart > 200.f) return false;
+  float best = apart / 1.05f;
+  int last = -1;
+  bool found = false;
+  for (int cus : {96, 160, 256}) {
+    const ShareChoice c = choose_shares(runs, n_ctiles, n_units, cus * device_cus() / 256, slots, 1, false, 8.5f, 1.8f);
+    if (c.time < 0.f || c.per == last) continue;
+    last = c.per;
+    const SharePlan plan = make_shares(runs, n_ctiles, c.per);
+    Schedule both(places);
+    column_tiles(both, plan, 15.7f, 1.8f);
+    row_tiles(both, 8.2f, 2.4f);
+    const float t = both.end() + merge(plan, 0.024f) - 4.7f;
+    if (t < best) {
+      best = t;
+      one_plan = plan;
+      found = true;
+    }
+  }
+  return found;
+}
+
+// With column tiles for less than a round, one launch is taken when all workgroups of both passes fit the chip at one per
+// CU and the longer pass, with the extra work, is expected to end before the two would one after the other: with more
+// workgroups than CUs the two halves of the grid would queue behind each other on some CUs (16/2 heads, chunk 704 at 5632:
+// 7% slower in one launch).  The passes divide the CUs: for every number of shares of a dQ row tile the column tiles are
+// shared out over the rest.  Times in microseconds as measured: a dQ workgroup 7.5 + 2.5 per tile of 128 cache rows, a
+// dK/dV workgroup that computes its row statistics 8.5 + 1.8 per iteration.
+template <typename Cfg>
+BwdPlan plan_bwd(const AttnParams& p, const SegTable& seg) {
+  const int cus = device_cus(), n_units = p.B * p.Hkv, n_ctiles = seg.tile_begin[seg.n];
+  RowRuns none;
+  none.n = 0;
+  const IterRuns runs = tile_iterations<Cfg, false>(p, seg, none);
+  BwdPlan best;
+  best.dq_splits = 0;
+  best.kv_first = true;
+  best.ts.part = p.tail_part;
+  float kv_alone = 0.f;
+  best.ts.plan = share_plan(runs, n_units, n_ctiles, p.G, p.C, slots_in(p.tail_bytes), kv_alone);
+  const SplitPlan sp = split_plan(p.B, p.Hkv, p.G, p.C);
+  if (!p.pending) return best;
+  const int tiles = (p.q_start + p.C + 127) / 128;
+  const size_t dq_bytes = (size_t)p.B * p.Hq * p.C * 128 * sizeof(float);
+  auto dq_wgs = [&](int n) { return n > 1 ? sp.items * n : p.B * p.Hq * ((p.C + 127) / 128); };
+  auto dq_part = [&](int n) { return n > 1 ? (n * dq_bytes + 255) / 256 * 256 : (size_t)0; };
+  if ((int64_t)n_units * n_ctiles >= cus) {
+    if (sp.items >= cus) return best;
+    const int n = rounds_in_one_launch(n_units * n_ctiles, runs.iters[0], sp.items, tiles, p.n_splits, dq_wgs);
+    if (n > 0 && dq_part(n) <= p.tail_bytes) {
+      best.dq_splits = n;
+      best.kv_first = false;
+      best.ts.part = p.tail_part + dq_part(n) / sizeof(float);
+      best.ts.plan = share_plan(runs, n_units, n_ctiles, p.G, p.C, slots_in(p.tail_bytes - dq_part(n)), kv_alone);
+    }
+    return best;
+  }
+  auto dq_time = [&](int n) { return 7.5f + 2.5f * ((tiles + n - 1) / n); };
+  auto merge_time = [&](int n) { return n > 1 ? 4.f + 0.02f * dq_wgs(n) : 0.f; };
+  float best_t = (dq_wgs(p.n_splits) + cus - 1) / cus * dq_time(p.n_splits) + merge_time(p.n_splits) + kv_alone + 2.f;
+  int per = 0;
+  for (int n = 1; n <= p.n_splits && dq_wgs(n) + n_units * n_ctiles <= cus; ++n) {
+    const size_t used = dq_part(n);
+    if (used > p.tail_bytes) break;
+    const ShareChoice c = choose_shares(runs, n_ctiles, n_units, cus - dq_wgs(n), slots_in(p.tail_bytes - used), 1, true, 8.5f, 1.8f);
+    // (both merges are one launch)
+    const float t = std::max(dq_time(n), c.longest) + (c.time - c.longest) + (n > 1 ? merge_time(n) - (c.per ? 4.f : 0.f) : 0.f);
+    if (c.time >= 0.f && t < best_t) {
+      best_t = t;
+      best.dq_splits = n;
+      best.kv_first = c.longest >= dq_time(n);
+      best.ts.part = p.tail_part + used / sizeof(float);
+      per = c.per;
+    }
+  }
+  if (best.dq_splits > 0) {
+    best.ts.plan = make_shares(runs, n_ctiles, per);
+  } else if (SharePlan plan; n_ctiles <= runs.n_tiles && one_launch_behind_column_tiles(p, runs, n_ctiles, slots_in(p.tail_bytes), best.ts.plan, plan)) {
+    best.dq_splits = 1;
+    best.ts.plan = plan;
+  }
+  return best;
+}
+
+// dQ over selected columns takes the place of n shares per row tile of the dense pass: as many as keep a share's length,
+// and whole row tiles only where those are no more workgroups
+int sparse_shares(const AttnParams& p, const SegTable& runs, int n) {
+  const int tiles = (p.q_start + p.C + 127) / 128, m = std::max(1, (visited_tiles(p, runs) * n + tiles - 1) / tiles);
+  if (n == 1 || m > 1) return std::min(m, n);
+  return p.B * p.Hq * ((p.C + 127) / 128) <= n * split_plan(p.B, p.Hkv, p.G, p.C).items ? 1 : 2;
+}
+
+}  // namespace
+}  // namespace seco
