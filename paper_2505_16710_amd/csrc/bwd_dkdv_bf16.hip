@@ -50,9 +50,8 @@ int launch_dkdv_bf16(const AttnParams& p, const SegTable& seg, hipStream_t s) {
   if (dq) p.pending->dq = false;
   const SegTable* runs = dq && p.pending->sparse ? &p.pending->runs : nullptr;
   if (seg.tile_begin[seg.n] == 0) return dq ? launch_dq_bf16_now(p, runs, s) : SECO_OK;
-  // (over selected columns, where dQ ran with an earlier table or lies over O, the sums of gK / gV are divided as they would
-  // be otherwise: the same bits)
-  const BwdPlan plan = plan_bwd<Cfg>(p, seg);
+  // (where dQ visits selected columns or lies over O, the sums of gK / gV are divided as they would be otherwise: the same bits)
+  const BwdPlan plan = plan_bwd<Cfg>(p, seg, dq);
   if (dq && plan.dq_splits > 0 && !dq_over_inputs(p, 2)) {
     AttnParams pf = p;
     pf.n_splits = runs ? sparse_shares(p, *runs, plan.dq_splits) : plan.dq_splits;

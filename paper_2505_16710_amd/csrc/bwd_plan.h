@@ -164,8 +164,9 @@ bool one_launch_behind_column_tiles(const AttnParams& p, const IterRuns& runs, i
 // 7% slower in one launch).  The passes divide the CUs: for every number of shares of a dQ row tile the column tiles are
 // shared out over the rest.  Times in microseconds as measured: a dQ workgroup 7.5 + 2.5 per tile of 128 cache rows, a
 // dK/dV workgroup that computes its row statistics 8.5 + 1.8 per iteration.
+// dq: the dQ pass is still to go out, so that it may share the launch (it goes with the first table of more runs than one holds)
 template <typename Cfg>
-BwdPlan plan_bwd(const AttnParams& p, const SegTable& seg) {
+BwdPlan plan_bwd(const AttnParams& p, const SegTable& seg, bool dq) {
   const int cus = device_cus(), n_units = p.B * p.Hkv, n_ctiles = seg.tile_begin[seg.n];
   RowRuns none;
   none.n = 0;
@@ -176,8 +177,8 @@ BwdPlan plan_bwd(const AttnParams& p, const SegTable& seg) {
   best.ts.part = p.tail_part;
   float kv_alone = 0.f;
   best.ts.plan = share_plan(runs, n_units, n_ctiles, p.G, p.C, slots_in(p.tail_bytes), kv_alone);
+  if (!dq) return best;
   const SplitPlan sp = split_plan(p.B, p.Hkv, p.G, p.C);
-  if (!p.pending) return best;
   const int tiles = (p.q_start + p.C + 127) / 128;
   const size_t dq_bytes = (size_t)p.B * p.Hq * p.C * 128 * sizeof(float);
   auto dq_wgs = [&](int n) { return n > 1 ? sp.items * n : p.B * p.Hq * ((p.C + 127) / 128); };

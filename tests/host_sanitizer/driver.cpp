@@ -9,6 +9,7 @@
 #include <cstring>
 #include <vector>
 
+#include "bwd_plan.h"
 #include "seco.h"
 #include "stub_launch.h"
 
@@ -29,6 +30,8 @@ static seco_desc desc(int dtype = SECO_BF16, int C = 256, int q_start = 256, int
   for (auto s : ss) { s[0] = (int64_t)Hq << 22; s[1] = (int64_t)1 << 22; s[2] = D; }
   return d;
 }
+
+struct Cfg { static constexpr int kCols = 128, kBQ = 64; };   // (of the dK/dV kernel)
 
 static void* const FAKE = reinterpret_cast<void*>(0x10000);
 static float* const FAKEF = reinterpret_cast<float*>(0x10000);
@@ -276,6 +279,25 @@ int main() {
     p.C = 1; p.B = p.Hq = 1;                                                            // (strides that reach no row do not count)
     p.os[0] = p.os[1] = (int64_t)1 << 61;
     CHECK(!seco::o_over_inputs(p, 4));
+  }
+  // ---- the plan of a backward: both passes in one launch only while dQ is still to go out ----
+  {
+    const int shapes[][4] = {{8, 8, 64, 6400}, {32, 8, 745, 0}, {8, 2, 32, 3488}, {32, 8, 32, 0}};
+    for (const auto& sh : shapes) {
+      const seco_desc d = desc(SECO_BF16, sh[2], sh[3], sh[0], sh[1]);
+      CHECK(seco_chunk_attn_bwd(&d, FAKE, FAKE, FAKE, FAKE, FAKEF, FAKE, FAKE, FAKEF, FAKEF, FAKE,
+                                seco_workspace_bytes(&d, SECO_OP_BWD), nullptr) == SECO_OK);
+      const seco::AttnParams p = g_stub.last;
+      const seco::SegTable& seg = g_stub.dkdv_tables.back();
+      const seco::BwdPlan with = seco::plan_bwd<Cfg>(p, seg, true), without = seco::plan_bwd<Cfg>(p, seg, false);
+      CHECK(with.dq_splits > 0 && without.dq_splits == 0 && without.ts.part == p.tail_part);
+      seco::RowRuns none;
+      none.n = 0;
+      float time;
+      const seco::SharePlan alone = seco::share_plan(seco::tile_iterations<Cfg, false>(p, seg, none), p.B * p.Hkv, seg.tile_begin[seg.n], p.G,
+                                                     p.C, seco::slots_in(p.tail_bytes), time);
+      CHECK(without.ts.plan.n_tiles == alone.n_tiles && without.ts.plan.n_entries == alone.n_entries);
+    }
   }
   std::puts("host sanitizer run: all checks passed");
   return 0;
