@@ -64,34 +64,34 @@ int rounds_in_one_launch(int n_kv, int iters, int items, int tiles, int max_spli
 class Schedule {
  public:
   static constexpr int kMost = 64;
-  explicit Schedule(int places) : n_(1) { at_[0] = 0.f, of_[0] = places; }
+  explicit Schedule(int places) : first_(0), end_(1) { at_[0] = 0.f, of_[0] = places; }
   void run(float time, int count) {
     while (count > 0) {
-      const int k = std::min(of_[0], count);
-      const float t = at_[0] + time;
+      const int k = std::min(of_[first_], count);
+      const float t = at_[first_] + time;
       count -= k;
-      if ((of_[0] -= k) == 0) {
-        --n_;
-        std::copy(at_ + 1, at_ + 1 + n_, at_);
-        std::copy(of_ + 1, of_ + 1 + n_, of_);
-      }
-      int i = n_;
-      while (i > 0 && at_[i - 1] > t + 0.25f) --i;
-      if (i > 0 && at_[i - 1] >= t - 0.25f) {
+      if ((of_[first_] -= k) == 0) ++first_;
+      int i = end_;
+      while (i > first_ && at_[i - 1] > t + 0.25f) --i;
+      if (i > first_ && at_[i - 1] >= t - 0.25f) {
         of_[i - 1] += k;
-      } else {
-        std::copy_backward(at_ + i, at_ + n_, at_ + n_ + 1);
-        std::copy_backward(of_ + i, of_ + n_, of_ + n_ + 1);
-        at_[i] = t, of_[i] = k;
-        ++n_;
+        continue;
       }
+      if (end_ == kRoom) {                     // (there are at most kMost groups)
+        std::copy(at_ + first_, at_ + end_, at_);
+        std::copy(of_ + first_, of_ + end_, of_);
+        i -= first_, end_ -= first_, first_ = 0;
+      }
+      for (int j = end_++; j > i; --j) at_[j] = at_[j - 1], of_[j] = of_[j - 1];   // (few: most end last)
+      at_[i] = t, of_[i] = k;
     }
   }
-  float end() const { return at_[n_ - 1]; }
+  float end() const { return at_[end_ - 1]; }
 
  private:
-  float at_[kMost + 1];
-  int of_[kMost + 1], n_;
+  static constexpr int kRoom = 4 * kMost;
+  float at_[kRoom];
+  int of_[kRoom], first_, end_;                // groups [first_, end_)
 };
 
 // Fewer column tiles than a round, but more workgroups in all than fit at once: the plan of sharing out the column tiles with
@@ -103,6 +103,9 @@ class Schedule {
 // slower; two -> one, us:
 //   32/8  745 at 0: 50.9 -> 39.1   873 at 0: 55.9 -> 43.2   1482 at 445: 134.5 -> 131   16/8  1174 at 0: 58 -> 45
 //   8/8  2156 at 5: 84.9 -> 63.9   x 2  1011 at 96: 58.6 -> 40.9
+// The search itself takes 0.3 - 1.1 us of the host (745 rows 0.6, 1174 1.1; two sequences of 400 at 100, where it finds nothing,
+// 0.3), beside 3 of a launch: three in four calls that reach it are taken, and a bound on the time from the work alone tells
+// one in fifty of the others, so there is none.
 bool one_launch_behind_column_tiles(const AttnParams& p, const IterRuns& runs, int n_ctiles, int slots, const SharePlan& apart_plan,
                                     SharePlan& one_plan) {
   const int n_units = p.B * p.Hkv, places = device_cus() / 8, mtiles = (p.C + 127) / 128, heads = p.B * p.Hq / 8;
@@ -111,14 +114,17 @@ bool one_launch_behind_column_tiles(const AttnParams& p, const IterRuns& runs, i
   if (row_wgs > device_cus() && p.q_start >= 2 * p.C) return false;      // (row_shares divides dQ's second round)
   auto column_tiles = [&](Schedule& sc, const SharePlan& plan, float wg, float iter) {
     for (int u = 0; u < n_units / 8; ++u) {
-      int tile = 0, i = 0;
-      for (int r = 0; r < runs.n; ++r)
-        for (int c = 0; c < runs.count[r]; ++c, ++tile) {
-          const bool listed = tile >= n_ctiles - plan.n_tiles;
-          const int k = listed ? plan.first[i + 1] - plan.first[i] : 1;
-          if (listed) ++i;
-          sc.run(wg + iter * runs.iters[r] / k, k);
+      int listed = plan.n_tiles - n_ctiles;                              // position in the list of the next tile, once not negative
+      for (int r = 0; r < runs.n; ++r) {
+        const int whole = std::clamp(-listed, 0, runs.count[r]), shared = runs.count[r] - whole;
+        sc.run(wg + iter * runs.iters[r], whole);
+        listed += whole;
+        if (shared > 0) {                                                // (tiles of equal length have equally many shares)
+          const int k = plan.first[listed + 1] - plan.first[listed];
+          sc.run(wg + iter * runs.iters[r] / k, k * shared);
+          listed += shared;
         }
+      }
     }
   };
   auto row_tiles = [&](Schedule& sc, float wg, float tile) {
@@ -140,8 +146,10 @@ bool one_launch_behind_column_tiles(const AttnParams& p, const IterRuns& runs, i
   float best = apart / 1.05f;
   int last = -1;
   bool found = false;
-  for (int cus : {96, 160, 256}) {
-    const ShareChoice c = choose_shares(runs, n_ctiles, n_units, cus * device_cus() / 256, slots, 1, false, 8.5f, 1.8f);
+  const int cus[3] = {96 * device_cus() / 256, 160 * device_cus() / 256, device_cus()};
+  ShareChoice choices[3];
+  choose_shares(runs, n_ctiles, n_units, cus, slots, 1, false, 8.5f, 1.8f, choices);
+  for (const ShareChoice& c : choices) {
     if (c.time < 0.f || c.per == last) continue;
     last = c.per;
     const SharePlan plan = make_shares(runs, n_ctiles, c.per);

@@ -261,11 +261,13 @@ inline void for_last(const IterRuns& r, int n, const F& f) {
 // workgroup takes wg + iter per iteration; partial sums 4 + 0.03 per share (written and read again) + 0.02 per tile.
 // fit: all workgroups of the list must run at once, on `cus` compute units.
 struct ShareChoice { int per; float time, longest; };
-inline ShareChoice choose_shares(const IterRuns& r, int n, int n_units, int cus, int slots, int min_ways, bool fit, float wg, float iter) {
+template <int N>
+inline void choose_shares(const IterRuns& r, int n, int n_units, const int (&cus)[N], int slots, int min_ways, bool fit, float wg, float iter,
+                          ShareChoice (&best)[N]) {      // for each of N numbers of compute units
   static const int ways[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32};
   int most = 0;
   for_last(r, n, [&](int it, int) { most = it > most ? it : most; });
-  ShareChoice best{0, -1.f, 0.f};
+  for (ShareChoice& c : best) c = ShareChoice{0, -1.f, 0.f};
   for (int w : ways) {
     if (w < min_ways) continue;
     const int per = (most + w - 1) / w;
@@ -280,13 +282,24 @@ inline ShareChoice choose_shares(const IterRuns& r, int n, int n_units, int cus,
       const float t = wg + (it + k - 1) / k * iter;
       if (t > longest) longest = t;
     });
-    if (entries > kMaxEntries || shared * n_units > slots || (fit && entries * n_units > cus)) break;
-    const float even = sum * n_units / cus;
-    float t = entries * n_units <= cus ? longest : even + 0.5f * longest > longest + wg ? even + 0.5f * longest : longest + wg;
-    if (shared > 0) t += 4.f + (0.03f * shared + 0.02f * tiles) * n_units;
-    if (best.time < 0.f || t < best.time) best = ShareChoice{w > 1 ? per : 0, t, longest};
+    if (entries > kMaxEntries || shared * n_units > slots) break;
+    bool any = false;                                    // (more ways are more workgroups still)
+    for (int i = 0; i < N; ++i) {
+      if (fit && entries * n_units > cus[i]) continue;
+      any = true;
+      const float even = sum * n_units / cus[i];
+      float t = entries * n_units <= cus[i] ? longest : even + 0.5f * longest > longest + wg ? even + 0.5f * longest : longest + wg;
+      if (shared > 0) t += 4.f + (0.03f * shared + 0.02f * tiles) * n_units;
+      if (best[i].time < 0.f || t < best[i].time) best[i] = ShareChoice{w > 1 ? per : 0, t, longest};
+    }
+    if (!any) break;
   }
-  return best;
+}
+inline ShareChoice choose_shares(const IterRuns& r, int n, int n_units, int cus, int slots, int min_ways, bool fit, float wg, float iter) {
+  const int one[1] = {cus};
+  ShareChoice best[1];
+  choose_shares(r, n, n_units, one, slots, min_ways, fit, wg, iter, best);
+  return best[0];
 }
 inline SharePlan make_shares(const IterRuns& r, int n, int per) {
   SharePlan sp;

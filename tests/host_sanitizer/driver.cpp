@@ -3,6 +3,7 @@
 // and never dereferenced; what runs for real is everything the entry points do before a launch: validation, the
 // column-segment tables of the dK/dV pass, the run tables of the column-weighted dQ and of the transposed order,
 // the workspace layout, chunk selection and the weight vectors.
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -297,6 +298,34 @@ int main() {
       const seco::SharePlan alone = seco::share_plan(seco::tile_iterations<Cfg, false>(p, seg, none), p.B * p.Hkv, seg.tile_begin[seg.n], p.G,
                                                      p.C, seco::slots_in(p.tail_bytes), time);
       CHECK(without.ts.plan.n_tiles == alone.n_tiles && without.ts.plan.n_entries == alone.n_entries);
+    }
+  }
+  // workgroups laid out in groups end when they do one by one (whole microseconds: no two groups are taken as one), also past the
+  // room for groups; the choice of shares for several numbers of compute units is that for each
+  {
+    unsigned x = 12345;
+    auto draw = [&](int n) { return (int)((x = x * 1664525u + 1013904223u) >> 16) % n; };
+    for (int places : {1, 3, 32, 64}) {
+      seco::Schedule sc(places);
+      std::vector<int> at(places, 0);
+      for (int i = 0; i < 600; ++i) {
+        const int time = 1 + draw(i % 7 == 0 ? 500 : 40), count = 1 + draw(2 * places);
+        sc.run((float)time, count);
+        for (int c = 0; c < count; ++c) *std::min_element(at.begin(), at.end()) += time;
+        CHECK(sc.end() == (float)*std::max_element(at.begin(), at.end()));
+      }
+    }
+    for (int i = 0; i < 200; ++i) {
+      const int rows = 64 * (1 + draw(60)), n = 1 + draw(40), units = 1 + draw(16), cus[3] = {96, 160, 256};
+      const seco::IterRuns r = seco::iter_runs(n, [&](int t) { return std::max(1, rows / 64 - 2 * std::max(0, t - n / 2)); });
+      for (bool fit : {false, true}) {
+        seco::ShareChoice c[3];
+        seco::choose_shares(r, n, units, cus, 256, 1, fit, 8.5f, 1.8f, c);
+        for (int k = 0; k < 3; ++k) {
+          const seco::ShareChoice one = seco::choose_shares(r, n, units, cus[k], 256, 1, fit, 8.5f, 1.8f);
+          CHECK(c[k].per == one.per && c[k].time == one.time && c[k].longest == one.longest);
+        }
+      }
     }
   }
   std::puts("host sanitizer run: all checks passed");
