@@ -76,7 +76,7 @@ int launch_dq_bf16_now(const AttnParams& p, const SegTable* runs, hipStream_t s)
   const int total = p.B * p.Hq * n_mtiles;
   if (!runs) {
     const SplitPlan plan = split_plan(p.B, p.Hkv, p.G, p.C);
-    const RowShares rs = row_shares(p.B * p.Hkv, plan.n_mtiles, total, p.q_start, p.C, p.tail_bytes / (BM * kHeadDim * sizeof(float)), 7.5f, 2.7f);
+    const RowShares rs = row_shares(p.B * p.Hkv, plan.n_mtiles, total, p.q_start, p.C, p.tail_bytes / (BM * kHeadDim * sizeof(float)), kDqTime);
     if (rs.shares > 1) {
       AttnParams ps = p;
       ps.rows_whole = rs.whole;

@@ -50,12 +50,16 @@ int rounds_in_one_launch(int n_kv, int iters, int items, int tiles, int max_spli
   const float cus = (float)device_cus(), kv = n_kv / cus;
   if (iters > (n_kv <= device_cus() ? 4 : 12)) return 0;
   int n = 1;
-  while (n < max_splits && 8.f + 2.7f * ((tiles + n - 1) / n) > 0.9f * kv * (14.f + 2.f * iters)) ++n;
+  while (n < max_splits && kDqFrontTime.of((tiles + n - 1) / n) > 0.9f * kv * kDkdvRoundTime.of(iters)) ++n;
   const int full = n_kv / device_cus();
   const float tail = kv - full;
-  const float rest = tail > 0.f ? 9.2f + 0.6f * iters + tail * (5.6f + 1.7f * iters) : 0.f;
-  const float apart = 12.2f + full * (15.2f + 2.2f * iters) + rest + 1.7f * items * tiles / cus;
-  const float one = 5.3f + 2.3f * dq_wgs(n) * tiles / (n * cus) + kv * (14.f + 2.2f * iters) + 0.6f * iters;
+  // fit: full rounds of dK/dV and a last one, dQ, what is around them; in one launch they share the chip evenly, and a last
+  // workgroup ends alone
+  constexpr WgTime kFull{15.2f, 2.2f}, kLast{9.2f, 0.6f}, kLastPart{5.6f, 1.7f}, kEven{14.f, 2.2f};
+  constexpr float kDqTile = 1.7f, kDqTileOne = 2.3f, kAlone = 0.6f, kAroundApart = 12.2f, kAroundOne = 5.3f;
+  const float rest = tail > 0.f ? kLast.of(iters) + tail * kLastPart.of(iters) : 0.f;
+  const float apart = kAroundApart + full * kFull.of(iters) + rest + kDqTile * items * tiles / cus;
+  const float one = kAroundOne + kDqTileOne * dq_wgs(n) * tiles / (n * cus) + kv * kEven.of(iters) + kAlone * iters;
   return 1.03f * one < apart ? n : 0;
 }
 
@@ -112,34 +116,37 @@ bool one_launch_behind_column_tiles(const AttnParams& p, const IterRuns& runs, i
   const int row_wgs = p.B * p.Hq * mtiles;
   if (n_units % 8 != 0 || places > Schedule::kMost || row_wgs >= 2 * device_cus()) return false;
   if (row_wgs > device_cus() && p.q_start >= 2 * p.C) return false;      // (row_shares divides dQ's second round)
-  auto column_tiles = [&](Schedule& sc, const SharePlan& plan, float wg, float iter) {
+  // fit: workgroups of both passes one after the other and in one launch, what overlaps between launches, a share in a merge
+  constexpr WgTime kKv{14.9f, 1.7f}, kKvOne{15.7f, 1.8f}, kDq{7.1f, 1.7f}, kDqOne{8.2f, 2.4f};
+  constexpr float kAroundApart = -1.6f, kAroundOne = -4.7f, kShareApart = 0.03f, kShareOne = 0.024f, kShareDq = 0.02f;
+  auto column_tiles = [&](Schedule& sc, const SharePlan& plan, WgTime wg) {
     for (int u = 0; u < n_units / 8; ++u) {
       int listed = plan.n_tiles - n_ctiles;                              // position in the list of the next tile, once not negative
       for (int r = 0; r < runs.n; ++r) {
         const int whole = std::clamp(-listed, 0, runs.count[r]), shared = runs.count[r] - whole;
-        sc.run(wg + iter * runs.iters[r], whole);
+        sc.run(wg.of(runs.iters[r]), whole);
         listed += whole;
         if (shared > 0) {                                                // (tiles of equal length have equally many shares)
           const int k = plan.first[listed + 1] - plan.first[listed];
-          sc.run(wg + iter * runs.iters[r] / k, k * shared);
+          sc.run(wg.wg + wg.step * runs.iters[r] / k, k * shared);
           listed += shared;
         }
       }
     }
   };
-  auto row_tiles = [&](Schedule& sc, float wg, float tile) {
-    for (int mt = mtiles; mt > 0; --mt) sc.run(wg + tile * ((p.q_start + std::min(mt * 128, p.C) + 127) / 128), heads);
+  auto row_tiles = [&](Schedule& sc, WgTime wg) {
+    for (int mt = mtiles; mt > 0; --mt) sc.run(wg.of((p.q_start + std::min(mt * 128, p.C) + 127) / 128), heads);
   };
-  auto merge = [&](const SharePlan& plan, float each) { return plan.n_shared > 0 ? 4.f + each * plan.first[plan.n_shared] * n_units : 0.f; };
+  auto merge = [&](const SharePlan& plan, float each) { return plan.n_shared > 0 ? kMergeLaunch + each * plan.first[plan.n_shared] * n_units : 0.f; };
   Schedule kv(places);
-  column_tiles(kv, apart_plan, 14.9f, 1.7f);
-  float apart = kv.end() + merge(apart_plan, 0.03f) - 1.6f;
+  column_tiles(kv, apart_plan, kKv);
+  float apart = kv.end() + merge(apart_plan, kShareApart) + kAroundApart;
   if (p.n_splits > 1) {
     const int wgs = split_plan(p.B, p.Hkv, p.G, p.C).items * p.n_splits, tiles = (p.q_start + p.C + 127) / 128;
-    apart += (wgs + device_cus() - 1) / device_cus() * (7.1f + 1.7f * ((tiles + p.n_splits - 1) / p.n_splits)) + 4.f + 0.02f * wgs;
+    apart += (wgs + device_cus() - 1) / device_cus() * kDq.of((tiles + p.n_splits - 1) / p.n_splits) + kMergeLaunch + kShareDq * wgs;
   } else {
     Schedule dq(places);
-    row_tiles(dq, 7.1f, 1.7f);
+    row_tiles(dq, kDq);
     apart += dq.end();
   }
   if (apart > 200.f) return false;
@@ -148,15 +155,15 @@ bool one_launch_behind_column_tiles(const AttnParams& p, const IterRuns& runs, i
   bool found = false;
   const int cus[3] = {96 * device_cus() / 256, 160 * device_cus() / 256, device_cus()};
   ShareChoice choices[3];
-  choose_shares(runs, n_ctiles, n_units, cus, slots, 1, false, 8.5f, 1.8f, choices);
+  choose_shares(runs, n_ctiles, n_units, cus, slots, 1, false, kDkdvOwnTime, choices);
   for (const ShareChoice& c : choices) {
     if (c.time < 0.f || c.per == last) continue;
     last = c.per;
     const SharePlan plan = make_shares(runs, n_ctiles, c.per);
     Schedule both(places);
-    column_tiles(both, plan, 15.7f, 1.8f);
-    row_tiles(both, 8.2f, 2.4f);
-    const float t = both.end() + merge(plan, 0.024f) - 4.7f;
+    column_tiles(both, plan, kKvOne);
+    row_tiles(both, kDqOne);
+    const float t = both.end() + merge(plan, kShareOne) + kAroundOne;
     if (t < best) {
       best = t;
       one_plan = plan;
@@ -170,8 +177,7 @@ bool one_launch_behind_column_tiles(const AttnParams& p, const IterRuns& runs, i
 // CU and the longer pass, with the extra work, is expected to end before the two would one after the other: with more
 // workgroups than CUs the two halves of the grid would queue behind each other on some CUs (16/2 heads, chunk 704 at 5632:
 // 7% slower in one launch).  The passes divide the CUs: for every number of shares of a dQ row tile the column tiles are
-// shared out over the rest.  Times in microseconds as measured: a dQ workgroup 7.5 + 2.5 per tile of 128 cache rows, a
-// dK/dV workgroup that computes its row statistics 8.5 + 1.8 per iteration.
+// shared out over the rest (kDqBesideTime, kDkdvOwnTime).
 // dq: the dQ pass is still to go out, so that it may share the launch (it goes with the first table of more runs than one holds)
 template <typename Cfg>
 BwdPlan plan_bwd(const AttnParams& p, const SegTable& seg, bool dq) {
@@ -202,16 +208,16 @@ BwdPlan plan_bwd(const AttnParams& p, const SegTable& seg, bool dq) {
     }
     return best;
   }
-  auto dq_time = [&](int n) { return 7.5f + 2.5f * ((tiles + n - 1) / n); };
-  auto merge_time = [&](int n) { return n > 1 ? 4.f + 0.02f * dq_wgs(n) : 0.f; };
-  float best_t = (dq_wgs(p.n_splits) + cus - 1) / cus * dq_time(p.n_splits) + merge_time(p.n_splits) + kv_alone + 2.f;
+  auto dq_time = [&](int n) { return kDqBesideTime.of((tiles + n - 1) / n); };
+  auto merge_time = [&](int n) { return n > 1 ? kMergeLaunch + 0.02f * dq_wgs(n) : 0.f; };
+  float best_t = (dq_wgs(p.n_splits) + cus - 1) / cus * dq_time(p.n_splits) + merge_time(p.n_splits) + kv_alone + 2.f;   // (2: between the launches)
   int per = 0;
   for (int n = 1; n <= p.n_splits && dq_wgs(n) + n_units * n_ctiles <= cus; ++n) {
     const size_t used = dq_part(n);
     if (used > p.tail_bytes) break;
-    const ShareChoice c = choose_shares(runs, n_ctiles, n_units, cus - dq_wgs(n), slots_in(p.tail_bytes - used), 1, true, 8.5f, 1.8f);
+    const ShareChoice c = choose_shares(runs, n_ctiles, n_units, cus - dq_wgs(n), slots_in(p.tail_bytes - used), 1, true, kDkdvOwnTime);
     // (both merges are one launch)
-    const float t = std::max(dq_time(n), c.longest) + (c.time - c.longest) + (n > 1 ? merge_time(n) - (c.per ? 4.f : 0.f) : 0.f);
+    const float t = std::max(dq_time(n), c.longest) + (c.time - c.longest) + (n > 1 ? merge_time(n) - (c.per ? kMergeLaunch : 0.f) : 0.f);
     if (c.time >= 0.f && t < best_t) {
       best_t = t;
       best.dq_splits = n;

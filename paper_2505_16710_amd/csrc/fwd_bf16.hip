@@ -14,7 +14,7 @@ int launch_fwd_bf16(const AttnParams& p, hipStream_t s) {
   const int total = p.B * p.Hq * n_mtiles;
   if (p.tail_bytes > 0) {
     const SplitPlan plan = split_plan(p.B, p.Hkv, p.G, p.C);
-    const RowShares rs = row_shares(p.B * p.Hkv, plan.n_mtiles, total, p.q_start, p.C, p.tail_bytes / (BM * kHeadDim * sizeof(float)), 6.f, 1.8f);
+    const RowShares rs = row_shares(p.B * p.Hkv, plan.n_mtiles, total, p.q_start, p.C, p.tail_bytes / (BM * kHeadDim * sizeof(float)), kFwdTime);
     if (rs.shares > 1) {
       AttnParams ps = p;
       ps.rows_whole = rs.whole;

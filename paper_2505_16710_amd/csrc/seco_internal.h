@@ -108,6 +108,26 @@ struct SplitPlan {
 constexpr int kDefaultCUs = 256;
 int device_cus();
 
+// Times that the rules below and in bwd_plan.h weigh against each other, in microseconds: a workgroup takes `wg` around its loop
+// and `step` per step of it (forward, dQ: 128 cache rows; dK/dV: an iteration, 64 query rows of one head).  What a
+// workgroup takes depends on what runs beside it (the clock falls as the chip fills, dK/dV workgroups that end together wait for each
+// other's gK / gV), so a kernel has a line for each situation, and a rule uses the line of its own.  After a change to a kernel
+// its lines are measured anew: calls of the named kind at several numbers of steps, one workgroup per CU, kernel times from
+// seco_profile_read, a straight line through them; those called "fit": least squares over the calls that their rule
+// names, whole backward calls timed, with the offsets beside them.
+struct WgTime {
+  float wg, step;
+  float of(float steps) const { return wg + step * steps; }
+};
+constexpr WgTime kFwdTime{6.f, 1.8f};           // forward, dense calls of one round
+constexpr WgTime kDqTime{7.5f, 2.7f};           // dQ, likewise
+constexpr WgTime kDqBesideTime{7.5f, 2.5f};     // dQ while dK/dV workgroups have the other CUs
+constexpr WgTime kDkdvTime{8.f, 1.6f};          // dK/dV alone, at most a round
+constexpr WgTime kDkdvOwnTime{8.5f, 1.8f};      // dK/dV that computes its row statistics, dQ beside it
+constexpr WgTime kDkdvRoundTime{14.f, 2.f};     // the same over several rounds, dQ in front of it: fit (rounds_in_one_launch)
+constexpr WgTime kDqFrontTime{8.f, 2.7f};       // that dQ
+constexpr float kMergeLaunch = 4.f;             // a merge, without what it reads and writes
+
 inline SplitPlan split_plan(int B, int Hkv, int G, int C) {
   SplitPlan pl;
   const int cus = device_cus();
@@ -138,8 +158,7 @@ inline int split_count(const SplitPlan& pl, int kv_len) {
 // however few tiles it has, is divided.  Of every (batch, KV head)'s packed row tiles the first `whole` (together one round)
 // stay whole, the others have their cache rows divided among `shares` workgroups each, which run in short rounds of their
 // own; shares 1: nothing is divided.  slots: partial tiles that the workspace holds; n_plain: workgroups without packing,
-// the alternative.  Times in microseconds: wg + tile per 128 cache rows, a merge 5 + 0.03 per share; forward 6 + 1.8, dQ
-// 7.5 + 2.7 (in dense calls of one round).  Chosen where that comes out 5 % below the undivided call, and only where the
+// the alternative.  wg: kFwdTime or kDqTime; a merge 5 us + 0.03 per share.  Chosen where that comes out 5 % below the undivided call, and only where the
 // tiles are about equally long (a chunk of at most half of what precedes it: the rounds' lengths are those of the mean).
 // Microseconds before -> after, 32 heads on 8, batch 1:
 //   rows @ preceding    1100 @ 9000   1500 @ 9000   1300 @ 3000   1060 @ 30000   1900 @ 9000 (undivided by the rule)
@@ -148,16 +167,16 @@ inline int split_count(const SplitPlan& pl, int kv_len) {
 // and 16 heads on 2, 2500 @ 9000: 308 -> 234, 842 -> 738; 8 on 8, 4500 @ 12000: 372 -> 290.
 constexpr int kMaxRowShares = 8;
 struct RowShares { int whole, shares; };
-inline RowShares row_shares(int n_units, int n_mtiles, int n_plain, int q_start, int C, size_t slots, float wg, float tile) {
+inline RowShares row_shares(int n_units, int n_mtiles, int n_plain, int q_start, int C, size_t slots, WgTime wg) {
   const int cus = device_cus(), whole = cus / n_units, n_cut = n_mtiles - whole, tiles = (q_start + C / 2 + 127) / 128;
   RowShares best{0, 1};
   if (whole < 1 || n_cut < 1 || n_plain >= 2 * cus || q_start < 2 * C) return best;
-  const float one = wg + tile * tiles;
+  const float one = wg.of(tiles);
   float best_t = 0.95f * ((n_plain + cus - 1) / cus) * one;
   for (int k = 2; k <= kMaxRowShares && k <= q_start / 128; ++k) {
     const int64_t n = (int64_t)n_units * n_cut * k;
     if ((size_t)n > slots) break;
-    const float t = one + (n + cus - 1) / cus * (wg + tile * ((tiles + k - 1) / k)) + 5.f + 0.03f * n;
+    const float t = one + (n + cus - 1) / cus * wg.of((tiles + k - 1) / k) + 5.f + 0.03f * n;
     if (t < best_t) {
       best_t = t;
       best = RowShares{whole, k};
@@ -257,12 +276,12 @@ inline void for_last(const IterRuns& r, int n, const F& f) {
 }
 
 // How to share out the last n tiles of every unit: the most iterations a workgroup gets (0: nothing is shared out), the
-// time that is expected to take and how much of it the longest workgroup takes.  Times in microseconds, as measured: a
-// workgroup takes wg + iter per iteration; partial sums 4 + 0.03 per share (written and read again) + 0.02 per tile.
+// time that is expected to take and how much of it the longest workgroup takes.  wg: of a workgroup; partial sums take
+// 4 us + 0.03 per share (written and read again) + 0.02 per tile.
 // fit: all workgroups of the list must run at once, on `cus` compute units.
 struct ShareChoice { int per; float time, longest; };
 template <int N>
-inline void choose_shares(const IterRuns& r, int n, int n_units, const int (&cus)[N], int slots, int min_ways, bool fit, float wg, float iter,
+inline void choose_shares(const IterRuns& r, int n, int n_units, const int (&cus)[N], int slots, int min_ways, bool fit, WgTime wg,
                           ShareChoice (&best)[N]) {      // for each of N numbers of compute units
   static const int ways[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32};
   int most = 0;
@@ -278,8 +297,8 @@ inline void choose_shares(const IterRuns& r, int n, int n_units, const int (&cus
       const int k = it > per ? (it + per - 1) / per : 1;
       if (k > 1) shared += k * count, tiles += count;
       entries += k * count;
-      sum += count * (k * wg + it * iter);
-      const float t = wg + (it + k - 1) / k * iter;
+      sum += count * (k * wg.wg + it * wg.step);
+      const float t = wg.of((it + k - 1) / k);
       if (t > longest) longest = t;
     });
     if (entries > kMaxEntries || shared * n_units > slots) break;
@@ -288,17 +307,17 @@ inline void choose_shares(const IterRuns& r, int n, int n_units, const int (&cus
       if (fit && entries * n_units > cus[i]) continue;
       any = true;
       const float even = sum * n_units / cus[i];
-      float t = entries * n_units <= cus[i] ? longest : even + 0.5f * longest > longest + wg ? even + 0.5f * longest : longest + wg;
-      if (shared > 0) t += 4.f + (0.03f * shared + 0.02f * tiles) * n_units;
+      float t = entries * n_units <= cus[i] ? longest : even + 0.5f * longest > longest + wg.wg ? even + 0.5f * longest : longest + wg.wg;
+      if (shared > 0) t += kMergeLaunch + (0.03f * shared + 0.02f * tiles) * n_units;
       if (best[i].time < 0.f || t < best[i].time) best[i] = ShareChoice{w > 1 ? per : 0, t, longest};
     }
     if (!any) break;
   }
 }
-inline ShareChoice choose_shares(const IterRuns& r, int n, int n_units, int cus, int slots, int min_ways, bool fit, float wg, float iter) {
+inline ShareChoice choose_shares(const IterRuns& r, int n, int n_units, int cus, int slots, int min_ways, bool fit, WgTime wg) {
   const int one[1] = {cus};
   ShareChoice best[1];
-  choose_shares(r, n, n_units, one, slots, min_ways, fit, wg, iter, best);
+  choose_shares(r, n, n_units, one, slots, min_ways, fit, wg, best);
   return best[0];
 }
 inline SharePlan make_shares(const IterRuns& r, int n, int per) {
@@ -323,7 +342,6 @@ struct TailSplit {
   float* part;
   SharePlan plan;
 };
-constexpr float kDkdvWg = 8.f, kDkdvIter = 1.6f;
 // For a dK/dV pass that has the chip to itself; time: what it is expected to take from its last full round on
 inline SharePlan share_plan(const IterRuns& r, int n_units, int n_ctiles, int G, int n_rows, int slots, float& time) {
   const int cus = device_cus();
@@ -331,9 +349,9 @@ inline SharePlan share_plan(const IterRuns& r, int n_units, int n_ctiles, int G,
   const int tail = (int)(items % cus);
   const TailPlan tp = tail_plan(n_units, n_ctiles, G, n_rows);
   const int n = tp.hs > 1 ? tp.n_tiles : items < cus ? n_ctiles : (tail + n_units - 1) / n_units;
-  time = kDkdvWg + kDkdvIter * r.iters[0];
+  time = kDkdvTime.of(r.iters[0]);
   if (tail == 0 || slots < 2 * n_units || n > r.n_tiles) return make_shares(r, 0, 0);
-  const ShareChoice c = choose_shares(r, n, n_units, cus, slots, tp.hs > 1 ? tp.hs : 1, false, kDkdvWg, kDkdvIter);
+  const ShareChoice c = choose_shares(r, n, n_units, cus, slots, tp.hs > 1 ? tp.hs : 1, false, kDkdvTime);
   if (c.time >= 0.f) time = c.time;
   return make_shares(r, n, c.per);
 }

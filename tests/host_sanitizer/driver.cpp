@@ -320,9 +320,9 @@ int main() {
       const seco::IterRuns r = seco::iter_runs(n, [&](int t) { return std::max(1, rows / 64 - 2 * std::max(0, t - n / 2)); });
       for (bool fit : {false, true}) {
         seco::ShareChoice c[3];
-        seco::choose_shares(r, n, units, cus, 256, 1, fit, 8.5f, 1.8f, c);
+        seco::choose_shares(r, n, units, cus, 256, 1, fit, seco::kDkdvOwnTime, c);
         for (int k = 0; k < 3; ++k) {
-          const seco::ShareChoice one = seco::choose_shares(r, n, units, cus[k], 256, 1, fit, 8.5f, 1.8f);
+          const seco::ShareChoice one = seco::choose_shares(r, n, units, cus[k], 256, 1, fit, seco::kDkdvOwnTime);
           CHECK(c[k].per == one.per && c[k].time == one.time && c[k].longest == one.longest);
         }
       }
