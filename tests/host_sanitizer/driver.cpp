@@ -83,6 +83,15 @@ int main() {
     const size_t wf = seco_workspace_bytes(&d, SECO_OP_FWD);
     CHECK(seco_chunk_attn_fwd(&d, FAKE, FAKE, FAKE, FAKE, FAKEF, FAKE, wf, nullptr) == SECO_OK);
     CHECK(g_stub.last.n_splits > 1);
+    // row tiles between one and two rounds: divided only with all of an aligned workspace
+    const seco_desc sh = desc(SECO_BF16, 700, 2900, 48, 16);
+    const size_t wsh = seco_workspace_bytes(&sh, SECO_OP_FWD);
+    CHECK(wsh > 0);
+    for (const int off : {0, 16, -1}) {                     // whole, misaligned, one byte short
+      CHECK(seco_chunk_attn_fwd(&sh, FAKE, FAKE, FAKE, FAKE, FAKEF, static_cast<char*>(FAKE) + std::max(off, 0), wsh + std::min(off, 0),
+                                nullptr) == SECO_OK);
+      CHECK((g_stub.last.tail_bytes > 0) == (off == 0) && (g_stub.last.part != nullptr) == (off == 0) && g_stub.last.n_splits == 1);
+    }
     // the same call on the library's own scratch array
     g_stub.clear();
     CHECK(seco_chunk_attn_bwd_noalloc(&d, FAKE, FAKE, FAKE, FAKE, FAKEF, FAKE, FAKE, FAKEF, FAKEF, nullptr) == SECO_OK);

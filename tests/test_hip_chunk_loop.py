@@ -105,6 +105,19 @@ def test_losses_of_a_step_that_visits_every_chunk(dtype, cfg, N, kw):
     assert every == picked == some
 
 
+@pytest.mark.parametrize("transposed,wide_tail", [(True, False), (False, True), (True, True)])
+def test_losses_of_stage_2_in_the_transposed_order_and_behind_a_wide_tail(transposed, wide_tail):
+    """The same, with the transposed backward order and with an fp32 final norm and head behind the bf16 body; a ragged last chunk."""
+    _, dec, tok, tgt = _setup(BF16_CFG, 18, 2, 250, torch.bfloat16)
+    for n in ("norm_f", "head") if wide_tail else ():
+        dec.p[n] = om.init_params(BF16_CFG, 34)[n].detach().to(torch.float32).to(DEV).requires_grad_()
+    tok, tgt = tok.to(DEV), tgt.to(DEV)
+    every, _ = dec.step(tok, tgt, 64, transposed_backward=transposed)
+    picked, _ = dec.step(tok, tgt, 64, selected=[0, 1, 2, 3], factor=1.0, transposed_backward=transposed)
+    some, _ = dec.step(tok, tgt, 64, selected=[3, 1, 0], factor=4 / 3, transposed_backward=transposed)
+    assert every == picked == some
+
+
 def test_whole_sequence_stage1_with_kept_outputs_matches_oracle():
     """Stage 1 as one plain forward over the whole sequence, stage 2 from its kept O / LSE: same gradients as the
     oracle's Alg. 1 / Alg. 2 (to the usual tolerance; the launches differ in shape from the chunked stage 1)."""

@@ -408,6 +408,27 @@ def test_bf16_row_tiles_beyond_one_round_divided(B, Hq, Hkv, C, q_start):
             assert max_rel(to_host(dqs[0][b, h]), to_host(ref_dq)) <= TOL["bf16"]["dq"], (b, h)
 
 
+def test_forward_leaves_a_workspace_that_does_not_fit_alone():
+    """One byte short, or not on 256 bytes: the undivided forward, bit for bit, and nothing is written there."""
+    B, Hq, Hkv, C, q_start = 1, 48, 16, 700, 2900           # row tiles between one and two rounds
+    g = torch.Generator(device=DEV).manual_seed(67)
+    rand = lambda *shape: torch.randn(*shape, device=DEV, generator=g).to(torch.bfloat16)
+    q, k, v = rand(B, Hq, C, 128), rand(B, Hkv, q_start + C, 128), rand(B, Hkv, q_start + C, 128)
+    n = seco.seco_workspace_bytes(seco.binding.make_desc(q, k, q_start, 128 ** -0.5), seco.binding.SECO_OP_FWD)
+    assert n > 0
+    whole = seco.seco_chunk_attn_fwd(q, k, v, q_start, 128 ** -0.5, ws=False)
+    divided = seco.seco_chunk_attn_fwd(q, k, v, q_start, 128 ** -0.5)
+    assert not torch.equal(whole[0], divided[0])            # (its sums are formed in another order)
+    room = torch.full((n + 512,), 0xa5, dtype=torch.uint8, device=DEV)
+    for ws in (room[:n - 1], room[16:16 + n]):
+        got = seco.seco_chunk_attn_fwd(q, k, v, q_start, 128 ** -0.5, ws=ws)
+        assert torch.equal(got[0], whole[0]) and torch.equal(got[1], whole[1])
+        assert bool((room == 0xa5).all())
+    got = seco.seco_chunk_attn_fwd(q, k, v, q_start, 128 ** -0.5, ws=room[256:256 + n])
+    assert torch.equal(got[0], divided[0]) and torch.equal(got[1], divided[1])
+    assert bool((room[:256] == 0xa5).all()) and bool((room[256 + n:] == 0xa5).all())
+
+
 def _one_call(dtype, D, N, C, j, weights=None, seed=40):
     x = small_layer(seed, 1, 4, 2, N, D, dtype)
     q, k, v, do = (to_dev(x[n], dtype) for n in ("q", "k", "v", "do"))
