@@ -163,8 +163,9 @@ inline int split_count(const SplitPlan& pl, int kv_len) {
 // Microseconds before -> after, 32 heads on 8, batch 1:
 //   rows @ preceding    1100 @ 9000   1500 @ 9000   1300 @ 3000   1060 @ 30000   1900 @ 9000 (undivided by the rule)
 //   forward              268 -> 196    281 -> 265    106 -> 100    878 -> 597     328 -> 327
-//   backward, both passes 690 -> 586   805 -> 772    292 -> 280   2083 -> 1692   1004 -> 1004
-// and 16 heads on 2, 2500 @ 9000: 308 -> 234, 842 -> 738; 8 on 8, 4500 @ 12000: 372 -> 290.
+//   backward, both passes 684 -> 577   803 -> 764    291 -> 278   2097 -> 1691    977 -> 977
+// and 16 heads on 2, 2500 @ 9000: 308 -> 234, 844 -> 737; 8 on 8, 4500 @ 12000: 372 -> 290.  Least where dK/dV outweighs dQ and
+// the clock falls as idle CUs get work: two sequences of 777 @ 9324 844 -> 835 (dQ 404 -> 374 and a merge of 7, 2.07 -> 1.96 GHz).
 constexpr int kMaxRowShares = 8;
 struct RowShares { int whole, shares; };
 inline RowShares row_shares(int n_units, int n_mtiles, int n_plain, int q_start, int C, size_t slots, WgTime wg) {
