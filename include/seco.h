@@ -356,8 +356,8 @@ int spaco_gather_row_weights(const int32_t* selected_host, int32_t n_selected, i
  */
 typedef enum seco_profile_kind {
   SECO_PROFILE_FWD = 0,     /* forward kernel */
-  SECO_PROFILE_BWD = 1,     /* dQ and dK/dV in one launch: every fp32 backward, bf16 calls of short chunks or with few
-                               cache tiles where that is expected to pay; such a call has no SECO_PROFILE_DQ or _DKDV launch (delta = rowsum(dO * O), which
+  SECO_PROFILE_BWD = 1,     /* dQ and dK/dV in one launch: fp32 backwards, bf16 calls of short chunks or with few
+                               cache tiles where that is expected to pay, unless d_q lies over o; such a call has no SECO_PROFILE_DQ or _DKDV launch (delta = rowsum(dO * O), which
                                had this entry once, is no launch of its own on any path) */
   SECO_PROFILE_DQ = 2,      /* dQ kernel */
   SECO_PROFILE_DKDV = 3,    /* dK/dV kernel with the gK/gV accumulation, and the merge of shared-out cache tiles */
