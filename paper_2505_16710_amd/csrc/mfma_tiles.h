@@ -11,10 +11,20 @@
 // (ds_read_b64_tr_b16: lane i of a 16-lane group receives element i%4 of the 8 bytes
 // addressed by lanes i/4, 4+i/4, 8+i/4, 12+i/4) delivers exactly that.
 //
+// Operand layouts of v_mfma_f32_16x16x32_bf16 (D = A[16x32] * B[32x16] + C), lane l, g = l / 16:
+//   A: row  l % 16, contraction slots 8g .. 8g+7
+//   B: col  l % 16, contraction slots 8g .. 8g+7
+//   C: col  l % 16, register r holds row 4g + r
+// so two C tiles of 16 rows each make an operand over 32 contraction steps (pack44): slots 0-3 of group g are the first
+// tile's rows 4g .. 4g+3, slots 4-7 the second's.  Which row of an LDS tile stands for which row of A is free as long as
+// both products agree: row 4q + i of A is tile row 4 pi(q) + i, pi = 0, 2, 3, 1, the order in which neither the row
+// reads (served in groups of lanes 0-3, 12-15, 20-23, 24-27 and so on) nor the transpose reads (half-waves) have two
+// lanes on a bank; in plain order both took twice the LDS cycles.
+//
 // LDS tiles are row-major, 256 bytes per row (128 bf16), with the sixteen 16-byte chunks of a
-// row XOR-swizzled by a function of the row number so that both access patterns are free of
-// bank conflicts: 16 lanes reading the same chunk of 16 consecutive rows, and the transpose
-// read's 4 rows x 64 bytes per half-wave.
+// row XOR-swizzled by a function of the row number so that the access patterns are free of
+// bank conflicts: 16 lanes reading the same chunk of 16 consecutive rows, the transpose
+// read's 4 rows x 64 bytes per half-wave, and those of the 16-row operands above.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -40,6 +50,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 #define SECO_LDS __attribute__((address_space(3)))
 typedef SECO_LDS char lds_char;
@@ -104,6 +115,40 @@ __device__ __forceinline__ bf16x8 lds_tr8_at(lds_char* tile, TrOff off, int row0
 
 __device__ __forceinline__ f32x16 mfma(bf16x8 a, bf16x8 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
+
+__device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+// (pi of the operand layouts above, of a lane group)
+__device__ __forceinline__ int pi4(int group) { return ((group & 1) << 1) ^ ((group >> 1) * 3); }
+// operand over 32 contraction rows from two C tiles of 16 of them
+__device__ __forceinline__ bf16x8 pack44(const f32x4& x, const f32x4& y) {
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  u32x4 r;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const f32x2 v = i < 2 ? f32x2{x[2 * i], x[2 * i + 1]} : f32x2{y[2 * i - 4], y[2 * i - 3]};
+    r[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+  }
+  return __builtin_bit_cast(bf16x8, r);
+}
+// 16 rows (row0: multiple of 16; lane: row pi(l % 16)) as an operand, contraction 32 t .. 32 t + 31 of head_dim
+__device__ __forceinline__ bf16x8 lds_row16(lds_char* tile, int row0, int t, int lane) {
+  const int r = 4 * pi4((lane >> 2) & 3) + (lane & 3);
+  return *reinterpret_cast<SECO_LDS bf16x8*>(tile + tile_off(r, 4 * t + (lane >> 4)) + row0 * kRowBytes);
+}
+// head_dim column 16 db + lane % 16, contraction over the 32 rows from row0 (multiple of 16) on, slots as pack44's
+__device__ __forceinline__ bf16x8 lds_tr16(lds_char* tile, int row0, int db, int lane) {
+  const int ii = lane & 15;
+  lds_char* a = tile + tile_off(4 * pi4(lane >> 4) + (ii >> 2), 2 * db + ((ii & 3) >> 1)) + ((ii & 1) << 3) + row0 * kRowBytes;
+  const s16x4 x = __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<SECO_LDS s16x4*>(a));
+  const s16x4 y = __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<SECO_LDS s16x4*>(a + 16 * kRowBytes));
+  typedef short s16x8 __attribute__((ext_vector_type(8)));
+  const s16x8 r = {x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]};
+  return __builtin_bit_cast(bf16x8, r);
 }
 
 // registers 8t .. 8t+7 of a C tile, rounded to bf16 (pairwise, one v_cvt_pk_bf16_f32 per pair),
@@ -181,6 +226,13 @@ __device__ __forceinline__ void rows32_to_frags(bf16x8 (&f)[8], const bf16x8 (&x
 #pragma unroll
   for (int t = 0; t < 8; ++t) f[t] = lds_row8(own8k, lane & 31, 2 * t + (lane >> 5));
 }
+// As operands over 32 contraction steps: fragment 4 qb + t is rows 16 qb + l % 16, chunks 4 t + l / 16
+__device__ __forceinline__ void rows16_to_frags(bf16x8 (&f)[8], const bf16x8 (&x)[8], lds_char* own8k, int lane) {
+#pragma unroll
+  for (int j = 0; j < 8; ++j) lds_store16(own8k, 4 * j + (lane >> 4), lane & 15, x[j]);
+#pragma unroll
+  for (int t = 0; t < 8; ++t) f[t] = lds_row8(own8k, 16 * (t >> 2) + (lane & 15), 4 * (t & 3) + (lane >> 4));
+}
 // The way back: a 128 x 32 accumulator whose lanes own rows (lane: row l % 32, register 4 r4 + i of block db: column
 // 32 db + 8 r4 + 4 (l / 32) + i) as bf16 to rows of memory, whole rows at a time.
 template <typename F>
@@ -204,9 +256,29 @@ __device__ __forceinline__ void store_rows32(const F& value, __bf16* base, int64
     if (r0 + 4 * j < n_rows) *reinterpret_cast<bf16x8*>(dst) = lds_row8(own8k, 4 * j + (lane >> 4), lane & 15);
 }
 
+// The same for an accumulator of 16 x 16 tiles: value(db, qb, i) is column 16 db + 4 (l / 16) + i of row 16 qb + l % 16
+template <typename F>
+__device__ __forceinline__ void store_rows16(const F& value, __bf16* base, int64_t stride, int row0, int n_rows, lds_char* own8k) {
+  int lane = threadIdx.x & 63;
+  asm volatile("" : "+v"(lane));
+#pragma unroll
+  for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+    for (int db = 0; db < 8; ++db) {
+      bf16x4 v;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i] = (__bf16)value(db, qb, i);
+      *reinterpret_cast<SECO_LDS bf16x4*>(own8k + tile_off(16 * qb + (lane & 15), 2 * db + (lane >> 5)) + 8 * ((lane >> 4) & 1)) = v;
+    }
+  const int r0 = row0 + (lane >> 4);
+  __bf16* dst = base + (int64_t)r0 * stride + (lane & 15) * 8;
+#pragma unroll
+  for (int j = 0; j < 8; ++j, dst += 4 * stride)
+    if (r0 + 4 * j < n_rows) *reinterpret_cast<bf16x8*>(dst) = lds_row8(own8k, 4 * j + (lane >> 4), lane & 15);
+}
+
 // The same accumulator, fp32 and unscaled, to consecutive 512-byte rows (16.5 KiB of LDS)
 __device__ __forceinline__ void store_part32(const f32x16 (&acc)[4], float* base, int n_rows, lds_char* own) {
-  typedef float f32x4 __attribute__((ext_vector_type(4)));
   constexpr int kRow = 528;             // bytes; 16 of padding
   int lane = threadIdx.x & 63;
   asm volatile("" : "+v"(lane));
