@@ -7,8 +7,14 @@
 // swizzled, double-buffered LDS, copied global -> LDS directly one tile ahead; with KH = 2 (8 wavefronts, 128-row tiles) the two wavefronts
 // of a row block take one 64-row half of every tile each and their partial dQ are added
 // through LDS at the end.  Scores are again computed transposed (S^T = K Q^T, dP^T = V dO^T)
-// so that LSE and delta are per-lane scalars and dS^T feeds dQ^T += K^T dS^T from registers;
+// so that LSE and delta are two values per lane and dS^T feeds dQ^T += K^T dS^T from registers;
 // K^T comes from the same K tile through the LDS transpose read.
+//
+// Bound: power on long calls, as the forward, and products of 16x16x32 for the same reason (half the accumulator traffic of
+// 32x32x16): 2048 rows at 30720 of 32/8 heads 1278 -> 1236 us (2.03 GHz and the matrix pipe 59 % busy, before 1.81 and 66 %),
+// 1024 at 15360 345 -> 320, two sequences of 777 at 9324 366 -> 351.  Operands are read kAhead pairs of products ahead, held
+// there by a scheduling barrier per pair (2, 3, 4: within 1 %).  Writing dS of one block of 32 cache rows under the products
+// of the other (48 registers of scores for 32) spills 26 registers and more, which costs a third.
 //
 // Column-weighted dQ (SPARSE = true): the tiles are taken from a by-value table of runs of cache rows, each with
 // one positive weight w, instead of from all visible rows: dQ = s * sum over the runs of w * dS K.  A tile starts
@@ -32,6 +38,7 @@ namespace {
 
 constexpr int BM = 128;
 constexpr int BNW = 64;   // cache rows per wavefront and tile
+constexpr int kAhead = 3; // operand reads in flight ahead of the products
 
 // seg (SPARSE only): runs of cache rows in ascending order, each with a positive weight
 // smem: 4 * kTileBytes, [buf][K|V]
@@ -44,7 +51,7 @@ __device__ __forceinline__ void dq_bf16_body(const AttnParams& p, const SegTable
   // (the wavefront index through readfirstlane: the compiler then knows that it, and every tile coordinate and branch
   // condition derived from it, is uniform over the wavefront and keeps them in scalar registers)
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int l32 = lane & 31, g = lane >> 5;
+  const int l16 = lane & 15, g = lane >> 4, pg = pi4(g);
   const int rb = wave & 3, kh = (KH == 1 && !SPARSE) ? 0 : wave >> 2;
   int b, kvh, h, mt, m0, sp = 0;              // m0: first chunk-local row of this wavefront
   int n_sp = 1, slot = 0;                     // shares of this row tile; kShares: where this one's sums go
@@ -92,8 +99,7 @@ __device__ __forceinline__ void dq_bf16_body(const AttnParams& p, const SegTable
   }
 
   const int kv_len = p.q_start + p.C;
-  const int row = m0 + l32;
-  const int crow = min(row, p.C - 1);
+  const int row = m0 + l16;                    // this lane's first row; its second is 16 on
   const int qpos = p.q_start + row;
   // Q, dO, O, the row's LSE and (below) the first K/V tile are all requested before the first of them is waited for:
   // a workgroup starts with one memory round trip
@@ -104,8 +110,8 @@ __device__ __forceinline__ void dq_bf16_body(const AttnParams& p, const SegTable
     load_rows32(dor, static_cast<const __bf16*>(p.d_o) + ob, p.os[2], m0, p.C - 1, lane);
     load_rows32(orow, static_cast<const __bf16*>(p.o) + ob, p.os[2], m0, p.C - 1, lane);
   }
-  const int64_t stat = ((int64_t)b * p.Hq + h) * p.C + crow;
-  const float lse = p.lse[stat];
+  const float* lse_h = p.lse + ((int64_t)b * p.Hq + h) * p.C;
+  const float lse[2] = {lse_h[min(row, p.C - 1)], lse_h[min(row + 16, p.C - 1)]};
   const float c = p.scale * kLog2e;
 
   const __bf16* kbase = static_cast<const __bf16*>(p.k) + b * p.kvs[0] + kvh * p.kvs[1];
@@ -183,25 +189,18 @@ __device__ __forceinline__ void dq_bf16_body(const AttnParams& p, const SegTable
   };
 
   // lane-dependent parts of the LDS operand addresses (constant for the whole kernel)
-  int r_off[8];
-  TrOff t_off[4];
   // (dense variants: the wavefront's half of the tile, for KH = 2, is part of the per-lane offsets, so that a tile's
   // base is a compile-time constant in the unrolled loop below)
+  int r_off[4], t_off[8];
   const int half_off = SPARSE ? 0 : kh * BNW * kRowBytes;
 #pragma unroll
-  for (int t = 0; t < 8; ++t) r_off[t] = row8_lane_off(l32, 2 * t + g) + half_off;
+  for (int t = 0; t < 4; ++t) r_off[t] = row16_lane_off(t, lane) + half_off;
 #pragma unroll
-  for (int db = 0; db < 4; ++db) {
-    t_off[db] = tr8_lane_off(db, lane);
-    t_off[db].lo += half_off;
-    t_off[db].hi += half_off;
-  }
+  for (int db = 0; db < 8; ++db) t_off[db] = tr16_lane_off(db, lane) + half_off;
 
-  f32x16 dq[4];
+  f32x4 dq[8][2];
 #pragma unroll
-  for (int db = 0; db < 4; ++db)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) dq[db][r] = 0.f;
+  for (int db = 0; db < 8; ++db) dq[db][0] = dq[db][1] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   Cur cur{0, n_begin * BN, 0};
   if constexpr (SPARSE) {
@@ -212,29 +211,32 @@ __device__ __forceinline__ void dq_bf16_body(const AttnParams& p, const SegTable
   if (n_begin < n_end) copy_tile(cur.col, 0);
   bf16x8 qf[8], dof[8], of[8];
   lds_char* own = smem + 2 * kTileBytes + wave * 8192;      // of the second tile buffer, which is empty until the loop
-  rows32_to_frags(qf, qr, own, lane);
-  rows32_to_frags(dof, dor, own, lane);
-  rows32_to_frags(of, orow, own, lane);
-  const float lse_c = lse * kLog2e;
-  // delta = rowsum(dO * O), from the dO fragments and the matching O fragments: a lane holds half of its row's
-  // head_dim (the other half is in lane ^ 32).  It is also written to the workspace for the dK/dV kernel that follows
-  // on the same stream, negated, together with -LSE / s (the log-sum-exp in units of the unscaled dot product): the
+  rows16_to_frags(qf, qr, own, lane);
+  rows16_to_frags(dof, dor, own, lane);
+  rows16_to_frags(of, orow, own, lane);
+  // delta = rowsum(dO * O), from the dO fragments and the matching O fragments: a lane holds a quarter of each of its two
+  // rows' head_dim (the rest is in lane ^ 16, ^ 32, ^ 48).  It is also written to the workspace for the dK/dV kernel that
+  // follows on the same stream, negated, together with -LSE / s (the log-sum-exp in units of the unscaled dot product): the
   // two values that kernel starts its MFMA chains from.
-  float delta;
-  {
-    float part[8];                     // by chunk of 8 elements, then pairwise (as OWN in bwd_dkdv_body.h adds them)
+  float lse_c[2], delta[2];
 #pragma unroll
-    for (int t = 0; t < 8; ++t) {
+  for (int qb = 0; qb < 2; ++qb) {
+    float part[4];                     // by chunk of 8 elements, then pairwise (as OWN in bwd_dkdv_body.h adds them)
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
       part[t] = 0.f;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) part[t] = __builtin_fmaf((float)of[t][i], (float)dof[t][i], part[t]);
+      for (int i = 0; i < 8; ++i) part[t] = __builtin_fmaf((float)of[4 * qb + t][i], (float)dof[4 * qb + t][i], part[t]);
     }
-    delta = ((part[0] + part[4]) + (part[2] + part[6])) + ((part[1] + part[5]) + (part[3] + part[7]));
-    delta += __shfl_xor(delta, 32);
-    if (kh == 0 && sp == 0 && g == 0 && row < p.C) {
-      const int64_t kept = ((int64_t)b * p.Hq + h) * p.stat_stride + p.stat_off + crow;
-      p.delta[kept] = -delta;
-      p.nlse2[kept] = -lse / p.scale;
+    float d = (part[0] + part[2]) + (part[1] + part[3]);
+    d += __shfl_xor(d, 32);
+    d += __shfl_xor(d, 16);
+    delta[qb] = d;
+    lse_c[qb] = lse[qb] * kLog2e;
+    if (kh == 0 && sp == 0 && g == 0 && row + 16 * qb < p.C) {
+      const int64_t kept = ((int64_t)b * p.Hq + h) * p.stat_stride + p.stat_off + row + 16 * qb;
+      p.delta[kept] = -d;
+      p.nlse2[kept] = -lse[qb] / p.scale;
     }
   }
   dma_wait_all();
@@ -263,42 +265,30 @@ __device__ __forceinline__ void dq_bf16_body(const AttnParams& p, const SegTable
 
   if (KH == 2) {
     // add the partial dQ of the two column halves of each row block through LDS
-    typedef float f32x4 __attribute__((ext_vector_type(4)));
     lds_char* slot = smem + rb * (17 * 1024);
     if (kh == 1) {
 #pragma unroll
-      for (int db = 0; db < 4; ++db)
-#pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4) {
-          f32x4 v = {dq[db][4 * r4], dq[db][4 * r4 + 1], dq[db][4 * r4 + 2], dq[db][4 * r4 + 3]};
-          *reinterpret_cast<SECO_LDS f32x4*>(slot + ((db * 4 + r4) * 64 + lane) * 16) = v;
-        }
+      for (int i = 0; i < 16; ++i) *reinterpret_cast<SECO_LDS f32x4*>(slot + (i * 64 + lane) * 16) = dq[i >> 1][i & 1];
     }
     __syncthreads();
     if (kh == 1 || m0 >= p.C) return;
 #pragma unroll
-    for (int db = 0; db < 4; ++db)
-#pragma unroll
-      for (int r4 = 0; r4 < 4; ++r4) {
-        const f32x4 v = *reinterpret_cast<SECO_LDS f32x4*>(slot + ((db * 4 + r4) * 64 + lane) * 16);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) dq[db][4 * r4 + i] += v[i];
-      }
+    for (int i = 0; i < 16; ++i) dq[i >> 1][i & 1] += *reinterpret_cast<SECO_LDS f32x4*>(slot + (i * 64 + lane) * 16);
   }
 
   if constexpr (SPLIT == kShares) {
     if (n_sp > 1) {                            // all 32 rows: the merge takes those that exist
-      store_part32(dq, p.part + ((int64_t)slot * BM + rb * 32) * kHeadDim, 32, smem + rb * (17 * 1024));
+      store_part16(dq, p.part + ((int64_t)slot * BM + rb * 32) * kHeadDim, 32, smem + rb * (17 * 1024));
       return;
     }
   }
   if constexpr (SPLIT == kDivided) {
     float* po = p.part + ((int64_t)sp * p.B * p.Hq * p.C + ((int64_t)b * p.Hq + h) * p.C + m0) * kHeadDim;
-    store_part32(dq, po, p.C - m0, smem + rb * (17 * 1024));
+    store_part16(dq, po, p.C - m0, smem + rb * (17 * 1024));
     return;
   }
 
-  store_rows32([&](int db, int r) { return dq[db][r] * p.scale; },
+  store_rows16([&](int db, int qb, int i) { return dq[db][qb][i] * p.scale; },
                static_cast<__bf16*>(p.d_q) + b * p.qs[0] + h * p.qs[1], p.qs[2], m0, p.C,
                KH == 2 ? smem + rb * (17 * 1024) : smem + wave * 8192);
 }

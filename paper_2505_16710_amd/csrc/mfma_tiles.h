@@ -135,21 +135,29 @@ __device__ __forceinline__ bf16x8 pack44(const f32x4& x, const f32x4& y) {
   }
   return __builtin_bit_cast(bf16x8, r);
 }
-// 16 rows (row0: multiple of 16; lane: row pi(l % 16)) as an operand, contraction 32 t .. 32 t + 31 of head_dim
-__device__ __forceinline__ bf16x8 lds_row16(lds_char* tile, int row0, int t, int lane) {
-  const int r = 4 * pi4((lane >> 2) & 3) + (lane & 3);
-  return *reinterpret_cast<SECO_LDS bf16x8*>(tile + tile_off(r, 4 * t + (lane >> 4)) + row0 * kRowBytes);
+// Per-lane offsets of operands in a tile, constant for a whole kernel, and the reads themselves (row0: multiple of 16):
+// 16 rows (lane: row pi(l % 16)), contraction 32 t .. 32 t + 31 of head_dim
+__device__ __forceinline__ int row16_lane_off(int t, int lane) {
+  return tile_off(4 * pi4((lane >> 2) & 3) + (lane & 3), 4 * t + (lane >> 4));
 }
-// head_dim column 16 db + lane % 16, contraction over the 32 rows from row0 (multiple of 16) on, slots as pack44's
-__device__ __forceinline__ bf16x8 lds_tr16(lds_char* tile, int row0, int db, int lane) {
+__device__ __forceinline__ bf16x8 lds_at(lds_char* tile_plus_off, int row0) {
+  return *reinterpret_cast<SECO_LDS bf16x8*>(tile_plus_off + row0 * kRowBytes);
+}
+// head_dim column 16 db + lane % 16, contraction over the 32 rows from row0 on, slots as pack44's
+__device__ __forceinline__ int tr16_lane_off(int db, int lane) {
   const int ii = lane & 15;
-  lds_char* a = tile + tile_off(4 * pi4(lane >> 4) + (ii >> 2), 2 * db + ((ii & 3) >> 1)) + ((ii & 1) << 3) + row0 * kRowBytes;
+  return tile_off(4 * pi4(lane >> 4) + (ii >> 2), 2 * db + ((ii & 3) >> 1)) + ((ii & 1) << 3);
+}
+__device__ __forceinline__ bf16x8 lds_tr16_at(lds_char* tile_plus_off, int row0) {
+  lds_char* a = tile_plus_off + row0 * kRowBytes;
   const s16x4 x = __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<SECO_LDS s16x4*>(a));
   const s16x4 y = __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<SECO_LDS s16x4*>(a + 16 * kRowBytes));
   typedef short s16x8 __attribute__((ext_vector_type(8)));
   const s16x8 r = {x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]};
   return __builtin_bit_cast(bf16x8, r);
 }
+__device__ __forceinline__ bf16x8 lds_row16(lds_char* tile, int row0, int t, int lane) { return lds_at(tile + row16_lane_off(t, lane), row0); }
+__device__ __forceinline__ bf16x8 lds_tr16(lds_char* tile, int row0, int db, int lane) { return lds_tr16_at(tile + tr16_lane_off(db, lane), row0); }
 
 // registers 8t .. 8t+7 of a C tile, rounded to bf16 (pairwise, one v_cvt_pk_bf16_f32 per pair),
 // as an operand over 16 contraction steps
@@ -289,6 +297,24 @@ __device__ __forceinline__ void store_part32(const f32x16 (&acc)[4], float* base
       const f32x4 v = {acc[db][4 * r4], acc[db][4 * r4 + 1], acc[db][4 * r4 + 2], acc[db][4 * r4 + 3]};
       *reinterpret_cast<SECO_LDS f32x4*>(own + (lane & 31) * kRow + (32 * db + 8 * r4 + 4 * (lane >> 5)) * 4) = v;
     }
+#pragma unroll
+  for (int j = 0; j < 16; ++j) {
+    const int r = 2 * j + (lane >> 5);
+    const f32x4 v = *reinterpret_cast<SECO_LDS f32x4*>(own + r * kRow + (lane & 31) * 16);
+    if (r < n_rows) *reinterpret_cast<f32x4*>(base + r * kHeadDim + (lane & 31) * 4) = v;
+  }
+}
+
+// ... of 16 x 16 tiles (as store_rows16)
+__device__ __forceinline__ void store_part16(const f32x4 (&acc)[8][2], float* base, int n_rows, lds_char* own) {
+  constexpr int kRow = 528;             // bytes; 16 of padding
+  int lane = threadIdx.x & 63;
+  asm volatile("" : "+v"(lane));
+#pragma unroll
+  for (int db = 0; db < 8; ++db)
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb)
+      *reinterpret_cast<SECO_LDS f32x4*>(own + (16 * qb + (lane & 15)) * kRow + (16 * db + 4 * (lane >> 4)) * 4) = acc[db][qb];
 #pragma unroll
   for (int j = 0; j < 16; ++j) {
     const int r = 2 * j + (lane >> 5);
