@@ -40,10 +40,10 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-I", INCLUDE, "
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wall", "-Wno-unused-function", "-Wno-inline-asm"]
 # Machine scheduler strategy of the compiler, per source file (measured on the benchmark shapes, every strategy
-# tried on every matrix-core kernel): keeping memory (LDS) instructions in clauses is at least as good as the default on
-# the dK/dV kernel; the 8-wavefront forward is 3 % faster with the iterative ILP scheduler, the 4-wavefront forward and
-# the dQ kernels, whose order is fixed step by step in the source, 1 - 2 % with the plain ILP one.
-SCHED = {"fwd4_bf16.hip": "max-ilp", "bwd_dq_bf16.hip": "max-ilp", "fwd_bf16.hip": "iterative-ilp", "fwd4_split_bf16.hip": "iterative-ilp",
+# tried on every matrix-core kernel): the 8-wavefront forward is 3 % faster with the iterative ILP scheduler than with
+# memory (LDS) instructions kept in clauses, the 4-wavefront forward, the dQ and the dK/dV kernels, whose order is fixed
+# step by step in the source, 1 - 2 % with the plain ILP one; the launch that holds both passes is slower with either.
+SCHED = {"fwd4_bf16.hip": "max-ilp", "bwd_dq_bf16.hip": "max-ilp", "bwd_dkdv_bf16.hip": "max-ilp", "fwd_bf16.hip": "iterative-ilp", "fwd4_split_bf16.hip": "iterative-ilp",
          "fwd8_shares_bf16.hip": "iterative-ilp"}
 SCHED_DEFAULT = "max-memory-clause"
 # ... and up to half a per cent when the scheduler does not cluster memory operations

@@ -6,7 +6,7 @@
 namespace seco {
 namespace {
 
-template <int NCB, int RB, bool ROWS>
+template <int NCB, int RB, bool ROWS, class Products>
 __global__ __launch_bounds__(NCB * 128, 2) void dkdv_bf16_kernel(AttnParams p, SegTable seg, TailSplit ts,
                                                                   RowRuns rr, int total_items) {
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];   // Cfg::kSmemBytes (can exceed the 64 KiB static limit)
@@ -16,9 +16,9 @@ __global__ __launch_bounds__(NCB * 128, 2) void dkdv_bf16_kernel(AttnParams p, S
   // wavefronts 0 .. NCB-1: role A, the others role B (wavefront-uniform: a scalar branch)
   const int role_u = __builtin_amdgcn_readfirstlane((int)threadIdx.x / (64 * NCB));
   if (role_u == 0)
-    dkdv_bf16_body<NCB, RB, ROWS, 0>(p, seg, ts, rr, item, smem);
+    dkdv_bf16_body<NCB, RB, ROWS, 0, Products>(p, seg, ts, rr, item, smem);
   else
-    dkdv_bf16_body<NCB, RB, ROWS, 1>(p, seg, ts, rr, item, smem);
+    dkdv_bf16_body<NCB, RB, ROWS, 1, Products>(p, seg, ts, rr, item, smem);
 }
 
 template <int COLS>
@@ -28,10 +28,10 @@ __global__ __launch_bounds__(256) void dkdv_tail_merge_kernel(AttnParams p, SegT
 
 using Cfg = DkdvCfg<kColTileBf16 / 32, SECO_DKDV_RB>;
 
-template <bool ROWS>
+template <bool ROWS, class Products>
 int launch(const AttnParams& p, const SegTable& seg, const TailSplit& ts, const RowRuns& rr, hipStream_t s) {
   const int total = p.Hkv * p.B * (seg.tile_begin[seg.n] - ts.plan.n_tiles + ts.plan.n_entries);
-  auto kern = dkdv_bf16_kernel<kColTileBf16 / 32, SECO_DKDV_RB, ROWS>;
+  auto kern = dkdv_bf16_kernel<kColTileBf16 / 32, SECO_DKDV_RB, ROWS, Products>;
   static std::atomic<uint64_t> ready{0};
   if (!allow_lds(ready, reinterpret_cast<const void*>(kern), Cfg::kSmemBytes)) return SECO_ERR_LAUNCH;
   {
@@ -60,7 +60,8 @@ int launch_dkdv_bf16(const AttnParams& p, const SegTable& seg, hipStream_t s) {
   int rc = dq ? launch_dq_bf16_now(p, runs, s) : SECO_OK;
   RowRuns none;
   none.n = 0;
-  return rc ? rc : launch<false>(p, seg, plan.ts, none, s);
+  if (rc) return rc;
+  return plan.dq_splits > 0 ? launch<false, Products32>(p, seg, plan.ts, none, s) : launch<false, Products16>(p, seg, plan.ts, none, s);
 }
 
 int launch_dkdv_rows_bf16(const AttnParams& p, const SegTable& seg, const RowRuns& rr, hipStream_t s) {
@@ -71,7 +72,7 @@ int launch_dkdv_rows_bf16(const AttnParams& p, const SegTable& seg, const RowRun
   ts.part = p.tail_part;
   float time;
   ts.plan = share_plan(tile_iterations<Cfg, true>(p, seg, rr), p.B * p.Hkv, seg.tile_begin[seg.n], p.G, n_rows, slots_in(p.tail_bytes), time);
-  return launch<true>(p, seg, ts, rr, s);
+  return launch<true, Products16>(p, seg, ts, rr, s);
 }
 
 }  // namespace seco

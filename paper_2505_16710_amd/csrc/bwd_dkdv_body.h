@@ -80,6 +80,125 @@ struct DkdvCfg {
   static constexpr int kCols = NCB * 32;                                // cache rows per workgroup
 };
 
+// The products of a wavefront, in either shape of the matrix instructions: a chain is eight steps, each with one 16-byte
+// operand from LDS, and gives a row block's 32 x 32 scores (or dP); a sum is eight steps too and adds a row block to the
+// 32 x 128 accumulator.  Element e of a lane's sixteen scores is element e % 8 of operand half e / 8 of the second product,
+// and belongs to query row row_of(e) + lane_row and cache row col_of(e) + lane_col of the block.
+//
+// 16x16x32, for whole launches of this pass: they are bound by power, and these take half the accumulator traffic per
+// operation (2048 rows at 30720 of 32/8 heads 1949 -> 1841 us, 1024 at 15360 503 -> 477; the order of each step is fixed by a
+// scheduling barrier, without which 1868 and 485).
+struct Products16 {
+  using Tile = f32x4[2][2];              // [16 query rows][16 cache rows]
+  using Init = f32x4[2];
+  using Acc = f32x4[8][2];
+  int r_off[4], t_off[8], lane_row, lane_col;
+  __device__ __forceinline__ Products16(int lane, int r_region, int t_region) {
+    lane_col = lane & 15;
+    lane_row = 4 * pi4(lane >> 4);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) r_off[t] = row16_lane_off(t, lane) + r_region;
+#pragma unroll
+    for (int db = 0; db < 8; ++db) t_off[db] = tr16_lane_off(db, lane) + t_region;
+  }
+  static __device__ __forceinline__ int row_of(int e) { return 16 * ((e >> 2) & 1) + (e & 3); }
+  static __device__ __forceinline__ int col_of(int e) { return 16 * (e >> 3); }
+  static __device__ __forceinline__ void frags(bf16x8 (&f)[8], const bf16x8 (&x)[8], lds_char* own, int lane) { rows16_to_frags(f, x, own, lane); }
+  // operand i of a row block's chain (row0: the block's first row), and of its sum
+  __device__ __forceinline__ bf16x8 row_op(lds_char* tile, int row0, int i) const { return lds_at(tile + r_off[i >> 1], row0 + 16 * (i & 1)); }
+  __device__ __forceinline__ bf16x8 col_op(lds_char* tile, int row0, int i) const { return lds_tr16_at(tile + t_off[i], row0); }
+  // what a chain starts from: the statistic of the lane's query rows
+  __device__ __forceinline__ void chain_init(Init& x, SECO_LDS float* stat) const {
+#pragma unroll
+    for (int r = 0; r < 2; ++r) x[r] = *reinterpret_cast<SECO_LDS f32x4*>(stat + 16 * r + lane_row);
+  }
+  static __device__ __forceinline__ void add(Init& x, float v) {
+    x[0] += v;
+    x[1] += v;
+  }
+  static __device__ __forceinline__ void chain(Tile& x, int i, bf16x8 a, const bf16x8 (&frag)[8], const Init& init) {
+#pragma unroll
+    for (int c = 0; c < 2; ++c) x[i & 1][c] = mfma16(a, frag[4 * c + (i >> 1)], i < 2 ? init[i & 1] : x[i & 1][c]);
+  }
+  static __device__ __forceinline__ void sum(Acc& acc, int i, const bf16x8 (&pr)[2], bf16x8 b) {
+#pragma unroll
+    for (int c = 0; c < 2; ++c) acc[i][c] = mfma16(pr[c], b, acc[i][c]);
+  }
+  template <typename F>
+  static __device__ __forceinline__ void map(Tile& x, int e, const F& f) { x[(e >> 2) & 1][e >> 3][e & 3] = f(x[(e >> 2) & 1][e >> 3][e & 3]); }
+  static __device__ __forceinline__ bf16x8 pack(const Tile& x, int half) { return pack44(x[0][half], x[1][half]); }
+  static __device__ __forceinline__ void step_end() { __builtin_amdgcn_sched_barrier(0); }
+  static __device__ __forceinline__ void clear(Acc& acc) {
+#pragma unroll
+    for (int db = 0; db < 8; ++db) acc[db][0] = acc[db][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  // put(row of the wavefront's 32, column, value)
+  template <typename F>
+  static __device__ __forceinline__ void each(const Acc& acc, int lane, const F& put) {
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int db = 0; db < 8; ++db) put(16 * c + 4 * (lane >> 4) + i, 16 * db + (lane & 15), acc[db][c][i]);
+  }
+};
+// 32x32x16, for the short launches that hold dQ as well: a workgroup's few iterations wait for latencies, not for power, and
+// vector instructions cost less beside these (probe, cycles per 32 of the matrix pipe with 4 multiply-adds and an
+// exponential: 39 against 47): 512 rows at 3584 of 8/2 heads 47.5 us against 50.2, 512 at 0 of 32/8 30.0 against 31.0.  A
+// call whose passes could share a launch but for what its outputs lie over takes them too: the same bits of gK and gV.
+struct Products32 {
+  using Tile = f32x16;
+  using Init = f32x16;
+  using Acc = f32x16[4];
+  int r_off[8], lane_row, lane_col;
+  TrOff t_off[4];
+  __device__ __forceinline__ Products32(int lane, int r_region, int t_region) {
+    lane_col = lane & 31;
+    lane_row = 4 * (lane >> 5);
+#pragma unroll
+    for (int t = 0; t < 8; ++t) r_off[t] = row8_lane_off(lane & 31, 2 * t + (lane >> 5)) + r_region;
+#pragma unroll
+    for (int db = 0; db < 4; ++db) {
+      t_off[db] = tr8_lane_off(db, lane);
+      t_off[db].lo += t_region;
+      t_off[db].hi += t_region;
+    }
+  }
+  static __device__ __forceinline__ int row_of(int e) { return 8 * (e >> 2) + (e & 3); }
+  static __device__ __forceinline__ int col_of(int) { return 0; }
+  static __device__ __forceinline__ void frags(bf16x8 (&f)[8], const bf16x8 (&x)[8], lds_char* own, int lane) { rows32_to_frags(f, x, own, lane); }
+  __device__ __forceinline__ bf16x8 row_op(lds_char* tile, int row0, int i) const { return lds_at(tile + r_off[i], row0); }
+  __device__ __forceinline__ bf16x8 col_op(lds_char* tile, int row0, int i) const { return lds_tr8_at(tile, t_off[i & 3], row0 + 16 * (i >> 2)); }
+  __device__ __forceinline__ void chain_init(Init& x, SECO_LDS float* stat) const {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) x[r] = stat[row_of(r) + lane_row];
+  }
+  static __device__ __forceinline__ void add(Init& x, float v) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) x[r] += v;
+  }
+  static __device__ __forceinline__ void chain(Tile& x, int i, bf16x8 a, const bf16x8 (&frag)[8], const Init& init) { x = mfma(a, frag[i], i == 0 ? init : x); }
+  static __device__ __forceinline__ void sum(Acc& acc, int i, const bf16x8 (&pr)[2], bf16x8 b) { acc[i & 3] = mfma(pr[i >> 2], b, acc[i & 3]); }
+  template <typename F>
+  static __device__ __forceinline__ void map(Tile& x, int e, const F& f) { x[e] = f(x[e]); }
+  static __device__ __forceinline__ bf16x8 pack(const Tile& x, int half) { return pack8(x, half); }
+  static __device__ __forceinline__ void step_end() {}
+  static __device__ __forceinline__ void clear(Acc& acc) {
+#pragma unroll
+    for (int db = 0; db < 4; ++db)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[db][r] = 0.f;
+  }
+  template <typename F>
+  static __device__ __forceinline__ void each(const Acc& acc, int lane, const F& put) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+#pragma unroll
+      for (int db = 0; db < 4; ++db) put(row_of(r) + 4 * (lane >> 5), 32 * db + (lane & 31), acc[db][r]);
+  }
+};
+
 // (RB is fixed to 2 by the hand-pipelined main loop.)
 // ROWS: the query rows are taken from a table of runs (rows relative to p.q_start, each run with one weight whose
 // log2 is added to -LSE, i.e. its probabilities are scaled by the weight) instead of being all p.C rows with weight 1.
@@ -88,7 +207,7 @@ struct DkdvCfg {
 // loop, unrolled over the ring slots, the register allocator could not keep the working set in registers.
 // OWN: the row statistics (-LSE / s and -delta) are computed here, from the O and dO rows of each stage, instead of being
 // taken from the arrays the dQ kernel leaves: for the launch that runs both passes at once.
-template <int NCB, int RB, bool ROWS, int ROLE, bool OWN = false>
+template <int NCB, int RB, bool ROWS, int ROLE, class Products, bool OWN = false>
 __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTable& seg, const TailSplit& ts,
                                                const RowRuns& rr, int item, lds_char* smem) {
   using Cfg = DkdvCfg<NCB, RB>;
@@ -100,7 +219,6 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
   lds_char* pbuf = smem + Cfg::kPRegion;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int l32 = lane & 31, g = lane >> 5;
   constexpr int role = ROLE;
   const int cb = wave % NCB;
   // item -> (batch, kv head, column tile, share of the tile's iterations); the listed tiles come last in a unit
@@ -125,7 +243,6 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
 
   const int kv_len = p.q_start + p.C;
   const int n0 = c0 + cb * 32;     // first cache row of this wavefront
-  const int col = n0 + l32;        // this lane's cache row in the score tile
   // role A holds K^T fragments, role B holds V^T fragments
   bf16x8 frag[8], fr[8];
   load_rows32(fr, static_cast<const __bf16*>(role == 0 ? p.k : p.v) + b * p.kvs[0] + kvh * p.kvs[1], p.kvs[2], n0, kv_len - 1, lane);
@@ -274,25 +391,11 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
   };
 
   // lane-dependent parts of the LDS operand addresses (constant for the whole kernel)
-  int r_off[8];
-  TrOff t_off[4];
   // role A reads rows of Q and transposed blocks of dO, role B rows of dO and transposed blocks of Q: the region of
   // the tile an offset is used with is part of the offset
-  const int r_region = role == 0 ? 0 : kDoRegion, t_region = role == 0 ? kDoRegion : 0;
-#pragma unroll
-  for (int t = 0; t < 8; ++t) r_off[t] = row8_lane_off(l32, 2 * t + g) + r_region;
-#pragma unroll
-  for (int db = 0; db < 4; ++db) {
-    t_off[db] = tr8_lane_off(db, lane);
-    t_off[db].lo += t_region;
-    t_off[db].hi += t_region;
-  }
-
-  f32x16 acc[4];   // role A: dV, role B: dK  (32 cache rows x 128)
-#pragma unroll
-  for (int db = 0; db < 4; ++db)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[db][r] = 0.f;
+  const Products op(lane, role == 0 ? 0 : kDoRegion, role == 0 ? kDoRegion : 0);
+  typename Products::Acc acc;   // role A: dV, role B: dK  (32 cache rows x 128)
+  Products::clear(acc);
 
   // P of the stage held in slot `slot`, row block rb, this wavefront's column block: p_lane is the lane-dependent
   // part of the address (the lane's 16 bytes of the wavefront's block), the rest a constant per slot and row block
@@ -300,40 +403,36 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
   auto pslot = [&](int slot, int rb) { return pbuf + (slot * NCB * RB + rb) * kPBytes + p_lane; };
 
   // zero the probabilities of a 32x32 block (first query position qpos0) that lie above the diagonal
-  // (register r of a score tile holds query row 8 (r / 4) + 4 g + r % 4 of the block: the lane-dependent part of the
-  // comparison is one value, the rest compile-time constants, so that nothing per-lane has to be kept for it)
-  auto mask_above_diagonal = [&](f32x16& s, int qpos0) {
+  // (the lane-dependent part of the comparison is one value, the rest compile-time constants, so that nothing per-lane has
+  // to be kept for it)
+  using Tile = typename Products::Tile;
+  using Init = typename Products::Init;
+  auto mask_above_diagonal = [&](Tile& s, int qpos0) {
     if (n0 + 31 > qpos0) {
-      const int ahead = col - qpos0 - 4 * g;
+      const int ahead = n0 + op.lane_col - qpos0 - op.lane_row;
 #pragma unroll
-      for (int r = 0; r < 16; ++r)
-        if (ahead > 8 * (r >> 2) + (r & 3)) s[r] = 0.f;
+      for (int e = 0; e < 16; ++e)
+        if (ahead + Products::col_of(e) > Products::row_of(e)) Products::map(s, e, [](float) { return 0.f; });
     }
   };
+  auto prob = [&](Tile& s, int e) { Products::map(s, e, [&](float x) { return fast_exp2(x * c2); }); };
 
   // role A: S = Q K^T for row block rb of the stage in `slot`, P = exp2(c2 * (S - LSE / s)) with the causal mask;
   // P goes to pbuf as two operand halves (lane-contiguous 16-byte words)
   auto scores = [&](int slot, int r0, int rb, float lw) {   // lw: log2 of the rows' weight, divided by c2
     lds_char* qt = smem + slot * kTileBytes;
-    SECO_LDS float* lse_s = reinterpret_cast<SECO_LDS float*>(smem + kStatRegion + slot * kStatBytes) + 32 * rb;
-    bf16x8 a[8];
+    Init init;
+    op.chain_init(init, reinterpret_cast<SECO_LDS float*>(smem + kStatRegion + slot * kStatBytes) + 32 * rb);
+    if constexpr (ROWS) Products::add(init, lw);
+    Tile s;
 #pragma unroll
-    for (int t = 0; t < 8; ++t) a[t] = lds_row8(qt, 32 * rb + l32, 2 * t + g);
-    f32x16 s;
+    for (int i = 0; i < 8; ++i) Products::chain(s, i, op.row_op(qt, 32 * rb, i), frag, init);
 #pragma unroll
-    for (int r = 0; r < 16; ++r) s[r] = lse_s[8 * (r >> 2) + 4 * g + (r & 3)];
-    if constexpr (ROWS) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) s[r] += lw;
-    }
-#pragma unroll
-    for (int t = 0; t < 8; ++t) s = mfma(a[t], frag[t], s);
-#pragma unroll
-    for (int r = 0; r < 16; ++r) s[r] = fast_exp2(s[r] * c2);
+    for (int e = 0; e < 16; ++e) prob(s, e);
     mask_above_diagonal(s, p.q_start + r0 + 32 * rb);
     lds_char* pb = pslot(slot, rb);
-    *reinterpret_cast<SECO_LDS bf16x8*>(pb) = pack8(s, 0);
-    *reinterpret_cast<SECO_LDS bf16x8*>(pb + 1024) = pack8(s, 1);
+    *reinterpret_cast<SECO_LDS bf16x8*>(pb) = Products::pack(s, 0);
+    *reinterpret_cast<SECO_LDS bf16x8*>(pb + 1024) = Products::pack(s, 1);
   };
 
   Pos cur{0, first_r0, first_ri};
@@ -363,7 +462,7 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
     }
   }
   // (through the third slot's Q and dO tiles and the P buffers, which are empty until the barriers below)
-  rows32_to_frags(frag, fr, wave < 4 ? smem + (wave < 2 ? 0 : kDoRegion) + 2 * kTileBytes + (wave & 1) * 8192
+  Products::frags(frag, fr, wave < 4 ? smem + (wave < 2 ? 0 : kDoRegion) + 2 * kTileBytes + (wave & 1) * 8192
                                      : pbuf + (wave - 4) * 8192, lane);
   settle8(frag);
   dma_wait_all();
@@ -397,10 +496,10 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
       pa1[t] = p_half(pslot(0, 1), t);
     }
 #pragma unroll
-    for (int i = 0; i < 8; ++i) x[i] = lds_tr8_at(smem, t_off[i & 3], 16 * (i >> 2));
+    for (int i = 0; i < 8; ++i) x[i] = op.col_op(smem, 0, i);
   } else {
 #pragma unroll
-    for (int t = 0; t < 8; ++t) x[t] = lds_row8_at(smem + r_off[t], 0);
+    for (int i = 0; i < 8; ++i) x[i] = op.row_op(smem, 0, i);
   }
 
   int slot = 0;   // it % kStages
@@ -437,39 +536,38 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
       // dV of row block 0; Q rows of row block 0 of the next stage come in behind
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
-        acc[i & 3] = mfma(pa0[i >> 2], x[i], acc[i & 3]);
-        x[i] = lds_row8_at(t1 + r_off[i], 0);
+        Products::sum(acc, i, pa0, x[i]);
+        x[i] = op.row_op(t1, 0, i);
+        Products::step_end();
       }
       issue_copies();
-      f32x16 s0, s1;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) s0[r] = lse_s[8 * (r >> 2) + 4 * g + (r & 3)];
-#pragma unroll
-      for (int r = 0; r < 16; ++r) s1[r] = lse_s[32 + 8 * (r >> 2) + 4 * g + (r & 3)];
+      Init init0, init1;
+      op.chain_init(init0, lse_s);
+      op.chain_init(init1, lse_s + 32);
       if constexpr (ROWS) {                   // probabilities of the next stage's rows carry their run's weight
         const float lw = rr.log2w[nxt.ri] / c2;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          s0[r] += lw;
-          s1[r] += lw;
-        }
+        Products::add(init0, lw);
+        Products::add(init1, lw);
       }
+      Tile s0, s1;
       // log2 P of row block 0 (chain started from -LSE); Q rows of row block 1 come in behind
 #pragma unroll
-      for (int t = 0; t < 8; ++t) {
-        s0 = mfma(x[t], frag[t], s0);
-        x[t] = lds_row8_at(t1 + r_off[t], 32);
+      for (int i = 0; i < 8; ++i) {
+        Products::chain(s0, i, x[i], frag, init0);
+        x[i] = op.row_op(t1, 32, i);
+        Products::step_end();
       }
       // log2 P of row block 1, with the exponentials of row block 0; dO^T of row block 1 (stage `it`) comes in behind
 #pragma unroll
-      for (int t = 0; t < 8; ++t) {
-        s1 = mfma(x[t], frag[t], s1);
-        x[t] = lds_tr8_at(t0, t_off[t & 3], 32 + 16 * (t >> 2));
-        s0[2 * t] = fast_exp2(s0[2 * t] * c2);
-        s0[2 * t + 1] = fast_exp2(s0[2 * t + 1] * c2);
+      for (int i = 0; i < 8; ++i) {
+        Products::chain(s1, i, x[i], frag, init1);
+        x[i] = op.col_op(t0, 32, i);
+        prob(s0, 2 * i);
+        prob(s0, 2 * i + 1);
+        Products::step_end();
       }
       mask_above_diagonal(s0, p.q_start + nxt.r0);
-      const bf16x8 pn0[2] = {pack8(s0, 0), pack8(s0, 1)};
+      const bf16x8 pn0[2] = {Products::pack(s0, 0), Products::pack(s0, 1)};
       lds_char* pw0 = pslot(slot1, 0);
       *reinterpret_cast<SECO_LDS bf16x8*>(pw0) = pn0[0];
       *reinterpret_cast<SECO_LDS bf16x8*>(pw0 + 1024) = pn0[1];
@@ -477,16 +575,17 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
       // stage comes in behind (for the first chain of the next iteration)
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
-        acc[i & 3] = mfma(pa1[i >> 2], x[i], acc[i & 3]);
-        x[i] = lds_tr8_at(t1, t_off[i & 3], 16 * (i >> 2));
-        s1[2 * i] = fast_exp2(s1[2 * i] * c2);
-        s1[2 * i + 1] = fast_exp2(s1[2 * i + 1] * c2);
+        Products::sum(acc, i, pa1, x[i]);
+        x[i] = op.col_op(t1, 0, i);
+        prob(s1, 2 * i);
+        prob(s1, 2 * i + 1);
+        Products::step_end();
       }
       mask_above_diagonal(s1, p.q_start + nxt.r0 + 32);
       pa0[0] = pn0[0];
       pa0[1] = pn0[1];
-      pa1[0] = pack8(s1, 0);
-      pa1[1] = pack8(s1, 1);
+      pa1[0] = Products::pack(s1, 0);
+      pa1[1] = Products::pack(s1, 1);
       lds_char* pw1 = pslot(slot1, 1);
       *reinterpret_cast<SECO_LDS bf16x8*>(pw1) = pa1[0];
       *reinterpret_cast<SECO_LDS bf16x8*>(pw1 + 1024) = pa1[1];
@@ -497,41 +596,45 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
       const bf16x8 ph0[2] = {p_half(pb0, 0), p_half(pb0, 1)};
       lds_char* pb1 = pslot(slot, 1);
       const bf16x8 ph1[2] = {p_half(pb1, 0), p_half(pb1, 1)};
-      f32x16 d0, d1;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) d0[r] = delta_s[8 * (r >> 2) + 4 * g + (r & 3)];
-#pragma unroll
-      for (int r = 0; r < 16; ++r) d1[r] = delta_s[32 + 8 * (r >> 2) + 4 * g + (r & 3)];
+      Init init0, init1;
+      op.chain_init(init0, delta_s);
+      op.chain_init(init1, delta_s + 32);
+      Tile d0, d1;
+      auto times = [&](Tile& d, const bf16x8 (&ph)[2], int e) { Products::map(d, e, [&](float x) { return x * (float)ph[e >> 3][e & 7]; }); };
       // dP - delta of row block 0 (chain started from -delta); dO rows of row block 1 come in behind
 #pragma unroll
-      for (int t = 0; t < 8; ++t) {
-        d0 = mfma(x[t], frag[t], d0);
-        x[t] = lds_row8_at(t0 + r_off[t], 32);
+      for (int i = 0; i < 8; ++i) {
+        Products::chain(d0, i, x[i], frag, init0);
+        x[i] = op.row_op(t0, 32, i);
+        Products::step_end();
       }
       issue_copies();
       // dP - delta of row block 1, with dS of row block 0; Q^T of row block 0 comes in behind
 #pragma unroll
-      for (int t = 0; t < 8; ++t) {
-        d1 = mfma(x[t], frag[t], d1);
-        x[t] = lds_tr8_at(t0, t_off[t & 3], 16 * (t >> 2));
-        d0[2 * t] *= (float)ph0[t >> 2][(2 * t) & 7];
-        d0[2 * t + 1] *= (float)ph0[t >> 2][(2 * t + 1) & 7];
+      for (int i = 0; i < 8; ++i) {
+        Products::chain(d1, i, x[i], frag, init1);
+        x[i] = op.col_op(t0, 0, i);
+        times(d0, ph0, 2 * i);
+        times(d0, ph0, 2 * i + 1);
+        Products::step_end();
       }
-      const bf16x8 ds0[2] = {pack8(d0, 0), pack8(d0, 1)};
+      const bf16x8 ds0[2] = {Products::pack(d0, 0), Products::pack(d0, 1)};
       // dK of row block 0, with dS of row block 1; Q^T of row block 1 comes in behind
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
-        acc[i & 3] = mfma(ds0[i >> 2], x[i], acc[i & 3]);
-        x[i] = lds_tr8_at(t0, t_off[i & 3], 32 + 16 * (i >> 2));
-        d1[2 * i] *= (float)ph1[i >> 2][(2 * i) & 7];
-        d1[2 * i + 1] *= (float)ph1[i >> 2][(2 * i + 1) & 7];
+        Products::sum(acc, i, ds0, x[i]);
+        x[i] = op.col_op(t0, 32, i);
+        times(d1, ph1, 2 * i);
+        times(d1, ph1, 2 * i + 1);
+        Products::step_end();
       }
-      const bf16x8 ds1[2] = {pack8(d1, 0), pack8(d1, 1)};
+      const bf16x8 ds1[2] = {Products::pack(d1, 0), Products::pack(d1, 1)};
       // dK of row block 1; dO rows of row block 0 of the next stage come in behind (for the next iteration)
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
-        acc[i & 3] = mfma(ds1[i >> 2], x[i], acc[i & 3]);
-        x[i] = lds_row8_at(t1 + r_off[i], 0);
+        Products::sum(acc, i, ds1, x[i]);
+        x[i] = op.row_op(t1, 0, i);
+        Products::step_end();
       }
     }
     dma_wait_all();
@@ -561,18 +664,13 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
   // does not keep the ones computed before the loop alive across it: the loop uses every register.)
   int tid_e = threadIdx.x;
   asm volatile("" : "+v"(tid_e));
-  typedef float f32x4 __attribute__((ext_vector_type(4)));
-  const int lane_e = tid_e & 63, l32_e = tid_e & 31, g_e = (tid_e >> 5) & 1, wave_e = tid_e >> 6;
+  const int lane_e = tid_e & 63, l32_e = tid_e & 31, wave_e = tid_e >> 6;
   const int n0_e = c0 + (wave_e % NCB) * 32;
   constexpr int kTurnRow = 528;                                          // bytes; 16 of padding
   static_assert(2 * NCB * 32 * kTurnRow <= Cfg::kSmemBytes, "the turned tiles fit the ring's LDS");
   lds_char* own = smem + wave_e * (32 * kTurnRow);
   auto turn_in = [&]() {
-#pragma unroll
-    for (int r = 0; r < 16; ++r)
-#pragma unroll
-      for (int db = 0; db < 4; ++db)
-        *reinterpret_cast<SECO_LDS float*>(own + (8 * (r >> 2) + 4 * g_e + (r & 3)) * kTurnRow + (32 * db + l32_e) * 4) = acc[db][r];
+    Products::each(acc, lane_e, [&](int row, int col, float x) { *reinterpret_cast<SECO_LDS float*>(own + row * kTurnRow + col * 4) = x; });
   };
   auto turned = [&](int j) {                                             // row 2 j + lane / 32, columns 4 (lane % 32) ..
     return *reinterpret_cast<SECO_LDS f32x4*>(own + (2 * j + (lane_e >> 5)) * kTurnRow + l32_e * 16);

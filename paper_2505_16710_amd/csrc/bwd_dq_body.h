@@ -13,7 +13,7 @@
 // Bound: power on long calls, as the forward, and products of 16x16x32 for the same reason (half the accumulator traffic of
 // 32x32x16): 2048 rows at 30720 of 32/8 heads 1278 -> 1236 us (2.03 GHz and the matrix pipe 59 % busy, before 1.81 and 66 %),
 // 1024 at 15360 345 -> 320, two sequences of 777 at 9324 366 -> 351.  Operands are read kAhead pairs of products ahead, held
-// there by a scheduling barrier per pair (2, 3, 4: within 1 %).  Writing dS of one block of 32 cache rows under the products
+// there by a scheduling barrier per pair (2, 3, 4: within 1 % here, in the launch with dK/dV 2 is the fastest).  Writing dS of one block of 32 cache rows under the products
 // of the other (48 registers of scores for 32) spills 26 registers and more, which costs a third.
 //
 // Column-weighted dQ (SPARSE = true): the tiles are taken from a by-value table of runs of cache rows, each with
@@ -38,7 +38,7 @@ namespace {
 
 constexpr int BM = 128;
 constexpr int BNW = 64;   // cache rows per wavefront and tile
-constexpr int kAhead = 3; // operand reads in flight ahead of the products
+constexpr int kAhead = 2; // operand reads in flight ahead of the products
 
 // seg (SPARSE only): runs of cache rows in ascending order, each with a positive weight
 // smem: 4 * kTileBytes, [buf][K|V]

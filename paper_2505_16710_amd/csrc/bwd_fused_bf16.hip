@@ -46,9 +46,9 @@ __global__ __launch_bounds__(512, 2) void bwd_fused_bf16_kernel(AttnParams p, Se
     RowRuns none;
     none.n = 0;
     if (__builtin_amdgcn_readfirstlane((int)threadIdx.x / (64 * kNcb)) == 0)
-      dkdv_bf16_body<kNcb, SECO_DKDV_RB, false, 0, true>(p, seg, ts, none, item, smem);
+      dkdv_bf16_body<kNcb, SECO_DKDV_RB, false, 0, Products32, true>(p, seg, ts, none, item, smem);
     else
-      dkdv_bf16_body<kNcb, SECO_DKDV_RB, false, 1, true>(p, seg, ts, none, item, smem);
+      dkdv_bf16_body<kNcb, SECO_DKDV_RB, false, 1, Products32, true>(p, seg, ts, none, item, smem);
   } else {
     constexpr int kSplit = SPLIT ? kDivided : kWholeTiles;
     if constexpr (std::is_same_v<RUNS, SegTable>)
