@@ -4,7 +4,9 @@
 namespace seco {
 
 int launch_fwd_bf16(const AttnParams& p, hipStream_t s) {
-  if (p.G * p.C <= 32) return launch_fwd_small_bf16(p, p.part ? split_plan(p.B, p.Hkv, p.G, p.C).max_splits : 1, s);
+  // (p.part: partial results of a divided cache; with p.tail_bytes, of the row tiles beyond one round)
+  const int max_splits = p.part && p.tail_bytes == 0 ? split_plan(p.B, p.Hkv, p.G, p.C).max_splits : 1;
+  if (fwd_small_pays(p, max_splits)) return launch_fwd_small_bf16(p, max_splits, s);
   if (p.n_splits > 1) {
     const SplitPlan plan = split_plan(p.B, p.Hkv, p.G, p.C);
     int rc = launch_fwd8_split_bf16(p, plan.n_mtiles, plan.items * p.n_splits, s);

@@ -1,14 +1,18 @@
-// Forward of a chunk with at most 32 query rows per KV head (C rows times the G query heads that share it): a few tokens
-// at the end of a cache.
+// Forward of a chunk with few query rows per KV head (C rows times the G query heads that share it) against a cache that is
+// short for the workgroups there are: a few tokens at the end of a cache, short chunks at up to some thousand rows.
 //
 // What bounds it is reading the cache once, or, where that is short, the latency of one pass through memory: the row tiles
 // of the other kernels would be mostly padding (a wavefront per head, four heads per workgroup, all on the same tile of
-// the cache, one tile after the other).  Here all rows of a KV head are one 32-row tile that every wavefront holds, and
-// the wavefronts divide the cache: each takes blocks of 32 cache rows on its own, K and V copied into its own 16 KiB of
-// LDS, no barrier in the loop.  Eight wavefronts keep 128 KiB in flight per CU.  Their sums meet in LDS; a long cache is
-// divided among n_splits workgroups whose partial results fwd_merge_kernel combines.
+// the cache, one tile after the other).  Here the rows of a KV head, packed, are row tiles of 32, a workgroup holds one in
+// every wavefront, and the wavefronts divide the cache: each takes blocks of 32 cache rows on its own, K and V copied into
+// its own 16 KiB of LDS, no barrier in the loop.  Eight wavefronts keep 128 KiB in flight per CU.  Their sums meet in LDS; a
+// long cache is divided among n_splits workgroups whose partial results fwd_merge_kernel combines: a quarter of what the
+// 8-wavefront kernel's tiles of 128 packed rows write.
 // Kernel times with the merge: 2 rows x 8 heads against 1101 cache rows 14.9 -> 10.0 us, 1 row x 32 heads (8 KV heads)
 // against 600 / 8828 15.8 -> 8.9 / 16.7 -> 13.8 us; 8 rows x 32 heads against 32008 rows 30.7 -> 28.1 us (4.7 TB/s).
+// Several row tiles, against the 8-wavefront kernel: 32 rows x 32 heads (8 KV heads) against 1032 / 4032 rows
+// 12.8 -> 11.3 / 17.7 -> 13.9; 16 rows against 16368 20.9 -> 19.0; 64 against 2064 18.2 -> 14.7; 2 x 96 against 1096
+// 18.9 -> 13.0.
 #include <algorithm>
 
 #include "mfma_tiles.h"
@@ -23,7 +27,7 @@ constexpr int kOwn = 16 * kTurnStep;                     // a wavefront's LDS: K
 constexpr int kQTile = kWaves * kOwn, kMl = kQTile + 8192, kSmem = kMl + kWaves * 32 * 2 * 4;
 static_assert(kOwn >= 2 * kBlock * kRowBytes && kOwn % 256 == 0, "a K and a V block");
 
-__global__ __launch_bounds__(kWaves * 64, 2) void fwd_small_bf16_kernel(AttnParams p, int total_items) {
+__global__ __launch_bounds__(kWaves * 64, 2) void fwd_small_bf16_kernel(AttnParams p, int n_mtiles, int total_items) {
   typedef float f32x4 __attribute__((ext_vector_type(4)));
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];
   lds_char* smem = (lds_char*)smem_raw;
@@ -31,7 +35,9 @@ __global__ __launch_bounds__(kWaves * 64, 2) void fwd_small_bf16_kernel(AttnPara
   if (item < 0) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, g = lane >> 5;
-  const int unit = item / p.n_splits, sp = item - unit * p.n_splits, b = unit / p.Hkv, kvh = unit - b * p.Hkv;
+  // item -> (batch, kv head), share of the cache, row tile: the tiles that read the same rows run side by side on one XCD
+  const int shared = item / n_mtiles, r0 = (item - shared * n_mtiles) * 32;
+  const int unit = shared / p.n_splits, sp = shared - unit * p.n_splits, b = unit / p.Hkv, kvh = unit - b * p.Hkv;
   const int n_rows = p.G * p.C, kv_len = p.q_start + p.C;
   const __bf16* kbase = static_cast<const __bf16*>(p.k) + b * p.kvs[0] + kvh * p.kvs[1];
   const __bf16* vbase = static_cast<const __bf16*>(p.v) + b * p.kvs[0] + kvh * p.kvs[1];
@@ -59,7 +65,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void fwd_small_bf16_kernel(AttnPara
   };
   // packed row r: head r / C of the group, chunk row r % C; rows past the last repeat it and are not stored
   {
-    const int r = min(4 * wave + (lane >> 4), n_rows - 1), hg = r / p.C;
+    const int r = min(r0 + 4 * wave + (lane >> 4), n_rows - 1), hg = r / p.C;
     dma4rows(smem + kQTile, 4 * wave, static_cast<const __bf16*>(p.q) + b * p.qs[0] + (kvh * p.G + hg) * p.qs[1] +
                                           (int64_t)(r - hg * p.C) * p.qs[2], lane);
   }
@@ -68,7 +74,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void fwd_small_bf16_kernel(AttnPara
     copy_block(kbase, kt, blk);
     copy_block(vbase, vt, blk);
   }
-  const int my_row = min(l32, n_rows - 1), qpos = p.q_start + my_row % p.C;
+  const int my_row = min(r0 + l32, n_rows - 1), qpos = p.q_start + my_row % p.C;
   const float c = p.scale * kLog2e;
   f32x16 o[4];
 #pragma unroll
@@ -162,7 +168,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void fwd_small_bf16_kernel(AttnPara
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
     const int r = (tid >> 5) + 16 * k;
-    if (r >= n_rows) break;
+    if (r0 + r >= n_rows) break;
     float rm = -INFINITY, rl = 0.f;
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) rm = fmaxf(rm, ml[2 * (w * 32 + r)]);
@@ -175,7 +181,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void fwd_small_bf16_kernel(AttnPara
 #pragma unroll
     for (int w = 0; w < kWaves; ++w)
       sum += *reinterpret_cast<SECO_LDS f32x4*>(smem + w * kOwn + (q >> 1) * kTurnStep + ((q & 1) * 32 + r) * 16);
-    const int hg = r / p.C, row = r - hg * p.C, h = kvh * p.G + hg;
+    const int hg = (r0 + r) / p.C, row = r0 + r - hg * p.C, h = kvh * p.G + hg;
     const int64_t rowid = ((int64_t)b * p.Hq + h) * p.C + row;
     if (p.n_splits > 1) {
       const int64_t part_row = (int64_t)sp * p.B * p.Hq * p.C + rowid;
@@ -195,20 +201,44 @@ __global__ __launch_bounds__(kWaves * 64, 2) void fwd_small_bf16_kernel(AttnPara
 
 }  // namespace
 
-int launch_fwd_small_bf16(AttnParams p, int max_splits, hipStream_t s) {
-  // A workgroup takes about 1.3 us per round of 8 blocks; dividing the cache costs a merge of about 4 us.  At most one
-  // workgroup per CU.
-  const int units = p.B * p.Hkv, rounds = ((p.q_start + p.C + kBlock - 1) / kBlock + kWaves - 1) / kWaves;
+namespace {
+// A round (eight blocks, one per wavefront) takes about 1.8 us and dividing the cache costs a merge of 4.3 (2, 4 and 5 rounds
+// of one row tile 8.4, 12.1 and 14.0 us; a round each and a merge 10.6).  At most one workgroup per CU.
+struct SmallPlan { int n_mtiles, n_splits, rounds; };      // rounds: of a workgroup
+SmallPlan small_plan(const AttnParams& p, int max_splits) {
+  SmallPlan sp;
+  sp.n_mtiles = (p.G * p.C + 31) / 32;
+  const int units = p.B * p.Hkv * sp.n_mtiles, all = ((p.q_start + p.C + kBlock - 1) / kBlock + kWaves - 1) / kWaves;
   int n = std::min(std::max(device_cus() / units, 1), max_splits);
-  const int each = (rounds + n - 1) / n;
-  n = (rounds + each - 1) / each;
-  p.n_splits = 13 * (rounds - each) > 40 ? n : 1;
-  const int total = units * p.n_splits;
+  const int each = (all + n - 1) / n;
+  n = (all + each - 1) / each;
+  sp.n_splits = 18 * (all - each) > 43 ? n : 1;
+  sp.rounds = sp.n_splits > 1 ? each : all;
+  return sp;
+}
+}  // namespace
+
+// The rounds tell the two kernels apart where the rows are more than one tile: here a workgroup's wavefronts share nothing
+// and a round is 256 cache rows for 32 query rows; the 8-wavefront kernel does 128 x 128 in the same time but starts, ends
+// and merges slower.  204 shapes of 48 - 800 packed rows at 300 - 30000, times there over times here: 1 - 6 rounds 1.01 - 1.55
+// (but for 0.98 and 0.99), 7 rounds 0.98 - 1.11, 8 0.89 - 1.03, 12 and more 0.71 - 1.03; with at most 64 rows, where both read the
+// cache at the memory's rate, 0.99 - 1.03 at 8.
+bool fwd_small_pays(const AttnParams& p, int max_splits) {
+  const int rows = p.G * p.C;
+  if (rows <= 32) return true;
+  if ((int64_t)p.B * p.Hkv * ((rows + 31) / 32) > device_cus()) return false;
+  return small_plan(p, max_splits).rounds <= (rows <= 64 ? 8 : 6);
+}
+
+int launch_fwd_small_bf16(AttnParams p, int max_splits, hipStream_t s) {
+  const SmallPlan sp = small_plan(p, max_splits);
+  const int n_mtiles = sp.n_mtiles, total = p.B * p.Hkv * n_mtiles * sp.n_splits;
+  p.n_splits = sp.n_splits;
   static std::atomic<uint64_t> ready{0};
   if (!allow_lds(ready, reinterpret_cast<const void*>(fwd_small_bf16_kernel), kSmem)) return SECO_ERR_LAUNCH;
   {
     ProfScope prof(kKernelFwd, s);
-    hipLaunchKernelGGL(fwd_small_bf16_kernel, dim3(xcd_grid(total)), dim3(kWaves * 64), kSmem, s, p, total);
+    hipLaunchKernelGGL(fwd_small_bf16_kernel, dim3(xcd_grid(total)), dim3(kWaves * 64), kSmem, s, p, n_mtiles, total);
   }
   const int rc = launch_status();
   return rc || p.n_splits == 1 ? rc : launch_fwd_merge(p, s);

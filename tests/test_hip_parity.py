@@ -879,6 +879,46 @@ def test_bf16_forward_of_a_few_rows(B, Hq, Hkv, C, q_start):
         assert max_rel(to_host(o), ref_o) <= TOL["bf16"]["o"] and max_rel(to_host(lse), ref_lse) <= TOL["bf16"]["lse"]
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,C,q_start", [
+    (1, 3, 1, 11, 0),        # 33 packed rows: a second tile of one row; everything on the diagonal
+    (2, 8, 2, 17, 700),      # 68: tiles that cut through heads, the last of four rows
+    (1, 8, 8, 64, 1023),     # two whole tiles per head, the diagonal across blocks
+    (1, 32, 8, 24, 3001),    # divided cache, the last share short
+    (1, 16, 2, 100, 1500),   # 25 tiles, several rounds
+])
+def test_bf16_forward_of_several_row_tiles_against_short_caches(B, Hq, Hkv, C, q_start):
+    test_bf16_forward_of_a_few_rows(B, Hq, Hkv, C, q_start)
+
+
+@pytest.mark.parametrize("Hq,Hkv,C,N,ws", [
+    (2, 1, 128, 2432, False),        # 8 wavefronts, whole row tiles
+    (16, 2, 128, 12288, None),       # ... the cache divided
+    (32, 8, 2048, 2560, None),       # 4 wavefronts
+])
+def test_forward_reference_moves_in_the_kernels_of_longer_calls(Hq, Hkv, C, N, ws):
+    """Scores that rise along the cache by 65 and by 147 in log2 units from one 64-column tile to a later one, and fall for every
+    second head: the reference is set, kept and moved within a tile's two halves of 32 columns and between tiles.  Against
+    fp32 on the device (bf16 products of P and V: the bars of this file)."""
+    s, g = 1 / np.sqrt(128), torch.Generator(device=DEV).manual_seed(81)
+    k = torch.zeros(1, Hkv, N, 128, device=DEV)
+    k[:, :, 100:128] = 2.0
+    k[:, :, 128:200] = 2.0
+    k[:, :, 150:200, :64] = 7.0
+    k[:, :, N // 2:] = 8.0
+    k += 0.01 * torch.randn(k.shape, device=DEV, generator=g)
+    q = torch.full((1, Hq, C, 128), 2.0, device=DEV)
+    q[:, 1::2] = -2.0
+    v = torch.randn(1, Hkv, N, 128, device=DEV, generator=g)
+    q, k, v = (t.to(torch.bfloat16) for t in (q, k, v))
+    o, lse = seco.seco_chunk_attn_fwd(q, k, v, N - C, s, ws=ws)
+    hidden = torch.arange(N, device=DEV)[None, :] > torch.arange(C, device=DEV)[:, None] + N - C
+    for h in range(Hq):
+        z = (q[0, h].float() @ k[0, h * Hkv // Hq].float().t() * s).masked_fill(hidden, float("-inf"))
+        assert torch.isfinite(o[0, h]).all() and torch.isfinite(lse[0, h]).all(), h
+        assert max_rel(to_host(o[0, h]), to_host(z.softmax(-1) @ v[0, h * Hkv // Hq].float())) <= TOL["bf16"]["o"], h
+        assert max_rel(to_host(lse[0, h]), to_host(z.logsumexp(-1))) <= TOL["bf16"]["lse"], h
+
+
 @pytest.mark.parametrize("order", ["accumulating", "transposed"])
 def test_step_captured_in_a_hip_graph_replays_identically(order):
     """The library allocates nothing, never synchronises and clears gK/gV with a kernel, so a whole SeCO step can be
