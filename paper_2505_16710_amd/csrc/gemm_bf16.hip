@@ -15,6 +15,7 @@
 // are XOR-ed with a function of the row such that row reads (ds_read_b128, 16 rows) and transpose reads
 // (ds_read_b64_tr_b16, 4 rows x 64 bytes) meet no bank conflict.  Both kinds of read deliver contraction slot s of
 // lane group g as element 8 g + s, so that any two operands can meet.  The tile leaves through LDS in rows of 16-byte stores.
+#include <algorithm>
 #include <type_traits>
 
 #include "decoder.h"
@@ -32,7 +33,8 @@ struct GemmArgs {
   const char* b;
   __bf16* c;
   __bf16* c2;       // kSilu: silu(C); kSiluBwd: the u that C is the gradient of silu at
-  int M, N, K, lda, ldb, ldc, tiles_m;
+  int M, N, K, lda, ldb, ldc, tiles_m, tiles_n;
+  int split_m, part_m, part_n;       // an XCD's part of the tiles (place_tiles); split_m 0: runs of them
 };
 
 __device__ __forceinline__ int flip(int row) { return (((row >> 1) & 1) << 2) | ((row >> 2) & 3); }
@@ -358,23 +360,47 @@ template <int NW, bool AKC, bool BKC, int EPI> struct ByK {
   static constexpr int kThreads = 64 * NW, kSmem = NW * 96 * kRow, kBM = 32, kBN = 64;
   static __device__ __forceinline__ void run(const GemmArgs& g, int item, lds_char* smem) { k_tile<NW, AKC, BKC, EPI>(g, item, smem); }
 };
-template <typename T> int items_of(GemmArgs& g) {
+// Which tiles the XCDs take (workgroups whose ids are equal mod 8 share an L2).  Runs of the tiles, column by column: an XCD
+// reads all rows of A and an eighth of B's columns.  Or split_m x 8 / split_m parts of part_m x part_n tiles, one for each XCD,
+// where that reads less than two thirds of it and leaves no XCD more tiles than an even share; with less to win the runs are as
+// fast or faster (512 x 1024 x 4096, 512 rows and columns for 640: 11.5 against 12.2 us).  Returns the grid.
+// us, runs -> parts: added to 4096 x 1024 over 2048 rows 24.2 -> 21.2, over 512 9.9 -> 8.6; 2048 x 1024 x 4096 25.6 -> 24.4;
+// 2048 x 1024 x 1536, rows of both contracted, 13.4 -> 12.4.
+template <typename T> int place_tiles(GemmArgs& g) {
   g.tiles_m = (g.M + T::kBM - 1) / T::kBM;
-  return g.tiles_m * ((g.N + T::kBN - 1) / T::kBN);
+  g.tiles_n = (g.N + T::kBN - 1) / T::kBN;
+  const int64_t total = (int64_t)g.tiles_m * g.tiles_n, even = (total + 7) / 8;
+  int64_t least = (2 * (std::min<int64_t>(g.tiles_m, even) * T::kBM + (even + g.tiles_m - 1) / g.tiles_m * T::kBN) + 2) / 3;
+  g.split_m = 0;
+  for (int sm = 2; sm <= 8; sm *= 2) {
+    const int64_t pm = (g.tiles_m + sm - 1) / sm, pn = (g.tiles_n + 8 / sm - 1) / (8 / sm), reads = pm * T::kBM + pn * T::kBN;
+    if (pm * pn > even || reads >= least) continue;
+    least = reads;
+    g.split_m = sm;
+    g.part_m = (int)pm;
+    g.part_n = (int)pn;
+  }
+  return g.split_m ? 8 * g.part_m * g.part_n : xcd_grid((int)total);
+}
+__device__ __forceinline__ int tile_of(const GemmArgs& g, int block) {
+  if (g.split_m == 0) return xcd_item(block, g.tiles_m * g.tiles_n);
+  const int xcd = block & 7, i = block >> 3, in = i / g.part_m;
+  const int tm = (xcd & (g.split_m - 1)) * g.part_m + (i - in * g.part_m), tn = xcd / g.split_m * g.part_n + in;
+  return tm < g.tiles_m && tn < g.tiles_n ? tn * g.tiles_m + tm : -1;
 }
 
 template <typename T>
-__global__ __launch_bounds__(T::kThreads, 2) void gemm_kernel(GemmArgs g, int total) {
+__global__ __launch_bounds__(T::kThreads, 2) void gemm_kernel(GemmArgs g) {
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];
-  const int item = xcd_item(blockIdx.x, total);          // neighbours share the columns of B (a weight matrix in two of the forms)
+  const int item = tile_of(g, blockIdx.x);
   if (item >= 0) T::run(g, item, (lds_char*)smem_raw);
 }
 template <typename T> int launch(GemmArgs g, hipStream_t s) {
   auto kern = gemm_kernel<T>;
   static std::atomic<uint64_t> ready{0};
   if (!allow_lds(ready, reinterpret_cast<const void*>(kern), T::kSmem)) return SECO_ERR_LAUNCH;
-  const int total = items_of<T>(g);
-  hipLaunchKernelGGL(kern, dim3(xcd_grid(total)), dim3(T::kThreads), T::kSmem, s, g, total);
+  const int grid = place_tiles<T>(g);
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(T::kThreads), T::kSmem, s, g);
   return launch_status();
 }
 // Which tile: measured over 64 .. 2048 rows against matrices of 1024 x 1024 .. 4096 x 1024 (us; K: contraction length).
@@ -419,15 +445,15 @@ template <bool AKC, bool BKC, int EPI> int pick(const GemmArgs& g, hipStream_t s
 // weight_first: which workgroups go in front.  Those of the weight gradient take rows / 64 steps, the others' time does not
 // depend on the rows: the longer ones first (512 rows, 4096 x 1024: 17.6 against 18.8; 320: 15.1 against 14.0).
 template <typename A, typename B>
-__global__ __launch_bounds__(512, 2) void gemm_pair_kernel(GemmArgs a, GemmArgs b, int total_a, int total_b, int first_grid, int weight_first) {
+__global__ __launch_bounds__(512, 2) void gemm_pair_kernel(GemmArgs a, GemmArgs b, int first_grid, int weight_first) {
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];
   const bool first = (int)blockIdx.x < first_grid, weight = first == (weight_first != 0);
-  const int item = xcd_item(first ? blockIdx.x : blockIdx.x - first_grid, weight ? total_b : total_a);
-  if (item < 0) return;
-  if (weight)
-    B::run(b, item, (lds_char*)smem_raw);
-  else
-    A::run(a, item, (lds_char*)smem_raw);
+  const int block = first ? blockIdx.x : blockIdx.x - first_grid;
+  if (weight) {
+    if (const int item = tile_of(b, block); item >= 0) B::run(b, item, (lds_char*)smem_raw);
+  } else {
+    if (const int item = tile_of(a, block); item >= 0) A::run(a, item, (lds_char*)smem_raw);
+  }
 }
 template <typename A, typename B> int launch_pair(GemmArgs a, GemmArgs b, hipStream_t s) {
   static_assert(A::kThreads == 512 && B::kThreads == 512, "workgroups of one size");
@@ -435,9 +461,8 @@ template <typename A, typename B> int launch_pair(GemmArgs a, GemmArgs b, hipStr
   auto kern = gemm_pair_kernel<A, B>;
   static std::atomic<uint64_t> ready{0};
   if (!allow_lds(ready, reinterpret_cast<const void*>(kern), smem)) return SECO_ERR_LAUNCH;
-  const int ta = items_of<A>(a), tb = items_of<B>(b), weight_first = b.K >= 448;
-  const int ga = xcd_grid(ta), gb = xcd_grid(tb);
-  hipLaunchKernelGGL(kern, dim3(ga + gb), dim3(512), smem, s, a, b, ta, tb, weight_first ? gb : ga, weight_first);
+  const int ga = place_tiles<A>(a), gb = place_tiles<B>(b), weight_first = b.K >= 448;
+  hipLaunchKernelGGL(kern, dim3(ga + gb), dim3(512), smem, s, a, b, weight_first ? gb : ga, weight_first);
   return launch_status();
 }
 constexpr int kApart = 1;           // (no seco_status)
@@ -485,7 +510,7 @@ extern "C" int dec_gemm(int form, int epilogue, const void* a, const void* b, vo
   if (!a || !b || !c || ((epilogue == DEC_GEMM_SILU || epilogue == DEC_GEMM_SILU_BWD) && !c2)) return SECO_ERR_NULL;
   if (((uintptr_t)a | (uintptr_t)b | (uintptr_t)c | (uintptr_t)c2) & 15u) return SECO_ERR_ALIGN;
   const GemmArgs g{static_cast<const char*>(a), static_cast<const char*>(b), static_cast<__bf16*>(c), static_cast<__bf16*>(c2),
-                   (int)M, (int)N, (int)K, (int)lda, (int)ldb, (int)ldc, 0};
+                   (int)M, (int)N, (int)K, (int)lda, (int)ldb, (int)ldc, 0, 0, 0, 0, 0};
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (form == DEC_GEMM_NN && epilogue == DEC_GEMM_STORE) return pick<true, false, kStore>(g, s);
   if (form == DEC_GEMM_NN && epilogue == DEC_GEMM_SILU) return pick<true, false, kSilu>(g, s);
@@ -503,9 +528,9 @@ extern "C" int dec_gemm_grads(const void* dy, const void* w, void* dx, void* u, 
   if (!dy || !w || !dx || !x || !dw) return SECO_ERR_NULL;
   if (((uintptr_t)dy | (uintptr_t)w | (uintptr_t)dx | (uintptr_t)u | (uintptr_t)x | (uintptr_t)dw) & 15u) return SECO_ERR_ALIGN;
   const GemmArgs a{static_cast<const char*>(dy), static_cast<const char*>(w), static_cast<__bf16*>(dx), static_cast<__bf16*>(u),
-                   (int)M, (int)K, (int)n, (int)n, (int)n, (int)K, 0};
+                   (int)M, (int)K, (int)n, (int)n, (int)n, (int)K, 0, 0, 0, 0, 0};
   const GemmArgs b{static_cast<const char*>(x), static_cast<const char*>(dy), static_cast<__bf16*>(dw), nullptr,
-                   (int)K, (int)n, (int)M, (int)K, (int)n, (int)n, 0};
+                   (int)K, (int)n, (int)M, (int)K, (int)n, (int)n, 0, 0, 0, 0, 0};
   hipStream_t s = static_cast<hipStream_t>(stream);
   int rc = u ? pair<kSiluBwd>(a, b, s) : pair<kStore>(a, b, s);
   if (rc != kApart) return rc;

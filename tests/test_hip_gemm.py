@@ -63,6 +63,15 @@ def test_gemm_forms_and_epilogues(form, epi, M, N, K):
     assert torch.equal(c[M], c_in[M]) and torch.equal(c2[M], c2_in[M])
 
 
+@pytest.mark.parametrize("form,epi,M,N,K", [
+    (TN, ADD, 4096, 1024, 72), (TN, STORE, 4088, 1032, 64),   # 128 x 128 tiles in four by two parts; in eight by one, the last tiles short
+    (NN, STORE, 2048, 1032, 2112), (NT, STORE, 2040, 1024, 192),   # 128 x 64 and 64 x 64 tiles
+    (NN, SILU, 8, 8192, 64),                                   # one row of tiles: runs
+])
+def test_gemm_tiles_in_one_part_for_each_xcd(form, epi, M, N, K):
+    test_gemm_forms_and_epilogues(form, epi, M, N, K)
+
+
 @pytest.mark.parametrize("M,K,n,silu", [
     (512, 1024, 4096, False), (512, 4096, 1024, True), (448, 1024, 1536, False), (447, 1024, 1024, False), (1, 64, 64, False),
     (33, 72, 128, True), (200, 1000, 1536, False), (250, 4104, 1088, True), (320, 4096, 1024, True), (500, 4000, 512, True),
