@@ -165,6 +165,14 @@ def test_rmsnorm_backward(dtype, d, rows, d_in):
         assert torch.equal(dev["part"].cpu()[rows:], part[rows:])
 
 
+@pytest.mark.parametrize("dtype,d", [(F32, 64), (F32, 260), (F32, 512), (F32, 516), (F32, 1024), (F32, 131), (F32, 1028),
+                                     (BF16, 512), (BF16, 520), (BF16, 1024), (BF16, 1032), (BF16, 2048), (BF16, 255), (BF16, 2056)])
+@pytest.mark.parametrize("rows,d_in", [(257, "in place"), (513, "apart"), (1030, "in place")])
+def test_rmsnorm_backward_with_a_wavefront_per_row(dtype, d, rows, d_in):
+    """Both sides of its lengths (64, 128 and 256 words) and of its rows; a last round in which wavefronts have none."""
+    test_rmsnorm_backward(dtype, d, rows, d_in)
+
+
 @pytest.mark.parametrize("dtype", [F32, BF16])
 @pytest.mark.parametrize("v", [1, 29, 2048, 4104, 10000])
 def test_cross_entropy_targets(dtype, v):
