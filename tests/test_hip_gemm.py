@@ -98,6 +98,33 @@ def test_both_gradients_in_one_launch(M, K, n, silu):
     assert torch.equal(dx, dx2) and torch.equal(dw, dw2)
 
 
+def test_silu_and_its_derivative_at_every_u():
+    """Both at all values of u, those whose e^-u leaves fp32 among their neighbours: u out of a product with the identity, one as
+    the gradient behind the SiLU.  Error: half an ulp of bf16, 2^-8 of the value at most, and that of e^-u, whose argument is
+    rounded to 2^-24 of up to 128: less than 2^-14.  Near u = -1.28 the derivative is a difference of numbers around one (2^-22);
+    where e^-u > 2^128 ends fp32 the result is zero instead of |u| 2^-128 at most, |u| < 90 while that counts: 2^-121."""
+    lib = seco.load_library()
+    P, I = C.c_void_p, C.c_int64
+    lib.dec_gemm.argtypes = [C.c_int, C.c_int, P, P, P, P] + [I] * 6 + [P]
+    u = torch.arange(65536, device=DEV, dtype=torch.int32).to(torch.int16).view(torch.bfloat16)
+    finite = torch.where(torch.isfinite(u), u, torch.zeros_like(u)).view(64, 1024)
+    eye, ones = torch.eye(64, device=DEV, dtype=torch.bfloat16), torch.ones(1024, 64, device=DEV, dtype=torch.bfloat16)
+    c, act, grad = (torch.empty(64, 1024, device=DEV, dtype=torch.bfloat16) for _ in range(3))
+    s = torch.cuda.current_stream().cuda_stream
+
+    def close(x, ref, ud):
+        bound = ref.abs() * (2.0 ** -8 + 2.0 ** -14) + torch.where(ud.abs() < 2, 2.0 ** -22, 2.0 ** -121)
+        return bool(((x.double() - ref).abs() <= bound).all())
+    assert lib.dec_gemm(NN, SILU, eye.data_ptr(), finite.data_ptr(), c.data_ptr(), act.data_ptr(), 64, 1024, 64, 64, 1024, 1024, s) == 0
+    ud = finite.double()
+    sig = torch.sigmoid(ud)
+    assert torch.equal(c, finite) and close(act, ud * sig, ud)
+    u = u.view(64, 1024).contiguous()
+    assert lib.dec_gemm(NT, SILU_BWD, eye.data_ptr(), ones.data_ptr(), grad.data_ptr(), u.data_ptr(), 64, 1024, 64, 64, 64, 1024, s) == 0
+    fin = torch.isfinite(u)
+    assert close(grad[fin], (sig * (1 + ud * (1 - sig)))[fin], ud[fin]) and bool(torch.isnan(grad[torch.isnan(u)]).all())
+
+
 def test_gemm_refuses_what_it_cannot_do():
     lib = seco.load_library()
     I = C.c_int64
