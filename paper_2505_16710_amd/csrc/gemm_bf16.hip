@@ -79,18 +79,18 @@ __device__ __forceinline__ void stage_rest(lds_char* dst, const char* base, int 
 template <bool KC> struct Frag {
   int lo, hi;
   int chunk_t[KC ? 4 : 1];
-  __device__ void init(int blk, int lane) {
+  __device__ void init(int blk, int lane, int t0 = 0) {   // t0: which of a step's 16 elements t = 0 stands for
     if (KC) {
       const int row = lane & 31;
       lo = blk * 32 * kRow + row * kRow;
 #pragma unroll
-      for (int t = 0; t < (KC ? 4 : 1); ++t) chunk_t[t] = lo + (((2 * t + (lane >> 5)) ^ flip(row)) << 4);
+      for (int t = 0; t < (KC ? 4 : 1); ++t) chunk_t[t] = lo + (((2 * (t0 + t) + (lane >> 5)) ^ flip(row)) << 4);
       hi = 0;
     } else {
-      const int ii = lane & 15, row = 8 * (lane >> 5) + (ii >> 2);
+      const int ii = lane & 15, row = 8 * (lane >> 5) + (ii >> 2), first = 16 * t0 * kRow;
       const int chunk = 4 * (blk & 1) + 2 * ((lane >> 4) & 1) + ((ii & 3) >> 1), sub = (ii & 1) << 3;
-      lo = (blk >> 1) * 64 * kRow + row * kRow + ((chunk ^ flip(row)) << 4) + sub;
-      hi = (blk >> 1) * 64 * kRow + (row + 4) * kRow + ((chunk ^ flip(row + 4)) << 4) + sub;
+      lo = first + (blk >> 1) * 64 * kRow + row * kRow + ((chunk ^ flip(row)) << 4) + sub;
+      hi = first + (blk >> 1) * 64 * kRow + (row + 4) * kRow + ((chunk ^ flip(row + 4)) << 4) + sub;
       chunk_t[0] = 0;
     }
   }
@@ -156,14 +156,16 @@ __device__ __forceinline__ void emit(const GemmArgs& g, int64_t at, const F4& lo
   }
 }
 
-// KH groups of 2 x WN wavefronts, each with a ring of kStages slots; group kh takes the steps kh, kh + KH, ...
-template <int BM, int BN, int KH, int kStages, int WN, bool AKC, bool BKC, int EPI>
+// KH groups of 2 x WN x KW wavefronts, each with a ring of kStages slots; group kh takes the steps kh, kh + KH, ..., and of each
+// step the wavefronts of equal kw a KW-th.
+template <int BM, int BN, int KH, int kStages, int WN, bool AKC, bool BKC, int EPI, int KW>
 __device__ __forceinline__ void ring_tile(const GemmArgs& g, int item, lds_char* smem_all) {
-  constexpr int kSlot = (BM + BN) * kRow, GW = 2 * WN, MB = BM / 64, NB = BN / (32 * WN);
+  constexpr int kSlot = (BM + BN) * kRow, GW = 2 * WN * KW, MB = BM / 64, NB = BN / (32 * WN);
   constexpr int kPerWave = BM / (8 * GW) + BN / (8 * GW);            // copies per wavefront and step
-  constexpr int kRing = kStages * kSlot;
+  constexpr int kRing = kStages * kSlot, kImage = kRing / KW;   // kImage: for a wavefront's part of the sums
   const int tid = threadIdx.x, lane = tid & 63, wave_all = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wave = wave_all % GW, kh = KH == 1 ? 0 : wave_all / GW;
+  const int kw = KW == 1 ? 0 : wave / (2 * WN), wt = KW == 1 ? wave : wave % (2 * WN);
   lds_char* smem = smem_all + kh * kRing;
   const int tn = item / g.tiles_m, tm = item - tn * g.tiles_m;
   const int m0 = tm * BM, n0 = tn * BN;
@@ -190,9 +192,9 @@ __device__ __forceinline__ void ring_tile(const GemmArgs& g, int item, lds_char*
   Frag<AKC> fa[MB];
   Frag<BKC> fb[NB];
 #pragma unroll
-  for (int i = 0; i < MB; ++i) fa[i].init(wave / WN * MB + i, lane);
+  for (int i = 0; i < MB; ++i) fa[i].init(wt / WN * MB + i, lane, kw * (4 / KW));
 #pragma unroll
-  for (int i = 0; i < NB; ++i) fb[i].init(wave % WN * NB + i, lane);
+  for (int i = 0; i < NB; ++i) fb[i].init(wt % WN * NB + i, lane, kw * (4 / KW));
   f32x16 acc[MB][NB];
 #pragma unroll
   for (int i = 0; i < MB; ++i)
@@ -205,7 +207,7 @@ __device__ __forceinline__ void ring_tile(const GemmArgs& g, int item, lds_char*
     lds_char* ta = smem + slot * kSlot;
     lds_char* tb = ta + BM * kRow;
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
+    for (int t = 0; t < 4 / KW; ++t) {
       bf16x8 x[MB], y[NB];
 #pragma unroll
       for (int i = 0; i < MB; ++i) x[i] = fa[i].read(ta, t);
@@ -263,16 +265,16 @@ __device__ __forceinline__ void ring_tile(const GemmArgs& g, int item, lds_char*
 
   __syncthreads();
   typedef float f32x4 __attribute__((ext_vector_type(4)));
-  constexpr int kTurnRow = BM * (BN + 4) * 4 <= kRing ? (BN + 4) * 4 : BN * 4;   // padded where there is room
-  static_assert(BM * kTurnRow <= kRing, "the tile fits the ring");
+  constexpr int kTurnRow = BM * (BN + 4) * 4 <= kImage ? (BN + 4) * 4 : BN * 4;   // padded where there is room
+  static_assert(BM * kTurnRow <= kImage && kImage % 16 == 0, "the tile fits");
 #pragma unroll
   for (int i = 0; i < MB; ++i)
 #pragma unroll
     for (int j = 0; j < NB; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r)
-        *reinterpret_cast<SECO_LDS float*>(smem + ((wave / WN * MB + i) * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * kTurnRow +
-                                           ((wave % WN * NB + j) * 32 + (lane & 31)) * 4) = acc[i][j][r];
+        *reinterpret_cast<SECO_LDS float*>(smem + kw * kImage + ((wt / WN * MB + i) * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * kTurnRow +
+                                           ((wt % WN * NB + j) * 32 + (lane & 31)) * 4) = acc[i][j][r];
   __syncthreads();
   if (col >= g.N) return;
 #pragma unroll
@@ -281,9 +283,10 @@ __device__ __forceinline__ void ring_tile(const GemmArgs& g, int item, lds_char*
     if (row >= g.M) break;
     lds_char* src = smem_all + lr * kTurnRow + (tid % kPerRow) * 32;
     f32x4 lo = *reinterpret_cast<SECO_LDS f32x4*>(src), hi = *reinterpret_cast<SECO_LDS f32x4*>(src + 16);
-    if constexpr (KH == 2) {
-      lo += *reinterpret_cast<SECO_LDS f32x4*>(src + kRing);
-      hi += *reinterpret_cast<SECO_LDS f32x4*>(src + kRing + 16);
+#pragma unroll
+    for (int v = 1; v < KH * KW; ++v) {
+      lo += *reinterpret_cast<SECO_LDS f32x4*>(src + v * kImage);
+      hi += *reinterpret_cast<SECO_LDS f32x4*>(src + v * kImage + 16);
     }
     const int64_t at = (int64_t)row * g.ldc + col;
     emit<EPI>(g, at, lo, hi, kMeets ? old[i] : met<EPI>(g, at));
@@ -368,10 +371,10 @@ __device__ __forceinline__ void k_tile(const GemmArgs& g, int item, lds_char* sm
 }
 
 // A way to work a product: workgroups of kThreads with kSmem bytes of LDS, one per item
-template <int BM, int BN, int KH, int ST, int WN, bool AKC, bool BKC, int EPI> struct Ring {
-  static constexpr int kThreads = 128 * WN * KH, kSmem = KH * ST * (BM + BN) * kRow, kBM = BM, kBN = BN;
+template <int BM, int BN, int KH, int ST, int WN, bool AKC, bool BKC, int EPI, int KW = 1> struct Ring {
+  static constexpr int kThreads = 128 * WN * KW * KH, kSmem = KH * ST * (BM + BN) * kRow, kBM = BM, kBN = BN;
   static __device__ __forceinline__ void run(const GemmArgs& g, int item, lds_char* smem) {
-    ring_tile<BM, BN, KH, ST, WN, AKC, BKC, EPI>(g, item, smem);
+    ring_tile<BM, BN, KH, ST, WN, AKC, BKC, EPI, KW>(g, item, smem);
   }
 };
 template <int NW, bool AKC, bool BKC, int EPI> struct ByK {
@@ -433,7 +436,10 @@ template <typename T> int launch(GemmArgs g, hipStream_t s) {
 //    9.5; in two groups with two slots, which turn and add twice the sums through LDS, 10.5, and 11.4 while what the sums
 //    are added to was only requested when they were there);
 //  - 64 x 64 tiles that fit one round: those, two groups, three slots (512 x 1024 x 4096: 14.6; 18.5 with one group);
-//  - more of them: 128 x 64 for a long contraction of rows of A (2048 x 1024 x 4096: 25 against 27 with 64 x 128); else, where
+//  - more of them: 128 x 64 for a long contraction of rows of A (2048 x 1024 x 4096: 25 against 27 with 64 x 128), forward with the
+//    steps halved between wavefronts that hold 64 x 64 of the tile, two thirds of the LDS reads and two more images to add (as
+//    64 x 32 of whole steps -> so: 2048 x 1024 x 4096 26.9 -> 24.1, 1500 rows 23.0 -> 21.8; the data gradient 24.2 / 24.6; 128 x 128 tiles
+//    so halved 12.8 -> 12.3 at 2048 x 1536 x 1024, 5.0 -> 5.6 at 1536 x 1536 x 192); else, where
 //    the rows of B are contracted, 64 x 128, eight wavefronts side by side, three slots: a third less from L2 than 64 x 64 with two
 //    slots and two workgroups per CU (1024 x 1536 over 512 rows: 5.7 against 6.3, 512 x 4096 x 1024 with the SiLU: 9.9 / 10.4;
 //    2048 x 1024 over 2048: 13.7 / 14.9 with 128 x 64); else those (512 x 4096 x 1024 back through the SiLU: 9.5; 10.2 with 64 x 128).
@@ -446,7 +452,7 @@ template <bool AKC, bool BKC, int EPI, typename F> int with_way(const GemmArgs& 
   if (20 * big >= 11 * cus) return f(Way<Ring<128, 128, 1, 3, 4, AKC, BKC, EPI>>());
   if (m64 * n64 <= cus) return f(Way<Ring<64, 64, 2, 3, 2, AKC, BKC, EPI>>());
   if constexpr (AKC)
-    if (g.K >= 2048) return f(Way<Ring<128, 64, 2, 3, 2, AKC, BKC, EPI>>());
+    if (g.K >= 2048) return f(Way<Ring<128, 64, 2, 3, BKC ? 2 : 1, AKC, BKC, EPI, BKC ? 1 : 2>>());
   if constexpr (!BKC)
     return f(Way<Ring<64, 128, 1, 3, 4, AKC, BKC, EPI>>());
   else

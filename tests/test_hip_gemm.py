@@ -23,6 +23,7 @@ STORE, ADD, SILU, SILU_BWD = 0, 1, 2, 3
     (NN, STORE, 640, 1024, 320), (NT, SILU_BWD, 700, 1000, 512),   # 64 x 64 tiles that fit one round, 32 x 64 do not
     (NN, STORE, 300, 4096, 64),            # more 64 x 64 tiles than CUs, two slots
     (NT, STORE, 1500, 1032, 2112),         # 128 x 64 tiles
+    (NN, STORE, 1500, 1032, 2112), (NN, SILU, 2048, 1024, 2048),   # ... the steps halved between wavefronts, an odd number of them
     (TN, ADD, 2040, 2056, 200),            # 128 x 128 tiles, two groups, a remainder of the contraction
     (NN, SILU, 2050, 4104, 128),           # 128 x 128 tiles, one group, two workgroups per CU
     (NN, SILU, 500, 4000, 192), (TN, ADD, 1000, 1544, 200), (TN, STORE, 1000, 1544, 128),   # 64 x 128 tiles
