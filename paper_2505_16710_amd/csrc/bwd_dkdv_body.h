@@ -503,7 +503,9 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
   }
 
   int slot = 0;   // it % kStages
-  for (int it = 0; it < n_iter; ++it) {
+  __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0): or the compiler waits for these operands in every iteration
+  // (role A's last iteration follows the loop)
+  for (int it = 0; it < n_iter - (role == 0 ? 1 : 0); ++it) {
     const int slot1 = slot + 1 == kStages ? 0 : slot + 1;
     const int slot2 = slot1 + 1 == kStages ? 0 : slot1 + 1;
     // The copies of stage it + 2 are issued after the first MFMA chain of the iteration, not at its top: right
@@ -666,6 +668,36 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
   asm volatile("" : "+v"(tid_e));
   const int lane_e = tid_e & 63, l32_e = tid_e & 31, wave_e = tid_e >> 6;
   const int n0_e = c0 + (wave_e % NCB) * 32;
+  float* gbase = (role == 0 ? p.gv : p.gk) + b * p.gs[0] + kvh * p.gs[1] + l32_e * 4;
+  f32x4 old[16];
+  auto request_old = [&]() {
+#pragma unroll
+    for (int j = 0; j < 16; ++j)
+      old[j] = *reinterpret_cast<const f32x4*>(gbase + (int64_t)min(n0_e + 2 * j + (lane_e >> 5), c_end - 1) * p.gs[2]);
+  };
+  // Role A's last iteration: dV of the last stage, without the probabilities of a stage that does not exist, and with the old
+  // values of gV on their way in the registers those would take, under its products and role B's.  With few iterations to a
+  // tile that memory round trip is a good part of it: 32 rows at 16352 of 32/8 heads 94.4 -> 89.6 us for dQ and dK/dV, 128 at 4000 of
+  // 8/8 31.7 -> 29.5, 128 at 16256 of 32/8 150.3 -> 147.5, 512 at 15872 419 -> 417; 1024 rows or more the same.  (Role B's last
+  // iteration likewise: 128 at 16256 148.3, 128 at 4000 30.1, 2048 at 30720 0.3 % slower.)
+  if constexpr (role == 0) {
+    if (n_iter > 0) {
+      lds_char* t0 = smem + slot * kTileBytes;
+      if (!divided) request_old();
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        Products::sum(acc, i, pa0, x[i]);
+        x[i] = op.col_op(t0, 32, i);
+        Products::step_end();
+      }
+#pragma unroll
+      for (int i = 0; i < 8; ++i) Products::sum(acc, i, pa1, x[i]);
+      // (nothing is being copied any more; the old values need not have come)
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" : : : "memory");
+    } else if (!divided) {
+      request_old();
+    }
+  }
   constexpr int kTurnRow = 528;                                          // bytes; 16 of padding
   static_assert(2 * NCB * 32 * kTurnRow <= Cfg::kSmemBytes, "the turned tiles fit the ring's LDS");
   lds_char* own = smem + wave_e * (32 * kTurnRow);
@@ -687,13 +719,9 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
   }
   // exclusive read-modify-write of this workgroup's gK/gV rows: role A adds dV, role B adds s * dK.  All old values
   // are requested before the tile is turned (rows past the tile's end read a clamped address and are not written
-  // back): one memory round trip, under the LDS work.
-  float* gbase = (role == 0 ? p.gv : p.gk) + b * p.gs[0] + kvh * p.gs[1] + l32_e * 4;
+  // back): one memory round trip, under the LDS work and, for role A, the last products.
   const float wf = role == 0 ? weight : weight * p.scale;
-  f32x4 old[16];
-#pragma unroll
-  for (int j = 0; j < 16; ++j)
-    old[j] = *reinterpret_cast<const f32x4*>(gbase + (int64_t)min(n0_e + 2 * j + (lane_e >> 5), c_end - 1) * p.gs[2]);
+  if constexpr (role != 0) request_old();
   turn_in();
 #pragma unroll
   for (int j = 0; j < 16; ++j) {

@@ -640,6 +640,17 @@ def test_transposed_backward_order_gives_the_same_layer_gradients(B, Hq, Hkv, N,
     assert np.array_equal(got["gk"], again["gk"]) and np.array_equal(got["gv"], again["gv"])
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,N,C", [
+    (1, 2, 2, 250, 64),      # one head: four iterations to a column tile, three, two, one (58 rows)
+    (2, 3, 1, 130, 65),      # three heads: nine and six, the second stage of each with one row
+])
+def test_dkdv_of_a_few_iterations(B, Hq, Hkv, N, C):
+    test_transposed_backward_order_gives_the_same_layer_gradients(B, Hq, Hkv, N, C)     # dK/dV in launches of their own
+    test_bf16_backward_of_a_short_call_in_one_launch(B, Hq, Hkv, N, C, None)
+    if C % 64 == 0:                                 # (what row weights need)
+        test_spaco_in_the_transposed_order(B, Hq, Hkv, N, C, [(N - 1) // C, 0])
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,N,C,sel", [
     (1, 4, 2, 1024, 128, [7, 5, 4, 1]),     # runs of one and of two selected chunks, gaps between them
     (2, 4, 1, 1100, 128, [8, 6, 3, 2, 0]),  # the last chunk is short (76 rows) and selected
