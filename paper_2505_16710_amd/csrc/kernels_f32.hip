@@ -1,4 +1,5 @@
 // Backward of one chunk, fp32: dQ and dK/dV (f32_tiles.h).
+#include <algorithm>
 #include <type_traits>
 
 #include "f32_tiles.h"
@@ -314,9 +315,20 @@ __global__ __launch_bounds__(NW * 64) void bwd_f32_kernel(AttnParams p, Runs dq_
 // Wavefronts per workgroup: as many as the register file holds of the kernel at that head_dim.
 template <int NT> constexpr int kBwdWaves = NT <= 8 ? 8 : 4;
 
+inline int64_t columns_of(const OneRun& t) { return t.end - t.begin; }
+inline int64_t columns_of(const SegTable& t) {
+  int64_t n = 0;
+  for (int i = 0; i < t.n; ++i) n += t.col_end[i] - t.col_begin[i];
+  return n;
+}
+
 // Few row tiles: as in the forward, two or four workgroups for each, which compute a part of dQ's columns apiece (a third of
 // the work).  64 + 128 tiles of head_dim 64 10.9 -> 10.1 us; 15 + 120 of 128 23.3 -> 19.1 (four); 28 + 252 of 64 18.1 -> 16.5 (two: the
 // others' CUs may be shared a little, 64 + 256 gain nothing); 120 + 120 of 128 by two 26.2 -> 28.1.
+// Where the whole tiles have a CU each and the halves would not, `crowded` says whether sharing costs more than the halves save: the
+// time of a dQ tile goes with its columns, that of the column tiles which share a CU (the last, launched last) with the rows they
+// see.  Of 55 calls measured, of head_dim 32 .. 256, none below the line is slower whole: 64 + 192 of 64 over 768 columns 17.7 -> 14.8 us, 
+// 64 + 160 over 640 14.4 -> 12.8, 66 + 174 of 128 over 917 36.8 -> 33.1; beyond it 57 + 159 of 128 over 843 take 30.6 whole, 26.7 in halves.
 template <int NT, int NO, typename Runs>
 int bwd_launch(const AttnParams& p, const Runs& dq_runs, const Runs& seg, int64_t n_dq, int64_t n_kv, hipStream_t s) {
   constexpr int NW = kBwdWaves<NT>, smem = 2 * NW * kPart<NT> * 4;
@@ -329,13 +341,18 @@ int bwd_launch(const AttnParams& p, const Runs& dq_runs, const Runs& seg, int64_
   hipLaunchKernelGGL(kern, dim3((unsigned)(n_dq + n_kv)), dim3(NW * 64), smem, s, p, dq_runs, seg, (int)n_dq);
   return launch_status();
 }
+inline bool crowded(const AttnParams& p, int64_t columns, int64_t n_dq, int64_t n_kv, int64_t cus) {
+  const int64_t shared = n_dq * 2 + n_kv - cus, rows = std::min<int64_t>(p.C, kRows * shared / (p.Hkv * p.B));
+  return n_dq + n_kv <= cus && shared > 0 && 4 * columns < 1200 + 11 * rows * p.G;
+}
 template <int NT, typename Runs>
 int bwd_parts(const AttnParams& p, const Runs& dq_runs, const Runs& seg, int64_t n_dq, int64_t n_kv, hipStream_t s) {
   const int64_t cus = device_cus();
   if constexpr (NT < 16 || std::is_same<Runs, OneRun>::value) {    // (with the table scalar registers are short at the longest rows)
     if (dq_over_inputs(p, sizeof(float))) return bwd_launch<NT, NT>(p, dq_runs, seg, n_dq, n_kv, s);
     if (n_dq * 4 + n_kv <= cus) return bwd_launch<NT, (NT + 3) / 4>(p, dq_runs, seg, n_dq, n_kv, s);
-    if (n_dq * 2 + n_kv <= cus + cus / 4) return bwd_launch<NT, (NT + 1) / 2>(p, dq_runs, seg, n_dq, n_kv, s);
+    if (n_dq * 2 + n_kv <= cus + cus / 4 && !crowded(p, columns_of(dq_runs), n_dq, n_kv, cus))
+      return bwd_launch<NT, (NT + 1) / 2>(p, dq_runs, seg, n_dq, n_kv, s);
   }
   return bwd_launch<NT, NT>(p, dq_runs, seg, n_dq, n_kv, s);
 }

@@ -98,6 +98,13 @@ def test_fp32_row_tiles_with_several_workgroups(D, Hq, C, q_start):
         assert max_rel(to_host(gk), ref[1] * factor) <= 1e-4 and max_rel(to_host(gv), ref[2] * factor) <= 1e-4
 
 
+@pytest.mark.parametrize("D", [36, 64, 132, 256])
+@pytest.mark.parametrize("Hq,C,q_start", [(4, 256, 2000), (4, 208, 2500), (4, 208, 2495)])
+def test_fp32_row_tiles_beside_more_column_tiles_than_free_cus(D, Hq, C, q_start):
+    """Whole row tiles where halves would share their CUs for longer than they save, and halves beyond that line."""
+    test_fp32_row_tiles_with_several_workgroups(D, Hq, C, q_start)
+
+
 @pytest.mark.parametrize("dtype,D,Hq,Hkv,C,q_start", [
     ("f32", 64, 4, 4, 256, 768),        # 64 row tiles: four workgroups for each where O lies elsewhere
     ("f32", 128, 8, 2, 250, 100),       # 128: two
