@@ -1,5 +1,5 @@
 // Forward of one chunk, bf16 matrix cores, 4-wavefront workgroups (Eq. 1 at the attention layer): the shape used
-// when a call has at least two row tiles per CU.  A workgroup owns 128 query rows of one head, a wavefront 32 of them;
+// when a call has two row tiles per CU or close to it (launch_fwd_bf16).  A workgroup owns 128 query rows of one head, a wavefront 32 of them;
 // S^T = K Q^T so that a lane owns query rows; O^T += V^T P^T from registers.  K tiles stream through a ring of three LDS
 // slots and V tiles through a ring of two, and S of tile n+1 is computed while the exponentials of tile n are taken (the
 // two instruction streams are written interleaved), so that the matrix pipe runs while the vector ALU works: 5 %

@@ -7,7 +7,7 @@
 // registers.  K and V tiles stream through swizzled LDS tiles shared by the workgroup, copied
 // global -> LDS directly ahead of their use.  Two shapes of workgroup:
 //   4 wavefronts (fwd4_bf16.hip): tiles of 64 cache rows, 80 KiB of LDS -> two workgroups per CU; used when a
-//       call has at least two row tiles per CU;
+//       call has two row tiles per CU or close to it (launch_fwd_bf16);
 //   8 wavefronts (this header): tiles of 128 cache rows in two buffers of a K and a V tile; wavefront (rb, kh)
 //       handles row block rb and the kh-th 64-row half of every tile, and the two partial (max, sum, O) of a
 //       row block are merged through LDS at the end.  One such workgroup fills a CU with two wavefronts per

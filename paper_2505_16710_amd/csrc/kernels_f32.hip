@@ -327,7 +327,7 @@ inline int64_t columns_of(const SegTable& t) {
 // others' CUs may be shared a little, 64 + 256 gain nothing); 120 + 120 of 128 by two 26.2 -> 28.1.
 // Where the whole tiles have a CU each and the halves would not, `crowded` says whether sharing costs more than the halves save: the
 // time of a dQ tile goes with its columns, that of the column tiles which share a CU (the last, launched last) with the rows they
-// see.  Of 55 calls measured, of head_dim 32 .. 256, none below the line is slower whole: 64 + 192 of 64 over 768 columns 17.7 -> 14.8 us, 
+// see.  Of 55 calls measured, of head_dim 32 .. 256, none below the line is slower whole: 64 + 192 of 64 over 768 columns 17.7 -> 14.8 us,
 // 64 + 160 over 640 14.4 -> 12.8, 66 + 174 of 128 over 917 36.8 -> 33.1; beyond it 57 + 159 of 128 over 843 take 30.6 whole, 26.7 in halves.
 template <int NT, int NO, typename Runs>
 int bwd_launch(const AttnParams& p, const Runs& dq_runs, const Runs& seg, int64_t n_dq, int64_t n_kv, hipStream_t s) {

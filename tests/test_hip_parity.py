@@ -415,6 +415,12 @@ def test_bf16_row_tiles_beyond_one_round_divided(B, Hq, Hkv, C, q_start):
             assert max_rel(to_host(dqs[0][b, h]), to_host(ref_dq)) <= TOL["bf16"]["dq"], (b, h)
 
 
+@pytest.mark.parametrize("q_start", [6599, 6600])
+def test_bf16_row_tiles_for_two_workgroups_on_most_cus(q_start):
+    """416 tiles for 256 CUs, on both sides of the cache length from which they go to workgroups of four wavefronts."""
+    test_bf16_row_tiles_beyond_one_round_divided(1, 16, 8, 3300, q_start)
+
+
 def test_forward_leaves_a_workspace_that_does_not_fit_alone():
     """One byte short, or not on 256 bytes: the undivided forward, bit for bit, and nothing is written there."""
     B, Hq, Hkv, C, q_start = 1, 48, 16, 700, 2900           # row tiles between one and two rounds
