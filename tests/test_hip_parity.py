@@ -421,6 +421,41 @@ def test_bf16_row_tiles_for_two_workgroups_on_most_cus(q_start):
     test_bf16_row_tiles_beyond_one_round_divided(1, 16, 8, 3300, q_start)
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,C,q_start", [
+    (1, 11, 1, 3200, 10),      # 275 row tiles of one unit on eight XCDs, 26 column tiles
+    (1, 18, 2, 2000, 5),       # 288 of two on four each
+    (2, 10, 2, 1700, 70),      # 280 of four on two each
+    (1, 24, 4, 1500, 9),       # 288 of four, seven rounds of shared-out column tiles
+])
+def test_bf16_tiles_of_a_unit_dealt_to_several_xcds(B, Hq, Hkv, C, q_start):
+    """More tiles than CUs with fewer than eight (batch, KV head) pairs: every tile is done once, whole or shared out.  Gradients are
+    added to what is there; fp32 on the device."""
+    N, s, G = q_start + C, 1 / np.sqrt(128), Hq // Hkv
+    g = torch.Generator(device=DEV).manual_seed(91)
+    q, do, k, v = (torch.randn(B, h, n, 128, device=DEV, generator=g).to(torch.bfloat16)
+                   for h, n in ((Hq, C), (Hq, C), (Hkv, N), (Hkv, N)))
+    o, lse = seco.seco_chunk_attn_fwd(q, k, v, q_start, s)
+    gk, gv = torch.full((B, Hkv, N, 128), 0.5, device=DEV), torch.full((B, Hkv, N, 128), -0.25, device=DEV)
+    dq = seco.seco_chunk_attn_bwd(q, k, v, o, lse, do, gk, gv, q_start, s)
+    rows = torch.arange(C, device=DEV)[:, None] + q_start
+    for b in range(B):
+        for kh in range(Hkv):
+            kf, vf, rk, rv = k[b, kh].float(), v[b, kh].float(), 0.5, -0.25
+            for h in range(kh * G, kh * G + G):
+                qf, dof = q[b, h].float(), do[b, h].float()
+                z = (qf @ kf.t() * s).masked_fill(torch.arange(N, device=DEV)[None, :] > rows, float("-inf"))
+                ref_l = z.logsumexp(-1)
+                p = torch.exp(z - ref_l[:, None])
+                ref_o = p @ vf
+                ds = p * (dof @ vf.t() - (dof * ref_o).sum(-1, keepdim=True))
+                assert max_rel(to_host(o[b, h]), to_host(ref_o)) <= TOL["bf16"]["o"], (b, h)
+                assert max_rel(to_host(lse[b, h]), to_host(ref_l)) <= TOL["bf16"]["lse"], (b, h)
+                assert max_rel(to_host(dq[b, h]), to_host(s * ds @ kf)) <= TOL["bf16"]["dq"], (b, h)
+                rk, rv = rk + s * ds.t() @ qf, rv + p.t() @ dof
+            assert max_rel(to_host(gk[b, kh]), to_host(rk)) <= TOL["bf16"]["gk"], (b, kh)
+            assert max_rel(to_host(gv[b, kh]), to_host(rv)) <= TOL["bf16"]["gv"], (b, kh)
+
+
 def test_forward_leaves_a_workspace_that_does_not_fit_alone():
     """One byte short, or not on 256 bytes: the undivided forward, bit for bit, and nothing is written there."""
     B, Hq, Hkv, C, q_start = 1, 48, 16, 700, 2900           # row tiles between one and two rounds
