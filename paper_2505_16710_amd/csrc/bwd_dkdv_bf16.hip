@@ -11,7 +11,7 @@ __global__ __launch_bounds__(NCB * 128, 2) void dkdv_bf16_kernel(AttnParams p, S
                                                                   RowRuns rr, int total_items) {
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];   // Cfg::kSmemBytes (can exceed the 64 KiB static limit)
   lds_char* smem = (lds_char*)smem_raw;
-  const int item = xcd_item(blockIdx.x, total_items, p.B * p.Hkv, total_items);
+  const int item = xcd_item(blockIdx.x, total_items, p.B * p.Hkv);
   if (item < 0) return;
   // wavefronts 0 .. NCB-1: role A, the others role B (wavefront-uniform: a scalar branch)
   const int role_u = __builtin_amdgcn_readfirstlane((int)threadIdx.x / (64 * NCB));
@@ -36,7 +36,7 @@ int launch(const AttnParams& p, const SegTable& seg, const TailSplit& ts, const 
   if (!allow_lds(ready, reinterpret_cast<const void*>(kern), Cfg::kSmemBytes)) return SECO_ERR_LAUNCH;
   {
     ProfScope prof(kKernelDkdv, s);   // the merge of the divided tiles counts as part of the dK/dV pass
-    hipLaunchKernelGGL(kern, dim3(xcd_grid(total, p.B * p.Hkv, total)), dim3(Cfg::kThreads), Cfg::kSmemBytes, s, p, seg, ts, rr, total);
+    hipLaunchKernelGGL(kern, dim3(xcd_grid(total, p.B * p.Hkv)), dim3(Cfg::kThreads), Cfg::kSmemBytes, s, p, seg, ts, rr, total);
     if (ts.plan.n_shared > 0)
       hipLaunchKernelGGL(dkdv_tail_merge_kernel<kColTileBf16>, dim3(tail_merge_grid<kColTileBf16>(p, ts)), dim3(256), 0, s, p, seg, ts);
   }

@@ -10,7 +10,7 @@ template <int KH, int SPLIT, bool SPARSE>
 __global__ __launch_bounds__(256 * KH, 2) void dq_bf16_kernel(AttnParams p, SegTable seg, int n_mtiles, int total_items) {
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];
   const int item = SPLIT == kShares ? shares_item(blockIdx.x, p.B * p.Hkv * p.rows_whole, total_items)
-                                     : xcd_item(blockIdx.x, total_items, SPLIT == kDivided ? 8 : p.B * p.Hkv, total_items);
+                                     : xcd_item(blockIdx.x, total_items, SPLIT == kDivided ? 8 : p.B * p.Hkv);
   if (item < 0) return;
   dq_bf16_body<KH, SPLIT, SPARSE>(p, seg, n_mtiles, item, (lds_char*)smem_raw);
 }
@@ -24,7 +24,7 @@ int launch_kh(const AttnParams& p, const SegTable& seg, int n_mtiles, int total,
   {
     ProfScope prof(kKernelDq, s);
     const int units = SPLIT == kWholeTiles ? p.B * p.Hkv : 8, first = SPLIT == kShares ? p.B * p.Hkv * p.rows_whole : 0;
-    hipLaunchKernelGGL(kern, dim3(xcd_grid(first, units, total) + xcd_grid(total - first, units, total)), dim3(256 * KH), smem, s, p, seg, n_mtiles, total);
+    hipLaunchKernelGGL(kern, dim3(xcd_grid(first, units) + xcd_grid(total - first, units)), dim3(256 * KH), smem, s, p, seg, n_mtiles, total);
   }
   return launch_status();
 }

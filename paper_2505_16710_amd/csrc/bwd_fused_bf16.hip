@@ -40,8 +40,7 @@ __global__ __launch_bounds__(512, 2) void bwd_fused_bf16_kernel(AttnParams p, Se
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];
   lds_char* smem = (lds_char*)smem_raw;
   const bool first = (int)blockIdx.x < first_grid, kv = first == (kv_first != 0);
-  const int item = xcd_item(first ? blockIdx.x : blockIdx.x - first_grid, kv ? kv_total : dq_total, SPLIT && !kv ? 8 : p.B * p.Hkv,
-                            kv_total + dq_total);
+  const int item = xcd_item(first ? blockIdx.x : blockIdx.x - first_grid, kv ? kv_total : dq_total);
   if (item < 0) return;
   if (kv) {
     RowRuns none;
@@ -92,8 +91,7 @@ int launch(const AttnParams& p, const SegTable& seg, const TailSplit& ts, const 
   auto kern = bwd_fused_bf16_kernel<SPLIT, RUNS>;
   static std::atomic<uint64_t> ready{0};
   if (!allow_lds(ready, reinterpret_cast<const void*>(kern), kSmem)) return SECO_ERR_LAUNCH;
-  const int all = kv_total + dq_total, kv = xcd_grid(kv_total, p.B * p.Hkv, all), dq = xcd_grid(dq_total, SPLIT ? 8 : p.B * p.Hkv, all);
-  const int first = kv_first ? kv : dq, second = kv_first ? dq : kv;
+  const int first = xcd_grid(kv_first ? kv_total : dq_total), second = xcd_grid(kv_first ? dq_total : kv_total);
   {
     ProfScope prof(kKernelBwd, s);
     hipLaunchKernelGGL(kern, dim3(first + second), dim3(512), kSmem, s, p, seg, ts, n_mtiles, kv_total, dq_total, first,

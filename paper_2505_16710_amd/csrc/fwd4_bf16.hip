@@ -32,7 +32,7 @@ __global__ __launch_bounds__(256, 2) void fwd4_bf16_kernel(AttnParams p, int n_m
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];   // 5 * kTileBytes: K ring (3 tiles), V ring (2 tiles)
   lds_char* smem = (lds_char*)smem_raw;
 
-  const int item = xcd_item(blockIdx.x, total_items, p.B * p.Hkv, total_items);
+  const int item = xcd_item(blockIdx.x, total_items, p.B * p.Hkv);
   if (item < 0) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int l16 = lane & 15, g = lane >> 4, pg = pi4(g);
@@ -270,7 +270,7 @@ int launch_fwd4_bf16(const AttnParams& p, int n_mtiles, int total, hipStream_t s
   if (!allow_lds(ready, reinterpret_cast<const void*>(fwd4_bf16_kernel), smem)) return SECO_ERR_LAUNCH;
   {
     ProfScope prof(kKernelFwd, s);
-    hipLaunchKernelGGL(fwd4_bf16_kernel, dim3(xcd_grid(total, p.B * p.Hkv, total)), dim3(256), smem, s, p, n_mtiles, total);
+    hipLaunchKernelGGL(fwd4_bf16_kernel, dim3(xcd_grid(total, p.B * p.Hkv)), dim3(256), smem, s, p, n_mtiles, total);
   }
   return launch_status();
 }

@@ -52,7 +52,7 @@ __global__ __launch_bounds__(512, 2) void fwd8_bf16_kernel(AttnParams p, int n_m
   lds_char* smem = (lds_char*)smem_raw;
 
   const int item = SPLIT == kShares ? shares_item(blockIdx.x, p.B * p.Hkv * p.rows_whole, total_items)
-                                     : xcd_item(blockIdx.x, total_items, SPLIT == kDivided ? 8 : p.B * p.Hkv, total_items);
+                                     : xcd_item(blockIdx.x, total_items, SPLIT == kDivided ? 8 : p.B * p.Hkv);
   if (item < 0) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int l32 = lane & 31, g = lane >> 5;
@@ -369,7 +369,7 @@ int launch_fwd8(const AttnParams& p, int n_mtiles, int total, hipStream_t s) {
   {
     ProfScope prof(kKernelFwd, s);
     const int units = SPLIT == kWholeTiles ? p.B * p.Hkv : 8, first = SPLIT == kShares ? p.B * p.Hkv * p.rows_whole : 0;
-    hipLaunchKernelGGL(kern, dim3(xcd_grid(first, units, total) + xcd_grid(total - first, units, total)), dim3(512), smem, s, p, n_mtiles, total);
+    hipLaunchKernelGGL(kern, dim3(xcd_grid(first, units) + xcd_grid(total - first, units)), dim3(512), smem, s, p, n_mtiles, total);
   }
   return launch_status();
 }
