@@ -29,6 +29,7 @@ SOURCES = [
     "fwd_small_bf16.hip",
     "bwd_dq_bf16.hip",
     "bwd_dkdv_bf16.hip",
+    "bwd_dkdv32_bf16.hip",
     "bwd_fused_bf16.hip",
     "decoder.hip",
     "gemm_bf16.hip",

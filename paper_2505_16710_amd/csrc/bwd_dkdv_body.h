@@ -128,6 +128,8 @@ struct Products16 {
   static __device__ __forceinline__ void map(Tile& x, int e, const F& f) { x[(e >> 2) & 1][e >> 3][e & 3] = f(x[(e >> 2) & 1][e >> 3][e & 3]); }
   static __device__ __forceinline__ bf16x8 pack(const Tile& x, int half) { return pack44(x[0][half], x[1][half]); }
   static __device__ __forceinline__ void step_end() { __builtin_amdgcn_sched_barrier(0); }
+  // (lgkmcnt(0): or the compiler waits for the operands that come with the loop in every iteration)
+  static __device__ __forceinline__ void loop_begins() { __builtin_amdgcn_s_waitcnt(0xc07f); }
   static __device__ __forceinline__ void clear(Acc& acc) {
 #pragma unroll
     for (int db = 0; db < 8; ++db) acc[db][0] = acc[db][1] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -184,6 +186,7 @@ struct Products32 {
   static __device__ __forceinline__ void map(Tile& x, int e, const F& f) { x[e] = f(x[e]); }
   static __device__ __forceinline__ bf16x8 pack(const Tile& x, int half) { return pack8(x, half); }
   static __device__ __forceinline__ void step_end() {}
+  static __device__ __forceinline__ void loop_begins() {}
   static __device__ __forceinline__ void clear(Acc& acc) {
 #pragma unroll
     for (int db = 0; db < 4; ++db)
@@ -503,7 +506,7 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
   }
 
   int slot = 0;   // it % kStages
-  __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0): or the compiler waits for these operands in every iteration
+  Products::loop_begins();
   // (role A's last iteration follows the loop)
   for (int it = 0; it < n_iter - (role == 0 ? 1 : 0); ++it) {
     const int slot1 = slot + 1 == kStages ? 0 : slot + 1;

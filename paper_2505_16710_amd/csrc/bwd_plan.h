@@ -35,6 +35,7 @@ struct BwdPlan {
   int dq_splits;
   bool kv_first;
   TailSplit ts;
+  float busy;        // of the CUs, in dK/dV by itself (share_plan)
 };
 // Column tiles for a round or more (n_kv of them, iters iterations each): in how many shares a row tile of dQ joins them
 // in one launch, dQ first; 0: not.  The column tiles of a round all start together and reach the read-modify-write of
@@ -190,7 +191,7 @@ BwdPlan plan_bwd(const AttnParams& p, const SegTable& seg, bool dq) {
   best.kv_first = true;
   best.ts.part = p.tail_part;
   float kv_alone = 0.f;
-  best.ts.plan = share_plan(runs, n_units, n_ctiles, p.G, p.C, slots_in(p.tail_bytes), kv_alone);
+  best.ts.plan = share_plan(runs, n_units, n_ctiles, p.G, p.C, slots_in(p.tail_bytes), kv_alone, &best.busy);
   if (!dq) return best;
   const SplitPlan sp = split_plan(p.B, p.Hkv, p.G, p.C);
   const int tiles = (p.q_start + p.C + 127) / 128;
@@ -204,7 +205,7 @@ BwdPlan plan_bwd(const AttnParams& p, const SegTable& seg, bool dq) {
       best.dq_splits = n;
       best.kv_first = false;
       best.ts.part = p.tail_part + dq_part(n) / sizeof(float);
-      best.ts.plan = share_plan(runs, n_units, n_ctiles, p.G, p.C, slots_in(p.tail_bytes - dq_part(n)), kv_alone);
+      best.ts.plan = share_plan(runs, n_units, n_ctiles, p.G, p.C, slots_in(p.tail_bytes - dq_part(n)), kv_alone, &best.busy);
     }
     return best;
   }

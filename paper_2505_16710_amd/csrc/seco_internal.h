@@ -280,14 +280,14 @@ inline void for_last(const IterRuns& r, int n, const F& f) {
 // time that is expected to take and how much of it the longest workgroup takes.  wg: of a workgroup; partial sums take
 // 4 us + 0.03 per share (written and read again) + 0.02 per tile.
 // fit: all workgroups of the list must run at once, on `cus` compute units.
-struct ShareChoice { int per; float time, longest; };
+struct ShareChoice { int per; float time, longest, even, span; };   // even, span: without the merge, if all CUs worked alike and as it is
 template <int N>
 inline void choose_shares(const IterRuns& r, int n, int n_units, const int (&cus)[N], int slots, int min_ways, bool fit, WgTime wg,
                           ShareChoice (&best)[N]) {      // for each of N numbers of compute units
   static const int ways[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32};
   int most = 0;
   for_last(r, n, [&](int it, int) { most = it > most ? it : most; });
-  for (ShareChoice& c : best) c = ShareChoice{0, -1.f, 0.f};
+  for (ShareChoice& c : best) c = ShareChoice{0, -1.f, 0.f, 0.f, 0.f};
   for (int w : ways) {
     if (w < min_ways) continue;
     const int per = (most + w - 1) / w;
@@ -309,8 +309,9 @@ inline void choose_shares(const IterRuns& r, int n, int n_units, const int (&cus
       any = true;
       const float even = sum * n_units / cus[i];
       float t = entries * n_units <= cus[i] ? longest : even + 0.5f * longest > longest + wg.wg ? even + 0.5f * longest : longest + wg.wg;
+      const float span = t;
       if (shared > 0) t += kMergeLaunch + (0.03f * shared + 0.02f * tiles) * n_units;
-      if (best[i].time < 0.f || t < best[i].time) best[i] = ShareChoice{w > 1 ? per : 0, t, longest};
+      if (best[i].time < 0.f || t < best[i].time) best[i] = ShareChoice{w > 1 ? per : 0, t, longest, even, span};
     }
     if (!any) break;
   }
@@ -343,17 +344,23 @@ struct TailSplit {
   float* part;
   SharePlan plan;
 };
-// For a dK/dV pass that has the chip to itself; time: what it is expected to take from its last full round on
-inline SharePlan share_plan(const IterRuns& r, int n_units, int n_ctiles, int G, int n_rows, int slots, float& time) {
+// For a dK/dV pass that has the chip to itself; time: what it is expected to take from its last full round on; busy: the part of its
+// workgroups' time in that of all CUs
+inline SharePlan share_plan(const IterRuns& r, int n_units, int n_ctiles, int G, int n_rows, int slots, float& time, float* busy = nullptr) {
   const int cus = device_cus();
   const int64_t items = (int64_t)n_units * n_ctiles;
   const int tail = (int)(items % cus);
   const TailPlan tp = tail_plan(n_units, n_ctiles, G, n_rows);
   const int n = tp.hs > 1 ? tp.n_tiles : items < cus ? n_ctiles : (tail + n_units - 1) / n_units;
   time = kDkdvTime.of(r.iters[0]);
+  const float full = (float)(items / cus);
+  if (busy) *busy = tail == 0 ? 1.f : (full + (float)tail / cus) / (full + 1.f);
   if (tail == 0 || slots < 2 * n_units || n > r.n_tiles) return make_shares(r, 0, 0);
   const ShareChoice c = choose_shares(r, n, n_units, cus, slots, tp.hs > 1 ? tp.hs : 1, false, kDkdvTime);
-  if (c.time >= 0.f) time = c.time;
+  if (c.time >= 0.f) {
+    if (busy) *busy = (full * time + c.even) / (full * time + c.span);
+    time = c.time;
+  }
   return make_shares(r, n, c.per);
 }
 
@@ -383,6 +390,8 @@ int launch_bwd_fused_bf16(const AttnParams& p, const SegTable& seg, const TailSp
 int launch_dq_bf16_now(const AttnParams& p, const SegTable* dq_runs, hipStream_t s);
 // the same with the query rows taken from runs (p.C: number of rows that may be addressed from p.q / p.d_o)
 int launch_dkdv_rows_bf16(const AttnParams& p, const SegTable& seg, const RowRuns& rr, hipStream_t s);
+// the kernel of either with 32x32x16 products (its own translation unit)
+int launch_dkdv32_bf16(const AttnParams& p, const SegTable& seg, const TailSplit& ts, const RowRuns& rr, bool rows, hipStream_t s);
 #ifndef SECO_DKDV_COLS
 #define SECO_DKDV_COLS 128
 #endif

@@ -425,7 +425,9 @@ def test_bf16_row_tiles_for_two_workgroups_on_most_cus(q_start):
     (1, 11, 1, 3200, 10),      # 275 row tiles of one unit on eight XCDs, 26 column tiles
     (1, 18, 2, 2000, 5),       # 288 of two on four each
     (2, 10, 2, 1700, 70),      # 280 of four on two each
-    (1, 24, 4, 1500, 9),       # 288 of four, seven rounds of shared-out column tiles
+    (1, 24, 4, 1500, 9),       # 288 of four
+    (1, 32, 8, 1095, 1694),    # (eight units; 176 column tiles of up to 72 iterations: 32x32x16 products of dK/dV)
+    (1, 8, 8, 1500, 2596),     # (as many column tiles as CUs: 16x16x32)
 ])
 def test_bf16_tiles_of_a_unit_dealt_to_several_xcds(B, Hq, Hkv, C, q_start):
     """More tiles than CUs with fewer than eight (batch, KV head) pairs: every tile is done once, whole or shared out.  Gradients are
