@@ -14,10 +14,9 @@ The projections and the MLP, the residual adds, norms, SiLU, loss and embedding 
 kernels of the library too (gemm_bf16.hip, decoder.hip), the derivatives are written out instead of being recorded, and
 a chunk is launched by one call of the binding's extension module (chunk_step_ext.cpp): at the row counts of a chunk a
 step is bound by the number of launches and the host time behind each (with autograd and framework operators, 27 ms for
-two layers over 4096 tokens in chunks of 512, of which the GPU worked 14; 3.8 now, 2.3 with the chunks joined).  Products whose type or alignment
+two layers over 4096 tokens in chunks of 512, of which the GPU worked 14; 3.8 now).  Products whose type or alignment
 the library's kernel does not take (fp32, row lengths that are not multiples of 8) and large ones, which the framework's
-kernels do faster, go through the framework's.  Only one chunk's activations are alive at a time, as in the paper, or
-those of a few short chunks that Alg. 1 walks as one: up to 2048 rows and 256 MiB (step's stage1_chunk_len: never).
+kernels do faster, go through the framework's.  Only one chunk's activations are alive at a time, as in the paper.
 There is no CPU path.  (LayerState, ChunkAttention and Rope are the same attention as autograd functions.)
 
 Parameters are bf16 or fp32 tensors on one GPU, all of one type, with two exceptions: gains may be of a narrower one, and
@@ -184,9 +183,6 @@ class ChunkedDecoder:
         keep_attention_outputs: stage 1 keeps every layer's O and LSE (2 + 4/D bytes per query element: with 288 GB
         of HBM that is cheap), and the rebuilt chunks of stage 2 take them back instead of running the attention
         forward again; the gradients are bit-identical to the recomputing schedule.
-        chunk_len: Alg. 1 walks neighbouring chunks at once as long as what they keep alive stays
-        under 256 MiB and 2048 rows (and can be had): its gradients do not depend on where the sequence is cut, and short
-        chunks are bound by their launches.  A stage1_chunk_len, be it chunk_len, keeps both lengths as given.
         stage1_chunk_len: chunk length of the inference pass only (default chunk_len).  Stage 1 holds no graph, so on a
         GPU with room for one layer's activations of the whole sequence it can run as a single chunk (a plain
         prefill); together with keep_attention_outputs, stage 2 then launches backward kernels only.  The caches
@@ -216,8 +212,6 @@ class ChunkedDecoder:
                 raise ValueError("Alg. 2 in the transposed order needs a chunk length that is a multiple of 64")
         for t in p.values():
             t.grad = None
-        # Alg. 1, both stages alike: the gradients do not depend on where the sequence is cut
-        join = selected is None and stage1_chunk_len is None and dq_weights is None
         c1 = stage1_chunk_len or chunk_len
         picked = None if selected is None else {int(i) for i in selected}
         order = range(len(starts) - 1, -1, -1) if selected is None else sorted(picked, reverse=True)
@@ -228,11 +222,7 @@ class ChunkedDecoder:
         ext = _b._ext or _b._load_ext()
         with torch.no_grad():
             run = ext.step_new((self.n_layers, self.Hq, self.Hkv, self.D, self.scale, self.rope_base, B, N, min(c1, N),
-                                min(chunk_len, N), transposed_backward, join), [p[n] for n in names])
-            if ext.step_span(run):          # several chunks at once
-                chunk_len = c1 = ext.step_span(run)
-                starts = list(range(0, N, chunk_len))
-                order = range(len(starts) - 1, -1, -1)
+                                min(chunk_len, N), transposed_backward), [p[n] for n in names])
             tokens, targets = tokens.to(torch.int64), targets.to(torch.int64)
             losses = torch.empty(N * B, dtype=torch.float32, device=dev)        # one per token, in stage-1 order
             # stage 2 rebuilds every chunk as stage 1 ran it, launch for launch: the losses come from there, and stage 1 ends

@@ -5,7 +5,7 @@
 // through the framework (17 - 19 us of host time per call), a two-layer step over 4096 tokens in chunks of 512 took
 // 9.1 ms, of which the GPU worked 6.7; here a launch costs 2 - 4 us of host time, activations are carved from two
 // blocks allocated once per step, and the products are the library's own (gemm_bf16.hip) where type, alignment and size
-// allow: 3.8 ms, in which the GPU is busy throughout, and 2.3 where short chunks are walked at once (joined).
+// allow: 3.8 ms, in which the GPU is busy throughout.
 #include <map>
 #include <memory>
 
@@ -70,7 +70,6 @@ struct Step {
   Arena stage1, stage2;
   void* s = nullptr;                               // stream of the current call
   bool trained = false;                            // a chunk has been back-propagated
-  int64_t span = 0;                                // rows of a sequence that are walked at once, 0: a chunk's
 
   at::TensorOptions opts() const { return emb.w.options().requires_grad(false); }
   Tensor view(void* p, at::IntArrayRef sizes) { return at::from_blob(p, sizes, opts()); }
@@ -419,21 +418,6 @@ void begin(Step& st) {
   st.s = stream(Py_None);
 }
 
-// Rows that Alg. 1 walks at once when the chunks are short: several whole chunks, as its gradients do not depend on where the
-// sequence is cut.  A chunk's launches are bound by their number (62 per chunk and two layers, 8 us each, whatever its rows) until
-// its products fill the chip, about 2048 rows; kJoinedBytes bounds the activations of what is joined, a thousandth of the
-// card's memory.  Two layers of width 1024 (MLP 4096, vocabulary 1024) over 4096 tokens, chunks of 256 / 512 / 1024 rows:
-// 5845 / 3821 / 2777 us one by one, 2315 joined (551 MiB of activations for the whole sequence at once: 1989).
-constexpr int64_t kJoinedRows = 2048;
-constexpr size_t kJoinedBytes = (size_t)256 << 20;
-int64_t joined(const Step& st, int64_t chunk, size_t bytes_per_row) {
-  const int64_t rows = std::min(kJoinedRows, (int64_t)(kJoinedBytes / bytes_per_row)) / st.B;
-  const int64_t k = (st.N + chunk - 1) / chunk, most = std::min(k, rows / chunk);
-  if (most < 2) return chunk;
-  const int64_t spans = (k + most - 1) / most;     // (of about equal length)
-  return (k + spans - 1) / spans * chunk;
-}
-
 // contiguous from a 16-byte boundary on, which a piece of a larger buffer need not be
 Tensor laid_out(const Tensor& t) {
   const Tensor c = t.contiguous();
@@ -479,12 +463,10 @@ Param gain(PyObject* o, int64_t dm, at::ScalarType rows) {
   return p;
 }
 
-// (config, params): config = (n_layers, Hq, Hkv, D, scale, rope_base or None, B, N, chunk rows of stage 1, of stage 2, transposed,
-// optional: whether short chunks may be joined);
+// (config, params): config = (n_layers, Hq, Hkv, D, scale, rope_base or None, B, N, chunk rows of stage 1, of stage 2, transposed);
 // params = [emb, head, norm_f, then norm1, norm2, wq, wk, wv, wo, w1, w2 of every layer] -> step
 PyObject* step_new(PyObject* const* a) {
-  if (!PyTuple_Check(a[0]) || PyTuple_GET_SIZE(a[0]) < 11 || PyTuple_GET_SIZE(a[0]) > 12 || !PyList_Check(a[1]))
-    raise(PyExc_TypeError, "expected (tuple of 11 or 12, list)");
+  if (!PyTuple_Check(a[0]) || PyTuple_GET_SIZE(a[0]) != 11 || !PyList_Check(a[1])) raise(PyExc_TypeError, "expected (tuple of 11, list)");
   auto cfg = [&](int i) { return PyTuple_GET_ITEM(a[0], i); };
   auto st = std::make_unique<Step>();
   st->L = integer(cfg(0));
@@ -496,7 +478,7 @@ PyObject* step_new(PyObject* const* a) {
   st->B = integer(cfg(6));
   st->N = integer(cfg(7));
   const int64_t c1 = integer(cfg(8)), c2 = integer(cfg(9));
-  const bool transposed = PyObject_IsTrue(cfg(10)) == 1, join = PyTuple_GET_SIZE(a[0]) == 12 && PyObject_IsTrue(cfg(11)) == 1;
+  const bool transposed = PyObject_IsTrue(cfg(10)) == 1;
   if (PyList_GET_SIZE(a[1]) != 3 + 8 * st->L) raise(PyExc_ValueError, "wrong number of parameters");
   if (st->L < 0 || st->Hq < 1 || st->Hkv < 1 || st->D < 1 || st->B < 1 || st->N < 1 || c1 < 1 || c2 < 1)
     raise(PyExc_ValueError, "sizes must be positive");
@@ -574,30 +556,14 @@ PyObject* step_new(PyObject* const* a) {
   auto layer_bytes = [&](int64_t R) { return (size_t)R * ((4 * st->dm + st->W + st->HD + 2 * st->ff) * e + 8 + 4 * st->Hq) + 12 * 256; };
   auto other_bytes = [&](int64_t R) { return (size_t)R * (3 * st->dm * e + st->V * st->head.w.element_size() + 4) + 8 * 256; };
   auto bwd_bytes = [&](int64_t R) { return (size_t)R * (2 * st->dm + st->ff + st->HD + st->W) * e + 8 * 256; };
-  auto lay_out = [&](int64_t rows1, int64_t rows2) {
-    const int64_t R1 = st->B * rows1, R2 = st->B * rows2;
-    st->stage1.create(layer_bytes(R1) + other_bytes(R1), em);
-    st->stage2.create(st->L * layer_bytes(R2) + other_bytes(R2) + bwd_bytes(R2), em);
-  };
-  auto both_ways = [&](int64_t R) { return (size_t)st->L * layer_bytes(R) + other_bytes(R) + bwd_bytes(R); };
-  const int64_t span = join ? joined(*st, c2, both_ways(2) - both_ways(1)) : c2;
-  if (span > c2) {
-    try {
-      lay_out(span, span);
-      st->span = span;
-    } catch (const c10::OutOfMemoryError&) {       // (a chunk's own rows may still fit)
-      st->stage1 = st->stage2 = Arena();
-    }
-  }
-  if (st->span == 0) lay_out(c1, c2);
+  const int64_t R1 = st->B * c1, R2 = st->B * c2;
+  st->stage1.create(layer_bytes(R1) + other_bytes(R1), em);
+  st->stage2.create(st->L * layer_bytes(R2) + other_bytes(R2) + bwd_bytes(R2), em);
   PyObject* cap = PyCapsule_New(st.get(), kName, [](PyObject* o) { delete static_cast<Step*>(PyCapsule_GetPointer(o, kName)); });
   if (!cap) throw Raised{};
   st.release();
   return cap;
 }
-
-// (step) -> rows of a sequence to walk at once, where step_new has joined chunks; 0: it has not
-PyObject* step_span(PyObject* const* a) { return PyLong_FromLongLong(step_of(a[0]).span); }
 
 // rows [s0, s1) of every sequence; the kernels read as many entries as the chunk has tokens
 Tensor chunk_of(const Step& st, const Tensor& t, int64_t s0, int64_t s1) {
@@ -725,7 +691,6 @@ PyObject* has_grad_hooks(PyObject* const* a) {
 }  // namespace
 
 PyMethodDef step_methods[] = {SECO_METHOD("step_new", step_new, 2),   SECO_METHOD("step_infer", step_infer, 7),
-                              SECO_METHOD("step_span", step_span, 1),
                               SECO_METHOD("step_zero", step_zero, 1), SECO_METHOD("step_train", step_train, 10),
                               SECO_METHOD("step_grads", step_grads, 1), SECO_METHOD("has_grad_hooks", has_grad_hooks, 1), {nullptr, nullptr, 0, nullptr}};
 

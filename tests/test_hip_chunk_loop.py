@@ -109,33 +109,32 @@ def test_losses_of_a_step_that_visits_every_chunk(dtype, cfg, N, kw):
     (torch.float32, F32_CFG, 5e-4, False, False), (torch.float32, F32_CFG, 5e-4, False, True),
     (torch.bfloat16, BF16_CFG, 6e-2, False, False), (torch.bfloat16, BF16_CFG, 6e-2, False, True),
     (torch.bfloat16, BF16_CFG, 6e-2, True, False)])
-def test_alg1_chunk_by_chunk_where_short_chunks_would_be_joined(dtype, cfg, tol, transposed, keep):
-    """A stage1_chunk_len keeps the chunks as given: the relay over four of them, the last one ragged; without it they are walked
-    at once, with the same gradients."""
+def test_alg1_walks_the_chunks_it_is_given(dtype, cfg, tol, transposed, keep):
+    """The relay over four chunks, the last one ragged.  chunk_len is the caller's bound on the activations alive: a step takes no
+    more memory, and gives the same bits, than one whose stage1_chunk_len repeats it, and less than the sequence as one chunk."""
     N, C = 230, 64
     p64, dec, tok, tgt = _setup(cfg, 36, 2, N, dtype)
     loss_ref, g_ref = om.monolithic_grads(cfg, p64, tok, tgt)
-    for c1 in (C, None):
-        loss, g = dec.step(tok.to(DEV), tgt.to(DEV), C, stage1_chunk_len=c1, keep_attention_outputs=keep, transposed_backward=transposed)
-        assert abs(loss - float(loss_ref)) < (1e-4 if dtype is torch.float32 else 2e-2) * abs(float(loss_ref))
-        _compare(g_ref, g, tol)
+    tok, tgt = tok.to(DEV), tgt.to(DEV)
 
-
-def test_joined_chunks_are_whole_chunks_of_about_equal_length_within_the_bounds():
-    """33 chunks of 100 rows, the last of 40, two sequences: at most 2048 rows in all, so spans of ten chunks, or nine; and nothing is
-    joined where two chunks are more than that."""
-    from paper_2505_16710_amd import binding
-    _, dec, tok, tgt = _setup(F32_CFG, 37, 2, 3240, torch.float32)
-    ext, spans = binding._ext or binding._load_ext(), []
-    names = ["emb", "head", "norm_f"] + [f"l{l}.{n}" for l in range(3) for n in ("norm1", "norm2", "wq", "wk", "wv", "wo", "w1", "w2")]
-    for c, join in ((100, True), (100, False), (513, True), (512, True), (5000, True)):
-        run = ext.step_new((3, 4, 2, 32, 32 ** -0.5, None, 2, 3240, min(c, 3240), min(c, 3240), False, join), [dec.p[n] for n in names])
-        spans.append(ext.step_span(run))
-    assert spans == [900, 0, 0, 1024, 0]
-    one, g_one = dec.step(tok.to(DEV), tgt.to(DEV), 100)
-    each, g_each = dec.step(tok.to(DEV), tgt.to(DEV), 100, stage1_chunk_len=100)
-    assert abs(one - each) < 1e-4 * abs(each)
-    _compare({n: t.double().cpu() for n, t in g_each.items()}, g_one, 5e-4)
+    def step(c, c1):
+        for _ in range(2):                      # (the first one brings what outlives a step)
+            torch.cuda.reset_peak_memory_stats()
+            before = torch.cuda.memory_allocated()
+            loss, g = dec.step(tok, tgt, c, stage1_chunk_len=c1, keep_attention_outputs=keep, transposed_backward=transposed)
+            peak = torch.cuda.max_memory_allocated() - before
+            g = {n: t.double().cpu() for n, t in g.items()}
+            for t in dec.p.values():
+                t.grad = None
+        return loss, g, peak
+    loss, g, peak = step(C, None)
+    assert abs(loss - float(loss_ref)) < (1e-4 if dtype is torch.float32 else 2e-2) * abs(float(loss_ref))
+    _compare(g_ref, g, tol)
+    again, g_again, peak_again = step(C, C)
+    assert loss == again and peak == peak_again
+    for n in g:
+        assert torch.equal(g[n], g_again[n]), n
+    assert peak < step(N, None)[2]
 
 
 @pytest.mark.parametrize("transposed,wide_tail", [(True, False), (False, True), (True, True)])
