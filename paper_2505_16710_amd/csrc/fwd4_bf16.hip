@@ -12,6 +12,11 @@
 // 30720 938 -> 922.  Operand reads are held two pairs of products ahead by scheduling barriers: left to the compiler they
 // came one ahead and the kernel was 1 - 2 % slower; four ahead spill.
 //
+// With its order fixed so, a wavefront is nearly always ready to issue, and of the two on a SIMD the older one then gets
+// all it can use: the two workgroups of a CU end one behind the other.  TURNS raises the priority over the scores and exponentials and
+// lowers it over O, so that they alternate: two halves of the chip's power at a time as well (2048 rows at 15000 470 -> 455 us).
+// turns_pay below says where.
+//
 // (A translation unit of its own, with a scheduler strategy of its own, see build.py: max-ilp; max-memory-clause 1 %
 // slower, iterative-ilp 10 %.)
 #include "mfma_tiles.h"
@@ -28,6 +33,7 @@ constexpr int kTileBytes = BN * kRowBytes;
 constexpr int kKSlots = 3;
 constexpr int kAhead = 2; // operand reads in flight ahead of the products
 
+template <bool TURNS>
 __global__ __launch_bounds__(256, 2) void fwd4_bf16_kernel(AttnParams p, int n_mtiles, int total_items) {
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];   // 5 * kTileBytes: K ring (3 tiles), V ring (2 tiles)
   lds_char* smem = (lds_char*)smem_raw;
@@ -119,8 +125,7 @@ __global__ __launch_bounds__(256, 2) void fwd4_bf16_kernel(AttnParams p, int n_m
     }
   };
 
-  // One tile.  PIPE: `cur` holds S of tile n (slot ks of the K ring) on entry, `nxt` S of tile n+1 on exit;
-  // otherwise S of tile n is computed here first.
+  // One tile: `cur` holds S of tile n (slot ks of the K ring) on entry, `nxt` S of tile n+1 on exit.
   auto tile_body = [&](int n, int ks, int vs, f32x4 (&cur)[4][2], f32x4 (&nxt)[4][2]) {
     const int ks1 = ks + 1 == kKSlots ? 0 : ks + 1;
     if (n + 2 < n_tiles) copy_ring(kbase, n + 2, ks1 + 1 == kKSlots ? 0 : ks1 + 1);
@@ -163,13 +168,14 @@ __global__ __launch_bounds__(256, 2) void fwd4_bf16_kernel(AttnParams p, int n_m
       // whatever the slot holds; the result is never used.)
       float sum[2] = {0.f, 0.f};
       bf16x8 va[kAhead];
+      if constexpr (TURNS) __builtin_amdgcn_s_setprio(1);
       {
         lds_char* kt1 = smem + ks1 * kTileBytes;
 #pragma unroll
         for (int rb = 0; rb < 4; ++rb) nxt[rb][0] = nxt[rb][1] = f32x4{0.f, 0.f, 0.f, 0.f};
         // written interleaved: a pair of MFMAs of the next tile's chains, then two exponentials of this tile; operands are
-        // read four pairs ahead
-        bf16x8 ka[4];
+        // read kAhead pairs ahead
+        bf16x8 ka[kAhead];
 #pragma unroll
         for (int i = 0; i < kAhead; ++i) ka[i] = lds_row16(kt1, 16 * (i & 3), i >> 2, lane);
         __builtin_amdgcn_sched_barrier(0);
@@ -208,6 +214,7 @@ __global__ __launch_bounds__(256, 2) void fwd4_bf16_kernel(AttnParams p, int n_m
       }
       l_run[0] += sum[0];
       l_run[1] += sum[1];
+      if constexpr (TURNS) __builtin_amdgcn_s_setprio(0);
       bf16x8 pb[2];
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
@@ -262,17 +269,36 @@ __global__ __launch_bounds__(256, 2) void fwd4_bf16_kernel(AttnParams p, int n_m
                static_cast<__bf16*>(p.o_out) + b * p.os[0] + h * p.os[1], p.os[2], m0, p.C, smem + wave * 8192);
 }
 
+// Whether the workgroups of a CU take turns.  If not, the older one ends first, which is what a launch wants only where its next
+// tile then starts at a better time; else its last tiles start late or run alone.  600 calls of 1 - 8 rounds (two workgroups per CU) measured;
+// 1.03 times as fast by this rule, us without -> with turns:
+//   5125 rows at 5125 of 16/8 heads 359 -> 315    2372 at 1221 of 32/8 112 -> 98     7428 at 0 of 16/8 220 -> 202
+//   two of 4126 at 0 of 8/8 107 -> 98             15863 at 0 of 32/8 1671 -> 1641
+// Without where long and short tiles meet, up to 1.6 rounds and around three: a causal chunk with little before it (2556 at 0 of 32/8 61 ->
+// 63, 12412 at 0 of 8/8 291 -> 305, 2476 at 281 69 -> 71, 5229 at 0 201 -> 206; but 2842 at 848 118 -> 107), unless an XCD has two KV
+// heads one behind the other; and with tiles alike, a little over two rounds (4551 at 11084 948 -> 990, two of 8215 at 6682 of 8/8 654 ->
+// 694; at 2.56 rounds, 5159 at 6104, 695 -> 667).
+inline bool turns_pay(const AttnParams& p, int total) {
+  const float rounds = total / (2.f * device_cus()), before = (float)p.q_start / p.C;
+  if (p.B * p.Hkv <= 8 && before < 0.8f * (1.6f - rounds)) return false;
+  if (p.B * p.Hkv <= 8 && before < 0.1f && rounds >= 2.4f && rounds < 3.25f) return false;
+  return !(before >= 0.15f && rounds >= 2.02f && rounds < 2.55f);
+}
+
+template <bool TURNS>
+int launch(const AttnParams& p, int n_mtiles, int total, hipStream_t s) {
+  constexpr int smem = 5 * kTileBytes;
+  static std::atomic<uint64_t> ready{0};
+  if (!allow_lds(ready, reinterpret_cast<const void*>(fwd4_bf16_kernel<TURNS>), smem)) return SECO_ERR_LAUNCH;
+  ProfScope prof(kKernelFwd, s);
+  hipLaunchKernelGGL(fwd4_bf16_kernel<TURNS>, dim3(xcd_grid(total, p.B * p.Hkv)), dim3(256), smem, s, p, n_mtiles, total);
+  return launch_status();
+}
+
 }  // namespace
 
 int launch_fwd4_bf16(const AttnParams& p, int n_mtiles, int total, hipStream_t s) {
-  constexpr int smem = 5 * kTileBytes;
-  static std::atomic<uint64_t> ready{0};
-  if (!allow_lds(ready, reinterpret_cast<const void*>(fwd4_bf16_kernel), smem)) return SECO_ERR_LAUNCH;
-  {
-    ProfScope prof(kKernelFwd, s);
-    hipLaunchKernelGGL(fwd4_bf16_kernel, dim3(xcd_grid(total, p.B * p.Hkv)), dim3(256), smem, s, p, n_mtiles, total);
-  }
-  return launch_status();
+  return turns_pay(p, total) ? launch<true>(p, n_mtiles, total, s) : launch<false>(p, n_mtiles, total, s);
 }
 
 }  // namespace seco

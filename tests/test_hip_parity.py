@@ -421,6 +421,23 @@ def test_bf16_row_tiles_for_two_workgroups_on_most_cus(q_start):
     test_bf16_row_tiles_beyond_one_round_divided(1, 16, 8, 3300, q_start)
 
 
+def test_bf16_forward_in_one_call_and_in_chunks_bit_for_bit():
+    """Four wavefronts, two workgroups to a CU: 4096 rows (1024 tiles), and as two chunks (512 each), of which the first has nothing
+    before it and its workgroups take no turns.  A row's sums do not depend on that; two heads in fp32 on the device."""
+    Hq, Hkv, N, s = 32, 8, 4096, 1 / np.sqrt(128)
+    g = torch.Generator(device=DEV).manual_seed(92)
+    q, k, v = (torch.randn(1, h, N, 128, device=DEV, generator=g).to(torch.bfloat16) for h in (Hq, Hkv, Hkv))
+    o, lse = seco.seco_chunk_attn_fwd(q, k, v, 0, s)
+    for r in (slice(0, 2048), slice(2048, 4096)):
+        oc, lc = seco.seco_chunk_attn_fwd(q[:, :, r], k, v, r.start, s)
+        assert torch.equal(oc, o[:, :, r]) and torch.equal(lc, lse[:, :, r]), r
+    hidden = torch.arange(N, device=DEV)[None, :] > torch.arange(N, device=DEV)[:, None]
+    for h in (0, 31):
+        z = (q[0, h].float() @ k[0, h * Hkv // Hq].float().t() * s).masked_fill(hidden, float("-inf"))
+        assert max_rel(to_host(o[0, h]), to_host(z.softmax(-1) @ v[0, h * Hkv // Hq].float())) <= TOL["bf16"]["o"], h
+        assert max_rel(to_host(lse[0, h]), to_host(z.logsumexp(-1))) <= TOL["bf16"]["lse"], h
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,C,q_start", [
     (1, 11, 1, 3200, 10),      # 275 row tiles of one unit on eight XCDs, 26 column tiles
     (1, 18, 2, 2000, 5),       # 288 of two on four each
