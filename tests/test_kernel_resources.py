@@ -12,9 +12,8 @@ import pytest
 
 from paper_2505_16710_amd import build as B
 
-KERNEL_FILES = ["fwd_bf16.hip", "fwd4_bf16.hip", "fwd4_split_bf16.hip", "fwd8_shares_bf16.hip", "bwd_dq_bf16.hip", "bwd_dkdv_bf16.hip", "bwd_fused_bf16.hip",
-                "fwd_small_bf16.hip", "gemm_bf16.hip", "fwd_f32.hip",
-                "kernels_f32.hip"]
+# (the others hold host code and kernels that move or reduce rows)
+KERNEL_FILES = [s for s in B.SOURCES if s.endswith(".hip") and s not in ("seco_api.hip", "elementwise.hip", "decoder.hip")]
 # blocks of 16 of the head_dim from which on one wavefront per SIMD is taken
 ONE_WAVE = {"fwd_f32_kernel": 16, "bwd_f32_kernel": 8}
 
@@ -79,6 +78,6 @@ def test_matrix_core_kernels_do_not_spill():
             assert sspill <= 24, (src, name, sspill)
             spilling.add(src if sspill else None)
             assert occ is not None and occ >= _least_waves(name), (src, name, occ)
-    assert seen >= 56                    # 5 forward, 6 dQ, 1 dK/dV, 2 one-launch, 30 product, 12 fp32 instantiations at least
+    assert seen >= 60                    # 6 forward, 6 dQ, 4 dK/dV, 2 one-launch, 30 product, 12 fp32 instantiations at least
     for src in sorted(x for x in spilling if x):
         assert _lane_moves_in_loops(src) == [], src
