@@ -13,6 +13,7 @@
 #include "bwd_plan.h"
 #include "seco.h"
 #include "stub_launch.h"
+#include "xcd_map.h"
 
 #define CHECK(cond)                                                        \
   do {                                                                     \
@@ -255,6 +256,23 @@ int main() {
     CHECK(rope_rotate(&d, 0, FAKE, FAKE, 0, 10000.f, 0, nullptr) == SECO_ERR_RANGE);
     CHECK(kvgrad_readout(&d, FAKEF, FAKEF, FAKE, FAKE, INFINITY, nullptr) == SECO_ERR_RANGE);
   }
+  // ---- work items and workgroups: every item once, those of a unit on its XCDs ----
+  for (int units : {1, 2, 3, 4, 5, 8, 16})
+    for (int run : {1, 7, 31, 64, 65, 128, 130, 256, 257, 519}) {
+      const int total = run * units, first = total / 3;
+      const bool dealt = seco::xcds_share_units(total, units);
+      CHECK(dealt == (total > 256 && (units == 1 || units == 2 || units == 4)));
+      std::vector<int> taken(total, 0), taken2(total, 0);
+      for (int block = 0; block < seco::xcd_grid(total, units); ++block) {
+        const int item = seco::xcd_item(block, total, units);
+        CHECK(item < total);
+        if (item >= 0) ++taken[item];
+        if (item >= 0 && dealt) CHECK((block & 7) / (8 / units) == item / run);
+      }
+      for (int block = 0; block < seco::xcd_grid(first) + seco::xcd_grid(total - first); ++block)
+        if (const int item = seco::shares_item(block, first, total); item >= 0) ++taken2[item];
+      CHECK(std::count(taken.begin(), taken.end(), 1) == total && std::count(taken2.begin(), taken2.end(), 1) == total);
+    }
   // ---- where an output lies over an input ----
   {
     static char mem[1 << 20];

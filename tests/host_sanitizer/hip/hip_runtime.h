@@ -9,6 +9,7 @@
 #define __device__
 #define __host__
 #define __global__
+#define __forceinline__ inline
 #define __align__(n) __attribute__((aligned(n)))
 #define HIP_SYMBOL(x) (&(x))
 
