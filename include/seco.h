@@ -392,9 +392,11 @@ size_t seco_workspace_bytes_preferred(const seco_desc* desc, int op);
  *       of workgroups would be at most half full
  *   [3] workgroups per such tile, at least (1: none); [2] * [3] * batch * n_kv_heads never exceeds the device's
  *       compute units
- * Four things they do not cover: a forward of at most 32 query rows per KV head (chunk_len * n_q_heads / n_kv_heads)
- * divides the cache by a rule of its own; a forward or dQ pass with between one and two rounds of row tiles divides those
- * beyond the first; a backward that runs in one launch (SECO_PROFILE_BWD) chooses its own number
+ * Four things they do not cover: a forward of at most 32 query rows per KV head (chunk_len * n_q_heads / n_kv_heads),
+ * or of more while row tiles of 32 of them are at most one for each compute unit and a workgroup has at most 1536 cache
+ * rows to go through (2048 with 64 query rows or fewer), takes such tiles and divides the cache by a rule of its own, so that [0] and [1] are
+ * not its; a forward or dQ pass with between one and two rounds of row tiles divides those beyond the first (the forward not
+ * from 1.6 rounds on behind at least 2400 cache rows, twice the chunk, with at most eight (batch, KV head) pairs); a backward that runs in one launch (SECO_PROFILE_BWD) chooses its own number
  * of shares for both passes; a dK/dV pass whose tiles all fit one round, or whose estimated time falls, shares tiles
  * out further, by query rows.
  * Returns SECO_OK, or the status of an invalid desc; SECO_ERR_DTYPE for fp32 (its kernels have one shape).

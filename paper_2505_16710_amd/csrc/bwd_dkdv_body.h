@@ -384,7 +384,7 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
       float d = 0.f;
 #pragma unroll
       for (int j = 0; j < 8; ++j) d = __builtin_fmaf((float)w.o[i][j], (float)w.d[i][j], d);
-      d = row16_sum(d);   // (in the order of the dQ kernel, whose lanes hold every second chunk: the same bits)
+      d = row16_sum(d);   // (in the order of the dQ kernel, whose lanes hold every fourth chunk: the same bits)
       const int lr = 8 * wave + 4 * i + (lane >> 4);
       if ((lane & 15) == 0) {
         stat[lr] = x.r0 + lr < p.C ? -w.lse[i] / p.scale : -INFINITY;

@@ -380,7 +380,7 @@ int launch_fwd4_bf16(const AttnParams& p, int n_mtiles, int total, hipStream_t s
 int launch_fwd8_split_bf16(const AttnParams& p, int n_mtiles, int total, hipStream_t s);
 // ... and its variant that divides the row tiles beyond the first round, with the merge behind it
 int launch_fwd8_shares_bf16(const AttnParams& p, int n_mtiles, hipStream_t s);
-// at most 32 query rows per KV head; max_splits: how many partial results the workspace holds (1: there is none)
+// few query rows per KV head (fwd_small_pays); max_splits: how many partial results the workspace holds (1: there is none)
 int launch_fwd_small_bf16(AttnParams p, int max_splits, hipStream_t s);
 bool fwd_small_pays(const AttnParams& p, int max_splits);   // whether that kernel is the faster one (rows, cache, divisions at hand)
 // dq_runs: NULL for all visible cache rows with weight 1; else runs of cache rows (ascending, disjoint), each with
