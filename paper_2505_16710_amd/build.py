@@ -28,6 +28,7 @@ SOURCES = [
     "fwd8_shares_bf16.hip",
     "fwd_small_bf16.hip",
     "bwd_dq_bf16.hip",
+    "bwd_dq32_bf16.hip",
     "bwd_dkdv_bf16.hip",
     "bwd_dkdv32_bf16.hip",
     "bwd_fused_bf16.hip",
@@ -43,8 +44,9 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-I", INCLUDE, "
 # Machine scheduler strategy of the compiler, per source file (measured on the benchmark shapes, every strategy
 # tried on every matrix-core kernel): the 8-wavefront forward is 3 % faster with the iterative ILP scheduler than with
 # memory (LDS) instructions kept in clauses, the 4-wavefront forward, the dQ and the dK/dV kernels, whose order is fixed
-# step by step in the source, 1 - 2 % with the plain ILP one (dK/dV with 32x32x16 products 3 - 7 % slower); the launch that holds both passes is slower with either.
-SCHED = {"fwd4_bf16.hip": "max-ilp", "bwd_dq_bf16.hip": "max-ilp", "bwd_dkdv_bf16.hip": "max-ilp", "fwd_bf16.hip": "iterative-ilp", "fwd4_split_bf16.hip": "iterative-ilp",
+# step by step in the source, 1 - 2 % with the plain ILP one (dK/dV with 32x32x16 products 3 - 7 % slower; dQ with those 3 %
+# faster with the iterative one); the launch that holds both passes is slower with either.
+SCHED = {"fwd4_bf16.hip": "max-ilp", "bwd_dq_bf16.hip": "max-ilp", "bwd_dkdv_bf16.hip": "max-ilp", "bwd_dq32_bf16.hip": "iterative-ilp", "fwd_bf16.hip": "iterative-ilp", "fwd4_split_bf16.hip": "iterative-ilp",
          "fwd8_shares_bf16.hip": "iterative-ilp"}
 SCHED_DEFAULT = "max-memory-clause"
 # ... and up to half a per cent when the scheduler does not cluster memory operations

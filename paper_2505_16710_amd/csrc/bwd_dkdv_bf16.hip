@@ -32,7 +32,7 @@ int launch_dkdv_bf16(const AttnParams& p, const SegTable& seg, hipStream_t s) {
   const bool dq = p.pending && p.pending->dq;
   if (dq) p.pending->dq = false;
   const SegTable* runs = dq && p.pending->sparse ? &p.pending->runs : nullptr;
-  if (seg.tile_begin[seg.n] == 0) return dq ? launch_dq_bf16_now(p, runs, s) : SECO_OK;
+  if (seg.tile_begin[seg.n] == 0) return dq ? launch_dq_bf16_now(p, runs, true, s) : SECO_OK;
   // (where dQ visits selected columns or lies over O, the sums of gK / gV are divided as they would be otherwise: the same bits)
   const BwdPlan plan = plan_bwd<Cfg>(p, seg, dq);
   if (dq && plan.dq_splits > 0 && !dq_over_inputs(p, 2)) {
@@ -40,7 +40,7 @@ int launch_dkdv_bf16(const AttnParams& p, const SegTable& seg, hipStream_t s) {
     pf.n_splits = runs ? sparse_shares(p, *runs, plan.dq_splits) : plan.dq_splits;
     return launch_bwd_fused_bf16(pf, seg, plan.ts, plan.kv_first, runs, s);
   }
-  int rc = dq ? launch_dq_bf16_now(p, runs, s) : SECO_OK;
+  int rc = dq ? launch_dq_bf16_now(p, runs, plan.dq_splits == 0, s) : SECO_OK;
   RowRuns none;
   none.n = 0;
   if (rc) return rc;

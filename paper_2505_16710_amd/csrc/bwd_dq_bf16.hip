@@ -1,32 +1,15 @@
 // dQ of one chunk, bf16: the launch shapes of the kernel in bwd_dq_body.h.
 #include <algorithm>
 
-#include "bwd_dq_body.h"
+#include "bwd_dq_kernel.h"
 
 namespace seco {
 namespace {
 
-template <int KH, int SPLIT, bool SPARSE>
-__global__ __launch_bounds__(256 * KH, 2) void dq_bf16_kernel(AttnParams p, SegTable seg, int n_mtiles, int total_items) {
-  extern __shared__ __attribute__((aligned(16))) char smem_raw[];
-  const int item = SPLIT == kShares ? shares_item(blockIdx.x, p.B * p.Hkv * p.rows_whole, total_items)
-                                     : xcd_item(blockIdx.x, total_items, SPLIT == kDivided ? 8 : p.B * p.Hkv);
-  if (item < 0) return;
-  dq_bf16_body<KH, SPLIT, SPARSE>(p, seg, n_mtiles, item, (lds_char*)smem_raw);
-}
-
-template <int KH, int SPLIT, bool SPARSE>
-int launch_kh(const AttnParams& p, const SegTable& seg, int n_mtiles, int total, hipStream_t s) {
-  constexpr int smem = 4 * BNW * KH * kRowBytes;
-  auto kern = dq_bf16_kernel<KH, SPLIT, SPARSE>;
-  static std::atomic<uint64_t> ready{0};
-  if (!allow_lds(ready, reinterpret_cast<const void*>(kern), smem)) return SECO_ERR_LAUNCH;
-  {
-    ProfScope prof(kKernelDq, s);
-    const int units = SPLIT == kWholeTiles ? p.B * p.Hkv : 8, first = SPLIT == kShares ? p.B * p.Hkv * p.rows_whole : 0;
-    hipLaunchKernelGGL(kern, dim3(xcd_grid(first, units) + xcd_grid(total - first, units)), dim3(256 * KH), smem, s, p, seg, n_mtiles, total);
-  }
-  return launch_status();
+template <int KH, int SPLIT>
+int launch(const AttnParams& p, const SegTable& seg, bool sparse, int n_mtiles, int total, hipStream_t s) {
+  return sparse ? launch_dq_kernel<KH, SPLIT, true, DqProducts16>(p, seg, n_mtiles, total, s)
+                : launch_dq_kernel<KH, SPLIT, false, DqProducts16>(p, seg, n_mtiles, total, s);
 }
 
 // Row tiles that were divided (kShares): dQ = scale * (sum of the shares, in order).  A thread: four elements of a row.
@@ -52,14 +35,14 @@ __global__ __launch_bounds__(256) void dq_shares_merge_kernel(AttnParams p, int 
 // runs == nullptr: all visible cache rows, weight 1.  The pass is left for the dK/dV launcher, which may be able to run
 // both at once.
 int launch_dq_bf16(const AttnParams& p, const SegTable* runs, hipStream_t s) {
-  if (!p.pending) return launch_dq_bf16_now(p, runs, s);
+  if (!p.pending) return launch_dq_bf16_now(p, runs, true, s);
   p.pending->dq = true;
   p.pending->sparse = runs != nullptr;
   if (runs) p.pending->runs = *runs;
   return SECO_OK;
 }
 
-int launch_dq_bf16_now(const AttnParams& p, const SegTable* runs, hipStream_t s) {
+int launch_dq_bf16_now(const AttnParams& p, const SegTable* runs, bool alone, hipStream_t s) {
   SegTable none = {};
   const SegTable& seg = runs ? *runs : none;
   // (over selected columns: as many shares as those are worth, not the whole cache)
@@ -69,8 +52,7 @@ int launch_dq_bf16_now(const AttnParams& p, const SegTable* runs, hipStream_t s)
     AttnParams ps = p;
     ps.n_splits = n_splits;
     const int total = plan.items * n_splits;
-    int rc = runs ? launch_kh<2, kDivided, true>(ps, seg, plan.n_mtiles, total, s)
-                  : launch_kh<2, kDivided, false>(ps, seg, plan.n_mtiles, total, s);
+    int rc = launch<2, kDivided>(ps, seg, runs != nullptr, plan.n_mtiles, total, s);
     return rc ? rc : launch_dq_merge(ps, s);
   }
   const int n_mtiles = (p.C + BM - 1) / BM;
@@ -84,16 +66,15 @@ int launch_dq_bf16_now(const AttnParams& p, const SegTable* runs, hipStream_t s)
       ps.n_splits = rs.shares;
       ps.part = p.tail_part;
       const int n_cut = plan.n_mtiles - rs.whole;
-      const int rc = launch_kh<2, kShares, false>(ps, seg, plan.n_mtiles, p.B * p.Hkv * (rs.whole + n_cut * rs.shares), s);
+      const int rc = launch_dq_kernel<2, kShares, false, DqProducts16>(ps, seg, plan.n_mtiles, p.B * p.Hkv * (rs.whole + n_cut * rs.shares), s);
       if (rc) return rc;
       ProfScope prof(kKernelMerge, s);
       hipLaunchKernelGGL(dq_shares_merge_kernel, dim3(p.B * p.Hkv * n_cut * 16), dim3(256), 0, s, ps, n_cut);
       return launch_status();
     }
   }
-  if (total < 2 * device_cus())
-    return runs ? launch_kh<2, kWholeTiles, true>(p, seg, n_mtiles, total, s) : launch_kh<2, kWholeTiles, false>(p, seg, n_mtiles, total, s);
-  return runs ? launch_kh<1, kWholeTiles, true>(p, seg, n_mtiles, total, s) : launch_kh<1, kWholeTiles, false>(p, seg, n_mtiles, total, s);
+  if (total >= 2 * device_cus()) return launch<1, kWholeTiles>(p, seg, runs != nullptr, n_mtiles, total, s);
+  return alone && dq_leaves_cus(total, (int64_t)p.B * p.Hq * p.C) ? launch_dq32_bf16(p, runs, n_mtiles, total, s) : launch<2, kWholeTiles>(p, seg, runs != nullptr, n_mtiles, total, s);
 }
 
 }  // namespace seco

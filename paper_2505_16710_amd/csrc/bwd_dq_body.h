@@ -7,7 +7,7 @@
 // swizzled, double-buffered LDS, copied global -> LDS directly one tile ahead; with KH = 2 (8 wavefronts, 128-row tiles) the two wavefronts
 // of a row block take one 64-row half of every tile each and their partial dQ are added
 // through LDS at the end.  Scores are again computed transposed (S^T = K Q^T, dP^T = V dO^T)
-// so that LSE and delta are two values per lane and dS^T feeds dQ^T += K^T dS^T from registers;
+// so that LSE and delta are one or two values per lane and dS^T feeds dQ^T += K^T dS^T from registers;
 // K^T comes from the same K tile through the LDS transpose read.
 //
 // Bound: power on long calls, as the forward, and products of 16x16x32 for the same reason (half the accumulator traffic of
@@ -40,18 +40,108 @@ constexpr int BM = 128;
 constexpr int BNW = 64;   // cache rows per wavefront and tile
 constexpr int kAhead = 2; // operand reads in flight ahead of the products
 
+// The products of a wavefront, in either shape of the matrix instructions: what a lane holds of its 32 query rows.
+// 16x16x32: two rows, 16 apart, and of each of their fragments every fourth chunk of head_dim.
+struct DqProducts16 {
+  static constexpr bool k16 = true;
+  static constexpr int kRows = 2;
+  using Acc = f32x4[8][2];
+  int r_off[4], t_off[8];                      // lane-dependent parts of the LDS operand addresses, constant for the whole kernel
+  __device__ __forceinline__ DqProducts16(int lane, int base) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t) r_off[t] = row16_lane_off(t, lane) + base;
+#pragma unroll
+    for (int db = 0; db < 8; ++db) t_off[db] = tr16_lane_off(db, lane) + base;
+  }
+  static __device__ __forceinline__ void frags(bf16x8 (&f)[8], const bf16x8 (&x)[8], lds_char* own, int lane) { rows16_to_frags(f, x, own, lane); }
+  static __device__ __forceinline__ void clear(Acc& acc) {
+#pragma unroll
+    for (int db = 0; db < 8; ++db) acc[db][0] = acc[db][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  // x y summed over head_dim, for each of the lane's rows (by chunk of 8 elements, then pairwise, as OWN in bwd_dkdv_body.h adds them)
+  static __device__ __forceinline__ float dot(int qb, const bf16x8 (&x)[8], const bf16x8 (&y)[8]) {
+    float part[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      part[t] = 0.f;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) part[t] = __builtin_fmaf((float)x[4 * qb + t][i], (float)y[4 * qb + t][i], part[t]);
+    }
+    float d = (part[0] + part[2]) + (part[1] + part[3]);
+    d += __shfl_xor(d, 32);
+    return d + __shfl_xor(d, 16);
+  }
+  static __device__ __forceinline__ f32x4 piece(const Acc& acc, int i) { return acc[i >> 1][i & 1]; }
+  static __device__ __forceinline__ void add(Acc& acc, int i, f32x4 x) { acc[i >> 1][i & 1] += x; }
+  static __device__ __forceinline__ void store_part(const Acc& acc, float* base, int n_rows, lds_char* own) { store_part16(acc, base, n_rows, own); }
+  static __device__ __forceinline__ void store(const Acc& acc, float scale, __bf16* base, int64_t stride, int row0, int n_rows, lds_char* own8k) {
+    store_rows16([&](int db, int qb, int i) { return acc[db][qb][i] * scale; }, base, stride, row0, n_rows, own8k);
+  }
+};
+// 32x32x16: one row, every second chunk.  For launches of whole row tiles that leave CUs without work (dq_leaves_cus): with the clock
+// as high as it goes what counts is the room for vector instructions (see Products32 in bwd_dkdv_body.h).
+struct DqProducts32 {
+  static constexpr bool k16 = false;
+  static constexpr int kRows = 1;
+  using Acc = f32x16[4];
+  int r_off[8];
+  TrOff t_off[4];
+  __device__ __forceinline__ DqProducts32(int lane, int base) {
+#pragma unroll
+    for (int t = 0; t < 8; ++t) r_off[t] = row8_lane_off(lane & 31, 2 * t + (lane >> 5)) + base;
+#pragma unroll
+    for (int db = 0; db < 4; ++db) {
+      t_off[db] = tr8_lane_off(db, lane);
+      t_off[db].lo += base;
+      t_off[db].hi += base;
+    }
+  }
+  static __device__ __forceinline__ void frags(bf16x8 (&f)[8], const bf16x8 (&x)[8], lds_char* own, int lane) { rows32_to_frags(f, x, own, lane); }
+  static __device__ __forceinline__ void clear(Acc& acc) {
+#pragma unroll
+    for (int db = 0; db < 4; ++db)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[db][r] = 0.f;
+  }
+  static __device__ __forceinline__ float dot(int, const bf16x8 (&x)[8], const bf16x8 (&y)[8]) {
+    float part[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      part[t] = 0.f;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) part[t] = __builtin_fmaf((float)x[t][i], (float)y[t][i], part[t]);
+    }
+    const float d = ((part[0] + part[4]) + (part[2] + part[6])) + ((part[1] + part[5]) + (part[3] + part[7]));
+    return d + __shfl_xor(d, 32);
+  }
+  static __device__ __forceinline__ f32x4 piece(const Acc& acc, int i) {
+    const f32x16& x = acc[i >> 2];
+    const int r = 4 * (i & 3);
+    return f32x4{x[r], x[r + 1], x[r + 2], x[r + 3]};
+  }
+  static __device__ __forceinline__ void add(Acc& acc, int i, f32x4 x) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) acc[i >> 2][4 * (i & 3) + r] += x[r];
+  }
+  static __device__ __forceinline__ void store(const Acc& acc, float scale, __bf16* base, int64_t stride, int row0, int n_rows, lds_char* own8k) {
+    store_rows32([&](int db, int r) { return acc[db][r] * scale; }, base, stride, row0, n_rows, own8k);
+  }
+};
+
 // seg (SPARSE only): runs of cache rows in ascending order, each with a positive weight
 // smem: 4 * kTileBytes, [buf][K|V]
 // FUSED: inside the kernel that holds dK/dV too, where scalar registers are short (opaque)
-template <int KH, int SPLIT, bool SPARSE, bool FUSED = false>
+template <int KH, int SPLIT, bool SPARSE, class Products, bool FUSED = false>
 __device__ __forceinline__ void dq_bf16_body(const AttnParams& p, const SegTable& seg, int n_mtiles, int item, lds_char* smem) {
   static_assert(!SPLIT || KH == 2, "the split variant uses the 8-wavefront shape");
+  static_assert(Products::k16 || (KH == 2 && !SPLIT), "32x32x16: whole row tiles of 8 wavefronts");
   constexpr int BN = BNW * KH;
   constexpr int kTileBytes = BN * kRowBytes;
   // (the wavefront index through readfirstlane: the compiler then knows that it, and every tile coordinate and branch
   // condition derived from it, is uniform over the wavefront and keeps them in scalar registers)
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int l16 = lane & 15, g = lane >> 4, pg = pi4(g);
+  constexpr int kRows = Products::kRows, kLaneRows = 32 / kRows;     // query rows of a lane; lanes of a wavefront with rows of their own
+  const int g = lane / kLaneRows, pg = Products::k16 ? pi4(g) : g;
   const int rb = wave & 3, kh = (KH == 1 && !SPARSE) ? 0 : wave >> 2;
   int b, kvh, h, mt, m0, sp = 0;              // m0: first chunk-local row of this wavefront
   int n_sp = 1, slot = 0;                     // shares of this row tile; kShares: where this one's sums go
@@ -99,7 +189,7 @@ __device__ __forceinline__ void dq_bf16_body(const AttnParams& p, const SegTable
   }
 
   const int kv_len = p.q_start + p.C;
-  const int row = m0 + l16;                    // this lane's first row; its second is 16 on
+  const int row = m0 + lane % kLaneRows;       // this lane's first row; a second one is 16 on
   const int qpos = p.q_start + row;
   // Q, dO, O, the row's LSE and (below) the first K/V tile are all requested before the first of them is waited for:
   // a workgroup starts with one memory round trip
@@ -111,7 +201,9 @@ __device__ __forceinline__ void dq_bf16_body(const AttnParams& p, const SegTable
     load_rows32(orow, static_cast<const __bf16*>(p.o) + ob, p.os[2], m0, p.C - 1, lane);
   }
   const float* lse_h = p.lse + ((int64_t)b * p.Hq + h) * p.C;
-  const float lse[2] = {lse_h[min(row, p.C - 1)], lse_h[min(row + 16, p.C - 1)]};
+  float lse[kRows];
+#pragma unroll
+  for (int qb = 0; qb < kRows; ++qb) lse[qb] = lse_h[min(row + 16 * qb, p.C - 1)];
   const float c = p.scale * kLog2e;
 
   const __bf16* kbase = static_cast<const __bf16*>(p.k) + b * p.kvs[0] + kvh * p.kvs[1];
@@ -188,19 +280,11 @@ __device__ __forceinline__ void dq_bf16_body(const AttnParams& p, const SegTable
     }
   };
 
-  // lane-dependent parts of the LDS operand addresses (constant for the whole kernel)
   // (dense variants: the wavefront's half of the tile, for KH = 2, is part of the per-lane offsets, so that a tile's
   // base is a compile-time constant in the unrolled loop below)
-  int r_off[4], t_off[8];
-  const int half_off = SPARSE ? 0 : kh * BNW * kRowBytes;
-#pragma unroll
-  for (int t = 0; t < 4; ++t) r_off[t] = row16_lane_off(t, lane) + half_off;
-#pragma unroll
-  for (int db = 0; db < 8; ++db) t_off[db] = tr16_lane_off(db, lane) + half_off;
-
-  f32x4 dq[8][2];
-#pragma unroll
-  for (int db = 0; db < 8; ++db) dq[db][0] = dq[db][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const Products pr(lane, SPARSE ? 0 : kh * BNW * kRowBytes);
+  typename Products::Acc dq;
+  Products::clear(dq);
 
   Cur cur{0, n_begin * BN, 0};
   if constexpr (SPARSE) {
@@ -211,26 +295,16 @@ __device__ __forceinline__ void dq_bf16_body(const AttnParams& p, const SegTable
   if (n_begin < n_end) copy_tile(cur.col, 0);
   bf16x8 qf[8], dof[8], of[8];
   lds_char* own = smem + 2 * kTileBytes + wave * 8192;      // of the second tile buffer, which is empty until the loop
-  rows16_to_frags(qf, qr, own, lane);
-  rows16_to_frags(dof, dor, own, lane);
-  rows16_to_frags(of, orow, own, lane);
-  // delta = rowsum(dO * O), from the dO fragments and the matching O fragments: a lane holds a quarter of each of its two
-  // rows' head_dim (the rest is in lane ^ 16, ^ 32, ^ 48).  It is also written to the workspace for the dK/dV kernel that
-  // follows on the same stream, negated, together with -LSE / s (the log-sum-exp in units of the unscaled dot product): the
-  // two values that kernel starts its MFMA chains from.
-  float lse_c[2], delta[2];
+  Products::frags(qf, qr, own, lane);
+  Products::frags(dof, dor, own, lane);
+  Products::frags(of, orow, own, lane);
+  // delta = rowsum(dO * O), from the dO fragments and the matching O fragments.  It is also written to the workspace for the
+  // dK/dV kernel that follows on the same stream, negated, together with -LSE / s (the log-sum-exp in units of the unscaled dot
+  // product): the two values that kernel starts its MFMA chains from.
+  float lse_c[kRows], delta[kRows];
 #pragma unroll
-  for (int qb = 0; qb < 2; ++qb) {
-    float part[4];                     // by chunk of 8 elements, then pairwise (as OWN in bwd_dkdv_body.h adds them)
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      part[t] = 0.f;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) part[t] = __builtin_fmaf((float)of[4 * qb + t][i], (float)dof[4 * qb + t][i], part[t]);
-    }
-    float d = (part[0] + part[2]) + (part[1] + part[3]);
-    d += __shfl_xor(d, 32);
-    d += __shfl_xor(d, 16);
+  for (int qb = 0; qb < kRows; ++qb) {
+    const float d = Products::dot(qb, of, dof);
     delta[qb] = d;
     lse_c[qb] = lse[qb] * kLog2e;
     if (kh == 0 && sp == 0 && g == 0 && row + 16 * qb < p.C) {
@@ -268,29 +342,28 @@ __device__ __forceinline__ void dq_bf16_body(const AttnParams& p, const SegTable
     lds_char* slot = smem + rb * (17 * 1024);
     if (kh == 1) {
 #pragma unroll
-      for (int i = 0; i < 16; ++i) *reinterpret_cast<SECO_LDS f32x4*>(slot + (i * 64 + lane) * 16) = dq[i >> 1][i & 1];
+      for (int i = 0; i < 16; ++i) *reinterpret_cast<SECO_LDS f32x4*>(slot + (i * 64 + lane) * 16) = Products::piece(dq, i);
     }
     __syncthreads();
     if (kh == 1 || m0 >= p.C) return;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) dq[i >> 1][i & 1] += *reinterpret_cast<SECO_LDS f32x4*>(slot + (i * 64 + lane) * 16);
+    for (int i = 0; i < 16; ++i) Products::add(dq, i, *reinterpret_cast<SECO_LDS f32x4*>(slot + (i * 64 + lane) * 16));
   }
 
   if constexpr (SPLIT == kShares) {
     if (n_sp > 1) {                            // all 32 rows: the merge takes those that exist
-      store_part16(dq, p.part + ((int64_t)slot * BM + rb * 32) * kHeadDim, 32, smem + rb * (17 * 1024));
+      Products::store_part(dq, p.part + ((int64_t)slot * BM + rb * 32) * kHeadDim, 32, smem + rb * (17 * 1024));
       return;
     }
   }
   if constexpr (SPLIT == kDivided) {
     float* po = p.part + ((int64_t)sp * p.B * p.Hq * p.C + ((int64_t)b * p.Hq + h) * p.C + m0) * kHeadDim;
-    store_part16(dq, po, p.C - m0, smem + rb * (17 * 1024));
+    Products::store_part(dq, po, p.C - m0, smem + rb * (17 * 1024));
     return;
   }
 
-  store_rows16([&](int db, int qb, int i) { return dq[db][qb][i] * p.scale; },
-               static_cast<__bf16*>(p.d_q) + b * p.qs[0] + h * p.qs[1], p.qs[2], m0, p.C,
-               KH == 2 ? smem + rb * (17 * 1024) : smem + wave * 8192);
+  Products::store(dq, p.scale, static_cast<__bf16*>(p.d_q) + b * p.qs[0] + h * p.qs[1], p.qs[2], m0, p.C,
+                  KH == 2 ? smem + rb * (17 * 1024) : smem + wave * 8192);
 }
 
 }  // namespace

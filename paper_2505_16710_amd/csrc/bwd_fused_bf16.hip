@@ -52,9 +52,9 @@ __global__ __launch_bounds__(512, 2) void bwd_fused_bf16_kernel(AttnParams p, Se
   } else {
     constexpr int kSplit = SPLIT ? kDivided : kWholeTiles;
     if constexpr (std::is_same_v<RUNS, SegTable>)
-      dq_bf16_body<2, kSplit, true, true>(p, runs, n_mtiles, item, smem);
+      dq_bf16_body<2, kSplit, true, DqProducts16, true>(p, runs, n_mtiles, item, smem);
     else
-      dq_bf16_body<2, kSplit, false, true>(p, seg, n_mtiles, item, smem);
+      dq_bf16_body<2, kSplit, false, DqProducts16, true>(p, seg, n_mtiles, item, smem);
   }
 }
 

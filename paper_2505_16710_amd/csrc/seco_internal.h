@@ -389,7 +389,15 @@ int launch_dq_bf16(const AttnParams& p, const SegTable* dq_runs, hipStream_t s);
 int launch_dkdv_bf16(const AttnParams& p, const SegTable& seg, hipStream_t s);
 // dQ (p.n_splits workgroups per row tile; runs as for launch_dq_bf16) and dK/dV in one launch
 int launch_bwd_fused_bf16(const AttnParams& p, const SegTable& seg, const TailSplit& ts, bool kv_first, const SegTable* runs, hipStream_t s);
-int launch_dq_bf16_now(const AttnParams& p, const SegTable* dq_runs, hipStream_t s);
+// alone: not a call whose passes could share a launch but for what its outputs lie over (which takes that launch's products)
+int launch_dq_bf16_now(const AttnParams& p, const SegTable* dq_runs, bool alone, hipStream_t s);
+// its kernel in whole row tiles with 32x32x16 products (a translation unit of its own), for launches of so few rows that these are the
+// faster ones: up to 0.72 of what a row tile on every CU holds (n_rows: over all heads and batches).  us, 16x16x32 -> 32x32x16
+// products, of 160 calls of 100 - 256 whole tiles: 0.51 1041 rows at 4430 of 16/8 heads 100 -> 96; 0.52 two of 530 at 1322 of 16/2 42.0 ->
+// 40.3; 0.63 643 at 4396 of 32/8 95 -> 92; 0.70 two of 719 at 10360 of 16/8 209 -> 202; but 0.74 two of 380 at 9644 of 32/8 186 ->
+// 190; 0.83 1693 at 4482 of 16/8 117 -> 121; 0.88 899 at 6342 of 32/8 142 -> 149 (short causal ones up to 3 % either way).
+inline bool dq_leaves_cus(int total, int64_t n_rows) { return total <= device_cus() && 25 * n_rows <= 18 * 128 * (int64_t)device_cus(); }
+int launch_dq32_bf16(const AttnParams& p, const SegTable* dq_runs, int n_mtiles, int total, hipStream_t s);
 // the same with the query rows taken from runs (p.C: number of rows that may be addressed from p.q / p.d_o)
 int launch_dkdv_rows_bf16(const AttnParams& p, const SegTable& seg, const RowRuns& rr, hipStream_t s);
 // the kernel of either with 32x32x16 products (its own translation unit)

@@ -273,6 +273,7 @@ int main() {
         if (const int item = seco::shares_item(block, first, total); item >= 0) ++taken2[item];
       CHECK(std::count(taken.begin(), taken.end(), 1) == total && std::count(taken2.begin(), taken2.end(), 1) == total);
     }
+  CHECK(seco::dq_leaves_cus(256, 23592) && !seco::dq_leaves_cus(256, 23593) && !seco::dq_leaves_cus(257, 257));
   // ---- where an output lies over an input ----
   {
     static char mem[1 << 20];

@@ -475,6 +475,40 @@ def test_bf16_tiles_of_a_unit_dealt_to_several_xcds(B, Hq, Hkv, C, q_start):
             assert max_rel(to_host(gv[b, kh]), to_host(rv)) <= TOL["bf16"]["gv"], (b, kh)
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,C,q_start", [
+    (1, 32, 8, 641, 1503),     # 192 row tiles, the last of a head with one row; of 256, 0.63 of the rows: 32x32x16 products
+    (1, 32, 8, 769, 1503),     # 224, 0.75: 16x16x32
+    (1, 8, 8, 2300, 2900),     # 144
+    (2, 16, 2, 517, 1290),     # 160
+])
+def test_bf16_dq_of_whole_row_tiles_on_either_side_of_the_products_rule(B, Hq, Hkv, C, q_start):
+    """dQ over all columns and over runs that start and end inside tiles, against fp32 on the device; weights of 1 give the
+    same bits, and gK and gV do not depend on the columns that dQ visits."""
+    N, s, n = q_start + C, 1 / np.sqrt(128), -(-(q_start + C) // 300)
+    g = torch.Generator(device=DEV).manual_seed(93)
+    q, do, k, v = (torch.randn(B, h, m, 128, device=DEV, generator=g).to(torch.bfloat16)
+                   for h, m in ((Hq, C), (Hq, C), (Hkv, N), (Hkv, N)))
+    plan = seco.seco_launch_plan(seco.binding.make_desc(q, k, q_start, s), -(-N // 128))
+    assert plan[0] == 1                                       # whole tiles
+    o, lse = seco.seco_chunk_attn_fwd(q, k, v, q_start, s)
+    def run(wq):
+        gk, gv = (torch.zeros(B, Hkv, N, 128, device=DEV) for _ in range(2))
+        return seco.spaco_chunk_attn_bwd(q, k, v, o, lse, do, gk, gv, q_start, s, [1.0] * n, 300, dq_weight=wq), gk, gv
+    wq = [(0.0, 1.5, 1.5, 0.0, 0.25)[i % 5] for i in range(n - 1)] + [1.0]
+    dense, ones, some = run(None), run([1.0] * n), run(wq)
+    assert all(torch.equal(a, b) for a, b in zip(dense, ones))
+    assert torch.equal(some[1], dense[1]) and torch.equal(some[2], dense[2])
+    rows = torch.arange(C, device=DEV)[:, None] + q_start
+    col_w = torch.tensor(wq, device=DEV).repeat_interleave(300)[:N]
+    for b in range(B):
+        for h in range(Hq):
+            kf, vf, qf, dof, of = (t.float() for t in (k[b, h * Hkv // Hq], v[b, h * Hkv // Hq], q[b, h], do[b, h], o[b, h]))
+            z = (qf @ kf.t() * s).masked_fill(torch.arange(N, device=DEV)[None, :] > rows, float("-inf"))
+            ds = torch.exp(z - lse[b, h][:, None]) * (dof @ vf.t() - (dof * of).sum(-1, keepdim=True))
+            assert max_rel(to_host(dense[0][b, h]), to_host(s * ds @ kf)) <= TOL["bf16"]["dq"], (b, h)
+            assert max_rel(to_host(some[0][b, h]), to_host(s * (ds * col_w) @ kf)) <= TOL["bf16"]["dq"], (b, h)
+
+
 def test_forward_leaves_a_workspace_that_does_not_fit_alone():
     """One byte short, or not on 256 bytes: the undivided forward, bit for bit, and nothing is written there."""
     B, Hq, Hkv, C, q_start = 1, 48, 16, 700, 2900           # row tiles between one and two rounds

@@ -78,6 +78,6 @@ def test_matrix_core_kernels_do_not_spill():
             assert sspill <= 24, (src, name, sspill)
             spilling.add(src if sspill else None)
             assert occ is not None and occ >= _least_waves(name), (src, name, occ)
-    assert seen >= 60                    # 6 forward, 6 dQ, 4 dK/dV, 2 one-launch, 30 product, 12 fp32 instantiations at least
+    assert seen >= 63                    # 6 forward, 9 dQ, 4 dK/dV, 2 one-launch, 30 product, 12 fp32 instantiations at least
     for src in sorted(x for x in spilling if x):
         assert _lane_moves_in_loops(src) == [], src
