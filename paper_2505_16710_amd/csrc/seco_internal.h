@@ -357,6 +357,14 @@ inline SharePlan share_plan(const IterRuns& r, int n_units, int n_ctiles, int G,
   time = kDkdvTime.of(r.iters[0]);
   const float full = (float)(items / cus);
   if (busy) *busy = tail == 0 ? 1.f : (full + (float)tail / cus) / (full + 1.f);
+  // One full round, whose tiles on the diagonal end early (of further rounds the next tiles would follow).  us, dK/dV taken for busy
+  // throughout -> so (kBusy): 4096 rows at 0 of 32/8 heads 370 -> 353, two of 1933 at 0 of 8/8 55.4 -> 53.3, 3300 at 700 of 16/8 157 ->
+  // 152.  With two pairs for the eight XCDs half of these idle and the others work as in a full launch (16384 at 0 of 16/2 3125 -> 3174).
+  if (busy && items == cus && n_units >= 4) {
+    float sum = 0.f;
+    for_last(r, r.n_tiles, [&](int it, int count) { sum += count * kDkdvTime.of(it); });
+    *busy = sum / (r.n_tiles * time);
+  }
   if (tail == 0 || slots < 2 * n_units || n > r.n_tiles) return make_shares(r, 0, 0);
   const ShareChoice c = choose_shares(r, n, n_units, cus, slots, tp.hs > 1 ? tp.hs : 1, false, kDkdvTime);
   if (c.time >= 0.f) {

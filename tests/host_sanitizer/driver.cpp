@@ -273,6 +273,15 @@ int main() {
         if (const int item = seco::shares_item(block, first, total); item >= 0) ++taken2[item];
       CHECK(std::count(taken.begin(), taken.end(), 1) == total && std::count(taken2.begin(), taken2.end(), 1) == total);
     }
+  // one round of column tiles, alike or on the diagonal: how busy it keeps the compute units
+  for (const int* s : {(const int[]){32, 8}, (const int[]){64, 4}, (const int[]){128, 2}}) {
+    const seco::IterRuns alike = seco::iter_runs(s[0], [](int) { return 40; }), causal = seco::iter_runs(s[0], [&](int t) { return 2 * (s[0] - t); });
+    float time, busy;
+    seco::share_plan(alike, s[1], s[0], 1, 2560, 256, time, &busy);
+    CHECK(busy == 1.f);
+    CHECK(seco::share_plan(causal, s[1], s[0], 1, 128 * s[0], 256, time, &busy).n_tiles == 0);
+    CHECK(s[1] >= 4 ? busy > 0.5f && busy < 0.7f : busy == 1.f);
+  }
   CHECK(seco::dq_leaves_cus(256, 23592) && !seco::dq_leaves_cus(256, 23593) && !seco::dq_leaves_cus(257, 257));
   // ---- where an output lies over an input ----
   {

@@ -445,6 +445,7 @@ def test_bf16_forward_in_one_call_and_in_chunks_bit_for_bit():
     (1, 24, 4, 1500, 9),       # 288 of four
     (1, 32, 8, 1095, 1694),    # (eight units; 176 column tiles of up to 72 iterations: 32x32x16 products of dK/dV)
     (1, 8, 8, 1500, 2596),     # (as many column tiles as CUs: 16x16x32)
+    (2, 8, 8, 1990, 7),        # (as many, most on the diagonal: 32x32x16)
 ])
 def test_bf16_tiles_of_a_unit_dealt_to_several_xcds(B, Hq, Hkv, C, q_start):
     """More tiles than CUs with fewer than eight (batch, KV head) pairs: every tile is done once, whole or shared out.  Gradients are
