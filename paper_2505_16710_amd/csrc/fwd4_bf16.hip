@@ -15,7 +15,7 @@
 // With its order fixed so, a wavefront is nearly always ready to issue, and of the two on a SIMD the older one then gets
 // all it can use: the two workgroups of a CU end one behind the other.  TURNS raises the priority over the scores and exponentials and
 // lowers it over O, so that they alternate: two halves of the chip's power at a time as well (2048 rows at 15000 470 -> 455 us).
-// turns_pay below says where.
+// turns_pay (seco_internal.h) says where.
 //
 // (A translation unit of its own, with a scheduler strategy of its own, see build.py: max-ilp; max-memory-clause 1 %
 // slower, iterative-ilp 10 %.)
@@ -267,22 +267,6 @@ __global__ __launch_bounds__(256, 2) void fwd4_bf16_kernel(AttnParams p, int n_m
   }
   store_rows16([&](int db, int qb, int i) { return o[db][qb][i] * inv[qb]; },
                static_cast<__bf16*>(p.o_out) + b * p.os[0] + h * p.os[1], p.os[2], m0, p.C, smem + wave * 8192);
-}
-
-// Whether the workgroups of a CU take turns.  If not, the older one ends first, which is what a launch wants only where its next
-// tile then starts at a better time; else its last tiles start late or run alone.  600 calls of 1 - 8 rounds (two workgroups per CU) measured;
-// 1.03 times as fast by this rule, us without -> with turns:
-//   5125 rows at 5125 of 16/8 heads 359 -> 315    2372 at 1221 of 32/8 112 -> 98     7428 at 0 of 16/8 220 -> 202
-//   two of 4126 at 0 of 8/8 107 -> 98             15863 at 0 of 32/8 1671 -> 1641
-// Without where long and short tiles meet, up to 1.6 rounds and around three: a causal chunk with little before it (2556 at 0 of 32/8 61 ->
-// 63, 12412 at 0 of 8/8 291 -> 305, 2476 at 281 69 -> 71, 5229 at 0 201 -> 206; but 2842 at 848 118 -> 107), unless an XCD has two KV
-// heads one behind the other; and with tiles alike, a little over two rounds (4551 at 11084 948 -> 990, two of 8215 at 6682 of 8/8 654 ->
-// 694; at 2.56 rounds, 5159 at 6104, 695 -> 667).
-inline bool turns_pay(const AttnParams& p, int total) {
-  const float rounds = total / (2.f * device_cus()), before = (float)p.q_start / p.C;
-  if (p.B * p.Hkv <= 8 && before < 0.8f * (1.6f - rounds)) return false;
-  if (p.B * p.Hkv <= 8 && before < 0.1f && rounds >= 2.4f && rounds < 3.25f) return false;
-  return !(before >= 0.15f && rounds >= 2.02f && rounds < 2.55f);
 }
 
 template <bool TURNS>

@@ -384,6 +384,25 @@ constexpr int kColTileF32 = 16;    // columns per workgroup in launch_dkdv_f32
 int launch_fwd_bf16(const AttnParams& p, hipStream_t s);
 // the 4-wavefront forward kernel (its own translation unit)
 int launch_fwd4_bf16(const AttnParams& p, int n_mtiles, int total, hipStream_t s);
+// Whether the workgroups of a CU take turns.  If not, the older one ends first, which is what a launch wants only where its next
+// tile then starts at a better time; else its last tiles start late or run alone.  600 calls of 1 - 8 rounds (two workgroups per CU) measured;
+// 1.03 times as fast by this rule, us without -> with turns:
+//   5125 rows at 5125 of 16/8 heads 359 -> 315    2372 at 1221 of 32/8 112 -> 98     7428 at 0 of 16/8 220 -> 202
+//   two of 4126 at 0 of 8/8 107 -> 98             15863 at 0 of 32/8 1671 -> 1641
+// Without where long and short tiles meet, up to 1.6 rounds and around three: a causal chunk with little before it (2556 at 0 of 32/8 61 ->
+// 63, 12412 at 0 of 8/8 291 -> 305, 2476 at 281 69 -> 71, 5229 at 0 201 -> 206; but 2842 at 848 118 -> 107), unless an XCD has two KV
+// heads one behind the other; and with tiles alike, a little over two rounds (4551 at 11084 948 -> 990, two of 8215 at 6682 of 8/8 654 ->
+// 694; at 2.56 rounds, 5159 at 6104, 695 -> 667).
+// Nor where an XCD has three or four KV heads and, with two full rounds or a little more, the tiles of the last begin as those of the
+// first end (4096 at 0 of 32/32 heads 157 -> 162, 5400 at 0 of 24/24 197 -> 205, 3994 at 300 of 32/32 166 -> 174, at 1800 249 -> 253;
+// but 3964 at 0 of 32/32, a tile of each head less, 156 -> 148, and two or eight heads to an XCD 1.04 - 1.1 times as fast with turns).
+inline bool turns_pay(const AttnParams& p, int total) {
+  const float rounds = total / (2.f * device_cus()), before = (float)p.q_start / p.C;
+  if (p.B * p.Hkv <= 8 && before < 0.8f * (1.6f - rounds)) return false;
+  if (p.B * p.Hkv <= 8 && before < 0.1f && rounds >= 2.4f && rounds < 3.25f) return false;
+  if ((p.B * p.Hkv == 24 || p.B * p.Hkv == 32) && before < 0.5f && rounds >= 2.f && rounds < 2.2f) return false;
+  return !(before >= 0.15f && rounds >= 2.02f && rounds < 2.55f);
+}
 // the 8-wavefront forward kernel's short-chunk variant, which writes partials (likewise)
 int launch_fwd8_split_bf16(const AttnParams& p, int n_mtiles, int total, hipStream_t s);
 // ... and its variant that divides the row tiles beyond the first round, with the merge behind it

@@ -283,6 +283,17 @@ int main() {
     CHECK(s[1] >= 4 ? busy > 0.5f && busy < 0.7f : busy == 1.f);
   }
   CHECK(seco::dq_leaves_cus(256, 23592) && !seco::dq_leaves_cus(256, 23593) && !seco::dq_leaves_cus(257, 257));
+  // the 4-wavefront forward's turns: not with three or four KV heads to an XCD from two rounds on
+  for (const int* s : {(const int[]){32, 4096, 0, 1024, 0}, (const int[]){32, 3994, 300, 1024, 0}, (const int[]){32, 4471, 0, 1120, 0}, (const int[]){24, 5400, 0, 1032, 0},
+                       (const int[]){32, 3964, 0, 992, 1}, (const int[]){32, 4600, 0, 1152, 1}, (const int[]){32, 4000, 4000, 1024, 1},
+                       (const int[]){16, 4096, 0, 1024, 1}, (const int[]){64, 4096, 0, 1024, 1}}) {
+    seco::AttnParams p{};
+    p.B = 1;
+    p.Hkv = s[0];
+    p.C = s[1];
+    p.q_start = s[2];
+    CHECK(seco::turns_pay(p, s[3]) == (s[4] != 0));
+  }
   // ---- where an output lies over an input ----
   {
     static char mem[1 << 20];
