@@ -202,8 +202,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void fwd_small_bf16_kernel(AttnPara
 }  // namespace
 
 namespace {
-// A round (eight blocks, one per wavefront) takes about 1.8 us and dividing the cache costs a merge of 4.3 (2, 4 and 5 rounds
-// of one row tile 8.4, 12.1 and 14.0 us; a round each and a merge 10.6).  At most one workgroup per CU.
+// Rounds of eight blocks, one per wavefront; divided where that pays (small_divides).  At most one workgroup per CU.
 struct SmallPlan { int n_mtiles, n_splits, rounds; };      // rounds: of a workgroup
 SmallPlan small_plan(const AttnParams& p, int max_splits) {
   SmallPlan sp;
@@ -212,7 +211,7 @@ SmallPlan small_plan(const AttnParams& p, int max_splits) {
   int n = std::min(std::max(device_cus() / units, 1), max_splits);
   const int each = (all + n - 1) / n;
   n = (all + each - 1) / each;
-  sp.n_splits = 18 * (all - each) > 43 ? n : 1;
+  sp.n_splits = small_divides(p.B * p.Hkv, all - each) ? n : 1;
   sp.rounds = sp.n_splits > 1 ? each : all;
   return sp;
 }

@@ -410,6 +410,12 @@ int launch_fwd8_shares_bf16(const AttnParams& p, int n_mtiles, hipStream_t s);
 // few query rows per KV head (fwd_small_pays); max_splits: how many partial results the workspace holds (1: there is none)
 int launch_fwd_small_bf16(AttnParams p, int max_splits, hipStream_t s);
 bool fwd_small_pays(const AttnParams& p, int max_splits);   // whether that kernel is the faster one (rows, cache, divisions at hand)
+// Whether it divides the cache of `pairs` (batch, KV head) pairs, which saves a workgroup `saved` rounds of eight blocks.  A round takes
+// about 1.8 us and the merge 4.3 (2, 4 and 5 rounds of one row tile 8.4, 12.1 and 14.0 us; a round each and a merge 10.6).  From about 7
+// pairs for 16 CUs on undivided workgroups already read at nearly the memory's rate, and three rounds saved are less than the merge: us,
+// whole -> divided, buffers in no cache, 128 pairs at 1336 / 1592 rows 21.3 -> 22.5 / 24.4 -> 24.8 (in one: 17.4 -> 20.2); 64 at 1080 16.5 -> 14.3, 96
+// at 1592 22.9 -> 20.7.
+inline bool small_divides(int pairs, int saved) { return 18 * saved > (16 * pairs > 7 * device_cus() ? 60 : 43); }
 // dq_runs: NULL for all visible cache rows with weight 1; else runs of cache rows (ascending, disjoint), each with
 // a positive weight (tile_begin is not used)
 int launch_dq_bf16(const AttnParams& p, const SegTable* dq_runs, hipStream_t s);

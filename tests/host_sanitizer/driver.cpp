@@ -283,6 +283,8 @@ int main() {
     CHECK(s[1] >= 4 ? busy > 0.5f && busy < 0.7f : busy == 1.f);
   }
   CHECK(seco::dq_leaves_cus(256, 23592) && !seco::dq_leaves_cus(256, 23593) && !seco::dq_leaves_cus(257, 257));
+  // the small forward's cache: three rounds saved are worth a merge until its workgroups read at the memory's rate
+  CHECK(seco::small_divides(8, 3) && seco::small_divides(112, 3) && !seco::small_divides(113, 3) && seco::small_divides(128, 4) && !seco::small_divides(1, 2));
   // the 4-wavefront forward's turns: not with three or four KV heads to an XCD from two rounds on
   for (const int* s : {(const int[]){32, 4096, 0, 1024, 0}, (const int[]){32, 3994, 300, 1024, 0}, (const int[]){32, 4471, 0, 1120, 0}, (const int[]){24, 5400, 0, 1032, 0},
                        (const int[]){32, 3964, 0, 992, 1}, (const int[]){32, 4600, 0, 1152, 1}, (const int[]){32, 4000, 4000, 1024, 1},
