@@ -393,14 +393,16 @@ int launch_fwd4_bf16(const AttnParams& p, int n_mtiles, int total, hipStream_t s
 // 63, 12412 at 0 of 8/8 291 -> 305, 2476 at 281 69 -> 71, 5229 at 0 201 -> 206; but 2842 at 848 118 -> 107), unless an XCD has two KV
 // heads one behind the other; and with tiles alike, a little over two rounds (4551 at 11084 948 -> 990, two of 8215 at 6682 of 8/8 654 ->
 // 694; at 2.56 rounds, 5159 at 6104, 695 -> 667).
-// Nor where an XCD has three or four KV heads and, with two full rounds or a little more, the tiles of the last begin as those of the
-// first end (4096 at 0 of 32/32 heads 157 -> 162, 5400 at 0 of 24/24 197 -> 205, 3994 at 300 of 32/32 166 -> 174, at 1800 249 -> 253;
-// but 3964 at 0 of 32/32, a tile of each head less, 156 -> 148, and two or eight heads to an XCD 1.04 - 1.1 times as fast with turns).
+// Nor where an XCD has three or four KV heads and the tiles of the last begin as those of the first end: four heads with two full rounds
+// or a little more (4096 at 0 of 32/32 157 -> 162, 3994 at 300 166 -> 174, at 1800 249 -> 253; but 3964 at 0, a tile of each
+// head less, 156 -> 148), three with 1.7 to 2.95 and little before the chunk (5400 at 0 of 24/24 197 -> 205, 5917 226 -> 233, 7900 363 -> 377;
+// 200 calls).  With two or eight heads to an XCD turns are 1.04 - 1.1 times as fast there.
 inline bool turns_pay(const AttnParams& p, int total) {
   const float rounds = total / (2.f * device_cus()), before = (float)p.q_start / p.C;
   if (p.B * p.Hkv <= 8 && before < 0.8f * (1.6f - rounds)) return false;
   if (p.B * p.Hkv <= 8 && before < 0.1f && rounds >= 2.4f && rounds < 3.25f) return false;
-  if ((p.B * p.Hkv == 24 || p.B * p.Hkv == 32) && before < 0.5f && rounds >= 2.f && rounds < 2.2f) return false;
+  if (p.B * p.Hkv == 24 && rounds >= 1.7f && (rounds < 2.02f ? before < 0.6f : rounds < 2.95f - 2.f * before)) return false;
+  if (p.B * p.Hkv == 32 && before < 0.5f && rounds >= 2.f && rounds < 2.2f) return false;
   return !(before >= 0.15f && rounds >= 2.02f && rounds < 2.55f);
 }
 // the 8-wavefront forward kernel's short-chunk variant, which writes partials (likewise)

@@ -285,8 +285,9 @@ int main() {
   CHECK(seco::dq_leaves_cus(256, 23592) && !seco::dq_leaves_cus(256, 23593) && !seco::dq_leaves_cus(257, 257));
   // the small forward's cache: three rounds saved are worth a merge until its workgroups read at the memory's rate
   CHECK(seco::small_divides(8, 3) && seco::small_divides(112, 3) && !seco::small_divides(113, 3) && seco::small_divides(128, 4) && !seco::small_divides(1, 2));
-  // the 4-wavefront forward's turns: not with three or four KV heads to an XCD from two rounds on
-  for (const int* s : {(const int[]){32, 4096, 0, 1024, 0}, (const int[]){32, 3994, 300, 1024, 0}, (const int[]){32, 4471, 0, 1120, 0}, (const int[]){24, 5400, 0, 1032, 0},
+  // the 4-wavefront forward's turns: not with three or four KV heads to an XCD around two rounds
+  for (const int* s : {(const int[]){32, 4096, 0, 1024, 0}, (const int[]){32, 3994, 300, 1024, 0}, (const int[]){32, 4471, 0, 1120, 0}, (const int[]){24, 5400, 0, 1032, 0}, (const int[]){24, 4900, 0, 936, 0}, (const int[]){24, 7000, 600, 1320, 0},
+                       (const int[]){24, 7500, 0, 1416, 0}, (const int[]){24, 7900, 0, 1488, 0}, (const int[]){24, 8192, 0, 1536, 1}, (const int[]){24, 7900, 600, 1488, 1}, (const int[]){24, 4300, 0, 816, 1}, (const int[]){24, 4900, 4000, 936, 1},
                        (const int[]){32, 3964, 0, 992, 1}, (const int[]){32, 4600, 0, 1152, 1}, (const int[]){32, 4000, 4000, 1024, 1},
                        (const int[]){16, 4096, 0, 1024, 1}, (const int[]){64, 4096, 0, 1024, 1}}) {
     seco::AttnParams p{};
