@@ -105,6 +105,20 @@ def test_losses_of_a_step_that_visits_every_chunk(dtype, cfg, N, kw):
     assert every == picked == some
 
 
+@pytest.mark.parametrize("keep", [False, True])
+def test_step_that_leaves_the_last_chunk_out(keep):
+    """Stage 2 then does not start with the last chunk, and stage 1 has to run it: the same losses, and the oracle's gradients.  With
+    the last chunk as the only one stage 1 runs the others for their cache rows."""
+    _, dec, tok, tgt = _setup(F32_CFG, 19, 1, 120, torch.float32)
+    p64, tok_g, tgt_g = {n: t.detach().double().cpu().requires_grad_() for n, t in dec.p.items()}, tok.to(DEV), tgt.to(DEV)
+    every, _ = dec.step(tok_g, tgt_g, 32, keep_attention_outputs=keep)
+    for sel in ([2, 0], [3], [0]):
+        loss, g = dec.step(tok_g, tgt_g, 32, selected=sel, factor=1.5, keep_attention_outputs=keep)
+        assert loss == every, sel
+        _, g_ref = om.spaco_grads(F32_CFG, p64, tok, tgt, 32, sel, 1.5)
+        _compare(g_ref, g, 5e-4)
+
+
 @pytest.mark.parametrize("dtype,cfg,tol,transposed,keep", [
     (torch.float32, F32_CFG, 5e-4, False, False), (torch.float32, F32_CFG, 5e-4, False, True),
     (torch.bfloat16, BF16_CFG, 6e-2, False, False), (torch.bfloat16, BF16_CFG, 6e-2, False, True),
