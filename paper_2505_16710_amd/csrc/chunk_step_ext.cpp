@@ -565,12 +565,13 @@ PyObject* step_new(PyObject* const* a) {
   return cap;
 }
 
-// rows [s0, s1) of every sequence; the kernels read as many entries as the chunk has tokens
+// rows [s0, s1) of every sequence; the kernels read as many entries as the chunk has tokens, one behind the other (of one sequence
+// reshape alone would give a view with the stride of t's columns)
 Tensor chunk_of(const Step& st, const Tensor& t, int64_t s0, int64_t s1) {
   if (t.device() != st.emb.w.device() || t.scalar_type() != at::kLong || t.dim() != 2 || t.size(0) != st.B || t.size(1) < s1)
     raise(PyExc_ValueError, "tokens, targets: int64 [B, N] on the parameters' GPU");
   if (s0 < 0 || s1 <= s0 || s1 > st.N) raise(PyExc_ValueError, "chunk outside the sequence");
-  return t.slice(1, s0, s1).reshape({-1});
+  return t.slice(1, s0, s1).reshape({-1}).contiguous();
 }
 
 // where the losses of rows [s0, s1) of every sequence go

@@ -105,6 +105,19 @@ def test_losses_of_a_step_that_visits_every_chunk(dtype, cfg, N, kw):
     assert every == picked == some
 
 
+@pytest.mark.parametrize("B", [1, 2])
+def test_tokens_and_targets_of_any_stride(B):
+    _, dec, tok, tgt = _setup(F32_CFG, 20, B, 96, torch.float32)
+    loss, g = dec.step(tok.to(DEV), tgt.to(DEV), 40)
+    g = {n: t.clone() for n, t in g.items()}
+    strided = [torch.stack((t, t * 0 + 1), -1).to(DEV).flatten(1)[:, ::2] for t in (tok, tgt)]
+    assert strided[0].stride(1) == 2
+    loss_s, g_s = dec.step(*strided, 40)
+    assert loss_s == loss
+    for n in g:
+        assert torch.equal(g_s[n], g[n]), n
+
+
 @pytest.mark.parametrize("keep", [False, True])
 def test_step_that_leaves_the_last_chunk_out(keep):
     """Stage 2 then does not start with the last chunk, and stage 1 has to run it: the same losses, and the oracle's gradients.  With
