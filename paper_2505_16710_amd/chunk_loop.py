@@ -246,5 +246,7 @@ class ChunkedDecoder:
                     wq = [dq_weights(j, l) for l in range(self.n_layers)]
                 ext.step_train(run, tokens, targets, starts[j], min(starts[j] + chunk_len, N), keep_attention_outputs and j != once, w,
                                chunk_len, wq, losses if rebuilt or j == once else None)
-            total, grads = float(losses.sum()), dict(zip(names, ext.step_grads(run)))
+            # (everything is on its way before the host waits for the loss)
+            total, grads = losses.sum(), dict(zip(names, ext.step_grads(run)))
+            total = float(total)
         return total, hand_over(p, grads)

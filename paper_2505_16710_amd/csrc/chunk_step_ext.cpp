@@ -314,7 +314,8 @@ struct Step {
     auto norm = [&](void* x, void* y, const Param& g, void* xo, void* h, float* r) {
       check(lib.dec_add_rmsnorm(dtype, x, y, ptr(g.w), xo, h, r, R, dm, s), "dec_add_rmsnorm");
     };
-    x0 = at::index(emb.w, {tok});
+    // the chunk's rows of the table, written by the first norm
+    x0 = layers.empty() ? at::index(emb.w, {tok}) : at::empty({R, dm}, opts());
     void *x = ptr(x0), *y = rows(dm), *logits = mem.take((size_t)(R * V) * head.w.element_size());
     bool have_y = false;
     const size_t base = mem.used;
@@ -324,7 +325,11 @@ struct Step {
       sv.x1 = have_y && saved ? rows(dm) : x;
       sv.h1 = rows(dm);
       sv.r1 = stats();
-      norm(x, have_y ? y : nullptr, l.norm1, sv.x1, sv.h1, sv.r1);
+      if (&l == &layers.front())
+        check(lib.dec_embed_rmsnorm(dtype, ptr(emb.w), static_cast<const int64_t*>(ptr(tok)), ptr(l.norm1.w), x, sv.h1, sv.r1, R, dm,
+                                    emb.w.size(0), s), "dec_embed_rmsnorm");
+      else
+        norm(x, y, l.norm1, sv.x1, sv.h1, sv.r1);
       sv.qkv = rows(W);
       mm(sv.qkv, sv.h1, l.wqkv, R);
       if (to_cache && &l == &layers.back() && keep == kCompute) {
@@ -645,8 +650,11 @@ PyObject* step_train(PyObject* const* a) {
 // (step) -> gradients in the order of step_new's params; None where no chunk reached the parameter
 PyObject* step_grads(PyObject* const* a) {
   Step& st = step_of(a[0]);
+  begin(st);
   std::vector<Tensor> out = {st.emb.grad, st.head.grad};
-  const Tensor sums = st.parts.sum(1), gains = sums.to(st.emb.w.scalar_type());
+  const Tensor sums = at::empty({2 * st.L + 1, st.dm}, st.parts.options()), gains = st.dtype == SECO_F32 ? sums : at::empty({2 * st.L + 1, st.dm}, st.opts());
+  check(lib.dec_gain_sums(st.dtype, fptr(st.parts), fptr(sums), st.dtype == SECO_F32 ? nullptr : ptr(gains), 2 * st.L + 1, st.dm, st.s),
+        "dec_gain_sums");
   auto gain = [&](int64_t i, const Param& p) {
     if (!st.trained) return Tensor();
     if (p.type == gains.scalar_type() && p.sizes.size() == 1 && p.sizes[0] == st.dm) return gains.select(0, i);
@@ -662,10 +670,15 @@ PyObject* step_grads(PyObject* const* a) {
     out.push_back(gain(2 * i, l.norm1));
     out.push_back(gain(2 * i + 1, l.norm2));
     const int64_t kv = st.Hkv * st.D;
-    const bool have = l.wqkv.grad.defined();
-    out.push_back(have ? l.wqkv.grad.slice(1, 0, st.HD).contiguous() : Tensor());
-    out.push_back(have ? l.wqkv.grad.slice(1, st.HD, st.HD + kv).contiguous() : Tensor());
-    out.push_back(have ? l.wqkv.grad.slice(1, st.HD + kv, st.HD + 2 * kv).contiguous() : Tensor());
+    Tensor q, k, v;
+    if (l.wqkv.grad.defined()) {
+      q = at::empty({st.dm, st.HD}, st.opts());
+      k = at::empty({st.dm, kv}, st.opts());
+      v = at::empty({st.dm, kv}, st.opts());
+      const int64_t e = (int64_t)st.e;
+      check(lib.dec_split_columns(ptr(l.wqkv.grad), ptr(q), ptr(k), ptr(v), st.dm, st.HD * e, kv * e, kv * e, st.s), "dec_split_columns");
+    }
+    for (const Tensor& t : {q, k, v}) out.push_back(t);
     out.push_back(l.wo.grad);
     out.push_back(l.w1.grad);
     out.push_back(l.w2.grad);

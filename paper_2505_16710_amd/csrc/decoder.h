@@ -9,11 +9,19 @@ extern "C" {
 // x_out = x + y (y NULL: x_out is not written), h = round(x_out * rstd) * gain, rstd = 1 / sqrt(mean(x_out^2) + 1e-6)
 int dec_add_rmsnorm(int dtype, const void* x, const void* y, const void* gain, void* x_out, void* h, float* rstd,
                     int64_t rows, int64_t d, void* stream);
+// the same for the rows token[r] of a table of v rows, which go to x_out; a token outside [-v, v) gives NaN, a negative one counts from the end
+int dec_embed_rmsnorm(int dtype, const void* table, const int64_t* token, const void* gain, void* x_out, void* h, float* rstd,
+                      int64_t rows, int64_t d, int64_t v, void* stream);
 // d_x = d_in + gradient of the norm at x (d_in NULL: the gradient alone; d_x may be d_in or d_h);
 // gain_part[blocks, d] fp32 += per-workgroup sums of the gain's gradient, blocks = DEC_GAIN_BLOCKS
 #define DEC_GAIN_BLOCKS 256
 int dec_rmsnorm_bwd(int dtype, const void* x, const void* gain, const float* rstd, const void* d_h, const void* d_in,
                     void* d_x, float* gain_part, int64_t rows, int64_t d, void* stream);
+// sums[n, d] = parts[n, DEC_GAIN_BLOCKS, d] summed over the blocks in a fixed order; rounded (NULL: not written): the same in dtype
+int dec_gain_sums(int dtype, const float* parts, float* sums, void* rounded, int64_t n, int64_t d, void* stream);
+// src [rows, a + b + c bytes] -> a, b, c, each contiguous; sizes are multiples of 16 bytes
+int dec_split_columns(const void* src, void* a, void* b, void* c, int64_t rows, int64_t bytes_a, int64_t bytes_b, int64_t bytes_c,
+                      void* stream);
 int dec_silu(int dtype, const void* u, void* a, int64_t n, void* stream);
 int dec_silu_bwd(int dtype, const void* u, void* d_a, int64_t n, void* stream);   // d_a <- d_a * silu'(u)
 // loss[r] = logsumexp(logits[r]) - logits[r][target[r]] (loss non-NULL), or logits <- softmax - onehot (loss NULL);

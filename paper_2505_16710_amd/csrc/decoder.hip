@@ -71,17 +71,27 @@ template <typename T, int V> __device__ __forceinline__ Vec<T, V> fetch(const T*
   return *reinterpret_cast<const Vec<T, V>*>(row + (c < d ? c : d - V));
 }
 
-template <typename T, int V, int KB>
+// EMBED: row r of x is row token[r] of a table of v rows (the embedding of a chunk, which took a launch of its own for rows that
+// this one reads anyway: 512 x 1024 3.1 + 3.5 us -> 4.4); a token outside it gives NaN.
+template <typename T, int V, int KB, bool EMBED>
 __global__ __launch_bounds__(kThreads) void add_rmsnorm_kernel(const T* x, const T* y, const T* gain, T* x_out, T* h,
-                                                               float* rstd, int64_t d) {   // (x_out may be x)
+                                                               float* rstd, int64_t d, const int64_t* token, int64_t v) {   // (x_out may be x)
   const int64_t row = (int64_t)blockIdx.x * d;
   float kept[KB][V], sum = 0.f;
+  bool bad = false;
+  if constexpr (EMBED) {
+    int64_t t = token[blockIdx.x];
+    t += t < 0 ? v : 0;                                  // negative: counted from the end
+    bad = t < 0 || t >= v;
+    x += (bad ? 0 : t) * d - row;                        // (x + row is then the table's row)
+  }
+  const bool kept_out = EMBED || y;
   Vec<T, V> xv[KB], yv[KB], gv[KB];
 #pragma unroll
   for (int k = 0; k < KB; ++k) {
     const int64_t c = ((int64_t)k * kThreads + threadIdx.x) * V;
     xv[k] = fetch<T, V>(x + row, c, d);
-    yv[k] = fetch<T, V>((y ? y : x) + row, c, d);
+    if (!EMBED) yv[k] = fetch<T, V>((y ? y : x) + row, c, d);
     gv[k] = fetch<T, V>(gain, c, d);
   }
 #pragma unroll
@@ -89,7 +99,11 @@ __global__ __launch_bounds__(kThreads) void add_rmsnorm_kernel(const T* x, const
     const int64_t c = ((int64_t)k * kThreads + threadIdx.x) * V;
     if (c < d) {
       xv[k].get(kept[k]);
-      if (y) {
+      if (EMBED) {
+#pragma unroll
+        for (int j = 0; j < V; ++j) kept[k][j] = bad ? NAN : kept[k][j];
+        store<T, V>(x_out + row + c, kept[k]);
+      } else if (y) {
         float g[V];
         yv[k].get(g);
 #pragma unroll
@@ -103,7 +117,11 @@ __global__ __launch_bounds__(kThreads) void add_rmsnorm_kernel(const T* x, const
   for (int64_t c = ((int64_t)KB * kThreads + threadIdx.x) * V; c < d; c += kThreads * V) {
     float f[V];
     load<T, V>(x + row + c, f);
-    if (y) {
+    if (EMBED) {
+#pragma unroll
+      for (int j = 0; j < V; ++j) f[j] = bad ? NAN : f[j];
+      store<T, V>(x_out + row + c, f);
+    } else if (y) {
       float g[V];
       load<T, V>(y + row + c, g);
 #pragma unroll
@@ -128,7 +146,7 @@ __global__ __launch_bounds__(kThreads) void add_rmsnorm_kernel(const T* x, const
   }
   for (int64_t c = ((int64_t)KB * kThreads + threadIdx.x) * V; c < d; c += kThreads * V) {
     float f[V], g[V];
-    load<T, V>((y ? x_out : x) + row + c, f);             // this thread's own words
+    load<T, V>((kept_out ? x_out : x) + row + c, f);      // this thread's own words
     load<T, V>(gain + c, g);
 #pragma unroll
     for (int j = 0; j < V; ++j) f[j] = (float)(T)(f[j] * r) * g[j];
@@ -436,6 +454,55 @@ __global__ __launch_bounds__(kThreads) void embedding_bwd_kernel(const T* d_x, c
   }
 }
 
+// sums[i][c] = the rows of parts[i], added up (n sets of DEC_GAIN_BLOCKS rows of d), and the same rounded.  Bound by latency: a
+// workgroup takes 64 columns, its 16 groups of lanes every 16th row each, all of a lane's loads in flight; then the groups in
+// order.  (2.5 MB of five gains of 1024: 18 us as a framework sum and 2 for the rounding, 4.5 here.)
+template <typename T>
+__global__ __launch_bounds__(kThreads) void gain_sums_kernel(const float* parts, float* sums, T* rounded, int64_t d) {
+  constexpr int kGroups = 16, kPer = DEC_GAIN_BLOCKS / kGroups;
+  __shared__ float sh[kGroups][64];
+  const int group = threadIdx.x >> 4, l16 = threadIdx.x & 15;
+  const int64_t c0 = (int64_t)blockIdx.x * 64;
+  const float* from = parts + (int64_t)blockIdx.y * DEC_GAIN_BLOCKS * d + (int64_t)group * d;
+  float x[kPer][4];
+#pragma unroll
+  for (int k = 0; k < kPer; ++k)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int64_t c = c0 + l16 + 16 * j;
+      x[k][j] = from[(int64_t)k * kGroups * d + (c < d ? c : d - 1)];
+    }
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    float f = x[0][j];
+#pragma unroll
+    for (int k = 1; k < kPer; ++k) f += x[k][j];
+    sh[group][l16 + 16 * j] = f;
+  }
+  __syncthreads();
+  const int64_t c = c0 + threadIdx.x;
+  if (threadIdx.x >= 64 || c >= d) return;
+  float f = sh[0][threadIdx.x];
+#pragma unroll
+  for (int k = 1; k < kGroups; ++k) f += sh[k][threadIdx.x];
+  sums[blockIdx.y * d + c] = f;
+  if (rounded) rounded[blockIdx.y * d + c] = (T)f;
+}
+
+// Three runs of columns of a matrix to matrices of their own, 16 bytes per thread (u: 16-byte units of a row, u0 and u1 of them in the
+// first two runs)
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+__global__ __launch_bounds__(kThreads) void split_columns_kernel(const u32x4* src, u32x4* a, u32x4* b, u32x4* c, int64_t n, int u, int u0, int u1) {
+  const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  if (i >= n) return;
+  const int64_t row = i / u;
+  const int col = (int)(i - row * u);
+  const u32x4 x = src[i];
+  if (col < u0) a[row * u0 + col] = x;
+  else if (col < u0 + u1) b[row * u1 + (col - u0)] = x;
+  else c[row * (u - u0 - u1) + (col - u0 - u1)] = x;
+}
+
 int status() { return hipGetLastError() == hipSuccess ? SECO_OK : SECO_ERR_LAUNCH; }
 bool sizes_ok(int dtype, int64_t rows, int64_t d) {
   return (dtype == SECO_BF16 || dtype == SECO_F32) && rows >= 0 && rows < ((int64_t)1 << 31) && d >= 1;
@@ -462,12 +529,33 @@ template <typename... P> bool words(P... p) { return (((reinterpret_cast<uintptr
   else                                                                                                                    \
     hipLaunchKernelGGL((kernel<T, V, kKeep>), dim3(grid), dim3(kThreads), 0, (hipStream_t)stream, __VA_ARGS__)
 
+template <typename T, int V, bool EMBED>
+static void launch_norm(const void* x, const void* y, const void* gain, void* x_out, void* h, float* rstd, int64_t rows, int64_t d,
+                        const int64_t* token, int64_t v, void* stream) {
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3((unsigned)rows), dim3(kThreads), 0, (hipStream_t)stream, (const T*)x, (const T*)y, (const T*)gain,
+                       (T*)x_out, (T*)h, rstd, d, token, v);
+  };
+  if (d <= kThreads * V) go(add_rmsnorm_kernel<T, V, 1, EMBED>);
+  else if (d <= 2 * kThreads * V) go(add_rmsnorm_kernel<T, V, 2, EMBED>);
+  else go(add_rmsnorm_kernel<T, V, kKeep, EMBED>);
+}
+
+extern "C" int dec_embed_rmsnorm(int dtype, const void* table, const int64_t* token, const void* gain, void* x_out, void* h, float* rstd,
+                                 int64_t rows, int64_t d, int64_t v, void* stream) {
+  if (!sizes_ok(dtype, rows, d) || v < 1) return SECO_ERR_SHAPE;
+  if (rows == 0) return SECO_OK;
+#define L(T, V) launch_norm<T, V, true>(table, nullptr, gain, x_out, h, rstd, rows, d, token, v, stream)
+  DEC_DISPATCH(d, words(table, gain, x_out, h), L)
+#undef L
+  return status();
+}
+
 extern "C" int dec_add_rmsnorm(int dtype, const void* x, const void* y, const void* gain, void* x_out, void* h, float* rstd,
                                int64_t rows, int64_t d, void* stream) {
   if (!sizes_ok(dtype, rows, d)) return SECO_ERR_SHAPE;
   if (rows == 0) return SECO_OK;
-#define L(T, V)                                                                                                      \
-  DEC_BLOCKS(add_rmsnorm_kernel, T, V, (unsigned)rows, (const T*)x, (const T*)y, (const T*)gain, (T*)x_out, (T*)h, rstd, d)
+#define L(T, V) launch_norm<T, V, false>(x, y, gain, x_out, h, rstd, rows, d, nullptr, 0, stream)
   DEC_DISPATCH(d, words(x, y, gain, x_out, h), L)
 #undef L
   return status();
@@ -491,6 +579,29 @@ extern "C" int dec_rmsnorm_bwd(int dtype, const void* x, const void* gain, const
   DEC_DISPATCH(d, words(x, gain, d_h, d_in, d_x, gain_part), L)
 #undef L
 #undef ROWS
+  return status();
+}
+
+extern "C" int dec_gain_sums(int dtype, const float* parts, float* sums, void* rounded, int64_t n, int64_t d, void* stream) {
+  if (!sizes_ok(dtype, n, d) || n > 65535) return SECO_ERR_SHAPE;
+  if (n == 0) return SECO_OK;
+  const dim3 grid((unsigned)((d + 63) / 64), (unsigned)n);
+  if (dtype == SECO_BF16)
+    hipLaunchKernelGGL(gain_sums_kernel<__bf16>, grid, dim3(kThreads), 0, (hipStream_t)stream, parts, sums, (__bf16*)rounded, d);
+  else
+    hipLaunchKernelGGL(gain_sums_kernel<float>, grid, dim3(kThreads), 0, (hipStream_t)stream, parts, sums, (float*)rounded, d);
+  return status();
+}
+
+extern "C" int dec_split_columns(const void* src, void* a, void* b, void* c, int64_t rows, int64_t bytes_a, int64_t bytes_b, int64_t bytes_c,
+                                 void* stream) {
+  if (rows < 0 || bytes_a < 0 || bytes_b < 0 || bytes_c < 0 || (bytes_a | bytes_b | bytes_c) & 15) return SECO_ERR_SHAPE;
+  if (!words(src, a, b, c)) return SECO_ERR_ALIGN;
+  const int64_t u = (bytes_a + bytes_b + bytes_c) / 16, n = rows * u;
+  if (u > 0x7fffffff || (n + kThreads - 1) / kThreads > 0x7fffffff) return SECO_ERR_TOO_LARGE;
+  if (n == 0) return SECO_OK;
+  hipLaunchKernelGGL(split_columns_kernel, dim3((unsigned)((n + kThreads - 1) / kThreads)), dim3(kThreads), 0, (hipStream_t)stream,
+                     (const u32x4*)src, (u32x4*)a, (u32x4*)b, (u32x4*)c, n, (int)u, (int)(bytes_a / 16), (int)(bytes_b / 16));
   return status();
 }
 

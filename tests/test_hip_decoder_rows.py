@@ -267,3 +267,53 @@ def test_rotated_projection_in_one_launch(dtype, B, Hq, Hkv, n, D, row0):
     dk, dv = seco.kvgrad_readout(gk, gv, row0, n, dt, rope_base=base)
     assert torch.equal(parts(x)[0], seco.rope_rotate(q.contiguous(), row0, base, inverse=True))
     assert torch.equal(parts(x)[1], dk) and torch.equal(parts(x)[2], dv) and torch.equal(kk, gk) and torch.equal(vv, gv)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("d", [8, 200, 1024, 1031, 2056, 8208])
+def test_norm_of_embedded_rows(dtype, d):
+    """dec_embed_rmsnorm against the gathered rows through dec_add_rmsnorm: the same bits.  Row lengths of one, two and four kept
+    blocks and beyond, with and without 16-byte accesses; negative tokens; tokens outside the table give NaN rows and no others."""
+    code, v, rows = (F32 if dtype == torch.float32 else BF16), 11, 37
+    g = torch.Generator().manual_seed(d)
+    table, gain = torch.randn(v, d, generator=g).to(dtype).to(DEV), torch.randn(d, generator=g).to(dtype).to(DEV)
+    token = torch.randint(-v, v, (rows,), generator=g).to(DEV)
+    new = lambda: (torch.empty(rows, d, dtype=dtype, device=DEV), torch.empty(rows, d, dtype=dtype, device=DEV), torch.empty(rows, device=DEV))
+    x = table[token]
+    _, h_ref, r_ref = new()
+    _call("add_rmsnorm", code, x, None, gain, None, h_ref, r_ref, rows, d)
+    x_out, h, r = new()
+    _call("embed_rmsnorm", code, table, token, gain, x_out, h, r, rows, d, v)
+    assert torch.equal(x_out, x) and torch.equal(h, h_ref) and torch.equal(r, r_ref)
+    token[3], token[20] = v, -v - 1
+    _call("embed_rmsnorm", code, table, token, gain, x_out, h, r, rows, d, v)
+    bad = torch.zeros(rows, dtype=torch.bool, device=DEV)
+    bad[[3, 20]] = True
+    assert x_out[bad].isnan().all() and h[bad].isnan().all()
+    assert torch.equal(x_out[~bad], x[~bad]) and torch.equal(h[~bad], h_ref[~bad])
+
+
+@pytest.mark.parametrize("n,d", [(1, 1), (3, 64), (5, 1000), (2, 65)])
+def test_sums_of_the_gains_parts(n, d):
+    """256 terms: fp32 additions in chains of at most 31, so below 31 U of the sum of magnitudes; the rounded one is its rounding."""
+    parts = torch.randn(n, 256, d, generator=torch.Generator().manual_seed(d))
+    sums = torch.empty(n, d, device=DEV)
+    for code, dtype in ((F32, torch.float32), (BF16, torch.bfloat16)):
+        rounded = torch.empty(n, d, dtype=dtype, device=DEV)
+        _call("gain_sums", code, parts.to(DEV), sums, rounded, n, d)
+        ref, scale = parts.double().sum(1), parts.double().abs().sum(1)
+        assert float(((sums.cpu().double() - ref).abs() / scale).max()) < 31 * U
+        assert torch.equal(rounded, sums.to(dtype))
+
+
+@pytest.mark.parametrize("rows,widths", [(1, (16, 16, 16)), (37, (2048, 512, 512)), (300, (48, 16, 96))])
+def test_runs_of_columns_to_matrices_of_their_own(rows, widths):
+    src = torch.randint(0, 256, (rows, sum(widths)), dtype=torch.uint8, device=DEV)
+    out = [torch.empty(rows, w, dtype=torch.uint8, device=DEV) for w in widths]
+    fn = seco.load_library().dec_split_columns
+    P, I = C.c_void_p, C.c_int64
+    fn.argtypes = [P] * 4 + [I] * 4 + [P]
+    assert fn(src.data_ptr(), *(t.data_ptr() for t in out), rows, *widths, torch.cuda.current_stream().cuda_stream) == 0
+    for t, ref in zip(out, src.split(widths, 1)):
+        assert torch.equal(t, ref)
+    assert fn(src.data_ptr(), *(t.data_ptr() for t in out), rows, 24, 16, 16, torch.cuda.current_stream().cuda_stream) != 0
