@@ -145,8 +145,10 @@ struct Step {
   // both gradients of y = x w: grad[K, n] += x[M, K]^T d_y[M, n], d_x[M, K] = d_y w^T (u non-NULL: times silu'(u))
   void grads(Param& w, void* x, void* dx, void* dy, int64_t M, void* u = nullptr) {
     const int64_t K = w.w.size(0), n = w.w.size(1);
-    if (w.wanted && w.grad.defined() && own(w, DEC_GEMM_TN, K, n, M, K, n, n) && own(w, DEC_GEMM_NT, M, K, n, n, n, K)) {
-      check(lib.dec_gemm_grads(dy, ptr(w.w), dx, u, x, ptr(w.grad), M, K, n, s), "dec_gemm_grads");
+    if (w.wanted && own(w, DEC_GEMM_TN, K, n, M, K, n, n) && own(w, DEC_GEMM_NT, M, K, n, n, n, K)) {
+      const bool first = !w.grad.defined();
+      if (first) w.grad = at::empty({K, n}, w.w.options().requires_grad(false));
+      check((first ? lib.dec_gemm_first_grads : lib.dec_gemm_grads)(dy, ptr(w.w), dx, u, x, ptr(w.grad), M, K, n, s), "dec_gemm_grads");
     } else {
       add(w, x, dy, M);
       mm_bwd(dx, dy, w, M, u);

@@ -51,6 +51,8 @@ int dec_gemm(int form, int epilogue, const void* a, const void* b, void* c, void
 // Both gradients of y[M,n] = x[M,K] w[K,n], contiguous: dx[M,K] = dy w^T (u non-NULL: times silu'(u)), dw += x^T dy; what
 // dec_gemm computes for either, bit for bit, in one launch where that pays.  No output may overlap an operand of the other.
 int dec_gemm_grads(const void* dy, const void* w, void* dx, void* u, const void* x, void* dw, int64_t M, int64_t K, int64_t n, void* stream);
+// the same with dw = x^T dy
+int dec_gemm_first_grads(const void* dy, const void* w, void* dx, void* u, const void* x, void* dw, int64_t M, int64_t K, int64_t n, void* stream);
 #ifdef __cplusplus
 }
 #endif

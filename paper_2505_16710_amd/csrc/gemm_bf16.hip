@@ -492,18 +492,19 @@ template <typename A, typename B> int launch_pair(GemmArgs a, GemmArgs b, hipStr
 constexpr int kApart = 1;           // (no seco_status)
 // In one launch where the data gradient takes one of the small tiles and as many of its workgroups share a CU as by itself
 // (64 x 64 tiles with two slots: two; larger products would gain less than 5 %).  kApart: not
-template <int EPI> int pair(const GemmArgs& a, const GemmArgs& b, hipStream_t s) {
-  using Wide = Ring<128, 128, 1, 3, 4, false, false, kAdd>;
+// EPI_W: what becomes of the weight gradient: kAdd, or kStore for a step's first chunk
+template <int EPI, int EPI_W> int pair(const GemmArgs& a, const GemmArgs& b, hipStream_t s) {
+  using Wide = Ring<128, 128, 1, 3, 4, false, false, EPI_W>;
   using Two = Ring<64, 64, 2, 2, 2, true, true, EPI>;
   return with_way<true, true, EPI>(a, [&](auto way_a) {
     using A = typename decltype(way_a)::type;
     if constexpr (A::kThreads == 512 && A::kBM <= 64) {
-      return with_way<false, false, kAdd>(b, [&](auto way_b) {
+      return with_way<false, false, EPI_W>(b, [&](auto way_b) {
         using B = typename decltype(way_b)::type;
         if constexpr (!std::is_same_v<A, Two> && B::kThreads == 512)
           return launch_pair<A, B>(a, b, s);
         else if constexpr (std::is_same_v<A, Two> && std::is_same_v<B, Wide>)
-          return launch_pair<A, Ring<128, 128, 1, 2, 4, false, false, kAdd>>(a, b, s);     // (the same sums)
+          return launch_pair<A, Ring<128, 128, 1, 2, 4, false, false, EPI_W>>(a, b, s);     // (the same sums)
         else if constexpr (std::is_same_v<A, Two> && 2 * B::kSmem <= 160 * 1024 && B::kThreads == 512)
           return launch_pair<A, B>(a, b, s);
         else
@@ -545,8 +546,8 @@ extern "C" int dec_gemm(int form, int epilogue, const void* a, const void* b, vo
   return SECO_ERR_SHAPE;
 }
 
-extern "C" int dec_gemm_grads(const void* dy, const void* w, void* dx, void* u, const void* x, void* dw, int64_t M, int64_t K, int64_t n,
-                              void* stream) {
+static int gemm_grads(bool first, const void* dy, const void* w, void* dx, void* u, const void* x, void* dw, int64_t M, int64_t K, int64_t n,
+                      void* stream) {
   using namespace seco;
   if (!dec_gemm_supported(DEC_GEMM_NT, M, K, n, n, n, K) || !dec_gemm_supported(DEC_GEMM_TN, K, n, M, K, n, n)) return SECO_ERR_SHAPE;
   if (!dy || !w || !dx || !x || !dw) return SECO_ERR_NULL;
@@ -556,8 +557,16 @@ extern "C" int dec_gemm_grads(const void* dy, const void* w, void* dx, void* u, 
   const GemmArgs b{static_cast<const char*>(x), static_cast<const char*>(dy), static_cast<__bf16*>(dw), nullptr,
                    (int)K, (int)n, (int)M, (int)K, (int)n, (int)n, 0, 0, 0, 0, 0};
   hipStream_t s = static_cast<hipStream_t>(stream);
-  int rc = u ? pair<kSiluBwd>(a, b, s) : pair<kStore>(a, b, s);
+  int rc = first ? (u ? pair<kSiluBwd, kStore>(a, b, s) : pair<kStore, kStore>(a, b, s)) : u ? pair<kSiluBwd, kAdd>(a, b, s) : pair<kStore, kAdd>(a, b, s);
   if (rc != kApart) return rc;
   rc = u ? pick<true, true, kSiluBwd>(a, s) : pick<true, true, kStore>(a, s);
-  return rc ? rc : pick<false, false, kAdd>(b, s);
+  return rc ? rc : first ? pick<false, false, kStore>(b, s) : pick<false, false, kAdd>(b, s);
+}
+extern "C" int dec_gemm_grads(const void* dy, const void* w, void* dx, void* u, const void* x, void* dw, int64_t M, int64_t K, int64_t n,
+                              void* stream) {
+  return gemm_grads(false, dy, w, dx, u, x, dw, M, K, n, stream);
+}
+extern "C" int dec_gemm_first_grads(const void* dy, const void* w, void* dx, void* u, const void* x, void* dw, int64_t M, int64_t K, int64_t n,
+                                    void* stream) {
+  return gemm_grads(true, dy, w, dx, u, x, dw, M, K, n, stream);
 }

@@ -99,6 +99,28 @@ def test_both_gradients_in_one_launch(M, K, n, silu):
     assert torch.equal(dx, dx2) and torch.equal(dw, dw2)
 
 
+@pytest.mark.parametrize("M,K,n,silu", [
+    (512, 4096, 1024, True), (512, 1024, 4096, False), (447, 1024, 1024, False), (1, 64, 64, False), (33, 72, 128, True),
+    (320, 4096, 1024, True), (1024, 4096, 1024, True), (2050, 1024, 4096, False),
+])
+def test_first_gradients_in_one_launch(M, K, n, silu):
+    """As above where there is nothing to add to yet: what the weight gradient holds before does not matter."""
+    lib = seco.load_library()
+    P, I = C.c_void_p, C.c_int64
+    lib.dec_gemm.argtypes = [C.c_int, C.c_int, P, P, P, P] + [I] * 6 + [P]
+    lib.dec_gemm_first_grads.argtypes = [P] * 6 + [I] * 3 + [P]
+    g = torch.Generator(device=DEV).manual_seed(M + K + n)
+    dy, w, x, u = (torch.randn(*s, generator=g, device=DEV).to(torch.bfloat16) for s in ((M, n), (K, n), (M, K), (M, K)))
+    dx, dw = (torch.full(s, float("nan"), device=DEV, dtype=torch.bfloat16) for s in ((M, K), (K, n)))
+    dx2, dw2, s = dx.clone(), dw.clone(), torch.cuda.current_stream().cuda_stream
+    ptr = lambda t: t.data_ptr()
+    assert lib.dec_gemm(TN, STORE, ptr(x), ptr(dy), ptr(dw), None, K, n, M, K, n, n, s) == 0
+    assert lib.dec_gemm(NT, SILU_BWD if silu else STORE, ptr(dy), ptr(w), ptr(dx), ptr(u) if silu else None, M, K, n, n, n, K, s) == 0
+    assert lib.dec_gemm_first_grads(ptr(dy), ptr(w), ptr(dx2), ptr(u) if silu else None, ptr(x), ptr(dw2), M, K, n, s) == 0
+    torch.cuda.synchronize()
+    assert torch.equal(dx, dx2) and torch.equal(dw, dw2)
+
+
 def test_silu_and_its_derivative_at_every_u():
     """Both at all values of u, those whose e^-u leaves fp32 among their neighbours: u out of a product with the identity, one as
     the gradient behind the SiLU.  Error: half an ulp of bf16, 2^-8 of the value at most, and that of e^-u, whose argument is
