@@ -163,9 +163,16 @@ template <typename T, int V, int KB>
 __global__ __launch_bounds__(kThreads) void rmsnorm_bwd_rows_kernel(const T* x, const T* gain, const float* rstd, const T* d_h,
                                                                     const T* d_in, T* d_x, float* gain_part, int64_t rows, int64_t d) {
   constexpr int kWaves = kThreads / 64;
+  constexpr int kOld = (KB * 64 * V + kThreads - 1) / kThreads;
   __shared__ float sh[kWaves][KB * 64 * V];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  float dg[KB][V];
+  float* part = gain_part + (int64_t)blockIdx.x * d;
+  float dg[KB][V], old[kOld];                             // old: of this thread's elements of the share, under the rows' loads
+#pragma unroll
+  for (int k = 0; k < kOld; ++k) {
+    const int64_t c = k * kThreads + threadIdx.x;
+    old[k] = part[c < d ? c : d - 1];
+  }
   Vec<T, V> gv[KB];
 #pragma unroll
   for (int k = 0; k < KB; ++k) {
@@ -221,9 +228,11 @@ __global__ __launch_bounds__(kThreads) void rmsnorm_bwd_rows_kernel(const T* x, 
 #pragma unroll
     for (int j = 0; j < V; ++j) sh[wave][(k * 64 + lane) * V + j] = dg[k][j];
   __syncthreads();
-  float* part = gain_part + (int64_t)blockIdx.x * d;
-  for (int64_t c = threadIdx.x; c < d; c += kThreads) {
-    float f = part[c];
+#pragma unroll
+  for (int k = 0; k < kOld; ++k) {
+    const int64_t c = k * kThreads + threadIdx.x;
+    if (c >= d) break;
+    float f = old[k];
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) f += sh[w][c];
     part[c] = f;
