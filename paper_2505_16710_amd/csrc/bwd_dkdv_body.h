@@ -362,35 +362,31 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
     }
   };
 
-  // OWN: a wavefront takes 8 of the stage's 64 rows, 16 lanes per row; requested an iteration before the stage's copies
-  // and finished with them, so that nobody waits for either
-  struct OwnRows { bf16x8 o[2], d[2]; float lse[2]; };
+  // OWN: each wavefront of role B (the other one has the exponentials) takes 16 of the stage's rows: their LSE, requested an iteration
+  // before the stage's copies and left for role A with them, and the O rows, requested with the copies; delta, which role B needs an
+  // iteration after that, comes from those and the dO tile that has landed by then.
+  const int own_lr = 16 * cb + 4 * pi4((lane >> 2) & 3) + (lane & 3);      // this lane's row of a stage (pi4: no bank conflicts)
+  auto load_lse = [&](Pos x) { return p.lse[((int64_t)b * p.Hq + (int64_t)kvh * p.G + x.hg) * p.C + min(x.r0 + own_lr, p.C - 1)]; };
+  auto put_lse = [&](Pos x, int slot, float lse) {
+    SECO_LDS float* stat = reinterpret_cast<SECO_LDS float*>(smem + kStatRegion + slot * kStatBytes);
+    const float v = x.r0 + own_lr < p.C ? -lse / p.scale : -INFINITY;
+    if (lane < 16) stat[own_lr] = v;
+  };
+  struct OwnRows { bf16x8 o[4]; };
   auto load_own = [&](Pos x) {
     OwnRows w;
-    const __bf16* obase = static_cast<const __bf16*>(p.o) + b * p.os[0] + ((int64_t)kvh * p.G + x.hg) * p.os[1];
+    const __bf16* row = static_cast<const __bf16*>(p.o) + b * p.os[0] + ((int64_t)kvh * p.G + x.hg) * p.os[1] +
+                        (int64_t)min(x.r0 + own_lr, p.C - 1) * p.os[2] + (lane >> 4) * 8;
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int row = min(x.r0 + 8 * wave + 4 * i + (lane >> 4), p.C - 1);
-      w.o[i] = *reinterpret_cast<const bf16x8*>(obase + (int64_t)row * p.os[2] + (lane & 15) * 8);
-      w.d[i] = *reinterpret_cast<const bf16x8*>(dobase + x.hg * p.os[1] + (int64_t)row * p.os[2] + (lane & 15) * 8);
-      w.lse[i] = p.lse[((int64_t)b * p.Hq + (int64_t)kvh * p.G + x.hg) * p.C + row];
-    }
+    for (int t = 0; t < 4; ++t) w.o[t] = *reinterpret_cast<const bf16x8*>(row + 32 * t);
     return w;
   };
-  auto put_own = [&](Pos x, int slot, const OwnRows& w) {
-    SECO_LDS float* stat = reinterpret_cast<SECO_LDS float*>(smem + kStatRegion + slot * kStatBytes);
+  auto put_delta = [&](int slot, const OwnRows& w) {
+    bf16x8 d[4];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      float d = 0.f;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) d = __builtin_fmaf((float)w.o[i][j], (float)w.d[i][j], d);
-      d = row16_sum(d);   // (in the order of the dQ kernel, whose lanes hold every fourth chunk: the same bits)
-      const int lr = 8 * wave + 4 * i + (lane >> 4);
-      if ((lane & 15) == 0) {
-        stat[lr] = x.r0 + lr < p.C ? -w.lse[i] / p.scale : -INFINITY;
-        stat[BQ + lr] = -d;
-      }
-    }
+    for (int t = 0; t < 4; ++t) d[t] = lds_row8(smem + kDoRegion + slot * kTileBytes, own_lr, 4 * t + (lane >> 4));
+    const float x = row16_dot(w.o, d, lane);
+    if (lane < 16) reinterpret_cast<SECO_LDS float*>(smem + kStatRegion + slot * kStatBytes)[BQ + own_lr] = -x;
   };
 
   // lane-dependent parts of the LDS operand addresses (constant for the whole kernel)
@@ -448,7 +444,8 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
     cur.r0 += skip * BQ;
   }
   Pos nxt = advance(cur);
-  OwnRows own_rows;        // of the stage two ahead
+  OwnRows own_rows;        // of the next stage
+  float own_lse = 0.f;     // of the stage two ahead
   {
     const Src s0 = src_of(cur), s1 = src_of(nxt);
     copy_stage(cur, 0, s0);
@@ -457,11 +454,12 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
       copy_stage(nxt, 1, s1);
       if constexpr (!OWN) copy_stat(nxt, 1, s1);
     }
-    if constexpr (OWN) {
-      const OwnRows w0 = load_own(cur), w1 = load_own(n_iter > 1 ? nxt : cur);
-      own_rows = load_own(n_iter > 2 ? advance(nxt) : cur);
-      put_own(cur, 0, w0);
-      if (n_iter > 1) put_own(nxt, 1, w1);
+    if constexpr (OWN && role == 1) {
+      const float lse0 = load_lse(cur), lse1 = load_lse(n_iter > 1 ? nxt : cur);
+      own_lse = load_lse(n_iter > 2 ? advance(nxt) : cur);
+      own_rows = load_own(cur);
+      put_lse(cur, 0, lse0);
+      if (n_iter > 1) put_lse(nxt, 1, lse1);
     }
   }
   // (through the third slot's Q and dO tiles and the P buffers, which are empty until the barriers below)
@@ -473,6 +471,9 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
   if constexpr (role == 0) {
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) scores(0, cur.r0, rb, ROWS ? rr.log2w[cur.ri] / c2 : 0.f);
+  } else if constexpr (OWN) {
+    put_delta(0, own_rows);
+    if (n_iter > 1) own_rows = load_own(nxt);
   }
   __syncthreads();
   Pos nxt2 = advance(nxt);
@@ -519,11 +520,14 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
     auto issue_copies = [&]() {
       if (it + 2 < n_iter) {
         copy_stage(nxt2, slot2, src2);
-        if constexpr (OWN) {
-          put_own(nxt2, slot2, own_rows);
-          if (it + 3 < n_iter) own_rows = load_own(advance(nxt2));
-        } else {
-          copy_stat(nxt2, slot2, src2);
+        if constexpr (!OWN) copy_stat(nxt2, slot2, src2);
+      }
+      if constexpr (OWN && role == 1) {
+        if (it + 1 < n_iter) put_delta(slot1, own_rows);
+        if (it + 2 < n_iter) {
+          own_rows = load_own(nxt2);
+          put_lse(nxt2, slot2, own_lse);
+          if (it + 3 < n_iter) own_lse = load_lse(advance(nxt2));
         }
       }
     };

@@ -58,18 +58,12 @@ struct DqProducts16 {
 #pragma unroll
     for (int db = 0; db < 8; ++db) acc[db][0] = acc[db][1] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
-  // x y summed over head_dim, for each of the lane's rows (by chunk of 8 elements, then pairwise, as OWN in bwd_dkdv_body.h adds them)
-  static __device__ __forceinline__ float dot(int qb, const bf16x8 (&x)[8], const bf16x8 (&y)[8]) {
-    float part[4];
+  // delta of the lane's rows: O (as load_rows32 brings it) times dO (the same, and its fragments)
+  static __device__ __forceinline__ void row_dots(float (&d)[kRows], const bf16x8 (&o)[8], const bf16x8 (&)[8], const bf16x8 (&dof)[8], lds_char* own, int lane) {
+    bf16x8 of[8];
+    rows16_to_frags(of, o, own, lane);
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      part[t] = 0.f;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) part[t] = __builtin_fmaf((float)x[4 * qb + t][i], (float)y[4 * qb + t][i], part[t]);
-    }
-    float d = (part[0] + part[2]) + (part[1] + part[3]);
-    d += __shfl_xor(d, 32);
-    return d + __shfl_xor(d, 16);
+    for (int qb = 0; qb < 2; ++qb) d[qb] = row16_dot(of + 4 * qb, dof + 4 * qb, lane);
   }
   static __device__ __forceinline__ f32x4 piece(const Acc& acc, int i) { return acc[i >> 1][i & 1]; }
   static __device__ __forceinline__ void add(Acc& acc, int i, f32x4 x) { acc[i >> 1][i & 1] += x; }
@@ -103,16 +97,12 @@ struct DqProducts32 {
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[db][r] = 0.f;
   }
-  static __device__ __forceinline__ float dot(int, const bf16x8 (&x)[8], const bf16x8 (&y)[8]) {
-    float part[8];
-#pragma unroll
-    for (int t = 0; t < 8; ++t) {
-      part[t] = 0.f;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) part[t] = __builtin_fmaf((float)x[t][i], (float)y[t][i], part[t]);
-    }
-    const float d = ((part[0] + part[4]) + (part[2] + part[6])) + ((part[1] + part[5]) + (part[3] + part[7]));
-    return d + __shfl_xor(d, 32);
+  static __device__ __forceinline__ void row_dots(float (&d)[kRows], const bf16x8 (&o)[8], const bf16x8 (&d_o)[8], const bf16x8 (&)[8], lds_char* own, int lane) {
+    bf16x8 of[8], df[8];                       // (the operands of 16x16x32: the same bits)
+    rows16_to_frags(of, o, own, lane);
+    rows16_to_frags(df, d_o, own, lane);
+    const float lo = row16_dot(of, df, lane), hi = row16_dot(of + 4, df + 4, lane);
+    d[0] = lane & 16 ? hi : lo;
   }
   static __device__ __forceinline__ f32x4 piece(const Acc& acc, int i) {
     const f32x16& x = acc[i >> 2];
@@ -293,23 +283,21 @@ __device__ __forceinline__ void dq_bf16_body(const AttnParams& p, const SegTable
   }
   Cur nxt = cur;
   if (n_begin < n_end) copy_tile(cur.col, 0);
-  bf16x8 qf[8], dof[8], of[8];
+  bf16x8 qf[8], dof[8];
   lds_char* own = smem + 2 * kTileBytes + wave * 8192;      // of the second tile buffer, which is empty until the loop
   Products::frags(qf, qr, own, lane);
   Products::frags(dof, dor, own, lane);
-  Products::frags(of, orow, own, lane);
-  // delta = rowsum(dO * O), from the dO fragments and the matching O fragments.  It is also written to the workspace for the
+  // delta = rowsum(dO * O).  It is also written to the workspace for the
   // dK/dV kernel that follows on the same stream, negated, together with -LSE / s (the log-sum-exp in units of the unscaled dot
   // product): the two values that kernel starts its MFMA chains from.
   float lse_c[kRows], delta[kRows];
+  Products::row_dots(delta, orow, dor, dof, own, lane);
 #pragma unroll
   for (int qb = 0; qb < kRows; ++qb) {
-    const float d = Products::dot(qb, of, dof);
-    delta[qb] = d;
     lse_c[qb] = lse[qb] * kLog2e;
     if (kh == 0 && sp == 0 && g == 0 && row + 16 * qb < p.C) {
       const int64_t kept = ((int64_t)b * p.Hq + h) * p.stat_stride + p.stat_off + row + 16 * qb;
-      p.delta[kept] = -d;
+      p.delta[kept] = -delta[qb];
       p.nlse2[kept] = -lse[qb] / p.scale;
     }
   }

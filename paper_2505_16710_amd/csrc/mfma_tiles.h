@@ -211,6 +211,18 @@ __device__ __forceinline__ uint32_t opaque(uint32_t scalar) {
 }
 __device__ __forceinline__ void dma_wait_all() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
+// rowsum(x * y) of 16 rows, x and y as operands (lane l: some row for l % 16, the same in both; fragment t: chunk 4 t + l / 16): the
+// diagonal of X Y^T.  Every lane gets the sum of its row.  Four matrix instructions and a dozen others, where products in fp32 and a
+// sum over lanes take a hundred; all kernels that need such sums take this one, so that they have the same bits.
+__device__ __forceinline__ float row16_dot(const bf16x8* x, const bf16x8* y, int lane) {
+  f32x4 d = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int t = 0; t < 4; ++t) d = mfma16(x[t], y[t], d);
+  // element (i, i) is register i % 4 of lane i + 16 (i / 4)
+  const float mine = lane & 2 ? (lane & 1 ? d[3] : d[2]) : lane & 1 ? d[1] : d[0];
+  return __shfl(mine, (lane & 15) + 4 * (lane & 12));
+}
+
 // Make the compiler wait, here, for the load that produces `v`.  Used on operand fragments that are
 // loaded once before a loop: otherwise the first use inside the loop carries a conservative vmcnt wait
 // on every iteration, which would also wait for the asynchronous tile copies issued in the loop.
@@ -323,19 +335,6 @@ __device__ __forceinline__ void store_part16(const f32x4 (&acc)[8][2], float* ba
     const f32x4 v = *reinterpret_cast<SECO_LDS f32x4*>(own + r * kRow + (lane & 31) * 16);
     if (r < n_rows) *reinterpret_cast<f32x4*>(base + r * kHeadDim + (lane & 31) * 4) = v;
   }
-}
-
-// Sum over the 16 lanes of a row, by lane bits 3, 2, 1, 0; every lane gets it.  (Cross-lane reads of the vector ALU: rotations
-// by 8 and 4 equal exchanges of those bits once the sums repeat with that period.)
-__device__ __forceinline__ float row16_sum(float x) {
-  auto other = [](float v, auto ctrl) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), decltype(ctrl)::value, 0xf, 0xf, true));
-  };
-  x += other(x, std::integral_constant<int, 0x128>{});   // row_ror:8
-  x += other(x, std::integral_constant<int, 0x124>{});   // row_ror:4
-  x += other(x, std::integral_constant<int, 0x4e>{});    // quad_perm:[2,3,0,1]
-  x += other(x, std::integral_constant<int, 0xb1>{});    // quad_perm:[1,0,3,2]
-  return x;
 }
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
