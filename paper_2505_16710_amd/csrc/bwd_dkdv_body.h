@@ -225,19 +225,27 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
   constexpr int role = ROLE;
   const int cb = wave % NCB;
   // item -> (batch, kv head, column tile, share of the tile's iterations); the listed tiles come last in a unit
-  const int n_ctiles = seg.tile_begin[seg.n];
-  const int n_whole = n_ctiles - ts.plan.n_tiles;
+  const int n_whole = p.n_ctiles - ts.plan.n_tiles;
+  // (in long launches of its own the kernel is 0.5 - 1 % faster behind plain divisions: it is bound by power, and with another
+  // prologue the loop's registers come out otherwise)
   const int per_unit = n_whole + ts.plan.n_entries;
-  const int unit = item / per_unit, in_unit = item % per_unit;
+  const int unit = OWN ? over(item, p.by_unit) : item / per_unit, in_unit = item - unit * per_unit;
   int tile = in_unit, share = 0, n_shares = 1;
   if (in_unit >= n_whole) {
-    const int entry = in_unit - n_whole, pos = ts.plan.tile_of[entry];
+    // (whole words of the tables: there are no scalar loads of less, and through vector loads, one behind the other, this takes 0.5 us)
+    typedef uint32_t __attribute__((may_alias)) word;
+    const int entry = in_unit - n_whole;
+    const int pos = *reinterpret_cast<const word*>(ts.plan.tile_of + (entry & ~3)) >> (8 * (entry & 3)) & 0xff;
+    const word* first = reinterpret_cast<const word*>(ts.plan.first + (pos & ~1));
+    uint32_t lo = first[0], hi = first[1];
+    asm("" : "+s"(lo), "+s"(hi));                  // (or the compiler makes loads of half a word of them)
+    const int begin = pos & 1 ? lo >> 16 : lo & 0xffff;
     tile = n_whole + pos;
-    share = entry - ts.plan.first[pos];
-    n_shares = ts.plan.first[pos + 1] - ts.plan.first[pos];
+    share = entry - begin;
+    n_shares = (int)(pos & 1 ? hi & 0xffff : lo >> 16) - begin;
   }
   const bool divided = n_shares > 1;
-  const int kvh = unit % p.Hkv, b = unit / p.Hkv;
+  const int b = over(unit, p.by_Hkv), kvh = unit - b * p.Hkv;
   int si = 0;
   while (si + 1 < seg.n && tile >= seg.tile_begin[si + 1]) ++si;
   const int c0 = seg.col_begin[si] + (tile - seg.tile_begin[si]) * Cfg::kCols;
@@ -272,8 +280,16 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
   }
   // this workgroup's share of the tile's iterations: [it0, it0 + n_iter)
   const int n_all = n_rt * p.G;
-  const int it0 = divided ? (int)((int64_t)share * n_all / n_shares) : 0;
-  const int n_iter = (divided ? (int)((int64_t)(share + 1) * n_all / n_shares) : n_all) - it0;
+  int it0 = 0, n_iter = n_all;
+  if (divided) {
+    // share i begins at floor(i n_all / n_shares) = i each + floor(i rest / n_shares), i and rest less than 2^9: a product with the
+    // reciprocal is exact, half added (two 64-bit divisions are 300 instructions)
+    const int each = n_all / n_shares, rest = n_all - each * n_shares;
+    const float inv = __builtin_amdgcn_rcpf((float)n_shares);
+    auto begin = [&](int i) { return i * each + (int)(((float)(i * rest) + 0.5f) * inv); };
+    it0 = begin(share);
+    n_iter = begin(share + 1) - it0;
+  }
   // rows [x.r0, row_limit(x)) of a stage exist; the others are masked
   auto row_limit = [&](Pos x) { return ROWS ? rr.end[x.ri] : p.C; };
   auto advance = [&](Pos x) {
@@ -311,8 +327,27 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
     Src r;
     r.q = qbase + x.hg * p.qs[1] + (int64_t)x.r0 * p.qs[2];
     r.d_o = dobase + x.hg * p.os[1] + (int64_t)x.r0 * p.os[2];
-    r.stat = (wave_u == 0 ? p.nlse2 : p.delta) + stat_base + (int64_t)x.hg * p.stat_stride + x.r0;
+    r.stat = OWN ? p.lse + ((int64_t)b * p.Hq + (int64_t)kvh * p.G + x.hg) * p.C + x.r0
+                 : (wave_u == 0 ? p.nlse2 : p.delta) + stat_base + (int64_t)x.hg * p.stat_stride + x.r0;
     return r;
+  };
+  // (all rows, no runs) one stage on: BQ rows further, or, behind a head's last stage, back to the first stage's row
+  // of the next head
+  const int64_t q_step = (int64_t)BQ * p.qs[2], do_step = (int64_t)BQ * p.os[2];
+  const int64_t back_rows = (int64_t)(n_rt - 1) * BQ;
+  const int64_t q_wrap = p.qs[1] - back_rows * p.qs[2], do_wrap = p.os[1] - back_rows * p.os[2];
+  const int64_t stat_wrap = (OWN ? p.C : p.stat_stride) - back_rows;
+  auto stat_step = [&](Pos from, Pos to) { return to.hg != from.hg ? stat_wrap : (int64_t)BQ; };
+  auto next_src = [&](Src x, Pos from, Pos to) {
+    if constexpr (ROWS) {
+      x = src_of(to);
+    } else {
+      const bool wrap = to.hg != from.hg;
+      x.q += wrap ? q_wrap : q_step;
+      x.d_o += wrap ? do_wrap : do_step;
+      x.stat += stat_step(from, to);
+    }
+    return x;
   };
   auto copy_stage = [&](Pos x, int slot, const Src& src) {
     if (x.r0 + BQ <= row_limit(x)) {
@@ -325,14 +360,15 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
         dma16_sbase(q_src, q_lane_off[i], dst);
         dma16_sbase(do_src, do_lane_off[i], dst + kDoRegion);
       }
-    } else {
-      lds_char* qt = smem + slot * kTileBytes;
+    } else {                                   // rows past the chunk repeat its last one
+      const __bf16* q_src = src.q;
+      const __bf16* do_src = src.d_o;
 #pragma unroll
       for (int i = 0; i < kCopies; ++i) {
-        const int r = 4 * (wave + NW * i);
-        const int src_row = min(x.r0 + r + (lane >> 4), p.C - 1);
-        dma4rows(qt, r, qbase + x.hg * p.qs[1] + (int64_t)src_row * p.qs[2], lane);
-        dma4rows(qt + kDoRegion, r, dobase + x.hg * p.os[1] + (int64_t)src_row * p.os[2], lane);
+        const uint32_t dst = lds_wave + slot * kTileBytes + i * (4 * NW * kRowBytes);
+        const uint32_t past = max(4 * (wave + NW * i) + (lane >> 4) + x.r0 - (p.C - 1), 0);
+        dma16_sbase(q_src, q_lane_off[i] - __umul24(past, (uint32_t)p.qs[2] * 2u), dst);
+        dma16_sbase(do_src, do_lane_off[i] - __umul24(past, (uint32_t)p.os[2] * 2u), dst + kDoRegion);
       }
     }
   };
@@ -366,19 +402,21 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
   // before the stage's copies and left for role A with them, and the O rows, requested with the copies; delta, which role B needs an
   // iteration after that, comes from those and the dO tile that has landed by then.
   const int own_lr = 16 * cb + 4 * pi4((lane >> 2) & 3) + (lane & 3);      // this lane's row of a stage (pi4: no bank conflicts)
-  auto load_lse = [&](Pos x) { return p.lse[((int64_t)b * p.Hq + (int64_t)kvh * p.G + x.hg) * p.C + min(x.r0 + own_lr, p.C - 1)]; };
+  auto own_row = [&](Pos x) { return (uint32_t)min(own_lr, p.C - 1 - x.r0); };
+  auto load_lse = [&](Pos x, const float* stat) { return stat[own_row(x)]; };   // stat: of the stage's first row
   auto put_lse = [&](Pos x, int slot, float lse) {
     SECO_LDS float* stat = reinterpret_cast<SECO_LDS float*>(smem + kStatRegion + slot * kStatBytes);
     const float v = x.r0 + own_lr < p.C ? -lse / p.scale : -INFINITY;
     if (lane < 16) stat[own_lr] = v;
   };
   struct OwnRows { bf16x8 o[4]; };
-  auto load_own = [&](Pos x) {
+  const int64_t o_from_do = static_cast<const char*>(p.o) - static_cast<const char*>(p.d_o);   // (their strides are the same)
+  auto load_own = [&](Pos x, const Src& src) {
     OwnRows w;
-    const __bf16* row = static_cast<const __bf16*>(p.o) + b * p.os[0] + ((int64_t)kvh * p.G + x.hg) * p.os[1] +
-                        (int64_t)min(x.r0 + own_lr, p.C - 1) * p.os[2] + (lane >> 4) * 8;
+    global_bytes from = scalar_address(reinterpret_cast<const char*>(src.d_o) + o_from_do);
+    const uint32_t off = __umul24(own_row(x), (uint32_t)p.os[2] * 2u) + (uint32_t)(lane >> 4) * 16u;
 #pragma unroll
-    for (int t = 0; t < 4; ++t) w.o[t] = *reinterpret_cast<const bf16x8*>(row + 32 * t);
+    for (int t = 0; t < 4; ++t) w.o[t] = global_load16(from, off + 64u * t);
     return w;
   };
   auto put_delta = [&](int slot, const OwnRows& w) {
@@ -446,8 +484,10 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
   Pos nxt = advance(cur);
   OwnRows own_rows;        // of the next stage
   float own_lse = 0.f;     // of the stage two ahead
+  Pos nxt2 = advance(nxt);
+  const Src s0 = src_of(cur), s1 = next_src(s0, cur, nxt);
+  Src src2 = next_src(s1, nxt, nxt2);
   {
-    const Src s0 = src_of(cur), s1 = src_of(nxt);
     copy_stage(cur, 0, s0);
     if constexpr (!OWN) copy_stat(cur, 0, s0);
     if (n_iter > 1) {
@@ -455,9 +495,10 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
       if constexpr (!OWN) copy_stat(nxt, 1, s1);
     }
     if constexpr (OWN && role == 1) {
-      const float lse0 = load_lse(cur), lse1 = load_lse(n_iter > 1 ? nxt : cur);
-      own_lse = load_lse(n_iter > 2 ? advance(nxt) : cur);
-      own_rows = load_own(cur);
+      const float lse0 = load_lse(cur, s0.stat);
+      const float lse1 = n_iter > 1 ? load_lse(nxt, s1.stat) : 0.f;
+      if (n_iter > 2) own_lse = load_lse(nxt2, src2.stat);
+      own_rows = load_own(cur, s0);
       put_lse(cur, 0, lse0);
       if (n_iter > 1) put_lse(nxt, 1, lse1);
     }
@@ -473,17 +514,9 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
     for (int rb = 0; rb < RB; ++rb) scores(0, cur.r0, rb, ROWS ? rr.log2w[cur.ri] / c2 : 0.f);
   } else if constexpr (OWN) {
     put_delta(0, own_rows);
-    if (n_iter > 1) own_rows = load_own(nxt);
+    if (n_iter > 1) own_rows = load_own(nxt, s1);
   }
   __syncthreads();
-  Pos nxt2 = advance(nxt);
-  Src src2 = src_of(nxt2);
-  // (all rows, no runs) one stage on: BQ rows further, or, behind a head's last stage, back to the first stage's row
-  // of the next head
-  const int64_t q_step = (int64_t)BQ * p.qs[2], do_step = (int64_t)BQ * p.os[2];
-  const int64_t back_rows = (int64_t)(n_rt - 1) * BQ;
-  const int64_t q_wrap = p.qs[1] - back_rows * p.qs[2], do_wrap = p.os[1] - back_rows * p.os[2];
-  const int64_t stat_wrap = p.stat_stride - back_rows;
 
   // One operand buffer x[8] rotates through the four MFMA chains of an iteration: while a chain consumes x[t], the
   // operand of the next chain is requested into the same register ("comes in behind").  The last chain of an
@@ -525,9 +558,9 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
       if constexpr (OWN && role == 1) {
         if (it + 1 < n_iter) put_delta(slot1, own_rows);
         if (it + 2 < n_iter) {
-          own_rows = load_own(nxt2);
+          own_rows = load_own(nxt2, src2);
           put_lse(nxt2, slot2, own_lse);
-          if (it + 3 < n_iter) own_lse = load_lse(advance(nxt2));
+          if (const Pos nxt3 = advance(nxt2); it + 3 < n_iter) own_lse = load_lse(nxt3, src2.stat + stat_step(nxt2, nxt3));
         }
       }
     };
@@ -652,14 +685,7 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
     nxt = nxt2;
     {
       const Pos adv = advance(nxt2);
-      if constexpr (ROWS) {
-        src2 = src_of(adv);
-      } else {
-        const bool wrap = adv.hg != nxt2.hg;
-        src2.q += wrap ? q_wrap : q_step;
-        src2.d_o += wrap ? do_wrap : do_step;
-        src2.stat += wrap ? stat_wrap : (int64_t)BQ;
-      }
+      src2 = next_src(src2, nxt2, adv);
       nxt2 = adv;
     }
     slot = slot1;

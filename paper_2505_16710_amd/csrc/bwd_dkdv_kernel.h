@@ -25,11 +25,12 @@ __global__ __launch_bounds__(NCB * 128, 2) void dkdv_bf16_kernel(AttnParams p, S
 
 template <bool ROWS, class Products>
 int launch_dkdv_kernel(const AttnParams& p, const SegTable& seg, const TailSplit& ts, const RowRuns& rr, hipStream_t s) {
-  const int total = p.Hkv * p.B * (seg.tile_begin[seg.n] - ts.plan.n_tiles + ts.plan.n_entries);
+  AttnParams pl = p;
+  const int per_unit = for_column_tiles(pl, seg, ts), total = p.Hkv * p.B * per_unit;
   auto kern = dkdv_bf16_kernel<kColTileBf16 / 32, SECO_DKDV_RB, ROWS, Products>;
   static std::atomic<uint64_t> ready{0};
   if (!allow_lds(ready, reinterpret_cast<const void*>(kern), Cfg::kSmemBytes)) return SECO_ERR_LAUNCH;
-  hipLaunchKernelGGL(kern, dim3(xcd_grid(total, p.B * p.Hkv)), dim3(Cfg::kThreads), Cfg::kSmemBytes, s, p, seg, ts, rr, total);
+  hipLaunchKernelGGL(kern, dim3(xcd_grid(total, p.B * p.Hkv)), dim3(Cfg::kThreads), Cfg::kSmemBytes, s, pl, seg, ts, rr, total);
   return launch_status();
 }
 

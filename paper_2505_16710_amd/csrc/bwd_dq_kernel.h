@@ -24,7 +24,7 @@ int launch_dq_kernel(const AttnParams& p, const SegTable& seg, int n_mtiles, int
   {
     ProfScope prof(kKernelDq, s);
     const int units = SPLIT == kWholeTiles ? p.B * p.Hkv : 8, first = SPLIT == kShares ? p.B * p.Hkv * p.rows_whole : 0;
-    hipLaunchKernelGGL(kern, dim3(xcd_grid(first, units) + xcd_grid(total - first, units)), dim3(256 * KH), smem, s, p, seg, n_mtiles, total);
+    hipLaunchKernelGGL(kern, dim3(xcd_grid(first, units) + xcd_grid(total - first, units)), dim3(256 * KH), smem, s, for_launch(p, n_mtiles), seg, n_mtiles, total);
   }
   return launch_status();
 }

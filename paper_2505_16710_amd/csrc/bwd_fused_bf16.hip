@@ -17,6 +17,7 @@
 //   16/8 x 2  29, 2 of 64  24.5 -> 14.8     16/2 188, 8 of 35  51 -> 38
 //   32/8  32, 2 of 64      28.1 -> 15.8     32/8 128, 4 of 32  41 -> 23
 //   32/8 256, 4 of 16      51 -> 38         8/8   64, 8 of 64  25.4 -> 15.2
+#include <cstddef>
 #include <type_traits>
 
 #include "bwd_dkdv_body.h"
@@ -29,6 +30,7 @@ namespace {
 using Cfg = DkdvCfg<kColTileBf16 / 32, SECO_DKDV_RB>;
 constexpr int kNcb = kColTileBf16 / 32, kDqSmem = 4 * BNW * 2 * kRowBytes;
 constexpr int kSmem = Cfg::kSmemBytes > kDqSmem ? Cfg::kSmemBytes : kDqSmem;
+static_assert(offsetof(TailSplit, plan.tile_of) % 4 == 0 && offsetof(TailSplit, plan.first) % 4 == 0, "tables read in words");
 static_assert(Cfg::kThreads == 512, "both passes in workgroups of 8 wavefronts");
 
 // The first first_grid workgroups are those of dK/dV (kv_first: the pass with the longer workgroups) or of dQ; both numbers are rounded up to whole XCD rounds.
@@ -91,10 +93,12 @@ int launch(const AttnParams& p, const SegTable& seg, const TailSplit& ts, const 
   auto kern = bwd_fused_bf16_kernel<SPLIT, RUNS>;
   static std::atomic<uint64_t> ready{0};
   if (!allow_lds(ready, reinterpret_cast<const void*>(kern), kSmem)) return SECO_ERR_LAUNCH;
+  AttnParams pl = for_launch(p, n_mtiles);
+  for_column_tiles(pl, seg, ts);
   const int first = xcd_grid(kv_first ? kv_total : dq_total), second = xcd_grid(kv_first ? dq_total : kv_total);
   {
     ProfScope prof(kKernelBwd, s);
-    hipLaunchKernelGGL(kern, dim3(first + second), dim3(512), kSmem, s, p, seg, ts, n_mtiles, kv_total, dq_total, first,
+    hipLaunchKernelGGL(kern, dim3(first + second), dim3(512), kSmem, s, pl, seg, ts, n_mtiles, kv_total, dq_total, first,
                        kv_first ? 1 : 0, runs);
   }
   return launch_status();

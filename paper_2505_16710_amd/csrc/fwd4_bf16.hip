@@ -43,11 +43,9 @@ __global__ __launch_bounds__(256, 2) void fwd4_bf16_kernel(AttnParams p, int n_m
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int l16 = lane & 15, g = lane >> 4, pg = pi4(g);
   // item -> (batch, kv head, row tile (heavy first), head within the group)
-  const int hg = item % p.G;
-  int rest = item / p.G;
-  const int mt = n_mtiles - 1 - rest % n_mtiles;
-  rest /= n_mtiles;
-  const int kvh = rest % p.Hkv, b = rest / p.Hkv, h = kvh * p.G + hg;
+  const int tiles = over(item, p.by_G), hg = item - tiles * p.G, rest = over(tiles, p.by_tiles);
+  const int mt = n_mtiles - 1 - (tiles - rest * n_mtiles);
+  const int b = over(rest, p.by_Hkv), kvh = rest - b * p.Hkv, h = kvh * p.G + hg;
   const int m0 = mt * BM + wave * 32;          // first chunk-local row of this wavefront
 
   const int kv_len = p.q_start + p.C;
@@ -275,7 +273,7 @@ int launch(const AttnParams& p, int n_mtiles, int total, hipStream_t s) {
   static std::atomic<uint64_t> ready{0};
   if (!allow_lds(ready, reinterpret_cast<const void*>(fwd4_bf16_kernel<TURNS>), smem)) return SECO_ERR_LAUNCH;
   ProfScope prof(kKernelFwd, s);
-  hipLaunchKernelGGL(fwd4_bf16_kernel<TURNS>, dim3(xcd_grid(total, p.B * p.Hkv)), dim3(256), smem, s, p, n_mtiles, total);
+  hipLaunchKernelGGL(fwd4_bf16_kernel<TURNS>, dim3(xcd_grid(total, p.B * p.Hkv)), dim3(256), smem, s, for_launch(p, n_mtiles), n_mtiles, total);
   return launch_status();
 }
 

@@ -64,10 +64,10 @@ __global__ __launch_bounds__(512, 2) void fwd8_bf16_kernel(AttnParams p, int n_m
     int rest;
     if constexpr (SPLIT == kDivided) {
       n_sp = p.n_splits;
-      sp = item % n_sp;
-      rest = item / n_sp;
-      mt = n_mtiles - 1 - rest % n_mtiles;
-      rest /= n_mtiles;
+      const int tiles = over(item, p.by_splits);
+      sp = item - tiles * n_sp;
+      rest = over(tiles, p.by_tiles);
+      mt = n_mtiles - 1 - (tiles - rest * n_mtiles);
     } else {
       const int n_cut = n_mtiles - p.rows_whole, n_first = p.B * p.Hkv * p.rows_whole;   // (the whole tiles come first)
       if (item < n_first) {
@@ -82,10 +82,10 @@ __global__ __launch_bounds__(512, 2) void fwd8_bf16_kernel(AttnParams p, int n_m
         mt = n_cut - 1 - e / n_sp;
       }
     }
-    kvh = rest % p.Hkv;
-    b = rest / p.Hkv;
+    b = over(rest, p.by_Hkv);
+    kvh = rest - b * p.Hkv;
     const int v0 = mt * BM + rb * 32;          // packed row: head v0 / Cpad of the group, row v0 % Cpad
-    int hg = v0 / p.Cpad;
+    int hg = over(v0, p.by_Cpad);
     m0 = v0 - hg * p.Cpad;
     if (hg >= p.G) {                           // past the last head of the group: idle wavefront (m0 >= C)
       hg = p.G - 1;
@@ -94,12 +94,10 @@ __global__ __launch_bounds__(512, 2) void fwd8_bf16_kernel(AttnParams p, int n_m
     h = kvh * p.G + hg;
   } else {
     // item -> (batch, kv head, row tile (heavy first), head within the group)
-    const int hg = item % p.G;
-    int rest = item / p.G;
-    mt = n_mtiles - 1 - rest % n_mtiles;
-    rest /= n_mtiles;
-    kvh = rest % p.Hkv;
-    b = rest / p.Hkv;
+    const int tiles = over(item, p.by_G), hg = item - tiles * p.G, rest = over(tiles, p.by_tiles);
+    mt = n_mtiles - 1 - (tiles - rest * n_mtiles);
+    b = over(rest, p.by_Hkv);
+    kvh = rest - b * p.Hkv;
     h = kvh * p.G + hg;
     m0 = mt * BM + rb * 32;
   }
@@ -118,7 +116,7 @@ __global__ __launch_bounds__(512, 2) void fwd8_bf16_kernel(AttnParams p, int n_m
     int rows_end = 0;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int v = mt * BM + r * 32, hh = v / p.Cpad, mm = v - hh * p.Cpad;
+      const int v = mt * BM + r * 32, hh = over(v, p.by_Cpad), mm = v - hh * p.Cpad;
       if (hh < p.G && mm < p.C) rows_end = max(rows_end, min(mm + 32, p.C));
     }
     wg_kv_end = rows_end ? p.q_start + rows_end : 0;
@@ -134,7 +132,7 @@ __global__ __launch_bounds__(512, 2) void fwd8_bf16_kernel(AttnParams p, int n_m
     n_end = (sp + 1) * n_tiles / n_sp;
   }
   if constexpr (SPLIT == kDivided) {
-    const int per = (n_tiles + p.n_splits - 1) / p.n_splits;
+    const int per = over(n_tiles + p.n_splits - 1, p.by_splits);
     n_begin = sp * per;
     n_end = min(n_tiles, n_begin + per);
     if (n_begin >= n_end) {                    // nothing to do for this split: an empty partial (max = -inf)
@@ -164,15 +162,16 @@ __global__ __launch_bounds__(512, 2) void fwd8_bf16_kernel(AttnParams p, int n_m
         dma16_sbase(kt_src, lane_off[i], dst);
         dma16_sbase(vt_src, lane_off[i], dst + kTileBytes);
       }
-    } else {
-      lds_char* kt = smem + buf * 2 * kTileBytes;
-      lds_char* vt = kt + kTileBytes;
+    } else {                                   // rows past the cache's end repeat its last one
+      const __bf16* kt_src = kbase + (int64_t)n * BN * p.kvs[2];
+      const __bf16* vt_src = vbase + (int64_t)n * BN * p.kvs[2];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int r = 4 * (wave + 4 * KH * i);
-        const int64_t off = (int64_t)min(n * BN + r + (lane >> 4), kv_len - 1) * p.kvs[2];
-        dma4rows(kt, r, kbase + off, lane);
-        dma4rows(vt, r, vbase + off, lane);
+        const uint32_t dst = lds_wave + buf * 2 * kTileBytes + i * (16 * KH * kRowBytes);
+        const uint32_t past = max(4 * (wave + 4 * KH * i) + (lane >> 4) + n * BN - (kv_len - 1), 0);
+        const uint32_t off = lane_off[i] - __umul24(past, (uint32_t)p.kvs[2] * 2u);
+        dma16_sbase(kt_src, off, dst);
+        dma16_sbase(vt_src, off, dst + kTileBytes);
       }
     }
   };
@@ -369,7 +368,7 @@ int launch_fwd8(const AttnParams& p, int n_mtiles, int total, hipStream_t s) {
   {
     ProfScope prof(kKernelFwd, s);
     const int units = SPLIT == kWholeTiles ? p.B * p.Hkv : 8, first = SPLIT == kShares ? p.B * p.Hkv * p.rows_whole : 0;
-    hipLaunchKernelGGL(kern, dim3(xcd_grid(first, units) + xcd_grid(total - first, units)), dim3(512), smem, s, p, n_mtiles, total);
+    hipLaunchKernelGGL(kern, dim3(xcd_grid(first, units) + xcd_grid(total - first, units)), dim3(512), smem, s, for_launch(p, n_mtiles), n_mtiles, total);
   }
   return launch_status();
 }

@@ -36,13 +36,13 @@ __global__ __launch_bounds__(kWaves * 64, 2) void fwd_small_bf16_kernel(AttnPara
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, g = lane >> 5;
   // item -> (batch, kv head), share of the cache, row tile: the tiles that read the same rows run side by side on one XCD
-  const int shared = item / n_mtiles, r0 = (item - shared * n_mtiles) * 32;
-  const int unit = shared / p.n_splits, sp = shared - unit * p.n_splits, b = unit / p.Hkv, kvh = unit - b * p.Hkv;
+  const int shared = over(item, p.by_tiles), r0 = (item - shared * n_mtiles) * 32;
+  const int unit = over(shared, p.by_splits), sp = shared - unit * p.n_splits, b = over(unit, p.by_Hkv), kvh = unit - b * p.Hkv;
   const int n_rows = p.G * p.C, kv_len = p.q_start + p.C;
   const __bf16* kbase = static_cast<const __bf16*>(p.k) + b * p.kvs[0] + kvh * p.kvs[1];
   const __bf16* vbase = static_cast<const __bf16*>(p.v) + b * p.kvs[0] + kvh * p.kvs[1];
   // blocks of this workgroup: [first, last), dealt to the wavefronts in turn
-  const int n_blocks = (kv_len + kBlock - 1) / kBlock, per = (n_blocks + p.n_splits - 1) / p.n_splits;
+  const int n_blocks = (kv_len + kBlock - 1) / kBlock, per = over(n_blocks + p.n_splits - 1, p.by_splits);
   const int first = sp * per, last = min(n_blocks, first + per);
   lds_char* kt = smem + wave * kOwn;
   lds_char* vt = kt + kBlock * kRowBytes;
@@ -52,20 +52,23 @@ __global__ __launch_bounds__(kWaves * 64, 2) void fwd_small_bf16_kernel(AttnPara
     lane_off[i] = (uint32_t)((lane >> 4) * (p.kvs[2] * 2)) + (uint32_t)(((lane & 15) ^ swz(4 * i + (lane >> 4))) << 4);
   // eight copies of four rows each: one block of K (dst kt) or V (dst vt)
   auto copy_block = [&](const __bf16* base, lds_char* dst, int blk) {
+    const uint32_t d = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)dst);
     if ((blk + 1) * kBlock <= kv_len) {
-      const uint32_t d = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)dst);
 #pragma unroll
       for (int i = 0; i < 8; ++i)
         dma16_sbase(base + (int64_t)(blk * kBlock + 4 * i) * p.kvs[2], lane_off[i & 3], d + i * 4 * kRowBytes);
-    } else {
+    } else {                                   // rows past the cache's end repeat its last one
+      const __bf16* first_row = base + (int64_t)(blk * kBlock) * p.kvs[2];
 #pragma unroll
-      for (int i = 0; i < 8; ++i)
-        dma4rows(dst, 4 * i, base + (int64_t)min(blk * kBlock + 4 * i + (lane >> 4), kv_len - 1) * p.kvs[2], lane);
+      for (int i = 0; i < 8; ++i) {            // (4 i rows on less those past the end: not negative, lane_off being that of lane / 16 rows)
+        const int back = max(4 * i + (lane >> 4) + blk * kBlock - (kv_len - 1), 0);
+        dma16_sbase(first_row, lane_off[i & 3] + __umul24(4 * i, (uint32_t)p.kvs[2] * 2u) - __umul24(back, (uint32_t)p.kvs[2] * 2u), d + i * 4 * kRowBytes);
+      }
     }
   };
   // packed row r: head r / C of the group, chunk row r % C; rows past the last repeat it and are not stored
   {
-    const int r = min(r0 + 4 * wave + (lane >> 4), n_rows - 1), hg = r / p.C;
+    const int r = min(r0 + 4 * wave + (lane >> 4), n_rows - 1), hg = over(r, p.by_C);
     dma4rows(smem + kQTile, 4 * wave, static_cast<const __bf16*>(p.q) + b * p.qs[0] + (kvh * p.G + hg) * p.qs[1] +
                                           (int64_t)(r - hg * p.C) * p.qs[2], lane);
   }
@@ -74,7 +77,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void fwd_small_bf16_kernel(AttnPara
     copy_block(kbase, kt, blk);
     copy_block(vbase, vt, blk);
   }
-  const int my_row = min(r0 + l32, n_rows - 1), qpos = p.q_start + my_row % p.C;
+  const int my_row = min(r0 + l32, n_rows - 1), qpos = p.q_start + my_row - over(my_row, p.by_C) * p.C;
   const float c = p.scale * kLog2e;
   f32x16 o[4];
 #pragma unroll
@@ -181,7 +184,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void fwd_small_bf16_kernel(AttnPara
 #pragma unroll
     for (int w = 0; w < kWaves; ++w)
       sum += *reinterpret_cast<SECO_LDS f32x4*>(smem + w * kOwn + (q >> 1) * kTurnStep + ((q & 1) * 32 + r) * 16);
-    const int hg = (r0 + r) / p.C, row = r0 + r - hg * p.C, h = kvh * p.G + hg;
+    const int hg = over(r0 + r, p.by_C), row = r0 + r - hg * p.C, h = kvh * p.G + hg;
     const int64_t rowid = ((int64_t)b * p.Hq + h) * p.C + row;
     if (p.n_splits > 1) {
       const int64_t part_row = (int64_t)sp * p.B * p.Hq * p.C + rowid;
@@ -237,7 +240,7 @@ int launch_fwd_small_bf16(AttnParams p, int max_splits, hipStream_t s) {
   if (!allow_lds(ready, reinterpret_cast<const void*>(fwd_small_bf16_kernel), kSmem)) return SECO_ERR_LAUNCH;
   {
     ProfScope prof(kKernelFwd, s);
-    hipLaunchKernelGGL(fwd_small_bf16_kernel, dim3(xcd_grid(total)), dim3(kWaves * 64), kSmem, s, p, n_mtiles, total);
+    hipLaunchKernelGGL(fwd_small_bf16_kernel, dim3(xcd_grid(total)), dim3(kWaves * 64), kSmem, s, for_launch(p, n_mtiles), n_mtiles, total);
   }
   const int rc = launch_status();
   return rc || p.n_splits == 1 ? rc : launch_fwd_merge(p, s);

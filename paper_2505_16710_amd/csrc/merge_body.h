@@ -50,8 +50,8 @@ __device__ __forceinline__ bool merge_partials(const f32x4 (&x)[K], int n_splits
   return true;
 }
 // element offset of row `rowid` = (b * Hq + h) * C + row of a strided [B, Hq, C, 128] tensor
-__device__ __forceinline__ int64_t row_offset(const AttnParams& p, int64_t rowid, const int64_t s[3]) {
-  const int bh = (int)(rowid / p.C), row = (int)(rowid - (int64_t)bh * p.C), b = bh / p.Hq;
+__device__ __forceinline__ int64_t row_offset(const AttnParams& p, int64_t rowid, const int64_t s[3]) {   // (less than 2^31 rows)
+  const int bh = over((int)rowid, p.by_C), row = (int)rowid - bh * p.C, b = over(bh, p.by_Hq);
   return b * s[0] + (bh - b * p.Hq) * s[1] + (int64_t)row * s[2];
 }
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));

@@ -223,6 +223,17 @@ __device__ __forceinline__ float row16_dot(const bf16x8* x, const bf16x8* y, int
   return __shfl(mine, (lane & 15) + 4 * (lane & 12));
 }
 
+// An address that is the same for all lanes of a wavefront, in scalar registers, and a load from there with a 32-bit lane offset
+typedef __attribute__((address_space(1))) const char* global_bytes;
+__device__ __forceinline__ global_bytes scalar_address(const void* p) {
+  const uint64_t at = (uint64_t)(uintptr_t)p;
+  return (global_bytes)((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(at >> 32)) << 32 |
+                        (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)at));
+}
+__device__ __forceinline__ bf16x8 global_load16(global_bytes from, uint32_t lane_off) {
+  return *reinterpret_cast<__attribute__((address_space(1))) const bf16x8*>(from + lane_off);
+}
+
 // Make the compiler wait, here, for the load that produces `v`.  Used on operand fragments that are
 // loaded once before a loop: otherwise the first use inside the loop carries a conservative vmcnt wait
 // on every iteration, which would also wait for the asynchronous tile copies issued in the loop.
@@ -237,10 +248,16 @@ __device__ __forceinline__ void settle8(const bf16x8 (&v)[8]) {
 // Loaded straight into their layout the fragments are 32 bytes of each of 32 rows per instruction, which the address
 // unit takes one cache line at a time: about 57 cycles per instruction and CU, 11e3 cycles before a dQ workgroup of
 // 8 wavefronts could start; whole rows take 16.
+// (base, row0: the same for a wavefront.  From a scalar address and 32-bit lane offsets, a row stride being less than 2^24 bytes: with
+// 64-bit row numbers times strides the 24 loads of a dQ wavefront are 240 vector instructions.)
 __device__ __forceinline__ void load_rows32(bf16x8 (&x)[8], const __bf16* base, int64_t stride, int row0, int last_row, int lane) {
+  const int first = __builtin_amdgcn_readfirstlane(min(row0, last_row));
+  global_bytes from = scalar_address(base + first * stride);
 #pragma unroll
-  for (int j = 0; j < 8; ++j)
-    x[j] = *reinterpret_cast<const bf16x8*>(base + (int64_t)min(row0 + 4 * j + (lane >> 4), last_row) * stride + (lane & 15) * 8);
+  for (int j = 0; j < 8; ++j) {
+    const uint32_t r = (uint32_t)min(4 * j + (lane >> 4), last_row - first);
+    x[j] = global_load16(from, __umul24(r, (uint32_t)stride * 2u) + (uint32_t)(lane & 15) * 16u);
+  }
 }
 __device__ __forceinline__ void rows32_to_frags(bf16x8 (&f)[8], const bf16x8 (&x)[8], lds_char* own8k, int lane) {
 #pragma unroll

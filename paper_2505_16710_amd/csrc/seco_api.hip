@@ -66,6 +66,13 @@ AttnParams make_params(const seco_desc* d) {
   p.q_start = d->q_start;
   p.G = d->n_q_heads / d->n_kv_heads;
   p.scale = d->softmax_scale;
+  p.n_splits = 1;
+  p.Cpad = (d->chunk_len + 31) / 32 * 32;
+  p.by_C = make_div(p.C);
+  p.by_Cpad = make_div(p.Cpad);
+  p.by_Hq = make_div(p.Hq);
+  p.by_Hkv = make_div(p.Hkv);
+  p.by_G = make_div(p.G);
   p.stat_stride = d->chunk_len;
   p.stat_off = 0;
   for (int i = 0; i < 3; ++i) {
@@ -199,7 +206,6 @@ int backward(const seco_desc* d, const void* q, const void* k, const void* v, co
   p.nlse2 = d->dtype == SECO_BF16 ? reinterpret_cast<float*>(static_cast<char*>(ws) + row_stat_bytes(d)) : nullptr;
   p.gk = gk; p.gv = gv;
   p.n_splits = splits_for(d);
-  p.Cpad = (d->chunk_len + 31) / 32 * 32;
   p.part = reinterpret_cast<float*>(static_cast<char*>(ws) + delta_bytes(d));
   use_tail_part(p, d);
   hipStream_t s = static_cast<hipStream_t>(stream);
@@ -307,7 +313,6 @@ int backward_gather(const seco_desc* d, const void* q_rows, const void* k, const
   p.stat_off = d->q_start;
   p.gk = gk; p.gv = gv;
   p.n_splits = splits_for(d);
-  p.Cpad = (d->chunk_len + 31) / 32 * 32;
   p.part = reinterpret_cast<float*>(static_cast<char*>(ws) + delta_bytes(d));
   use_tail_part(p, d);
   hipStream_t s = static_cast<hipStream_t>(stream);
@@ -315,6 +320,7 @@ int backward_gather(const seco_desc* d, const void* q_rows, const void* k, const
   // dK/dV: the query rows are the chunk's and the later ones, the cache rows the chunk's own
   AttnParams pr = p;
   pr.C = (int)rows;
+  pr.by_C = make_div(pr.C);
   SegTable seg;
   std::memset(&seg, 0, sizeof(seg));
   seg.n = 1;
@@ -443,7 +449,6 @@ extern "C" int seco_chunk_attn_fwd(const seco_desc* desc, const void* q, const v
   AttnParams p = make_params(desc);
   p.q = q; p.k = k_cache; p.v = v_cache; p.o_out = o; p.lse = lse;
   p.n_splits = 1;
-  p.Cpad = (desc->chunk_len + 31) / 32 * 32;
   const size_t part_bytes = split_part_bytes(desc);
   if (part_bytes && ws && !(reinterpret_cast<uintptr_t>(ws) & 255u) && ws_bytes >= part_bytes + split_ml_bytes(desc)) {
     p.n_splits = splits_for(desc);

@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include "fast_div.h"
 #include "seco.h"
 
 namespace seco {
@@ -35,8 +36,20 @@ struct AttnParams {
   int B, Hq, Hkv, D, C, q_start, G;
   float scale;
   int64_t qs[3], os[3], kvs[3], gs[3];
+  Div by_C, by_Cpad, by_Hq, by_Hkv, by_G;
+  Div by_tiles, by_splits;   // row tiles and n_splits of a launch (for_launch)
+  int n_ctiles;              // dK/dV: column tiles of a (batch, KV head), and its workgroups
+  Div by_unit;
   PendingDq* pending;   // backward, host side: a dQ pass that is announced but not launched yet
 };
+
+// What a kernel of row tiles is launched with
+inline AttnParams for_launch(const AttnParams& p, int n_mtiles) {
+  AttnParams x = p;
+  x.by_tiles = make_div(n_mtiles);
+  x.by_splits = make_div(p.n_splits);
+  return x;
+}
 
 // Memory that a [B, H, rows, D] tensor lies in, first byte to last (strides in elements, none negative).
 struct Span { uintptr_t begin, end; };
@@ -241,8 +254,8 @@ struct SharePlan {
   int n_tiles;                        // column tiles in the list, the last ones of every (batch, KV head)
   int n_shared;                       // of these, how many are shared out: the first ones (they see the most rows)
   int n_entries;                      // workgroups per (batch, KV head) for the list
-  uint8_t tile_of[kMaxEntries];       // list position of a workgroup's tile
-  uint16_t first[kMaxEntries + 1];    // first workgroup of a list position; shared tiles come first, so for them it is
+  uint8_t tile_of[kMaxEntries];       // list position of a workgroup's tile (the kernel reads words: 4-byte boundaries)
+  uint16_t first[kMaxEntries + 2];    // first workgroup of a list position; shared tiles come first, so for them it is
 };                                    // also the first slot of partial sums
 
 // Iterations of the last n_tiles (at most kMaxEntries) column tiles of a (batch, KV head), as runs of equal numbers; they do
@@ -346,6 +359,13 @@ struct TailSplit {
   float* part;
   SharePlan plan;
 };
+// What a launch of column tiles is told of them; returns the workgroups of a (batch, KV head)
+inline int for_column_tiles(AttnParams& p, const SegTable& seg, const TailSplit& ts) {
+  p.n_ctiles = seg.tile_begin[seg.n];
+  const int per_unit = p.n_ctiles - ts.plan.n_tiles + ts.plan.n_entries;
+  p.by_unit = make_div(per_unit);
+  return per_unit;
+}
 // For a dK/dV pass that has the chip to itself; time: what it is expected to take from its last full round on; busy: the part of its
 // workgroups' time in that of all CUs
 inline SharePlan share_plan(const IterRuns& r, int n_units, int n_ctiles, int G, int n_rows, int slots, float& time, float* busy = nullptr) {

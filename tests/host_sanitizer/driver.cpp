@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "bwd_plan.h"
+#include "fast_div.h"
 #include "seco.h"
 #include "stub_launch.h"
 #include "xcd_map.h"
@@ -39,6 +40,14 @@ static void* const FAKE = reinterpret_cast<void*>(0x10000);
 static float* const FAKEF = reinterpret_cast<float*>(0x10000);
 
 int main() {
+  // ---- division by multiplication: around every multiple that can go wrong, up to the largest dividend ----
+  for (int d : {1, 2, 3, 5, 7, 31, 32, 33, 255, 640, 641, 4095, 65537, 16777213, 1 << 30, (1 << 30) + 1, 0x7fffffff}) {
+    const seco::Div by = seco::make_div(d);
+    for (int64_t k : {(int64_t)0, (int64_t)1, (int64_t)2, (int64_t)97, (int64_t)0x7fffffff / d / 2, (int64_t)0x7fffffff / d})
+      for (int64_t n = k * d - 2; n <= k * d + 2; ++n)
+        if (n >= 0 && n <= 0x7fffffff) CHECK(seco::over((int)n, by) == (int)(n / d));
+    CHECK(seco::over(0x7fffffff, by) == 0x7fffffff / d);
+  }
   // ---- validation codes (nothing may be launched) ----
   {
     seco_desc d = desc();
