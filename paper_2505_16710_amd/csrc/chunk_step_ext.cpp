@@ -195,6 +195,17 @@ struct Step {
     check(rc, "dec_rope_qkv");
     return true;
   }
+  // the joint projection of h, its queries turned and its keys and values in the cache
+  void project(Layer& l, void* qkv, void* h, int64_t C, int64_t q_start) {
+    const int64_t M = B * C;
+    if (rope_base != 0.0 && D == 128 && own(l.wqkv, DEC_GEMM_NN, M, W, dm, dm, W, W)) {
+      const int64_t st[3] = {l.k.stride(0), l.k.stride(1), l.k.stride(2)};
+      const int rc = lib.dec_gemm_qkv(h, ptr(l.wqkv.w), qkv, ptr(l.k), ptr(l.v), st, B, Hq, Hkv, C, dm, q_start, (float)rope_base, s);
+      if (rc != SECO_ERR_TOO_LARGE) return check(rc, "dec_gemm_qkv");
+    }
+    mm(qkv, h, l.wqkv, M);
+    append(l, qkv, C, q_start);
+  }
   void append(Layer& l, void* qkv, int64_t C, int64_t q_start) {
     if (rope_qkv(l, qkv, C, q_start, false)) return;
     rotate(qkv, C, q_start, false);
@@ -223,7 +234,7 @@ struct Step {
     else
       check(lib.kvgrad_readout(&d, fptr(l.gk), fptr(l.gv), dk, dv, 1.f, s), "kvgrad_readout");
   }
-  // O and LSE of the chunk; its k / v enter the cache.  (kReuse: the rebuilt chunk has the same inputs and the kernels are
+  // O and LSE of the chunk, whose k / v are in the cache.  (kReuse: the rebuilt chunk has the same inputs and the kernels are
   // deterministic, so the values are identical and the cache rows already hold this chunk's K/V.)
   void attention(Layer& l, Saved& sv, int64_t C, int64_t q_start, Keep keep, Arena& mem) {
     if (keep == kReuse) {
@@ -244,7 +255,6 @@ struct Step {
       sv.lse = fptr(sv.keep_lse);
       return;
     }
-    append(l, sv.qkv, C, q_start);
     if (keep == kStore) {
       sv.keep_o = at::empty({B, C, Hq, D}, opts());
       sv.keep_lse = at::empty({B, Hq, C}, opts().dtype(at::kFloat));
@@ -333,11 +343,11 @@ struct Step {
       else
         norm(x, y, l.norm1, sv.x1, sv.h1, sv.r1);
       sv.qkv = rows(W);
-      mm(sv.qkv, sv.h1, l.wqkv, R);
-      if (to_cache && &l == &layers.back() && keep == kCompute) {
-        append(l, sv.qkv, C, q_start);
-        return nullptr;
-      }
+      if (keep == kReuse)
+        mm(sv.qkv, sv.h1, l.wqkv, R);
+      else
+        project(l, sv.qkv, sv.h1, C, q_start);
+      if (to_cache && &l == &layers.back() && keep == kCompute) return nullptr;
       attention(l, sv, C, q_start, keep, mem);
       if (to_cache && &l == &layers.back()) return nullptr;
       mm(y, sv.o, l.wo, R);

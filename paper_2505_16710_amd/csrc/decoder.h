@@ -53,6 +53,10 @@ int dec_gemm(int form, int epilogue, const void* a, const void* b, void* c, void
 int dec_gemm_grads(const void* dy, const void* w, void* dx, void* u, const void* x, void* dw, int64_t M, int64_t K, int64_t n, void* stream);
 // the same with dw = x^T dy
 int dec_gemm_first_grads(const void* dy, const void* w, void* dx, void* u, const void* x, void* dw, int64_t M, int64_t K, int64_t n, void* stream);
+// The joint projection qkv[B C, (Hq + 2 Hkv) 128] = h[B C, K] w and what dec_rope_qkv makes of it, bit for bit, in one launch up to tiles of
+// 64 rows; the key and value columns of qkv may be written or not
+int dec_gemm_qkv(const void* h, const void* w, void* qkv, void* k, void* v, const int64_t* kv_stride, int64_t B, int64_t Hq, int64_t Hkv,
+                 int64_t C, int64_t K, int64_t row0, float base, void* stream);
 #ifdef __cplusplus
 }
 #endif

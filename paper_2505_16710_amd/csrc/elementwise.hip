@@ -3,6 +3,7 @@
 // embedding; and the merge steps of the split forward / dQ kernels (short chunks).
 #include "merge_body.h"
 #include "decoder.h"
+#include "rope.h"
 #include "seco_internal.h"
 
 namespace seco {
@@ -242,35 +243,6 @@ int launch_readout(void* oa, void* ob, const float* ga, const float* gb, float s
   return launch_status();
 }
 
-// Sine and cosine in fp64: the nearest multiple n of pi/2 is taken off in two fused steps (pi/2 as the sum of two
-// doubles, so that the remainder is good to an ulp of 1 for |n| up to 2^40), and on the remaining |x| <= pi/4 the Taylor
-// series up to x^15 and x^16 are exact to 1e-16.
-__device__ __forceinline__ void sincos_f64(double theta, double& sn, double& cs) {
-  const double n = rint(theta * 0.63661977236758134308);        // 2 / pi
-  double x = fma(-n, 1.57079632679489655800, theta);
-  x = fma(-n, 6.12323399573676603587e-17, x);
-  const double y = x * x;
-  double ps = -1.0 / 1307674368000.0, pc = 1.0 / 20922789888000.0;
-  ps = fma(ps, y, 1.0 / 6227020800.0);
-  pc = fma(pc, y, -1.0 / 87178291200.0);
-  ps = fma(ps, y, -1.0 / 39916800.0);
-  pc = fma(pc, y, 1.0 / 479001600.0);
-  ps = fma(ps, y, 1.0 / 362880.0);
-  pc = fma(pc, y, -1.0 / 3628800.0);
-  ps = fma(ps, y, -1.0 / 5040.0);
-  pc = fma(pc, y, 1.0 / 40320.0);
-  ps = fma(ps, y, 1.0 / 120.0);
-  pc = fma(pc, y, -1.0 / 720.0);
-  ps = fma(ps, y, -1.0 / 6.0);
-  pc = fma(pc, y, 1.0 / 24.0);
-  pc = fma(pc, y, -0.5);
-  const double s0 = fma(x * y, ps, x), c0 = fma(y, pc, 1.0);
-  const int q = (int)(n - 4.0 * floor(0.25 * n));                // n mod 4
-  const double a = q & 1 ? c0 : s0, b = q & 1 ? s0 : c0;
-  sn = q & 2 ? -a : a;
-  cs = (q + 1) & 2 ? -b : b;
-}
-
 template <typename T> struct Quad;                               // four consecutive elements, one memory access
 template <> struct Quad<float> {
   float4 v;
@@ -294,11 +266,6 @@ template <> struct Quad<__bf16> {
 // as blockIdx.z == 1: the same rows, scaled and converted but not rotated, so that keys and values take one pass and
 // one launch.
 constexpr int kRopeHeads = 4;
-// base^(-2 i / D) for i = 4 grp + j is a product of powers the host has computed: pow[k] = base^(-8 2^k / D) for bit k of
-// grp, and step = base^(-2 / D), j times (an fp64 exp2 per element pair was half of the kernel's arithmetic).
-struct RopePowers {
-  double pow[6], step;
-};
 template <typename TIn, typename TOut>
 __global__ __launch_bounds__(256) void rope_rows_kernel(TOut* out, const TIn* in, TOut* plain_out, const TIn* plain_in,
                                                         int B, int H, int C,   // (out may be in)
@@ -336,15 +303,9 @@ __global__ __launch_bounds__(256) void rope_rows_kernel(TOut* out, const TIn* in
   load(y);                                                // in flight during the fp64 arithmetic
   double sn[4], cs[4];
   if (!plain) {                                           // (uniform over the workgroup)
-    double theta = (double)(pos0 + row);
+    rope_sines(pos0 + row, grp, powers, sn, cs);
 #pragma unroll
-    for (int k = 0; k < 6; ++k) theta *= grp >> k & 1 ? powers.pow[k] : 1.0;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      sincos_f64(theta, sn[j], cs[j]);
-      sn[j] *= (double)sign;
-      theta *= powers.step;
-    }
+    for (int j = 0; j < 4; ++j) sn[j] *= (double)sign;
   }
   while (true) {
 #pragma unroll
@@ -377,7 +338,7 @@ __global__ __launch_bounds__(256) void rope_rows_kernel(TOut* out, const TIn* in
 // cache, 512 rows of 8/2 heads take 4 us each, of which 3 are the launch and the first loads.)
 // One head group of one row: this thread's four pairs of kRopeHeads heads.
 template <typename TIn, typename TOut>
-__device__ __forceinline__ void rope_group(TOut* dst, const TIn* src, int64_t os1, int64_t is1, int heads, int D, int grp, double theta,
+__device__ __forceinline__ void rope_group(TOut* dst, const TIn* src, int64_t os1, int64_t is1, int heads, int D, int grp, int64_t pos,
                                            const RopePowers& powers, double sign, bool plain) {
   Quad<TIn> x[kRopeHeads][2];
 #pragma unroll
@@ -388,14 +349,9 @@ __device__ __forceinline__ void rope_group(TOut* dst, const TIn* src, int64_t os
     }
   double sn[4], cs[4];
   if (!plain) {
+    rope_sines(pos, grp, powers, sn, cs);
 #pragma unroll
-    for (int k = 0; k < 6; ++k) theta *= grp >> k & 1 ? powers.pow[k] : 1.0;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      sincos_f64(theta, sn[j], cs[j]);
-      sn[j] *= sign;
-      theta *= powers.step;
-    }
+    for (int j = 0; j < 4; ++j) sn[j] *= sign;
   }
 #pragma unroll
   for (int k = 0; k < kRopeHeads; ++k)
@@ -405,14 +361,7 @@ __device__ __forceinline__ void rope_group(TOut* dst, const TIn* src, int64_t os
       for (int j = 0; j < 4; ++j) {
         lo[j] = x[k][0].get(j);
         hi[j] = x[k][1].get(j);
-        if (!plain) {
-          const double a = (double)lo[j], c = (double)hi[j];
-          lo[j] = (float)(a * cs[j] - c * sn[j]);
-          hi[j] = (float)(c * cs[j] + a * sn[j]);
-          // (rounded to fp32 and then to the storage type, as rope_rows_kernel does: the compiler would take the two steps
-          // as one, and two of 524288 elements differ)
-          asm("" : "+v"(lo[j]), "+v"(hi[j]));
-        }
+        if (!plain) rope_pair(lo[j], hi[j], sn[j], cs[j]);
       }
       *reinterpret_cast<Quad<TOut>*>(dst + k * os1) = Quad<TOut>::of(lo);
       *reinterpret_cast<Quad<TOut>*>(dst + k * os1 + D / 2) = Quad<TOut>::of(hi);
@@ -427,24 +376,18 @@ __global__ __launch_bounds__(256) void rope_qkv_kernel(T* qkv, TG* k, TG* v, int
   const int y = is_q ? blockIdx.y : (int)blockIdx.y - n_q - (plain ? n_kv : 0);
   const int H = is_q ? Hq : Hkv, groups = (H + kRopeHeads - 1) / kRopeHeads, b = y / groups, h0 = (y - b * groups) * kRopeHeads;
   const int heads = min(kRopeHeads, H - h0);
-  const double theta = (double)(row0 + row), sign = INV ? -1.0 : 1.0;
+  const int64_t pos = row0 + row;
+  const double sign = INV ? -1.0 : 1.0;
   T* here = qkv + ((int64_t)b * C + row) * ((int64_t)(Hq + 2 * Hkv) * D) + (int64_t)(h0 + (is_q ? 0 : plain ? Hq + Hkv : Hq)) * D + grp * 4;
   if (is_q) {
-    rope_group(here, (const T*)here, D, D, heads, D, grp, theta, powers, sign, false);
+    rope_group(here, (const T*)here, D, D, heads, D, grp, pos, powers, sign, false);
   } else {
     TG* there = (plain ? v : k) + b * ks0 + h0 * ks1 + (row0 + row) * ks2 + grp * 4;
     if constexpr (INV)
-      rope_group(here, (const TG*)there, D, ks1, heads, D, grp, theta, powers, sign, plain);
+      rope_group(here, (const TG*)there, D, ks1, heads, D, grp, pos, powers, sign, plain);
     else
-      rope_group(there, (const T*)here, ks1, D, heads, D, grp, theta, powers, sign, plain);
+      rope_group(there, (const T*)here, ks1, D, heads, D, grp, pos, powers, sign, plain);
   }
-}
-
-RopePowers rope_powers(int D, float base) {
-  RopePowers powers;
-  powers.step = exp2(-2.0 / D * log2((double)base));
-  for (int k = 0; k < 6; ++k) powers.pow[k] = exp2(-8.0 * (1 << k) / D * log2((double)base));
-  return powers;
 }
 
 int launch_rope_rows(void* out, const void* in, void* plain_out, const void* plain_in, int in_kind, int out_kind, int B,

@@ -20,13 +20,14 @@
 
 #include "decoder.h"
 #include "mfma_tiles.h"
+#include "rope.h"
 #include "seco_internal.h"
 
 namespace seco {
 namespace {
 
 constexpr int kStep = 64, kRow = 128;   // contraction elements per step; bytes per LDS row
-enum Epilogue { kStore, kAdd, kSilu, kSiluBwd };
+enum Epilogue { kStore, kAdd, kSilu, kSiluBwd, kQkv };
 
 struct GemmArgs {
   const char* a;
@@ -36,11 +37,22 @@ struct GemmArgs {
   int M, N, K, lda, ldb, ldc, tiles_m, tiles_n;
   int split_m, part_m, part_n;       // an XCD's part of the tiles (place_tiles); split_m 0: runs of them
 };
+// kQkv: C is the joint projection [B C, (Hq + 2 Hkv) 128], whose query heads leave rotated; the key heads go rotated, the value heads
+// as they are, to rows row0 .. of the cache
+struct QkvArgs : GemmArgs {
+  __bf16 *k, *v;
+  int64_t ks[3], row0;
+  int chunk, Hq, Hkv;
+  Div by_chunk;
+  RopePowers powers;
+};
+template <int EPI> using ArgsOf = std::conditional_t<EPI == kQkv, QkvArgs, GemmArgs>;
 
 __device__ __forceinline__ int flip(int row) { return (((row >> 1) & 1) << 2) | ((row >> 2) & 3); }
 
 // Copies of one operand by W wavefronts: instruction i of a wavefront brings the staged rows 8 (wave + W i) .. + 7.
-template <bool KC, int BO, int W = 4> struct Stage {
+// GAP (KR): columns left out in the middle of a panel
+template <bool KC, int BO, int W = 4, int GAP = 0> struct Stage {
   static constexpr int kCopies = BO / (8 * W);
   uint32_t off[kCopies];      // this lane's source, relative to the step's base
   // o0: first outer index of the tile, n_outer: how many there are (KR: a multiple of 8); rows / chunks past the end repeat the last
@@ -52,7 +64,8 @@ template <bool KC, int BO, int W = 4> struct Stage {
         off[i] = (uint32_t)min(o0 + lr, n_outer - 1) * (uint32_t)(ld * 2) + (((lane & 7) ^ flip(lr)) << 4);
       } else {
         const int krow = lr & 63;
-        off[i] = (uint32_t)krow * (uint32_t)(ld * 2) + (uint32_t)min(o0 + (lr & ~63) + (((lane & 7) ^ flip(krow)) << 3), n_outer - 8) * 2u;
+        const int chunk = (lane & 7) ^ flip(krow);
+        off[i] = (uint32_t)krow * (uint32_t)(ld * 2) + (uint32_t)min(o0 + (lr & ~63) + (chunk << 3) + (chunk >> 2) * GAP, n_outer - 8) * 2u;
       }
     }
   }
@@ -156,10 +169,45 @@ __device__ __forceinline__ void emit(const GemmArgs& g, int64_t at, const F4& lo
   }
 }
 
+// The columns of a tile of kQkv are pairs (c, c + 64) of one head: all of its 128, or, 64 wide, 32 from either half, so that a thread
+// finds both elements of four pairs among the tile's sums (a tile of half rows reads half lines of B: 0.9 us at 512 rows).  The sines
+// are computed while the first operands are on their way, which covers half of their time (0.8 us; one pair behind each step of the
+// contraction all of it shows).  Product and rotation, 8/2 heads of a 1024-wide model, in two launches -> one, us: 64 rows 7.5 -> 5.2,
+// 256 9.0 -> 6.5, 512 9.7 -> 7.8, 1024 12.3 -> 10.5; the product alone 4.4, 5.3, 6.2, 8.6.
+template <int BN> __device__ __forceinline__ int qkv_column(int tn) { return BN == 64 ? (tn >> 1) * 128 + (tn & 1) * 32 : tn * BN; }
+struct Sines {
+  double sn[4], cs[4];
+};
+// of row r of C and the pairs from column c of a head on
+__device__ __forceinline__ void qkv_sines(const QkvArgs& g, int r, int c, Sines& x) {
+  const int b = over(r, g.by_chunk);
+  rope_sines(g.row0 + r - b * g.chunk, c >> 2, g.powers, x.sn, x.cs);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) asm volatile("" : "+v"(x.sn[j]), "+v"(x.cs[j]));     // (here, not behind the products)
+}
+// four pairs of row r, from column col = 128 head + c on
+template <typename F4>
+__device__ __forceinline__ void emit_qkv(const QkvArgs& g, int r, int col, const F4& lo, const F4& hi, const Sines& x) {
+  const int head = col >> 7, c = col & 127, b = over(r, g.by_chunk), kv = head - g.Hq, vh = kv - g.Hkv;
+  typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+  bf16x4 out[2];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    float l = (float)(__bf16)lo[j], h = (float)(__bf16)hi[j];
+    if (vh < 0) rope_pair(l, h, x.sn[j], x.cs[j]);
+    out[0][j] = (__bf16)l;
+    out[1][j] = (__bf16)h;
+  }
+  __bf16* to = kv < 0 ? g.c + (int64_t)r * g.ldc + col
+                      : (vh < 0 ? g.k : g.v) + b * g.ks[0] + (vh < 0 ? kv : vh) * g.ks[1] + (g.row0 + r - b * g.chunk) * g.ks[2] + c;
+  *reinterpret_cast<bf16x4*>(to) = out[0];
+  *reinterpret_cast<bf16x4*>(to + 64) = out[1];
+}
+
 // KH groups of 2 x WN x KW wavefronts, each with a ring of kStages slots; group kh takes the steps kh, kh + KH, ..., and of each
 // step the wavefronts of equal kw a KW-th.
 template <int BM, int BN, int KH, int kStages, int WN, bool AKC, bool BKC, int EPI, int KW>
-__device__ __forceinline__ void ring_tile(const GemmArgs& g, int item, lds_char* smem_all) {
+__device__ __forceinline__ void ring_tile(const ArgsOf<EPI>& g, int item, lds_char* smem_all) {
   constexpr int kSlot = (BM + BN) * kRow, GW = 2 * WN * KW, MB = BM / 64, NB = BN / (32 * WN);
   constexpr int kPerWave = BM / (8 * GW) + BN / (8 * GW);            // copies per wavefront and step
   constexpr int kRing = kStages * kSlot, kImage = kRing / KW;   // kImage: for a wavefront's part of the sums
@@ -168,10 +216,10 @@ __device__ __forceinline__ void ring_tile(const GemmArgs& g, int item, lds_char*
   const int kw = KW == 1 ? 0 : wave / (2 * WN), wt = KW == 1 ? wave : wave % (2 * WN);
   lds_char* smem = smem_all + kh * kRing;
   const int tn = item / g.tiles_m, tm = item - tn * g.tiles_m;
-  const int m0 = tm * BM, n0 = tn * BN;
+  const int m0 = tm * BM, n0 = EPI == kQkv ? qkv_column<BN>(tn) : tn * BN;
 
   Stage<AKC, BM, GW> sa;
-  Stage<BKC, BN, GW> sb;
+  Stage<BKC, BN, GW, EPI == kQkv && BN == 64 ? 32 : 0> sb;
   sa.init(m0, g.M, g.lda, wave, lane);
   sb.init(n0, g.N, g.ldb, wave, lane);
   const int64_t step_a = AKC ? kStep * 2 : (int64_t)kStep * g.lda * 2, step_b = BKC ? kStep * 2 : (int64_t)kStep * g.ldb * 2;
@@ -189,6 +237,15 @@ __device__ __forceinline__ void ring_tile(const GemmArgs& g, int item, lds_char*
   for (int s = 0; s < kStages - 1; ++s)
     if (s < n_steps) copy(s);
 
+  constexpr int kPerRow = BN / 8, kRows = 64 * GW * KH / kPerRow;
+  Sines sines[EPI == kQkv ? BM / kRows : 1];
+  const int pairs = n0 + (tid % kPerRow) * 4;              // kQkv: this thread's first column
+  if constexpr (EPI == kQkv) {
+    if (n0 < (g.Hq + g.Hkv) * 128) {
+#pragma unroll
+      for (int i = 0; i < BM / kRows; ++i) qkv_sines(g, min(m0 + i * kRows + tid / kPerRow, g.M - 1), pairs & 127, sines[i]);
+    }
+  }
   Frag<AKC> fa[MB];
   Frag<BKC> fb[NB];
 #pragma unroll
@@ -222,7 +279,6 @@ __device__ __forceinline__ void ring_tile(const GemmArgs& g, int item, lds_char*
 
   // where this thread's part of the tile leaves, and what it meets there: requested behind the last wait for operands, in
   // front of the last step's products
-  constexpr int kPerRow = BN / 8, kRows = 64 * GW * KH / kPerRow;
   const int col = n0 + (tid % kPerRow) * 8;
   bf16x8 old[BM / kRows];
   auto request_old = [&]() {
@@ -281,12 +337,17 @@ __device__ __forceinline__ void ring_tile(const GemmArgs& g, int item, lds_char*
   for (int i = 0; i < BM / kRows; ++i) {
     const int lr = i * kRows + tid / kPerRow, row = m0 + lr;
     if (row >= g.M) break;
-    lds_char* src = smem_all + lr * kTurnRow + (tid % kPerRow) * 32;
-    f32x4 lo = *reinterpret_cast<SECO_LDS f32x4*>(src), hi = *reinterpret_cast<SECO_LDS f32x4*>(src + 16);
+    constexpr int kBetween = EPI == kQkv ? BN * 2 : 16;       // bytes between a thread's two quads of a row
+    lds_char* src = smem_all + lr * kTurnRow + (tid % kPerRow) * (EPI == kQkv ? 16 : 32);
+    f32x4 lo = *reinterpret_cast<SECO_LDS f32x4*>(src), hi = *reinterpret_cast<SECO_LDS f32x4*>(src + kBetween);
 #pragma unroll
     for (int v = 1; v < KH * KW; ++v) {
       lo += *reinterpret_cast<SECO_LDS f32x4*>(src + v * kImage);
-      hi += *reinterpret_cast<SECO_LDS f32x4*>(src + v * kImage + 16);
+      hi += *reinterpret_cast<SECO_LDS f32x4*>(src + v * kImage + kBetween);
+    }
+    if constexpr (EPI == kQkv) {
+      emit_qkv(g, row, pairs, lo, hi, sines[i]);
+      continue;
     }
     const int64_t at = (int64_t)row * g.ldc + col;
     emit<EPI>(g, at, lo, hi, kMeets ? old[i] : met<EPI>(g, at));
@@ -299,14 +360,14 @@ __device__ __forceinline__ void ring_tile(const GemmArgs& g, int item, lds_char*
 // MFMA) on half of the CUs; here an operand is read from LDS once (1.5 KiB per MFMA), twice the CUs work, and the copies of
 // all wavefronts are in flight at once.
 template <int NW, bool AKC, bool BKC, int EPI>
-__device__ __forceinline__ void k_tile(const GemmArgs& g, int item, lds_char* smem_all) {
+__device__ __forceinline__ void k_tile(const ArgsOf<EPI>& g, int item, lds_char* smem_all) {
   constexpr int BM = 32, BN = 64, kSlot = (BM + BN) * kRow;
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   lds_char* smem = smem_all + w * kSlot;
   const int tn = item / g.tiles_m, tm = item - tn * g.tiles_m;
-  const int m0 = tm * BM, n0 = tn * BN;
+  const int m0 = tm * BM, n0 = EPI == kQkv ? qkv_column<BN>(tn) : tn * BN;
   Stage<AKC, BM, 1> sa;
-  Stage<BKC, BN, 1> sb;
+  Stage<BKC, BN, 1, EPI == kQkv ? 32 : 0> sb;
   sa.init(m0, g.M, g.lda, 0, lane);
   sb.init(n0, g.N, g.ldb, 0, lane);
   const int64_t step_a = AKC ? kStep * 2 : (int64_t)kStep * g.lda * 2, step_b = BKC ? kStep * 2 : (int64_t)kStep * g.ldb * 2;
@@ -320,6 +381,10 @@ __device__ __forceinline__ void k_tile(const GemmArgs& g, int item, lds_char* sm
     pb += NW * step_b;
   };
   if (w < n_steps) copy();
+  Sines sines;
+  const int pairs = n0 + (threadIdx.x & 7) * 4;
+  if constexpr (EPI == kQkv)
+    if (n0 < (g.Hq + g.Hkv) * 128 && w < BM / 8) qkv_sines(g, min(m0 + (int)(threadIdx.x >> 3), g.M - 1), pairs & 127, sines);
   Frag<AKC> fa;
   Frag<BKC> fb[2];
   fa.init(0, lane);
@@ -362,9 +427,13 @@ __device__ __forceinline__ void k_tile(const GemmArgs& g, int item, lds_char* sm
   f32x4 lo = {0.f, 0.f, 0.f, 0.f}, hi = lo;
 #pragma unroll
   for (int v = 0; v < NW; ++v) {
-    lds_char* src = smem_all + v * kSlot + lr * kTurnRow + (threadIdx.x & 7) * 32;
+    lds_char* src = smem_all + v * kSlot + lr * kTurnRow + (threadIdx.x & 7) * (EPI == kQkv ? 16 : 32);
     lo += *reinterpret_cast<SECO_LDS f32x4*>(src);
-    hi += *reinterpret_cast<SECO_LDS f32x4*>(src + 16);
+    hi += *reinterpret_cast<SECO_LDS f32x4*>(src + (EPI == kQkv ? 128 : 16));
+  }
+  if constexpr (EPI == kQkv) {
+    emit_qkv(g, m0 + lr, pairs, lo, hi, sines);
+    return;
   }
   const int64_t at = (int64_t)(m0 + lr) * g.ldc + col;
   emit<EPI>(g, at, lo, hi, met<EPI>(g, at));
@@ -372,14 +441,16 @@ __device__ __forceinline__ void k_tile(const GemmArgs& g, int item, lds_char* sm
 
 // A way to work a product: workgroups of kThreads with kSmem bytes of LDS, one per item
 template <int BM, int BN, int KH, int ST, int WN, bool AKC, bool BKC, int EPI, int KW = 1> struct Ring {
+  using Args = ArgsOf<EPI>;
   static constexpr int kThreads = 128 * WN * KW * KH, kSmem = KH * ST * (BM + BN) * kRow, kBM = BM, kBN = BN;
-  static __device__ __forceinline__ void run(const GemmArgs& g, int item, lds_char* smem) {
+  static __device__ __forceinline__ void run(const Args& g, int item, lds_char* smem) {
     ring_tile<BM, BN, KH, ST, WN, AKC, BKC, EPI, KW>(g, item, smem);
   }
 };
 template <int NW, bool AKC, bool BKC, int EPI> struct ByK {
+  using Args = ArgsOf<EPI>;
   static constexpr int kThreads = 64 * NW, kSmem = NW * 96 * kRow, kBM = 32, kBN = 64;
-  static __device__ __forceinline__ void run(const GemmArgs& g, int item, lds_char* smem) { k_tile<NW, AKC, BKC, EPI>(g, item, smem); }
+  static __device__ __forceinline__ void run(const Args& g, int item, lds_char* smem) { k_tile<NW, AKC, BKC, EPI>(g, item, smem); }
 };
 // Which tiles the XCDs take (workgroups whose ids are equal mod 8 share an L2).  Runs of the tiles, column by column: an XCD
 // reads all rows of A and an eighth of B's columns.  Or split_m x 8 / split_m parts of part_m x part_n tiles, one for each XCD,
@@ -411,12 +482,12 @@ __device__ __forceinline__ int tile_of(const GemmArgs& g, int block) {
 }
 
 template <typename T>
-__global__ __launch_bounds__(T::kThreads, 2) void gemm_kernel(GemmArgs g) {
+__global__ __launch_bounds__(T::kThreads, 2) void gemm_kernel(typename T::Args g) {
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];
   const int item = tile_of(g, blockIdx.x);
   if (item >= 0) T::run(g, item, (lds_char*)smem_raw);
 }
-template <typename T> int launch(GemmArgs g, hipStream_t s) {
+template <typename T> int launch(typename T::Args g, hipStream_t s) {
   auto kern = gemm_kernel<T>;
   static std::atomic<uint64_t> ready{0};
   if (!allow_lds(ready, reinterpret_cast<const void*>(kern), T::kSmem)) return SECO_ERR_LAUNCH;
@@ -565,6 +636,43 @@ static int gemm_grads(bool first, const void* dy, const void* w, void* dx, void*
 extern "C" int dec_gemm_grads(const void* dy, const void* w, void* dx, void* u, const void* x, void* dw, int64_t M, int64_t K, int64_t n,
                               void* stream) {
   return gemm_grads(false, dy, w, dx, u, x, dw, M, K, n, stream);
+}
+extern "C" int dec_gemm_qkv(const void* h, const void* w, void* qkv, void* k, void* v, const int64_t* kv_stride, int64_t B, int64_t Hq,
+                            int64_t Hkv, int64_t C, int64_t K, int64_t row0, float base, void* stream) {
+  using namespace seco;
+  if (!h || !w || !qkv || !k || !v || !kv_stride) return SECO_ERR_NULL;
+  if (B < 1 || Hq < 1 || Hkv < 1 || C < 1 || row0 < 0) return SECO_ERR_SHAPE;
+  if (!(base > 1.f) || !std::isfinite(base)) return SECO_ERR_RANGE;
+  const int64_t big = (int64_t)1 << 30;
+  if (B > 65535 || C > big || Hq > 65535 || Hkv > 65535) return SECO_ERR_TOO_LARGE;
+  const int64_t M = B * C, N = (Hq + 2 * Hkv) * 128;
+  for (int i = 0; i < 3; ++i)
+    if (kv_stride[i] < 0 || kv_stride[i] % 8 != 0) return SECO_ERR_ALIGN;
+  if (((uintptr_t)h | (uintptr_t)w | (uintptr_t)qkv | (uintptr_t)k | (uintptr_t)v) & 15u) return SECO_ERR_ALIGN;
+  if (!dec_gemm_supported(DEC_GEMM_NN, M, N, K, K, N, N)) return SECO_ERR_SHAPE;
+  QkvArgs g;
+  static_cast<GemmArgs&>(g) = {static_cast<const char*>(h), static_cast<const char*>(w), static_cast<__bf16*>(qkv), nullptr,
+                               (int)M, (int)N, (int)K, (int)K, (int)N, (int)N, 0, 0, 0, 0, 0};
+  g.k = static_cast<__bf16*>(k);
+  g.v = static_cast<__bf16*>(v);
+  for (int i = 0; i < 3; ++i) g.ks[i] = kv_stride[i];
+  g.row0 = row0;
+  g.chunk = (int)C;
+  g.Hq = (int)Hq;
+  g.Hkv = (int)Hkv;
+  g.by_chunk = make_div((int)C);
+  g.powers = rope_powers(128, base);
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  const int rc = with_way<true, false, kQkv>(g, [&](auto way) {
+    using T = typename decltype(way)::type;
+    if constexpr (T::kBM <= 64)
+      return launch<T>(g, s);
+    else
+      return kApart;             // (a thread of the large tiles would hold the sines of four rows or more)
+  });
+  if (rc != kApart) return rc;
+  if (const int st = pick<true, false, kStore>(g, s)) return st;
+  return dec_rope_qkv(SECO_BF16, 0, qkv, k, v, kv_stride, B, Hq, Hkv, C, 128, row0, base, stream);
 }
 extern "C" int dec_gemm_first_grads(const void* dy, const void* w, void* dx, void* u, const void* x, void* dw, int64_t M, int64_t K, int64_t n,
                                     void* stream) {

@@ -317,3 +317,27 @@ def test_runs_of_columns_to_matrices_of_their_own(rows, widths):
     for t, ref in zip(out, src.split(widths, 1)):
         assert torch.equal(t, ref)
     assert fn(src.data_ptr(), *(t.data_ptr() for t in out), rows, 24, 16, 16, torch.cuda.current_stream().cuda_stream) != 0
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,n,K,row0", [
+    (1, 1, 1, 1, 64, 0), (2, 3, 1, 17, 192, 5), (1, 9, 9, 33, 128, 30000),        # tiles of 32 x 64, half of a head
+    (1, 8, 2, 512, 1024, 1024), (2, 8, 2, 201, 128, 3),                           # 64 x 64
+    (1, 8, 2, 1000, 192, 7), (3, 8, 2, 333, 64, 0),                               # 64 x 128, a whole head
+    (1, 8, 2, 1000, 2048, 1), (1, 8, 2, 2048, 64, 9),                             # 128 rows: in two launches
+])
+def test_projection_rotated_in_its_product(B, Hq, Hkv, n, K, row0):
+    """dec_gemm_qkv against dec_gemm and dec_rope_qkv: the same bits of queries and cache, and nothing else of the cache is written."""
+    base, N, W = 500000.0, row0 + n + 5, (Hq + 2 * Hkv) * 128
+    gen = torch.Generator(device=DEV).manual_seed(n + K)
+    h, w = (torch.randn(*s, generator=gen, device=DEV).to(torch.bfloat16) for s in ((B * n, K), (K, W)))
+    k, v = (torch.randn(B, N, Hkv, 128, generator=gen, device=DEV).to(torch.bfloat16).transpose(1, 2) for _ in range(2))
+    lib, s, p = seco.load_library(), C.c_void_p(torch.cuda.current_stream().cuda_stream), lambda t: C.c_void_p(t.data_ptr())
+    i64, st = lambda *x: [C.c_int64(y) for y in x], (C.c_int64 * 3)(*k.stride()[:3])
+    want, wk, wv = torch.empty(B * n, W, dtype=torch.bfloat16, device=DEV), k.clone(), v.clone()
+    assert wk.stride() == k.stride()
+    assert lib.dec_gemm(0, 0, p(h), p(w), p(want), None, *i64(B * n, W, K, K, W, W), s) == 0
+    assert lib.dec_rope_qkv(BF16, 0, p(want), p(wk), p(wv), st, *i64(B, Hq, Hkv, n, 128, row0), C.c_float(base), s) == 0
+    got = torch.empty_like(want)
+    assert lib.dec_gemm_qkv(p(h), p(w), p(got), p(k), p(v), st, *i64(B, Hq, Hkv, n, K, row0), C.c_float(base), s) == 0
+    torch.cuda.synchronize()
+    assert torch.equal(got[:, :Hq * 128], want[:, :Hq * 128]) and torch.equal(k, wk) and torch.equal(v, wv)
