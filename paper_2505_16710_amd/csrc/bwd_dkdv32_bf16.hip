@@ -4,8 +4,9 @@
 
 namespace seco {
 
-int launch_dkdv32_bf16(const AttnParams& p, const SegTable& seg, const TailSplit& ts, const RowRuns& rr, bool rows, hipStream_t s) {
-  return rows ? launch_dkdv_kernel<true, Products32>(p, seg, ts, rr, s) : launch_dkdv_kernel<false, Products32>(p, seg, ts, rr, s);
+int launch_dkdv32_bf16(const AttnParams& p, const SegTable& seg, const TailSplit& ts, const RowRuns& rr, Rows mode, hipStream_t s) {
+  if (mode == kRuns) return launch_dkdv_kernel<kRuns, Products32>(p, seg, ts, rr, s);
+  return mode == kJoined ? launch_dkdv_kernel<kJoined, Products32>(p, seg, ts, rr, s) : launch_dkdv_kernel<kAll, Products32>(p, seg, ts, rr, s);
 }
 
 }  // namespace seco

@@ -39,7 +39,7 @@
 // A workgroup occupies a whole CU, so a launch runs in rounds of 256 column tiles and a last round with few
 // tiles costs as much as a full one.  The last column tiles of every (batch, KV head) are therefore shared out
 // where that is expected to pay (share_plan in seco_internal.h): a share is a run of the tile's iterations (64 query rows
-// of one head each, cut through heads where the number of shares asks for it), its fp32 sums go to the workspace, and
+// of one head each, or of several heads: kJoined; cut through heads where the number of shares asks for it), its fp32 sums go to the workspace, and
 // a merge adds them to gK/gV in the order of the shares (still one writer per element and a fixed summation order, so
 // results stay reproducible).
 //
@@ -203,17 +203,22 @@ struct Products32 {
 };
 
 // (RB is fixed to 2 by the hand-pipelined main loop.)
-// ROWS: the query rows are taken from a table of runs (rows relative to p.q_start, each run with one weight whose
-// log2 is added to -LSE, i.e. its probabilities are scaled by the weight) instead of being all p.C rows with weight 1.
+// MODE: kAll: the query rows are all p.C rows of each head with weight 1, a head's in stages of its own.
+// kRuns: they are taken from a table of runs (rows relative to p.q_start, each run with one weight whose
+// log2 is added to -LSE, i.e. its probabilities are scaled by the weight).
+// kJoined: as kAll, but the stages cut the rows of all heads of the group one behind the other, so that only the last stage of all
+// has rows that do not exist: 32 rows of 4 heads are two iterations instead of four half empty ones, 70 are five instead of eight.
+// A stage with rows of several heads takes its addresses per lane and, on the diagonal, a position per row (joined_pays).
 // ROLE: 0 = role A, 1 = role B.  The body of a wavefront is instantiated once per role, so that a role's accumulators
 // and working set are the variables of a loop of its own: with both roles as the two arms of a branch inside one
 // loop, unrolled over the ring slots, the register allocator could not keep the working set in registers.
 // OWN: the row statistics (-LSE / s and -delta) are computed here, from the O and dO rows of each stage, instead of being
 // taken from the arrays the dQ kernel leaves: for the launch that runs both passes at once.
-template <int NCB, int RB, bool ROWS, int ROLE, class Products, bool OWN = false>
+template <int NCB, int RB, Rows MODE, int ROLE, class Products, bool OWN = false>
 __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTable& seg, const TailSplit& ts,
                                                const RowRuns& rr, int item, lds_char* smem) {
   using Cfg = DkdvCfg<NCB, RB>;
+  constexpr bool ROWS = MODE == kRuns, JOINED = MODE == kJoined;
   constexpr int BQ = Cfg::kBQ, kTileBytes = Cfg::kTileBytes;
   constexpr int kDoRegion = Cfg::kDoRegion, kStatRegion = Cfg::kStatRegion, kStatBytes = Cfg::kStatBytes;
   constexpr int NW = 2 * NCB;                 // wavefronts
@@ -268,18 +273,28 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
   const int rt0 = max(0, c0 - p.q_start) / BQ;
   struct Pos { int hg, r0, ri; };   // head within the group, first chunk-local row of the stage, run of rows
   // first stage of a head, and the number of stages per head
-  int first_ri = 0, first_r0 = rt0 * BQ, n_rt;
+  int first_ri = 0, first_r0 = rt0 * BQ, n_rt = 0;
+  // (joined) rows of a head; r0 of a stage counts from first_r0 on.  One stage on: heads and rows, and another head where its rows end
+  const int len = p.C - first_r0;
+  int adv_h = 0, adv_r = BQ;
+  float inv_len = 0.f;
   if constexpr (ROWS) {
     while (first_ri + 1 < rr.n && rr.end[first_ri] <= first_r0) ++first_ri;
     first_r0 = max(first_r0, rr.begin[first_ri]);
     n_rt = (rr.end[first_ri] - first_r0 + BQ - 1) / BQ;
     for (int i = first_ri + 1; i < rr.n; ++i) n_rt += (rr.end[i] - rr.begin[i] + BQ - 1) / BQ;
     n_rt = max(n_rt, 0);
+  } else if constexpr (JOINED) {
+    if (len < BQ) {                           // (quotients below 128 by the reciprocal, half added to the dividend: exact)
+      inv_len = __builtin_amdgcn_rcpf((float)len);
+      adv_h = (int)((BQ + 0.5f) * inv_len);
+      adv_r = BQ - adv_h * len;
+    }
   } else {
     n_rt = (p.C + BQ - 1) / BQ - rt0;
   }
   // this workgroup's share of the tile's iterations: [it0, it0 + n_iter)
-  const int n_all = n_rt * p.G;
+  const int n_all = JOINED ? (len * p.G + BQ - 1) / BQ : n_rt * p.G;
   int it0 = 0, n_iter = n_all;
   if (divided) {
     // share i begins at floor(i n_all / n_shares) = i each + floor(i rest / n_shares), i and rest less than 2^9: a product with the
@@ -291,14 +306,28 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
     n_iter = begin(share + 1) - it0;
   }
   // rows [x.r0, row_limit(x)) of a stage exist; the others are masked
-  auto row_limit = [&](Pos x) { return ROWS ? rr.end[x.ri] : p.C; };
+  auto row_limit = [&](Pos x) { return ROWS ? rr.end[x.ri] : JOINED ? len : p.C; };
+  auto inside = [&](Pos x) { return x.r0 + BQ <= row_limit(x); };        // (joined: of one head)
+  // (joined) how many rows there are from the stage's first on, and where its row lr is: `rows` further and `heads` times from the end
+  // of one head's rows to the start of the next one's; rows that do not exist repeat the last one
+  auto rows_left = [&](Pos x) { return (p.G - x.hg) * len - x.r0; };
+  auto heads_in = [&](int local) { return len < BQ ? (int)(((float)local + 0.5f) * inv_len) : (local >= len ? 1 : 0); };
+  struct At { int rows, heads; };
+  auto row_at = [&](Pos x, int lr) {
+    if (inside(x)) return At{lr, 0};
+    const int rows = min(lr, rows_left(x) - 1);
+    return At{rows, heads_in(x.r0 + rows)};
+  };
   auto advance = [&](Pos x) {
-    x.r0 += BQ;
+    x.r0 += JOINED ? adv_r : BQ;
     if constexpr (ROWS) {
       if (x.r0 >= rr.end[x.ri]) {
         if (++x.ri == rr.n) { x.ri = first_ri; x.r0 = first_r0; x.hg += 1; }
         else x.r0 = rr.begin[x.ri];
       }
+    } else if constexpr (JOINED) {
+      x.hg += adv_h;
+      if (x.r0 >= len) { x.r0 -= len; x.hg += 1; }
     } else {
       if (x.r0 >= p.C) { x.r0 = first_r0; x.hg += 1; }
     }
@@ -325,10 +354,11 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
   auto src_of = [&](Pos x) {
     Src r;
-    r.q = qbase + x.hg * p.qs[1] + (int64_t)x.r0 * p.qs[2];
-    r.d_o = dobase + x.hg * p.os[1] + (int64_t)x.r0 * p.os[2];
-    r.stat = OWN ? p.lse + ((int64_t)b * p.Hq + (int64_t)kvh * p.G + x.hg) * p.C + x.r0
-                 : (wave_u == 0 ? p.nlse2 : p.delta) + stat_base + (int64_t)x.hg * p.stat_stride + x.r0;
+    const int row = JOINED ? x.r0 + first_r0 : x.r0;
+    r.q = qbase + x.hg * p.qs[1] + (int64_t)row * p.qs[2];
+    r.d_o = dobase + x.hg * p.os[1] + (int64_t)row * p.os[2];
+    r.stat = OWN ? p.lse + ((int64_t)b * p.Hq + (int64_t)kvh * p.G + x.hg) * p.C + row
+                 : (wave_u == 0 ? p.nlse2 : p.delta) + stat_base + (int64_t)x.hg * p.stat_stride + row;
     return r;
   };
   // (all rows, no runs) one stage on: BQ rows further, or, behind a head's last stage, back to the first stage's row
@@ -337,9 +367,12 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
   const int64_t back_rows = (int64_t)(n_rt - 1) * BQ;
   const int64_t q_wrap = p.qs[1] - back_rows * p.qs[2], do_wrap = p.os[1] - back_rows * p.os[2];
   const int64_t stat_wrap = (OWN ? p.C : p.stat_stride) - back_rows;
-  auto stat_step = [&](Pos from, Pos to) { return to.hg != from.hg ? stat_wrap : (int64_t)BQ; };
+  auto stat_step = [&](Pos from, Pos to) {
+    if constexpr (JOINED) return (int64_t)((to.hg - from.hg) * p.C + to.r0 - from.r0);          // (asked with OWN only)
+    return to.hg != from.hg ? stat_wrap : (int64_t)BQ;
+  };
   auto next_src = [&](Src x, Pos from, Pos to) {
-    if constexpr (ROWS) {
+    if constexpr (ROWS || JOINED) {
       x = src_of(to);
     } else {
       const bool wrap = to.hg != from.hg;
@@ -349,8 +382,13 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
     }
     return x;
   };
+  // (joined) bytes from the group's first row on, less than 2^32 (joined_pays); from: elements to the stage's first row
+  auto group_offset = [&](int64_t from, At at, const int64_t (&stride)[3]) {
+    return 2u * ((uint32_t)from + __umul24(at.rows, (uint32_t)stride[2]) + (uint32_t)at.heads * ((uint32_t)stride[1] - (uint32_t)len * (uint32_t)stride[2]));
+  };
+  const int stat_turn = (OWN ? p.C : p.stat_stride) - len;
   auto copy_stage = [&](Pos x, int slot, const Src& src) {
-    if (x.r0 + BQ <= row_limit(x)) {
+    if (inside(x)) {
       const __bf16* q_src = src.q;
       const __bf16* do_src = src.d_o;
       const uint32_t lds = OWN ? opaque(lds_wave) : lds_wave;
@@ -359,6 +397,16 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
         const uint32_t dst = lds + slot * kTileBytes + i * (4 * NW * kRowBytes);
         dma16_sbase(q_src, q_lane_off[i], dst);
         dma16_sbase(do_src, do_lane_off[i], dst + kDoRegion);
+      }
+    } else if constexpr (JOINED) {
+#pragma unroll
+      for (int i = 0; i < kCopies; ++i) {
+        const uint32_t dst = lds_wave + slot * kTileBytes + i * (4 * NW * kRowBytes);
+        const int lr = 4 * (wave + NW * i) + (lane >> 4);
+        const At at = row_at(x, lr);
+        const uint32_t chunk = (uint32_t)((lane & 15) ^ swz(lr)) << 4;
+        dma16_sbase(qbase, group_offset(src.q - qbase, at, p.qs) + chunk, dst);
+        dma16_sbase(dobase, group_offset(src.d_o - dobase, at, p.os) + chunk, dst + kDoRegion);
       }
     } else {                                   // rows past the chunk repeat its last one
       const __bf16* q_src = src.q;
@@ -378,7 +426,7 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
   static_assert(BQ == 64, "one 64-lane copy per row statistic");
   const uint32_t lds_stat = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)smem + kStatRegion + (wave & 1) * BQ * 4);
   auto copy_stat = [&](Pos x, int slot, const Src& src) {
-    if (x.r0 + BQ <= row_limit(x)) {
+    if (inside(x)) {
       if (wave_u < 2) {
         const uint64_t a = (uint64_t)(uintptr_t)src.stat;
         // (wavefront-uniform by construction; the halves go through readfirstlane so that the compiler keeps them
@@ -389,6 +437,16 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
                      :
                      : "v"(lane * 4), "s"(src), "s"(lds_stat + slot * kStatBytes)
                      : "memory", "m0");
+      }
+    } else if (JOINED) {
+      if (wave_u < 2) {
+        const At at = row_at(x, lane);
+        const float* from = src.stat + at.rows + at.heads * stat_turn;
+        if (rows_left(x) >= BQ)
+          asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dword %0, off" : : "v"(from), "s"(lds_stat + slot * kStatBytes) : "memory", "m0");
+        else
+          *reinterpret_cast<SECO_LDS float*>(smem + kStatRegion + slot * kStatBytes + (wave_u * BQ + lane) * 4) =
+              wave_u == 0 && lane >= rows_left(x) ? -INFINITY : *from;
       }
     } else if (wave_u < 2) {             // (wavefront-uniform control flow only: the copies above need scalar addresses)
       const int row = x.r0 + lane;
@@ -403,16 +461,30 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
   // iteration after that, comes from those and the dO tile that has landed by then.
   const int own_lr = 16 * cb + 4 * pi4((lane >> 2) & 3) + (lane & 3);      // this lane's row of a stage (pi4: no bank conflicts)
   auto own_row = [&](Pos x) { return (uint32_t)min(own_lr, p.C - 1 - x.r0); };
-  auto load_lse = [&](Pos x, const float* stat) { return stat[own_row(x)]; };   // stat: of the stage's first row
+  auto load_lse = [&](Pos x, const float* stat) {                              // stat: of the stage's first row
+    if constexpr (JOINED) {
+      const At at = row_at(x, own_lr);
+      return stat[at.rows + at.heads * stat_turn];
+    } else {
+      return stat[own_row(x)];
+    }
+  };
   auto put_lse = [&](Pos x, int slot, float lse) {
     SECO_LDS float* stat = reinterpret_cast<SECO_LDS float*>(smem + kStatRegion + slot * kStatBytes);
-    const float v = x.r0 + own_lr < p.C ? -lse / p.scale : -INFINITY;
+    const float v = (JOINED ? own_lr < rows_left(x) : x.r0 + own_lr < p.C) ? -lse / p.scale : -INFINITY;
     if (lane < 16) stat[own_lr] = v;
   };
   struct OwnRows { bf16x8 o[4]; };
   const int64_t o_from_do = static_cast<const char*>(p.o) - static_cast<const char*>(p.d_o);   // (their strides are the same)
   auto load_own = [&](Pos x, const Src& src) {
     OwnRows w;
+    if constexpr (JOINED) {
+      global_bytes group = scalar_address(reinterpret_cast<const char*>(dobase) + o_from_do);
+      const uint32_t off = group_offset(src.d_o - dobase, row_at(x, own_lr), p.os) + (uint32_t)(lane >> 4) * 16u;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) w.o[t] = global_load16(group, off + 64u * t);
+      return w;
+    }
     global_bytes from = scalar_address(reinterpret_cast<const char*>(src.d_o) + o_from_do);
     const uint32_t off = __umul24(own_row(x), (uint32_t)p.os[2] * 2u) + (uint32_t)(lane >> 4) * 16u;
 #pragma unroll
@@ -444,7 +516,28 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
   // to be kept for it)
   using Tile = typename Products::Tile;
   using Init = typename Products::Init;
-  auto mask_above_diagonal = [&](Tile& s, int qpos0) {
+  auto mask_above_diagonal = [&](Tile& s, Pos x, int rb) {
+    if (JOINED && !inside(x)) {                // each row from its own head's first one on
+      const int first = p.q_start + first_r0;
+      if (n0 + 31 > first) {
+        const int at = x.r0 + 32 * rb, ahead = n0 + op.lane_col - first;
+        if (len >= 32) {                       // (at most one head's end in 32 rows)
+          const int local0 = at - heads_in(at) * len + op.lane_row, over0 = ahead - local0, over1 = over0 + len, to_end = len - local0;
+#pragma unroll
+          for (int e = 0; e < 16; ++e)
+            if ((Products::row_of(e) < to_end ? over0 : over1) + Products::col_of(e) > Products::row_of(e))
+              Products::map(s, e, [](float) { return 0.f; });
+        } else {
+#pragma unroll
+          for (int e = 0; e < 16; ++e) {
+            const int local = at + op.lane_row + Products::row_of(e);
+            if (ahead + Products::col_of(e) > local - heads_in(local) * len) Products::map(s, e, [](float) { return 0.f; });
+          }
+        }
+      }
+      return;
+    }
+    const int qpos0 = p.q_start + (JOINED ? first_r0 : 0) + x.r0 + 32 * rb;
     if (n0 + 31 > qpos0) {
       const int ahead = n0 + op.lane_col - qpos0 - op.lane_row;
 #pragma unroll
@@ -456,7 +549,7 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
 
   // role A: S = Q K^T for row block rb of the stage in `slot`, P = exp2(c2 * (S - LSE / s)) with the causal mask;
   // P goes to pbuf as two operand halves (lane-contiguous 16-byte words)
-  auto scores = [&](int slot, int r0, int rb, float lw) {   // lw: log2 of the rows' weight, divided by c2
+  auto scores = [&](int slot, Pos x, int rb, float lw) {   // lw: log2 of the rows' weight, divided by c2
     lds_char* qt = smem + slot * kTileBytes;
     Init init;
     op.chain_init(init, reinterpret_cast<SECO_LDS float*>(smem + kStatRegion + slot * kStatBytes) + 32 * rb);
@@ -466,14 +559,17 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
     for (int i = 0; i < 8; ++i) Products::chain(s, i, op.row_op(qt, 32 * rb, i), frag, init);
 #pragma unroll
     for (int e = 0; e < 16; ++e) prob(s, e);
-    mask_above_diagonal(s, p.q_start + r0 + 32 * rb);
+    mask_above_diagonal(s, x, rb);
     lds_char* pb = pslot(slot, rb);
     *reinterpret_cast<SECO_LDS bf16x8*>(pb) = Products::pack(s, 0);
     *reinterpret_cast<SECO_LDS bf16x8*>(pb + 1024) = Products::pack(s, 1);
   };
 
-  Pos cur{0, first_r0, first_ri};
-  if (it0 > 0) {
+  Pos cur{0, JOINED ? 0 : first_r0, first_ri};
+  if (JOINED && it0 > 0) {
+    cur.hg = it0 * BQ / len;
+    cur.r0 = it0 * BQ - cur.hg * len;
+  } else if (it0 > 0) {
     cur.hg = it0 / n_rt;
     int skip = it0 - cur.hg * n_rt;
     if constexpr (ROWS) {
@@ -511,7 +607,7 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
   __syncthreads();
   if constexpr (role == 0) {
 #pragma unroll
-    for (int rb = 0; rb < RB; ++rb) scores(0, cur.r0, rb, ROWS ? rr.log2w[cur.ri] / c2 : 0.f);
+    for (int rb = 0; rb < RB; ++rb) scores(0, cur, rb, ROWS ? rr.log2w[cur.ri] / c2 : 0.f);
   } else if constexpr (OWN) {
     put_delta(0, own_rows);
     if (n_iter > 1) own_rows = load_own(nxt, s1);
@@ -608,7 +704,7 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
         prob(s0, 2 * i + 1);
         Products::step_end();
       }
-      mask_above_diagonal(s0, p.q_start + nxt.r0);
+      mask_above_diagonal(s0, nxt, 0);
       const bf16x8 pn0[2] = {Products::pack(s0, 0), Products::pack(s0, 1)};
       lds_char* pw0 = pslot(slot1, 0);
       *reinterpret_cast<SECO_LDS bf16x8*>(pw0) = pn0[0];
@@ -623,7 +719,7 @@ __device__ __forceinline__ void dkdv_bf16_body(const AttnParams& p, const SegTab
         prob(s1, 2 * i + 1);
         Products::step_end();
       }
-      mask_above_diagonal(s1, p.q_start + nxt.r0 + 32);
+      mask_above_diagonal(s1, nxt, 1);
       pa0[0] = pn0[0];
       pa0[1] = pn0[1];
       pa1[0] = Products::pack(s1, 0);

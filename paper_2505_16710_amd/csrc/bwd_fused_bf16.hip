@@ -36,7 +36,7 @@ static_assert(Cfg::kThreads == 512, "both passes in workgroups of 8 wavefronts")
 // The first first_grid workgroups are those of dK/dV (kv_first: the pass with the longer workgroups) or of dQ; both numbers are rounded up to whole XCD rounds.
 // RUNS: nothing, or the SegTable of dQ over selected columns
 struct AllColumns {};
-template <bool SPLIT, typename RUNS>
+template <bool SPLIT, typename RUNS, Rows MODE>
 __global__ __launch_bounds__(512, 2) void bwd_fused_bf16_kernel(AttnParams p, SegTable seg, TailSplit ts, int n_mtiles,
                                                                 int kv_total, int dq_total, int first_grid, int kv_first, RUNS runs) {
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];
@@ -48,9 +48,9 @@ __global__ __launch_bounds__(512, 2) void bwd_fused_bf16_kernel(AttnParams p, Se
     RowRuns none;
     none.n = 0;
     if (__builtin_amdgcn_readfirstlane((int)threadIdx.x / (64 * kNcb)) == 0)
-      dkdv_bf16_body<kNcb, SECO_DKDV_RB, false, 0, Products32, true>(p, seg, ts, none, item, smem);
+      dkdv_bf16_body<kNcb, SECO_DKDV_RB, MODE, 0, Products32, true>(p, seg, ts, none, item, smem);
     else
-      dkdv_bf16_body<kNcb, SECO_DKDV_RB, false, 1, Products32, true>(p, seg, ts, none, item, smem);
+      dkdv_bf16_body<kNcb, SECO_DKDV_RB, MODE, 1, Products32, true>(p, seg, ts, none, item, smem);
   } else {
     constexpr int kSplit = SPLIT ? kDivided : kWholeTiles;
     if constexpr (std::is_same_v<RUNS, SegTable>)
@@ -87,10 +87,10 @@ int launch_merges(const AttnParams& p, const SegTable& seg, const TailSplit& ts,
   return launch_status();
 }
 
-template <bool SPLIT, typename RUNS>
+template <bool SPLIT, typename RUNS, Rows MODE>
 int launch(const AttnParams& p, const SegTable& seg, const TailSplit& ts, const RUNS& runs, int n_mtiles, int kv_total, int dq_total,
            bool kv_first, hipStream_t s) {
-  auto kern = bwd_fused_bf16_kernel<SPLIT, RUNS>;
+  auto kern = bwd_fused_bf16_kernel<SPLIT, RUNS, MODE>;
   static std::atomic<uint64_t> ready{0};
   if (!allow_lds(ready, reinterpret_cast<const void*>(kern), kSmem)) return SECO_ERR_LAUNCH;
   AttnParams pl = for_launch(p, n_mtiles);
@@ -106,16 +106,21 @@ int launch(const AttnParams& p, const SegTable& seg, const TailSplit& ts, const 
 
 }  // namespace
 
-int launch_bwd_fused_bf16(const AttnParams& p, const SegTable& seg, const TailSplit& ts, bool kv_first, const SegTable* runs, hipStream_t s) {
+int launch_bwd_fused_bf16(const AttnParams& p, const SegTable& seg, const TailSplit& ts, bool kv_first, bool joined, const SegTable* runs, hipStream_t s) {
   const int kv_total = p.B * p.Hkv * (seg.tile_begin[seg.n] - ts.plan.n_tiles + ts.plan.n_entries);
   const SplitPlan plan = split_plan(p.B, p.Hkv, p.G, p.C);
   const int mtiles = (p.C + BM - 1) / BM;
   const AllColumns all;
   const int whole = p.B * p.Hq * mtiles, divided = plan.items * p.n_splits;
-  const int rc = p.n_splits == 1 ? (runs ? launch<false>(p, seg, ts, *runs, mtiles, kv_total, whole, kv_first, s)
-                                         : launch<false>(p, seg, ts, all, mtiles, kv_total, whole, kv_first, s))
-                                 : (runs ? launch<true>(p, seg, ts, *runs, plan.n_mtiles, kv_total, divided, kv_first, s)
-                                         : launch<true>(p, seg, ts, all, plan.n_mtiles, kv_total, divided, kv_first, s));
+  auto go = [&](auto mode) {
+    constexpr Rows kMode = decltype(mode)::value;
+    if (p.n_splits == 1)
+      return runs ? launch<false, SegTable, kMode>(p, seg, ts, *runs, mtiles, kv_total, whole, kv_first, s)
+                  : launch<false, AllColumns, kMode>(p, seg, ts, all, mtiles, kv_total, whole, kv_first, s);
+    return runs ? launch<true, SegTable, kMode>(p, seg, ts, *runs, plan.n_mtiles, kv_total, divided, kv_first, s)
+                : launch<true, AllColumns, kMode>(p, seg, ts, all, plan.n_mtiles, kv_total, divided, kv_first, s);
+  };
+  const int rc = joined ? go(std::integral_constant<Rows, kJoined>()) : go(std::integral_constant<Rows, kAll>());
   return rc ? rc : launch_merges(p, seg, ts, s);
 }
 

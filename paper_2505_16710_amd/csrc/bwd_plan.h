@@ -12,7 +12,7 @@ constexpr size_t kSlotBytes = (size_t)2 * kColTileBf16 * 128 * sizeof(float);
 int slots_in(size_t bytes) { return (int)std::min(bytes / kSlotBytes, (size_t)device_cus()); }
 
 // Iterations of the last column tiles
-template <typename Cfg, bool ROWS>
+template <typename Cfg, Rows MODE>
 IterRuns tile_iterations(const AttnParams& p, const SegTable& seg, const RowRuns& rr) {
   // iterations of a column tile (as the kernel counts them)
   auto iters = [&](int tile) {
@@ -20,13 +20,31 @@ IterRuns tile_iterations(const AttnParams& p, const SegTable& seg, const RowRuns
     while (si + 1 < seg.n && tile >= seg.tile_begin[si + 1]) ++si;
     const int c0 = seg.col_begin[si] + (tile - seg.tile_begin[si]) * Cfg::kCols;
     const int r0 = (c0 > p.q_start ? c0 - p.q_start : 0) / Cfg::kBQ * Cfg::kBQ;
-    if (!ROWS) return ((p.C - r0 + Cfg::kBQ - 1) / Cfg::kBQ) * p.G;
+    if (MODE == kAll) return ((p.C - r0 + Cfg::kBQ - 1) / Cfg::kBQ) * p.G;
+    if (MODE == kJoined) return ((p.C - r0) * p.G + Cfg::kBQ - 1) / Cfg::kBQ;
     int n = 0;
     for (int i = 0; i < rr.n; ++i)
       if (rr.end[i] > r0) n += (rr.end[i] - (rr.begin[i] > r0 ? rr.begin[i] : r0) + Cfg::kBQ - 1) / Cfg::kBQ;
     return n * p.G;
   };
   return iter_runs(seg.tile_begin[seg.n], iters);
+}
+
+// Whether the stages of dK/dV cut the rows of a group's heads one behind the other (kJoined): by the part of the iterations that
+// saves.  From a quarter of a round of column tiles on, three in ten; with fewer tiles, whose iterations workgroups share out so that
+// less is gained from fewer of them than addresses and positions per row cost, two thirds, or half of four or less, which are not
+// shared out.  900 random calls of 2 - 1000 rows, time apart over time joined, by the part saved: more than 70 % 1.01 - 1.75, 1.3 on
+// average; 35 - 55 % 1.09 from 64 tiles on and 0.85 - 1.21 below; 20 - 35 % 0.94 - 1.12; less 0.95 - 1.02.  us, apart -> joined:
+//   32/8 heads  32 at 16352: 87.4 -> 75.4   16 at 8000: 48.0 -> 36.8   16/8 x 2  14 at 6000: 51.9 -> 47.6
+//   16/2  9 at 900: 17.0 -> 13.9   70 at 20000: 94.2 -> 64.4
+inline bool joined_pays(const AttnParams& p, const SegTable& seg) {
+  const int64_t rows = (int64_t)p.C * p.G, apart = (int64_t)(p.C + 63) / 64 * p.G, saved = apart - (rows + 63) / 64;
+  // (a group's rows are addressed by 32-bit offsets)
+  if (rows > 1 << 24) return false;
+  for (const int64_t* s : {p.qs, p.os})
+    if (p.G * s[1] + p.C * s[2] >= (int64_t)1 << 31) return false;
+  if (3 * saved >= 2 * apart || (apart <= 4 && 2 * saved >= apart)) return true;
+  return 10 * saved >= 3 * apart && 4 * p.B * p.Hkv * seg.tile_begin[seg.n] >= device_cus();
 }
 
 // Both passes of a dense call: in one launch with dq_splits workgroups per row tile for dQ (0: one after the other), and
@@ -181,11 +199,11 @@ bool one_launch_behind_column_tiles(const AttnParams& p, const IterRuns& runs, i
 // shared out over the rest (kDqBesideTime, kDkdvOwnTime).
 // dq: the dQ pass is still to go out, so that it may share the launch (it goes with the first table of more runs than one holds)
 template <typename Cfg>
-BwdPlan plan_bwd(const AttnParams& p, const SegTable& seg, bool dq) {
+BwdPlan plan_bwd(const AttnParams& p, const SegTable& seg, bool dq, bool joined) {
   const int cus = device_cus(), n_units = p.B * p.Hkv, n_ctiles = seg.tile_begin[seg.n];
   RowRuns none;
   none.n = 0;
-  const IterRuns runs = tile_iterations<Cfg, false>(p, seg, none);
+  const IterRuns runs = joined ? tile_iterations<Cfg, kJoined>(p, seg, none) : tile_iterations<Cfg, kAll>(p, seg, none);
   BwdPlan best;
   best.dq_splits = 0;
   best.kv_first = true;

@@ -101,6 +101,8 @@ struct PendingDq {
 // query row, begin a multiple of 64, ascending and disjoint; the probabilities of a run's rows are scaled by its
 // weight (log2w = log2 of the weight).  By value in the kernel arguments, like the column segments.
 constexpr int kMaxRowRuns = 24;
+// How the stages of the dK/dV pass take the query rows (bwd_dkdv_body.h)
+enum Rows { kAll, kRuns, kJoined };
 struct RowRuns {
   int n;
   int begin[kMaxRowRuns];
@@ -443,7 +445,7 @@ inline bool small_divides(int pairs, int saved) { return 18 * saved > (16 * pair
 int launch_dq_bf16(const AttnParams& p, const SegTable* dq_runs, hipStream_t s);
 int launch_dkdv_bf16(const AttnParams& p, const SegTable& seg, hipStream_t s);
 // dQ (p.n_splits workgroups per row tile; runs as for launch_dq_bf16) and dK/dV in one launch
-int launch_bwd_fused_bf16(const AttnParams& p, const SegTable& seg, const TailSplit& ts, bool kv_first, const SegTable* runs, hipStream_t s);
+int launch_bwd_fused_bf16(const AttnParams& p, const SegTable& seg, const TailSplit& ts, bool kv_first, bool joined, const SegTable* runs, hipStream_t s);
 // alone: not a call whose passes could share a launch but for what its outputs lie over (which takes that launch's products)
 int launch_dq_bf16_now(const AttnParams& p, const SegTable* dq_runs, bool alone, hipStream_t s);
 // its kernel in whole row tiles with 32x32x16 products (a translation unit of its own), for launches of so few rows that these are the
@@ -456,7 +458,7 @@ int launch_dq32_bf16(const AttnParams& p, const SegTable* dq_runs, int n_mtiles,
 // the same with the query rows taken from runs (p.C: number of rows that may be addressed from p.q / p.d_o)
 int launch_dkdv_rows_bf16(const AttnParams& p, const SegTable& seg, const RowRuns& rr, hipStream_t s);
 // the kernel of either with 32x32x16 products (its own translation unit)
-int launch_dkdv32_bf16(const AttnParams& p, const SegTable& seg, const TailSplit& ts, const RowRuns& rr, bool rows, hipStream_t s);
+int launch_dkdv32_bf16(const AttnParams& p, const SegTable& seg, const TailSplit& ts, const RowRuns& rr, Rows mode, hipStream_t s);
 #ifndef SECO_DKDV_COLS
 #define SECO_DKDV_COLS 128
 #endif

@@ -347,6 +347,50 @@ def test_bf16_backward_of_several_rounds_in_one_launch(B, Hq, Hkv, C, q_start, a
             assert max_rel(to_host(got[2][b, kh]), to_host(rv)) <= TOL["bf16"]["gv"], (b, kh)
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,C,q_start", [
+    (1, 4, 2, 1, 64),          # one row of two heads; a column tile that starts at it
+    (2, 8, 2, 5, 123),         # a stage of all four heads' rows, and 44 that do not exist
+    (1, 8, 1, 16, 240),        # heads that end with the stages
+    (1, 16, 2, 21, 300),       # a stage and its half end inside heads; the last stage 40 rows
+    (1, 16, 2, 31, 98),        # heads shorter than the 32 rows of a block of scores, on the diagonal
+    (2, 16, 4, 32, 96),
+    (2, 32, 8, 47, 1500),      # heads that end inside every stage and every block
+    (1, 32, 8, 66, 1100),      # a head's rows longer than a stage; its last two begin another column tile
+    (1, 64, 8, 70, 2500),      # shared out, a share's first stage behind a head's end
+    (1, 32, 8, 19, 8300),      # several rounds of column tiles
+    (1, 16, 8, 300, 40),       # stages of one head each (as before)
+])
+@pytest.mark.parametrize("rows_first", [False, True])
+def test_bf16_dkdv_stages_of_several_heads(B, Hq, Hkv, C, q_start, rows_first):
+    """Query rows of the heads of a group one behind the other in the stages of dK/dV, in both layouts, added to what the buffers
+    hold, in one launch and (dQ written over O) in two: the same bits, within the tolerance of fp32 on the device."""
+    N, s, G = q_start + C, 1 / np.sqrt(128), Hq // Hkv
+    g = torch.Generator(device=DEV).manual_seed(67)
+    rand = lambda *shape: torch.randn(*shape, device=DEV, generator=g).to(torch.bfloat16)
+    rows = lambda: rand(B, C, Hq, 136).transpose(1, 2)[..., :128] if rows_first else rand(B, Hq, C, 128)
+    q, do, k, v = rows(), rows(), rand(B, Hkv, N, 128), rand(B, Hkv, N, 128)
+    o = torch.empty_strided(do.shape, do.stride(), dtype=do.dtype, device=DEV)
+    _, lse = seco.seco_chunk_attn_fwd(q, k, v, q_start, s, o=o)
+    of = o.float()
+    def run(d_q):
+        gk, gv = torch.full((B, Hkv, N, 128), 0.5, device=DEV), torch.full((B, Hkv, N, 128), -0.25, device=DEV)
+        return seco.seco_chunk_attn_bwd(q, k, v, o, lse, do, gk, gv, q_start, s, d_q=d_q), gk, gv
+    got, again, over = run(None), run(None), run(o)
+    assert all(torch.equal(a, b) for a, b in zip(got, again))
+    assert torch.equal(got[1], over[1]) and torch.equal(got[2], over[2])
+    below = torch.arange(N, device=DEV)[None, :] > torch.arange(C, device=DEV)[:, None] + q_start
+    for b in range(B):
+        for kh in range(Hkv):
+            kf, vf, rk, rv = k[b, kh].float(), v[b, kh].float(), 0.5, -0.25
+            for h in range(kh * G, kh * G + G):
+                qf, dof = q[b, h].float(), do[b, h].float()
+                p = torch.exp((qf @ kf.t() * s).masked_fill(below, float("-inf")) - lse[b, h][:, None])
+                ds = p * (dof @ vf.t() - (dof * of[b, h]).sum(-1, keepdim=True))
+                rk, rv = rk + s * ds.t() @ qf, rv + p.t() @ dof
+            assert max_rel(to_host(got[1][b, kh]), to_host(rk)) <= TOL["bf16"]["gk"], (b, kh)
+            assert max_rel(to_host(got[2][b, kh]), to_host(rv)) <= TOL["bf16"]["gv"], (b, kh)
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,C,k,picked", [
     (1, 8, 2, 40, 30, [3, 29]),              # two tiles: whole row tiles, no merge of dQ
     (1, 32, 8, 33, 40, [0, 7, 8, 20, 39]),   # runs of one and two chunks that end inside a tile
