@@ -38,19 +38,18 @@ int launch_dkdv_bf16(const AttnParams& p, const SegTable& seg, hipStream_t s) {
   const SegTable* runs = dq && p.pending->sparse ? &p.pending->runs : nullptr;
   if (seg.tile_begin[seg.n] == 0) return dq ? launch_dq_bf16_now(p, runs, true, s) : SECO_OK;
   // (where dQ visits selected columns or lies over O, the sums of gK / gV are divided as they would be otherwise: the same bits)
-  const bool joined = joined_pays(p, seg);
-  const BwdPlan plan = plan_bwd<Cfg>(p, seg, dq, joined);
+  const BwdPlan plan = plan_bwd<Cfg>(p, seg, dq);
   if (dq && plan.dq_splits > 0 && !dq_over_inputs(p, 2)) {
     AttnParams pf = p;
     pf.n_splits = runs ? sparse_shares(p, *runs, plan.dq_splits) : plan.dq_splits;
-    return launch_bwd_fused_bf16(pf, seg, plan.ts, plan.kv_first, joined, runs, s);
+    return launch_bwd_fused_bf16(pf, seg, plan.ts, plan.kv_first, plan.joined, runs, s);
   }
   int rc = dq ? launch_dq_bf16_now(p, runs, plan.dq_splits == 0, s) : SECO_OK;
   RowRuns none;
   none.n = 0;
   if (rc) return rc;
   const bool p16 = plan.dq_splits == 0 && plan.busy >= kBusy;
-  return joined ? launch<kJoined>(p, seg, plan.ts, none, p16, s) : launch<kAll>(p, seg, plan.ts, none, p16, s);
+  return plan.joined ? launch<kJoined>(p, seg, plan.ts, none, p16, s) : launch<kAll>(p, seg, plan.ts, none, p16, s);
 }
 
 int launch_dkdv_rows_bf16(const AttnParams& p, const SegTable& seg, const RowRuns& rr, hipStream_t s) {
@@ -60,7 +59,7 @@ int launch_dkdv_rows_bf16(const AttnParams& p, const SegTable& seg, const RowRun
   TailSplit ts;
   ts.part = p.tail_part;
   float time, busy;
-  ts.plan = share_plan(tile_iterations<Cfg, kRuns>(p, seg, rr), p.B * p.Hkv, seg.tile_begin[seg.n], p.G, n_rows, slots_in(p.tail_bytes), time, &busy);
+  ts.plan = share_plan(tile_iterations<Cfg, true>(p, seg, rr), p.B * p.Hkv, seg.tile_begin[seg.n], p.G, n_rows, slots_in(p.tail_bytes), time, &busy);
   return launch<kRuns>(p, seg, ts, rr, busy >= kBusy, s);
 }
 

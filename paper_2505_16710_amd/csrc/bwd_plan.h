@@ -12,16 +12,15 @@ constexpr size_t kSlotBytes = (size_t)2 * kColTileBf16 * 128 * sizeof(float);
 int slots_in(size_t bytes) { return (int)std::min(bytes / kSlotBytes, (size_t)device_cus()); }
 
 // Iterations of the last column tiles
-template <typename Cfg, Rows MODE>
-IterRuns tile_iterations(const AttnParams& p, const SegTable& seg, const RowRuns& rr) {
+template <typename Cfg, bool ROWS>
+IterRuns tile_iterations(const AttnParams& p, const SegTable& seg, const RowRuns& rr, bool joined = false) {
   // iterations of a column tile (as the kernel counts them)
   auto iters = [&](int tile) {
     int si = 0;
     while (si + 1 < seg.n && tile >= seg.tile_begin[si + 1]) ++si;
     const int c0 = seg.col_begin[si] + (tile - seg.tile_begin[si]) * Cfg::kCols;
     const int r0 = (c0 > p.q_start ? c0 - p.q_start : 0) / Cfg::kBQ * Cfg::kBQ;
-    if (MODE == kAll) return ((p.C - r0 + Cfg::kBQ - 1) / Cfg::kBQ) * p.G;
-    if (MODE == kJoined) return ((p.C - r0) * p.G + Cfg::kBQ - 1) / Cfg::kBQ;
+    if (!ROWS) return joined ? ((p.C - r0) * p.G + Cfg::kBQ - 1) / Cfg::kBQ : ((p.C - r0 + Cfg::kBQ - 1) / Cfg::kBQ) * p.G;
     int n = 0;
     for (int i = 0; i < rr.n; ++i)
       if (rr.end[i] > r0) n += (rr.end[i] - (rr.begin[i] > r0 ? rr.begin[i] : r0) + Cfg::kBQ - 1) / Cfg::kBQ;
@@ -51,7 +50,7 @@ inline bool joined_pays(const AttnParams& p, const SegTable& seg) {
 // the column tiles that are shared out.
 struct BwdPlan {
   int dq_splits;
-  bool kv_first;
+  bool kv_first, joined;
   TailSplit ts;
   float busy;        // of the CUs, in dK/dV by itself (share_plan)
 };
@@ -199,12 +198,13 @@ bool one_launch_behind_column_tiles(const AttnParams& p, const IterRuns& runs, i
 // shared out over the rest (kDqBesideTime, kDkdvOwnTime).
 // dq: the dQ pass is still to go out, so that it may share the launch (it goes with the first table of more runs than one holds)
 template <typename Cfg>
-BwdPlan plan_bwd(const AttnParams& p, const SegTable& seg, bool dq, bool joined) {
+BwdPlan plan_bwd(const AttnParams& p, const SegTable& seg, bool dq) {
   const int cus = device_cus(), n_units = p.B * p.Hkv, n_ctiles = seg.tile_begin[seg.n];
   RowRuns none;
   none.n = 0;
-  const IterRuns runs = joined ? tile_iterations<Cfg, kJoined>(p, seg, none) : tile_iterations<Cfg, kAll>(p, seg, none);
   BwdPlan best;
+  best.joined = joined_pays(p, seg);
+  const IterRuns runs = tile_iterations<Cfg, false>(p, seg, none, best.joined);
   best.dq_splits = 0;
   best.kv_first = true;
   best.ts.part = p.tail_part;
