@@ -20,11 +20,7 @@ constexpr float kBusy = 0.74f;
 template <Rows MODE>
 int launch(const AttnParams& p, const SegTable& seg, const TailSplit& ts, const RowRuns& rr, bool p16, hipStream_t s) {
   ProfScope prof(kKernelDkdv, s);     // the merge of the divided tiles counts as part of the dK/dV pass
-  int rc;
-  if constexpr (MODE == kJoined)
-    rc = launch_dkdv32_bf16(p, seg, ts, rr, MODE, s);
-  else
-    rc = p16 ? launch_dkdv_kernel<MODE, Products16>(p, seg, ts, rr, s) : launch_dkdv32_bf16(p, seg, ts, rr, MODE, s);
+  const int rc = p16 ? launch_dkdv_kernel<MODE, Products16>(p, seg, ts, rr, s) : launch_dkdv32_bf16(p, seg, ts, rr, MODE, s);
   if (rc || ts.plan.n_shared == 0) return rc;
   hipLaunchKernelGGL(dkdv_tail_merge_kernel<kColTileBf16>, dim3(tail_merge_grid<kColTileBf16>(p, ts)), dim3(256), 0, s, p, seg, ts);
   return launch_status();

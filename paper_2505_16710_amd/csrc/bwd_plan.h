@@ -36,14 +36,18 @@ IterRuns tile_iterations(const AttnParams& p, const SegTable& seg, const RowRuns
 // average; 35 - 55 % 1.09 from 64 tiles on and 0.85 - 1.21 below; 20 - 35 % 0.94 - 1.12; less 0.95 - 1.02.  us, apart -> joined:
 //   32/8 heads  32 at 16352: 87.4 -> 75.4   16 at 8000: 48.0 -> 36.8   16/8 x 2  14 at 6000: 51.9 -> 47.6
 //   16/2  9 at 900: 17.0 -> 13.9   70 at 20000: 94.2 -> 64.4
-inline bool joined_pays(const AttnParams& p, const SegTable& seg) {
+// A dK/dV pass of its own, with its row statistics at hand and one and a half rounds of tiles or more: a tenth (120 random calls:
+// 0.98 - 1.24, 1.04 on average; by less 0.94 - 1.04).  150 at 16000 of 32/8 178.3 -> 172.0.
+inline bool joined_pays(const AttnParams& p, const SegTable& seg, bool apart_from_dq = false) {
   const int64_t rows = (int64_t)p.C * p.G, apart = (int64_t)(p.C + 63) / 64 * p.G, saved = apart - (rows + 63) / 64;
   // (a group's rows are addressed by 32-bit offsets)
   if (rows > 1 << 24) return false;
   for (const int64_t* s : {p.qs, p.os})
     if (p.G * s[1] + p.C * s[2] >= (int64_t)1 << 31) return false;
   if (3 * saved >= 2 * apart || (apart <= 4 && 2 * saved >= apart)) return true;
-  return 10 * saved >= 3 * apart && 4 * p.B * p.Hkv * seg.tile_begin[seg.n] >= device_cus();
+  const int64_t tiles = (int64_t)p.B * p.Hkv * seg.tile_begin[seg.n];
+  if (apart_from_dq && 10 * saved >= apart && 2 * tiles >= 3 * device_cus()) return true;
+  return 10 * saved >= 3 * apart && 4 * tiles >= device_cus();
 }
 
 // Both passes of a dense call: in one launch with dq_splits workgroups per row tile for dQ (0: one after the other), and
@@ -198,7 +202,7 @@ bool one_launch_behind_column_tiles(const AttnParams& p, const IterRuns& runs, i
 // shared out over the rest (kDqBesideTime, kDkdvOwnTime).
 // dq: the dQ pass is still to go out, so that it may share the launch (it goes with the first table of more runs than one holds)
 template <typename Cfg>
-BwdPlan plan_bwd(const AttnParams& p, const SegTable& seg, bool dq) {
+BwdPlan plan_both(const AttnParams& p, const SegTable& seg, bool dq) {
   const int cus = device_cus(), n_units = p.B * p.Hkv, n_ctiles = seg.tile_begin[seg.n];
   RowRuns none;
   none.n = 0;
@@ -252,6 +256,20 @@ BwdPlan plan_bwd(const AttnParams& p, const SegTable& seg, bool dq) {
     best.ts.plan = plan;
   }
   return best;
+}
+
+template <typename Cfg>
+BwdPlan plan_bwd(const AttnParams& p, const SegTable& seg, bool dq) {
+  BwdPlan plan = plan_both<Cfg>(p, seg, dq);
+  if (plan.dq_splits == 0 && !plan.joined && joined_pays(p, seg, true)) {
+    RowRuns none;
+    none.n = 0;
+    float time;
+    plan.joined = true;
+    plan.ts.plan = share_plan(tile_iterations<Cfg, false>(p, seg, none, true), p.B * p.Hkv, seg.tile_begin[seg.n], p.G, p.C,
+                              slots_in(p.tail_bytes), time, &plan.busy);
+  }
+  return plan;
 }
 
 // dQ over selected columns takes the place of n shares per row tile of the dense pass: as many as keep a share's length,

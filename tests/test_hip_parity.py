@@ -358,7 +358,9 @@ def test_bf16_backward_of_several_rounds_in_one_launch(B, Hq, Hkv, C, q_start, a
     (1, 32, 8, 66, 1100),      # a head's rows longer than a stage; its last two begin another column tile
     (1, 64, 8, 70, 2500),      # shared out, a share's first stage behind a head's end
     (1, 32, 8, 19, 8300),      # several rounds of column tiles
-    (1, 16, 8, 300, 40),       # stages of one head each (as before)
+    (1, 16, 8, 300, 40),       # stages of one head each
+    (1, 32, 8, 150, 6100),     # dK/dV by itself, 16x16x32 products
+    (2, 16, 2, 70, 13000),     # likewise, column tiles of the last round shared out
 ])
 @pytest.mark.parametrize("rows_first", [False, True])
 def test_bf16_dkdv_stages_of_several_heads(B, Hq, Hkv, C, q_start, rows_first):
