@@ -62,27 +62,20 @@ struct BwdPlan {
 // in one launch, dQ first; 0: not.  The column tiles of a round all start together and reach the read-modify-write of
 // gK / gV together, and the last round is seldom full; dQ's workgroups, of another length, fill it and put them out of step.
 // Shares: the fewest that end within 0.9 of the time the column tiles take (few workgroups, few partial sums).  Against it
-// stand the row statistics, computed anew in every iteration: beyond 12 iterations, or with a single full round of more than
-// 4, some shapes lost 3 - 10 %.  Both sides in microseconds as fitted to shapes of 16 - 1000 rows on 256 - 2560 tiles (4 % off);
-// one launch where it comes out 3 % ahead: 210 of 345 shapes, 1.14 times as fast, none more than 1.3 % slower.  Two -> one, us:
-//   32/8 heads  32 at 16256: 126 -> 110   64 at 8000: 75 -> 62   128 at 4000: 66 -> 53   128 at 16256: 175 (not taken: 177)
-//   8/8  128 at 4000: 43 -> 32            16/8  256 at 4000: 68 -> 55                    16/2  64 at 32000: 105 -> 92
-template <typename F>
-int rounds_in_one_launch(int n_kv, int iters, int items, int tiles, int max_splits, const F& dq_wgs) {
-  const float cus = (float)device_cus(), kv = n_kv / cus;
-  if (iters > (n_kv <= device_cus() ? 4 : 12)) return 0;
+// stand the row statistics, computed anew in every iteration.  So: up to 4 iterations; up to 8 behind more than a round, but
+// for four full rounds or more and nothing behind them; up to 12 where the last round is there to be filled, at most 0.65 of
+// it taken.  800 calls of 4 - 2400 rows on 256 - 3700 tiles, time of one launch over that of two: up to 4 iterations 0.66 - 0.98;
+// 5 - 8 0.69 - 1.04, 0.90 on average; 9 - 12 0.81 - 1.15, 0.92; not taken: 5 - 12 0.90 - 1.07, 0.99, 13 - 16
+// 0.88 - 1.27, more 0.84 - 1.47.  Two -> one, us:
+//   32/8 heads  32 at 16256: 103 -> 75   64 at 8128: 64 -> 52   128 at 8064: 83 -> 75   128 at 14000: 139 -> 124
+//   8/8  128 at 4000: 43 -> 32           16/8  256 at 8000: 92 -> 79                    16/2  64 at 32000: 105 -> 82
+inline int rounds_in_one_launch(int n_kv, int iters, int tiles, int max_splits) {
+  const int cus = device_cus(), full = n_kv / cus, rest = n_kv % cus;
+  const bool pays = iters <= 4 || (n_kv > cus && (iters <= 8 ? rest > 0 || full < 4 : iters <= 12 && rest > 0 && 20 * rest <= 13 * cus));
+  if (!pays) return 0;
   int n = 1;
-  while (n < max_splits && kDqFrontTime.of((tiles + n - 1) / n) > 0.9f * kv * kDkdvRoundTime.of(iters)) ++n;
-  const int full = n_kv / device_cus();
-  const float tail = kv - full;
-  // fit: full rounds of dK/dV and a last one, dQ, what is around them; in one launch they share the chip evenly, and a last
-  // workgroup ends alone
-  constexpr WgTime kFull{15.2f, 2.2f}, kLast{9.2f, 0.6f}, kLastPart{5.6f, 1.7f}, kEven{14.f, 2.2f};
-  constexpr float kDqTile = 1.7f, kDqTileOne = 2.3f, kAlone = 0.6f, kAroundApart = 12.2f, kAroundOne = 5.3f;
-  const float rest = tail > 0.f ? kLast.of(iters) + tail * kLastPart.of(iters) : 0.f;
-  const float apart = kAroundApart + full * kFull.of(iters) + rest + kDqTile * items * tiles / cus;
-  const float one = kAroundOne + kDqTileOne * dq_wgs(n) * tiles / (n * cus) + kv * kEven.of(iters) + kAlone * iters;
-  return 1.03f * one < apart ? n : 0;
+  while (n < max_splits && kDqFrontTime.of((tiles + n - 1) / n) > 0.9f * n_kv / cus * kDkdvRoundTime.of(iters)) ++n;
+  return n;
 }
 
 // When the last of a row of workgroups ends on `places` that take them in order: the places by the time they are free at, those
@@ -222,7 +215,7 @@ BwdPlan plan_both(const AttnParams& p, const SegTable& seg, bool dq) {
   auto dq_part = [&](int n) { return n > 1 ? (n * dq_bytes + 255) / 256 * 256 : (size_t)0; };
   if ((int64_t)n_units * n_ctiles >= cus) {
     if (sp.items >= cus) return best;
-    const int n = rounds_in_one_launch(n_units * n_ctiles, runs.iters[0], sp.items, tiles, p.n_splits, dq_wgs);
+    const int n = rounds_in_one_launch(n_units * n_ctiles, runs.iters[0], tiles, p.n_splits);
     if (n > 0 && dq_part(n) <= p.tail_bytes) {
       best.dq_splits = n;
       best.kv_first = false;
