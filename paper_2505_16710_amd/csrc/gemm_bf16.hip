@@ -355,13 +355,18 @@ __device__ __forceinline__ void ring_tile(const ArgsOf<EPI>& g, int item, lds_ch
 }
 
 // A product with few tiles and, often, a long contraction (the projections back to the residual stream: 512 x 1024 x 4096):
-// tiles of 32 x 64, and every wavefront takes steps of the contraction for the whole tile, w, w + NW, .., on its own, in LDS
+// tiles of 32 x 64 (BM 32), and every wavefront takes steps of the contraction for the whole tile, w, w + NW, .., on its own, in LDS
 // of its own: no barrier before the sums of the wavefronts meet.  What bounds 64 x 64 tiles there is LDS (2 KiB read per
 // MFMA) on half of the CUs; here an operand is read from LDS once (1.5 KiB per MFMA), twice the CUs work, and the copies of
 // all wavefronts are in flight at once.
-template <int NW, bool AKC, bool BKC, int EPI>
+// BM 64: an operand is read for twice as many products, by half as many workgroups (taller_beside).
+template <int BM> struct KSlot {      // a wavefront's operands, or its part of the sums
+  static constexpr int kTurnRow = (64 + 4) * 4, kBytes = std::max((BM + 64) * kRow, BM * kTurnRow);
+};
+template <int NW, int BM, bool AKC, bool BKC, int EPI>
 __device__ __forceinline__ void k_tile(const ArgsOf<EPI>& g, int item, lds_char* smem_all) {
-  constexpr int BM = 32, BN = 64, kSlot = (BM + BN) * kRow;
+  constexpr int BN = 64, MB = BM / 32, kSlot = KSlot<BM>::kBytes, kTurnRow = KSlot<BM>::kTurnRow;
+  static_assert(BM * 8 <= 64 * NW, "a thread for eight columns of a row");
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   lds_char* smem = smem_all + w * kSlot;
   const int tn = item / g.tiles_m, tm = item - tn * g.tiles_m;
@@ -385,41 +390,49 @@ __device__ __forceinline__ void k_tile(const ArgsOf<EPI>& g, int item, lds_char*
   const int pairs = n0 + (threadIdx.x & 7) * 4;
   if constexpr (EPI == kQkv)
     if (n0 < (g.Hq + g.Hkv) * 128 && w < BM / 8) qkv_sines(g, min(m0 + (int)(threadIdx.x >> 3), g.M - 1), pairs & 127, sines);
-  Frag<AKC> fa;
+  Frag<AKC> fa[MB];
   Frag<BKC> fb[2];
-  fa.init(0, lane);
+#pragma unroll
+  for (int i = 0; i < MB; ++i) fa[i].init(i, lane);
   fb[0].init(0, lane);
   fb[1].init(1, lane);
-  f32x16 acc[2];
+  f32x16 acc[MB][2];
 #pragma unroll
-  for (int j = 0; j < 2; ++j)
+  for (int i = 0; i < MB; ++i)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
   for (int it = w; it < n_steps; it += NW) {
     dma_wait_all();
-    bf16x8 x[4], y[2][4];
+    bf16x8 x[MB][4], y[2][4];
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-      x[t] = fa.read(smem, t);
+#pragma unroll
+      for (int i = 0; i < MB; ++i) x[i][t] = fa[i].read(smem, t);
       y[0][t] = fb[0].read(smem + BM * kRow, t);
       y[1][t] = fb[1].read(smem + BM * kRow, t);
     }
     // (all operands are in registers before the next copy overwrites them)
-    asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]), "+v"(y[0][0]), "+v"(y[0][1]), "+v"(y[0][2]),
+    asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(x[0][0]), "+v"(x[0][1]), "+v"(x[0][2]), "+v"(x[0][3]), "+v"(y[0][0]), "+v"(y[0][1]), "+v"(y[0][2]),
                  "+v"(y[0][3]), "+v"(y[1][0]), "+v"(y[1][1]), "+v"(y[1][2]), "+v"(y[1][3]) : : "memory");
+    if constexpr (MB == 2) asm volatile("" : "+v"(x[1][0]), "+v"(x[1][1]), "+v"(x[1][2]), "+v"(x[1][3]) : : "memory");
     if (it + NW < n_steps) copy();
 #pragma unroll
     for (int t = 0; t < 4; ++t)
 #pragma unroll
-      for (int j = 0; j < 2; ++j) acc[j] = mfma(x[t], y[j][t], acc[j]);
+      for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = mfma(x[i][t], y[j][t], acc[i][j]);
   }
-  constexpr int kTurnRow = (BN + 4) * 4;
-  static_assert(BM * kTurnRow <= kSlot, "a wavefront's sums fit its slot");
 #pragma unroll
-  for (int j = 0; j < 2; ++j)
+  for (int i = 0; i < MB; ++i)
 #pragma unroll
-    for (int r = 0; r < 16; ++r)
-      *reinterpret_cast<SECO_LDS float*>(smem + (8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * kTurnRow + (j * 32 + (lane & 31)) * 4) = acc[j][r];
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        *reinterpret_cast<SECO_LDS float*>(smem + (32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * kTurnRow + (j * 32 + (lane & 31)) * 4) =
+            acc[i][j][r];
   __syncthreads();
   const int lr = threadIdx.x >> 3, col = n0 + (threadIdx.x & 7) * 8;
   if (lr >= BM || m0 + lr >= g.M || col >= g.N) return;
@@ -447,10 +460,10 @@ template <int BM, int BN, int KH, int ST, int WN, bool AKC, bool BKC, int EPI, i
     ring_tile<BM, BN, KH, ST, WN, AKC, BKC, EPI, KW>(g, item, smem);
   }
 };
-template <int NW, bool AKC, bool BKC, int EPI> struct ByK {
+template <int NW, bool AKC, bool BKC, int EPI, int BM = 32> struct ByK {
   using Args = ArgsOf<EPI>;
-  static constexpr int kThreads = 64 * NW, kSmem = NW * 96 * kRow, kBM = 32, kBN = 64;
-  static __device__ __forceinline__ void run(const Args& g, int item, lds_char* smem) { k_tile<NW, AKC, BKC, EPI>(g, item, smem); }
+  static constexpr int kThreads = 64 * NW, kSmem = NW * KSlot<BM>::kBytes, kBM = BM, kBN = 64;
+  static __device__ __forceinline__ void run(const Args& g, int item, lds_char* smem) { k_tile<NW, BM, AKC, BKC, EPI>(g, item, smem); }
 };
 // Which tiles the XCDs take (workgroups whose ids are equal mod 8 share an L2).  Runs of the tiles, column by column: an XCD
 // reads all rows of A and an eighth of B's columns.  Or split_m x 8 / split_m parts of part_m x part_n tiles, one for each XCD,
@@ -500,7 +513,7 @@ template <typename T> int launch(typename T::Args g, hipStream_t s) {
 //  - forward and data gradient whose 32 x 64 tiles fit one round: those, the contraction divided among eight wavefronts (512 x
 //    1024 x 4096: 11.3 against 14.5 with 64 x 64 tiles, 512 x 1024 x 1024: 5.2 / 5.8, 320 x 1536 x 1024: 5.1 / 5.8; in two rounds
 //    they lose: 640 x 1024 x 1024 8.2 / 5.8; twelve wavefronts 11.6 and 5.5.  What bounds the long one now is what the L2s
-//    deliver: 196 MB in 8.5 us);
+//    deliver: 196 MB in 8.5 us; beside a weight gradient 64 x 64, taller_beside);
 //  - over 1.25 128 x 128 tiles per CU: those, four wavefronts and two slots, so that two workgroups share a CU
 //    (2048 x 4096 x 1024: 25; 31 with eight wavefronts, 35 with 64 x 64 tiles);
 //  - from 0.55 per CU on: 128 x 128, eight wavefronts side by side, three slots (added to a 4096 x 1024 product over 512 rows:
@@ -538,7 +551,7 @@ template <bool AKC, bool BKC, int EPI> int pick(const GemmArgs& g, hipStream_t s
 // with the SiLU's derivative 18.9 -> 17.6, 1024 x 1536 12.1 -> 10.3, 1024 x 1024 10.1 -> 8.6; 320 rows 17.5 -> 14.5, 16.6 -> 14.0,
 // -, 9.5 -> 7.7.
 // weight_first: which workgroups go in front.  Those of the weight gradient take rows / 64 steps, the others' time does not
-// depend on the rows: the longer ones first (512 rows, 4096 x 1024: 17.6 against 18.8; 320: 15.1 against 14.0).
+// depend on the rows: the longer ones first (512 rows, 4096 x 1024: 17.6 against 18.8; 320: 15.1 against 14.0).  data_first: taller_beside.
 template <typename A, typename B>
 __global__ __launch_bounds__(512, 2) void gemm_pair_kernel(GemmArgs a, GemmArgs b, int first_grid, int weight_first) {
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];
@@ -550,15 +563,31 @@ __global__ __launch_bounds__(512, 2) void gemm_pair_kernel(GemmArgs a, GemmArgs 
     if (const int item = tile_of(a, block); item >= 0) A::run(a, item, (lds_char*)smem_raw);
   }
 }
-template <typename A, typename B> int launch_pair(GemmArgs a, GemmArgs b, hipStream_t s) {
+template <typename A, typename B> int launch_pair(GemmArgs a, GemmArgs b, hipStream_t s, bool data_first = false) {
   static_assert(A::kThreads == 512 && B::kThreads == 512, "workgroups of one size");
   constexpr int smem = A::kSmem > B::kSmem ? A::kSmem : B::kSmem;
   auto kern = gemm_pair_kernel<A, B>;
   static std::atomic<uint64_t> ready{0};
   if (!allow_lds(ready, reinterpret_cast<const void*>(kern), smem)) return SECO_ERR_LAUNCH;
-  const int ga = place_tiles<A>(a), gb = place_tiles<B>(b), weight_first = b.K >= 448;
+  const int ga = place_tiles<A>(a), gb = place_tiles<B>(b), weight_first = b.K >= 448 && !data_first;
   hipLaunchKernelGGL(kern, dim3(ga + gb), dim3(512), smem, s, a, b, weight_first ? gb : ga, weight_first);
   return launch_status();
+}
+// Whether the 32 x 64 tiles of a data gradient whose contraction wavefronts divide become 64 x 64 ones beside a weight gradient in
+// bm x bn tiles.  By itself the taller tile only leaves CUs idle; here those work on the other product, and an operand comes from the L2s,
+// which bound both, a third less often (512 rows, 1024 x 4096: 134 for 201 MB).  They go in front, half of the chip for long, the weight
+// gradient's tiles on the other half (behind those: 22.3 for 17.3 us).  us, 32 rows -> 64:
+//   512 rows  1024 x 4096 19.1 -> 17.3   1024 x 2048 12.3 -> 10.6   1024 x 1536 10.4 -> 9.7   1024 x 512 7.0 -> 5.5
+//   384 rows  1024 x 4096 16.8 -> 16.3   1024 x 1536  9.5 ->  8.6   1024 x 1024  7.9 -> 7.3
+// From three eighths of the CUs on (320 rows, 1024 x 4096 15.3 / 15.9, 1024 x 1536 7.9 / 8.5; 64 rows 11.6 / 15.5), not where the
+// rows fill out the tiles badly (87 x 3008 x 256 3.9 / 4.2), nor, with more than 7/16 of the CUs taken and weight gradients in small
+// tiles, where some of those start a second round of an XCD's CUs by themselves (777 x 640 x 1024 9.8 / 10.8).  Of 101 random calls with 80 tiles
+// or more the rule takes 49: 0.98 - 1.42 times as fast, 1.11 on average.
+inline bool taller_beside(const GemmArgs& a, const GemmArgs& b, int bm, int bn) {
+  const int64_t n64 = (a.N + 63) / 64, low = (a.M + 31) / 32 * n64, tall = (a.M + 63) / 64 * n64, cus = device_cus();
+  if (8 * tall < 3 * cus || 16 * tall > 9 * low) return false;
+  const int64_t other = (int64_t)((b.M + bm - 1) / bm) * ((b.N + bn - 1) / bn), per_xcd = (tall + 7) / 8 + (other + 7) / 8;
+  return (bm == 128 && bn == 128) || 16 * tall <= 7 * cus || 8 * per_xcd <= cus || 32 * per_xcd >= 5 * cus;
 }
 constexpr int kApart = 1;           // (no seco_status)
 // In one launch where the data gradient takes one of the small tiles and as many of its workgroups share a CU as by itself
@@ -572,6 +601,9 @@ template <int EPI, int EPI_W> int pair(const GemmArgs& a, const GemmArgs& b, hip
     if constexpr (A::kThreads == 512 && A::kBM <= 64) {
       return with_way<false, false, EPI_W>(b, [&](auto way_b) {
         using B = typename decltype(way_b)::type;
+        if constexpr (std::is_same_v<A, ByK<8, true, true, EPI>> && B::kThreads == 512)
+          if (taller_beside(a, b, B::kBM, B::kBN))
+            return launch_pair<ByK<8, true, true, EPI, 64>, B>(a, b, s, true);        // (the same sums)
         if constexpr (!std::is_same_v<A, Two> && B::kThreads == 512)
           return launch_pair<A, B>(a, b, s);
         else if constexpr (std::is_same_v<A, Two> && std::is_same_v<B, Wide>)

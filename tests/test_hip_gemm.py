@@ -155,3 +155,28 @@ def test_gemm_refuses_what_it_cannot_do():
     ok = lib.dec_gemm_supported
     assert ok(NN, 5, 64, 64, 64, 64, 64) and ok(TN, 64, 64, 5, 64, 64, 64)
     assert not ok(NN, 5, 29, 64, 64, 29, 29) and not ok(NN, 5, 64, 96, 96, 64, 64) and not ok(TN, 60, 64, 64, 60, 64, 64)
+
+
+@pytest.mark.parametrize("first", [False, True])
+@pytest.mark.parametrize("M,K,n,silu", [
+    (384, 1024, 64, False), (383, 1024, 1536, True), (449, 1024, 512, False), (1001, 512, 576, True), (1472, 256, 2304, False),
+    (200, 1536, 1024, False), (8, 6144, 64, False), (775, 640, 1024, False),
+])
+def test_gradients_in_one_launch_with_taller_tiles(M, K, n, silu, first):
+    """Around the line where the data gradient takes 64 rows to a tile (96 tiles, rows that fill them or not, weight gradients that do
+    or do not fit beside): the bits of the product by itself, and nothing behind its last row."""
+    lib = seco.load_library()
+    P, I = C.c_void_p, C.c_int64
+    entry = lib.dec_gemm_first_grads if first else lib.dec_gemm_grads
+    lib.dec_gemm.argtypes = [C.c_int, C.c_int, P, P, P, P] + [I] * 6 + [P]
+    entry.argtypes = [P] * 6 + [I] * 3 + [P]
+    g = torch.Generator(device=DEV).manual_seed(M + K + n)
+    dy, w, x, u, dx, dw = (torch.randn(*s, generator=g, device=DEV).to(torch.bfloat16)
+                           for s in ((M, n), (K, n), (M, K), (M, K), (M + 1, K), (K + 1, n)))
+    dx2, dw2, s = dx.clone(), dw.clone(), torch.cuda.current_stream().cuda_stream
+    ptr = lambda t: t.data_ptr()
+    assert lib.dec_gemm(TN, STORE if first else ADD, ptr(x), ptr(dy), ptr(dw), None, K, n, M, K, n, n, s) == 0
+    assert lib.dec_gemm(NT, SILU_BWD if silu else STORE, ptr(dy), ptr(w), ptr(dx), ptr(u) if silu else None, M, K, n, n, n, K, s) == 0
+    assert entry(ptr(dy), ptr(w), ptr(dx2), ptr(u) if silu else None, ptr(x), ptr(dw2), M, K, n, s) == 0
+    torch.cuda.synchronize()
+    assert torch.equal(dx, dx2) and torch.equal(dw, dw2)
