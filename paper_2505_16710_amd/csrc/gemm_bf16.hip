@@ -581,8 +581,8 @@ template <typename A, typename B> int launch_pair(GemmArgs a, GemmArgs b, hipStr
 //   384 rows  1024 x 4096 16.8 -> 16.3   1024 x 1536  9.5 ->  8.6   1024 x 1024  7.9 -> 7.3
 // From three eighths of the CUs on (320 rows, 1024 x 4096 15.3 / 15.9, 1024 x 1536 7.9 / 8.5; 64 rows 11.6 / 15.5), not where the
 // rows fill out the tiles badly (87 x 3008 x 256 3.9 / 4.2), nor, with more than 7/16 of the CUs taken and weight gradients in small
-// tiles, where some of those start a second round of an XCD's CUs by themselves (777 x 640 x 1024 9.8 / 10.8).  Of 101 random calls with 80 tiles
-// or more the rule takes 49: 0.98 - 1.42 times as fast, 1.11 on average.
+// tiles, where some of those start a second round of an XCD's CUs by themselves (777 x 640 x 1024 9.8 / 10.8).  62 random calls that the rule
+// takes are 0.92 - 1.45 times as fast, 1.10 on average (each behind large products: in short bursts everything is faster).
 inline bool taller_beside(const GemmArgs& a, const GemmArgs& b, int bm, int bn) {
   const int64_t n64 = (a.N + 63) / 64, low = (a.M + 31) / 32 * n64, tall = (a.M + 63) / 64 * n64, cus = device_cus();
   if (8 * tall < 3 * cus || 16 * tall > 9 * low) return false;
