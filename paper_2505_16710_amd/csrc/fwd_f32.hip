@@ -22,7 +22,7 @@ __device__ __forceinline__ float squares(const Acc<NT>& x) {
 
 // O = softmax(s Q K^T) V and LSE, of O the columns of NO of the NT blocks (fwd_nt).  The next block's K and V are requested before the present one is worked on.
 template <int NT, int NO, int NW>
-__global__ __launch_bounds__(NW * 64, NT <= 12 ? 2 : 1) void fwd_f32_kernel(AttnParams p) {
+__global__ __launch_bounds__(NW * 64, NT <= 12 ? 2 : 1) void fwd_f32_kernel(AttnArgs p) {
   constexpr int kParts = (NT + NO - 1) / NO;
   constexpr bool kAhead = NT <= 8;                      // (longer rows do not leave the registers)
   extern __shared__ float part[];                       // an image per wavefront; then its (reference, sum) per row

@@ -62,7 +62,7 @@ __device__ __forceinline__ OneRun tile_at(const OneRun& t, int tile) { return {t
 // dQ = s * sum over the runs of cache rows of w * dS K (one run with weight 1 over all visible rows: the exact dQ); of dQ the
 // columns of NO of the NT blocks
 template <int NT, int NO, int NW, typename Runs>
-__device__ __forceinline__ void dq_f32(const AttnParams& p, const Runs& runs, int item_part, float* part) {
+__device__ __forceinline__ void dq_f32(const AttnArgs& p, const Runs& runs, int item_part, float* part) {
   constexpr int kParts = (NT + NO - 1) / NO;
   const int item = item_part / kParts, o0 = item_part % kParts * (16 * NO), n_o = kParts == 1 ? p.D : min(p.D - o0, 16 * NO);
   if (kParts > 1 && n_o <= 0) return;
@@ -168,7 +168,7 @@ __device__ __forceinline__ void dq_f32(const AttnParams& p, const Runs& runs, in
 // gK[c] += w * s * sum_h dS^T Q, gV[c] += w * sum_h P^T dO for 16 cache rows (exclusive owner); the wavefronts divide
 // the (query head, block of 16 query rows) pairs that see them.
 template <int NT, int NW, typename Runs>
-__device__ __forceinline__ void dkdv_f32(const AttnParams& p, const Runs& runs, int item, float* part) {
+__device__ __forceinline__ void dkdv_f32(const AttnArgs& p, const Runs& runs, int item, float* part) {
   constexpr bool kAhead = NT <= 5;                      // (longer rows do not leave the registers)
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), i = lane & 15, g = lane >> 4;
   const int tile = item / (p.Hkv * p.B), bh = item - tile * p.Hkv * p.B, b = bh / p.Hkv, kvh = bh - b * p.Hkv, D = p.D;
@@ -304,7 +304,7 @@ __device__ __forceinline__ void dkdv_f32(const AttnParams& p, const Runs& runs, 
 }
 
 template <int NT, int NO, int NW, typename Runs>
-__global__ __launch_bounds__(NW * 64) void bwd_f32_kernel(AttnParams p, Runs dq_runs, Runs seg, int n_dq) {
+__global__ __launch_bounds__(NW * 64) void bwd_f32_kernel(AttnArgs p, Runs dq_runs, Runs seg, int n_dq) {
   extern __shared__ float part[];                       // two images per wavefront
   if ((int)blockIdx.x < n_dq)
     dq_f32<NT, NO, NW>(p, dq_runs, blockIdx.x, part);

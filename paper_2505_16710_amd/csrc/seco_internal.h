@@ -9,8 +9,9 @@ namespace seco {
 
 struct PendingDq;
 
-// Everything a kernel needs to know about one chunk call (validated by the host side).
-struct AttnParams {
+// Everything a kernel needs to know about one chunk call (validated by the host side): what all of them need, and all that the
+// fp32 kernels are launched with (with the divisors a backward call of 10 us takes 0.1 more), and ...
+struct AttnArgs {
   const void* q;
   const void* k;
   const void* v;
@@ -36,6 +37,9 @@ struct AttnParams {
   int B, Hq, Hkv, D, C, q_start, G;
   float scale;
   int64_t qs[3], os[3], kvs[3], gs[3];
+};
+// ... the rest.
+struct AttnParams : AttnArgs {
   Div by_C, by_Cpad, by_Hq, by_Hkv, by_G;
   Div by_tiles, by_splits;   // row tiles and n_splits of a launch (for_launch)
   int n_ctiles;              // dK/dV: column tiles of a (batch, KV head), and its workgroups
