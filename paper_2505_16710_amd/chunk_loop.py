@@ -180,6 +180,10 @@ class ChunkedDecoder:
         The derivatives are written out, not recorded: hooks of the parameters run once per step, with its gradient
         (hand_over), not once per chunk, and saved-tensor hooks have nothing to see.
 
+        Negative tokens count from the end of the embedding table.  A token outside it raises IndexError when the step is through,
+        and no parameter receives a gradient; a target outside the head's columns (other than -100, which is left out) makes the
+        loss and the gradients NaN.
+
         keep_attention_outputs: stage 1 keeps every layer's O and LSE (2 + 4/D bytes per query element: with 288 GB
         of HBM that is cheap), and the rebuilt chunks of stage 2 take them back instead of running the attention
         forward again; the gradients are bit-identical to the recomputing schedule.
@@ -247,6 +251,9 @@ class ChunkedDecoder:
                 ext.step_train(run, tokens, targets, starts[j], min(starts[j] + chunk_len, N), keep_attention_outputs and j != once, w,
                                chunk_len, wq, losses if rebuilt or j == once else None)
             # (everything is on its way before the host waits for the loss)
-            total, grads = losses.sum(), dict(zip(names, ext.step_grads(run)))
-            total = float(total)
+            result, grads = ext.step_result(run), dict(zip(names, ext.step_grads(run)))
+            torch.sum(losses, 0, out=result[0])
+            total, outside = result.tolist()
+        if outside:
+            raise IndexError("tokens: an index is out of range of the embedding table")
         return total, hand_over(p, grads)

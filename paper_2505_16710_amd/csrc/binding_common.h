@@ -25,7 +25,7 @@ using at::Tensor;
   X(seco_workspace_bytes) X(kvgrad_zero) X(kvgrad_accumulate) X(kv_append) X(kvgrad_readout) X(kv_append_rope)      \
   X(kvgrad_readout_rope) X(rope_rotate) X(dec_add_rmsnorm) X(dec_rmsnorm_bwd) X(dec_silu) X(dec_silu_bwd)             \
   X(dec_cross_entropy) X(dec_cross_entropy_both) X(dec_embedding_bwd) X(dec_gemm_supported) X(dec_gemm) X(dec_gemm_grads) X(dec_gemm_first_grads)      \
-  X(dec_rope_qkv) X(dec_gemm_qkv) X(dec_gain_sums) X(dec_split_columns) X(dec_embed_rmsnorm)
+  X(dec_rope_qkv) X(dec_gemm_qkv) X(dec_gain_sums) X(dec_split_columns) X(dec_embed_rmsnorm_checked)
 struct Lib {
 #define X(name) decltype(&::name) name = nullptr;
   SECO_ENTRIES(X)

@@ -66,6 +66,7 @@ struct Step {
   Param emb, head, norm_f;
   float* part_f = nullptr;
   Tensor parts;
+  Tensor result;                                   // the loss (the caller's sum), and 1 if a token lies outside the embedding table
   std::vector<Layer> layers;
   Arena stage1, stage2;
   void* s = nullptr;                               // stream of the current call
@@ -338,8 +339,8 @@ struct Step {
       sv.h1 = rows(dm);
       sv.r1 = stats();
       if (&l == &layers.front())
-        check(lib.dec_embed_rmsnorm(dtype, ptr(emb.w), static_cast<const int64_t*>(ptr(tok)), ptr(l.norm1.w), x, sv.h1, sv.r1, R, dm,
-                                    emb.w.size(0), s), "dec_embed_rmsnorm");
+        check(lib.dec_embed_rmsnorm_checked(dtype, ptr(emb.w), static_cast<const int64_t*>(ptr(tok)), ptr(l.norm1.w), x, sv.h1, sv.r1, R, dm,
+                                            emb.w.size(0), fptr(result) + 1, s), "dec_embed_rmsnorm");
       else
         norm(x, y, l.norm1, sv.x1, sv.h1, sv.r1);
       sv.qkv = rows(W);
@@ -538,7 +539,9 @@ PyObject* step_new(PyObject* const* a) {
   st->V = st->head.w.size(1);
   st->ff = 0;
   const at::TensorOptions f32 = st->opts().dtype(at::kFloat);
-  st->parts = at::zeros({2 * st->L + 1, DEC_GAIN_BLOCKS, st->dm}, f32);
+  const int64_t n_parts = (2 * st->L + 1) * DEC_GAIN_BLOCKS * st->dm;
+  st->parts = at::zeros({n_parts + 2}, f32);
+  st->result = st->parts.slice(0, n_parts, n_parts + 2);
   auto part = [&](int64_t i) { return fptr(st->parts) + i * DEC_GAIN_BLOCKS * st->dm; };
   st->part_f = part(2 * st->L);
   st->layers.resize(st->L);
@@ -659,6 +662,9 @@ PyObject* step_train(PyObject* const* a) {
   Py_RETURN_NONE;
 }
 
+// (step) -> fp32 [2]: room for the loss, and 1 if a token of a chunk so far lies outside the embedding table, else 0
+PyObject* step_result(PyObject* const* a) { return THPVariable_Wrap(step_of(a[0]).result); }
+
 // (step) -> gradients in the order of step_new's params; None where no chunk reached the parameter
 PyObject* step_grads(PyObject* const* a) {
   Step& st = step_of(a[0]);
@@ -718,6 +724,6 @@ PyObject* has_grad_hooks(PyObject* const* a) {
 
 PyMethodDef step_methods[] = {SECO_METHOD("step_new", step_new, 2),   SECO_METHOD("step_infer", step_infer, 7),
                               SECO_METHOD("step_zero", step_zero, 1), SECO_METHOD("step_train", step_train, 10),
-                              SECO_METHOD("step_grads", step_grads, 1), SECO_METHOD("has_grad_hooks", has_grad_hooks, 1), {nullptr, nullptr, 0, nullptr}};
+                              SECO_METHOD("step_result", step_result, 1), SECO_METHOD("step_grads", step_grads, 1), SECO_METHOD("has_grad_hooks", has_grad_hooks, 1), {nullptr, nullptr, 0, nullptr}};
 
 }  // namespace seco_ext

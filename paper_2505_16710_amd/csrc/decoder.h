@@ -12,6 +12,9 @@ int dec_add_rmsnorm(int dtype, const void* x, const void* y, const void* gain, v
 // the same for the rows token[r] of a table of v rows, which go to x_out; a token outside [-v, v) gives NaN, a negative one counts from the end
 int dec_embed_rmsnorm(int dtype, const void* table, const int64_t* token, const void* gain, void* x_out, void* h, float* rstd,
                       int64_t rows, int64_t d, int64_t v, void* stream);
+// ... and *outside (NULL: nothing) becomes 1 if there is such a token; else it stays as it is
+int dec_embed_rmsnorm_checked(int dtype, const void* table, const int64_t* token, const void* gain, void* x_out, void* h, float* rstd,
+                              int64_t rows, int64_t d, int64_t v, float* outside, void* stream);
 // d_x = d_in + gradient of the norm at x (d_in NULL: the gradient alone; d_x may be d_in or d_h);
 // gain_part[blocks, d] fp32 += per-workgroup sums of the gain's gradient, blocks = DEC_GAIN_BLOCKS
 #define DEC_GAIN_BLOCKS 256

@@ -72,10 +72,11 @@ template <typename T, int V> __device__ __forceinline__ Vec<T, V> fetch(const T*
 }
 
 // EMBED: row r of x is row token[r] of a table of v rows (the embedding of a chunk, which took a launch of its own for rows that
-// this one reads anyway: 512 x 1024 3.1 + 3.5 us -> 4.4); a token outside it gives NaN.
+// this one reads anyway: 512 x 1024 3.1 + 3.5 us -> 4.4); a token outside it gives NaN, and 1 in *outside where that is asked for.
 template <typename T, int V, int KB, bool EMBED>
 __global__ __launch_bounds__(kThreads) void add_rmsnorm_kernel(const T* x, const T* y, const T* gain, T* x_out, T* h,
-                                                               float* rstd, int64_t d, const int64_t* token, int64_t v) {   // (x_out may be x)
+                                                               float* rstd, int64_t d, const int64_t* token, int64_t v,
+                                                               float* outside) {   // (x_out may be x)
   const int64_t row = (int64_t)blockIdx.x * d;
   float kept[KB][V], sum = 0.f;
   bool bad = false;
@@ -83,6 +84,7 @@ __global__ __launch_bounds__(kThreads) void add_rmsnorm_kernel(const T* x, const
     int64_t t = token[blockIdx.x];
     t += t < 0 ? v : 0;                                  // negative: counted from the end
     bad = t < 0 || t >= v;
+    if (bad && outside && threadIdx.x == 0) *outside = 1.f;
     x += (bad ? 0 : t) * d - row;                        // (x + row is then the table's row)
   }
   const bool kept_out = EMBED || y;
@@ -540,31 +542,36 @@ template <typename... P> bool words(P... p) { return (((reinterpret_cast<uintptr
 
 template <typename T, int V, bool EMBED>
 static void launch_norm(const void* x, const void* y, const void* gain, void* x_out, void* h, float* rstd, int64_t rows, int64_t d,
-                        const int64_t* token, int64_t v, void* stream) {
+                        const int64_t* token, int64_t v, float* outside, void* stream) {
   auto go = [&](auto kern) {
     hipLaunchKernelGGL(kern, dim3((unsigned)rows), dim3(kThreads), 0, (hipStream_t)stream, (const T*)x, (const T*)y, (const T*)gain,
-                       (T*)x_out, (T*)h, rstd, d, token, v);
+                       (T*)x_out, (T*)h, rstd, d, token, v, outside);
   };
   if (d <= kThreads * V) go(add_rmsnorm_kernel<T, V, 1, EMBED>);
   else if (d <= 2 * kThreads * V) go(add_rmsnorm_kernel<T, V, 2, EMBED>);
   else go(add_rmsnorm_kernel<T, V, kKeep, EMBED>);
 }
 
-extern "C" int dec_embed_rmsnorm(int dtype, const void* table, const int64_t* token, const void* gain, void* x_out, void* h, float* rstd,
-                                 int64_t rows, int64_t d, int64_t v, void* stream) {
+extern "C" int dec_embed_rmsnorm_checked(int dtype, const void* table, const int64_t* token, const void* gain, void* x_out, void* h, float* rstd,
+                                         int64_t rows, int64_t d, int64_t v, float* outside, void* stream) {
   if (!sizes_ok(dtype, rows, d) || v < 1) return SECO_ERR_SHAPE;
   if (rows == 0) return SECO_OK;
-#define L(T, V) launch_norm<T, V, true>(table, nullptr, gain, x_out, h, rstd, rows, d, token, v, stream)
+#define L(T, V) launch_norm<T, V, true>(table, nullptr, gain, x_out, h, rstd, rows, d, token, v, outside, stream)
   DEC_DISPATCH(d, words(table, gain, x_out, h), L)
 #undef L
   return status();
+}
+
+extern "C" int dec_embed_rmsnorm(int dtype, const void* table, const int64_t* token, const void* gain, void* x_out, void* h, float* rstd,
+                                 int64_t rows, int64_t d, int64_t v, void* stream) {
+  return dec_embed_rmsnorm_checked(dtype, table, token, gain, x_out, h, rstd, rows, d, v, nullptr, stream);
 }
 
 extern "C" int dec_add_rmsnorm(int dtype, const void* x, const void* y, const void* gain, void* x_out, void* h, float* rstd,
                                int64_t rows, int64_t d, void* stream) {
   if (!sizes_ok(dtype, rows, d)) return SECO_ERR_SHAPE;
   if (rows == 0) return SECO_OK;
-#define L(T, V) launch_norm<T, V, false>(x, y, gain, x_out, h, rstd, rows, d, nullptr, 0, stream)
+#define L(T, V) launch_norm<T, V, false>(x, y, gain, x_out, h, rstd, rows, d, nullptr, 0, nullptr, stream)
   DEC_DISPATCH(d, words(x, y, gain, x_out, h), L)
 #undef L
   return status();

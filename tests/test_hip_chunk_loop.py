@@ -384,3 +384,23 @@ def test_step_whose_products_are_partly_the_frameworks():
     assert abs(loss_a - loss_b) < 1e-3 * loss_b
     for n in g_a:
         assert float((g_a[n].float() - g_b[n].float()).norm() / g_b[n].float().norm()) < 2e-2, n
+
+
+@pytest.mark.parametrize("dtype,cfg", [(torch.float32, F32_CFG), (torch.bfloat16, BF16_CFG)])
+@pytest.mark.parametrize("at,token", [(0, 29), (100, -30), (127, 1 << 40)])
+def test_tokens_outside_the_embedding_table_are_refused(dtype, cfg, at, token):
+    """In any chunk and schedule, also where no loss could tell (targets left out from that position on); negative ones within the
+    table count from its end, and a step behind a refused one is what it was."""
+    _, dec, tok, tgt = _setup(cfg, 23, 1, 128, dtype)
+    tok, tgt = tok.to(DEV), tgt.to(DEV)
+    loss, g = dec.step(tok, tgt, 32)
+    g = {n: t.clone() for n, t in g.items()}
+    bad, some = tok.clone(), tgt.clone()
+    bad[0, at], some[0, at:] = token, -100
+    for kw in ({}, {"selected": [2, 0], "factor": 2.0}, {"selected": [3]}, {"keep_attention_outputs": True}, {"stage1_chunk_len": 128}):
+        for targets in (tgt, some):
+            with pytest.raises(IndexError):
+                dec.step(bad, targets, 32, **kw)
+            assert all(t.grad is None for t in dec.p.values())
+    again, g_again = dec.step(torch.where(tok % 2 == 0, tok - cfg.vocab, tok), tgt, 32)
+    assert again == loss and all(torch.equal(g[n], g_again[n]) for n in g)
