@@ -61,25 +61,38 @@ struct BwdPlan {
 // Column tiles for a round or more (n_kv of them, iters iterations each): in how many shares a row tile of dQ joins them
 // in one launch, dQ first; 0: not.  The column tiles of a round all start together and reach the read-modify-write of
 // gK / gV together, and the last round is seldom full; dQ's workgroups, of another length, fill it and put them out of step.
-// Shares: the fewest that end within 0.9 of the time the column tiles take (few workgroups, few partial sums).  Against it
-// stand the row statistics, computed anew in every iteration.  So: up to 4 iterations; up to 8 behind more than a round, but
-// for four full rounds or more and nothing behind them; up to 12 where the last round is there to be filled, at most 0.65 of
-// it taken.  800 calls of 4 - 2400 rows on 256 - 3700 tiles, time of one launch over that of two: up to 4 iterations 0.66 - 0.98;
-// 5 - 8 0.69 - 1.04, 0.90 on average; 9 - 12 0.81 - 1.15, 0.92; not taken: 5 - 12 0.90 - 1.07, 0.99, 13 - 16
-// 0.88 - 1.27, more 0.84 - 1.47.  Two -> one, us:
+// Against it stand the row statistics, computed anew in every iteration.  So: up to 4 iterations; up to 8 behind more than a round, but
+// for four full rounds or more and nothing behind them; up to 12 where a last round leaves a tenth of all rounds' time or more, or where
+// dQ's row tiles are half of the CUs or more, so that its own round leaves CUs without work.  Beyond 4 iterations those tiles, whole in one
+// launch, may hold padding that they do not hold packed and divided: with two fifths more of them, from 9 iterations on three in ten,
+// only where the last round leaves three tenths or more.  5200 calls of 4 - 2400 rows on 256 - 3700 tiles and 2100 with padding, time of one launch
+// over that of two: up to 4 iterations 0.55 - 0.99; 5 - 8 0.62 - 1.10, 0.90 on average, with that padding 0.98 - 1.30, 1.14 (three tenths
+// left or more 0.73 - 1.01, 0.88); 9 - 12 0.74 - 1.18, 0.93, with padding 0.84 - 1.22, 1.05 (0.75 - 1.03, 0.95), others 0.87 - 1.17, 1.00; 13 - 16 0.82 - 1.22, 1.03.
+// Shares: the fewest that end within 0.9 of the time the column tiles take (few workgroups, few partial sums).  Of 1 to 1.25 rounds the last
+// leaves most CUs to dQ: an empirical 1.55 rounds, as long as the CUs without dQ's workgroups hold all column tiles in two (time over that
+// with the rounds there are, 5 - 8 iterations: 0.86 - 1.18, 0.97 on average; where they do not 0.87 - 1.16, 1.06), and with 7 or 8 iterations
+// only up to a sixteenth of the second round if its tiles are shared out (beyond it 0.86 - 1.18, 1.00, but some calls longer than in two
+// launches); more shares than that leave few CUs to the first column tiles (66 rows at 4663 of 48/8 heads, 240 workgroups for 160: 55 -> 69 us).
+// Two launches -> one, us:
 //   32/8 heads  32 at 16256: 103 -> 75   64 at 8128: 64 -> 52   128 at 8064: 83 -> 75   128 at 14000: 139 -> 124
 //   8/8  128 at 4000: 43 -> 32           16/8  256 at 8000: 92 -> 79                    16/2  64 at 32000: 105 -> 82
-inline int rounds_in_one_launch(int n_kv, int iters, int tiles, int max_splits) {
+// row_tiles, whole: those of dQ packed, and whole in one launch; shared: whether column tiles are shared out
+inline int rounds_in_one_launch(int n_kv, int iters, int tiles, int max_splits, int row_tiles, int whole, bool shared) {
   const int cus = device_cus(), full = n_kv / cus, rest = n_kv % cus;
-  const bool pays = iters <= 4 || (n_kv > cus && (iters <= 8 ? rest > 0 || full < 4 : iters <= 12 && rest > 0 && 20 * rest <= 13 * cus));
+  auto left_over = [&](int tenths) { return rest > 0 && 10 * (cus - rest) >= tenths * cus * (full + 1); };
+  const bool pays = iters <= 4 || (n_kv > cus && (iters <= 8 ? rest > 0 || full < 4 : iters <= 12 && (left_over(1) || 2 * row_tiles > cus)));
   if (!pays) return 0;
-  // (up to a quarter of a second round is not over when the first is: 1.55 rounds.  64 such calls 1.03 times as fast with the fewer
-  // shares that leaves, 0.90 - 1.14; 64 rows at 4032 of 32/8 heads 34.6 -> 32.1 us, 67 at 17016 of 16/2 81.9 -> 66.6; up to one and a half
-  // rounds 0.995)
-  const float rounds = 4 * n_kv < 5 * cus ? 1.55f : (float)n_kv / cus;
-  int n = 1;
-  while (n < max_splits && kDqFrontTime.of((tiles + n - 1) / n) > 0.9f * rounds * kDkdvRoundTime.of(iters)) ++n;
-  return n;
+  auto shares = [&](float rounds) {
+    int n = 1;
+    while (n < max_splits && kDqFrontTime.of((tiles + n - 1) / n) > 0.9f * rounds * kDkdvRoundTime.of(iters)) ++n;
+    return n;
+  };
+  const bool few_behind = 4 * n_kv < 5 * cus;
+  int n = shares(few_behind ? 1.55f : (float)n_kv / cus);
+  if (few_behind && iters <= 8 && (2 * (cus - (n > 1 ? n * row_tiles : whole)) < n_kv || (iters > 6 && shared && 16 * n_kv > 17 * cus)))
+    if (const int more = shares((float)n_kv / cus); 16 * more * row_tiles < 15 * cus) n = more;
+  const bool padded = n == 1 && 10 * whole > (iters <= 8 ? 14 : 13) * row_tiles;
+  return padded && iters > 4 && !left_over(3) ? 0 : n;
 }
 
 // When the last of a row of workgroups ends on `places` that take them in order: the places by the time they are free at, those
@@ -219,7 +232,7 @@ BwdPlan plan_both(const AttnParams& p, const SegTable& seg, bool dq) {
   auto dq_part = [&](int n) { return n > 1 ? (n * dq_bytes + 255) / 256 * 256 : (size_t)0; };
   if ((int64_t)n_units * n_ctiles >= cus) {
     if (sp.items >= cus) return best;
-    const int n = rounds_in_one_launch(n_units * n_ctiles, runs.iters[0], tiles, p.n_splits);
+    const int n = rounds_in_one_launch(n_units * n_ctiles, runs.iters[0], tiles, p.n_splits, sp.items, dq_wgs(1), best.ts.plan.n_shared > 0);
     if (n > 0 && dq_part(n) <= p.tail_bytes) {
       best.dq_splits = n;
       best.kv_first = false;

@@ -360,6 +360,19 @@ int main() {
       CHECK(without.ts.plan.n_tiles == alone.n_tiles && without.ts.plan.n_entries == alone.n_entries);
     }
   }
+  // a round or more of column tiles: one launch by their iterations, by what a last round leaves over, and by dQ's row tiles, which
+  // in one launch of full workgroups are whole and hold padding.  (B, Hq, Hkv, C, q_start, shares of dQ; 0: two launches)
+  for (const int* s : {(const int[]){4, 64, 8, 64, 11814, 0}, (const int[]){4, 64, 8, 41, 4359, 0}, (const int[]){4, 48, 8, 44, 12097, 0},   // half of them padding
+                       (const int[]){4, 48, 8, 50, 1050, 1}, (const int[]){4, 32, 8, 145, 10190, 0}, (const int[]){4, 32, 8, 85, 1190, 1},
+                       (const int[]){1, 16, 4, 175, 14784, 0}, (const int[]){1, 24, 8, 181, 7240, 0}, (const int[]){1, 32, 32, 617, 3916, 1},   // full rounds but for a tenth
+                       (const int[]){1, 8, 8, 532, 6442, 4},
+                       (const int[]){1, 16, 4, 88, 8779, 10}, (const int[]){1, 48, 8, 66, 4663, 4}, (const int[]){1, 32, 8, 64, 4032, 4}}) {   // a little over a round, one round
+    seco_desc d = desc(SECO_BF16, s[3], s[4], s[1], s[2]);
+    d.batch = s[0];
+    CHECK(seco_chunk_attn_bwd(&d, FAKE, FAKE, FAKE, FAKE, FAKEF, FAKE, FAKE, FAKEF, FAKEF, FAKE,
+                              seco_workspace_bytes(&d, SECO_OP_BWD), nullptr) == SECO_OK);
+    CHECK(seco::plan_bwd<Cfg>(g_stub.last, g_stub.dkdv_tables.back(), true).dq_splits == s[5]);
+  }
   // workgroups laid out in groups end when they do one by one (whole microseconds: no two groups are taken as one), also past the
   // room for groups; the choice of shares for several numbers of compute units is that for each
   {
