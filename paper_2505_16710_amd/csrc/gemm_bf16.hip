@@ -573,21 +573,10 @@ template <typename A, typename B> int launch_pair(GemmArgs a, GemmArgs b, hipStr
   hipLaunchKernelGGL(kern, dim3(ga + gb), dim3(512), smem, s, a, b, weight_first ? gb : ga, weight_first);
   return launch_status();
 }
-// Whether the 32 x 64 tiles of a data gradient whose contraction wavefronts divide become 64 x 64 ones beside a weight gradient in
-// bm x bn tiles.  By itself the taller tile only leaves CUs idle; here those work on the other product, and an operand comes from the L2s,
-// which bound both, a third less often (512 rows, 1024 x 4096: 134 for 201 MB).  They go in front, half of the chip for long, the weight
-// gradient's tiles on the other half (behind those: 22.3 for 17.3 us).  us, 32 rows -> 64:
-//   512 rows  1024 x 4096 19.1 -> 17.3   1024 x 2048 12.3 -> 10.6   1024 x 1536 10.4 -> 9.7   1024 x 512 7.0 -> 5.5
-//   384 rows  1024 x 4096 16.8 -> 16.3   1024 x 1536  9.5 ->  8.6   1024 x 1024  7.9 -> 7.3
-// From three eighths of the CUs on (320 rows, 1024 x 4096 15.3 / 15.9, 1024 x 1536 7.9 / 8.5; 64 rows 11.6 / 15.5), not where the
-// rows fill out the tiles badly (87 x 3008 x 256 3.9 / 4.2), nor, with more than 7/16 of the CUs taken and weight gradients in small
-// tiles, where some of those start a second round of an XCD's CUs by themselves (777 x 640 x 1024 9.8 / 10.8).  62 random calls that the rule
-// takes are 0.92 - 1.45 times as fast, 1.10 on average (each behind large products: in short bursts everything is faster).
+// taller_pays of the tiles: a data gradient in 32 x 64 or 64 x 64, beside a weight gradient in bm x bn
 inline bool taller_beside(const GemmArgs& a, const GemmArgs& b, int bm, int bn) {
-  const int64_t n64 = (a.N + 63) / 64, low = (a.M + 31) / 32 * n64, tall = (a.M + 63) / 64 * n64, cus = device_cus();
-  if (8 * tall < 3 * cus || 16 * tall > 9 * low) return false;
-  const int64_t other = (int64_t)((b.M + bm - 1) / bm) * ((b.N + bn - 1) / bn), per_xcd = (tall + 7) / 8 + (other + 7) / 8;
-  return (bm == 128 && bn == 128) || 16 * tall <= 7 * cus || 8 * per_xcd <= cus || 32 * per_xcd >= 5 * cus;
+  const int64_t n64 = (a.N + 63) / 64;
+  return taller_pays(a.M, a.K, (a.M + 31) / 32 * n64, (a.M + 63) / 64 * n64, (int64_t)((b.M + bm - 1) / bm) * ((b.N + bn - 1) / bn));
 }
 constexpr int kApart = 1;           // (no seco_status)
 // In one launch where the data gradient takes one of the small tiles and as many of its workgroups share a CU as by itself

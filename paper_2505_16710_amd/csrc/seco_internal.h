@@ -468,6 +468,29 @@ int launch_dkdv32_bf16(const AttnParams& p, const SegTable& seg, const TailSplit
 #endif
 constexpr int kColTileBf16 = SECO_DKDV_COLS;  // columns per workgroup in launch_dkdv_bf16
 
+// Both gradients of a product in one launch (gemm_bf16.hip): whether the 32 x 64 tiles (`low`) of a data gradient whose contraction
+// wavefronts divide become 64 x 64 ones (`tall`) beside `other` tiles of a weight gradient.  By itself the taller tile only leaves CUs
+// idle; here those work on the other product, and an operand comes from the L2s, which bound both, a third less often (512 rows,
+// 1024 x 4096: 134 for 201 MB).  They go in front, half of the chip for long, the weight gradient's tiles on the other half (behind those:
+// 22.3 for 17.3 us).  us, 32 rows -> 64:
+//   512 rows  1024 x 4096 19.1 -> 17.3   1024 x 2048 12.3 -> 10.6   1024 x 1536 10.4 -> 9.7   1024 x 512 7.0 -> 5.5
+//   384 rows  1024 x 4096 16.8 -> 16.3   1024 x 1536  9.5 ->  8.6   1024 x 1024  7.9 -> 7.3
+// What it gains first is a round: a workgroup has a CU to itself, and with fewer of them an XCD's 32 CUs are done in one round where they
+// took two (530 random calls: time over that with low tiles 0.69 - 1.05, 0.84 on average).  With as many rounds as before it gains what the
+// L2s deliver less, where the data gradient reads more than the weight gradient (a contraction of twice the rows), from 320 rows and an eighth of
+// a round behind the first on, while the long workgroups are half of the CUs or fewer and the second round does not take a second half for
+// a few more (207 calls 0.77 - 1.06, 0.91; the others 0.81 - 1.28, 1.01: 97 rows, 3520 x 1280 12.0 / 13.3; 1015, 448 x 1344 11.8 / 12.7; 331,
+// 1408 x 2880 16.9 / 19.0).  Not with fewer tall tiles than three eighths of the CUs (320 rows, 1024 x 4096 15.3 / 15.9; 64 rows 11.6 / 15.5).
+// (Each call timed behind large products: in short bursts everything is faster.)
+inline bool taller_pays(int64_t rows, int64_t contraction, int64_t low, int64_t tall, int64_t other) {
+  const int64_t cus = device_cus();
+  auto per_xcd = [&](int64_t n) { return (n + 7) / 8 + (other + 7) / 8; };
+  auto rounds = [&](int64_t n) { return (8 * per_xcd(n) + cus - 1) / cus; };
+  if (8 * tall < 3 * cus) return false;
+  const int64_t all = 64 * per_xcd(tall);
+  return rounds(tall) < rounds(low) || (rows >= 320 && contraction >= 2 * rows && 2 * tall <= cus && all >= 9 * cus && all <= 12 * cus);
+}
+
 // Bandwidth-bound helpers; each takes a pair of tensors (gK and gV, keys and values) handled by one launch,
 // a NULL member of the pair is skipped.
 int launch_kvgrad_zero(float* ga, float* gb, int B, int H, int D, const int64_t gs[3], int64_t r0, int64_t r1,

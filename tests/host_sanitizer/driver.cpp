@@ -292,6 +292,13 @@ int main() {
     CHECK(s[1] >= 4 ? busy > 0.5f && busy < 0.7f : busy == 1.f);
   }
   CHECK(seco::dq_leaves_cus(256, 23592) && !seco::dq_leaves_cus(256, 23593) && !seco::dq_leaves_cus(257, 257));
+  // taller tiles beside a weight gradient (rows, K, n, that gradient's tiles): a round of an XCD saved, or long contractions
+  for (const int* s : {(const int[]){512, 1024, 4096, 256, 1}, (const int[]){512, 1024, 2048, 128, 1}, (const int[]){512, 1024, 1024, 256, 1}, (const int[]){384, 1024, 1536, 192, 1},
+                       (const int[]){140, 2560, 192, 120, 1}, (const int[]){97, 3520, 1280, 280, 0}, (const int[]){1015, 448, 1344, 147, 0}, (const int[]){2701, 192, 5312, 249, 0}, (const int[]){331, 1408, 2880, 253, 0},
+                       (const int[]){1139, 384, 128, 12, 0}, (const int[]){320, 1024, 4096, 256, 0}, (const int[]){87, 3008, 256, 188, 0}}) {
+    const int n64 = (s[1] + 63) / 64;
+    CHECK(seco::taller_pays(s[0], s[2], (s[0] + 31) / 32 * n64, (s[0] + 63) / 64 * n64, s[3]) == (s[4] != 0));
+  }
   // the small forward's cache: three rounds saved are worth a merge until its workgroups read at the memory's rate
   CHECK(seco::small_divides(8, 3) && seco::small_divides(112, 3) && !seco::small_divides(113, 3) && seco::small_divides(128, 4) && !seco::small_divides(1, 2));
   // the 4-wavefront forward's turns: not with three or four KV heads to an XCD around two rounds

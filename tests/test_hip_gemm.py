@@ -161,6 +161,7 @@ def test_gemm_refuses_what_it_cannot_do():
 @pytest.mark.parametrize("M,K,n,silu", [
     (384, 1024, 64, False), (383, 1024, 1536, True), (449, 1024, 512, False), (1001, 512, 576, True), (1472, 256, 2304, False),
     (200, 1536, 1024, False), (8, 6144, 64, False), (775, 640, 1024, False),
+    (140, 2560, 192, True), (512, 1024, 2048, False),      # a round of an XCD saved: last tiles of 12 rows, and beside 128 x 128 ones
 ])
 def test_gradients_in_one_launch_with_taller_tiles(M, K, n, silu, first):
     """Around the line where the data gradient takes 64 rows to a tile (96 tiles, rows that fill them or not, weight gradients that do
