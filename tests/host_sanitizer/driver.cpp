@@ -39,7 +39,57 @@ struct Cfg { static constexpr int kCols = 128, kBQ = 64; };   // (of the dK/dV k
 static void* const FAKE = reinterpret_cast<void*>(0x10000);
 static float* const FAKEF = reinterpret_cast<float*>(0x10000);
 
-int main() {
+// Calls named on the command line (joined_shapes.py), which the rules are to plan with stages of several heads' rows (kJoined):
+// d:B,Hq,Hkv,C,q_start dense; g:...,later rows the transposed order; s:B,Hq,Hkv,C,chunks,selected... dQ over those; w:...,chunks... dK/dV
+// over those.  Between them they have to reach every form of the kernel.
+struct Forms {
+  bool divided, whole, apart16, apart32, shared_one, shared_apart, late_one, late_apart, late_gather, selected_divided, selected_whole;
+};
+static void check_joined(const char* arg, Forms& seen) {
+  std::vector<int> v;
+  for (const char* c = arg + 1; *c; c += std::strcspn(c, ",")) v.push_back(std::atoi(++c));
+  const char kind = arg[0];
+  const bool chunks = kind == 's' || kind == 'w';
+  const int C = v[3], n = chunks ? v[4] : 1, q_start = chunks ? (n - 1) * C : v[4];
+  seco_desc d = desc(SECO_BF16, C, q_start, v[1], v[2]);
+  d.batch = v[0];
+  const size_t bytes = seco_workspace_bytes(&d, SECO_OP_BWD);
+  std::vector<float> w(n, kind == 'w' ? 0.f : 1.f), wq(n, 0.f);
+  for (size_t i = 5; i < v.size() && chunks; ++i) (kind == 's' ? wq : w)[v[i]] = 1.f + i;
+  w[n - 1] = wq[n - 1] = 1.f;
+  const int rc =
+      kind == 'g'   ? seco_chunk_attn_bwd_gather(&d, FAKE, FAKE, FAKE, FAKE, FAKEF, FAKE, FAKE, FAKEF, FAKEF, FAKEF, (q_start + C + v[5] + 3) / 4 * 4,
+                                                 v[5], FAKE, bytes, nullptr)
+      : kind == 'd' ? seco_chunk_attn_bwd(&d, FAKE, FAKE, FAKE, FAKE, FAKEF, FAKE, FAKE, FAKEF, FAKEF, FAKE, bytes, nullptr)
+      : kind == 's' ? spaco_chunk_attn_bwd_sparse_dq(&d, FAKE, FAKE, FAKE, FAKE, FAKEF, FAKE, FAKE, FAKEF, FAKEF, w.data(), wq.data(), n, C, FAKE,
+                                                     bytes, nullptr)
+                    : spaco_chunk_attn_bwd(&d, FAKE, FAKE, FAKE, FAKE, FAKEF, FAKE, FAKE, FAKEF, FAKEF, w.data(), n, C, FAKE, bytes, nullptr);
+  CHECK(rc == SECO_OK);
+  const seco::AttnParams& p = g_stub.last;
+  const seco::SegTable& seg = g_stub.dkdv_tables.back();
+  const seco::BwdPlan plan = seco::plan_bwd<Cfg>(p, seg, kind != 'g');
+  if (!plan.joined) std::fprintf(stderr, "%s: stages of one head each\n", arg);
+  CHECK(plan.joined);
+  // (late: the last column tile begins a stage or more behind the chunk's first row)
+  const int begin = seg.col_begin[seg.n - 1], last = begin + (seg.col_end[seg.n - 1] - begin - 1) / Cfg::kCols * Cfg::kCols;
+  const bool late = last >= p.q_start + Cfg::kBQ, one = plan.dq_splits > 0, shared = plan.ts.plan.n_shared > 0;
+  if (kind == 'g') {
+    seen.late_gather |= late;
+  } else if (kind == 's') {
+    CHECK(one);
+    (seco::sparse_shares(p, g_stub.dq_tables.back(), plan.dq_splits) > 1 ? seen.selected_divided : seen.selected_whole) = true;
+  } else if (kind == 'd') {
+    (one ? (plan.dq_splits > 1 ? seen.divided : seen.whole) : plan.busy >= 0.74f ? seen.apart16 : seen.apart32) = true;   // (kBusy)
+    if (shared) (one ? seen.shared_one : seen.shared_apart) = true;
+    if (late) (one ? seen.late_one : seen.late_apart) = true;
+  }
+}
+
+int main(int argc, char** argv) {
+  Forms seen{};
+  for (int i = 1; i < argc; ++i) check_joined(argv[i], seen);
+  CHECK(argc == 1 || (seen.divided && seen.whole && seen.apart16 && seen.apart32 && seen.shared_one && seen.shared_apart && seen.late_one &&
+                      seen.late_apart && seen.late_gather && seen.selected_divided && seen.selected_whole));
   // ---- division by multiplication: around every multiple that can go wrong, up to the largest dividend ----
   for (int d : {1, 2, 3, 5, 7, 31, 32, 33, 255, 640, 641, 4095, 65537, 16777213, 1 << 30, (1 << 30) + 1, 0x7fffffff}) {
     const seco::Div by = seco::make_div(d);

@@ -10,6 +10,7 @@ from oracle import attention as A
 from oracle import selection as S
 from workloads import CONFIGS, full_layer, small_layer, kv_group, Config
 
+import joined_shapes
 from hip_driver import DEV, max_rel, max_rel_per_head, run_layer, to_dev, to_host
 
 pytestmark = pytest.mark.gpu
@@ -347,26 +348,15 @@ def test_bf16_backward_of_several_rounds_in_one_launch(B, Hq, Hkv, C, q_start, a
             assert max_rel(to_host(got[2][b, kh]), to_host(rv)) <= TOL["bf16"]["gv"], (b, kh)
 
 
-@pytest.mark.parametrize("B,Hq,Hkv,C,q_start", [
-    (1, 4, 2, 1, 64),          # one row of two heads; a column tile that starts at it
-    (2, 8, 2, 5, 123),         # a stage of all four heads' rows, and 44 that do not exist
-    (1, 8, 1, 16, 240),        # heads that end with the stages
-    (1, 16, 2, 21, 300),       # a stage and its half end inside heads; the last stage 40 rows
-    (1, 16, 2, 31, 98),        # heads shorter than the 32 rows of a block of scores, on the diagonal
-    (2, 16, 4, 32, 96),
-    (2, 32, 8, 47, 1500),      # heads that end inside every stage and every block
-    (1, 32, 8, 66, 1100),      # a head's rows longer than a stage; its last two begin another column tile
-    (1, 64, 8, 70, 2500),      # shared out, a share's first stage behind a head's end
-    (1, 32, 8, 19, 8300),      # several rounds of column tiles
-    (1, 16, 8, 300, 40),       # stages of one head each
-    (1, 32, 8, 150, 6100),     # dK/dV by itself, 16x16x32 products
-    (2, 16, 2, 70, 13000),     # likewise, column tiles of the last round shared out
+@pytest.mark.parametrize("B,Hq,Hkv,C,q_start", joined_shapes.DENSE + [
+    # near the rule's line, stages of one head each
+    (1, 16, 2, 21, 300), (1, 16, 2, 31, 98), (2, 32, 8, 47, 1500), (1, 16, 8, 300, 40), (1, 32, 8, 150, 6100), (2, 16, 2, 70, 13000),
 ])
 @pytest.mark.parametrize("rows_first", [False, True])
 def test_bf16_dkdv_stages_of_several_heads(B, Hq, Hkv, C, q_start, rows_first):
     """Query rows of the heads of a group one behind the other in the stages of dK/dV, in both layouts, added to what the buffers
     hold, in one launch and (dQ written over O) in two: the same bits, within the tolerance of fp32 on the device."""
-    N, s, G = q_start + C, 1 / np.sqrt(128), Hq // Hkv
+    N, s = q_start + C, 1 / np.sqrt(128)
     g = torch.Generator(device=DEV).manual_seed(67)
     rand = lambda *shape: torch.randn(*shape, device=DEV, generator=g).to(torch.bfloat16)
     rows = lambda: rand(B, C, Hq, 136).transpose(1, 2)[..., :128] if rows_first else rand(B, Hq, C, 128)
@@ -380,17 +370,68 @@ def test_bf16_dkdv_stages_of_several_heads(B, Hq, Hkv, C, q_start, rows_first):
     got, again, over = run(None), run(None), run(o)
     assert all(torch.equal(a, b) for a, b in zip(got, again))
     assert torch.equal(got[1], over[1]) and torch.equal(got[2], over[2])
+    _check_gk_gv(q, k, v, of, lse, do, q_start, s, got[1], got[2], 0.5, -0.25)
+
+
+def _check_gk_gv(q, k, v, of, lse, do, q_start, s, gk, gv, gk0, gv0, col_w=1.0):
+    """gK and gV (gk0 and gv0 before) within the tolerance of fp32 on the device; col_w: each cache row's weight."""
+    B, Hq, C, _ = q.shape
+    Hkv, N = k.shape[1:3]
+    G = Hq // Hkv
     below = torch.arange(N, device=DEV)[None, :] > torch.arange(C, device=DEV)[:, None] + q_start
     for b in range(B):
         for kh in range(Hkv):
-            kf, vf, rk, rv = k[b, kh].float(), v[b, kh].float(), 0.5, -0.25
+            kf, vf, rk, rv = k[b, kh].float(), v[b, kh].float(), gk0, gv0
             for h in range(kh * G, kh * G + G):
                 qf, dof = q[b, h].float(), do[b, h].float()
                 p = torch.exp((qf @ kf.t() * s).masked_fill(below, float("-inf")) - lse[b, h][:, None])
                 ds = p * (dof @ vf.t() - (dof * of[b, h]).sum(-1, keepdim=True))
-                rk, rv = rk + s * ds.t() @ qf, rv + p.t() @ dof
-            assert max_rel(to_host(got[1][b, kh]), to_host(rk)) <= TOL["bf16"]["gk"], (b, kh)
-            assert max_rel(to_host(got[2][b, kh]), to_host(rv)) <= TOL["bf16"]["gv"], (b, kh)
+                rk, rv = rk + s * (ds * col_w).t() @ qf, rv + (p * col_w).t() @ dof
+            assert max_rel(to_host(gk[b, kh]), to_host(rk)) <= TOL["bf16"]["gk"], (b, kh)
+            assert max_rel(to_host(gv[b, kh]), to_host(rv)) <= TOL["bf16"]["gv"], (b, kh)
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,C,q_start,later", joined_shapes.GATHER)
+def test_bf16_transposed_order_with_stages_of_several_heads(B, Hq, Hkv, C, q_start, later):
+    """A chunk's gK and gV rows from its own query rows and the later ones, row statistics of the later rows from their own calls."""
+    N, s = q_start + C + later, 1 / np.sqrt(128)
+    g = torch.Generator(device=DEV).manual_seed(68)
+    q, do, k, v = (torch.randn(B, h, N, 128, device=DEV, generator=g).to(torch.bfloat16) for h in (Hq, Hq, Hkv, Hkv))
+    chunks = [(s0, n) for s0, n in ((q_start, C), (q_start + C, later)) if n]
+    o, dq = torch.empty_like(q), torch.empty_like(q)          # (q, o and their gradients share their strides)
+    lses = [seco.seco_chunk_attn_fwd(q[:, :, s0:s0 + n], k, v, s0, s, o=o[:, :, s0:s0 + n])[1] for s0, n in chunks]
+    gk, gv = (torch.full((B, Hkv, N, 128), float("nan"), device=DEV) for _ in range(2))
+    stats = torch.full((2, B, Hq, (N + 3) // 4 * 4), float("nan"), device=DEV)
+    seco.kvgrad_zero(gk, gv)
+    for (s0, n), lse in reversed(list(zip(chunks, lses))):
+        seco.seco_chunk_attn_bwd_gather(q[:, :, s0:], k, v, o[:, :, s0:s0 + n], lse, do[:, :, s0:], gk, gv, s0, s, n, stats, d_q=dq[:, :, s0:s0 + n])
+    rows = slice(q_start, N)
+    inside = ((torch.arange(N, device=DEV) >= q_start) & (torch.arange(N, device=DEV) < q_start + C)).float()
+    mine = slice(q_start, q_start + C)
+    gk_mine, gv_mine = torch.zeros_like(gk), torch.zeros_like(gv)
+    gk_mine[:, :, mine], gv_mine[:, :, mine] = gk[:, :, mine], gv[:, :, mine]
+    _check_gk_gv(q[:, :, rows], k, v, o[:, :, rows].float(), torch.cat(lses, 2), do[:, :, rows], q_start, s, gk_mine, gv_mine, 0.0, 0.0, inside)
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,C,k,weights", joined_shapes.WEIGHTED)
+def test_bf16_chunk_weights_with_stages_of_several_heads(B, Hq, Hkv, C, k, weights):
+    """Every chunk's own weight, negative and equal neighbours among them; rows of chunks without one stay as they are.  dQ over all columns
+    and over the weighted chunks: the same gK and gV."""
+    N, s, j = k * C, 1 / np.sqrt(128), (k - 1) * C
+    g = torch.Generator(device=DEV).manual_seed(69)
+    rand = lambda *shape: torch.randn(*shape, device=DEV, generator=g).to(torch.bfloat16)
+    q, do, kc, vc = rand(B, Hq, C, 128), rand(B, Hq, C, 128), rand(B, Hkv, N, 128), rand(B, Hkv, N, 128)
+    o, lse = seco.seco_chunk_attn_fwd(q, kc, vc, j, s)
+    w = [weights.get(i, 0.0) for i in range(k)]
+    def run(dq_weight):
+        gk, gv = torch.full((B, Hkv, N, 128), 0.5, device=DEV), torch.full((B, Hkv, N, 128), -0.25, device=DEV)
+        seco.spaco_chunk_attn_bwd(q, kc, vc, o, lse, do, gk, gv, j, s, w, C, dq_weight=dq_weight)
+        return gk, gv
+    got, again, sparse = run(None), run(None), run([2.0 if i in weights else 0.0 for i in range(k - 1)] + [1.0])
+    assert all(torch.equal(a, b) for a, b in zip(got + got, again + sparse))
+    col_w = torch.tensor(w, device=DEV).repeat_interleave(C)
+    assert (got[0][:, :, col_w == 0] == 0.5).all() and (got[1][:, :, col_w == 0] == -0.25).all()
+    _check_gk_gv(q, kc, vc, o.float(), lse, do, j, s, *got, 0.5, -0.25, col_w)
 
 
 @pytest.mark.parametrize("B,Hq,Hkv,C,k,picked", [
@@ -399,9 +440,10 @@ def test_bf16_dkdv_stages_of_several_heads(B, Hq, Hkv, C, q_start, rows_first):
     (2, 8, 1, 129, 9, [1, 2, 3, 6, 8]),      # row tiles of one row
     (1, 8, 8, 64, 90, [5, 50, 89]),          # column tiles for more than one round behind dQ's
     (1, 16, 2, 300, 30, [0, 28, 29]),        # two launches
+    *joined_shapes.SELECTED,                 # stages of several heads' rows, whole row tiles and shares
 ])
 def test_bf16_dq_over_selected_columns_with_dkdv_in_one_launch(B, Hq, Hkv, C, k, picked):
-    """dQ against fp32 on the device; gK and gV have the bits of the call whose dQ sees all columns."""
+    """dQ, gK and gV against fp32 on the device; gK and gV have the bits of the call whose dQ sees all columns."""
     N, s, G, j = k * C, 1 / np.sqrt(128), Hq // Hkv, (k - 1) * C
     g = torch.Generator(device=DEV).manual_seed(66)
     rand = lambda *shape: torch.randn(*shape, device=DEV, generator=g).to(torch.bfloat16)
@@ -414,6 +456,7 @@ def test_bf16_dq_over_selected_columns_with_dkdv_in_one_launch(B, Hq, Hkv, C, k,
     got, again, dense = run(wq), run(wq), run(None)
     assert all(torch.equal(a, b) for a, b in zip(got, again))
     assert torch.equal(got[1], dense[1]) and torch.equal(got[2], dense[2])
+    _check_gk_gv(q, kc, vc, o.float(), lse, do, j, s, got[1], got[2], 0.0, 0.0)
     rows = torch.arange(C, device=DEV)[:, None] + j
     col_w = torch.tensor(wq, device=DEV).repeat_interleave(C)
     for b in range(B):
