@@ -398,9 +398,11 @@ int main(int argc, char** argv) {
     p.os[0] = p.os[1] = (int64_t)1 << 61;
     CHECK(!seco::o_over_inputs(p, 4));
   }
-  // ---- the plan of a backward: both passes in one launch only while dQ is still to go out ----
+  // ---- the plan of a backward: both passes in one launch only while dQ is still to go out; by itself dK/dV shares out the iterations of
+  // the stages that it walks (joined: of several heads' rows; the last two only then, {32, 8, 199, 8127} with shared tiles) ----
   {
-    const int shapes[][4] = {{8, 8, 64, 6400}, {32, 8, 745, 0}, {8, 2, 32, 3488}, {32, 8, 32, 0}};
+    const int shapes[][6] = {{8, 8, 64, 6400, 1, 0}, {32, 8, 745, 0, 1, 0}, {8, 2, 32, 3488, 1, 1}, {32, 8, 32, 0, 1, 1},
+                             {32, 4, 1200, 4000, 0, 0}, {32, 8, 150, 16000, 0, 1}, {32, 8, 199, 8127, 0, 1}};
     for (const auto& sh : shapes) {
       const seco_desc d = desc(SECO_BF16, sh[2], sh[3], sh[0], sh[1]);
       CHECK(seco_chunk_attn_bwd(&d, FAKE, FAKE, FAKE, FAKE, FAKEF, FAKE, FAKE, FAKEF, FAKEF, FAKE,
@@ -408,13 +410,27 @@ int main(int argc, char** argv) {
       const seco::AttnParams p = g_stub.last;
       const seco::SegTable& seg = g_stub.dkdv_tables.back();
       const seco::BwdPlan with = seco::plan_bwd<Cfg>(p, seg, true), without = seco::plan_bwd<Cfg>(p, seg, false);
-      CHECK(with.dq_splits > 0 && without.dq_splits == 0 && without.ts.part == p.tail_part);
+      CHECK((with.dq_splits > 0) == (sh[4] != 0) && without.dq_splits == 0 && without.ts.part == p.tail_part);
+      CHECK(without.joined == (sh[5] != 0) && (sh[4] || with.joined == without.joined));
       seco::RowRuns none;
       none.n = 0;
-      float time;
-      const seco::SharePlan alone = seco::share_plan(seco::tile_iterations<Cfg, false>(p, seg, none), p.B * p.Hkv, seg.tile_begin[seg.n], p.G,
-                                                     p.C, seco::slots_in(p.tail_bytes), time);
-      CHECK(without.ts.plan.n_tiles == alone.n_tiles && without.ts.plan.n_entries == alone.n_entries);
+      float time, busy;
+      const seco::IterRuns runs = seco::tile_iterations<Cfg, false>(p, seg, none, without.joined);
+      const seco::SharePlan alone = seco::share_plan(runs, p.B * p.Hkv, seg.tile_begin[seg.n], p.G, p.C, seco::slots_in(p.tail_bytes), time, &busy);
+      const seco::BwdPlan& apart = sh[4] ? without : with;
+      const seco::SharePlan& got = apart.ts.plan;
+      CHECK(apart.busy == busy && got.n_tiles == alone.n_tiles && got.n_shared == alone.n_shared && got.n_entries == alone.n_entries);
+      CHECK(std::equal(alone.tile_of, alone.tile_of + alone.n_entries, got.tile_of));
+      CHECK(alone.n_tiles == 0 || std::equal(alone.first, alone.first + alone.n_tiles + 1, got.first));
+      // no workgroup of a shared tile is left without an iteration
+      for (int i = 0; i < got.n_shared; ++i) {
+        int tile = i, it = 0;
+        seco::for_last(runs, got.n_tiles, [&](int iters, int count) {
+          if (tile >= 0 && tile < count) it = iters;
+          tile -= count;
+        });
+        CHECK(got.first[i + 1] - got.first[i] <= it);
+      }
     }
   }
   // a round or more of column tiles: one launch by their iterations, by what a last round leaves over, and by dQ's row tiles, which
