@@ -14,7 +14,7 @@ The projections and the MLP, the residual adds, norms, SiLU, loss and embedding 
 kernels of the library too (gemm_bf16.hip, decoder.hip), the derivatives are written out instead of being recorded, and
 a chunk is launched by one call of the binding's extension module (chunk_step_ext.cpp): at the row counts of a chunk a
 step is bound by the number of launches and the host time behind each (with autograd and framework operators, 27 ms for
-two layers over 4096 tokens in chunks of 512, of which the GPU worked 14; 3.8 now).  Products whose type or alignment
+two layers over 4096 tokens in chunks of 512, of which the GPU worked 14; 3.4 now).  Products whose type or alignment
 the library's kernel does not take (fp32, row lengths that are not multiples of 8) and large ones, which the framework's
 kernels do faster, go through the framework's.  Only one chunk's activations are alive at a time, as in the paper.
 There is no CPU path.  (LayerState, ChunkAttention and Rope are the same attention as autograd functions.)

@@ -32,12 +32,12 @@ IterRuns tile_iterations(const AttnParams& p, const SegTable& seg, const RowRuns
 // Whether the stages of dK/dV cut the rows of a group's heads one behind the other (kJoined): by the part of the iterations that
 // saves.  From a quarter of a round of column tiles on, three in ten; with fewer tiles, whose iterations workgroups share out so that
 // less is gained from fewer of them than addresses and positions per row cost, two thirds, or half of four or less, which are not
-// shared out.  900 random calls of 2 - 1000 rows, time apart over time joined, by the part saved: more than 70 % 1.01 - 1.75, 1.3 on
-// average; 35 - 55 % 1.09 from 64 tiles on and 0.85 - 1.21 below; 20 - 35 % 0.94 - 1.12; less 0.95 - 1.02.  us, apart -> joined:
+// shared out.  15700 random calls of 1 - 1000 rows, time joined over time apart, by the part saved: more than 70 % 0.47 - 1.11, 0.74 on
+// average; 35 - 70 % 0.60 - 1.08, 0.90; 30 - 35 % 0.77 - 1.17, 0.96; of those not taken 0.59 - 1.43, 0.99.  us, apart -> joined:
 //   32/8 heads  32 at 16352: 87.4 -> 75.4   16 at 8000: 48.0 -> 36.8   16/8 x 2  14 at 6000: 51.9 -> 47.6
 //   16/2  9 at 900: 17.0 -> 13.9   70 at 20000: 94.2 -> 64.4
-// A dK/dV pass of its own, with its row statistics at hand and one and a half rounds of tiles or more: a tenth (120 random calls:
-// 0.98 - 1.24, 1.04 on average; by less 0.94 - 1.04).  150 at 16000 of 32/8 178.3 -> 172.0.
+// A dK/dV pass of its own, with its row statistics at hand and one and a half rounds of tiles or more: a tenth (330 of the calls: 0.88 -
+// 1.10, 0.96 on average).  150 at 16000 of 32/8 178.3 -> 172.0.
 inline bool joined_pays(const AttnParams& p, const SegTable& seg, bool apart_from_dq = false) {
   const int64_t rows = (int64_t)p.C * p.G, apart = (int64_t)(p.C + 63) / 64 * p.G, saved = apart - (rows + 63) / 64;
   // (a group's rows are addressed by 32-bit offsets)

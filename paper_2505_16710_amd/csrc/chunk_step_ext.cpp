@@ -5,7 +5,7 @@
 // through the framework (17 - 19 us of host time per call), a two-layer step over 4096 tokens in chunks of 512 took
 // 9.1 ms, of which the GPU worked 6.7; here a launch costs 2 - 4 us of host time, activations are carved from two
 // blocks allocated once per step, and the products are the library's own (gemm_bf16.hip) where type, alignment and size
-// allow: 3.8 ms, in which the GPU is busy throughout.
+// allow: 3.4 ms, in which the GPU is busy throughout.
 #include <map>
 #include <memory>
 
